@@ -96,8 +96,10 @@ int monarch_fwd_ex(const void* x, const void* R, const void* L, void* y,
  * runs the fused forward on the packed copies, which removes the weights from the LDS traffic of
  * the kernel.  fp32 layers with square blocks p = q = s of 32 or 64 (any k) run on the fp32 matrix cores, one
  * launch per block-diagonal factor with the vector between the factors kept in `workspace` (the packed flag
- * means nothing to them and is ignored).  Every other shape runs exactly as monarch_fwd_ex and ignores the
- * workspace.
+ * means nothing to them and is ignored).  Shapes that only the shape-generic kernels serve (p, q and s of 16 or more) run
+ * on the matrix cores too, with the vector between the factors in `workspace`; for them the workspace is optional, and
+ * without one (or with a short one) the call runs as monarch_fwd_ex.  Every other shape runs exactly as monarch_fwd_ex
+ * and ignores the workspace.
  * `workspace` (device memory, 256-byte aligned, caller-owned) must hold at least
  * monarch_fwd_workspace_bytes(...) bytes when that is non-zero.  Without MONARCH_FLAG_WS_PACKED its
  * contents on entry are ignored; on exit it holds the packed copies of R and L, and a later call with
@@ -138,8 +140,8 @@ int monarch_fwd_bias(const void* x, const void* R, const void* L, const void* bi
                      monarch_dtype dtype, void* stream,
                      void* workspace, size_t workspace_bytes, unsigned flags);
 
-/* Bytes of device scratch monarch_fwd_ws needs for this problem (0 when the shape has no
- * packed-weight kernel, and on invalid arguments). */
+/* Bytes of device scratch monarch_fwd_ws needs or can use for this problem (0 when the shape has no
+ * kernel that takes any, and on invalid arguments). */
 size_t monarch_fwd_workspace_bytes(int64_t batch, int n_in, int k, int q, int s,
                                    monarch_dtype dtype, unsigned flags);
 
@@ -153,9 +155,9 @@ size_t monarch_fwd_workspace_bytes(int64_t batch, int n_in, int k, int q, int s,
  *   dx[b][kk*p+i]= sum_j R[kk][j][i] * dY1[b][kk][j]
  * U is recomputed from x (no activation is saved by the forward call).  dx, dR
  * and dL are overwritten, never accumulated into.  The matrix-core kernels sum
- * per-chunk partial gradients in a fixed order (bit-reproducible); the
- * shape-generic fallback reduces dR/dL with fp32 atomics across workgroups, so
- * its results are reproducible only up to fp32 summation order.  `workspace` must hold at least
+ * per-chunk partial gradients in a fixed order (bit-reproducible); the SIMT
+ * fallback (blocks below 16, MONARCH_FLAG_GENERIC) reduces dR/dL with fp32 atomics across
+ * workgroups, so its results are reproducible only up to fp32 summation order.  `workspace` must hold at least
  * monarch_bwd_workspace_bytes(...) bytes (device memory, 256-byte aligned);
  * its contents on entry are ignored and on exit are unspecified. */
 int monarch_bwd(const void* dy, const void* x, const void* R, const void* L,
@@ -258,8 +260,8 @@ int monarch_fwd_t(const void* x, const void* R, const void* L, void* y,
                   monarch_dtype dtype, void* stream,
                   void* workspace, size_t workspace_bytes, unsigned flags);
 
-/* Bytes of device scratch monarch_fwd_t needs (0 for the shape-generic SIMT kernels and the fp32 m = 16
- * kernel, and on invalid arguments). */
+/* Bytes of device scratch monarch_fwd_t needs or can use (0 for the shape-generic SIMT kernels and the fp32 m = 16
+ * kernel, and on invalid arguments; optional for the shape-generic matrix-core kernels, as in monarch_fwd_ws). */
 size_t monarch_fwd_t_workspace_bytes(int64_t batch, int n_in, int k, int q, int s,
                                      monarch_dtype dtype, unsigned flags);
 

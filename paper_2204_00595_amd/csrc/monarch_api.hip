@@ -62,7 +62,8 @@ int make_problem(Problem& pb, int64_t batch, int n_in, int k, int q, int s, int 
     return MONARCH_OK;
 }
 
-enum Family { FAM_NONE = 0, FAM_GENERIC, FAM_MFMA };
+// FAM_GENERIC: the SIMT kernels; FAM_OPS: the shape-generic kernels on the matrix cores (blocks of 16 and more)
+enum Family { FAM_NONE = 0, FAM_GENERIC, FAM_OPS, FAM_MFMA };
 
 Family pick_fwd(const Problem& pb)
 {
@@ -74,14 +75,26 @@ Family pick_fwd(const Problem& pb)
 Family pick_bwd(const Problem& pb)
 {
     if (!(pb.flags & MONARCH_FLAG_GENERIC) && mfma_bwd_supported(pb)) return FAM_MFMA;
+    if (ops_supported(pb)) return FAM_OPS;
     if (generic_bwd_supported(pb)) return FAM_GENERIC;
     return FAM_NONE;
+}
+
+// Forward with a workspace on a shape no tuned forward serves: the matrix-core kernels, which keep the vector between
+// the factors in the workspace.  The workspace is optional there: without one (or with a short one) the SIMT kernels run.
+bool fwd_uses_ops(const Problem& pb)
+{
+    return !(pb.flags & MONARCH_FLAG_GENERIC) && !mfma_fwd_ws_supported(pb) && !mfma_fwd_supported(pb) && ops_supported(pb);
+}
+bool room_for(const void* workspace, size_t bytes, size_t need)
+{
+    return workspace && bytes >= need && (uintptr_t)workspace % 256 == 0;
 }
 
 // Backward scratch: the kernel family's own area, then the partial rows of the bias gradient.
 size_t bwd_kernel_need(const Problem& pb, Family fam)
 {
-    return align_up(fam == FAM_MFMA ? mfma_bwd_workspace(pb) : generic_bwd_workspace(pb), 256);
+    return align_up(fam == FAM_MFMA ? mfma_bwd_workspace(pb) : fam == FAM_OPS ? ops_bwd_workspace(pb) : generic_bwd_workspace(pb), 256);
 }
 size_t bwd_need(const Problem& pb, Family fam)
 {
@@ -148,6 +161,10 @@ int fwd_layer(const void* x, const void* R, const void* L, const void* bias, boo
         }
         rc = mfma_fwd_ws(pb, x, R, L, y, workspace, st);
         bias_done = bias_done || mfma_fwd_fuses_bias(pb, true);
+    } else if (fwd_uses_ops(pb) && (batch == 0 || room_for(workspace, workspace_bytes, ops_fwd_workspace(pb)))) {
+        if (batch == 0) return MONARCH_OK;
+        rc = ops_fwd(pb, x, R, L, y, workspace, st);
+        bias_done = true;
     } else {
         pb.flags &= ~MONARCH_FLAG_WS_PACKED;  // no packed-weight kernel: nothing to reuse
         const Family fam = pick_fwd(pb);
@@ -211,6 +228,9 @@ int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* save
         if (fused) pb.x_pre = x_pre;
         rc = mfma_bwd(pb, dy, x, R, L, dx, dR, dL, workspace, st);
         if (rc || fused || !x_pre) return rc;
+    } else if (fam == FAM_OPS) {
+        rc = ops_bwd(pb, dy, x, R, L, dx, dR, dL, workspace, st);
+        if (rc || !x_pre) return rc;
     } else {
         rc = generic_bwd(pb, dy, x, R, L, dx, dR, dL, workspace, st);
         if (rc || !x_pre) return rc;
@@ -249,8 +269,9 @@ size_t monarch_fwd_workspace_bytes(int64_t batch, int n_in, int k, int q, int s,
 {
     Problem pb;
     if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags)) return 0;
-    if ((flags & MONARCH_FLAG_GENERIC) || !mfma_fwd_ws_supported(pb)) return 0;
-    return mfma_fwd_ws_workspace(pb);
+    if (flags & MONARCH_FLAG_GENERIC) return 0;
+    if (mfma_fwd_ws_supported(pb)) return mfma_fwd_ws_workspace(pb);
+    return fwd_uses_ops(pb) ? ops_fwd_workspace(pb) : 0;
 }
 
 int monarch_fwd_ws(const void* x, const void* R, const void* L, void* y, int64_t batch, int n_in, int k,
@@ -260,11 +281,13 @@ int monarch_fwd_ws(const void* x, const void* R, const void* L, void* y, int64_t
     Problem pb;
     int rc = make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags);
     if (rc) return rc;
-    if ((flags & MONARCH_FLAG_GENERIC) || !mfma_fwd_ws_supported(pb))
+    const bool ops = fwd_uses_ops(pb) && room_for(workspace, workspace_bytes, ops_fwd_workspace(pb));
+    if ((flags & MONARCH_FLAG_GENERIC) || (!mfma_fwd_ws_supported(pb) && !ops))
         return monarch_fwd_ex(x, R, L, y, batch, n_in, k, q, s, dtype, stream, flags & ~MONARCH_FLAG_WS_PACKED);
     if (flags & MONARCH_FLAG_WGRAD_F32) return MONARCH_ERR_INVALID;  // backward-only flag
     if (!R || !L || ((!x || !y) && batch > 0)) return MONARCH_ERR_INVALID;
     if (!aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(y, 16)) return MONARCH_ERR_INVALID;
+    if (ops) return batch == 0 ? MONARCH_OK : ops_fwd(pb, x, R, L, y, workspace, (hipStream_t)stream);
     if (!workspace || workspace_bytes < mfma_fwd_ws_workspace(pb) || !aligned(workspace, 256))
         return MONARCH_ERR_WORKSPACE;
     if (batch == 0) return MONARCH_OK;
@@ -275,8 +298,12 @@ int monarch_fwd_static(const void* x, const void* R, const void* L, void* y, int
                        int q, int s, monarch_dtype dtype, void* stream, unsigned flags)
 {
     if (flags & MONARCH_FLAG_WS_PACKED) return MONARCH_ERR_INVALID;  // the shared array is nobody's to keep between calls
-    const size_t need = monarch_fwd_workspace_bytes(batch, n_in, k, q, s, dtype, flags);
-    if (need > kStaticWorkspaceBytes) return MONARCH_ERR_WORKSPACE;
+    size_t need = monarch_fwd_workspace_bytes(batch, n_in, k, q, s, dtype, flags);
+    if (need > kStaticWorkspaceBytes) {
+        Problem pb;
+        if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags) || !fwd_uses_ops(pb)) return MONARCH_ERR_WORKSPACE;
+        need = 0;  // the shape-generic kernels can do without
+    }
     void* ws = nullptr;
     if (need > 0) {
         const int rc = static_workspace(&ws);
@@ -305,7 +332,7 @@ size_t monarch_saved_bytes(int64_t batch, int n_in, int k, int q, int s, monarch
 {
     Problem pb;
     if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags)) return 0;
-    if ((flags & MONARCH_FLAG_GENERIC) || !saved_supported(pb)) return 0;
+    if ((flags & MONARCH_FLAG_GENERIC) || !(saved_supported(pb) || (fwd_uses_ops(pb) && pick_bwd(pb) == FAM_OPS))) return 0;
     return align_up((size_t)(batch > 0 ? batch : 1) * pb.kq() * pb.esize(), 256);
 }
 
@@ -322,6 +349,7 @@ int monarch_fwd_save(const void* x, const void* R, const void* L, void* y, void*
     if (!aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(y, 16)) return MONARCH_ERR_INVALID;
     if (!saved || saved_bytes < need || !aligned(saved, 16)) return MONARCH_ERR_WORKSPACE;
     if (batch == 0) return MONARCH_OK;
+    if (fwd_uses_ops(pb)) return ops_fwd(pb, x, R, L, y, saved, (hipStream_t)stream);
     pb.saved = saved;
     return mfma_fwd(pb, x, R, L, y, (hipStream_t)stream);
 }
@@ -373,8 +401,9 @@ size_t monarch_fwd_t_workspace_bytes(int64_t batch, int n_in, int k, int q, int 
 {
     Problem pb;
     if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags)) return 0;
-    if ((flags & MONARCH_FLAG_GENERIC) || !mfma_fwd_t_supported(pb)) return 0;
-    return mfma_fwd_t_workspace(pb);
+    if (flags & MONARCH_FLAG_GENERIC) return 0;
+    if (mfma_fwd_t_supported(pb)) return mfma_fwd_t_workspace(pb);
+    return ops_supported(pb) ? ops_fwd_t_workspace(pb) : 0;
 }
 
 int monarch_fwd_t(const void* x, const void* R, const void* L, void* y, int64_t batch, int n_in, int k, int q, int s,
@@ -393,6 +422,8 @@ int monarch_fwd_t(const void* x, const void* R, const void* L, void* y, int64_t 
         if (batch == 0) return MONARCH_OK;
         return mfma_fwd_t(pb, x, R, L, y, workspace, st);
     }
+    if (batch > 0 && ops_supported(pb) && room_for(workspace, workspace_bytes, ops_fwd_t_workspace(pb)))
+        return ops_fwd_t(pb, x, R, L, y, workspace, st);
     if (!generic_fwd_t_supported(pb)) return MONARCH_ERR_UNSUPPORTED;
     if (batch == 0) return MONARCH_OK;
     return generic_fwd_t(pb, x, R, L, y, st);
@@ -532,7 +563,7 @@ const char* monarch_kernel_name(int pass, int n_in, int k, int q, int s, monarch
     }
     const Family fam = pass != 1 ? pick_fwd(pb) : pick_bwd(pb);
     if (pass == 2) return (!(flags & MONARCH_FLAG_GENERIC) && mfma_fwd_ws_supported(pb)) ? mfma_fwd_ws_name(pb) : monarch_kernel_name(0, n_in, k, q, s, dtype, flags);
-    if (fam == FAM_GENERIC) return pass == 0 ? "generic_fwd" : "generic_bwd";
+    if (fam == FAM_GENERIC || fam == FAM_OPS) return pass != 1 ? "generic_fwd" : "generic_bwd";
     if (fam == FAM_MFMA) return pass == 0 ? mfma_fwd_name(pb) : mfma_bwd_name(pb);
     return "unsupported";
 }

@@ -50,6 +50,17 @@ int generic_fwd(const Problem& pb, const void* x, const void* R, const void* L, 
 int generic_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L,
                 void* dx, void* dR, void* dL, void* ws, hipStream_t st);
 
+// ---- shape-generic multiply on the matrix cores, one launch per contraction (monarch_ops.hip): blocks of 16 and more, both
+// dtypes and readings; `U` / the workspaces hold the vector between the factors ----
+bool ops_supported(const Problem& pb);
+size_t ops_fwd_workspace(const Problem& pb);
+int ops_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* U, hipStream_t st);
+size_t ops_fwd_t_workspace(const Problem& pb);
+int ops_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
+size_t ops_bwd_workspace(const Problem& pb);
+int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL,
+            void* ws, hipStream_t st);  // pb.saved (may be null): U as ops_fwd left it
+
 // dense form of the Monarch matrix, (k*s) x n_in row-major (any shape, both readings)
 int launch_to_dense(const Problem& pb, const void* R, const void* L, void* M, hipStream_t st);
 

@@ -1,0 +1,649 @@
+// Shape-generic multiply on the matrix cores, fp32 and bf16: any k, any block sizes from 16 up, both readings of the mid
+// permutation.  It serves the calls that bring a workspace on every shape without a kernel of its own (fp32 Transformer
+// layers, block sizes that are multiples of nothing); without a workspace, or below 16, the SIMT kernels of
+// monarch_generic.hip run.
+//
+// Every step of Section 3.3 and every adjoint of one is a batched contraction whose operands lie in memory with three
+// element strides each (block, row, contraction index), and the permutations are nothing but such strides:
+//   step 1         U[b][j*k + kk]  = sum_i x[b][kk*p + i] R[kk][j][i]       (default reading: U is the permuted vector)
+//   step 2, 3      y[b][l*k + c]   = sum_r U[b][c*q + r] L[c][l][r]
+//   backward       dU[b][c*q + r]  = sum_l dy[b][l*k + c] L[c][l][r]
+//                  dx[b][kk*p + i] = sum_j dU[b][j*k + kk] R[kk][j][i]
+//                  dL[c][l][r]     = sum_b dy[b][l*k + c] U[b][c*q + r],   dR likewise from dU and x
+// With MONARCH_FLAG_PERM_B the vector between the factors is kept in stage-1 order and the strides on either side of it
+// change places.  So there is one kernel, ops_gemm_kernel: O[g][m][n] = sum_k A[g][m][k] B[g][n][k].
+//
+// What bounds it: fp32 layers the fp32 matrix cores (v_mfma_f32_32x32x2_f32, 154 TFLOP/s in a large product; a 128 x 128
+// tile needs 16 B/clk of LDS reads per CU, far below the 128 there are), small and odd bf16 layers the memory system (every
+// operand element is staged once per tile, in 2-byte pieces where nothing better is aligned).  The intermediate goes
+// through memory (for most shapes it stays in the last-level cache): a fused kernel would hold all k blocks of a row tile,
+// which leaves the large shapes one 16-row tile per CU.
+// Measured against the SIMT kernels: 768 -> 768 fp32, k = 4, 12608 rows: forward 741 -> 96 us, backward 3570 -> 255 us (one
+// contraction of 3.7 GFLOP takes 46 to 57 us, its matrix-core floor is 24: the cores are busy 62 % of the time of a busy CU,
+// and 2.3 rounds of workgroups leave a quarter of the launch on partly filled CUs); 196 -> 256 bf16, blocks of 49 and 64,
+// 32768 rows: forward 61 -> 40 us, backward 388 -> 92 us; 4096 -> 1024 fp32, 16384 rows: 105 TFLOP/s in the data path,
+// 92 in the weight gradients.
+#include <type_traits>
+#include "monarch_internal.h"
+#include "monarch_device.h"
+#include "monarch_mfma_common.h"
+
+namespace monarch {
+namespace {
+
+constexpr int kThreads = 256;  // four waves
+
+typedef __attribute__((ext_vector_type(4))) short s16x4;
+
+template <typename T> struct OpType;
+template <> struct OpType<float> { static constexpr int KC = 32, KSTEP = 8; };   // contraction indices per chunk / per MFMA group
+template <> struct OpType<bf16_t> { static constexpr int KC = 32, KSTEP = 16; };
+
+// One operand: element (g, row, k) at p[g*g_s + row*r_s + k*k_s].
+struct OpOperand {
+    const void* p;
+    int64_t g_s, r_s, k_s;
+    bool vec;  // 16-byte pieces along the contiguous index are aligned
+};
+struct OpDesc {
+    OpOperand a, b;
+    void* o;           // output, or the partial tiles [split][g][m][n] (fp32)
+    int64_t o_g, o_m, o_n;  // element (g, m, n) goes to g*o_g + m*o_m + n*o_n ...
+    int o_mid;         // ... or, 1: to the stage-1 position of element g*N + n of the permuted vector (default reading)
+    const void* bias;  // added to o at the offset g*o_g + n*o_n (may be null)
+    int64_t M, K;
+    int N, G;
+    int tiles_m, tiles_n;
+    int nouter, deal;  // row tiles (or batch chunks); 1: they are dealt to the XCDs
+    int64_t k_chunk;   // contraction indices per batch chunk (K when the contraction is not split)
+    int blocks;        // workgroups
+};
+
+// Buffer accesses: the base is uniform, a lane adds a 32-bit offset, and a lane whose offset is kNowhere reads zero or
+// writes nothing.  So a ragged tile needs no branch around a load -- with branches the compiler cannot count the loads in
+// flight and waits for all of them at the first use, which undoes the prefetching.
+constexpr uint32_t kNowhere = 0xffffffffu, kBufferBytes = 0x7fffffffu;  // ops_supported keeps a tile's extent below 2 GiB
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, kBufferBytes, 0x00020000);
+}
+
+// A C x O tile of an operand (C: extent along the index with the unit or smallest stride, O: along the other one) on
+// its way from memory to LDS [o][c], row stride LSTR elements.  Elements past the limits read as zeros.
+// VEC: 16-byte pieces along c; else single elements at any stride (fp32: a dword per element; bf16: two 2-byte loads per
+// dword, joined on the way to LDS so that nothing waits for them here).
+template <typename T, int C, int O, int LSTR, bool VEC>
+struct OpTile {
+    static constexpr int EPD = 4 / (int)sizeof(T);                   // elements per dword
+    static constexpr int V = VEC ? 16 / (int)sizeof(T) : EPD;        // elements per piece
+    static constexpr int PPO = C / V;                                // pieces per o
+    static constexpr int kPieces = PPO * O;
+    static constexpr int NP = (kPieces + kThreads - 1) / kThreads;   // per thread
+    static constexpr int kLoads = VEC ? 1 : EPD, kDwords = VEC ? 4 : EPD;
+    static_assert(C % V == 0 && LSTR * sizeof(T) % 16 == 0, "tile");
+    static_assert(VEC || kPieces % kThreads == 0, "element-wise tiles divide over the threads");
+    uint32_t r[NP * kDwords];
+
+    __device__ __forceinline__ void fetch(const T* base, uint32_t os, uint32_t cs, int olim, int clim, int tid)
+    {
+        const auto rs = buffer_at(base);
+        const int o0 = tid / PPO, c0 = (tid % PPO) * V;
+        const uint32_t v0 = (o0 * os + c0 * cs) * (uint32_t)sizeof(T);
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            // where the pieces of a row divide the workgroup, a thread's pieces share c and step in o by a uniform amount
+            constexpr bool kEven = kThreads % PPO == 0;
+            const int idx = tid + n * kThreads;
+            const int o = kEven ? o0 + n * (kThreads / PPO) : idx / PPO, c = kEven ? c0 : (idx % PPO) * V;
+            const uint32_t vo = kEven ? v0 : (o * os + c * cs) * (uint32_t)sizeof(T);
+            const uint32_t so = kEven ? n * (kThreads / PPO) * os * (uint32_t)sizeof(T) : 0u;
+            bool in = o < olim;
+            if constexpr (kPieces % kThreads != 0) in = in && idx < kPieces;
+#pragma unroll
+            for (int e = 0; e < kLoads; ++e) {
+                const uint32_t at = in && c + e < clim ? vo : kNowhere;
+                if constexpr (VEC) {
+                    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, at, so, 0);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) r[4 * n + w] = v[w];
+                } else if constexpr (EPD == 1) {
+                    r[n] = __builtin_amdgcn_raw_buffer_load_b32(rs, at, so, 0);
+                } else {
+                    r[2 * n + e] = __builtin_amdgcn_raw_buffer_load_b16(rs, at, so + e * cs * (uint32_t)sizeof(T), 0);
+                }
+            }
+        }
+    }
+    __device__ __forceinline__ void store(T* lds, int tid) const
+    {
+#pragma unroll
+        for (int n = 0; n < NP; ++n) {
+            const int idx = tid + n * kThreads, o = idx / PPO, c = (idx % PPO) * V;
+            if constexpr (VEC) {
+                if (kPieces % kThreads == 0 || idx < kPieces)
+                    *reinterpret_cast<u32x4*>(lds + o * LSTR + c) = u32x4{r[4 * n], r[4 * n + 1], r[4 * n + 2], r[4 * n + 3]};
+            } else {
+                *reinterpret_cast<uint32_t*>(lds + o * LSTR + c) = EPD == 1 ? r[n] : (r[n * EPD] | (r[n * EPD + EPD - 1] << 16));
+            }
+        }
+    }
+};
+
+// LDS row strides: contraction-contiguous tiles [row][KC] + 16 bytes (eight lanes of a b128 read then start in eight
+// different bank groups); row-contiguous tiles [k][rows]: fp32 + 16 bytes, bf16 odd multiples of 64 bytes, so that the
+// four rows a half wave of the transposing read touches fall on disjoint bank quarters.
+template <typename T, bool RC, int ROWS>
+constexpr int op_lstr()
+{
+    if (!RC) return OpType<T>::KC + 16 / (int)sizeof(T);
+    if (sizeof(T) == 4) return ROWS + 4;
+    return ROWS % 64 == 32 ? ROWS : ROWS + 32;
+}
+
+__device__ __forceinline__ u32x2 op_lds_tr16(const bf16_t* p)
+{
+    s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16((s16x4 __attribute__((address_space(3)))*)(const_cast<bf16_t*>(p)));
+    return __builtin_bit_cast(u32x2, v);
+}
+
+// The MFMA operands of KSTEP contraction indices k0 .. k0 + KSTEP-1 for the 32 rows from r0: lane (row = lane % 32,
+// h = lane / 32) holds the indices k0 + (KSTEP/2)*h .. of its row (fp32: four values = four K = 2 steps).
+template <typename T, bool RC, int LSTR> struct OpFrag;
+template <bool RC, int LSTR>
+struct OpFrag<float, RC, LSTR> {
+    float v[4];
+    __device__ __forceinline__ void read(const float* lds, int r0, int k0, int lane)
+    {
+        const int row = r0 + (lane & 31), k = k0 + 4 * (lane >> 5);
+        if constexpr (!RC) {
+            const f32x4 t = *reinterpret_cast<const f32x4*>(lds + row * LSTR + k);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = t[e];
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = lds[(k + e) * LSTR + row];
+        }
+    }
+};
+template <bool RC, int LSTR>
+struct OpFrag<bf16_t, RC, LSTR> {
+    bf16x8 v;
+    __device__ __forceinline__ void read(const bf16_t* lds, int r0, int k0, int lane)
+    {
+        if constexpr (!RC) {
+            v = as_bf16x8(lds128(lds + (r0 + (lane & 31)) * LSTR + k0 + 8 * (lane >> 5)));
+        } else {
+            // transposing read: within 16 lanes, lane i gets element i % 4 of lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4
+            const int G = lane >> 4, j = lane & 15;
+            const bf16_t* p = lds + (k0 + 8 * (G >> 1) + (j >> 2)) * LSTR + r0 + 16 * (G & 1) + 4 * (j & 3);
+            const u32x2 lo = op_lds_tr16(p), hi = op_lds_tr16(p + 4 * LSTR);
+            v = as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]});
+        }
+    }
+};
+template <bool RA, int LA, bool RB, int LB>
+__device__ __forceinline__ f32x16 op_mma(const OpFrag<float, RA, LA>& a, const OpFrag<float, RB, LB>& b, f32x16 c)
+{
+#pragma unroll
+    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[e], b.v[e], c, 0, 0, 0);
+    return c;
+}
+template <bool RA, int LA, bool RB, int LB>
+__device__ __forceinline__ f32x16 op_mma(const OpFrag<bf16_t, RA, LA>& a, const OpFrag<bf16_t, RB, LB>& b, f32x16 c)
+{
+    return mfma32(a.v, b.v, c);
+}
+
+template <int WM_, int WN_, int MT_, int NT_>
+struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32
+    static constexpr int WM = WM_, WN = WN_, MT = MT_, NT = NT_;
+    static constexpr int TM = WM * MT * 32, TN = WN * NT * 32;
+};
+
+// RA / RB: the operand's row index (not the contraction) is the contiguous one.  PARTIAL: fp32 partial tiles of a split
+// contraction instead of the output.
+// Workgroup order: the row tile (PARTIAL: the batch chunk) is dealt to the XCDs, and the blocks and column tiles of one
+// row tile follow each other on that XCD: strided operands and outputs of the k blocks share their cache lines, which
+// then meet in one L2.
+template <typename T, class Cfg, bool RA, bool RB, bool PARTIAL, bool AV, bool BV>
+__global__ void __launch_bounds__(kThreads, 2)
+ops_gemm_kernel(const OpDesc d0, const OpDesc d1)
+{
+    constexpr int KC = OpType<T>::KC, KSTEP = OpType<T>::KSTEP, MT = Cfg::MT, NT = Cfg::NT, TM = Cfg::TM, TN = Cfg::TN;
+    constexpr int LA = op_lstr<T, RA, TM>(), LB = op_lstr<T, RB, TN>();
+    constexpr int SZA = RA ? KC * LA : TM * LA, SZB = RB ? KC * LB : TN * LB;
+    using TA = OpTile<T, RA ? TM : KC, RA ? KC : TM, LA, AV>;
+    using TB = OpTile<T, RB ? TN : KC, RB ? KC : TN, LB, BV>;
+    extern __shared__ __align__(16) unsigned char op_lds[];
+    T* const lds = reinterpret_cast<T*>(op_lds);
+
+    int bid = (int)blockIdx.x;
+    const bool second = bid >= d0.blocks;
+    const OpDesc& d = second ? d1 : d0;
+    if (second) bid -= d0.blocks;
+    const int inner = d.G * d.tiles_n * (PARTIAL ? d.tiles_m : 1);
+    const int seq = d.deal ? bid >> 3 : bid;
+    const int outer = d.deal ? (seq / inner) * 8 + (bid & 7) : seq / inner;
+    if (outer >= d.nouter) return;
+    int in = seq % inner;
+    const int g = in % d.G;
+    in /= d.G;
+    const int tn = in % d.tiles_n;
+    const int tm = PARTIAL ? in / d.tiles_n : outer;
+    const int64_t m0 = (int64_t)tm * TM;
+    const int n0 = tn * TN;
+    const int64_t k_lo = PARTIAL ? (int64_t)outer * d.k_chunk : 0;
+    const int64_t k_len = PARTIAL ? (d.K - k_lo < d.k_chunk ? d.K - k_lo : d.k_chunk) : d.K;
+    const int mlim = d.M - m0 < TM ? (int)(d.M - m0) : TM, nlim = d.N - n0 < TN ? d.N - n0 : TN;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave % Cfg::WM, wn = wave / Cfg::WM;
+    const T* pa = static_cast<const T*>(d.a.p) + g * d.a.g_s + m0 * d.a.r_s + k_lo * d.a.k_s;
+    const T* pb = static_cast<const T*>(d.b.p) + g * d.b.g_s + (int64_t)n0 * d.b.r_s + k_lo * d.b.k_s;
+    const uint32_t a_o = (uint32_t)(RA ? d.a.k_s : d.a.r_s), a_c = (uint32_t)(RA ? d.a.r_s : d.a.k_s);
+    const uint32_t b_o = (uint32_t)(RB ? d.b.k_s : d.b.r_s), b_c = (uint32_t)(RB ? d.b.r_s : d.b.k_s);
+
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+
+    // two chunks are on their way from memory while one is multiplied: with one, a chunk's time on the matrix cores
+    // (0.4 to 0.9 us) does not cover a load's
+    struct Stage {
+        TA a;
+        TB b;
+    };
+    Stage s0, s1;
+    auto fetch = [&](Stage& s, int64_t kk) {
+        const int64_t left = k_len - kk;
+        const int klim = left < KC ? (left > 0 ? (int)left : 0) : KC;
+        s.a.fetch(pa + kk * d.a.k_s, a_o, a_c, RA ? klim : mlim, RA ? mlim : klim, tid);
+        s.b.fetch(pb + kk * d.b.k_s, b_o, b_c, RB ? klim : nlim, RB ? nlim : klim, tid);
+        __builtin_amdgcn_sched_barrier(0);  // in this order: the wait for a chunk counts the loads behind it
+    };
+    auto put = [&](const Stage& s, int buf) {
+        s.a.store(lds + buf * (SZA + SZB), tid);
+        s.b.store(lds + buf * (SZA + SZB) + SZA, tid);
+    };
+    auto multiply = [&](int buf, int64_t kk) {
+        const T* la = lds + buf * (SZA + SZB);
+        const T* lb = la + SZA;
+        const int left = (int)(k_len - kk < KC ? k_len - kk : KC);
+#pragma unroll
+        for (int t = 0; t < KC / KSTEP; ++t) {
+            if (t * KSTEP < left) {
+                OpFrag<T, RA, LA> af[MT];
+                OpFrag<T, RB, LB> bf[NT];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) af[i].read(la, (wm * MT + i) * 32, t * KSTEP, lane);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) bf[j].read(lb, (wn * NT + j) * 32, t * KSTEP, lane);
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) acc[i][j] = op_mma(af[i], bf[j], acc[i][j]);
+            }
+        }
+    };
+    // chunk c is multiplied from LDS buffer c % 2; chunk c + 1 goes there from its registers at the end of step c, and
+    // chunk c + 3 is requested into the registers so freed
+    fetch(s0, 0);
+    fetch(s1, KC);
+    put(s0, 0);
+    fetch(s0, 2 * KC);
+    lds_barrier();
+    for (int64_t kk = 0; kk < k_len; kk += 2 * KC) {
+        multiply(0, kk);
+        if (kk + KC >= k_len) break;
+        put(s1, 1);
+        fetch(s1, kk + 3 * KC);
+        lds_barrier();
+        multiply(1, kk + KC);
+        if (kk + 2 * KC >= k_len) break;
+        put(s0, 0);
+        fetch(s0, kk + 4 * KC);
+        lds_barrier();
+    }
+
+    const int col = lane & 31, rh = 4 * (lane >> 5);
+    using OT = typename std::conditional<PARTIAL, float, T>::type;
+    OT* O = static_cast<OT*>(d.o);
+    uint32_t o_m = (uint32_t)d.o_m;
+    if constexpr (PARTIAL) {
+        O += (((int64_t)outer * d.G + g) * d.M + m0) * d.N;
+        o_m = (uint32_t)d.N;
+    } else {
+        O += m0 * d.o_m;
+    }
+    const auto out = buffer_at(O);
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int n = (wn * NT + j) * 32 + col;
+        uint32_t off = (uint32_t)(n0 + n);
+        float bv = 0.f;
+        if constexpr (!PARTIAL) {
+            off = (uint32_t)g * (uint32_t)d.o_g + off * (uint32_t)d.o_n;
+            if (d.o_mid) {
+                const uint32_t f = (uint32_t)(g * d.N + n0 + n), jj = f / (uint32_t)d.G;
+                off = (f - jj * (uint32_t)d.G) * (uint32_t)d.N + jj;
+            }
+            if (d.bias) {
+                const uint32_t at = n < nlim ? off * (uint32_t)sizeof(T) : kNowhere;
+                if constexpr (sizeof(T) == 4) bv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buffer_at(d.bias), at, 0, 0));
+                else bv = bf16_to_f32((bf16_t)__builtin_amdgcn_raw_buffer_load_b16(buffer_at(d.bias), at, 0, 0));
+            }
+        }
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int m = (wm * MT + i) * 32 + 8 * (r / 4) + rh + r % 4;
+                const uint32_t at = m < mlim && n < nlim ? (m * o_m + off) * (uint32_t)sizeof(OT) : kNowhere;
+                const float v = acc[i][j][r] + bv;
+                if constexpr (sizeof(OT) == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, at, 0, 0);
+                else __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v), out, at, 0, 0);
+            }
+    }
+}
+
+// out[e] = sum over the batch chunks, in order, of P[z][e], for both gradients.
+struct OpSum {
+    const float* P;
+    void* out;
+    int64_t n;
+    int nz;
+};
+template <typename OT>
+__global__ void __launch_bounds__(256) ops_sum_kernel(OpSum s0, OpSum s1, int64_t blocks0)
+{
+    const bool second = (int64_t)blockIdx.x >= blocks0;
+    const OpSum& s = second ? s1 : s0;
+    const int64_t i = ((int64_t)blockIdx.x - (second ? blocks0 : 0)) * 256 + threadIdx.x;
+    if (i >= s.n) return;
+    float v = 0.f;
+    int z = 0;
+    for (; z + 4 <= s.nz; z += 4) {
+        float t[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) t[e] = s.P[(z + e) * s.n + i];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v += t[e];
+    }
+    for (; z < s.nz; ++z) v += s.P[z * s.n + i];
+    Elem<OT>::store(static_cast<OT*>(s.out) + i, v);
+}
+
+// ---- host side ----
+
+// 16-byte pieces along the contiguous index need every other stride, the extent and the base to be multiples of a piece.
+bool pieces_aligned(const void* p, int64_t s1, int64_t s2, int64_t contiguous_stride, int64_t extent, int esize)
+{
+    const int v = 16 / esize;
+    return contiguous_stride == 1 && (uintptr_t)p % 16 == 0 && s1 % v == 0 && s2 % v == 0 && extent % v == 0;
+}
+
+template <typename T, class Cfg, bool RA, bool RB, bool PARTIAL, bool AV, bool BV>
+int launch_cfg(const OpDesc& d0, const OpDesc& d1, hipStream_t st)
+{
+    constexpr int KC = OpType<T>::KC;
+    constexpr int LA = op_lstr<T, RA, Cfg::TM>(), LB = op_lstr<T, RB, Cfg::TN>();
+    constexpr size_t lds = 2 * sizeof(T) * (size_t)((RA ? KC * LA : Cfg::TM * LA) + (RB ? KC * LB : Cfg::TN * LB));
+    auto kernel = ops_gemm_kernel<T, Cfg, RA, RB, PARTIAL, AV, BV>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds)) return hip_status(e);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(d0.blocks + d1.blocks)), dim3(kThreads), lds, st, d0, d1);
+    return hip_status(hipGetLastError());
+}
+
+using Cfg128x128 = OpCfg<2, 2, 2, 2>;
+using Cfg128x96 = OpCfg<4, 1, 1, 3>;
+using Cfg128x64 = OpCfg<2, 2, 2, 1>;
+using Cfg64x64 = OpCfg<2, 2, 1, 1>;
+struct TileSize {
+    int m, n;
+};
+constexpr int kTileSizes = 4;
+constexpr TileSize kTiles[kTileSizes] = {{128, 128}, {128, 96}, {128, 64}, {64, 64}};
+
+template <typename T, bool RA, bool RB, bool PARTIAL, bool AV, bool BV>
+int launch_tile(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
+{
+    if constexpr (AV && BV) {
+        if (cfg == 0) return launch_cfg<T, Cfg128x128, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
+        if (cfg == 1) return launch_cfg<T, Cfg128x96, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
+    }
+    switch (cfg) {
+        case 2: return launch_cfg<T, Cfg128x64, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
+        default: return launch_cfg<T, Cfg64x64, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
+    }
+}
+// The three kinds of contraction with the piece widths that occur: A in 16-byte pieces only together with B (a strided
+// A is the rule in the backward), anything that does not fit element by element.
+template <typename T>
+int launch_op(bool w_rc, int cfg, const OpDesc& d, hipStream_t st)
+{
+    const OpDesc none{};
+    const bool av = d.a.vec && d.b.vec;
+    if (!w_rc) {
+        return av ? launch_tile<T, false, false, false, true, true>(cfg, d, none, st)
+                  : launch_tile<T, false, false, false, false, false>(cfg, d, none, st);
+    }
+    return av      ? launch_tile<T, false, true, false, true, true>(cfg, d, none, st)
+         : d.b.vec ? launch_tile<T, false, true, false, false, true>(cfg, d, none, st)
+                   : launch_tile<T, false, true, false, false, false>(cfg, d, none, st);
+}
+template <typename T>
+int launch_wgrad(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
+{
+    const bool bv = d0.b.vec && d1.b.vec;
+    return bv ? launch_tile<T, true, true, true, false, true>(cfg, d0, d1, st)
+              : launch_tile<T, true, true, true, false, false>(cfg, d0, d1, st);
+}
+
+int64_t tiles(int64_t n, int t) { return (n + t - 1) / t; }
+
+// The tile that finishes first under a simple model: up to 256 workgroups run one per CU; beyond, rounds of two per CU
+// that share it.  A workgroup costs its (padded) tile plus a fixed share for filling and draining the pipeline.
+// Operands taken element by element need registers that the two largest tiles do not have.
+int pick_tile(int64_t M, int N, int G, bool pieces)
+{
+    int best = kTileSizes - 1;
+    double best_t = 1e30;
+    for (int c = pieces ? 0 : 2; c < kTileSizes; ++c) {
+        const double wgs = (double)tiles(M, kTiles[c].m) * tiles(N, kTiles[c].n) * G;
+        const double pairs = wgs / 512, rounds = wgs <= 256 ? 0.5 : pairs < 4 ? (double)((int64_t)(pairs + 0.999)) : pairs;
+        const double t = rounds * (kTiles[c].m * kTiles[c].n + 2048);
+        if (t < best_t) {
+            best_t = t;
+            best = c;
+        }
+    }
+    return best;
+}
+
+// Where the row tiles (batch chunks) do not come out even over the eight XCDs, whole ones per XCD would leave some of
+// them idle: the workgroups are then numbered straight through.
+void deal(OpDesc& d, int nouter, int inner)
+{
+    const int64_t even = tiles(nouter, 8) * 8;
+    d.nouter = nouter;
+    d.deal = 5 * even <= 6 * nouter;
+    d.blocks = (int)((d.deal ? even : nouter) * inner);
+}
+
+// element (g, row, k) of an operand; `rc`: its row index is the contiguous one
+OpOperand operand(const void* p, int64_t g_s, int64_t r_s, int64_t k_s, bool rc, int64_t rows, int64_t K, int esize)
+{
+    return OpOperand{p, g_s, r_s, k_s,
+                     rc ? pieces_aligned(p, g_s, k_s, r_s, rows, esize) : pieces_aligned(p, g_s, r_s, k_s, K, esize)};
+}
+
+// One step of the data path: O (rows x blocks x N) = A x W per block.
+int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t lda, int K, const void* w, bool w_rc, int N,
+            void* o, int64_t o_g, int64_t o_n, int64_t ldo, const void* bias, hipStream_t st, bool o_mid = false)
+{
+    const int e = (int)pb.esize();
+    OpDesc d{};
+    d.a = operand(a, a_g, lda, a_k, false, pb.B, K, e);
+    d.b = w_rc ? operand(w, (int64_t)K * N, 1, N, true, N, K, e) : operand(w, (int64_t)K * N, K, 1, false, N, K, e);
+    d.o = o;
+    d.o_g = o_g;
+    d.o_m = ldo;
+    d.o_n = o_n;
+    d.o_mid = o_mid ? 1 : 0;
+    d.bias = bias;
+    d.M = pb.B;
+    d.K = K;
+    d.N = N;
+    d.G = pb.k;
+    const int cfg = pick_tile(d.M, N, d.G, d.a.vec && d.b.vec);
+    d.tiles_m = (int)tiles(d.M, kTiles[cfg].m);
+    d.tiles_n = (int)tiles(N, kTiles[cfg].n);
+    d.k_chunk = K;
+    deal(d, d.tiles_m, d.tiles_n * d.G);
+    return pb.dtype == 0 ? launch_op<float>(w_rc, cfg, d, st) : launch_op<bf16_t>(w_rc, cfg, d, st);
+}
+
+// Batch chunks of the weight-gradient contractions: about four workgroups per CU over both (768 -> 768 fp32: 131 us with
+// two, 104 with four), at least four pipeline chunks of rows each, and whole sets of eight, since a chunk belongs to an XCD
+// (4096 -> 1024 fp32 with three chunks: three XCDs busy, 1088 us; with eight 465 us).
+struct WgradPlan {
+    int cfg;
+    int nz;
+    int64_t rows;  // per chunk
+};
+WgradPlan wgrad_plan(const Problem& pb)
+{
+    constexpr int KC = 32;
+    const int M[2] = {pb.s, pb.q}, N[2] = {pb.q, pb.p};
+    WgradPlan pl{};
+    double best = 1e30;
+    for (int c = 2; c < kTileSizes; ++c) {  // dy is taken element by element: the two smaller tiles; of them the smallest padded area, weighted by the larger tiles' better reuse
+        double area = 0;
+        for (int i = 0; i < 2; ++i) area += (double)tiles(M[i], kTiles[c].m) * tiles(N[i], kTiles[c].n) * (kTiles[c].m * kTiles[c].n + 2048);
+        if (area < best) {
+            best = area;
+            pl.cfg = c;
+        }
+    }
+    int64_t t = 0;
+    for (int i = 0; i < 2; ++i) t += tiles(M[i], kTiles[pl.cfg].m) * tiles(N[i], kTiles[pl.cfg].n) * pb.k;
+    const int64_t rows = pb.B > 0 ? pb.B : 1, most = tiles(rows, 4 * KC);
+    int64_t nz = tiles(1024, (int)t);
+    if (nz > 1) nz = tiles(nz, 8) * 8;  // whole sets of the eight XCDs
+    nz = nz > most ? most : nz;
+    pl.rows = tiles(tiles(rows, (int)nz), KC) * KC;
+    pl.nz = (int)tiles(rows, (int)pl.rows);
+    return pl;
+}
+
+size_t mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B > 0 ? pb.B : 1) * pb.kq() * pb.esize(), 256); }
+
+// element strides of the vector between the factors: kept permuted (default reading) or in stage-1 order (PERM_B)
+struct Mid {
+    int64_t s1_g, s1_n;  // seen from stage 1: (kk, j)
+    int64_t s2_g, s2_n;  // seen from stage 2: (c, r)
+};
+Mid mid(const Problem& pb)
+{
+    if (!pb.perm_b()) return Mid{1, pb.k, pb.q, 1};
+    return Mid{pb.q, 1, 1, pb.k};
+}
+
+int stage1(const Problem& pb, const void* x, const void* R, void* U, hipStream_t st)
+{
+    const Mid m = mid(pb);
+    return data_op(pb, x, pb.p, 1, pb.n_in, pb.p, R, false, pb.q, U, m.s1_g, m.s1_n, pb.kq(), nullptr, st);
+}
+
+}  // namespace
+
+// Blocks below 16 would leave most of every 32 x 32 tile empty; the index arithmetic of a tile is 32-bit.
+bool ops_supported(const Problem& pb)
+{
+    if (pb.flags & 4u) return false;  // MONARCH_FLAG_GENERIC: the SIMT kernels
+    if (pb.p < 16 || pb.q < 16 || pb.s < 16) return false;
+    if (pb.n_in > (1 << 20) || pb.kq() > (1 << 20) || pb.n_out() > (1 << 20)) return false;  // 32-bit offsets inside a tile
+    const int64_t rows = pb.B > 0 ? pb.B : 1;
+    const int widest = pb.p > pb.q ? (pb.p > pb.s ? pb.p : pb.s) : (pb.q > pb.s ? pb.q : pb.s);
+    return (tiles(rows, 64) + 8) * tiles(widest, 32) * pb.k < (1LL << 30);
+}
+
+size_t ops_fwd_workspace(const Problem& pb) { return mid_bytes(pb); }
+
+// U: the vector between the factors (mid_bytes), left there for ops_bwd
+int ops_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* U, hipStream_t st)
+{
+    if (int rc = stage1(pb, x, R, U, st)) return rc;
+    const Mid m = mid(pb);
+    return data_op(pb, U, m.s2_g, m.s2_n, pb.kq(), pb.q, L, false, pb.s, y, 1, pb.k, pb.n_out(), pb.bias, st);
+}
+
+size_t ops_fwd_t_workspace(const Problem& pb) { return mid_bytes(pb); }
+
+// y = x M: the dx path on its own
+int ops_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* dU, hipStream_t st)
+{
+    // the vector between the factors in stage-1 order: written in short pieces once, read in long ones twice (dx, dR)
+    if (int rc = data_op(pb, x, 1, pb.k, pb.n_out(), pb.s, L, true, pb.q, dU, 1, pb.k, pb.kq(), nullptr, st, !pb.perm_b())) return rc;
+    return data_op(pb, dU, pb.q, 1, pb.kq(), pb.q, R, true, pb.p, y, pb.p, 1, pb.n_in, nullptr, st);
+}
+
+size_t ops_bwd_workspace(const Problem& pb)
+{
+    const WgradPlan pl = wgrad_plan(pb);
+    return 2 * mid_bytes(pb) + align_up((size_t)pl.nz * (pb.n_R() + pb.n_L()) * 4, 256);
+}
+
+int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL,
+            void* ws, hipStream_t st)
+{
+    if (pb.B == 0) {
+        const bool f = pb.wgrad_f32();
+        int rc = f ? launch_fill_zero_f32((float*)dR, pb.n_R(), st) : launch_fill_zero_u16((uint16_t*)dR, pb.n_R(), st);
+        if (rc) return rc;
+        return f ? launch_fill_zero_f32((float*)dL, pb.n_L(), st) : launch_fill_zero_u16((uint16_t*)dL, pb.n_L(), st);
+    }
+    char* w = static_cast<char*>(ws);
+    const void* U = pb.saved;
+    if (!U) {
+        if (int rc = stage1(pb, x, R, w, st)) return rc;
+        U = w;
+    }
+    void* dU = w + mid_bytes(pb);
+    if (int rc = ops_fwd_t(pb, dy, R, L, dx, dU, st)) return rc;
+
+    const Mid m = mid(pb);
+    const WgradPlan pl = wgrad_plan(pb);
+    const int e = (int)pb.esize();
+    float* P = reinterpret_cast<float*>(w + 2 * mid_bytes(pb));
+    OpDesc d[2] = {};
+    d[0].a = operand(dy, 1, pb.k, pb.n_out(), true, pb.s, pb.B, e);
+    d[0].b = operand(U, m.s2_g, m.s2_n, pb.kq(), true, pb.q, pb.B, e);
+    d[1].a = operand(dU, pb.q, 1, pb.kq(), true, pb.q, pb.B, e);
+    d[1].b = operand(x, pb.p, 1, pb.n_in, true, pb.p, pb.B, e);
+    const int M[2] = {pb.s, pb.q}, N[2] = {pb.q, pb.p};
+    for (int i = 0; i < 2; ++i) {
+        d[i].o = i ? P + (size_t)pl.nz * pb.n_L() : P;
+        d[i].M = M[i];
+        d[i].N = N[i];
+        d[i].K = pb.B;
+        d[i].G = pb.k;
+        d[i].tiles_m = (int)tiles(M[i], kTiles[pl.cfg].m);
+        d[i].tiles_n = (int)tiles(N[i], kTiles[pl.cfg].n);
+        d[i].k_chunk = pl.rows;
+        deal(d[i], pl.nz, d[i].tiles_m * d[i].tiles_n * pb.k);
+    }
+    const int rc = pb.dtype == 0 ? launch_wgrad<float>(pl.cfg, d[0], d[1], st) : launch_wgrad<bf16_t>(pl.cfg, d[0], d[1], st);
+    if (rc) return rc;
+    const OpSum s0{P, dL, (int64_t)pb.n_L(), pl.nz}, s1{P + (size_t)pl.nz * pb.n_L(), dR, (int64_t)pb.n_R(), pl.nz};
+    const int64_t b0 = tiles(s0.n, 256), b1 = tiles(s1.n, 256);
+    if (pb.wgrad_f32()) hipLaunchKernelGGL(ops_sum_kernel<float>, dim3((unsigned)(b0 + b1)), dim3(256), 0, st, s0, s1, b0);
+    else hipLaunchKernelGGL(ops_sum_kernel<bf16_t>, dim3((unsigned)(b0 + b1)), dim3(256), 0, st, s0, s1, b0);
+    return hip_status(hipGetLastError());
+}
+
+}  // namespace monarch

@@ -1,0 +1,53 @@
+"""The shape-generic matrix-core kernels (one launch per contraction) at the sizes where they can go wrong: block sizes
+around the 32-wide tiles and the 32-deep chunks, aligned and unaligned pieces, row counts around the tiles and around
+the number at which row tiles and batch chunks are dealt to the XCDs; with and without a workspace."""
+import numpy as np
+import pytest
+
+import oracle
+import parity_util
+from paper_2204_00595_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+TOL = {"f32": 1e-5, "bf16": 2e-2}
+# B, k, p, q, s
+CASES = [(1, 4, 16, 16, 16), (65, 2, 17, 16, 250), (300, 4, 49, 49, 64), (129, 3, 33, 31, 97), (1100, 1, 64, 95, 128),
+         (3000, 4, 96, 64, 160), (640, 8, 101, 37, 16), (900, 4, 192, 192, 36)]
+
+
+def _dev(a, dtype):
+    return torch.from_numpy(np.ascontiguousarray(a)).to("cuda").to(torch.float32 if dtype == "f32" else torch.bfloat16)
+
+
+@pytest.mark.parametrize("reading", [0, 1], ids=["reading_a", "reading_b"])
+@pytest.mark.parametrize("dtype", ["f32", "bf16"])
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_every_call_on_the_shape_generic_kernels(case, dtype, reading):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    sh = synth.Shape("ops_%s" % (case,), dtype, *case, config=400 + parity_util.stable_seed(str(case)))
+    flags = B.MONARCH_FLAG_PERM_B if reading else 0
+    rd = oracle.READING_B if reading else oracle.READING_A
+    x, R, L, dy = synth.make_inputs(sh)
+    bias = synth.quantize(synth.normal(77, (sh.n_out,)), dtype)
+    xd, Rd, Ld, dyd, bd = (_dev(a, dtype) for a in (x, R, L, dy, bias))
+    want_y, want_g = oracle.fwd(x, R, L, rd), oracle.bwd_bias(dy, x, R, L, rd)
+
+    def check(name, got, want):
+        parity_util.check("%s.%s" % (sh.name, name), got.float().cpu().numpy(), want, TOL[dtype])
+
+    check("y_ws", B.monarch_fwd_ws(xd, Rd, Ld, flags=flags), want_y)
+    check("y", B.monarch_fwd(xd, Rd, Ld, flags=flags), want_y)   # no workspace: the kernels that need none
+    check("y_bias", B.monarch_fwd_bias(xd, Rd, Ld, bd, flags=flags), oracle.fwd_bias(x, R, L, bias, rd))
+    check("xM", B.monarch_fwd_t(dyd, Rd, Ld, flags=flags), oracle.fwd_t(dy, R, L, rd))
+    y, saved = B.monarch_fwd_save(xd, Rd, Ld, flags=flags)
+    check("y_save", y, want_y)
+    plain = B.monarch_bwd_bias(dyd, xd, Rd, Ld, flags=flags)
+    again = B.monarch_bwd_saved(dyd, xd, saved, Rd, Ld, flags=flags, want_dbias=True)
+    for name, a, b, w in zip(("dx", "dR", "dL", "dbias"), plain, again, want_g):
+        check(name, a, w)
+        check(name + "_saved", b, w)
+        assert torch.equal(a, b) or saved is None, name   # fixed summation order
