@@ -3,8 +3,8 @@
 ``monarch_linear(x, R, L, bias)`` is differentiable: its forward is ``monarch_fwd_bias`` (or, without a
 bias and with ``save_intermediate=True``, ``monarch_fwd_save``), its backward ``monarch_bwd_bias`` /
 ``monarch_bwd_saved``.  ``MonarchLinear`` holds the two factors (and the bias) as parameters.  Leading
-dimensions of ``x`` are flattened into the batch.  Everything runs in the HIP kernels; there is no
-fallback for CPU tensors.
+dimensions of ``x`` are flattened into the batch.  The autograd node is native (``csrc/monarch_torch.cpp``).
+Everything runs in the HIP kernels; there is no fallback for CPU tensors.
 """
 from __future__ import annotations
 
@@ -15,42 +15,10 @@ import torch
 from . import binding
 
 
-class _MonarchLinearFn(torch.autograd.Function):
-    @staticmethod
-    def forward(ctx, x, R, L, bias, save_intermediate):
-        k, q, p = R.shape
-        x2 = x.reshape(-1, k * p)
-        if not x2.is_contiguous():
-            x2 = x2.contiguous()
-        saved = None
-        if bias is None and save_intermediate:
-            y, saved = binding.monarch_fwd_save(x2, R, L)
-        elif bias is None:
-            y = binding.monarch_fwd(x2, R, L)
-        else:
-            y = binding.monarch_fwd_bias(x2, R, L, bias)
-        ctx.save_for_backward(x2, R, L, saved if saved is not None else x2.new_empty(0))
-        ctx.has_saved = saved is not None
-        ctx.has_bias = bias is not None
-        ctx.x_shape = x.shape
-        return y.reshape(*x.shape[:-1], y.shape[-1])
-
-    @staticmethod
-    def backward(ctx, dy):
-        x2, R, L, saved = ctx.saved_tensors
-        k, s, q = L.shape
-        dy2 = dy.reshape(-1, k * s)
-        if not dy2.is_contiguous():
-            dy2 = dy2.contiguous()
-        dx, dR, dL, dbias = binding.monarch_bwd_saved(dy2, x2, saved if ctx.has_saved else None, R, L,
-                                                      want_dbias=ctx.has_bias)
-        return dx.reshape(ctx.x_shape), dR, dL, dbias, None
-
-
 def monarch_linear(x: torch.Tensor, R: torch.Tensor, L: torch.Tensor, bias: torch.Tensor | None = None,
                    save_intermediate: bool = True) -> torch.Tensor:
     """y = x M^T (+ bias) with M = P L P^T R; differentiable in x, R, L and bias."""
-    return _MonarchLinearFn.apply(x, R, L, bias, save_intermediate)
+    return binding._native_calls.linear(x, R, L, bias, save_intermediate)
 
 
 class MonarchLinear(torch.nn.Module):

@@ -1,13 +1,16 @@
-"""Builds libmonarch.so (HIP, gfx950) in-tree with hipcc.  No torch involved."""
+"""Builds libmonarch.so (HIP, gfx950; no torch involved) in-tree with hipcc, then the binding's native module _native.so
+(host code over torch's C++ API) with the C++ compiler."""
 from __future__ import annotations
 
 import os
 import subprocess
 import sys
+import sysconfig
 
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmonarch.so")
+NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["monarch_api.hip", "monarch_generic.hip", "monarch_mfma.hip", "monarch_mfma_fwd_wide.hip", "monarch_mfma_fwd_frag.hip", "monarch_mfma_tiled.hip", "monarch_project.hip", "monarch_complex.hip", "monarch_stage_mfma.hip", "monarch_act.hip", "monarch_ops.hip",
            "monarch_mfma_bwd_wide.hip", "monarch_mfma_y1.hip", "monarch_mfma_wgrad.hip", "monarch_mfma_sq64.hip", "monarch_mfma_sq16.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -19,12 +22,35 @@ FLAGS = [
 ]
 
 
+def _torch_dir() -> str:
+    import torch
+    return os.path.dirname(torch.__file__)
+
+
+def compile_native(obj: str) -> subprocess.Popen:
+    inc = os.path.join(_torch_dir(), "include")
+    cmd = [os.environ.get("CXX", "g++"), "-O2", "-std=c++17", "-fPIC", "-D__HIP_PLATFORM_AMD__=1", "-DUSE_ROCM=1",
+           "-I" + inc, "-I" + os.path.join(inc, "torch", "csrc", "api", "include"), "-I" + sysconfig.get_paths()["include"],
+           "-I/opt/rocm/include", "-c", os.path.join(CSRC, "monarch_torch.cpp"), "-o", obj]
+    return subprocess.Popen(cmd, stdout=subprocess.PIPE, stderr=subprocess.STDOUT)
+
+
+def link_native(obj: str) -> None:
+    tmp = NATIVE + ".tmp%d" % os.getpid()
+    subprocess.check_call([os.environ.get("CXX", "g++"), "-shared", "-o", tmp, obj, "-L" + os.path.join(_torch_dir(), "lib"),
+                           "-lc10", "-lc10_hip", "-ltorch_cpu", "-ltorch_python", "-L" + HERE, "-l:libmonarch.so",
+                           "-Wl,-rpath,$ORIGIN"])
+    os.replace(tmp, NATIVE)
+
+
 def build(verbose: bool = False, jobs: int = 4) -> str:
     """Compile every source to an object (in parallel) and link libmonarch.so."""
     objdir = os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
     procs = []
     objs = []
+    native_obj = os.path.join(objdir, "monarch_torch.o")
+    native = compile_native(native_obj)
     for src in SOURCES:
         obj = os.path.join(objdir, src.replace(".hip", ".o"))
         objs.append(obj)
@@ -51,6 +77,11 @@ def build(verbose: bool = False, jobs: int = 4) -> str:
     tmp = LIB + ".tmp%d" % os.getpid()
     subprocess.check_call([HIPCC, "-shared", "-fPIC", "--offload-arch=gfx950", "-o", tmp] + objs)
     os.replace(tmp, LIB)
+    said = native.communicate()[0].decode()
+    if native.returncode != 0:
+        sys.stderr.write(said)
+        raise RuntimeError("the native module did not compile")
+    link_native(native_obj)
     return LIB
 
 
