@@ -1,88 +1,165 @@
 // Projection of a dense n x n matrix, n = m^2, onto the square Monarch matrices (Section 3.3,
-// Theorem 1, Algorithm 1): with At[l][j][k][i] = A[l*m + j][k*m + i], the slice At[:, j, k, :] of the
+// Theorem 1, Algorithm 1): with At[l][j][k][i] = A[l*m + j][k*m + i], the slice G = At[:, j, k, :] of the
 // closest Monarch matrix is the best rank-1 approximation sigma_1 u_1 v_1^T of that slice of A, and
 // L[j][:][k] = sqrt(sigma_1) u_1,  R[k][j][:] = sqrt(sigma_1) v_1.
 //
-// The leading singular triple comes from a one-sided (Hestenes) Jacobi SVD, one wavefront per slice:
-// lane c owns column c of the slice G (m values in registers) and column c of the accumulated
-// rotations V (starts as the identity).  A sweep visits every pair of columns once, m/2 disjoint pairs
-// at a time in round-robin tournament order; a pair (p, q) is rotated so that its two columns of G
-// become orthogonal, and the same rotation is applied to V, so that G = (slice) * V throughout.  At
-// convergence the columns of G are sigma_c u_c and the columns of V are v_c.  Partner columns are read
-// with cross-lane shuffles; both lanes of a pair compute the rotation from the same three numbers
-// (their squared norms and their inner product, summed in the same order), so they agree bit for bit.
-// The sweep loop is bounded (kMaxSweeps), so every wave ends whatever the data.
+// Only the leading triple is needed: v_1 is the leading eigenvector of S = G^T G, and u_1 = G v_1 / sigma_1.  (Forming S costs
+// the leading pair no accuracy: the relative gap of sigma^2 is twice that of sigma.)  One wavefront per slice squares S
+// (scaled to trace 1) until it is of rank one: after t squarings the second eigenvalue has shrunk to (sigma_2/sigma_1)^(2^(t+1)),
+// so a gap of 1e-6 is resolved in about twenty squarings, and rounding in a later squaring meets a wider gap than in the first.
+//
+// A squaring of a symmetric matrix on the fp32 matrix cores needs next to no data movement: lane (c, h) of a 16 x 16
+// accumulator tile holds S[4h + r][c] = S[c][4h + r], which is what the same lane has to bring as either operand of
+// contraction step r.  Tiles below the diagonal are transposes of those above, by way of LDS.
+//
+// What bounds it: the matrix cores, 32 clocks for each of the NT^2 (NT + 1) / 2 * 4 steps of a squaring (m = 32: 768 clocks, one
+// wave per SIMD; m = 64: 5120, four).  The one-sided Jacobi SVD that was here before (all m triples, three cross-lane
+// shuffles per element and rotation) took 784 us for m = 32 and 5.8 ms for m = 64, and was less accurate (products
+// 2e-5 off at m = 64, here 5e-7).
 #include "monarch_internal.h"
 #include "monarch_device.h"
+#include "monarch_mfma_common.h"
 
 namespace monarch {
 namespace {
 
-constexpr int kMaxSweeps = 40;
-constexpr float kOrthTol = 3e-7f;  // a pair counts as orthogonal when |<p, q>| <= kOrthTol * |p| |q|
+constexpr int kMaxSquarings = 32;     // relative gaps down to 1e-8, below fp32
+constexpr float kRankOne = 1e-4f;     // 1 - |S|_F^2 at trace 1, about twice the second eigenvalue; one squaring more follows
+constexpr int kWavesPerBlock = 4;     // slices of neighbouring k: their rows of A lie next to each other
 
-template <typename T, int MT>
-__global__ void __launch_bounds__(64) project_kernel(const T* __restrict__ A, T* __restrict__ R, T* __restrict__ L, int m)
+__device__ __forceinline__ float wave_sum(float v)
 {
-    const int j = blockIdx.x / m, k = blockIdx.x - j * m;
-    const int c = threadIdx.x;
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
+    return v;
+}
+
+// NT x NT tiles of 16 x 16
+template <typename T, int NT>
+__global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* __restrict__ A, T* __restrict__ R, T* __restrict__ L, int m)
+{
+    constexpr int H = 4, TS = 16, NA = 4;             // lanes per column of a tile, its side, values per lane
+    constexpr int GT = TS * NT / H;                   // steps of H rows of G
+    constexpr int GP = NT == 3 ? 16 : GT;             // ... rounded up to a power of two
+    constexpr int kStride = TS + 4, kUpper = NT * (NT - 1) / 2;
+    __shared__ __align__(16) float shared[kWavesPerBlock][kUpper > 0 ? kUpper * TS * kStride : H * GP];
+    const int slice = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
+    if (slice >= m * m) return;  // no barriers below
+    float* const lds = shared[threadIdx.x >> 6];
+    const int j = slice / m, k = slice - j * m;
+    const int lane = threadIdx.x & 63, c = lane & 15, h = lane >> 4;
     const size_t n = (size_t)m * m;
-    float g[MT], v[MT];
+
+    // g[a][t] = G[H*t + h][TS*a + c]
+    float g[NT][GT];
+    float big = 0.f;
 #pragma unroll
-    for (int r = 0; r < MT; ++r) {
-        g[r] = (r < m && c < m) ? Elem<T>::load(A + ((size_t)r * m + j) * n + (size_t)k * m + c) : 0.f;
-        v[r] = (r == c && c < m) ? 1.f : 0.f;
-    }
-    const int me = (m + 1) & ~1;  // players of the tournament: the columns, plus a zero column when m is odd
-    for (int sweep = 0; sweep < kMaxSweeps; ++sweep) {
-        float worst = 0.f;  // largest |<p, q>| / (|p| |q|) met in this sweep
-        for (int t = 0; t < me - 1; ++t) {
-            int partner = c;
-            if (c < me) {
-                if (c == me - 1) partner = t;
-                else if (c == t) partner = me - 1;
-                else {
-                    partner = (2 * t - c) % (me - 1);
-                    if (partner < 0) partner += me - 1;
-                }
-            }
-            float alpha = 0.f, gamma = 0.f;
+    for (int t = 0; t < GT; ++t)
 #pragma unroll
-            for (int r = 0; r < MT; ++r) {
-                const float o = __shfl(g[r], partner);
-                alpha = fmaf(g[r], g[r], alpha);
-                gamma = fmaf(g[r], o, gamma);
-            }
-            const float beta = __shfl(alpha, partner);
-            const bool first = c < partner;
-            const float ap = first ? alpha : beta, aq = first ? beta : alpha;
-            const float denom = sqrtf(ap) * sqrtf(aq);
-            float cs = 1.f, sn = 0.f;
-            if (partner != c && fabsf(gamma) > kOrthTol * denom) {
-                const float zeta = (aq - ap) / (2.f * gamma);
-                const float tt = copysignf(1.f, zeta) / (fabsf(zeta) + sqrtf(1.f + zeta * zeta));
-                cs = 1.f / sqrtf(1.f + tt * tt);
-                sn = cs * tt;
-                worst = fmaxf(worst, fabsf(gamma) / denom);
-            }
-            // p' = cs p - sn q,  q' = sn p + cs q
-            const float mine = cs, theirs = first ? -sn : sn;
-#pragma unroll
-            for (int r = 0; r < MT; ++r) {
-                const float og = __shfl(g[r], partner), ov = __shfl(v[r], partner);
-                g[r] = fmaf(theirs, og, mine * g[r]);
-                v[r] = fmaf(theirs, ov, mine * v[r]);
-            }
+        for (int a = 0; a < NT; ++a) {
+            const int l = H * t + h, i = TS * a + c;
+            g[a][t] = (l < m && i < m) ? Elem<T>::load(A + ((size_t)l * m + j) * n + (size_t)k * m + i) : 0.f;
         }
 #pragma unroll
-        for (int d = 32; d >= 1; d >>= 1) worst = fmaxf(worst, __shfl_xor(worst, d));
-        if (worst == 0.f) break;  // no pair was rotated: every pair is orthogonal to tolerance
-    }
-    // the column with the largest norm is sigma_1 u_1 (ties: the lowest column index)
-    float best = 0.f;
+    for (int t = 0; t < GT; ++t)
 #pragma unroll
-    for (int r = 0; r < MT; ++r) best = fmaf(g[r], g[r], best);
-    int who = c;
+        for (int a = 0; a < NT; ++a) big = fmaxf(big, fabsf(g[a][t]));
+#pragma unroll
+    for (int d = 32; d >= 1; d >>= 1) big = fmaxf(big, __shfl_xor(big, d));
+    // a power of two brings the largest entry near one: the squares neither overflow nor vanish
+    int ex = 0;
+    if (big > 0.f) (void)frexpf(big, &ex);
+    float trace = 0.f;  // of S
+#pragma unroll
+    for (int t = 0; t < GT; ++t)
+#pragma unroll
+        for (int a = 0; a < NT; ++a) {
+            g[a][t] = ldexpf(g[a][t], -ex);
+            trace = fmaf(g[a][t], g[a][t], trace);
+        }
+    trace = wave_sum(trace);
+
+    f32x4 S[NT][NT];  // S[a][b]: rows of tile a, columns of tile b
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int b = 0; b < NT; ++b)
+#pragma unroll
+            for (int r = 0; r < NA; ++r) S[a][b][r] = 0.f;
+#pragma unroll
+    for (int t = 0; t < GT; ++t)
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = 0; b < NT; ++b) S[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[a][t], g[b][t], S[a][b], 0, 0, 0);
+
+    // S = S^2
+    auto square = [&]() {
+        f32x4 Q[NT][NT];
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = a; b < NT; ++b)
+#pragma unroll
+                for (int r = 0; r < NA; ++r) Q[a][b][r] = 0.f;
+#pragma unroll
+        for (int e = 0; e < NT; ++e)
+#pragma unroll
+            for (int r = 0; r < NA; ++r)
+#pragma unroll
+                for (int a = 0; a < NT; ++a)
+#pragma unroll
+                    for (int b = a; b < NT; ++b) Q[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(S[e][a][r], S[e][b][r], Q[a][b], 0, 0, 0);
+        int at = 0;
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = a + 1; b < NT; ++b, at += TS * kStride)
+#pragma unroll
+                for (int r = 0; r < NA; ++r) lds[at + (4 * h + r) * kStride + c] = Q[a][b][r];
+        __builtin_amdgcn_wave_barrier();
+        at = 0;
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = a + 1; b < NT; ++b, at += TS * kStride)
+                Q[b][a] = *reinterpret_cast<const f32x4*>(lds + at + c * kStride + 4 * h);
+        __builtin_amdgcn_wave_barrier();
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = 0; b < NT; ++b) S[a][b] = Q[a][b];
+    };
+    for (int it = 0; it < kMaxSquarings; ++it) {
+        const float inv = trace > 0.f ? 1.f / trace : 0.f;
+        float norm2 = 0.f;  // |S|_F^2 at trace 1: the trace of the square, and 1 exactly when S is of rank one
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+#pragma unroll
+                for (int r = 0; r < NA; ++r) {
+                    S[a][b][r] *= inv;
+                    norm2 = fmaf(S[a][b][r], S[a][b][r], norm2);
+                }
+        trace = wave_sum(norm2);
+        square();
+        if (!(1.f - trace > kRankOne)) break;  // NaN ends it too
+    }
+
+    // v_1 is every column of S up to scale: the row with the largest diagonal entry
+    float best = -1.f;
+    int who = 0;
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+#pragma unroll
+        for (int r = 0; r < NA; ++r) {
+            const int row = 4 * h + r;
+            if (row == c && S[a][a][r] > best) {
+                best = S[a][a][r];
+                who = TS * a + c;
+            }
+        }
 #pragma unroll
     for (int d = 32; d >= 1; d >>= 1) {
         const float ob = __shfl_xor(best, d);
@@ -92,30 +169,99 @@ __global__ void __launch_bounds__(64) project_kernel(const T* __restrict__ A, T*
             who = ow;
         }
     }
-    const float sigma = sqrtf(best), root = sqrtf(sigma);
-    float ul = 0.f, vl = 0.f;  // lane l keeps element l of the winning columns
+    float v[NT];
 #pragma unroll
-    for (int r = 0; r < MT; ++r) {
-        const float a = __shfl(g[r], who), b = __shfl(v[r], who);
-        if (c == r) {
-            ul = a;
-            vl = b;
+    for (int a = 0; a < NT; ++a) {
+        v[a] = 0.f;
+#pragma unroll
+        for (int e = 0; e < NT; ++e)
+#pragma unroll
+            for (int r = 0; r < NA; ++r)
+                if (TS * e + 4 * h + r == who) v[a] = S[e][a][r];
+        // one of the H lanes of a column has it, the others zero
+#pragma unroll
+        for (int d = TS; d < 64; d <<= 1) v[a] += __shfl_xor(v[a], d);
+    }
+
+    // Twice u = G v, with one step v = G^T u in between: what rounding left of the other vectors shrinks with their singular
+    // values, and v is the image of u.
+    float u = 0.f, sigma2 = 0.f;
+    int l = 0;
+#pragma unroll
+    for (int pass = 0; pass < 2; ++pass) {
+        float nv = 0.f;
+#pragma unroll
+        for (int a = 0; a < NT; ++a) nv = fmaf(v[a], v[a], nv);
+        nv = wave_sum(nv) / H;
+        const float unit = nv > 0.f ? 1.f / sqrtf(nv) : 0.f;
+        float w[GP];
+#pragma unroll
+        for (int a = 0; a < NT; ++a) v[a] *= unit;
+#pragma unroll
+        for (int t = 0; t < GP; ++t) {
+            w[t] = 0.f;
+            if (t < GT)
+#pragma unroll
+                for (int a = 0; a < NT; ++a) w[t] = fmaf(g[a][t], v[a], w[t]);
+        }
+        // sum over the TS lanes of a row, each lane keeping half of its values at every step while it has more than one
+        int left = GP, t0 = 0;
+#pragma unroll
+        for (int d = TS / 2; d >= 1; d >>= 1) {
+            if (left > 1) {
+                left >>= 1;
+                const bool upper = (lane & d) != 0;
+                t0 = 2 * t0 + (upper ? 1 : 0);
+#pragma unroll
+                for (int t = 0; t < GP / 2; ++t)
+                    if (t < left) {
+                        const float give = upper ? w[t] : w[t + left];
+                        const float keep = upper ? w[t + left] : w[t];
+                        w[t] = keep + __shfl_xor(give, d);
+                    }
+            } else {
+                w[0] += __shfl_xor(w[0], d);
+            }
+        }
+        u = w[0];
+        l = H * t0 + h;
+        constexpr int kHeld = TS / GP;  // lanes that hold the same element
+        sigma2 = wave_sum(u * u) / kHeld;
+        if (pass == 0) {
+            __builtin_amdgcn_wave_barrier();
+            lds[l] = u;
+            __builtin_amdgcn_wave_barrier();
+#pragma unroll
+            for (int a = 0; a < NT; ++a) v[a] = 0.f;
+#pragma unroll
+            for (int t = 0; t < GT; ++t) {
+                const float ut = lds[H * t + h];
+#pragma unroll
+                for (int a = 0; a < NT; ++a) v[a] = fmaf(g[a][t], ut, v[a]);
+            }
+#pragma unroll
+            for (int a = 0; a < NT; ++a)
+#pragma unroll
+                for (int d = TS; d < 64; d <<= 1) v[a] += __shfl_xor(v[a], d);
         }
     }
-    if (c < m) {
-        Elem<T>::store(L + ((size_t)j * m + c) * m + k, sigma > 0.f ? ul / root : 0.f);
-        Elem<T>::store(R + ((size_t)k * m + j) * m + c, vl * root);
-    }
+    const float sigma = sqrtf(sigma2);
+    // sqrt(sigma_1) of the unscaled slice
+    const float root = sqrtf((ex & 1) ? 2.f * sigma : sigma), scale = ldexpf(1.f, (ex - (ex & 1)) / 2);
+    if (l < m) Elem<T>::store(L + ((size_t)j * m + l) * m + k, sigma > 0.f ? u / sigma * root * scale : 0.f);
+#pragma unroll
+    for (int a = 0; a < NT; ++a)
+        if (h == 0 && TS * a + c < m) Elem<T>::store(R + ((size_t)k * m + j) * m + TS * a + c, v[a] * root * scale);
 }
 
 template <typename T>
 void launch_t(const void* A, void* R, void* L, int m, hipStream_t st)
 {
-    const dim3 grid((unsigned)(m * m)), block(64);
-    if (m <= 8) hipLaunchKernelGGL((project_kernel<T, 8>), grid, block, 0, st, (const T*)A, (T*)R, (T*)L, m);
-    else if (m <= 16) hipLaunchKernelGGL((project_kernel<T, 16>), grid, block, 0, st, (const T*)A, (T*)R, (T*)L, m);
-    else if (m <= 32) hipLaunchKernelGGL((project_kernel<T, 32>), grid, block, 0, st, (const T*)A, (T*)R, (T*)L, m);
-    else hipLaunchKernelGGL((project_kernel<T, 64>), grid, block, 0, st, (const T*)A, (T*)R, (T*)L, m);
+    const dim3 grid((unsigned)((m * m + kWavesPerBlock - 1) / kWavesPerBlock)), block(64 * kWavesPerBlock);
+    if (m <= 16) hipLaunchKernelGGL((project_kernel<T, 1>), grid, block, 0, st, (const T*)A, (T*)R, (T*)L, m);
+    else if (m <= 32) hipLaunchKernelGGL((project_kernel<T, 2>), grid, block, 0, st, (const T*)A, (T*)R, (T*)L, m);
+    else if (m <= 48) hipLaunchKernelGGL((project_kernel<T, 3>), grid, block, 0, st, (const T*)A, (T*)R, (T*)L, m);
+    else hipLaunchKernelGGL((project_kernel<T, 4>), grid, block, 0, st, (const T*)A, (T*)R, (T*)L, m);
 }
 
 }  // namespace
