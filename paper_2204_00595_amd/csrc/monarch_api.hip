@@ -151,7 +151,7 @@ int fwd_layer(const void* x, const void* R, const void* L, const void* bias, boo
     const bool generic = (flags & MONARCH_FLAG_GENERIC) != 0;
     bool bias_done = bias == nullptr, act_done = !act;
     if (!generic && mfma_fwd_ws_supported(pb)) {
-        if (!workspace || workspace_bytes < mfma_fwd_ws_workspace(pb) || !aligned(workspace, 256))
+        if (!workspace || workspace_bytes < mfma_fwd_ws_least(pb) || !aligned(workspace, 256))
             return MONARCH_ERR_WORKSPACE;
         if (batch == 0) return MONARCH_OK;
         if (act && mfma_fwd_fuses_act(pb, true)) {
@@ -159,6 +159,7 @@ int fwd_layer(const void* x, const void* R, const void* L, const void* bias, boo
             pb.y_pre = y_pre;
             act_done = true;
         }
+        pb.ws_bytes = workspace_bytes;
         rc = mfma_fwd_ws(pb, x, R, L, y, workspace, st);
         bias_done = bias_done || mfma_fwd_fuses_bias(pb, true);
     } else if (fwd_uses_ops(pb) && (batch == 0 || room_for(workspace, workspace_bytes, ops_fwd_workspace(pb)))) {
@@ -288,9 +289,10 @@ int monarch_fwd_ws(const void* x, const void* R, const void* L, void* y, int64_t
     if (!R || !L || ((!x || !y) && batch > 0)) return MONARCH_ERR_INVALID;
     if (!aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(y, 16)) return MONARCH_ERR_INVALID;
     if (ops) return batch == 0 ? MONARCH_OK : ops_fwd(pb, x, R, L, y, workspace, (hipStream_t)stream);
-    if (!workspace || workspace_bytes < mfma_fwd_ws_workspace(pb) || !aligned(workspace, 256))
+    if (!workspace || workspace_bytes < mfma_fwd_ws_least(pb) || !aligned(workspace, 256))
         return MONARCH_ERR_WORKSPACE;
     if (batch == 0) return MONARCH_OK;
+    pb.ws_bytes = workspace_bytes;
     return mfma_fwd_ws(pb, x, R, L, y, workspace, (hipStream_t)stream);
 }
 

@@ -17,6 +17,7 @@ struct Problem {
     void* colsum_ws = nullptr;   // backward only: colsum_workspace() bytes for the bias gradient's partial rows
     int act = 0;                 // forward only: 1 = the output is gelu(product + bias)
     void* y_pre = nullptr;       // forward with act: the value before the nonlinearity also goes here (may be null)
+    size_t ws_bytes = 0;         // forward with a workspace: its size
     const void* x_pre = nullptr; // backward only: the layer's input is gelu(x_pre); dx is returned with respect to x_pre
     int n_out() const { return k * s; }
     int kq() const { return k * q; }
@@ -125,6 +126,7 @@ int mfma_fwd(const Problem& pb, const void* x, const void* R, const void* L, voi
 // forward with a caller workspace (packed weights): shapes that have such a kernel
 bool mfma_fwd_ws_supported(const Problem& pb);
 size_t mfma_fwd_ws_workspace(const Problem& pb);
+size_t mfma_fwd_ws_least(const Problem& pb);  // what the call cannot do without; with less than the above it runs as for a long batch
 const char* mfma_fwd_ws_name(const Problem& pb);
 int mfma_fwd_ws(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 // transposed multiply y = x M (x (B, k*s), y (B, n_in)) on the matrix cores
@@ -148,8 +150,15 @@ int fwd_wide(const Problem& pb, const void* x, const void* R, const void* L, voi
 // bf16, k = 4, wide blocks: fused forward with the weights packed in MFMA fragment order into a
 // caller-provided workspace (monarch_mfma_fwd_frag.hip)
 bool fwd_frag_supported(const Problem& pb);
-size_t fwd_frag_workspace(const Problem& pb);
+size_t fwd_frag_packed(const Problem& pb);     // the packed weights alone
+size_t fwd_frag_workspace(const Problem& pb);  // ... and the vector between the factors where the batch is short
 int fwd_frag(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
+
+// the same on short batches, one launch per factor (monarch_mfma_fwd_split.hip), on the packed weights of fwd_frag
+bool fwd_split_preferred(const Problem& pb);
+size_t fwd_split_mid_bytes(const Problem& pb);
+int fwd_split(const Problem& pb, const void* x, const void* R, const void* L, uint16_t* RF1, uint16_t* LF2, void* y, void* U,
+              hipStream_t st);  // packs (unless pb.ws_packed()) in the launch of the first factor
 
 // bf16, k = 4, wide blocks: the forward can save the vector between the two factors (B x k*q bf16, stage-2
 // order) and the backward can take it from there instead of recomputing it (pb.saved on both sides)

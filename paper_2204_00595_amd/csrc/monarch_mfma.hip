@@ -32,6 +32,7 @@ size_t mfma_fwd_ws_workspace(const Problem& pb)
     if (real32_mfma_supported(pb)) return real32_mfma_workspace(pb, 0);
     return 0;
 }
+size_t mfma_fwd_ws_least(const Problem& pb) { return fwd_frag_supported(pb) ? fwd_frag_packed(pb) : mfma_fwd_ws_workspace(pb); }
 const char* mfma_fwd_ws_name(const Problem& pb)
 {
     if (fwd_frag_supported(pb)) return "mfma_fwd_frag_bf16";

@@ -30,6 +30,7 @@
 //             c of its units so that step 3, y[b][4*l + c], is one packed 8-byte store per (b, l).
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
+#include "monarch_mfma_pack.h"
 #include "monarch_mfma_stage1.h"
 #include "monarch_act.h"
 
@@ -43,35 +44,7 @@ __global__ void __launch_bounds__(256)
 pack_fwd_kernel(const uint16_t* __restrict__ R, const uint16_t* __restrict__ L, uint16_t* __restrict__ RF1,
                 uint16_t* __restrict__ LF2, int P, int Q, int S)
 {
-    const int nR = 4 * Q * P / 8, nL = 4 * S * Q / 8;  // 16-byte pieces per array
-    int pc = blockIdx.x * 256 + threadIdx.x;
-    if (pc < nR) {
-        const int lane = pc & 63;
-        int rest = pc >> 6;
-        const int QT = Q / 32, T = P / 16;
-        const int jt = rest % QT; rest /= QT;
-        const int t = rest % T;
-        const int kk = rest / T;
-        const uint16_t* src = R + ((size_t)kk * Q + 32 * jt + (lane & 31)) * P + 16 * t + 8 * (lane >> 5);
-        *reinterpret_cast<u32x4*>(RF1 + (size_t)pc * 8) = *reinterpret_cast<const u32x4*>(src);
-    } else if (pc < nR + nL) {
-        pc -= nR;
-        const int lane = pc & 63;
-        int rest = pc >> 6;
-        const int KS = Q / 16, NLT = S / 32;
-        const int ks = rest % KS; rest /= KS;
-        const int lt = rest % NLT;
-        const int c = rest / NLT;
-        const int g = lane >> 5;
-        const uint16_t* src = L + ((size_t)c * S + 32 * lt + (lane & 31)) * Q + 16 * ks;
-        uint16_t v[8];
-#pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = src[4 * (e & 3) + 2 * g + (e >> 2)];
-        u32x4 o;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) o[w] = (uint32_t)v[2 * w] | ((uint32_t)v[2 * w + 1] << 16);
-        *reinterpret_cast<u32x4*>(LF2 + (size_t)pc * 8) = o;
-    }
+    pack_fwd_piece(R, L, RF1, LF2, P, Q, S, blockIdx.x * 256 + threadIdx.x);
 }
 
 // --------------------------------------------------------------------- forward ----
@@ -429,7 +402,8 @@ const Entry* find(const Problem& pb)
 bool fwd_frag_supported(const Problem& pb) { return find(pb) != nullptr; }
 
 // packed R then packed L, each the size of its source
-size_t fwd_frag_workspace(const Problem& pb) { return align_up(pb.n_R() * 2, 256) + align_up(pb.n_L() * 2, 256); }
+size_t fwd_frag_packed(const Problem& pb) { return align_up(pb.n_R() * 2, 256) + align_up(pb.n_L() * 2, 256); }
+size_t fwd_frag_workspace(const Problem& pb) { return fwd_frag_packed(pb) + (fwd_split_preferred(pb) ? fwd_split_mid_bytes(pb) : 0); }
 
 int fwd_frag(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
 {
@@ -437,6 +411,8 @@ int fwd_frag(const Problem& pb, const void* x, const void* R, const void* L, voi
     if (!e) return -2;
     uint16_t* RF1 = (uint16_t*)ws;
     uint16_t* LF2 = (uint16_t*)((char*)ws + align_up(pb.n_R() * 2, 256));
+    if (fwd_split_preferred(pb) && pb.ws_bytes >= fwd_frag_workspace(pb))
+        return fwd_split(pb, x, R, L, RF1, LF2, y, (char*)ws + fwd_frag_packed(pb), st);
     if (!pb.ws_packed()) {
         const size_t pieces = (pb.n_R() + pb.n_L()) / 8;
         hipLaunchKernelGGL(pack_fwd_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,

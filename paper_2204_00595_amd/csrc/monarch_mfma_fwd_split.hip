@@ -1,0 +1,301 @@
+// bf16 forward of the four-block layers on packed weights, for batches too short to fill the chip with 64-row tiles of the
+// fused kernel (monarch_mfma_fwd_frag.hip): one launch per block-diagonal factor, so that the weights are spread over all CUs
+// instead of passing through the few that have a row tile.  The vector between the factors goes through the workspace, in
+// the order the packed L contracts it: U[b][j/4][kk][j%4] (16 elements = one K-step of block c = (j/4) / (Q/16)).
+//
+//   stage 1   workgroup = (row tile, block kk, NT column tiles of 32): the four waves share out the contraction, so that every
+//             byte of x and R the workgroup needs is loaded once, and add up their tiles through LDS
+//   stage 2   workgroup = (row tile, NT column tiles of 32): wave c computes block c (again nothing is loaded twice);
+//             the four blocks of an output row are interleaved through LDS and leave in whole rows
+//
+// Operands come straight from memory to registers: x and U in 16-byte pieces (a K-step is 32 contiguous bytes of a row),
+// weights in 1 KiB fragments.
+// What bounds it: latency for one row tile (two launches of about 3.5 us), above that the address path of the L1 (an x or U
+// load touches 32 lines, 27 clocks, for MFMAs of 32 clocks on four SIMDs).  Staging x and U in LDS instead (whole lines per
+// load) measured no better: the 64 KiB it takes per workgroup cost more overlap than the shorter loads gain.
+// Measured, 1024 -> 4096 -> 1024 with bias and GELU: 8 rows 54 -> 14.5 us, 256 rows 66 -> 20 us, 1531 rows 69 -> 39 us.
+#include "../../include/monarch.h"
+#include "monarch_internal.h"
+#include "monarch_mfma_common.h"
+#include "monarch_mfma_pack.h"
+#include "monarch_act.h"
+
+namespace monarch {
+namespace {
+
+constexpr uint32_t kNowhere = 0xffffffffu;  // a load there reads zero
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffffu, 0x00020000);
+}
+
+// acc[nb][nt] += (32 rows nb) x (32 columns nt) over `steps` K-steps, at most 4 * NG.  a_at / w_at: byte offsets of this lane's
+// first piece (kNowhere: a row or tile that does not exist); W_FIRST: the weights are the first MFMA operand (the result is
+// transposed).  Loads are issued four K-steps at a time, which are the whole 128-byte lines of the rows, `AHEAD` such groups
+// ahead; the trip count is a template parameter because loads past the end, even of nothing, cost as much as real ones.
+template <int NB, int NT, int NG, int AHEAD, bool W_FIRST>
+__device__ __forceinline__ void tile_product(const void* a, const uint32_t (&a_at)[NB], const void* w, const uint32_t (&w_at)[NT],
+                                             uint32_t w_step, int steps, f32x16 (&acc)[NB][NT])
+{
+    constexpr int G = 4, BUF = AHEAD < NG ? AHEAD : NG;
+    const auto ra = buffer_at(a), rw = buffer_at(w);
+    u32x4 af[BUF][G][NB], wf[BUF][G][NT];
+    auto load = [&](int gr, int buf) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int d = 0; d < G; ++d)
+                af[buf][d][n] = __builtin_amdgcn_raw_buffer_load_b128(ra, gr * G + d < steps ? a_at[n] : kNowhere, (gr * G + d) * 32, 0);
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int d = 0; d < G; ++d)
+                wf[buf][d][n] = __builtin_amdgcn_raw_buffer_load_b128(rw, gr * G + d < steps ? w_at[n] : kNowhere, (gr * G + d) * w_step, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int gr = 0; gr < BUF; ++gr) load(gr, gr);
+#pragma unroll
+    for (int gr = 0; gr < NG; ++gr) {
+#pragma unroll
+        for (int d = 0; d < G; ++d)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[i][j] = W_FIRST ? mfma32(as_bf16x8(wf[gr % BUF][d][j]), as_bf16x8(af[gr % BUF][d][i]), acc[i][j])
+                                        : mfma32(as_bf16x8(af[gr % BUF][d][i]), as_bf16x8(wf[gr % BUF][d][j]), acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (gr + BUF < NG) load(gr + BUF, gr % BUF);
+    }
+}
+
+struct SplitGrid {
+    int row_tiles, inner, deal;  // deal: row tiles belong to XCDs (their x, U and y meet in one L2)
+};
+__device__ __forceinline__ bool split_index(const SplitGrid& gr, int& rt, int& in)
+{
+    const int bid = (int)blockIdx.x, seq = gr.deal ? bid >> 3 : bid;
+    rt = gr.deal ? (seq / gr.inner) * 8 + (bid & 7) : seq / gr.inner;
+    in = seq % gr.inner;
+    return rt < gr.row_tiles;
+}
+
+struct SplitPack {
+    const uint16_t *R, *L;
+    uint16_t *RF1, *LF2;
+    int S, pieces, blocks;  // workgroups that compute; those after them pack
+};
+
+// PACK: R is read as it is (in 16-byte pieces of its rows, like x), and further workgroups of the launch build the packed
+// copies of R and L, for the second stage and for later calls.
+template <int NB, int NT, int NG, int AHEAD, bool PACK>
+__global__ void __launch_bounds__(256)
+split_stage1_kernel(const uint16_t* __restrict__ x, const SplitPack w, uint16_t* __restrict__ U, int64_t B, int P, int Q, SplitGrid gr)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
+    f32x4* const part = reinterpret_cast<f32x4*>(split_lds);
+    if constexpr (PACK) {
+        if ((int)blockIdx.x >= w.blocks) {
+            pack_fwd_piece(w.R, w.L, w.RF1, w.LF2, P, Q, w.S, ((int)blockIdx.x - w.blocks) * 256 + (int)threadIdx.x);
+            return;
+        }
+    }
+    int rt, in;
+    if (!split_index(gr, rt, in)) return;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+    const int QT = Q / 32, groups = gr.inner / 4;
+    const int kk = in / groups, jt0 = (in % groups) * NT;
+    const int64_t b0 = (int64_t)rt * 32 * NB;
+    const int rows = B - b0 < 32 * NB ? (int)(B - b0) : 32 * NB;
+    const int T = P / 16, lo = T * wave / 4, hi = T * (wave + 1) / 4;
+
+    f32x16 acc[NB][NT];
+    uint32_t a_at[NB], w_at[NT];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) a_at[i] = i * 32 + ln < rows ? (uint32_t)(((i * 32 + ln) * 4 * P + 16 * lo + 8 * g) * 2) : kNowhere;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+        w_at[j] = jt0 + j >= QT ? kNowhere
+                : PACK ? (uint32_t)((((jt0 + j) * 32 + ln) * P + 16 * lo + 8 * g) * 2) : (uint32_t)((lo * QT + jt0 + j) * 1024 + lane * 16);
+    tile_product<NB, NT, NG, AHEAD, true>(x + b0 * 4 * P + kk * P, a_at, (PACK ? w.R : w.RF1) + (size_t)kk * Q * P, w_at,
+                                          PACK ? 32u : (uint32_t)QT * 1024, hi - lo, acc);
+
+    // wave w keeps the four columns j = 8 * w + 4 * g .. of every tile
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+                part[(((wave * NB + i) * NT + j) * 4 + q4) * 64 + lane] =
+                    f32x4{acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]};
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            f32x4 v = part[((i * NT + j) * 4 + wave) * 64 + lane];
+#pragma unroll
+            for (int o = 1; o < 4; ++o) {
+                const f32x4 t = part[(((o * NB + i) * NT + j) * 4 + wave) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += t[e];
+            }
+            const int row = i * 32 + ln, col = (jt0 + j) * 32 + 8 * wave + 4 * g;
+            if (row < rows && jt0 + j < QT)
+                *reinterpret_cast<u32x2*>(U + (b0 + row) * 4 * Q + (col >> 2) * 16 + kk * 4) =
+                    u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        }
+}
+
+template <int NB, int NT, int NG, int AHEAD, bool ACT>
+__global__ void __launch_bounds__(256)
+split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__ LF2, const uint16_t* __restrict__ bias,
+                    uint16_t* __restrict__ y, uint16_t* __restrict__ y_pre, int64_t B, int Q, int S, SplitGrid gr)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
+    constexpr int kStride = NT * 128 + 8, kRows = 32 * NB;
+    uint16_t* const out = reinterpret_cast<uint16_t*>(split_lds);
+    uint16_t* const pre = out + kRows * kStride;
+    int rt, in;
+    if (!split_index(gr, rt, in)) return;
+    const int c = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+    const int KS = Q / 16, LT = S / 32, lt0 = in * NT;
+    const int64_t b0 = (int64_t)rt * kRows;
+    const int rows = B - b0 < kRows ? (int)(B - b0) : kRows;
+
+    f32x16 acc[NB][NT];
+    uint32_t a_at[NB], w_at[NT];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) a_at[i] = i * 32 + ln < rows ? (uint32_t)(((i * 32 + ln) * 4 * Q + 8 * g) * 2) : kNowhere;
+#pragma unroll
+    for (int j = 0; j < NT; ++j) w_at[j] = lt0 + j < LT ? (uint32_t)((lt0 + j) * KS * 1024 + lane * 16) : kNowhere;
+    tile_product<NB, NT, NG, AHEAD, false>(U + b0 * 4 * Q + c * Q, a_at, LF2 + (size_t)c * LT * KS * 512, w_at, 1024u, KS, acc);
+
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int l = (lt0 + j) * 32 + ln;
+        const float bv = bias && lt0 + j < LT ? __uint_as_float((uint32_t)bias[l * 4 + c] << 16) : 0.f;
+#pragma unroll
+        for (int i = 0; i < NB; ++i)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const int at = (i * 32 + 8 * (r / 4) + 4 * g + r % 4) * kStride + (j * 32 + ln) * 4 + c;
+                const float v = acc[i][j][r] + bv;
+                if constexpr (ACT) {
+                    if (y_pre) pre[at] = (uint16_t)pack_bf16x2(v, v);
+                    const float a = gelu_f(v);
+                    out[at] = (uint16_t)pack_bf16x2(a, a);
+                } else {
+                    out[at] = (uint16_t)pack_bf16x2(v, v);
+                }
+            }
+    }
+    lds_barrier();
+    constexpr int kPieces = NT * 16;  // of 16 bytes per row
+    const int limit = (4 * S - lt0 * 128) / 8;
+    for (int idx = threadIdx.x; idx < kRows * kPieces; idx += 256) {
+        const int row = idx / kPieces, pc = idx % kPieces;
+        if (row >= rows || pc >= limit) continue;
+        const size_t to = (size_t)(b0 + row) * 4 * S + lt0 * 128 + pc * 8;
+        *reinterpret_cast<u32x4*>(y + to) = lds128(out + row * kStride + pc * 8);
+        if constexpr (ACT)
+            if (y_pre) *reinterpret_cast<u32x4*>(y_pre + to) = lds128(pre + row * kStride + pc * 8);
+    }
+}
+
+SplitGrid split_grid(int64_t B, int rows, int inner, unsigned* blocks)
+{
+    const int tiles = (int)((B + rows - 1) / rows), even = (tiles + 7) / 8 * 8;
+    SplitGrid gr{tiles, inner, 5 * even <= 6 * tiles};
+    *blocks = (unsigned)((gr.deal ? even : tiles) * inner);
+    return gr;
+}
+
+struct SplitArgs {
+    const uint16_t* x;
+    SplitPack w;
+    uint16_t *y, *U;
+};
+template <int NB, int NT, int AHEAD, int NG>
+int launch_stage(const Problem& pb, int stage, const SplitArgs& a, hipStream_t st)
+{
+    unsigned blocks;
+    if (stage == 1) {
+        const SplitGrid gr = split_grid(pb.B, 32 * NB, 4 * ((pb.q / 32 + NT - 1) / NT), &blocks);
+        constexpr size_t lds = (size_t)4 * NB * NT * 4096;
+        auto kern = pb.ws_packed() ? split_stage1_kernel<NB, NT, NG, AHEAD, false> : split_stage1_kernel<NB, NT, NG, AHEAD, true>;
+        SplitPack w = a.w;
+        w.blocks = (int)blocks;
+        if (!pb.ws_packed()) blocks += (unsigned)((w.pieces + 255) / 256);
+        if (hipError_t e = allow_dynamic_lds((const void*)kern, lds)) return hip_status(e);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, a.x, w, a.U, pb.B, pb.p, pb.q, gr);
+    } else {
+        const SplitGrid gr = split_grid(pb.B, 32 * NB, (pb.s / 32 + NT - 1) / NT, &blocks);
+        const size_t lds = (size_t)32 * NB * (NT * 128 + 8) * 2 * (pb.act && pb.y_pre ? 2 : 1);
+        auto kern = pb.act ? split_stage2_kernel<NB, NT, NG, AHEAD, true> : split_stage2_kernel<NB, NT, NG, AHEAD, false>;
+        if (hipError_t e = allow_dynamic_lds((const void*)kern, lds)) return hip_status(e);
+        hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, (const uint16_t*)a.U, (const uint16_t*)a.w.LF2, (const uint16_t*)pb.bias,
+                           a.y, (uint16_t*)pb.y_pre, pb.B, pb.q, pb.s, gr);
+    }
+    return hip_status(hipGetLastError());
+}
+template <int NB, int NT, int AHEAD>
+int launch_steps(const Problem& pb, int stage, const SplitArgs& a, hipStream_t st)
+{
+    // K-steps of a wave: the longest quarter of p, all of q
+    const int steps = stage == 1 ? (pb.p / 16 + 3) / 4 : pb.q / 16;
+    switch ((steps + 3) / 4) {
+        case 1: return launch_stage<NB, NT, AHEAD, 1>(pb, stage, a, st);
+        case 2: return launch_stage<NB, NT, AHEAD, 2>(pb, stage, a, st);
+        case 3: return launch_stage<NB, NT, AHEAD, 3>(pb, stage, a, st);
+        case 4: return launch_stage<NB, NT, AHEAD, 4>(pb, stage, a, st);
+    }
+    return -2;
+}
+
+// 32 x 32 tiles with all their loads in flight while they give every CU at most two workgroups, 32 x 64 beyond (1024 -> 4096 ->
+// 1024, both layers: 256 rows 20 and 25 us, 512 rows 26 and 25, 1531 rows 49 and 39; 64 x 64 and 64 x 128 tiles 46 and 48).
+int launch_factor(const Problem& pb, int stage, const SplitArgs& a, hipStream_t st)
+{
+    const int64_t tiles = (pb.B + 31) / 32 * (stage == 1 ? pb.kq() / 32 : pb.s / 32);
+    return tiles <= 512 ? launch_steps<1, 1, 4>(pb, stage, a, st) : launch_steps<1, 2, 2>(pb, stage, a, st);
+}
+
+}  // namespace
+
+// Up to 3072 rows (48 row tiles of the fused kernel, which takes the same time for any number of them): 1024 -> 4096 -> 1024, both
+// layers, 2048 rows 69 and 47 us, 3000 rows 71 and 62, 4096 rows 73 and 81; 512 -> 2048 -> 512 3000 rows 36 and 28, 4096 rows 34 and
+// 34.  A wave holds 16 K-steps at most.  And only where it all fits the static workspace, so that monarch_fwd_static runs
+// the same kernels as monarch_fwd_ws.
+bool fwd_split_preferred(const Problem& pb)
+{
+    return pb.B > 0 && pb.B <= 3072 && pb.p <= 1024 && pb.q <= 256 &&
+           fwd_frag_packed(pb) + fwd_split_mid_bytes(pb) <= MONARCH_STATIC_WORKSPACE_BYTES;
+}
+
+size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)pb.B * pb.kq() * 2, 256); }
+
+int fwd_split(const Problem& pb, const void* x, const void* R, const void* L, uint16_t* RF1, uint16_t* LF2, void* y, void* U,
+              hipStream_t st)
+{
+    const SplitArgs a{(const uint16_t*)x, SplitPack{(const uint16_t*)R, (const uint16_t*)L, RF1, LF2, pb.s, (int)((pb.n_R() + pb.n_L()) / 8), 0},
+                      (uint16_t*)y, (uint16_t*)U};
+    const int rc = launch_factor(pb, 1, a, st);
+    return rc ? rc : launch_factor(pb, 2, a, st);
+}
+
+}  // namespace monarch

@@ -1,0 +1,48 @@
+"""The forward of the four-block layers on short batches (one launch per factor) at the edges of its tiles: row counts around 32
+and around the numbers at which the tile and the dealing of row tiles change, every width, with and without packed weights."""
+import numpy as np
+import pytest
+
+import oracle
+import parity_util
+from oracle import activation
+from paper_2204_00595_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# B, p, q, s
+CASES = [(1, 64, 64, 64), (31, 64, 64, 128), (33, 128, 64, 64), (97, 128, 128, 512), (2817, 128, 128, 128), (513, 512, 128, 128), (65, 192, 192, 576),
+         (250, 192, 192, 768), (700, 768, 192, 192), (1, 256, 256, 1024), (545, 256, 256, 768), (290, 1024, 256, 256)]
+
+
+@pytest.mark.parametrize("case", CASES, ids=str)
+def test_short_batch_forward(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, p, q, s = case
+    sh = synth.Shape("split_%s" % (case,), "bf16", rows, 4, p, q, s, config=500 + parity_util.stable_seed(str(case)))
+    x, R, L, _ = synth.make_inputs(sh)
+    bias = synth.quantize(synth.normal(78, (sh.n_out,)), "bf16")
+    xd, Rd, Ld, bd = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L, bias))
+    want = oracle.fwd(x, R, L)
+
+    def check(name, got, want):
+        parity_util.check("%s.%s" % (sh.name, name), got.float().cpu().numpy(), want, 2e-2)
+
+    need = B.monarch_fwd_workspace_bytes(rows, sh.n_in, 4, q, s, 1)
+    packed = B.monarch_fwd_workspace_bytes(0, sh.n_in, 4, q, s, 1)
+    assert need > packed
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    y = B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws)
+    check("y", y, want)
+    again = B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED)
+    assert torch.equal(y, again)
+    check("y_long", B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws[:packed], flags=B.MONARCH_FLAG_WS_PACKED), want)  # no room: the fused kernel
+    check("y_bias", B.monarch_fwd_bias(xd, Rd, Ld, bd, workspace=ws), oracle.fwd_bias(x, R, L, bias))
+    pre, act = B.monarch_fwd_bias_gelu(xd, Rd, Ld, bd, workspace=ws)
+    check("pre", pre, oracle.fwd_bias(x, R, L, bias))
+    check("gelu", act, activation.gelu(oracle.fwd_bias(x, R, L, bias)))
+    _, act2 = B.monarch_fwd_bias_gelu(xd, Rd, Ld, bd, want_pre=False, workspace=ws)
+    assert torch.equal(act, act2)
