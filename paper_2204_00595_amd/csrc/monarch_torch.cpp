@@ -256,12 +256,15 @@ Saved fwd_save(const Tensor& x, const Tensor& R, const Tensor& L, Tensor y, Tens
     sh.check_factors(R, L);
     y = out(y, "y", {sh.B, sh.n_out()}, sh.dtype, sh.device);
     const size_t need = monarch_saved_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
-    if (!saved.defined() && need) saved = make({(int64_t)need}, at::kByte, sh.device);
+    // nothing to save for this shape: the forward that has a workspace (fp32, k = 64 blocks of 64, 12000 rows: 6050 us without
+    // one, which is the SIMT kernels there, 290 with)
+    if (!need) return Saved{fwd_layer("monarch_fwd_save", x, R, L, {}, Act::none, {}, false, y, {}, flags, st).y, Tensor()};
+    if (!saved.defined()) saved = make({(int64_t)need}, at::kByte, sh.device);
     const Bytes b(saved);
     const int rc = monarch_fwd_save(ptr(x), ptr(R), ptr(L), ptr(y), b.p, b.n, sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s,
                                     sh.code(), w.stream(), flags);
     if (rc) raise_status(rc, "monarch_fwd_save");
-    return Saved{y, need ? saved : Tensor()};
+    return Saved{y, saved};
 }
 
 // Every backward: `x_pre` (the layer's input is gelu(x_pre)) and `saved` (the vector between the factors) may be missing.
@@ -400,7 +403,7 @@ struct LinearFn : torch::autograd::Function<LinearFn> {
         Saved r;
         if (bias.has_value()) r.y = fwd_layer("monarch_fwd_bias", x2, R, L, *bias, Act::none, {}, false, {}, {}, 0, current).y;
         else if (save_intermediate) r = fwd_save(x2, R, L, {}, {}, 0, current);
-        else r.y = fwd(x2, R, L, {}, 0, current);
+        else r.y = fwd_layer("monarch_fwd_ws", x2, R, L, {}, Act::none, {}, false, {}, {}, 0, current).y;
         ctx->save_for_backward({x2, R, L, r.saved});
         if (bias.has_value()) ctx->saved_data["bias"] = true;
         if (x.dim() == 2) return r.y;
