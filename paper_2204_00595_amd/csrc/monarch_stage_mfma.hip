@@ -1,5 +1,5 @@
 // Complex-valued Monarch multiply on the matrix cores (complex64, fp32 arithmetic), for square blocks
-// p = q = s in {16, 32, 64} and any k.  The paper's results hold over C (Notation Review); the steps are
+// p = q = s, a multiple of 8 from 16 to 64, and any k.  The paper's results hold over C (Notation Review); the steps are
 // those of Section 3.3 with the permutations of Definition 3.1, the gradients those of monarch_complex.hip.
 //
 // A complex product is a real product of twice the size: with a vector stored as interleaved (re, im) pairs,
@@ -35,6 +35,8 @@ namespace monarch {
 namespace {
 
 constexpr int kRT = 32;  // batch rows per tile
+template <int Q>
+constexpr int kTileWaves = (Q + 15) / 16;  // M tiles (16 outputs) of a block
 
 __device__ __forceinline__ f32x16 mfma_f32(float a, float b, f32x16 c)
 {
@@ -67,10 +69,12 @@ __device__ __forceinline__ void lds_store_c2(float2* dst, u32x4 v)  // two compl
 // single floats, src[row][i'*k + g] for the 2P real indices i' of the block.
 template <int P, int NTHR, int IN, bool REAL = false>
 struct ActTile {
-    static constexpr int kPieces = (IN == kInGather) ? kRT * P / NTHR : kRT * P / 2 / NTHR;  // per thread
+    static constexpr int kAll = (IN == kInGather) ? kRT * P : kRT * P / 2;
+    static constexpr int kPieces = (kAll + NTHR - 1) / NTHR;  // per thread
+    static __device__ __forceinline__ bool has(int idx) { return kAll % NTHR == 0 || idx < kAll; }
     static constexpr int kStride = (IN == kInT) ? kRT : P + 1;
     static constexpr int kLen = (IN == kInT) ? P * kRT : kRT * (P + 1);
-    static_assert((IN == kInGather ? kRT * P : kRT * P / 2) % NTHR == 0, "tile does not divide over the threads");
+    static_assert(!REAL || kAll % NTHR == 0, "tile does not divide over the threads");
     u32x4 v[IN == kInGather ? (kPieces + 1) / 2 : kPieces];
 
     __device__ __forceinline__ void fetch(const float2* __restrict__ src, int64_t rt, int g, int k, int64_t ld, int64_t B, int tid)
@@ -80,7 +84,7 @@ struct ActTile {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / (P / 2), c2 = idx - row * (P / 2);
-                v[n] = (row0 + row < B) ? ldg128(src + (row0 + row) * ld + (size_t)g * P + 2 * c2) : u32x4{0, 0, 0, 0};
+                v[n] = (has(idx) && row0 + row < B) ? ldg128(src + (row0 + row) * ld + (size_t)g * P + 2 * c2) : u32x4{0, 0, 0, 0};
             }
         } else if constexpr (IN == kInGather && REAL) {
             const float* srcf = reinterpret_cast<const float*>(src);
@@ -96,14 +100,15 @@ struct ActTile {
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / P, i = idx - row * P;
                 float2 t = make_float2(0.f, 0.f);
-                if (row0 + row < B) t = src[(row0 + row) * ld + (size_t)i * k + g];
+                if (has(idx) && row0 + row < B) t = src[(row0 + row) * ld + (size_t)i * k + g];
                 if (n & 1) { v[n / 2].z = __float_as_uint(t.x); v[n / 2].w = __float_as_uint(t.y); }
                 else { v[n / 2].x = __float_as_uint(t.x); v[n / 2].y = __float_as_uint(t.y); }
             }
         } else {
             const float2* tile = src + ((size_t)rt * k + g) * (P * kRT);
 #pragma unroll
-            for (int n = 0; n < kPieces; ++n) v[n] = ldg128(tile + 2 * (tid + n * NTHR));
+            for (int n = 0; n < kPieces; ++n)
+                if (has(tid + n * NTHR)) v[n] = ldg128(tile + 2 * (tid + n * NTHR));
         }
     }
 
@@ -113,7 +118,7 @@ struct ActTile {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / (P / 2), c2 = idx - row * (P / 2);
-                lds_store_c2(act + row * kStride + 2 * c2, v[n]);
+                if (has(idx)) lds_store_c2(act + row * kStride + 2 * c2, v[n]);
             }
         } else if constexpr (IN == kInGather && REAL) {
             float* actf = reinterpret_cast<float*>(act);
@@ -127,12 +132,13 @@ struct ActTile {
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / P, i = idx - row * P;
                 const u32x4 w = v[n / 2];
-                act[row * kStride + i] = (n & 1) ? make_float2(__uint_as_float(w.z), __uint_as_float(w.w))
+                if (has(idx)) act[row * kStride + i] = (n & 1) ? make_float2(__uint_as_float(w.z), __uint_as_float(w.w))
                                                  : make_float2(__uint_as_float(w.x), __uint_as_float(w.y));
             }
         } else {
 #pragma unroll
-            for (int n = 0; n < kPieces; ++n) *reinterpret_cast<u32x4*>(act + 2 * (tid + n * NTHR)) = v[n];
+            for (int n = 0; n < kPieces; ++n)
+                if (has(tid + n * NTHR)) *reinterpret_cast<u32x4*>(act + 2 * (tid + n * NTHR)) = v[n];
         }
     }
 
@@ -156,11 +162,12 @@ struct ActTile {
 // (CONJT: transposed), and since the permutations move single values, the two values of a result pair go to their
 // places separately (in the tiled workspace, to the pair slot [index / 2][row][index % 2] of the consumer's block).
 template <int P, int Q, int IN, int OUT, bool CONJT, bool REAL = false>
-__global__ void __launch_bounds__(4 * Q)
+__global__ void __launch_bounds__(kTileWaves<Q> * 64)
 cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float2* __restrict__ out, int64_t B,
               int k, int nsplit, int perm_b)
 {
-    constexpr int NTHR = 4 * Q;
+    constexpr int NTHR = kTileWaves<Q> * 64;
+    constexpr bool kWhole = Q % 16 == 0;  // else the last wave has outputs that do not exist
     using Tile = ActTile<P, NTHR, IN, REAL>;
     constexpr int OSTR = Q + 1;
     __shared__ __align__(16) float2 act[2][Tile::kLen];
@@ -192,7 +199,8 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
                 }
             }
         } else {
-            const int jw = 16 * mt + (col >> 1);
+            int jw = 16 * mt + (col >> 1);
+            if (!kWhole && jw >= Q) jw = Q - 1;
             const float2* Wg = W + (size_t)g * P * Q;
             constexpr float sgn = CONJT ? -1.f : 1.f;
 #pragma unroll
@@ -230,12 +238,14 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
             for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
-                    ost[col * OSTR + 16 * mt + 4 * q4 + 2 * kh + h] = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
+                    if (kWhole || 16 * mt + 4 * q4 + 2 * kh + h < Q)
+                        ost[col * OSTR + 16 * mt + 4 * q4 + 2 * kh + h] = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
             lds_barrier();
-            constexpr int kPieces = kRT * Q / 2 / NTHR;
+            constexpr int kAll = kRT * Q / 2, kPieces = (kAll + NTHR - 1) / NTHR;
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, r = idx / (Q / 2), c2 = idx - r * (Q / 2);
+                if (kAll % NTHR != 0 && idx >= kAll) continue;
                 const float2 v0 = ost[r * OSTR + 2 * c2], v1 = ost[r * OSTR + 2 * c2 + 1];
                 if (rt * kRT + r < B)
                     *reinterpret_cast<f32x4*>(out + (rt * kRT + r) * ld_out + (size_t)g * Q + 2 * c2) = f32x4{v0.x, v0.y, v1.x, v1.y};
@@ -246,6 +256,7 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
 #pragma unroll
                 for (int h = 0; h < 2; ++h) {
                     const int j = 16 * mt + 4 * q4 + 2 * kh + h;
+                    if (!kWhole && j >= Q) continue;
                     const float2 v = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
                     if constexpr (REAL) {
                         float* outf = reinterpret_cast<float*>(out);
@@ -304,7 +315,7 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
                  int nsplit)
 {
     constexpr int MTW = Scatter8<P, Q>::MTW;
-    constexpr int MTG = Q / 16 / MTW;  // groups of M tiles = workgroups per (block octet, split)
+    constexpr int MTG = kTileWaves<Q> / MTW;  // groups of M tiles = workgroups per (block octet, split)
     constexpr int NCH = MTW == 1 ? 1 : 4;  // pieces a tile's activations are fetched in
     constexpr int CH = P / 2 / NCH;        // input pairs per piece
     constexpr int OROW = Scatter8<P, Q>::kRow;
@@ -332,7 +343,8 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
                 A1[m][u] = wv.y;
             }
         } else {
-            const int jw = 16 * (mt0 + m) + (col >> 1);
+            int jw = 16 * (mt0 + m) + (col >> 1);
+            if (Q % 16 != 0 && jw >= Q) jw = Q - 1;  // an output that does not exist
             const float2* Wg = W + (size_t)g * P * Q;
 #pragma unroll
             for (int u = 0; u < P / 2; ++u) {
@@ -398,7 +410,7 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
             for (int n = 0; n < 4 * MTW; ++n) {  // 32 rows x 16 * MTW outputs x 4 pairs of blocks, 16 bytes each
                 const int idx = tid + n * 512, c2 = idx & 3, ll = (idx >> 2) % (16 * MTW), r = idx / (64 * MTW);
                 const float2 v0 = o[r * OROW + ll * 8 + 2 * c2], v1 = o[r * OROW + ll * 8 + 2 * c2 + 1];
-                if (rt * kRT + r < B)
+                if (rt * kRT + r < B && (Q % 16 == 0 || 16 * mt0 + ll < Q))
                     *reinterpret_cast<f32x4*>(out + (rt * kRT + r) * ld_out + (size_t)(16 * mt0 + ll) * k + 8 * oct + 2 * c2) =
                         f32x4{v0.x, v0.y, v1.x, v1.y};
             }
@@ -461,8 +473,8 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
                 float2* __restrict__ dwt, int64_t B, int k, int nsplit, int perm_b)
 {
     constexpr int MTW = kMTilesPerWaveGather<Q, REAL>;
-    constexpr int MTG = Q / 16 / MTW;
-    constexpr int NCHUNK = P / 16;
+    constexpr int MTG = kTileWaves<Q> / MTW;
+    constexpr int NCHUNK = (P + 15) / 16;
     constexpr int PLANE = Gather8<P>::kPlane;
     extern __shared__ __align__(16) float2 gat8[];
 
@@ -488,7 +500,8 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
                 A1[m][u] = Wf[(size_t)(2 * (2 * u + kh) + 1) * (2 * Q)];
             }
         } else {
-            const int jw = 16 * (mt0 + m) + (col >> 1);
+            int jw = 16 * (mt0 + m) + (col >> 1);
+            if (Q % 16 != 0 && jw >= Q) jw = Q - 1;
             const float2* Wg = W + (size_t)g * P * Q;
 #pragma unroll
             for (int u = 0; u < P / 2; ++u) {
@@ -510,7 +523,8 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
                 pre[n] = row < B ? ldg128(srcf + row * (2 * ld_in) + (size_t)(32 * ch + il) * k + 8 * oct + 4 * part) : u32x4{0, 0, 0, 0};
             } else {
                 const int c2 = idx & 3, ll = (idx >> 2) & 15;
-                pre[n] = row < B ? ldg128(in + row * ld_in + (size_t)(16 * ch + ll) * k + 8 * oct + 2 * c2) : u32x4{0, 0, 0, 0};
+                pre[n] = row < B && (P % 16 == 0 || 16 * ch + ll < P)
+                             ? ldg128(in + row * ld_in + (size_t)(16 * ch + ll) * k + 8 * oct + 2 * c2) : u32x4{0, 0, 0, 0};
             }
         }
     };
@@ -550,6 +564,7 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
             const float2* mine = buf + w * PLANE;
 #pragma unroll
             for (int u = 0; u < 8; ++u) {
+                if (ch * 8 + u >= P / 2) continue;  // the last chunk of a block that is no multiple of 16
                 const float2 xv = mine[col * 17 + 2 * u + kh];
 #pragma unroll
                 for (int m = 0; m < MTW; ++m) {
@@ -561,7 +576,8 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
                 if (mt0 == 0) {
                     float2* dst = dwt + (((size_t)rt * k + g) * P + 16 * ch) * kRT;
 #pragma unroll
-                    for (int n = 0; n < 8; ++n) dst[(2 * n + kh) * kRT + col] = mine[col * 17 + 2 * n + kh];
+                    for (int n = 0; n < 8; ++n)
+                        if (16 * ch + 2 * n < P) dst[(2 * n + kh) * kRT + col] = mine[col * 17 + 2 * n + kh];
                 }
             }
         }
@@ -582,6 +598,7 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
 #pragma unroll
                     for (int h = 0; h < 2; ++h) {
                         const int j = 16 * (mt0 + m) + 4 * q4 + 2 * kh + h;
+                        if (Q % 16 != 0 && j >= Q) continue;
                         const int d = mid_src(g * Q + j, k, Q, pb);
                         const int blk = d / Q, idx = d - blk * Q;
                         out[(((size_t)rt * k + blk) * Q + idx) * kRT + col] =
@@ -600,7 +617,10 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
 // wave read consecutive addresses for one row: [row][len] for row-major sources, [idx][32 + 1] for the tiled ones.
 template <int LEN, int NTHR, int MODE, bool REAL = false>
 struct WgTile {
-    static constexpr int kPieces = (MODE == kInGather) ? kRT * LEN / NTHR : kRT * LEN / 2 / NTHR;
+    static constexpr int kAll = (MODE == kInGather) ? kRT * LEN : kRT * LEN / 2;
+    static constexpr int kPieces = (kAll + NTHR - 1) / NTHR;
+    static __device__ __forceinline__ bool has(int idx) { return kAll % NTHR == 0 || idx < kAll; }
+    static_assert(!REAL || kAll % NTHR == 0, "tile does not divide over the threads");
     static constexpr int kLen = (MODE == kInT) ? LEN * (kRT + 1) : kRT * LEN;
     u32x4 v[MODE == kInGather ? (kPieces + 1) / 2 : kPieces];
 
@@ -611,7 +631,7 @@ struct WgTile {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / (LEN / 2), c2 = idx - row * (LEN / 2);
-                v[n] = (row0 + row < B) ? ldg128(src + (row0 + row) * ld + (size_t)g * LEN + 2 * c2) : u32x4{0, 0, 0, 0};
+                v[n] = (has(idx) && row0 + row < B) ? ldg128(src + (row0 + row) * ld + (size_t)g * LEN + 2 * c2) : u32x4{0, 0, 0, 0};
             }
         } else if constexpr (MODE == kInGather && REAL) {
             const float* srcf = reinterpret_cast<const float*>(src);
@@ -627,14 +647,15 @@ struct WgTile {
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / LEN, i = idx - row * LEN;
                 float2 t = make_float2(0.f, 0.f);
-                if (row0 + row < B) t = src[(row0 + row) * ld + (size_t)i * k + g];
+                if (has(idx) && row0 + row < B) t = src[(row0 + row) * ld + (size_t)i * k + g];
                 if (n & 1) { v[n / 2].z = __float_as_uint(t.x); v[n / 2].w = __float_as_uint(t.y); }
                 else { v[n / 2].x = __float_as_uint(t.x); v[n / 2].y = __float_as_uint(t.y); }
             }
         } else {
             const float2* tile = src + ((size_t)rt * k + g) * (LEN * kRT);
 #pragma unroll
-            for (int n = 0; n < kPieces; ++n) v[n] = ldg128(tile + 2 * (tid + n * NTHR));
+            for (int n = 0; n < kPieces; ++n)
+                if (has(tid + n * NTHR)) v[n] = ldg128(tile + 2 * (tid + n * NTHR));
         }
     }
 
@@ -642,7 +663,8 @@ struct WgTile {
     {
         if constexpr (MODE == kInNat) {
 #pragma unroll
-            for (int n = 0; n < kPieces; ++n) *reinterpret_cast<u32x4*>(t + 2 * (tid + n * NTHR)) = v[n];
+            for (int n = 0; n < kPieces; ++n)
+                if (has(tid + n * NTHR)) *reinterpret_cast<u32x4*>(t + 2 * (tid + n * NTHR)) = v[n];
         } else if constexpr (MODE == kInGather && REAL) {
             float* tf = reinterpret_cast<float*>(t);
 #pragma unroll
@@ -651,14 +673,14 @@ struct WgTile {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
                 const u32x4 w = v[n / 2];
-                t[tid + n * NTHR] = (n & 1) ? make_float2(__uint_as_float(w.z), __uint_as_float(w.w))
+                if (has(tid + n * NTHR)) t[tid + n * NTHR] = (n & 1) ? make_float2(__uint_as_float(w.z), __uint_as_float(w.w))
                                             : make_float2(__uint_as_float(w.x), __uint_as_float(w.y));
             }
         } else {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, i = idx / (kRT / 2), rp = idx - i * (kRT / 2);
-                lds_store_c2(t + i * (kRT + 1) + 2 * rp, v[n]);
+                if (has(idx)) lds_store_c2(t + i * (kRT + 1) + 2 * rp, v[n]);
             }
         }
     }
@@ -672,11 +694,11 @@ struct WgTile {
 // REAL: real fp32 operands, two consecutive values per float2: out[g][ma'][nb'] = sum_b A[b][g][ma'] * Bv[b][g][nb'] for
 // the 2*MA x 2*NB real indices; a K = 2 step contracts two batch rows, each lane picking its component of the pair.
 template <int MA, int NB, int AMODE, int BMODE, bool REAL = false>
-__global__ void __launch_bounds__(4 * MA)
+__global__ void __launch_bounds__(kTileWaves<MA> * 64)
 cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float2* __restrict__ part, int64_t B, int k,
               int Z, int64_t lda, int64_t ldb)
 {
-    constexpr int NTHR = 4 * MA;
+    constexpr int NTHR = kTileWaves<MA> * 64;
     constexpr int NTN = REAL ? (2 * NB + 31) / 32 : (NB + 31) / 32;
     using TA = WgTile<MA, NTHR, AMODE, REAL>;
     using TB = WgTile<NB, NTHR, BMODE, REAL>;
@@ -685,7 +707,8 @@ cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float
     const int g = (int)blockIdx.x / Z, z = (int)blockIdx.x - g * Z;
     const int tid = threadIdx.x, lane = tid & 63, mt = tid >> 6;
     const int col = lane & 31, kh = lane >> 5, e = lane & 1;
-    const int ma = 16 * mt + (col >> 1);
+    int ma = 16 * mt + (col >> 1);
+    if (MA % 16 != 0 && ma >= MA) ma = MA - 1;  // a row that does not exist
     const int64_t ntiles = (B + kRT - 1) / kRT;
 
     f32x16 acc[NTN];
@@ -754,7 +777,7 @@ cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float
             for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
                 for (int h = 0; h < 2; ++h)
-                    o[(16 * mt + 4 * q4 + 2 * kh + h) * NB + nb] = make_float2(acc[nt][4 * q4 + 2 * h], acc[nt][4 * q4 + 2 * h + 1]);
+                    if (MA % 16 == 0 || 16 * mt + 4 * q4 + 2 * kh + h < MA) o[(16 * mt + 4 * q4 + 2 * kh + h) * NB + nb] = make_float2(acc[nt][4 * q4 + 2 * h], acc[nt][4 * q4 + 2 * h + 1]);
         }
     }
 }
@@ -805,10 +828,10 @@ int wgrad_chunks(const Problem& pb)
 template <int M, int IN, int OUT, bool CONJT, bool REAL = false>
 int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hipStream_t st)
 {
-    const int nsplit = splits_for(pb, M / 16, 4096);
+    const int nsplit = splits_for(pb, kTileWaves<M>, 4096);
     const int64_t grid = (int64_t)pb.k * nsplit;
     if (grid > 0x7fffffffLL) return -2;
-    hipLaunchKernelGGL((cstage_kernel<M, M, IN, OUT, CONJT, REAL>), dim3((unsigned)grid), dim3(4 * M), 0, st, (const float2*)in,
+    hipLaunchKernelGGL((cstage_kernel<M, M, IN, OUT, CONJT, REAL>), dim3((unsigned)grid), dim3(64 * kTileWaves<M>), 0, st, (const float2*)in,
                        (const float2*)W, (float2*)out, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0);
     return hip_status(hipGetLastError());
 }
@@ -826,7 +849,7 @@ int splits8_for(const Problem& pb, int mtiles)
 template <int M, bool REAL = false>
 int launch_scatter8(const Problem& pb, const void* T, const void* W, void* out, hipStream_t st)
 {
-    constexpr int MTG = M / 16 / Scatter8<M, M>::MTW;
+    constexpr int MTG = kTileWaves<M> / Scatter8<M, M>::MTW;
     const int nsplit = splits8_for(pb, MTG);
     const int64_t grid = (int64_t)(pb.k / 8) * MTG * nsplit;
     if (grid > 0x7fffffffLL) return -2;
@@ -841,7 +864,7 @@ int launch_scatter8(const Problem& pb, const void* T, const void* W, void* out, 
 template <int M, bool EMIT, bool REAL = false>
 int launch_gather8(const Problem& pb, const void* in, const void* W, void* out, void* dwt, hipStream_t st)
 {
-    constexpr int MTG = M / 16 / kMTilesPerWaveGather<M, REAL>;
+    constexpr int MTG = kTileWaves<M> / kMTilesPerWaveGather<M, REAL>;
     const int nsplit = splits8_for(pb, MTG);
     const int64_t grid = (int64_t)(pb.k / 8) * MTG * nsplit;
     if (grid > 0x7fffffffLL) return -2;
@@ -863,9 +886,9 @@ int launch_wgrad(const Problem& pb, const void* A, const void* Bv, void* out, vo
     if (grid > 0x7fffffffLL) return -2;
     float2* dst = Z == 1 ? (float2*)out : (float2*)part;
     auto kern = cwgrad_kernel<M, M, AMODE, BMODE, REAL>;
-    const size_t lds = 2 * (size_t)(WgTile<M, 4 * M, AMODE, REAL>::kLen + WgTile<M, 4 * M, BMODE, REAL>::kLen) * sizeof(float2);
+    const size_t lds = 2 * (size_t)(WgTile<M, 64 * kTileWaves<M>, AMODE, REAL>::kLen + WgTile<M, 64 * kTileWaves<M>, BMODE, REAL>::kLen) * sizeof(float2);
     if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess) return -4;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(4 * M), lds, st, (const float2*)A, (const float2*)Bv, dst, pb.B,
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kTileWaves<M>), lds, st, (const float2*)A, (const float2*)Bv, dst, pb.B,
                        pb.k, Z, lda, ldb);
     int rc = hip_status(hipGetLastError());
     if (rc || Z == 1) return rc;
@@ -995,7 +1018,7 @@ int real32_mfma_bwd(const Problem& pb, const void* dy, const void* x, const void
 
 bool complex_mfma_supported(const Problem& pb)
 {
-    return pb.p == pb.q && pb.q == pb.s && (pb.p == 16 || pb.p == 32 || pb.p == 64);
+    return pb.p == pb.q && pb.q == pb.s && pb.p >= 16 && pb.p <= 64 && pb.p % 8 == 0;
 }
 
 // pass: 0 forward, 1 backward, 2 conjugate-transpose forward
@@ -1010,7 +1033,11 @@ int complex_mfma_fwd(const Problem& pb, const void* x, const void* R, const void
 {
     switch (pb.p) {
         case 16: return run_fwd<16>(pb, x, R, L, y, ws, st);
+        case 24: return run_fwd<24>(pb, x, R, L, y, ws, st);
         case 32: return run_fwd<32>(pb, x, R, L, y, ws, st);
+        case 40: return run_fwd<40>(pb, x, R, L, y, ws, st);
+        case 48: return run_fwd<48>(pb, x, R, L, y, ws, st);
+        case 56: return run_fwd<56>(pb, x, R, L, y, ws, st);
         case 64: return run_fwd<64>(pb, x, R, L, y, ws, st);
         default: return -2;
     }
@@ -1020,7 +1047,11 @@ int complex_mfma_fwd_h(const Problem& pb, const void* x, const void* R, const vo
 {
     switch (pb.p) {
         case 16: return run_fwd_h<16>(pb, x, R, L, y, ws, st);
+        case 24: return run_fwd_h<24>(pb, x, R, L, y, ws, st);
         case 32: return run_fwd_h<32>(pb, x, R, L, y, ws, st);
+        case 40: return run_fwd_h<40>(pb, x, R, L, y, ws, st);
+        case 48: return run_fwd_h<48>(pb, x, R, L, y, ws, st);
+        case 56: return run_fwd_h<56>(pb, x, R, L, y, ws, st);
         case 64: return run_fwd_h<64>(pb, x, R, L, y, ws, st);
         default: return -2;
     }
@@ -1031,7 +1062,11 @@ int complex_mfma_bwd(const Problem& pb, const void* dy, const void* x, const voi
 {
     switch (pb.p) {
         case 16: return run_bwd<16>(pb, dy, x, R, L, dx, dR, dL, ws, st);
+        case 24: return run_bwd<24>(pb, dy, x, R, L, dx, dR, dL, ws, st);
         case 32: return run_bwd<32>(pb, dy, x, R, L, dx, dR, dL, ws, st);
+        case 40: return run_bwd<40>(pb, dy, x, R, L, dx, dR, dL, ws, st);
+        case 48: return run_bwd<48>(pb, dy, x, R, L, dx, dR, dL, ws, st);
+        case 56: return run_bwd<56>(pb, dy, x, R, L, dx, dR, dL, ws, st);
         case 64: return run_bwd<64>(pb, dy, x, R, L, dx, dR, dL, ws, st);
         default: return -2;
     }

@@ -1,0 +1,35 @@
+"""The complex calls with a workspace at block sizes that are no multiple of the 16 outputs of a wave's tile, with block counts that
+are multiples of eight (the eight-blocks-per-workgroup stages) and not, and ragged batches."""
+import numpy as np
+import pytest
+
+from oracle import complex_ref
+from paper_2204_00595_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+def _normal(seed, shape, std):
+    return (synth.normal(seed, shape, std) + 1j * synth.normal(seed + 1, shape, std)).astype(np.complex64)
+
+
+@pytest.mark.parametrize("reading", [0, 1], ids=["reading_a", "reading_b"])
+@pytest.mark.parametrize("case", [(1, 24, 24), (700, 24, 24), (33, 40, 8), (257, 40, 5), (31, 48, 48), (515, 48, 3), (64, 56, 16), (2049, 56, 2)], ids=str)
+def test_blocks_between_the_tiles(case, reading):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, m, k = case
+    x, R, L, dy = (_normal(8800 + 10 * i, shp, std) for i, (shp, std) in enumerate(
+        (((rows, k * m), 1.0), ((k, m, m), m ** -0.5), ((k, m, m), m ** -0.5), ((rows, k * m), 1.0))))
+    xd, Rd, Ld, dyd = (torch.from_numpy(a).cuda() for a in (x, R, L, dy))
+    flags = B.MONARCH_FLAG_PERM_B if reading else 0
+    got = [B.monarch_fwd_c64_ws(xd, Rd, Ld, flags=flags), B.monarch_fwd_h_c64_ws(dyd, Rd, Ld, flags=flags)]
+    got += list(B.monarch_bwd_c64_ws(dyd, xd, Rd, Ld, flags=flags))
+    want = [complex_ref.fwd(x, R, L, reading), complex_ref.fwd_h(dy, R, L, reading)] + list(complex_ref.bwd(dy, x, R, L, reading))
+    for name, g, w in zip(("y", "xMh", "dx", "dR", "dL"), got, want):
+        g = g.cpu().numpy().astype(np.complex128)
+        rel = np.linalg.norm((g - w).reshape(g.shape[0], -1), axis=1) / np.linalg.norm(w.reshape(g.shape[0], -1), axis=1)
+        assert float(rel.max()) <= 4e-5, (name, int(rel.argmax()), float(rel.max()))   # no row, no block of a gradient
+        assert np.linalg.norm(g - w) / np.linalg.norm(w) <= 1e-5, name
