@@ -91,6 +91,13 @@ bool room_for(const void* workspace, size_t bytes, size_t need)
     return workspace && bytes >= need && (uintptr_t)workspace % 256 == 0;
 }
 
+// forward with a workspace on the packed-weight or stage kernels
+bool fwd_uses_ws(const Problem& pb, const void* workspace, size_t bytes)
+{
+    if ((pb.flags & MONARCH_FLAG_GENERIC) || !mfma_fwd_ws_supported(pb)) return false;
+    return !mfma_fwd_ws_optional(pb) || room_for(workspace, bytes, mfma_fwd_ws_workspace(pb));
+}
+
 // Backward scratch: the kernel family's own area, then the partial rows of the bias gradient.
 size_t bwd_kernel_need(const Problem& pb, Family fam)
 {
@@ -148,9 +155,8 @@ int fwd_layer(const void* x, const void* R, const void* L, const void* bias, boo
     if (y_pre && y_pre == y) return MONARCH_ERR_INVALID;
     pb.bias = bias;
     hipStream_t st = (hipStream_t)stream;
-    const bool generic = (flags & MONARCH_FLAG_GENERIC) != 0;
     bool bias_done = bias == nullptr, act_done = !act;
-    if (!generic && mfma_fwd_ws_supported(pb)) {
+    if (fwd_uses_ws(pb, workspace, workspace_bytes)) {
         if (!workspace || workspace_bytes < mfma_fwd_ws_least(pb) || !aligned(workspace, 256))
             return MONARCH_ERR_WORKSPACE;
         if (batch == 0) return MONARCH_OK;
@@ -283,7 +289,7 @@ int monarch_fwd_ws(const void* x, const void* R, const void* L, void* y, int64_t
     int rc = make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags);
     if (rc) return rc;
     const bool ops = fwd_uses_ops(pb) && room_for(workspace, workspace_bytes, ops_fwd_workspace(pb));
-    if ((flags & MONARCH_FLAG_GENERIC) || (!mfma_fwd_ws_supported(pb) && !ops))
+    if (!fwd_uses_ws(pb, workspace, workspace_bytes) && !ops)
         return monarch_fwd_ex(x, R, L, y, batch, n_in, k, q, s, dtype, stream, flags & ~MONARCH_FLAG_WS_PACKED);
     if (flags & MONARCH_FLAG_WGRAD_F32) return MONARCH_ERR_INVALID;  // backward-only flag
     if (!R || !L || ((!x || !y) && batch > 0)) return MONARCH_ERR_INVALID;

@@ -126,7 +126,8 @@ int mfma_fwd(const Problem& pb, const void* x, const void* R, const void* L, voi
 // forward with a caller workspace (packed weights): shapes that have such a kernel
 bool mfma_fwd_ws_supported(const Problem& pb);
 size_t mfma_fwd_ws_workspace(const Problem& pb);
-size_t mfma_fwd_ws_least(const Problem& pb);  // what the call cannot do without; with less than the above it runs as for a long batch
+size_t mfma_fwd_ws_least(const Problem& pb);   // what the call cannot do without; with less than the above it runs as for a long batch
+bool mfma_fwd_ws_optional(const Problem& pb);  // with less than mfma_fwd_ws_workspace it runs as without a workspace
 const char* mfma_fwd_ws_name(const Problem& pb);
 int mfma_fwd_ws(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 // transposed multiply y = x M (x (B, k*s), y (B, n_in)) on the matrix cores
@@ -155,6 +156,7 @@ size_t fwd_frag_workspace(const Problem& pb);  // ... and the vector between the
 int fwd_frag(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 
 // the same on short batches, one launch per factor (monarch_mfma_fwd_split.hip), on the packed weights of fwd_frag
+bool fwd_split_supported(const Problem& pb);
 bool fwd_split_preferred(const Problem& pb);
 size_t fwd_split_mid_bytes(const Problem& pb);
 int fwd_split(const Problem& pb, const void* x, const void* R, const void* L, uint16_t* RF1, uint16_t* LF2, void* y, void* U,

@@ -24,10 +24,14 @@ int mfma_fwd(const Problem& pb, const void* x, const void* R, const void* L, voi
     return -2;
 }
 
-bool mfma_fwd_ws_supported(const Problem& pb) { return fwd_frag_supported(pb) || sq64_supported(pb) || real32_mfma_supported(pb); }
+// packed weights: the fused kernel, the kernels for short batches, or both
+static bool fwd_packed(const Problem& pb) { return fwd_frag_supported(pb) || fwd_split_preferred(pb); }
+bool mfma_fwd_ws_optional(const Problem& pb) { return !fwd_frag_supported(pb) && fwd_split_preferred(pb); }
+
+bool mfma_fwd_ws_supported(const Problem& pb) { return fwd_packed(pb) || sq64_supported(pb) || real32_mfma_supported(pb); }
 size_t mfma_fwd_ws_workspace(const Problem& pb)
 {
-    if (fwd_frag_supported(pb)) return fwd_frag_workspace(pb);
+    if (fwd_packed(pb)) return fwd_frag_workspace(pb);
     if (sq64_supported(pb)) return fwd_sq64_workspace(pb);
     if (real32_mfma_supported(pb)) return real32_mfma_workspace(pb, 0);
     return 0;
@@ -36,13 +40,14 @@ size_t mfma_fwd_ws_least(const Problem& pb) { return fwd_frag_supported(pb) ? fw
 const char* mfma_fwd_ws_name(const Problem& pb)
 {
     if (fwd_frag_supported(pb)) return "mfma_fwd_frag_bf16";
+    if (fwd_packed(pb)) return "mfma_fwd_split_bf16";
     if (sq64_supported(pb)) return "mfma_fwd_sq64_packed_bf16";
     if (real32_mfma_supported(pb)) return "mfma_fwd_stages_f32";
     return "unsupported";
 }
 int mfma_fwd_ws(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
 {
-    if (fwd_frag_supported(pb)) return fwd_frag(pb, x, R, L, y, ws, st);
+    if (fwd_packed(pb)) return fwd_frag(pb, x, R, L, y, ws, st);
     if (sq64_supported(pb)) return fwd_sq64_ws(pb, x, R, L, y, ws, st);
     if (real32_mfma_supported(pb)) return real32_mfma_fwd(pb, x, R, L, y, ws, st);
     return -2;
@@ -84,7 +89,7 @@ int mfma_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, v
 // Which of the forward kernels add pb.bias in their own epilogue (the others need launch_bias_add).
 bool mfma_fwd_fuses_bias(const Problem& pb, bool with_ws)
 {
-    if (with_ws && fwd_frag_supported(pb)) return true;
+    if (with_ws && fwd_packed(pb)) return true;
     if (with_ws && sq64_supported(pb)) return false;
     // mfma_fwd's order of preference: wide, sq64 (no bias epilogue), then sq16 and the shape-generic kernel (both have one)
     return !fwd_wide_supported(pb) && !sq64_supported(pb) && (sq16_supported(pb) || tiled_fwd_supported(pb));
@@ -94,7 +99,7 @@ bool mfma_bwd_fuses_dbias(const Problem& pb) { return bwd_wide_supported(pb); }
 
 // The nonlinearity of the feed-forward block: applied in the epilogue of the packed-weight forward for the
 // four-block layer shapes, and in the dx epilogue of their (recomputing) backward.
-bool mfma_fwd_fuses_act(const Problem& pb, bool with_ws) { return with_ws && fwd_frag_supported(pb); }
+bool mfma_fwd_fuses_act(const Problem& pb, bool with_ws) { return with_ws && fwd_packed(pb); }
 bool mfma_bwd_fuses_act(const Problem& pb) { return bwd_wide_supported(pb) && !pb.saved; }
 
 bool mfma_bwd_supported(const Problem& pb)

@@ -407,12 +407,12 @@ size_t fwd_frag_workspace(const Problem& pb) { return fwd_frag_packed(pb) + (fwd
 
 int fwd_frag(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
 {
-    const Entry* e = find(pb);
-    if (!e) return -2;
+    const Entry* e = find(pb);  // may be null: shapes that only the kernels for short batches serve
     uint16_t* RF1 = (uint16_t*)ws;
     uint16_t* LF2 = (uint16_t*)((char*)ws + align_up(pb.n_R() * 2, 256));
     if (fwd_split_preferred(pb) && pb.ws_bytes >= fwd_frag_workspace(pb))
         return fwd_split(pb, x, R, L, RF1, LF2, y, (char*)ws + fwd_frag_packed(pb), st);
+    if (!e) return -2;
     if (!pb.ws_packed()) {
         const size_t pieces = (pb.n_R() + pb.n_L()) / 8;
         hipLaunchKernelGGL(pack_fwd_kernel, dim3((unsigned)((pieces + 255) / 256)), dim3(256), 0, st,

@@ -277,13 +277,19 @@ int launch_factor(const Problem& pb, int stage, const SplitArgs& a, hipStream_t 
 
 }  // namespace
 
-// Up to 3072 rows (48 row tiles of the fused kernel, which takes the same time for any number of them): 1024 -> 4096 -> 1024, both
-// layers, 2048 rows 69 and 47 us, 3000 rows 71 and 62, 4096 rows 73 and 81; 512 -> 2048 -> 512 3000 rows 36 and 28, 4096 rows 34 and
-// 34.  A wave holds 16 K-steps at most.  And only where it all fits the static workspace, so that monarch_fwd_static runs
-// the same kernels as monarch_fwd_ws.
+bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
+{
+    return pb.dtype == 1 && pb.k == 4 && !pb.perm_b() && pb.p % 16 == 0 && pb.q % 32 == 0 && pb.s % 32 == 0 && pb.p <= 1024 &&
+           pb.q <= 256;
+}
+
+// Where there is a fused kernel, up to 3072 rows (48 of its row tiles; it takes the same time for any number of them): 1024 -> 4096
+// -> 1024, both layers, 2048 rows 69 and 47 us, 3000 rows 71 and 62, 4096 rows 73 and 81; 512 -> 2048 -> 512 3000 rows 36 and 28,
+// 4096 rows 34 and 34.  Where the other choice is the shape-generic kernel (width 384: 47 us for 300 rows, 60 for 8000), up to
+// 8192.  And only where it all fits the static workspace, so that monarch_fwd_static runs the same kernels as monarch_fwd_ws.
 bool fwd_split_preferred(const Problem& pb)
 {
-    return pb.B > 0 && pb.B <= 3072 && pb.p <= 1024 && pb.q <= 256 &&
+    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= (fwd_frag_supported(pb) ? 3072 : 8192) &&
            fwd_frag_packed(pb) + fwd_split_mid_bytes(pb) <= MONARCH_STATIC_WORKSPACE_BYTES;
 }
 

@@ -1,4 +1,4 @@
-"""The forward of the four-block layers on short batches (one launch per factor) at the edges of its tiles: row counts around 32
+"""The forward of the four-block layers on short batches (one launch per factor, with or without a fused kernel) at the edges of its tiles: row counts around 32
 and around the numbers at which the tile and the dealing of row tiles change, every width, with and without packed weights."""
 import numpy as np
 import pytest
@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 
 # B, p, q, s
 CASES = [(1, 64, 64, 64), (31, 64, 64, 128), (33, 128, 64, 64), (97, 128, 128, 512), (2817, 128, 128, 128), (513, 512, 128, 128), (65, 192, 192, 576),
-         (250, 192, 192, 768), (700, 768, 192, 192), (1, 256, 256, 1024), (545, 256, 256, 768), (290, 1024, 256, 256)]
+         (250, 192, 192, 768), (700, 768, 192, 192), (45, 96, 96, 384), (1300, 384, 96, 96), (129, 48, 32, 96), (1, 256, 256, 1024), (545, 256, 256, 768), (290, 1024, 256, 256)]
 
 
 @pytest.mark.parametrize("case", CASES, ids=str)
