@@ -12,7 +12,7 @@ CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libmonarch.so")
 NATIVE = os.path.join(HERE, "_native.so")
 SOURCES = ["monarch_api.hip", "monarch_generic.hip", "monarch_mfma.hip", "monarch_mfma_fwd_wide.hip", "monarch_mfma_fwd_frag.hip", "monarch_mfma_fwd_split.hip", "monarch_mfma_tiled.hip", "monarch_project.hip", "monarch_complex.hip", "monarch_stage_mfma.hip", "monarch_act.hip", "monarch_ops.hip",
-           "monarch_mfma_bwd_wide.hip", "monarch_mfma_y1.hip", "monarch_mfma_wgrad.hip", "monarch_mfma_sq64.hip", "monarch_mfma_sq16.hip"]
+           "monarch_mfma_bwd_wide.hip", "monarch_mfma_bwd_split.hip", "monarch_mfma_y1.hip", "monarch_mfma_wgrad.hip", "monarch_mfma_sq64.hip", "monarch_mfma_sq16.hip"]
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
 FLAGS = [
     "-O3", "-std=c++17", "-fPIC", "--offload-arch=gfx950",

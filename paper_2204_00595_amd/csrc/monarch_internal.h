@@ -171,6 +171,12 @@ size_t bwd_wide_workspace(const Problem& pb);
 int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx,
              void* dR, void* dL, void* ws, hipStream_t st);
 
+// the same on short batches, one launch per adjoint factor (monarch_mfma_bwd_split.hip); blocks that are multiples of 32
+bool bwd_split_preferred(const Problem& pb);
+size_t bwd_split_workspace(const Problem& pb);
+int bwd_split(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL,
+              void* ws, hipStream_t st);
+
 // bf16, k = 4, wide blocks with long blocks (p >= 768): step 1 as a GEMM of its own, Y1[b][kk*q + j] (B x k*q bf16) from x and the
 // packed R of the backward's prep pass (monarch_mfma_y1.hip)
 bool y1_gemm_supported(const Problem& pb);

@@ -95,19 +95,20 @@ bool mfma_fwd_fuses_bias(const Problem& pb, bool with_ws)
     return !fwd_wide_supported(pb) && !sq64_supported(pb) && (sq16_supported(pb) || tiled_fwd_supported(pb));
 }
 
-bool mfma_bwd_fuses_dbias(const Problem& pb) { return bwd_wide_supported(pb); }
+bool mfma_bwd_fuses_dbias(const Problem& pb) { return bwd_split_preferred(pb) || bwd_wide_supported(pb); }
 
 // The nonlinearity of the feed-forward block: applied in the epilogue of the packed-weight forward for the
 // four-block layer shapes, and in the dx epilogue of their (recomputing) backward.
 bool mfma_fwd_fuses_act(const Problem& pb, bool with_ws) { return with_ws && fwd_packed(pb); }
-bool mfma_bwd_fuses_act(const Problem& pb) { return bwd_wide_supported(pb) && !pb.saved; }
+bool mfma_bwd_fuses_act(const Problem& pb) { return bwd_split_preferred(pb) || (bwd_wide_supported(pb) && !pb.saved); }
 
 bool mfma_bwd_supported(const Problem& pb)
 {
-    return bwd_wide_supported(pb) || bwd_sq64_supported(pb) || sq16_supported(pb) || tiled_bwd_supported(pb) || real32_mfma_supported(pb);
+    return bwd_split_preferred(pb) || bwd_wide_supported(pb) || bwd_sq64_supported(pb) || sq16_supported(pb) || tiled_bwd_supported(pb) || real32_mfma_supported(pb);
 }
 size_t mfma_bwd_workspace(const Problem& pb)
 {
+    if (bwd_split_preferred(pb)) return bwd_split_workspace(pb);
     if (bwd_wide_supported(pb)) return bwd_wide_workspace(pb);
     if (bwd_sq64_supported(pb)) return bwd_sq64_workspace(pb);
     if (sq16_supported(pb)) return bwd_sq16_workspace(pb);
@@ -127,6 +128,7 @@ const char* mfma_bwd_name(const Problem& pb)
 int mfma_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR,
              void* dL, void* ws, hipStream_t st)
 {
+    if (bwd_split_preferred(pb)) return bwd_split(pb, dy, x, R, L, dx, dR, dL, ws, st);
     if (bwd_wide_supported(pb)) return bwd_wide(pb, dy, x, R, L, dx, dR, dL, ws, st);
     if (bwd_sq64_supported(pb)) return bwd_sq64(pb, dy, x, R, L, dx, dR, dL, ws, st);
     if (sq16_supported(pb)) return bwd_sq16(pb, dy, x, R, L, dx, dR, dL, ws, st);

@@ -18,68 +18,11 @@
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
 #include "monarch_mfma_pack.h"
+#include "monarch_mfma_split.h"
 #include "monarch_act.h"
 
 namespace monarch {
 namespace {
-
-constexpr uint32_t kNowhere = 0xffffffffu;  // a load there reads zero
-__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
-{
-    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffffu, 0x00020000);
-}
-
-// acc[nb][nt] += (32 rows nb) x (32 columns nt) over `steps` K-steps, at most 4 * NG.  a_at / w_at: byte offsets of this lane's
-// first piece (kNowhere: a row or tile that does not exist); W_FIRST: the weights are the first MFMA operand (the result is
-// transposed).  Loads are issued four K-steps at a time, which are the whole 128-byte lines of the rows, `AHEAD` such groups
-// ahead; the trip count is a template parameter because loads past the end, even of nothing, cost as much as real ones.
-template <int NB, int NT, int NG, int AHEAD, bool W_FIRST>
-__device__ __forceinline__ void tile_product(const void* a, const uint32_t (&a_at)[NB], const void* w, const uint32_t (&w_at)[NT],
-                                             uint32_t w_step, int steps, f32x16 (&acc)[NB][NT])
-{
-    constexpr int G = 4, BUF = AHEAD < NG ? AHEAD : NG;
-    const auto ra = buffer_at(a), rw = buffer_at(w);
-    u32x4 af[BUF][G][NB], wf[BUF][G][NT];
-    auto load = [&](int gr, int buf) {
-#pragma unroll
-        for (int n = 0; n < NB; ++n)
-#pragma unroll
-            for (int d = 0; d < G; ++d)
-                af[buf][d][n] = __builtin_amdgcn_raw_buffer_load_b128(ra, gr * G + d < steps ? a_at[n] : kNowhere, (gr * G + d) * 32, 0);
-#pragma unroll
-        for (int n = 0; n < NT; ++n)
-#pragma unroll
-            for (int d = 0; d < G; ++d)
-                wf[buf][d][n] = __builtin_amdgcn_raw_buffer_load_b128(rw, gr * G + d < steps ? w_at[n] : kNowhere, (gr * G + d) * w_step, 0);
-        __builtin_amdgcn_sched_barrier(0);
-    };
-#pragma unroll
-    for (int gr = 0; gr < BUF; ++gr) load(gr, gr);
-#pragma unroll
-    for (int gr = 0; gr < NG; ++gr) {
-#pragma unroll
-        for (int d = 0; d < G; ++d)
-#pragma unroll
-            for (int i = 0; i < NB; ++i)
-#pragma unroll
-                for (int j = 0; j < NT; ++j)
-                    acc[i][j] = W_FIRST ? mfma32(as_bf16x8(wf[gr % BUF][d][j]), as_bf16x8(af[gr % BUF][d][i]), acc[i][j])
-                                        : mfma32(as_bf16x8(af[gr % BUF][d][i]), as_bf16x8(wf[gr % BUF][d][j]), acc[i][j]);
-        __builtin_amdgcn_sched_barrier(0);
-        if (gr + BUF < NG) load(gr + BUF, gr % BUF);
-    }
-}
-
-struct SplitGrid {
-    int row_tiles, inner, deal;  // deal: row tiles belong to XCDs (their x, U and y meet in one L2)
-};
-__device__ __forceinline__ bool split_index(const SplitGrid& gr, int& rt, int& in)
-{
-    const int bid = (int)blockIdx.x, seq = gr.deal ? bid >> 3 : bid;
-    rt = gr.deal ? (seq / gr.inner) * 8 + (bid & 7) : seq / gr.inner;
-    in = seq % gr.inner;
-    return rt < gr.row_tiles;
-}
 
 struct SplitPack {
     const uint16_t *R, *L;
@@ -87,72 +30,20 @@ struct SplitPack {
     int S, pieces, blocks;  // workgroups that compute; those after them pack
 };
 
-// PACK: R is read as it is (in 16-byte pieces of its rows, like x), and further workgroups of the launch build the packed
-// copies of R and L, for the second stage and for later calls.
+// PACK: R is read as it is, and further workgroups of the launch build the packed copies of R and L, for the second stage and for
+// later calls.
 template <int NB, int NT, int NG, int AHEAD, bool PACK>
 __global__ void __launch_bounds__(256)
 split_stage1_kernel(const uint16_t* __restrict__ x, const SplitPack w, uint16_t* __restrict__ U, int64_t B, int P, int Q, SplitGrid gr)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
-    f32x4* const part = reinterpret_cast<f32x4*>(split_lds);
     if constexpr (PACK) {
         if ((int)blockIdx.x >= w.blocks) {
             pack_fwd_piece(w.R, w.L, w.RF1, w.LF2, P, Q, w.S, ((int)blockIdx.x - w.blocks) * 256 + (int)threadIdx.x);
             return;
         }
     }
-    int rt, in;
-    if (!split_index(gr, rt, in)) return;
-    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
-    const int QT = Q / 32, groups = gr.inner / 4;
-    const int kk = in / groups, jt0 = (in % groups) * NT;
-    const int64_t b0 = (int64_t)rt * 32 * NB;
-    const int rows = B - b0 < 32 * NB ? (int)(B - b0) : 32 * NB;
-    const int T = P / 16, lo = T * wave / 4, hi = T * (wave + 1) / 4;
-
-    f32x16 acc[NB][NT];
-    uint32_t a_at[NB], w_at[NT];
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
-#pragma unroll
-    for (int i = 0; i < NB; ++i) a_at[i] = i * 32 + ln < rows ? (uint32_t)(((i * 32 + ln) * 4 * P + 16 * lo + 8 * g) * 2) : kNowhere;
-#pragma unroll
-    for (int j = 0; j < NT; ++j)
-        w_at[j] = jt0 + j >= QT ? kNowhere
-                : PACK ? (uint32_t)((((jt0 + j) * 32 + ln) * P + 16 * lo + 8 * g) * 2) : (uint32_t)((lo * QT + jt0 + j) * 1024 + lane * 16);
-    tile_product<NB, NT, NG, AHEAD, true>(x + b0 * 4 * P + kk * P, a_at, (PACK ? w.R : w.RF1) + (size_t)kk * Q * P, w_at,
-                                          PACK ? 32u : (uint32_t)QT * 1024, hi - lo, acc);
-
-    // wave w keeps the four columns j = 8 * w + 4 * g .. of every tile
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-                part[(((wave * NB + i) * NT + j) * 4 + q4) * 64 + lane] =
-                    f32x4{acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]};
-    lds_barrier();
-#pragma unroll
-    for (int i = 0; i < NB; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j) {
-            f32x4 v = part[((i * NT + j) * 4 + wave) * 64 + lane];
-#pragma unroll
-            for (int o = 1; o < 4; ++o) {
-                const f32x4 t = part[(((o * NB + i) * NT + j) * 4 + wave) * 64 + lane];
-#pragma unroll
-                for (int e = 0; e < 4; ++e) v[e] += t[e];
-            }
-            const int row = i * 32 + ln, col = (jt0 + j) * 32 + 8 * wave + 4 * g;
-            if (row < rows && jt0 + j < QT)
-                *reinterpret_cast<u32x2*>(U + (b0 + row) * 4 * Q + (col >> 2) * 16 + kk * 4) =
-                    u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
-        }
+    split_stage1<NB, NT, NG, AHEAD, PACK, false>(x, PACK ? w.R : w.RF1, U, B, P, Q, gr, (int)blockIdx.x, reinterpret_cast<f32x4*>(split_lds));
 }
 
 template <int NB, int NT, int NG, int AHEAD, bool ACT>
@@ -165,7 +56,7 @@ split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__
     uint16_t* const out = reinterpret_cast<uint16_t*>(split_lds);
     uint16_t* const pre = out + kRows * kStride;
     int rt, in;
-    if (!split_index(gr, rt, in)) return;
+    if (!split_index(gr, (int)blockIdx.x, rt, in)) return;
     const int c = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
     const int KS = Q / 16, LT = S / 32, lt0 = in * NT;
     const int64_t b0 = (int64_t)rt * kRows;
@@ -215,14 +106,6 @@ split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__
         if constexpr (ACT)
             if (y_pre) *reinterpret_cast<u32x4*>(y_pre + to) = lds128(pre + row * kStride + pc * 8);
     }
-}
-
-SplitGrid split_grid(int64_t B, int rows, int inner, unsigned* blocks)
-{
-    const int tiles = (int)((B + rows - 1) / rows), even = (tiles + 7) / 8 * 8;
-    SplitGrid gr{tiles, inner, 5 * even <= 6 * tiles};
-    *blocks = (unsigned)((gr.deal ? even : tiles) * inner);
-    return gr;
 }
 
 struct SplitArgs {

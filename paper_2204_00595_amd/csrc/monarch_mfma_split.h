@@ -1,0 +1,139 @@
+// Shared by the forward and backward of the four-block layers on short batches (monarch_mfma_fwd_split.hip,
+// monarch_mfma_bwd_split.hip): tile products straight from memory, the dealing of row tiles, the first factor.
+#pragma once
+#include "monarch_internal.h"
+#include "monarch_mfma_common.h"
+
+namespace monarch {
+namespace {
+
+constexpr uint32_t kNowhere = 0xffffffffu;  // a load there reads zero
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffffu, 0x00020000);
+}
+
+// acc[nb][nt] += (32 rows nb) x (32 columns nt) over `steps` K-steps, at most 4 * NG.  a_at / w_at: byte offsets of this lane's
+// first piece (kNowhere: a row or tile that does not exist); W_FIRST: the weights are the first MFMA operand (the result is
+// transposed).  Loads are issued four K-steps at a time, which are the whole 128-byte lines of the rows, `AHEAD` such groups
+// ahead; the trip count is a template parameter because loads past the end, even of nothing, cost as much as real ones.
+template <int NB, int NT, int NG, int AHEAD, bool W_FIRST>
+__device__ __forceinline__ void tile_product(const void* a, const uint32_t (&a_at)[NB], const void* w, const uint32_t (&w_at)[NT],
+                                             uint32_t w_step, int steps, f32x16 (&acc)[NB][NT])
+{
+    constexpr int G = 4, BUF = AHEAD < NG ? AHEAD : NG;
+    const auto ra = buffer_at(a), rw = buffer_at(w);
+    u32x4 af[BUF][G][NB], wf[BUF][G][NT];
+    auto load = [&](int gr, int buf) {
+#pragma unroll
+        for (int n = 0; n < NB; ++n)
+#pragma unroll
+            for (int d = 0; d < G; ++d)
+                af[buf][d][n] = __builtin_amdgcn_raw_buffer_load_b128(ra, gr * G + d < steps ? a_at[n] : kNowhere, (gr * G + d) * 32, 0);
+#pragma unroll
+        for (int n = 0; n < NT; ++n)
+#pragma unroll
+            for (int d = 0; d < G; ++d)
+                wf[buf][d][n] = __builtin_amdgcn_raw_buffer_load_b128(rw, gr * G + d < steps ? w_at[n] : kNowhere, (gr * G + d) * w_step, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+#pragma unroll
+    for (int gr = 0; gr < BUF; ++gr) load(gr, gr);
+#pragma unroll
+    for (int gr = 0; gr < NG; ++gr) {
+#pragma unroll
+        for (int d = 0; d < G; ++d)
+#pragma unroll
+            for (int i = 0; i < NB; ++i)
+#pragma unroll
+                for (int j = 0; j < NT; ++j)
+                    acc[i][j] = W_FIRST ? mfma32(as_bf16x8(wf[gr % BUF][d][j]), as_bf16x8(af[gr % BUF][d][i]), acc[i][j])
+                                        : mfma32(as_bf16x8(af[gr % BUF][d][i]), as_bf16x8(wf[gr % BUF][d][j]), acc[i][j]);
+        __builtin_amdgcn_sched_barrier(0);
+        if (gr + BUF < NG) load(gr + BUF, gr % BUF);
+    }
+}
+
+struct SplitGrid {
+    int row_tiles, inner, deal;  // deal: row tiles belong to XCDs (their x, U and y meet in one L2)
+};
+__device__ __forceinline__ bool split_index(const SplitGrid& gr, int bid, int& rt, int& in)
+{
+    const int seq = gr.deal ? bid >> 3 : bid;
+    rt = gr.deal ? (seq / gr.inner) * 8 + (bid & 7) : seq / gr.inner;
+    in = seq % gr.inner;
+    return rt < gr.row_tiles;
+}
+
+// Step 1 for one workgroup: Y1 of 32 * NB rows, block kk, NT column tiles of 32.  The four waves share out the contraction, so that
+// every byte of x and R the workgroup needs is loaded once, and add up their tiles through LDS (4 * NB * NT * 4 KiB).
+// DIRECT: W is R as it is (read in 16-byte pieces of its rows, like x), else the packed copy RF1.  NATURAL: out[b][kk*Q + j], else
+// the order the packed L contracts, out[b][j/4][kk][j%4].
+template <int NB, int NT, int NG, int AHEAD, bool DIRECT, bool NATURAL>
+__device__ __forceinline__ void split_stage1(const uint16_t* __restrict__ x, const uint16_t* __restrict__ W, uint16_t* __restrict__ U,
+                                             int64_t B, int P, int Q, const SplitGrid& gr, int bid, f32x4* part)
+{
+    int rt, in;
+    if (!split_index(gr, bid, rt, in)) return;
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, g = lane >> 5;
+    const int QT = Q / 32, groups = gr.inner / 4;
+    const int kk = in / groups, jt0 = (in % groups) * NT;
+    const int64_t b0 = (int64_t)rt * 32 * NB;
+    const int rows = B - b0 < 32 * NB ? (int)(B - b0) : 32 * NB;
+    const int T = P / 16, lo = T * wave / 4, hi = T * (wave + 1) / 4;
+
+    f32x16 acc[NB][NT];
+    uint32_t a_at[NB], w_at[NT];
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+#pragma unroll
+    for (int i = 0; i < NB; ++i) a_at[i] = i * 32 + ln < rows ? (uint32_t)(((i * 32 + ln) * 4 * P + 16 * lo + 8 * g) * 2) : kNowhere;
+#pragma unroll
+    for (int j = 0; j < NT; ++j)
+        w_at[j] = jt0 + j >= QT ? kNowhere
+                : DIRECT ? (uint32_t)((((jt0 + j) * 32 + ln) * P + 16 * lo + 8 * g) * 2) : (uint32_t)((lo * QT + jt0 + j) * 1024 + lane * 16);
+    tile_product<NB, NT, NG, AHEAD, true>(x + b0 * 4 * P + kk * P, a_at, W + (size_t)kk * Q * P, w_at,
+                                          DIRECT ? 32u : (uint32_t)QT * 1024, hi - lo, acc);
+
+    // wave w keeps the four columns j = 8 * w + 4 * g .. of every tile
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+                part[(((wave * NB + i) * NT + j) * 4 + q4) * 64 + lane] =
+                    f32x4{acc[i][j][4 * q4], acc[i][j][4 * q4 + 1], acc[i][j][4 * q4 + 2], acc[i][j][4 * q4 + 3]};
+    lds_barrier();
+#pragma unroll
+    for (int i = 0; i < NB; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j) {
+            f32x4 v = part[((i * NT + j) * 4 + wave) * 64 + lane];
+#pragma unroll
+            for (int o = 1; o < 4; ++o) {
+                const f32x4 t = part[(((o * NB + i) * NT + j) * 4 + wave) * 64 + lane];
+#pragma unroll
+                for (int e = 0; e < 4; ++e) v[e] += t[e];
+            }
+            const int row = i * 32 + ln, col = (jt0 + j) * 32 + 8 * wave + 4 * g;
+            if (row < rows && jt0 + j < QT)
+                *reinterpret_cast<u32x2*>(U + (b0 + row) * 4 * Q + (NATURAL ? kk * Q + col : (col >> 2) * 16 + kk * 4)) =
+                    u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        }
+}
+
+inline SplitGrid split_grid(int64_t B, int rows, int inner, unsigned* blocks)
+{
+    const int tiles = (int)((B + rows - 1) / rows), even = (tiles + 7) / 8 * 8;
+    SplitGrid gr{tiles, inner, 5 * even <= 6 * tiles};
+    *blocks = (unsigned)((gr.deal ? even : tiles) * inner);
+    return gr;
+}
+
+}  // namespace
+}  // namespace monarch

@@ -46,3 +46,40 @@ def test_short_batch_forward(case):
     check("gelu", act, activation.gelu(oracle.fwd_bias(x, R, L, bias)))
     _, act2 = B.monarch_fwd_bias_gelu(xd, Rd, Ld, bd, want_pre=False, workspace=ws)
     assert torch.equal(act, act2)
+
+
+# B, p, q, s: short-batch backward at the edges of its tiles, of its step counts (s = 1024 .. 32) and of its row limits
+BWD = [(1, 96, 96, 384), (33, 384, 96, 96), (4096, 32, 32, 64), (63, 64, 64, 64), (2559, 128, 128, 128), (97, 512, 128, 128), (545, 192, 192, 576),
+       (65, 192, 192, 768), (31, 768, 192, 192), (130, 256, 256, 1024), (290, 1024, 256, 256)]
+
+
+@pytest.mark.parametrize("case", BWD, ids=str)
+def test_short_batch_backward(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, p, q, s = case
+    sh = synth.Shape("bsplit_%s" % (case,), "bf16", rows, 4, p, q, s, config=600 + parity_util.stable_seed(str(case)))
+    x, R, L, dy = synth.make_inputs(sh)
+    pre = synth.quantize(synth.normal(79, (rows, sh.n_in)), "bf16")
+    xd, Rd, Ld, dyd, pred = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L, dy, pre))
+    want = oracle.bwd_bias(dy, x, R, L)
+
+    def check(name, got, want):
+        parity_util.check("%s.%s" % (sh.name, name), got.float().cpu().numpy(), want, 2e-2)
+
+    need = B.monarch_bwd_workspace_bytes(rows, sh.n_in, 4, q, s, 1)
+    ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")
+    got = B.monarch_bwd_bias(dyd, xd, Rd, Ld, workspace=ws)
+    for name, g, w in zip(("dx", "dR", "dL", "dbias"), got, want):
+        check(name, g, w)
+    again = B.monarch_bwd_bias(dyd, xd, Rd, Ld, workspace=ws)
+    assert all(torch.equal(a, b) for a, b in zip(got, again))
+    for name, g, w in zip(("dx32", "dR32", "dL32"), B.monarch_bwd(dyd, xd, Rd, Ld, workspace=ws, flags=B.MONARCH_FLAG_WGRAD_F32), want):
+        check(name, g, w)
+    act = B.monarch_bwd_bias_gelu_in(dyd, xd, pred, Rd, Ld, workspace=ws)
+    check("dx_pre", act[0], want[0] * activation.gelu_grad(pre))
+    assert all(torch.equal(a, b) for a, b in zip(got[1:], act[1:]))
+    _, saved = B.monarch_fwd_save(xd, Rd, Ld)
+    for name, g, w in zip(("dx_s", "dR_s", "dL_s"), B.monarch_bwd_saved(dyd, xd, saved, Rd, Ld), want):
+        check(name, g, w)
