@@ -219,9 +219,9 @@ int monarch_bwd_bias_gelu_in(const void* dy, const void* x, const void* x_pre,
  * also writes that vector into `saved` (monarch_saved_bytes(...) bytes, device memory, 16-byte
  * aligned, caller-owned, contents opaque); monarch_bwd_saved is monarch_bwd_bias that reads it from
  * there and skips the recompute.  x is still needed (dR).  `saved` must come from monarch_fwd_save
- * with the same x, R, L, shape and flags.  For shapes whose kernels have no such path
- * monarch_saved_bytes returns 0, `saved` may be NULL and the two calls are monarch_fwd_ex and
- * monarch_bwd_bias exactly; a NULL `saved` in monarch_bwd_saved always means "recompute".
+ * or monarch_fwd_bias_save with the same x, R, L, shape and flags.  For shapes whose kernels have no
+ * such path monarch_saved_bytes returns 0, `saved` may be NULL and the two calls are monarch_fwd_ex
+ * and monarch_bwd_bias exactly; a NULL `saved` in monarch_bwd_saved always means "recompute".
  * Errors as the calls they extend; a missing, misaligned or short `saved` buffer is
  * MONARCH_ERR_WORKSPACE. */
 size_t monarch_saved_bytes(int64_t batch, int n_in, int k, int q, int s,
@@ -230,6 +230,12 @@ int monarch_fwd_save(const void* x, const void* R, const void* L, void* y,
                      void* saved, size_t saved_bytes,
                      int64_t batch, int n_in, int k, int q, int s,
                      monarch_dtype dtype, void* stream, unsigned flags);
+/* monarch_fwd_save of the affine layer, y = x M^T + bias (bias as in monarch_fwd_bias; NULL: monarch_fwd_save).  With a
+ * bias, MONARCH_ERR_UNSUPPORTED for the shapes whose monarch_saved_bytes is 0. */
+int monarch_fwd_bias_save(const void* x, const void* R, const void* L, const void* bias, void* y,
+                          void* saved, size_t saved_bytes,
+                          int64_t batch, int n_in, int k, int q, int s,
+                          monarch_dtype dtype, void* stream, unsigned flags);
 int monarch_bwd_saved(const void* dy, const void* x, const void* saved, size_t saved_bytes,
                       const void* R, const void* L,
                       void* dx, void* dR, void* dL, void* dbias,

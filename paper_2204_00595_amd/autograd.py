@@ -1,7 +1,7 @@
 """torch.autograd glue for the library: no arithmetic here, only which C-ABI call runs when.
 
-``monarch_linear(x, R, L, bias)`` is differentiable: its forward is ``monarch_fwd_bias`` (or, without a
-bias and with ``save_intermediate=True``, ``monarch_fwd_save``), its backward ``monarch_bwd_bias`` /
+``monarch_linear(x, R, L, bias)`` is differentiable: its forward is ``monarch_fwd_bias`` (or, with
+``save_intermediate=True`` and where it pays, ``monarch_fwd_bias_save``), its backward ``monarch_bwd_bias`` /
 ``monarch_bwd_saved``.  ``MonarchLinear`` holds the two factors (and the bias) as parameters.  Leading
 dimensions of ``x`` are flattened into the batch.  The autograd node is native (``csrc/monarch_torch.cpp``).
 Everything runs in the HIP kernels; there is no fallback for CPU tensors.

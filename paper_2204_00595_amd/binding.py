@@ -34,7 +34,7 @@ EXPORTS = (
     "monarch_fwd", "monarch_fwd_ex", "monarch_fwd_ws", "monarch_fwd_static", "monarch_fwd_bias", "monarch_fwd_workspace_bytes", "monarch_bwd",
     "monarch_bwd_bias", "monarch_fwd_bias_gelu", "monarch_bwd_bias_gelu_in",
     "monarch_bwd_workspace_bytes",
-    "monarch_fwd_t", "monarch_fwd_t_workspace_bytes", "monarch_saved_bytes", "monarch_fwd_save", "monarch_bwd_saved", "monarch_fwd_c64", "monarch_fwd_h_c64", "monarch_bwd_c64", "monarch_fwd_c64_ws", "monarch_fwd_h_c64_ws", "monarch_bwd_c64_ws", "monarch_c64_workspace_bytes", "monarch_dft_factors", "monarch_to_dense", "monarch_project", "monarch_kernel_name", "monarch_status_string", "monarch_version", "monarch_stream_copy", "monarch_launch_probe",
+    "monarch_fwd_t", "monarch_fwd_t_workspace_bytes", "monarch_saved_bytes", "monarch_fwd_save", "monarch_fwd_bias_save", "monarch_bwd_saved", "monarch_fwd_c64", "monarch_fwd_h_c64", "monarch_bwd_c64", "monarch_fwd_c64_ws", "monarch_fwd_h_c64_ws", "monarch_bwd_c64_ws", "monarch_c64_workspace_bytes", "monarch_dft_factors", "monarch_to_dense", "monarch_project", "monarch_kernel_name", "monarch_status_string", "monarch_version", "monarch_stream_copy", "monarch_launch_probe",
 )
 
 _lib = None
@@ -88,6 +88,8 @@ def lib() -> ctypes.CDLL:
         L.monarch_saved_bytes.argtypes = [i64, ci, ci, ci, ci, ci, cu]
         L.monarch_fwd_save.restype = ci
         L.monarch_fwd_save.argtypes = [vp, vp, vp, vp, vp, sz, i64, ci, ci, ci, ci, ci, vp, cu]
+        L.monarch_fwd_bias_save.restype = ci
+        L.monarch_fwd_bias_save.argtypes = [vp, vp, vp, vp, vp, vp, sz, i64, ci, ci, ci, ci, ci, vp, cu]
         L.monarch_bwd_saved.restype = ci
         L.monarch_bwd_saved.argtypes = [vp, vp, vp, sz, vp, vp, vp, vp, vp, vp, i64, ci, ci, ci, ci, ci, vp, vp, sz, cu]
         L.monarch_fwd_c64.restype = ci
@@ -281,7 +283,15 @@ def monarch_fwd_save(x: torch.Tensor, R: torch.Tensor, L: torch.Tensor, y: torch
                      saved: torch.Tensor | None = None, flags: int = 0, stream=None):
     """(y, saved): y = x M^T, and the buffer monarch_bwd_saved reads instead of recomputing (None when
     the shape has no such path)."""
-    return _native_calls.fwd_save(x, R, L, y, saved, flags, stream)
+    return _native_calls.fwd_save(x, R, L, None, y, saved, flags, stream)
+
+
+def monarch_fwd_bias_save(x: torch.Tensor, R: torch.Tensor, L: torch.Tensor, bias: torch.Tensor, y: torch.Tensor | None = None,
+                          saved: torch.Tensor | None = None, flags: int = 0, stream=None):
+    """(y, saved) of the affine layer, y = x M^T + bias (saved is None when the shape has no such path)."""
+    if bias is None:
+        raise TypeError("bias must be a tensor")
+    return _native_calls.fwd_save(x, R, L, bias, y, saved, flags, stream)
 
 
 def monarch_bwd_saved(dy: torch.Tensor, x: torch.Tensor, saved: torch.Tensor | None, R: torch.Tensor, L: torch.Tensor,

@@ -347,16 +347,25 @@ size_t monarch_saved_bytes(int64_t batch, int n_in, int k, int q, int s, monarch
 int monarch_fwd_save(const void* x, const void* R, const void* L, void* y, void* saved, size_t saved_bytes,
                      int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, void* stream, unsigned flags)
 {
+    return monarch_fwd_bias_save(x, R, L, nullptr, y, saved, saved_bytes, batch, n_in, k, q, s, dtype, stream, flags);
+}
+
+int monarch_fwd_bias_save(const void* x, const void* R, const void* L, const void* bias, void* y, void* saved, size_t saved_bytes,
+                          int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, void* stream, unsigned flags)
+{
     const size_t need = monarch_saved_bytes(batch, n_in, k, q, s, dtype, flags);
-    if (need == 0) return monarch_fwd_ex(x, R, L, y, batch, n_in, k, q, s, dtype, stream, flags);
+    if (need == 0 && !bias) return monarch_fwd_ex(x, R, L, y, batch, n_in, k, q, s, dtype, stream, flags);
     Problem pb;
     int rc = make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags);
     if (rc) return rc;
     if (flags & (MONARCH_FLAG_WGRAD_F32 | MONARCH_FLAG_WS_PACKED)) return MONARCH_ERR_INVALID;
     if (!R || !L || ((!x || !y) && batch > 0)) return MONARCH_ERR_INVALID;
     if (!aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(y, 16)) return MONARCH_ERR_INVALID;
+    if (!aligned(bias, 16)) return MONARCH_ERR_INVALID;
+    if (need == 0) return MONARCH_ERR_UNSUPPORTED;
     if (!saved || saved_bytes < need || !aligned(saved, 16)) return MONARCH_ERR_WORKSPACE;
     if (batch == 0) return MONARCH_OK;
+    pb.bias = bias;
     if (fwd_uses_ops(pb)) return ops_fwd(pb, x, R, L, y, saved, (hipStream_t)stream);
     pb.saved = saved;
     return mfma_fwd(pb, x, R, L, y, (hipStream_t)stream);

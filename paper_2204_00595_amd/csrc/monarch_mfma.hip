@@ -91,8 +91,8 @@ bool mfma_fwd_fuses_bias(const Problem& pb, bool with_ws)
 {
     if (with_ws && fwd_packed(pb)) return true;
     if (with_ws && sq64_supported(pb)) return false;
-    // mfma_fwd's order of preference: wide, sq64 (no bias epilogue), then sq16 and the shape-generic kernel (both have one)
-    return !fwd_wide_supported(pb) && !sq64_supported(pb) && (sq16_supported(pb) || tiled_fwd_supported(pb));
+    // of mfma_fwd's kernels all but sq64 have a bias epilogue
+    return fwd_wide_supported(pb) || (!sq64_supported(pb) && (sq16_supported(pb) || tiled_fwd_supported(pb)));
 }
 
 bool mfma_bwd_fuses_dbias(const Problem& pb) { return bwd_split_preferred(pb) || bwd_wide_supported(pb); }

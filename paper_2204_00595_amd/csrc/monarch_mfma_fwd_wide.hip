@@ -121,11 +121,26 @@ __device__ __forceinline__ int unit_piece_off(int ln, int piece)
     return bi * 512 + r * 64 + 8 * (piece ^ r ^ (bi & 1));
 }
 
+// the bias (a uniform pointer) on a lane's four outputs y[row][4*l .. 4*l+3] of every row, before the rounding
+template <int K>
+__device__ __forceinline__ void add_bias(const uint16_t* __restrict__ bias, int l, f32x16* acc)
+{
+    static_assert(K == 4, "one 8-byte piece");
+    const u32x2 bb = *reinterpret_cast<const u32x2*>(bias + (size_t)l * K);
+    const float bv[K] = {__uint_as_float(bb[0] << 16), __uint_as_float(bb[0] & 0xffff0000u), __uint_as_float(bb[1] << 16),
+                         __uint_as_float(bb[1] & 0xffff0000u)};
+#pragma unroll
+    for (int c = 0; c < K; ++c)
+#pragma unroll
+        for (int e = 0; e < 16; ++e) acc[c][e] += bv[c];
+}
+
 // Stage 2 on full-line units (Q % 64 == 0 and room for the ring).  One pass of one wave:
 // work units u0 .. u0+UPW-1, work unit w = (l tile w / 2, row tile w % 2).
 template <typename C, bool ODD>
 __device__ __forceinline__ void stage2_pass_lines(const uint16_t* __restrict__ L, const uint16_t* y1s, uint16_t* stg,
-                                                  uint16_t* __restrict__ y, int64_t b0, int64_t B, int u0, int lane)
+                                                  const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, int64_t b0, int64_t B,
+                                                  int u0, int lane)
 {
     constexpr int UPW = C::UPW, K = 4, NLT = C::NLT, RD = C::D2;
     constexpr int TQ64 = C::Q / 64;
@@ -222,6 +237,7 @@ __device__ __forceinline__ void stage2_pass_lines(const uint16_t* __restrict__ L
     for (int i = 0; i < UPW; ++i) {
         const int ww = i + (ODD ? 1 : 0);
         const int l = (lt_lo + (ww >> 1)) * 32 + ln;
+        if (bias) add_bias<K>(bias, l, &acc[i * K]);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int64_t row = b0 + (ww & 1) * 32 + 8 * (e / 4) + 4 * g + (e % 4);
@@ -237,7 +253,8 @@ __device__ __forceinline__ void stage2_pass_lines(const uint16_t* __restrict__ L
 // unit u = (l tile u / 2, row tile u % 2).
 template <typename C, bool ODD>
 __device__ __forceinline__ void stage2_pass(const uint16_t* __restrict__ L, const uint16_t* y1s, uint16_t* stg,
-                                            uint16_t* __restrict__ y, int64_t b0, int64_t B, int u0, int lane)
+                                            const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, int64_t b0, int64_t B,
+                                            int u0, int lane)
 {
     constexpr int UPW = C::UPW, K = 4;
     const int ln = lane & 31, g = lane >> 5;
@@ -329,6 +346,7 @@ __device__ __forceinline__ void stage2_pass(const uint16_t* __restrict__ L, cons
     for (int i = 0; i < UPW; ++i) {
         const int uu = i + (ODD ? 1 : 0);
         const int l = (lt_lo + (uu >> 1)) * 32 + ln;
+        if (bias) add_bias<K>(bias, l, &acc[i * K]);
 #pragma unroll
         for (int e = 0; e < 16; ++e) {
             const int64_t row = b0 + (uu & 1) * 32 + 8 * (e / 4) + 4 * g + (e % 4);
@@ -345,7 +363,8 @@ __device__ __forceinline__ void stage2_pass(const uint16_t* __restrict__ L, cons
 template <typename C, bool SAVE>
 __global__ void __launch_bounds__(256)
 fwd_wide_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R,
-                const uint16_t* __restrict__ L, uint16_t* __restrict__ y, uint16_t* __restrict__ saved, int64_t B)
+                const uint16_t* __restrict__ L, const uint16_t* __restrict__ bias, uint16_t* __restrict__ y,
+                uint16_t* __restrict__ saved, int64_t B)
 {
     extern __shared__ __attribute__((aligned(1024))) uint16_t lds[];
     const int tid = threadIdx.x;
@@ -464,14 +483,14 @@ fwd_wide_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R,
             const int u0 = (ps * 4 + wave) * C::UPW;
             if constexpr (C::S2_LINES) {
                 if (u0 & 1)
-                    stage2_pass_lines<C, true>(L, lds, stg, y, b0, B, u0, lane);
+                    stage2_pass_lines<C, true>(L, lds, stg, bias, y, b0, B, u0, lane);
                 else
-                    stage2_pass_lines<C, false>(L, lds, stg, y, b0, B, u0, lane);
+                    stage2_pass_lines<C, false>(L, lds, stg, bias, y, b0, B, u0, lane);
             } else {
                 if (u0 & 1)
-                    stage2_pass<C, true>(L, lds, stg, y, b0, B, u0, lane);
+                    stage2_pass<C, true>(L, lds, stg, bias, y, b0, B, u0, lane);
                 else
-                    stage2_pass<C, false>(L, lds, stg, y, b0, B, u0, lane);
+                    stage2_pass<C, false>(L, lds, stg, bias, y, b0, B, u0, lane);
             }
         }
     }
@@ -517,7 +536,8 @@ int launch(const Problem& pb, const void* x, const void* R, const void* L, void*
     const int64_t grid = (pb.B + C::BM - 1) / C::BM;
     if (grid > 0x7fffffffLL) return -2;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid, (unsigned)pass_split(grid, C::PASSES)), dim3(256), C::LDS_BYTES, st,
-                       (const uint16_t*)x, (const uint16_t*)R, (const uint16_t*)L, (uint16_t*)y, (uint16_t*)pb.saved, pb.B);
+                       (const uint16_t*)x, (const uint16_t*)R, (const uint16_t*)L, (const uint16_t*)pb.bias, (uint16_t*)y,
+                       (uint16_t*)pb.saved, pb.B);
     return hip_status(hipGetLastError());
 }
 

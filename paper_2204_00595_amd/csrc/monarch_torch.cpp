@@ -248,21 +248,23 @@ Tensor fwd_t(const Tensor& x, const Tensor& R, const Tensor& L, Tensor y, Tensor
 struct Saved {
     Tensor y, saved;
 };
-Saved fwd_save(const Tensor& x, const Tensor& R, const Tensor& L, Tensor y, Tensor saved, unsigned flags, const StreamArg& st)
+Saved fwd_save(const Tensor& x, const Tensor& R, const Tensor& L, const Tensor& bias, Tensor y, Tensor saved, unsigned flags,
+               const StreamArg& st)
 {
     const Shape sh(x, R, L);
     const Where w(sh, st);
     check(x, "x", {sh.B, sh.n_in()}, sh.dtype, sh.device);
     sh.check_factors(R, L);
+    if (bias.defined()) check(bias, "bias", {sh.n_out()}, sh.dtype, sh.device);
     y = out(y, "y", {sh.B, sh.n_out()}, sh.dtype, sh.device);
     const size_t need = monarch_saved_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
     // nothing to save for this shape: the forward that has a workspace (fp32, k = 64 blocks of 64, 12000 rows: 6050 us without
     // one, which is the SIMT kernels there, 290 with)
-    if (!need) return Saved{fwd_layer("monarch_fwd_save", x, R, L, {}, Act::none, {}, false, y, {}, flags, st).y, Tensor()};
+    if (!need) return Saved{fwd_layer("monarch_fwd_save", x, R, L, bias, Act::none, {}, false, y, {}, flags, st).y, Tensor()};
     if (!saved.defined()) saved = make({(int64_t)need}, at::kByte, sh.device);
     const Bytes b(saved);
-    const int rc = monarch_fwd_save(ptr(x), ptr(R), ptr(L), ptr(y), b.p, b.n, sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s,
-                                    sh.code(), w.stream(), flags);
+    const int rc = monarch_fwd_bias_save(ptr(x), ptr(R), ptr(L), ptr(bias), ptr(y), b.p, b.n, sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q,
+                                         (int)sh.s, sh.code(), w.stream(), flags);
     if (rc) raise_status(rc, "monarch_fwd_save");
     return Saved{y, saved};
 }
@@ -386,9 +388,20 @@ Grads c64_bwd(bool with_ws, const Tensor& dy, const Tensor& x, const Tensor& R, 
 
 // ---- autograd ----
 
-// y = x M^T (+ bias).  Without a bias the forward can keep the vector between the factors for the backward
-// (save_intermediate), else the backward recomputes it.
+// y = x M^T (+ bias).  The forward can keep the vector between the factors for the backward (save_intermediate), else the
+// backward recomputes it.
 struct LinearFn : torch::autograd::Function<LinearFn> {
+    // Where keeping the vector pays, by the GPU time of a training step with bias, recomputed and kept: fp32 and odd blocks always
+    // (192 x 192, four blocks, fp32, 12608 rows: one contraction of 53 us of 400 less).  The bf16 layers of four blocks that are
+    // multiples of 64 have other forwards for the call that keeps nothing: short batches are faster on those (256 x 1024, 200 rows
+    // 49 and 73 us, 1000 rows 80 and 89; 2500 rows 153 and 126), and so are wide outputs over long batches (192 x 768: 7000 rows
+    // 115 and 112, 16384 rows 174 and 180; 768 x 192: 182 and 158).
+    static bool keeps(const Tensor& x, const Tensor& R, const Tensor& L)
+    {
+        const int64_t rows = x.size(0), p = R.size(2), q = R.size(1), s = L.size(1);
+        if (x.scalar_type() != at::kBFloat16 || R.size(0) != 4 || p % 64 || q % 64 || s % 64) return true;
+        return rows > 2048 && (s <= p || rows <= 8192);
+    }
     static Tensor rows_of(const Tensor& t, int64_t width)
     {
         if (t.dim() == 2 && t.is_contiguous()) return t;
@@ -401,8 +414,8 @@ struct LinearFn : torch::autograd::Function<LinearFn> {
         const Tensor x2 = rows_of(x, R.size(0) * R.size(2));
         const StreamArg current;
         Saved r;
-        if (bias.has_value()) r.y = fwd_layer("monarch_fwd_bias", x2, R, L, *bias, Act::none, {}, false, {}, {}, 0, current).y;
-        else if (save_intermediate) r = fwd_save(x2, R, L, {}, {}, 0, current);
+        if (save_intermediate && keeps(x2, R, L)) r = fwd_save(x2, R, L, bias.value_or(Tensor()), {}, {}, 0, current);
+        else if (bias.has_value()) r.y = fwd_layer("monarch_fwd_bias", x2, R, L, *bias, Act::none, {}, false, {}, {}, 0, current).y;
         else r.y = fwd_layer("monarch_fwd_ws", x2, R, L, {}, Act::none, {}, false, {}, {}, 0, current).y;
         ctx->save_for_backward({x2, R, L, r.saved});
         if (bias.has_value()) ctx->saved_data["bias"] = true;
@@ -514,12 +527,12 @@ MONARCH_CALL(py_fwd_t, 7)
     return THPVariable_Wrap(unlocked([&] { return fwd_t(x, R, L, y, ws, flags, st); }));
 MONARCH_END
 
-MONARCH_CALL(py_fwd_save, 7)
-    const Tensor x = tensor_arg(a[0], "x"), R = tensor_arg(a[1], "R"), L = tensor_arg(a[2], "L"), y = optional_arg(a[3], "y"),
-                 saved = optional_arg(a[4], "saved");
-    const unsigned flags = flags_arg(a[5]);
-    const StreamArg st = stream_arg(a[6]);
-    const Saved r = unlocked([&] { return fwd_save(x, R, L, y, saved, flags, st); });
+MONARCH_CALL(py_fwd_save, 8)
+    const Tensor x = tensor_arg(a[0], "x"), R = tensor_arg(a[1], "R"), L = tensor_arg(a[2], "L"), bias = optional_arg(a[3], "bias"),
+                 y = optional_arg(a[4], "y"), saved = optional_arg(a[5], "saved");
+    const unsigned flags = flags_arg(a[6]);
+    const StreamArg st = stream_arg(a[7]);
+    const Saved r = unlocked([&] { return fwd_save(x, R, L, bias, y, saved, flags, st); });
     return tuple_of({r.y, r.saved});
 MONARCH_END
 

@@ -51,3 +51,32 @@ def test_every_call_on_the_shape_generic_kernels(case, dtype, reading):
         check(name, a, w)
         check(name + "_saved", b, w)
         assert torch.equal(a, b) or saved is None, name   # fixed summation order
+
+
+# shape-generic fp32 and bf16, and the fused bf16 forward with and without full tiles of 64 rows and whole passes of l tiles
+@pytest.mark.parametrize("case", [(65, 4, 49, 33, 64, "f32"), (300, 3, 49, 49, 50, "bf16"), (1, 4, 64, 64, 128, "bf16"), (2051, 4, 192, 192, 576, "bf16"),
+                                  (2500, 4, 128, 64, 64, "bf16"), (97, 4, 1024, 256, 256, "bf16")], ids=str)
+def test_forward_with_bias_that_keeps_the_vector(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import autograd
+    from paper_2204_00595_amd import binding as B
+    *dims, dtype = case
+    sh = synth.Shape("keep_%s" % (case,), dtype, *dims, config=700 + parity_util.stable_seed(str(case)))
+    x, R, L, dy = synth.make_inputs(sh)
+    bias = synth.quantize(synth.normal(79, (sh.n_out,)), dtype)
+    xd, Rd, Ld, dyd, bd = (_dev(a, dtype) for a in (x, R, L, dy, bias))
+    want = (oracle.fwd_bias(x, R, L, bias), *oracle.bwd_bias(dy, x, R, L))
+    y, saved = B.monarch_fwd_bias_save(xd, Rd, Ld, bd)
+    assert saved is not None
+    got = (y, *B.monarch_bwd_saved(dyd, xd, saved, Rd, Ld, want_dbias=True))
+    layer = autograd.MonarchLinear(sh.n_in, sh.n_out, nblocks=sh.k, q=sh.q, device="cuda", dtype=xd.dtype)
+    with torch.no_grad():
+        for par, value in ((layer.R, Rd), (layer.L, Ld), (layer.bias, bd)):
+            par.copy_(value)
+    xg = xd.clone().requires_grad_(True)
+    out = layer(xg)
+    out.backward(dyd)
+    for name, a, b, w in zip(("y", "dx", "dR", "dL", "dbias"), got, (out, xg.grad, layer.R.grad, layer.L.grad, layer.bias.grad), want):
+        parity_util.check("%s.%s" % (sh.name, name), a.float().cpu().numpy(), w, TOL[dtype])
+        parity_util.check("%s.layer.%s" % (sh.name, name), b.detach().float().cpu().numpy(), w, TOL[dtype])
