@@ -222,8 +222,8 @@ int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* save
     hipStream_t st = (hipStream_t)stream;
     if (dbias) {
         void* cws = (char*)workspace + bwd_kernel_need(pb, fam);
-        if (batch > 0 && fam == FAM_MFMA && mfma_bwd_fuses_dbias(pb)) {
-            pb.dbias = dbias;  // computed at the tail of the backward's own launches
+        if (batch > 0 && (fam == FAM_OPS || (fam == FAM_MFMA && mfma_bwd_fuses_dbias(pb)))) {
+            pb.dbias = dbias;  // computed with the backward's own launches
             pb.colsum_ws = cws;
         } else {
             rc = launch_colsum(pb, dy, dbias, cws, st);

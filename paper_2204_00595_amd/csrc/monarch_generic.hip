@@ -321,8 +321,17 @@ int launch_colsum(const Problem& pb, const void* dy, void* dbias, void* ws, hipS
         return launch_fill_zero_u16((uint16_t*)dbias, n_out, st);
     }
     const ColsumJob cj = make_colsum_job(pb, dy, dbias, ws);
+    if (int rc = launch_colsum_partial(pb, cj, st)) return rc;
+    const dim3 g2((unsigned)colsum_final_blocks(cj));
+    if (cj.out_f32) hipLaunchKernelGGL(colsum_final_kernel<float>, g2, dim3(1024), 0, st, cj);
+    else hipLaunchKernelGGL(colsum_final_kernel<bf16_t>, g2, dim3(1024), 0, st, cj);
+    return hip_status(hipGetLastError());
+}
+
+int launch_colsum_partial(const Problem& pb, const ColsumJob& cj, hipStream_t st)
+{
     const dim3 grid((unsigned)colsum_partial_blocks(cj)), block(64 * ROWCOL_WAVES);
-    const bool cw4 = rowcol_cw(n_out) == 4;
+    const bool cw4 = rowcol_cw(cj.n_out) == 4;
     if (pb.dtype == 0) {
         if (cw4) hipLaunchKernelGGL((colsum_partial_kernel<float, 4>), grid, block, 0, st, cj);
         else hipLaunchKernelGGL((colsum_partial_kernel<float, 1>), grid, block, 0, st, cj);
@@ -330,10 +339,6 @@ int launch_colsum(const Problem& pb, const void* dy, void* dbias, void* ws, hipS
         if (cw4) hipLaunchKernelGGL((colsum_partial_kernel<bf16_t, 4>), grid, block, 0, st, cj);
         else hipLaunchKernelGGL((colsum_partial_kernel<bf16_t, 1>), grid, block, 0, st, cj);
     }
-    if (hipGetLastError() != hipSuccess) return -4;
-    const dim3 g2((unsigned)colsum_final_blocks(cj));
-    if (cj.out_f32) hipLaunchKernelGGL(colsum_final_kernel<float>, g2, dim3(1024), 0, st, cj);
-    else hipLaunchKernelGGL(colsum_final_kernel<bf16_t>, g2, dim3(1024), 0, st, cj);
     return hip_status(hipGetLastError());
 }
 

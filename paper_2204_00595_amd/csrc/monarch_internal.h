@@ -77,6 +77,7 @@ int launch_gelu_fwd(const Problem& pb, void* y, void* y_pre, hipStream_t st);
 int launch_gelu_bwd(const Problem& pb, void* dx, const void* x_pre, hipStream_t st);
 struct ColsumJob;
 ColsumJob make_colsum_job(const Problem& pb, const void* dy, void* dbias, void* ws);
+int launch_colsum_partial(const Problem& pb, const ColsumJob& cj, hipStream_t st);  // the first of its two passes
 
 // projection of a dense n x n matrix (n = m * m) onto the square Monarch matrices (monarch_project.hip)
 bool project_supported(int m);
