@@ -15,13 +15,13 @@
 //
 // What bounds it: fp32 layers the fp32 matrix cores (v_mfma_f32_32x32x2_f32, 154 TFLOP/s in a large product; a 128 x 128
 // tile needs 16 B/clk of LDS reads per CU, far below the 128 there are), small and odd bf16 layers the memory system (every
-// operand element is staged once per tile, in 2-byte pieces where nothing better is aligned).  The intermediate goes
+// operand element is staged once per tile, in 2-byte pieces where it is strided, else in 16-byte pieces wherever they start).  The intermediate goes
 // through memory (for most shapes it stays in the last-level cache): a fused kernel would hold all k blocks of a row tile,
 // which leaves the large shapes one 16-row tile per CU.
 // Measured against the SIMT kernels: 768 -> 768 fp32, k = 4, 12608 rows: forward 741 -> 96 us, backward 3570 -> 255 us (one
 // contraction of 3.7 GFLOP takes 46 to 57 us, its matrix-core floor is 24: the cores are busy 62 % of the time of a busy CU,
 // and 2.3 rounds of workgroups leave a quarter of the launch on partly filled CUs); 196 -> 256 bf16, blocks of 49 and 64,
-// 32768 rows: forward 61 -> 40 us, backward 388 -> 92 us; 4096 -> 1024 fp32, 16384 rows: 105 TFLOP/s in the data path,
+// 32768 rows: forward 61 -> 27 us, backward 388 -> 64 us (with the odd blocks in 2-byte pieces 40 and 69); 4096 -> 1024 fp32, 16384 rows: 105 TFLOP/s in the data path,
 // 92 in the weight gradients.
 #include <type_traits>
 #include "monarch_internal.h"
@@ -40,11 +40,17 @@ template <typename T> struct OpType;
 template <> struct OpType<float> { static constexpr int KC = 32, KSTEP = 8; };   // contraction indices per chunk / per MFMA group
 template <> struct OpType<bf16_t> { static constexpr int KC = 32, KSTEP = 16; };
 
+// How an operand is taken: kPieces16, 16-byte pieces along the contiguous index, all of them aligned and inside; kPiecesAny,
+// 16-byte pieces along it wherever they start (gfx950 loads from any address), a piece that crosses the limit being read from
+// the elements that end there and shifted into place on its way to LDS; kElements, single elements at any stride (fp32: a dword
+// per element; bf16: two 2-byte loads per dword, joined on the way to LDS so that nothing waits for them here).
+enum Take { kElements, kPiecesAny, kPieces16 };
+
 // One operand: element (g, row, k) at p[g*g_s + row*r_s + k*k_s].
 struct OpOperand {
     const void* p;
     int64_t g_s, r_s, k_s;
-    bool vec;  // 16-byte pieces along the contiguous index are aligned
+    Take take;
 };
 struct OpDesc {
     OpOperand a, b;
@@ -71,10 +77,9 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
 
 // A C x O tile of an operand (C: extent along the index with the unit or smallest stride, O: along the other one) on
 // its way from memory to LDS [o][c], row stride LSTR elements.  Elements past the limits read as zeros.
-// VEC: 16-byte pieces along c; else single elements at any stride (fp32: a dword per element; bf16: two 2-byte loads per
-// dword, joined on the way to LDS so that nothing waits for them here).
-template <typename T, int C, int O, int LSTR, bool VEC>
+template <typename T, int C, int O, int LSTR, Take TAKE>
 struct OpTile {
+    static constexpr bool VEC = TAKE != kElements;
     static constexpr int EPD = 4 / (int)sizeof(T);                   // elements per dword
     static constexpr int V = VEC ? 16 / (int)sizeof(T) : EPD;        // elements per piece
     static constexpr int PPO = C / V;                                // pieces per o
@@ -83,23 +88,30 @@ struct OpTile {
     static constexpr int kLoads = VEC ? 1 : EPD, kDwords = VEC ? 4 : EPD;
     static_assert(C % V == 0 && LSTR * sizeof(T) % 16 == 0, "tile");
     static_assert(VEC || kPieces % kThreads == 0, "element-wise tiles divide over the threads");
+    static constexpr bool kEven = kThreads % PPO == 0;  // a thread's pieces share c and step in o by a uniform amount
     uint32_t r[NP * kDwords];
+    int over[TAKE == kPiecesAny ? (kEven ? 1 : NP) : 1];  // elements of a piece past the limit
 
     __device__ __forceinline__ void fetch(const T* base, uint32_t os, uint32_t cs, int olim, int clim, int tid)
     {
-        const auto rs = buffer_at(base);
+        // the piece that ends at the limit may start before `base`, which is not the start of its row there
+        constexpr uint32_t kBack = TAKE == kPiecesAny ? 16 : 0;
+        const auto rs = buffer_at(reinterpret_cast<const char*>(base) - kBack);
         const int o0 = tid / PPO, c0 = (tid % PPO) * V;
-        const uint32_t v0 = (o0 * os + c0 * cs) * (uint32_t)sizeof(T);
+        const uint32_t v0 = (o0 * os + c0 * cs) * (uint32_t)sizeof(T) + kBack;
 #pragma unroll
         for (int n = 0; n < NP; ++n) {
-            // where the pieces of a row divide the workgroup, a thread's pieces share c and step in o by a uniform amount
-            constexpr bool kEven = kThreads % PPO == 0;
             const int idx = tid + n * kThreads;
             const int o = kEven ? o0 + n * (kThreads / PPO) : idx / PPO, c = kEven ? c0 : (idx % PPO) * V;
-            const uint32_t vo = kEven ? v0 : (o * os + c * cs) * (uint32_t)sizeof(T);
+            uint32_t vo = kEven ? v0 : (o * os + c * cs) * (uint32_t)sizeof(T) + kBack;
             const uint32_t so = kEven ? n * (kThreads / PPO) * os * (uint32_t)sizeof(T) : 0u;
             bool in = o < olim;
             if constexpr (kPieces % kThreads != 0) in = in && idx < kPieces;
+            if constexpr (TAKE == kPiecesAny) {
+                const int past = c + V > clim ? c + V - clim : 0;
+                over[kEven ? 0 : n] = past;
+                vo -= past * (uint32_t)sizeof(T);
+            }
 #pragma unroll
             for (int e = 0; e < kLoads; ++e) {
                 const uint32_t at = in && c + e < clim ? vo : kNowhere;
@@ -115,14 +127,28 @@ struct OpTile {
             }
         }
     }
+    // v without its first n elements (zeros follow); a piece with nothing inside was loaded as zeros
+    static __device__ __forceinline__ u32x4 drop(u32x4 v, int n)
+    {
+        const int bytes = n * (int)sizeof(T);
+        if (bytes & 8) v = u32x4{v[2], v[3], 0u, 0u};
+        if (bytes & 4) v = u32x4{v[1], v[2], v[3], 0u};
+        if constexpr (sizeof(T) == 2) {
+            const uint32_t s = (bytes & 2) * 8;
+            v = u32x4{__builtin_amdgcn_alignbit(v[1], v[0], s), __builtin_amdgcn_alignbit(v[2], v[1], s),
+                      __builtin_amdgcn_alignbit(v[3], v[2], s), v[3] >> s};
+        }
+        return v;
+    }
     __device__ __forceinline__ void store(T* lds, int tid) const
     {
 #pragma unroll
         for (int n = 0; n < NP; ++n) {
             const int idx = tid + n * kThreads, o = idx / PPO, c = (idx % PPO) * V;
             if constexpr (VEC) {
-                if (kPieces % kThreads == 0 || idx < kPieces)
-                    *reinterpret_cast<u32x4*>(lds + o * LSTR + c) = u32x4{r[4 * n], r[4 * n + 1], r[4 * n + 2], r[4 * n + 3]};
+                u32x4 v = {r[4 * n], r[4 * n + 1], r[4 * n + 2], r[4 * n + 3]};
+                if constexpr (TAKE == kPiecesAny) v = drop(v, over[kEven ? 0 : n]);
+                if (kPieces % kThreads == 0 || idx < kPieces) *reinterpret_cast<u32x4*>(lds + o * LSTR + c) = v;
             } else {
                 *reinterpret_cast<uint32_t*>(lds + o * LSTR + c) = EPD == 1 ? r[n] : (r[n * EPD] | (r[n * EPD + EPD - 1] << 16));
             }
@@ -206,7 +232,7 @@ struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32
 // Workgroup order: the row tile (PARTIAL: the batch chunk) is dealt to the XCDs, and the blocks and column tiles of one
 // row tile follow each other on that XCD: strided operands and outputs of the k blocks share their cache lines, which
 // then meet in one L2.
-template <typename T, class Cfg, bool RA, bool RB, bool PARTIAL, bool AV, bool BV>
+template <typename T, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
 __global__ void __launch_bounds__(kThreads, 2)
 ops_gemm_kernel(const OpDesc d0, const OpDesc d1)
 {
@@ -410,13 +436,15 @@ int launch_sum(const OpSum& s0, const OpSum& s1, const ColsumJob* cj, hipStream_
 // ---- host side ----
 
 // 16-byte pieces along the contiguous index need every other stride, the extent and the base to be multiples of a piece.
-bool pieces_aligned(const void* p, int64_t s1, int64_t s2, int64_t contiguous_stride, int64_t extent, int esize)
+// Otherwise they are taken wherever they start (no extent is shorter than a piece: blocks have at least 16 elements).
+Take take_of(const void* p, int64_t s1, int64_t s2, int64_t contiguous_stride, int64_t extent, int esize)
 {
     const int v = 16 / esize;
-    return contiguous_stride == 1 && (uintptr_t)p % 16 == 0 && s1 % v == 0 && s2 % v == 0 && extent % v == 0;
+    if (contiguous_stride != 1) return kElements;
+    return (uintptr_t)p % 16 == 0 && s1 % v == 0 && s2 % v == 0 && extent % v == 0 ? kPieces16 : kPiecesAny;
 }
 
-template <typename T, class Cfg, bool RA, bool RB, bool PARTIAL, bool AV, bool BV>
+template <typename T, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
 int launch_cfg(const OpDesc& d0, const OpDesc& d1, hipStream_t st)
 {
     constexpr int KC = OpType<T>::KC;
@@ -438,10 +466,10 @@ struct TileSize {
 constexpr int kTileSizes = 4;
 constexpr TileSize kTiles[kTileSizes] = {{128, 128}, {128, 96}, {128, 64}, {64, 64}};
 
-template <typename T, bool RA, bool RB, bool PARTIAL, bool AV, bool BV>
+template <typename T, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
 int launch_tile(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
 {
-    if constexpr (AV && BV) {
+    if constexpr (AV != kElements) {
         if (cfg == 0) return launch_cfg<T, Cfg128x128, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
         if (cfg == 1) return launch_cfg<T, Cfg128x96, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
     }
@@ -450,27 +478,32 @@ int launch_tile(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
         default: return launch_cfg<T, Cfg64x64, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
     }
 }
-// The three kinds of contraction with the piece widths that occur: A in 16-byte pieces only together with B (a strided
-// A is the rule in the backward), anything that does not fit element by element.
+// The three kinds of contraction with the ways of taking that occur: both operands in aligned pieces, both in pieces from
+// anywhere, or A element by element (it is strided in the backward, and in the forward under MONARCH_FLAG_PERM_B).
 template <typename T>
 int launch_op(bool w_rc, int cfg, const OpDesc& d, hipStream_t st)
 {
     const OpDesc none{};
-    const bool av = d.a.vec && d.b.vec;
+    const bool aligned = d.b.take == kPieces16;
     if (!w_rc) {
-        return av ? launch_tile<T, false, false, false, true, true>(cfg, d, none, st)
-                  : launch_tile<T, false, false, false, false, false>(cfg, d, none, st);
+        if (d.a.take == kElements) return launch_tile<T, false, false, false, kElements, kPiecesAny>(cfg, d, none, st);
+        return aligned && d.a.take == kPieces16 ? launch_tile<T, false, false, false, kPieces16, kPieces16>(cfg, d, none, st)
+                                                : launch_tile<T, false, false, false, kPiecesAny, kPiecesAny>(cfg, d, none, st);
     }
-    return av      ? launch_tile<T, false, true, false, true, true>(cfg, d, none, st)
-         : d.b.vec ? launch_tile<T, false, true, false, false, true>(cfg, d, none, st)
-                   : launch_tile<T, false, true, false, false, false>(cfg, d, none, st);
+    if (d.a.take == kElements) {
+        return aligned ? launch_tile<T, false, true, false, kElements, kPieces16>(cfg, d, none, st)
+                       : launch_tile<T, false, true, false, kElements, kPiecesAny>(cfg, d, none, st);
+    }
+    return aligned && d.a.take == kPieces16 ? launch_tile<T, false, true, false, kPieces16, kPieces16>(cfg, d, none, st)
+                                            : launch_tile<T, false, true, false, kPiecesAny, kPiecesAny>(cfg, d, none, st);
 }
 template <typename T>
 int launch_wgrad(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
 {
-    const bool bv = d0.b.vec && d1.b.vec;
-    return bv ? launch_tile<T, true, true, true, false, true>(cfg, d0, d1, st)
-              : launch_tile<T, true, true, true, false, false>(cfg, d0, d1, st);
+    const Take b = d0.b.take < d1.b.take ? d0.b.take : d1.b.take;
+    return b == kPieces16    ? launch_tile<T, true, true, true, kElements, kPieces16>(cfg, d0, d1, st)
+           : b == kPiecesAny ? launch_tile<T, true, true, true, kElements, kPiecesAny>(cfg, d0, d1, st)
+                             : launch_tile<T, true, true, true, kElements, kElements>(cfg, d0, d1, st);
 }
 
 int64_t tiles(int64_t n, int t) { return (n + t - 1) / t; }
@@ -508,7 +541,7 @@ void deal(OpDesc& d, int nouter, int inner)
 OpOperand operand(const void* p, int64_t g_s, int64_t r_s, int64_t k_s, bool rc, int64_t rows, int64_t K, int esize)
 {
     return OpOperand{p, g_s, r_s, k_s,
-                     rc ? pieces_aligned(p, g_s, k_s, r_s, rows, esize) : pieces_aligned(p, g_s, r_s, k_s, K, esize)};
+                     rc ? take_of(p, g_s, k_s, r_s, rows, esize) : take_of(p, g_s, r_s, k_s, K, esize)};
 }
 
 // One step of the data path: O (rows x blocks x N) = A x W per block.
@@ -529,7 +562,7 @@ int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t 
     d.K = K;
     d.N = N;
     d.G = pb.k;
-    const int cfg = pick_tile(d.M, N, d.G, d.a.vec && d.b.vec);
+    const int cfg = pick_tile(d.M, N, d.G, d.a.take != kElements);
     d.tiles_m = (int)tiles(d.M, kTiles[cfg].m);
     d.tiles_n = (int)tiles(N, kTiles[cfg].n);
     d.k_chunk = K;

@@ -14,7 +14,8 @@ pytestmark = pytest.mark.gpu
 TOL = {"f32": 1e-5, "bf16": 2e-2}
 # B, k, p, q, s
 CASES = [(1, 4, 16, 16, 16), (65, 2, 17, 16, 250), (300, 4, 49, 49, 64), (129, 3, 33, 31, 97), (1100, 1, 64, 95, 128),
-         (3000, 4, 96, 64, 160), (640, 8, 101, 37, 16), (900, 4, 192, 192, 36)]
+         (3000, 4, 96, 64, 160), (640, 8, 101, 37, 16), (900, 4, 192, 192, 36),
+         (4200, 4, 17, 16, 33), (130, 5, 33, 17, 65), (260, 1, 41, 129, 23)]   # pieces that start anywhere and end at the limit; many chunks
 
 
 def _dev(a, dtype):
