@@ -27,7 +27,14 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 constexpr int KB = 32;    // batch rows per pipeline step (two 16-row K-steps, one per wave of a group)
 constexpr int NTHR = 512;  // eight waves per workgroup
-constexpr int NSTG = 1;     // register stages of the operand loads (rows fetched NSTG steps before they are stored)
+
+// A load at this offset (past the end of the buffer, whatever is added to it) reads zeros; make_problem keeps KB rows of any
+// operand below it.
+constexpr uint32_t kNowhere = 0x80000000u;
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
+{
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffffu, 0x00020000);
+}
 
 // Padding of the LDS rows (bf16 elements).  A half wave of a transposing read touches four consecutive rows,
 // 64 bytes (16 banks) of each: with a row stride of an odd multiple of 64 bytes the four rows fall on disjoint
@@ -62,6 +69,9 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* T, int stride, int k0,
 template <int TM, int TN, bool DEINT, bool MSPLIT>
 __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int tile, const int zi)
 {
+    // register stages of the operand loads (rows fetched NSTG steps before they are stored): two for the 128 x 128 tile (feed-forward
+    // block of width 1024, 16384 rows: 82 -> 77 us in each layer); the smaller ones measured no faster with two
+    constexpr int NSTG = MSPLIT ? 2 : 1;
     constexpr int MT = TM / 32, NT = TN / 32;
     constexpr int MTW = MSPLIT ? MT / 2 : MT;  // m tiles of one wave
     static_assert(!MSPLIT || MT % 2 == 0, "row split");
@@ -84,14 +94,13 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
     const int64_t nrows = row_hi > row_lo ? row_hi - row_lo : 0;
 
     // ---- per-thread load tasks (16-byte pieces; DEINT A: 64-byte runs holding 8 m x 4 groups) ----
-    // Addresses are fixed for the whole chunk: global pointers at row_lo (advanced by a uniform row
-    // offset per step), LDS offsets inside a buffer, and the row of the task inside a step.
+    // Addresses are fixed for the whole chunk: byte offsets from the (uniform) first row of a step, LDS offsets inside a
+    // buffer, and the row of the task inside a step.
     constexpr int A_TASKS = DEINT ? (KB * TM / 8) : (4 * KB * TM / 8);
     constexpr int B_TASKS = 4 * KB * TN / 8;
     constexpr int A_PER = (A_TASKS + NTHR - 1) / NTHR, B_PER = (B_TASKS + NTHR - 1) / NTHR;
     u32x4 areg[NSTG][A_PER][DEINT ? 4 : 1], breg[NSTG][B_PER];
-    const uint16_t* pa[A_PER];
-    const uint16_t* pb[B_PER];
+    uint32_t pa[A_PER], pb[B_PER];
     int ra[A_PER], rb[B_PER], la[A_PER], lb[B_PER];
 #pragma unroll
     for (int t = 0; t < A_PER; ++t) {
@@ -101,13 +110,13 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
         if (DEINT) {
             const int r = task / (TM / 8), u = task % (TM / 8);
             ra[t] = tid + t * NTHR < A_TASKS ? r : (1 << 30);
-            pa[t] = d.A + (row_lo + r) * d.lda + (size_t)(m0 + 8 * u) * 4 + g0;
+            pa[t] = (uint32_t)(r * d.lda + (m0 + 8 * u) * 4 + g0) * 2;
             la[t] = r * SA + 8 * u;
         } else {
             const int g = task / (KB * TM / 8), rem = task % (KB * TM / 8);
             const int r = rem / (TM / 8), u = rem % (TM / 8);
             ra[t] = tid + t * NTHR < A_TASKS && g0 + g < d.G ? r : (1 << 30);  // a group past the last one: zeros
-            pa[t] = d.A + (row_lo + r) * d.lda + (size_t)(g0 + g) * d.a_g + m0 + 8 * u;
+            pa[t] = (uint32_t)(r * d.lda + (g0 + g) * d.a_g + m0 + 8 * u) * 2;
             la[t] = (g * KB + r) * SA + 8 * u;
         }
     }
@@ -118,27 +127,26 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
         const int r = rem / (TN / 8), u = rem % (TN / 8);
         const int n = n0 + 8 * u;
         rb[t] = tid + t * NTHR < B_TASKS && g0 + g < d.G ? r : (1 << 30);
-        pb[t] = d.Bm + (row_lo + r) * d.ldb + (size_t)(g0 + g) * d.b_g + (size_t)(n / d.seg_w) * d.b_seg + (n % d.seg_w);
+        pb[t] = (uint32_t)(r * d.ldb + (g0 + g) * d.b_g + (n / d.seg_w) * d.b_seg + (n % d.seg_w)) * 2;
         lb[t] = 4 * KB * SA + (g * KB + r) * SB + 8 * u;
     }
 
     // rows r0 .. r0+KB-1 of the chunk -> register stage `stg`; rows past the end of the chunk (and the
-    // slots of threads without a task) load nothing and read as zeros.  (Unconditional loads of a
-    // clamped row with the zeroing moved to store_step were measured 10 % slower.)
+    // slots of threads without a task) load nothing and read as zeros: a buffer load at an offset past the
+    // buffer's end.  A branch around each load instead makes the compiler lose count of the loads in flight
+    // and wait for all of them, which leaves no second stage.
     auto load_step = [&](int64_t r0, int stg) {
-        const int64_t oa = r0 * d.lda, ob = r0 * d.ldb;
+        const auto bufa = buffer_at(d.A + (row_lo + r0) * d.lda), bufb = buffer_at(d.Bm + (row_lo + r0) * d.ldb);
+        const int left = nrows - r0 < KB ? (int)(nrows - r0) : KB;
 #pragma unroll
         for (int t = 0; t < A_PER; ++t) {
-            const bool ok = r0 + ra[t] < nrows;
-            const uint16_t* p = pa[t] + oa;
+            const uint32_t at = ra[t] < left ? pa[t] : kNowhere;
 #pragma unroll
-            for (int w = 0; w < (DEINT ? 4 : 1); ++w) areg[stg][t][w] = ok ? ldg128(p + 8 * w) : u32x4{0, 0, 0, 0};
+            for (int w = 0; w < (DEINT ? 4 : 1); ++w) areg[stg][t][w] = __builtin_amdgcn_raw_buffer_load_b128(bufa, at, 16 * w, 0);
         }
 #pragma unroll
-        for (int t = 0; t < B_PER; ++t) {
-            const bool ok = r0 + rb[t] < nrows;
-            breg[stg][t] = ok ? ldg128(pb[t] + ob) : u32x4{0, 0, 0, 0};
-        }
+        for (int t = 0; t < B_PER; ++t)
+            breg[stg][t] = __builtin_amdgcn_raw_buffer_load_b128(bufb, rb[t] < left ? pb[t] : kNowhere, 0, 0);
     };
     // register stage -> LDS buffer
     auto store_step = [&](int64_t, int stg, uint16_t* buf) {
@@ -176,14 +184,15 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
 
     // Pipeline (one workgroup barrier per 32-row step, two LDS buffers, one register stage):
     // in step s the MFMAs read buffer s%2 while the rows of step s+1 go from registers to buffer
-    // (s+1)%2 and the rows of step s+2 are fetched into the registers just freed.  A wave reads the
+    // (s+1)%2 and the rows of step s+1+NSTG are fetched into the registers just freed.  A wave reads the
     // fragments of its own K-step (rows 16*kh .. 16*kh+15 of the step) before the staging work, so that
     // their LDS latency hides behind it.  The loop body has no branches (a step past the end of the
     // chunk works on zeros): control flow here makes the compiler shuffle the accumulators between blocks.
     if (nrows > 0) {  // (uniform) an empty chunk touches no memory and yields a zero partial tile
     load_step(0, 0);
     store_step(0, 0, lds);
-    load_step(KB, 0);
+    load_step(KB, 1 % NSTG);
+    if constexpr (NSTG == 2) load_step(2 * KB, 0);
     const int woff_a = grp * KB * SA, woff_b = 4 * KB * SA + grp * KB * SB;
     for (int64_t r0 = 0; r0 < nrows; r0 += 2 * KB) {
 #pragma unroll
@@ -195,8 +204,8 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
             const int krow = MSPLIT ? 0 : 16 * kh, mcol = MSPLIT ? kh * MTW * 32 : 0;
             if constexpr (MSPLIT) {
                 // large tiles: the next rows are requested first, so that they travel during the fragment reads too
-                store_step(r0 + (k + 1) * KB, 0, nxt);
-                load_step(r0 + (k + 2) * KB, 0);
+                store_step(r0 + (k + 1) * KB, (k + 1) % NSTG, nxt);
+                load_step(r0 + (k + 1 + NSTG) * KB, (k + 1) % NSTG);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
@@ -205,8 +214,8 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
             for (int nt = 0; nt < NT; ++nt) bfr[nt] = frag_tr(cur + woff_b, SB, krow, nt * 32, lane);
             __builtin_amdgcn_sched_barrier(0);
             if constexpr (!MSPLIT) {
-                store_step(r0 + (k + 1) * KB, 0, nxt);
-                load_step(r0 + (k + 2) * KB, 0);
+                store_step(r0 + (k + 1) * KB, (k + 1) % NSTG, nxt);
+                load_step(r0 + (k + 1 + NSTG) * KB, (k + 1) % NSTG);
                 __builtin_amdgcn_sched_barrier(0);
             }
 #pragma unroll
