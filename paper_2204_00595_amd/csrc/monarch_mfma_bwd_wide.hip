@@ -16,6 +16,7 @@
 //                  as an operand.  dY1 is also written to the workspace for dR.
 //   wgrad     dL and dR as batch-contracted GEMMs over (dy, Y1) and (dY1, x)
 //             (monarch_mfma_wgrad.hip), split over the batch, then one reduction pass.
+#include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
 #include "monarch_colsum.h"
@@ -150,46 +151,6 @@ __device__ __forceinline__ void copy_out_tile(const uint16_t* src, int stride, u
                 else *reinterpret_cast<u32x4*>(p) = v[i];
             }
         }
-    }
-}
-
-// The wave-private dx tile ([64][COLS] bf16 in LDS) goes out multiplied elementwise by gelu'(x_pre): the layer's
-// input was gelu(x_pre) and the caller wants the gradient with respect to x_pre.  Lane task i is row
-// lane / (COLS/8) + (512/COLS) * i, 16-byte piece lane % (COLS/8); `pre` holds the x_pre pieces of the same tasks
-// (fetched by load_pre_tile before the MFMA loop, so that their latency is hidden).
-template <int COLS>
-__device__ __forceinline__ void load_pre_tile(const uint16_t* pre, int64_t ld, int64_t b0, int64_t B, int lane,
-                                              u32x4 (&hp)[COLS / 8])
-{
-    constexpr int PER_ROW = COLS / 8;
-    static_assert(64 % PER_ROW == 0, "whole rows per round");
-#pragma unroll
-    for (int i = 0; i < PER_ROW; ++i) {
-        const int t = lane + i * 64;
-        int64_t row = b0 + t / PER_ROW;
-        row = row < B ? row : B - 1;  // rows past the end are read from a valid row and never stored
-        hp[i] = ldg128_nt(pre + row * ld + 8 * (t % PER_ROW));
-    }
-}
-
-template <int COLS>
-__device__ __forceinline__ void copy_out_tile_gelu(const uint16_t* src, int stride, uint16_t* dst, int64_t ld,
-                                                   int64_t b0, int64_t B, int lane, const u32x4 (&hp)[COLS / 8])
-{
-    constexpr int PER_ROW = COLS / 8;
-#pragma unroll
-    for (int i = 0; i < PER_ROW; ++i) {
-        const int t = lane + i * 64;
-        const int r = t / PER_ROW, u = t % PER_ROW;
-        const u32x4 v = lds128(src + (size_t)r * stride + 8 * u);
-        u32x4 o;
-#pragma unroll
-        for (int w = 0; w < 4; ++w) {
-            const float g0 = __uint_as_float(v[w] << 16), g1 = __uint_as_float(v[w] & 0xffff0000u);
-            const float h0 = __uint_as_float(hp[i][w] << 16), h1 = __uint_as_float(hp[i][w] & 0xffff0000u);
-            o[w] = pack_bf16x2(g0 * gelu_grad_f(h0), g1 * gelu_grad_f(h1));
-        }
-        if (b0 + r < B) stg128_nt(dst + (b0 + r) * ld + 8 * u, o);
     }
 }
 
@@ -370,17 +331,54 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
     };
 #pragma unroll
     for (int d = 0; d < NSB - 1; ++d) issue(d, d);
-    for (int ig = 0; ig < NIG; ++ig) {
+    // ACT: what leaves is multiplied by gelu'(x_pre), which costs the vector units two to three times what the tile costs the
+    // matrix cores, and a wave is alone on its SIMD: so the pieces of tile ig - 1 leave between the MFMAs of tile ig
+    // (1024 x 256, 16384 rows: 128 -> 117 us).  hp[i] holds the x_pre piece that task i multiplies by; it is replaced by the one
+    // of the next tile as soon as it is used.
+    constexpr int PIECES = C::DX_COLS / 8;
+    const auto pre_at = [&](int ig, int i) {
+        const int t = lane + i * 64;
+        int64_t row = b0 + t / PIECES;
+        row = row < B ? row : B - 1;  // rows past the end are read from a valid row and never stored
+        return x_pre + row * C::N_IN + kk * C::P + ig * C::DX_COLS + 8 * (t % PIECES);
+    };
+    const auto piece = [&](int i) {
+        const int t = lane + i * 64;
+        return lds128(stage + (size_t)(t / PIECES) * C::DX_STRIDE + 8 * (t % PIECES));
+    };
+    const auto put = [&](int ig, int i, const u32x4& v, const u32x4& h) {
+        const int t = lane + i * 64, r = t / PIECES;
+        u32x4 o;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const float g0 = __uint_as_float(v[w] << 16), g1 = __uint_as_float(v[w] & 0xffff0000u);
+            const float h0 = __uint_as_float(h[w] << 16), h1 = __uint_as_float(h[w] & 0xffff0000u);
+            o[w] = pack_bf16x2(g0 * gelu_grad_f(h0), g1 * gelu_grad_f(h1));
+        }
+        if (b0 + r < B) stg128_nt(dx + (b0 + r) * C::N_IN + kk * C::P + ig * C::DX_COLS + 8 * (t % PIECES), o);
+    };
+    u32x4 hp[ACT ? PIECES : 1];
+    if constexpr (ACT) {
+        static_assert(64 % PIECES == 0, "whole rows per round");
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) hp[i] = ldg128_nt(pre_at(0, i));
+    }
+    auto tile = [&](int ig, auto previous) {
+        constexpr bool kPrevious = ACT && decltype(previous)::value;
         f32x4 acc[C::IG * C::NBT];
 #pragma unroll
         for (int t = 0; t < C::IG * C::NBT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
-        u32x4 hp[C::DX_COLS / 8];
-        if constexpr (ACT) load_pre_tile<C::DX_COLS>(x_pre + kk * C::P + ig * C::DX_COLS, C::N_IN, b0, B, lane, hp);
 #pragma unroll
         for (int u = 0; u < U; ++u) {
             const int n = ig * U + u;
             __builtin_amdgcn_sched_barrier(0);
             if (n + NSB - 1 < NIG * U) issue(n + NSB - 1, (u + NSB - 1) % NSB);
+            const int i0 = u * PIECES / U, i1 = (u + 1) * PIECES / U;  // tasks of this step
+            u32x4 v[(PIECES + U - 1) / U];
+            if constexpr (kPrevious) {
+#pragma unroll
+                for (int i = i0; i < i1; ++i) v[i - i0] = piece(i);
+            }
             __builtin_amdgcn_sched_barrier(0);
 #pragma unroll
             for (int bt = 0; bt < C::NBT; ++bt) {
@@ -390,7 +388,15 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
                 for (int it = 0; it < C::IG; ++it)
                     acc[it * C::NBT + bt] = mfma16(as_bf16x8(af[u % NSB][it]), bfr, acc[it * C::NBT + bt]);
             }
+            if constexpr (kPrevious) {
+#pragma unroll
+                for (int i = i0; i < i1; ++i) {
+                    put(ig - 1, i, v[i - i0], hp[i]);
+                    hp[i] = ldg128_nt(pre_at(ig, i));
+                }
+            }
         }
+        if constexpr (kPrevious) wave_fence();  // the pieces of the previous tile have been read
         // D^T[i][b]: lane holds i = it*16 + 4*h + 0..3 for row b = bt*16 + l16
 #pragma unroll
         for (int it = 0; it < C::IG; ++it)
@@ -402,11 +408,16 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
             }
         // the staging tile is private to the wave: no workgroup barrier
         wave_fence();
-        if constexpr (ACT)
-            copy_out_tile_gelu<C::DX_COLS>(stage, C::DX_STRIDE, dx + kk * C::P + ig * C::DX_COLS, C::N_IN, b0, B, lane, hp);
-        else
+        if constexpr (!ACT) {
             copy_out_tile<C::DX_COLS, 64, true>(stage, C::DX_STRIDE, dx + kk * C::P + ig * C::DX_COLS, C::N_IN, b0, B, lane);
-        wave_fence();
+            wave_fence();
+        }
+    };
+    if constexpr (ACT) tile(0, std::false_type{});
+    for (int ig = ACT ? 1 : 0; ig < NIG; ++ig) tile(ig, std::bool_constant<ACT>{});
+    if constexpr (ACT) {
+#pragma unroll
+        for (int i = 0; i < PIECES; ++i) put(NIG - 1, i, piece(i), hp[i]);
     }
 }
 
