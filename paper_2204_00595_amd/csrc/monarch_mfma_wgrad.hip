@@ -98,6 +98,7 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
     // buffer, and the row of the task inside a step.
     constexpr int A_TASKS = DEINT ? (KB * TM / 8) : (4 * KB * TM / 8);
     constexpr int B_TASKS = 4 * KB * TN / 8;
+    static_assert(B_TASKS % NTHR == 0 && (DEINT || A_TASKS % NTHR == 0), "only de-interleaving leaves threads without a task");
     constexpr int A_PER = (A_TASKS + NTHR - 1) / NTHR, B_PER = (B_TASKS + NTHR - 1) / NTHR;
     u32x4 areg[NSTG][A_PER][DEINT ? 4 : 1], breg[NSTG][B_PER];
     uint32_t pa[A_PER], pb[B_PER];
@@ -152,7 +153,9 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
     auto store_step = [&](int64_t, int stg, uint16_t* buf) {
 #pragma unroll
         for (int t = 0; t < A_PER; ++t) {
-            if (ra[t] >= KB) continue;
+            uint16_t* to = buf + la[t];
+            if constexpr (A_TASKS % NTHR != 0)  // no branch here either: without a task the zeros go past the buffers
+                to = tid + t * NTHR < A_TASKS ? to : lds + 2 * BUF + 8 * lane;
             if (DEINT) {
                 // the run holds elements e = 4*m' + c (m' = 0..7); gather the 8 m' of each group c
 #pragma unroll
@@ -163,17 +166,14 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
                         const uint32_t lo = areg[stg][t][w][c >> 1], hi = areg[stg][t][w][2 + (c >> 1)];
                         v[w] = (c & 1) ? pick_hi16(lo, hi) : pick_lo16(lo, hi);
                     }
-                    *reinterpret_cast<u32x4*>(buf + c * KB * SA + la[t]) = v;
+                    *reinterpret_cast<u32x4*>(to + c * KB * SA) = v;
                 }
             } else {
-                *reinterpret_cast<u32x4*>(buf + la[t]) = areg[stg][t][0];
+                *reinterpret_cast<u32x4*>(to) = areg[stg][t][0];
             }
         }
 #pragma unroll
-        for (int t = 0; t < B_PER; ++t) {
-            if (rb[t] >= KB) continue;
-            *reinterpret_cast<u32x4*>(buf + lb[t]) = breg[stg][t];
-        }
+        for (int t = 0; t < B_PER; ++t) *reinterpret_cast<u32x4*>(buf + lb[t]) = breg[stg][t];
     };
 
     f32x16 acc[MTW * NT];
@@ -406,7 +406,9 @@ int tiles_of(const WgradDesc& d, int tm, int tn) { return (d.M / tm) * (d.N / tn
 template <int TM, int TN>
 int launch_gemm(const WgradDesc& d0, const WgradDesc* d1, int nz, hipStream_t st)
 {
-    constexpr size_t lds = (size_t)2 * 4 * KB * (TM + lds_pad(TM) + TN + lds_pad(TN)) * 2;  // two pipeline buffers
+    // two pipeline buffers; where not every thread has an A task, what the others store (four groups, 16 bytes per lane)
+    constexpr size_t surplus = KB * TM / 8 % NTHR != 0 ? (size_t)(3 * KB * (TM + lds_pad(TM)) + 512) * 2 : 0;
+    constexpr size_t lds = (size_t)2 * 4 * KB * (TM + lds_pad(TM) + TN + lds_pad(TN)) * 2 + surplus;
     static_assert(lds <= kMaxLdsBytes, "LDS");
     auto kern = wgrad_gemm_kernel<TM, TN>;
     if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess)
