@@ -489,3 +489,21 @@ def test_workload_table_matches_the_stated_shapes():
     x, R, L, dy = synth.make_inputs(w["vitb_proj"], rows=8)
     assert x.shape == (8, 768) and R.shape == (4, 192, 192) and L.shape == (4, 192, 192) and dy.shape == (8, 768)
     assert abs(float(R.std()) - 192 ** -0.5) < 0.002
+
+
+def test_bias_forward_that_saves_rejects_bad_arguments_without_a_gpu(binding):
+    L = binding.lib()
+    p = 4096  # never dereferenced
+    need = binding.monarch_saved_bytes(1000, 768, 4, 192, 192, 1)
+
+    def fwd(bias=p, sv=p, sv_bytes=need, batch=1000, n_in=768, k=4, q=192, s=192, dtype=1, flags=0):
+        return L.monarch_fwd_bias_save(p, p, p, bias, p, sv, sv_bytes, batch, n_in, k, q, s, dtype, None, flags)
+
+    assert fwd(bias=p + 8) == binding.MONARCH_ERR_INVALID
+    assert fwd(sv=None) == binding.MONARCH_ERR_WORKSPACE
+    assert fwd(sv_bytes=need - 1) == binding.MONARCH_ERR_WORKSPACE
+    assert fwd(flags=binding.MONARCH_FLAG_WS_PACKED) == binding.MONARCH_ERR_INVALID
+    assert fwd(batch=0, sv_bytes=binding.monarch_saved_bytes(0, 768, 4, 192, 192, 1)) == binding.MONARCH_OK
+    # shapes without the path: refused with a bias, the plain forward without one
+    assert fwd(n_in=4096, k=64, q=64, s=64) == binding.MONARCH_ERR_UNSUPPORTED
+    assert fwd(bias=None, sv=None, sv_bytes=0, batch=0, n_in=6, k=2, q=4, s=2, dtype=0) == binding.MONARCH_OK
