@@ -28,6 +28,7 @@
 //             matching slot order.  No instruction is spent on the permutation.
 //             Work is split over waves in units of (32 features l) x (32 rows); a wave keeps all four
 //             c of its units so that step 3, y[b][4*l + c], is one packed 8-byte store per (b, l).
+#include "../../include/monarch.h"
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
 #include "monarch_mfma_pack.h"
@@ -405,9 +406,13 @@ bool fwd_frag_supported(const Problem& pb) { return find(pb) != nullptr; }
 size_t fwd_frag_packed(const Problem& pb) { return align_up(pb.n_R() * 2, 256) + align_up(pb.n_L() * 2, 256); }
 size_t fwd_frag_workspace(const Problem& pb) { return fwd_frag_packed(pb) + (fwd_split_preferred(pb) ? fwd_split_mid_bytes(pb) : 0); }
 
-int fwd_frag(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
+int fwd_frag(const Problem& given, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
 {
+    Problem pb = given;
     const Entry* e = find(pb);  // may be null: shapes that only the kernels for short batches serve
+    // For those every call packs, whatever the flag says: a call on a long batch, or with a short workspace, runs without packed
+    // weights, so an earlier call may have left none (packing rides in the first launch).
+    if (!e) pb.flags &= ~MONARCH_FLAG_WS_PACKED;
     uint16_t* RF1 = (uint16_t*)ws;
     uint16_t* LF2 = (uint16_t*)((char*)ws + align_up(pb.n_R() * 2, 256));
     if (fwd_split_preferred(pb) && pb.ws_bytes >= fwd_frag_workspace(pb))

@@ -83,3 +83,23 @@ def test_short_batch_backward(case):
     _, saved = B.monarch_fwd_save(xd, Rd, Ld)
     for name, g, w in zip(("dx_s", "dR_s", "dL_s"), B.monarch_bwd_saved(dyd, xd, saved, Rd, Ld), want):
         check(name, g, w)
+
+
+# p, q, s without a fused kernel: what an earlier call left in the workspace depends on its batch and on the room it had
+@pytest.mark.parametrize("dims", [(96, 96, 384), (128, 128, 384), (384, 96, 96)], ids=str)
+def test_packed_flag_after_a_call_that_packed_nothing(dims):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    p, q, s = dims
+    sh = synth.Shape("flag_%s" % (dims,), "bf16", 40, 4, p, q, s, config=800 + parity_util.stable_seed(str(dims)))
+    x, R, L, _ = synth.make_inputs(sh)
+    xd, Rd, Ld = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L))
+    want = oracle.fwd(x, R, L)
+    need = B.monarch_fwd_workspace_bytes(40, sh.n_in, 4, q, s, 1)
+    long_x = torch.zeros((8193, sh.n_in), dtype=torch.bfloat16, device="cuda")
+    for first in (lambda ws: B.monarch_fwd_ws(long_x, Rd, Ld, workspace=ws), lambda ws: B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws[:256])):
+        ws = torch.full((need,), 0xFF, dtype=torch.uint8, device="cuda")   # NaN in bf16
+        first(ws)
+        y = B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED)
+        parity_util.check(sh.name, y.float().cpu().numpy(), want, 2e-2)
