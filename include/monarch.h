@@ -104,7 +104,10 @@ int monarch_fwd_ex(const void* x, const void* R, const void* L, void* y,
  * monarch_fwd_workspace_bytes(...) bytes when that is non-zero.  Without MONARCH_FLAG_WS_PACKED its
  * contents on entry are ignored; on exit it holds the packed copies of R and L, and a later call with
  * MONARCH_FLAG_WS_PACKED, the same shape and unchanged R and L may reuse them (R and L must still be
- * valid pointers but are not read).  Returns MONARCH_ERR_WORKSPACE if the workspace is missing, misaligned or too small. */
+ * valid pointers but are not read).  A call with that flag, on a shape that has a packed-weight kernel, only reads the
+ * workspace: several of them, on any streams, may use one set of packed weights at the same time.  Every other call that
+ * takes a workspace writes to it and must have it to itself.
+ * Returns MONARCH_ERR_WORKSPACE if the workspace is missing, misaligned or too small. */
 int monarch_fwd_ws(const void* x, const void* R, const void* L, void* y,
                    int64_t batch, int n_in, int k, int q, int s,
                    monarch_dtype dtype, void* stream,
@@ -139,6 +142,21 @@ int monarch_fwd_bias(const void* x, const void* R, const void* L, const void* bi
                      int64_t batch, int n_in, int k, int q, int s,
                      monarch_dtype dtype, void* stream,
                      void* workspace, size_t workspace_bytes, unsigned flags);
+
+/* monarch_fwd_ws, monarch_fwd_bias or (gelu != 0) monarch_fwd_bias_gelu on packed weights, with scratch memory of the call's
+ * own: `packed` is the workspace that one of those calls filled (it is only read; MONARCH_FLAG_WS_PACKED is implied), `scratch`
+ * (device memory, 256-byte aligned, monarch_fwd_packed_scratch_bytes(...) bytes, contents ignored and left unspecified) lets
+ * short batches keep the vector between the factors there and run as one launch per factor, which spreads the weights over all
+ * CUs (1024 -> 4096 -> 1024 with bias and gelu, 8 rows: 54 -> 15 us).  Without scratch, or with too little, the call runs as
+ * those calls with MONARCH_FLAG_WS_PACKED.  bias and y_pre may be NULL, y_pre must be without gelu.
+ * MONARCH_ERR_UNSUPPORTED for shapes without a packed-weight kernel; other errors as those calls.
+ * monarch_fwd_packed_scratch_bytes is 0 where no scratch is used, and on invalid arguments. */
+size_t monarch_fwd_packed_scratch_bytes(int64_t batch, int n_in, int k, int q, int s,
+                                        monarch_dtype dtype, unsigned flags);
+int monarch_fwd_packed(const void* x, const void* R, const void* L, const void* bias, int gelu, void* y_pre, void* y,
+                       int64_t batch, int n_in, int k, int q, int s,
+                       monarch_dtype dtype, void* stream,
+                       const void* packed, size_t packed_bytes, void* scratch, size_t scratch_bytes, unsigned flags);
 
 /* Bytes of device scratch monarch_fwd_ws needs or can use for this problem (0 when the shape has no
  * kernel that takes any, and on invalid arguments). */

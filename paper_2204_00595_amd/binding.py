@@ -31,7 +31,8 @@ MONARCH_FLAG_WS_PACKED = 8
 
 # every symbol include/monarch.h declares
 EXPORTS = (
-    "monarch_fwd", "monarch_fwd_ex", "monarch_fwd_ws", "monarch_fwd_static", "monarch_fwd_bias", "monarch_fwd_workspace_bytes", "monarch_bwd",
+    "monarch_fwd", "monarch_fwd_ex", "monarch_fwd_ws", "monarch_fwd_static", "monarch_fwd_bias", "monarch_fwd_workspace_bytes",
+    "monarch_fwd_packed", "monarch_fwd_packed_scratch_bytes", "monarch_bwd",
     "monarch_bwd_bias", "monarch_fwd_bias_gelu", "monarch_bwd_bias_gelu_in",
     "monarch_bwd_workspace_bytes",
     "monarch_fwd_t", "monarch_fwd_t_workspace_bytes", "monarch_saved_bytes", "monarch_fwd_save", "monarch_fwd_bias_save", "monarch_bwd_saved", "monarch_fwd_c64", "monarch_fwd_h_c64", "monarch_bwd_c64", "monarch_fwd_c64_ws", "monarch_fwd_h_c64_ws", "monarch_bwd_c64_ws", "monarch_c64_workspace_bytes", "monarch_dft_factors", "monarch_to_dense", "monarch_project", "monarch_kernel_name", "monarch_status_string", "monarch_version", "monarch_stream_copy", "monarch_launch_probe",
@@ -66,6 +67,10 @@ def lib() -> ctypes.CDLL:
         L.monarch_fwd_static.argtypes = [vp, vp, vp, vp, i64, ci, ci, ci, ci, ci, vp, cu]
         L.monarch_fwd_bias.restype = ci
         L.monarch_fwd_bias.argtypes = [vp, vp, vp, vp, vp, i64, ci, ci, ci, ci, ci, vp, vp, sz, cu]
+        L.monarch_fwd_packed.restype = ci
+        L.monarch_fwd_packed.argtypes = [vp] * 4 + [ci, vp, vp, i64, ci, ci, ci, ci, ci, vp, vp, sz, vp, sz, cu]
+        L.monarch_fwd_packed_scratch_bytes.restype = sz
+        L.monarch_fwd_packed_scratch_bytes.argtypes = [i64, ci, ci, ci, ci, ci, cu]
         L.monarch_bwd_bias.restype = ci
         L.monarch_bwd_bias.argtypes = [vp] * 8 + [i64, ci, ci, ci, ci, ci, vp, vp, sz, cu]
         L.monarch_fwd_bias_gelu.restype = ci
@@ -192,7 +197,11 @@ def monarch_fwd_workspace_bytes(batch: int, n_in: int, k: int, q: int, s: int, d
 
 def monarch_fwd_ws(x: torch.Tensor, R: torch.Tensor, L: torch.Tensor, y: torch.Tensor | None = None,
                    workspace: torch.Tensor | None = None, flags: int = 0, stream=None) -> torch.Tensor:
-    """y = x M^T through monarch_fwd_ws.  The workspace is allocated when not given."""
+    """y = x M^T through monarch_fwd_ws.  The workspace is allocated when not given.
+
+    With MONARCH_FLAG_WS_PACKED a workspace of packed weights is only read, here and in monarch_fwd_bias and
+    monarch_fwd_bias_gelu: calls on several streams may share it.  What short batches need beside it is taken from the
+    caching allocator for the call's stream (monarch_fwd_packed)."""
     return _native_calls.fwd_ws(x, R, L, y, workspace, flags, stream)
 
 

@@ -142,7 +142,7 @@ int static_workspace(void** out)
 // kernel does not do in its own epilogue follows as a pass over y.
 int fwd_layer(const void* x, const void* R, const void* L, const void* bias, bool act, void* y_pre, void* y,
               int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, void* stream, void* workspace,
-              size_t workspace_bytes, unsigned flags)
+              size_t workspace_bytes, unsigned flags, void* mid = nullptr)
 {
     Problem pb;
     int rc = make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags);
@@ -166,6 +166,7 @@ int fwd_layer(const void* x, const void* R, const void* L, const void* bias, boo
             act_done = true;
         }
         pb.ws_bytes = workspace_bytes;
+        pb.mid = mid;
         rc = mfma_fwd_ws(pb, x, R, L, y, workspace, st);
         bias_done = bias_done || mfma_fwd_fuses_bias(pb, true);
     } else if (fwd_uses_ops(pb) && (batch == 0 || room_for(workspace, workspace_bytes, ops_fwd_workspace(pb)))) {
@@ -334,6 +335,26 @@ int monarch_fwd_bias_gelu(const void* x, const void* R, const void* L, const voi
                           void* workspace, size_t workspace_bytes, unsigned flags)
 {
     return fwd_layer(x, R, L, bias, true, y_pre, y, batch, n_in, k, q, s, dtype, stream, workspace, workspace_bytes, flags);
+}
+
+size_t monarch_fwd_packed_scratch_bytes(int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, unsigned flags)
+{
+    Problem pb;
+    if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags) || (flags & MONARCH_FLAG_GENERIC)) return 0;
+    return fwd_frag_supported(pb) && fwd_split_preferred(pb) ? fwd_split_mid_bytes(pb) : 0;
+}
+
+int monarch_fwd_packed(const void* x, const void* R, const void* L, const void* bias, int gelu, void* y_pre, void* y, int64_t batch,
+                       int n_in, int k, int q, int s, monarch_dtype dtype, void* stream, const void* packed, size_t packed_bytes,
+                       void* scratch, size_t scratch_bytes, unsigned flags)
+{
+    Problem pb;
+    if (int rc = make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags)) return rc;
+    if ((flags & MONARCH_FLAG_GENERIC) || (y_pre && !gelu)) return MONARCH_ERR_INVALID;
+    if (!mfma_fwd_keeps_packed(pb)) return MONARCH_ERR_UNSUPPORTED;
+    const size_t need = monarch_fwd_packed_scratch_bytes(batch, n_in, k, q, s, dtype, flags);
+    return fwd_layer(x, R, L, bias, gelu != 0, y_pre, y, batch, n_in, k, q, s, dtype, stream, const_cast<void*>(packed), packed_bytes,
+                     flags | MONARCH_FLAG_WS_PACKED, need > 0 && room_for(scratch, scratch_bytes, need) ? scratch : nullptr);
 }
 
 size_t monarch_saved_bytes(int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, unsigned flags)

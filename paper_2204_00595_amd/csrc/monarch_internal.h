@@ -18,6 +18,7 @@ struct Problem {
     int act = 0;                 // forward only: 1 = the output is gelu(product + bias)
     void* y_pre = nullptr;       // forward with act: the value before the nonlinearity also goes here (may be null)
     size_t ws_bytes = 0;         // forward with a workspace: its size
+    void* mid = nullptr;         // forward on packed weights, which it only reads: fwd_split_mid_bytes() of the call's own (may be null)
     const void* x_pre = nullptr; // backward only: the layer's input is gelu(x_pre); dx is returned with respect to x_pre
     int n_out() const { return k * s; }
     int kq() const { return k * q; }
@@ -129,6 +130,7 @@ bool mfma_fwd_ws_supported(const Problem& pb);
 size_t mfma_fwd_ws_workspace(const Problem& pb);
 size_t mfma_fwd_ws_least(const Problem& pb);   // what the call cannot do without; with less than the above it runs as for a long batch
 bool mfma_fwd_ws_optional(const Problem& pb);  // with less than mfma_fwd_ws_workspace it runs as without a workspace
+bool mfma_fwd_keeps_packed(const Problem& pb); // every call without the packed flag leaves the packed weights in its workspace
 const char* mfma_fwd_ws_name(const Problem& pb);
 int mfma_fwd_ws(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 // transposed multiply y = x M (x (B, k*s), y (B, n_in)) on the matrix cores

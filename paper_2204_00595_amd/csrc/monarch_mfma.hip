@@ -37,6 +37,7 @@ size_t mfma_fwd_ws_workspace(const Problem& pb)
     return 0;
 }
 size_t mfma_fwd_ws_least(const Problem& pb) { return fwd_frag_supported(pb) ? fwd_frag_packed(pb) : mfma_fwd_ws_workspace(pb); }
+bool mfma_fwd_keeps_packed(const Problem& pb) { return fwd_frag_supported(pb) || sq64_supported(pb); }
 const char* mfma_fwd_ws_name(const Problem& pb)
 {
     if (fwd_frag_supported(pb)) return "mfma_fwd_frag_bf16";

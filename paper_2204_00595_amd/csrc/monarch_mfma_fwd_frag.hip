@@ -415,8 +415,10 @@ int fwd_frag(const Problem& given, const void* x, const void* R, const void* L, 
     if (!e) pb.flags &= ~MONARCH_FLAG_WS_PACKED;
     uint16_t* RF1 = (uint16_t*)ws;
     uint16_t* LF2 = (uint16_t*)((char*)ws + align_up(pb.n_R() * 2, 256));
-    if (fwd_split_preferred(pb) && pb.ws_bytes >= fwd_frag_workspace(pb))
-        return fwd_split(pb, x, R, L, RF1, LF2, y, (char*)ws + fwd_frag_packed(pb), st);
+    // A call that packs owns its workspace.  One on packed weights only reads them, since calls on other streams may be doing the
+    // same: its vector between the factors lies in memory of its own, and without any the fused kernel runs.
+    void* mid = pb.ws_packed() ? pb.mid : pb.ws_bytes >= fwd_frag_workspace(pb) ? (char*)ws + fwd_frag_packed(pb) : nullptr;
+    if (mid && fwd_split_preferred(pb)) return fwd_split(pb, x, R, L, RF1, LF2, y, mid, st);
     if (!e) return -2;
     if (!pb.ws_packed()) {
         const size_t pieces = (pb.n_R() + pb.n_L()) / 8;

@@ -218,7 +218,16 @@ Layer fwd_layer(const char* name, const Tensor& x, const Tensor& R, const Tensor
         if (need) ws = w.scratch(need);
     }
     const Bytes b(ws);
-    const int rc = act == Act::gelu
+    // a workspace of packed weights is only read (other streams may be using it): the vector between the factors of a short batch
+    // goes to memory of this call
+    const size_t mid = flags & MONARCH_FLAG_WS_PACKED ? monarch_fwd_packed_scratch_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q,
+                                                                                        (int)sh.s, sh.code(), flags)
+                                                      : 0;
+    const Tensor scratch = mid ? w.scratch(mid) : Tensor();
+    const int rc = mid
+        ? monarch_fwd_packed(ptr(x), ptr(R), ptr(L), ptr(bias), act == Act::gelu, ptr(y_pre), ptr(y), sh.B, (int)sh.n_in(), (int)sh.k,
+                             (int)sh.q, (int)sh.s, sh.code(), w.stream(), b.p, b.n, ptr(scratch), mid, flags)
+        : act == Act::gelu
         ? monarch_fwd_bias_gelu(ptr(x), ptr(R), ptr(L), ptr(bias), ptr(y_pre), ptr(y), sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q,
                                 (int)sh.s, sh.code(), w.stream(), b.p, b.n, flags)
         : monarch_fwd_bias(ptr(x), ptr(R), ptr(L), ptr(bias), ptr(y), sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s,

@@ -103,3 +103,41 @@ def test_packed_flag_after_a_call_that_packed_nothing(dims):
         first(ws)
         y = B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED)
         parity_util.check(sh.name, y.float().cpu().numpy(), want, 2e-2)
+
+
+# 8 and 3072 rows: the first and the last that the kernels of short batches take; 3073 and m = 64: the fused kernels
+@pytest.mark.parametrize("dims", [(8, 4, 256, 256, 1024), (3072, 4, 64, 64, 64), (3073, 4, 64, 64, 64), (70, 64, 64, 64, 64)], ids=str)
+def test_packed_weights_are_only_read(dims):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, k, p, q, s = dims
+    sh = synth.Shape("shared_%s" % (dims,), "bf16", rows, k, p, q, s, config=820 + parity_util.stable_seed(str(dims)))
+    x, R, L, _ = synth.make_inputs(sh)
+    bias = synth.quantize(synth.normal(81, (sh.n_out,)), "bf16")
+    xd, Rd, Ld, bd = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L, bias))
+    want = oracle.fwd_bias(x, R, L, bias)
+    ws = torch.zeros(B.monarch_fwd_workspace_bytes(rows, sh.n_in, k, q, s, 1), dtype=torch.uint8, device="cuda")
+    first = B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws)
+    ws[2 * (R.size + L.size):] = 0x5A   # what lies behind the packed weights is not the packed calls' either
+    kept = ws.clone()
+    nan = torch.full_like(Rd, float("nan")), torch.full_like(Ld, float("nan"))
+
+    def check(name, got, want):
+        parity_util.check("%s.%s" % (sh.name, name), got.float().cpu().numpy(), want, 2e-2)
+        assert torch.equal(ws, kept), name
+
+    y = B.monarch_fwd_ws(xd, *nan, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED)
+    check("y", y, oracle.fwd(x, R, L))
+    assert torch.equal(y, first)
+    check("bias", B.monarch_fwd_bias(xd, *nan, bd, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED), want)
+    pre, act = B.monarch_fwd_bias_gelu(xd, *nan, bd, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED)
+    check("pre", pre, want)
+    check("gelu", act, activation.gelu(want))
+    # through the C ABI, where nothing is allocated: the fused kernel
+    y.fill_(float("nan"))
+    st = int(torch.cuda.current_stream().cuda_stream)
+    rc = B.lib().monarch_fwd_ws(xd.data_ptr(), nan[0].data_ptr(), nan[1].data_ptr(), y.data_ptr(), rows, sh.n_in, k, q, s, 1, st,
+                                ws.data_ptr(), ws.numel(), B.MONARCH_FLAG_WS_PACKED)
+    assert rc == B.MONARCH_OK
+    check("y_abi", y, oracle.fwd(x, R, L))

@@ -507,3 +507,34 @@ def test_bias_forward_that_saves_rejects_bad_arguments_without_a_gpu(binding):
     # shapes without the path: refused with a bias, the plain forward without one
     assert fwd(n_in=4096, k=64, q=64, s=64) == binding.MONARCH_ERR_UNSUPPORTED
     assert fwd(bias=None, sv=None, sv_bytes=0, batch=0, n_in=6, k=2, q=4, s=2, dtype=0) == binding.MONARCH_OK
+
+
+def test_forward_on_shared_packed_weights_rejects_bad_arguments_without_a_gpu(binding):
+    L = binding.lib()
+    p = 4096  # never dereferenced
+    need = binding.monarch_fwd_workspace_bytes(0, 768, 4, 192, 192, 1)
+
+    def scratch(batch, n_in=768, k=4, q=192, s=192, dtype=1, flags=0):
+        return L.monarch_fwd_packed_scratch_bytes(batch, n_in, k, q, s, dtype, flags)
+
+    assert scratch(1) == 4 * 192 * 2 and scratch(3000) == 3000 * 4 * 192 * 2   # the vector between the factors
+    assert scratch(0) == scratch(3073) == scratch(8, flags=binding.MONARCH_FLAG_GENERIC) == scratch(8, n_in=770) == 0
+    assert scratch(8, n_in=384, q=96, s=384) == 0            # packs on every call
+    assert scratch(8, n_in=4096, k=64, q=64, s=64) == 0      # m = 64: one kernel for all batches
+
+    def call(ptrs=(p,) * 3, bias=p, gelu=1, y_pre=p, y=2 * p, ws=p, ws_bytes=need, flags=0, batch=0, n_in=768, k=4, q=192, s=192, dtype=1):
+        return L.monarch_fwd_packed(*ptrs, bias, gelu, y_pre, y, batch, n_in, k, q, s, dtype, None, ws, ws_bytes, None, 0, flags)
+
+    assert call() == binding.MONARCH_OK
+    assert call(bias=None, gelu=0, y_pre=None, flags=binding.MONARCH_FLAG_WS_PACKED) == binding.MONARCH_OK
+    assert call(gelu=0) == binding.MONARCH_ERR_INVALID           # y_pre without the nonlinearity
+    assert call(y=p) == binding.MONARCH_ERR_INVALID              # y_pre and y are one buffer
+    assert call(ptrs=(None, p, p), batch=1) == binding.MONARCH_ERR_INVALID
+    assert call(ptrs=(p, p, p + 8)) == binding.MONARCH_ERR_INVALID
+    assert call(n_in=770) == binding.MONARCH_ERR_INVALID
+    for f in (binding.MONARCH_FLAG_GENERIC, binding.MONARCH_FLAG_WGRAD_F32, 1024):
+        assert call(flags=f) == binding.MONARCH_ERR_INVALID
+    assert call(ws=None) == binding.MONARCH_ERR_WORKSPACE
+    assert call(ws_bytes=need - 1) == binding.MONARCH_ERR_WORKSPACE
+    for shape in (dict(n_in=384, q=96, s=384), dict(dtype=0), dict(flags=binding.MONARCH_FLAG_PERM_B)):   # nothing is kept packed
+        assert call(**shape) == binding.MONARCH_ERR_UNSUPPORTED
