@@ -361,8 +361,9 @@ size_t monarch_saved_bytes(int64_t batch, int n_in, int k, int q, int s, monarch
 {
     Problem pb;
     if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags)) return 0;
-    if ((flags & MONARCH_FLAG_GENERIC) || !(saved_supported(pb) || (fwd_uses_ops(pb) && pick_bwd(pb) == FAM_OPS))) return 0;
-    return align_up((size_t)(batch > 0 ? batch : 1) * pb.kq() * pb.esize(), 256);
+    if (flags & MONARCH_FLAG_GENERIC) return 0;
+    if (saved_supported(pb)) return align_up((size_t)(batch > 0 ? batch : 1) * pb.kq() * pb.esize(), 256);
+    return fwd_uses_ops(pb) && pick_bwd(pb) == FAM_OPS ? ops_fwd_workspace(pb) : 0;
 }
 
 int monarch_fwd_save(const void* x, const void* R, const void* L, void* y, void* saved, size_t saved_bytes,

@@ -11,18 +11,23 @@
 //                  dx[b][kk*p + i] = sum_j dU[b][j*k + kk] R[kk][j][i]
 //                  dL[c][l][r]     = sum_b dy[b][l*k + c] U[b][c*q + r],   dR likewise from dU and x
 // With MONARCH_FLAG_PERM_B the vector between the factors is kept in stage-1 order and the strides on either side of it
-// change places.  So there is one kernel, ops_gemm_kernel: O[g][m][n] = sum_k A[g][m][k] B[g][n][k].
+// change places.  So there is one contraction, ops_gemm: O[g][m][n] = sum_k A[g][m][k] B[g][n][k].
+//
+// Precision: U and dU are fp32 for both types, as in the SIMT kernels, and a product with one of them runs on the fp32 matrix
+// cores, its bf16 operand widened on the way to LDS; bf16 layers are rounded once, when a result is stored.  The products of two
+// bf16 operands (step 1 and dU) are exact on the bf16 matrix cores.
 //
 // What bounds it: fp32 layers the fp32 matrix cores (v_mfma_f32_32x32x2_f32, 154 TFLOP/s in a large product; a 128 x 128
 // tile needs 16 B/clk of LDS reads per CU, far below the 128 there are), small and odd bf16 layers the memory system (every
-// operand element is staged once per tile, in 2-byte pieces where it is strided, else in 16-byte pieces wherever they start).  The intermediate goes
+// operand element is staged once per tile, element by element where it is strided, else in 16-byte pieces wherever they start) and,
+// in the products with U and dU, the fp32 matrix cores.  The intermediate goes
 // through memory (for most shapes it stays in the last-level cache): a fused kernel would hold all k blocks of a row tile,
 // which leaves the large shapes one 16-row tile per CU.
 // Measured against the SIMT kernels: 768 -> 768 fp32, k = 4, 12608 rows: forward 741 -> 96 us, backward 3570 -> 255 us (one
 // contraction of 3.7 GFLOP takes 46 to 57 us, its matrix-core floor is 24: the cores are busy 62 % of the time of a busy CU,
 // and 2.3 rounds of workgroups leave a quarter of the launch on partly filled CUs); 196 -> 256 bf16, blocks of 49 and 64,
-// 32768 rows: forward 61 -> 27 us, backward 388 -> 64 us (with the odd blocks in 2-byte pieces 40 and 69); 4096 -> 1024 fp32, 16384 rows: 105 TFLOP/s in the data path,
-// 92 in the weight gradients.
+// 32768 rows: forward 61 -> 39 us, backward 388 -> 90 us (U and dU in 16 bits: 26 and 67 us, but results 2.35e-3 off in place of
+// 1.65e-3); 4096 -> 1024 fp32, 16384 rows: 105 TFLOP/s in the data path, 92 in the weight gradients.
 #include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
@@ -76,17 +81,19 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
 }
 
 // A C x O tile of an operand (C: extent along the index with the unit or smallest stride, O: along the other one) on
-// its way from memory to LDS [o][c], row stride LSTR elements.  Elements past the limits read as zeros.
-template <typename T, int C, int O, int LSTR, Take TAKE>
+// its way from memory (type T) to LDS [o][c] (type TL: T, or float for bf16), row stride LSTR elements.  Elements past the limits
+// read as zeros.
+template <typename T, typename TL, int C, int O, int LSTR, Take TAKE>
 struct OpTile {
     static constexpr bool VEC = TAKE != kElements;
+    static constexpr bool kWiden = sizeof(TL) != sizeof(T);
     static constexpr int EPD = 4 / (int)sizeof(T);                   // elements per dword
     static constexpr int V = VEC ? 16 / (int)sizeof(T) : EPD;        // elements per piece
     static constexpr int PPO = C / V;                                // pieces per o
     static constexpr int kPieces = PPO * O;
     static constexpr int NP = (kPieces + kThreads - 1) / kThreads;   // per thread
     static constexpr int kLoads = VEC ? 1 : EPD, kDwords = VEC ? 4 : EPD;
-    static_assert(C % V == 0 && LSTR * sizeof(T) % 16 == 0, "tile");
+    static_assert(C % V == 0 && LSTR * sizeof(TL) % 16 == 0, "tile");
     static_assert(VEC || kPieces % kThreads == 0, "element-wise tiles divide over the threads");
     static constexpr bool kEven = kThreads % PPO == 0;  // a thread's pieces share c and step in o by a uniform amount
     uint32_t r[NP * kDwords];
@@ -140,7 +147,7 @@ struct OpTile {
         }
         return v;
     }
-    __device__ __forceinline__ void store(T* lds, int tid) const
+    __device__ __forceinline__ void store(TL* lds, int tid) const
     {
 #pragma unroll
         for (int n = 0; n < NP; ++n) {
@@ -148,7 +155,18 @@ struct OpTile {
             if constexpr (VEC) {
                 u32x4 v = {r[4 * n], r[4 * n + 1], r[4 * n + 2], r[4 * n + 3]};
                 if constexpr (TAKE == kPiecesAny) v = drop(v, over[kEven ? 0 : n]);
-                if (kPieces % kThreads == 0 || idx < kPieces) *reinterpret_cast<u32x4*>(lds + o * LSTR + c) = v;
+                if (kPieces % kThreads == 0 || idx < kPieces) {
+                    if constexpr (kWiden) {
+#pragma unroll
+                        for (int w = 0; w < 4; w += 2)
+                            *reinterpret_cast<u32x4*>(lds + o * LSTR + c + 2 * w) =
+                                u32x4{v[w] << 16, v[w] & 0xffff0000u, v[w + 1] << 16, v[w + 1] & 0xffff0000u};
+                    } else {
+                        *reinterpret_cast<u32x4*>(lds + o * LSTR + c) = v;
+                    }
+                }
+            } else if constexpr (kWiden) {
+                *reinterpret_cast<u32x2*>(lds + o * LSTR + c) = u32x2{r[n * EPD] << 16, r[n * EPD + EPD - 1] << 16};
             } else {
                 *reinterpret_cast<uint32_t*>(lds + o * LSTR + c) = EPD == 1 ? r[n] : (r[n * EPD] | (r[n * EPD + EPD - 1] << 16));
             }
@@ -227,27 +245,28 @@ struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32
     static constexpr int TM = WM * MT * 32, TN = WN * NT * 32;
 };
 
-// RA / RB: the operand's row index (not the contraction) is the contiguous one.  PARTIAL: fp32 partial tiles of a split
-// contraction instead of the output.
+// One workgroup, `bid` of d.blocks.  TA, TB, TO: element types of the operands and the output in memory; two bf16 operands are
+// multiplied as such, else as fp32.  RA / RB: the operand's row index (not the contraction) is the contiguous one.  PARTIAL: fp32
+// partial tiles of a split contraction instead of the output.
 // Workgroup order: the row tile (PARTIAL: the batch chunk) is dealt to the XCDs, and the blocks and column tiles of one
 // row tile follow each other on that XCD: strided operands and outputs of the k blocks share their cache lines, which
 // then meet in one L2.
-template <typename T, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
-__global__ void __launch_bounds__(kThreads, 2)
-ops_gemm_kernel(const OpDesc d0, const OpDesc d1)
+template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
+struct OpGemm {
+    using T = typename std::conditional<sizeof(TA) == 2 && sizeof(TB) == 2, bf16_t, float>::type;
+    static constexpr int KC = OpType<T>::KC, LA = op_lstr<T, RA, Cfg::TM>(), LB = op_lstr<T, RB, Cfg::TN>();
+    static constexpr int SZA = RA ? KC * LA : Cfg::TM * LA, SZB = RB ? KC * LB : Cfg::TN * LB;
+    static constexpr size_t kLds = 2 * sizeof(T) * (size_t)(SZA + SZB);
+    static __device__ void run(const OpDesc& d, int bid, unsigned char* op_lds);
+};
+template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
+__device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>::run(const OpDesc& d, int bid, unsigned char* op_lds)
 {
     constexpr int KC = OpType<T>::KC, KSTEP = OpType<T>::KSTEP, MT = Cfg::MT, NT = Cfg::NT, TM = Cfg::TM, TN = Cfg::TN;
-    constexpr int LA = op_lstr<T, RA, TM>(), LB = op_lstr<T, RB, TN>();
-    constexpr int SZA = RA ? KC * LA : TM * LA, SZB = RB ? KC * LB : TN * LB;
-    using TA = OpTile<T, RA ? TM : KC, RA ? KC : TM, LA, AV>;
-    using TB = OpTile<T, RB ? TN : KC, RB ? KC : TN, LB, BV>;
-    extern __shared__ __align__(16) unsigned char op_lds[];
+    using TileA = OpTile<TA, T, RA ? TM : KC, RA ? KC : TM, LA, AV>;
+    using TileB = OpTile<TB, T, RB ? TN : KC, RB ? KC : TN, LB, BV>;
     T* const lds = reinterpret_cast<T*>(op_lds);
 
-    int bid = (int)blockIdx.x;
-    const bool second = bid >= d0.blocks;
-    const OpDesc& d = second ? d1 : d0;
-    if (second) bid -= d0.blocks;
     const int inner = d.G * d.tiles_n * (PARTIAL ? d.tiles_m : 1);
     const int seq = d.deal ? bid >> 3 : bid;
     const int outer = d.deal ? (seq / inner) * 8 + (bid & 7) : seq / inner;
@@ -265,8 +284,8 @@ ops_gemm_kernel(const OpDesc d0, const OpDesc d1)
 
     const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
     const int wm = wave % Cfg::WM, wn = wave / Cfg::WM;
-    const T* pa = static_cast<const T*>(d.a.p) + g * d.a.g_s + m0 * d.a.r_s + k_lo * d.a.k_s;
-    const T* pb = static_cast<const T*>(d.b.p) + g * d.b.g_s + (int64_t)n0 * d.b.r_s + k_lo * d.b.k_s;
+    const TA* pa = static_cast<const TA*>(d.a.p) + g * d.a.g_s + m0 * d.a.r_s + k_lo * d.a.k_s;
+    const TB* pb = static_cast<const TB*>(d.b.p) + g * d.b.g_s + (int64_t)n0 * d.b.r_s + k_lo * d.b.k_s;
     const uint32_t a_o = (uint32_t)(RA ? d.a.k_s : d.a.r_s), a_c = (uint32_t)(RA ? d.a.r_s : d.a.k_s);
     const uint32_t b_o = (uint32_t)(RB ? d.b.k_s : d.b.r_s), b_c = (uint32_t)(RB ? d.b.r_s : d.b.k_s);
 
@@ -281,8 +300,8 @@ ops_gemm_kernel(const OpDesc d0, const OpDesc d1)
     // two chunks are on their way from memory while one is multiplied: with one, a chunk's time on the matrix cores
     // (0.4 to 0.9 us) does not cover a load's
     struct Stage {
-        TA a;
-        TB b;
+        TileA a;
+        TileB b;
     };
     Stage s0, s1;
     auto fetch = [&](Stage& s, int64_t kk) {
@@ -337,7 +356,7 @@ ops_gemm_kernel(const OpDesc d0, const OpDesc d1)
     }
 
     const int col = lane & 31, rh = 4 * (lane >> 5);
-    using OT = typename std::conditional<PARTIAL, float, T>::type;
+    using OT = typename std::conditional<PARTIAL, float, TO>::type;
     OT* O = static_cast<OT*>(d.o);
     uint32_t o_m = (uint32_t)d.o_m;
     if constexpr (PARTIAL) {
@@ -359,8 +378,8 @@ ops_gemm_kernel(const OpDesc d0, const OpDesc d1)
                 off = (f - jj * (uint32_t)d.G) * (uint32_t)d.N + jj;
             }
             if (d.bias) {
-                const uint32_t at = n < nlim ? off * (uint32_t)sizeof(T) : kNowhere;
-                if constexpr (sizeof(T) == 4) bv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buffer_at(d.bias), at, 0, 0));
+                const uint32_t at = n < nlim ? off * (uint32_t)sizeof(TO) : kNowhere;
+                if constexpr (sizeof(TO) == 4) bv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(buffer_at(d.bias), at, 0, 0));
                 else bv = bf16_to_f32((bf16_t)__builtin_amdgcn_raw_buffer_load_b16(buffer_at(d.bias), at, 0, 0));
             }
         }
@@ -374,6 +393,30 @@ ops_gemm_kernel(const OpDesc d0, const OpDesc d1)
                 if constexpr (sizeof(OT) == 4) __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(v), out, at, 0, 0);
                 else __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v), out, at, 0, 0);
             }
+    }
+}
+
+template <class G>
+__global__ void __launch_bounds__(kThreads, 2)
+ops_gemm_kernel(const OpDesc d)
+{
+    extern __shared__ __align__(16) unsigned char op_lds[];
+    G::run(d, (int)blockIdx.x, op_lds);
+}
+// two contractions, the workgroups of the second behind those of the first
+template <class G0, class G1>
+__global__ void __launch_bounds__(kThreads, 2)
+ops_gemm_pair_kernel(const OpDesc d0, const OpDesc d1)
+{
+    extern __shared__ __align__(16) unsigned char op_lds[];
+    const int bid = (int)blockIdx.x;
+    const bool second = bid >= d0.blocks;
+    if constexpr (std::is_same<G0, G1>::value) {
+        const OpDesc& d = second ? d1 : d0;
+        G0::run(d, second ? bid - d0.blocks : bid, op_lds);
+    } else {
+        if (second) G1::run(d1, bid - d0.blocks, op_lds);
+        else G0::run(d0, bid, op_lds);
     }
 }
 
@@ -444,13 +487,19 @@ Take take_of(const void* p, int64_t s1, int64_t s2, int64_t contiguous_stride, i
     return (uintptr_t)p % 16 == 0 && s1 % v == 0 && s2 % v == 0 && extent % v == 0 ? kPieces16 : kPiecesAny;
 }
 
-template <typename T, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
-int launch_cfg(const OpDesc& d0, const OpDesc& d1, hipStream_t st)
+template <class G>
+int launch_one(const OpDesc& d, hipStream_t st)
 {
-    constexpr int KC = OpType<T>::KC;
-    constexpr int LA = op_lstr<T, RA, Cfg::TM>(), LB = op_lstr<T, RB, Cfg::TN>();
-    constexpr size_t lds = 2 * sizeof(T) * (size_t)((RA ? KC * LA : Cfg::TM * LA) + (RB ? KC * LB : Cfg::TN * LB));
-    auto kernel = ops_gemm_kernel<T, Cfg, RA, RB, PARTIAL, AV, BV>;
+    auto kernel = ops_gemm_kernel<G>;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), G::kLds)) return hip_status(e);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)d.blocks), dim3(kThreads), G::kLds, st, d);
+    return hip_status(hipGetLastError());
+}
+template <class G0, class G1>
+int launch_pair(const OpDesc& d0, const OpDesc& d1, hipStream_t st)
+{
+    constexpr size_t lds = G0::kLds > G1::kLds ? G0::kLds : G1::kLds;
+    auto kernel = ops_gemm_pair_kernel<G0, G1>;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds)) return hip_status(e);
     hipLaunchKernelGGL(kernel, dim3((unsigned)(d0.blocks + d1.blocks)), dim3(kThreads), lds, st, d0, d1);
     return hip_status(hipGetLastError());
@@ -466,44 +515,53 @@ struct TileSize {
 constexpr int kTileSizes = 4;
 constexpr TileSize kTiles[kTileSizes] = {{128, 128}, {128, 96}, {128, 64}, {64, 64}};
 
-template <typename T, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
-int launch_tile(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
+template <typename TA, typename TB, typename TO, bool RB, Take AV, Take BV>
+int launch_tile(int cfg, const OpDesc& d, hipStream_t st)
 {
     if constexpr (AV != kElements) {
-        if (cfg == 0) return launch_cfg<T, Cfg128x128, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
-        if (cfg == 1) return launch_cfg<T, Cfg128x96, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
+        if (cfg == 0) return launch_one<OpGemm<TA, TB, TO, Cfg128x128, false, RB, false, AV, BV>>(d, st);
+        if (cfg == 1) return launch_one<OpGemm<TA, TB, TO, Cfg128x96, false, RB, false, AV, BV>>(d, st);
     }
     switch (cfg) {
-        case 2: return launch_cfg<T, Cfg128x64, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
-        default: return launch_cfg<T, Cfg64x64, RA, RB, PARTIAL, AV, BV>(d0, d1, st);
+        case 2: return launch_one<OpGemm<TA, TB, TO, Cfg128x64, false, RB, false, AV, BV>>(d, st);
+        default: return launch_one<OpGemm<TA, TB, TO, Cfg64x64, false, RB, false, AV, BV>>(d, st);
     }
 }
-// The three kinds of contraction with the ways of taking that occur: both operands in aligned pieces, both in pieces from
-// anywhere, or A element by element (it is strided in the backward, and in the forward under MONARCH_FLAG_PERM_B).
-template <typename T>
+// The two kinds of contraction of the data path with the ways of taking that occur: both operands in aligned pieces, both in pieces
+// from anywhere, or A element by element (it is strided in the backward, and in the forward under MONARCH_FLAG_PERM_B).
+template <typename TA, typename TB, typename TO>
 int launch_op(bool w_rc, int cfg, const OpDesc& d, hipStream_t st)
 {
-    const OpDesc none{};
     const bool aligned = d.b.take == kPieces16;
     if (!w_rc) {
-        if (d.a.take == kElements) return launch_tile<T, false, false, false, kElements, kPiecesAny>(cfg, d, none, st);
-        return aligned && d.a.take == kPieces16 ? launch_tile<T, false, false, false, kPieces16, kPieces16>(cfg, d, none, st)
-                                                : launch_tile<T, false, false, false, kPiecesAny, kPiecesAny>(cfg, d, none, st);
+        if (d.a.take == kElements) return launch_tile<TA, TB, TO, false, kElements, kPiecesAny>(cfg, d, st);
+        return aligned && d.a.take == kPieces16 ? launch_tile<TA, TB, TO, false, kPieces16, kPieces16>(cfg, d, st)
+                                                : launch_tile<TA, TB, TO, false, kPiecesAny, kPiecesAny>(cfg, d, st);
     }
     if (d.a.take == kElements) {
-        return aligned ? launch_tile<T, false, true, false, kElements, kPieces16>(cfg, d, none, st)
-                       : launch_tile<T, false, true, false, kElements, kPiecesAny>(cfg, d, none, st);
+        return aligned ? launch_tile<TA, TB, TO, true, kElements, kPieces16>(cfg, d, st)
+                       : launch_tile<TA, TB, TO, true, kElements, kPiecesAny>(cfg, d, st);
     }
-    return aligned && d.a.take == kPieces16 ? launch_tile<T, false, true, false, kPieces16, kPieces16>(cfg, d, none, st)
-                                            : launch_tile<T, false, true, false, kPiecesAny, kPiecesAny>(cfg, d, none, st);
+    return aligned && d.a.take == kPieces16 ? launch_tile<TA, TB, TO, true, kPieces16, kPieces16>(cfg, d, st)
+                                            : launch_tile<TA, TB, TO, true, kPiecesAny, kPiecesAny>(cfg, d, st);
+}
+// dL from dy and U, dR from dU and x: T is the layer's type, U and dU are fp32
+template <typename T, Take BV>
+int launch_wgrad_take(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
+{
+    if (cfg == 2)
+        return launch_pair<OpGemm<T, float, float, Cfg128x64, true, true, true, kElements, BV>,
+                           OpGemm<float, T, float, Cfg128x64, true, true, true, kElements, BV>>(d0, d1, st);
+    return launch_pair<OpGemm<T, float, float, Cfg64x64, true, true, true, kElements, BV>,
+                       OpGemm<float, T, float, Cfg64x64, true, true, true, kElements, BV>>(d0, d1, st);
 }
 template <typename T>
 int launch_wgrad(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
 {
     const Take b = d0.b.take < d1.b.take ? d0.b.take : d1.b.take;
-    return b == kPieces16    ? launch_tile<T, true, true, true, kElements, kPieces16>(cfg, d0, d1, st)
-           : b == kPiecesAny ? launch_tile<T, true, true, true, kElements, kPiecesAny>(cfg, d0, d1, st)
-                             : launch_tile<T, true, true, true, kElements, kElements>(cfg, d0, d1, st);
+    return b == kPieces16    ? launch_wgrad_take<T, kPieces16>(cfg, d0, d1, st)
+           : b == kPiecesAny ? launch_wgrad_take<T, kPiecesAny>(cfg, d0, d1, st)
+                             : launch_wgrad_take<T, kElements>(cfg, d0, d1, st);
 }
 
 int64_t tiles(int64_t n, int t) { return (n + t - 1) / t; }
@@ -544,14 +602,14 @@ OpOperand operand(const void* p, int64_t g_s, int64_t r_s, int64_t k_s, bool rc,
                      rc ? take_of(p, g_s, k_s, r_s, rows, esize) : take_of(p, g_s, r_s, k_s, K, esize)};
 }
 
-// One step of the data path: O (rows x blocks x N) = A x W per block.
+// One step of the data path: O (rows x blocks x N) = A x W per block; W, and one of A and O, are of the layer's type.
+template <typename TA, typename TW, typename TO>
 int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t lda, int K, const void* w, bool w_rc, int N,
             void* o, int64_t o_g, int64_t o_n, int64_t ldo, const void* bias, hipStream_t st, bool o_mid = false)
 {
-    const int e = (int)pb.esize();
     OpDesc d{};
-    d.a = operand(a, a_g, lda, a_k, false, pb.B, K, e);
-    d.b = w_rc ? operand(w, (int64_t)K * N, 1, N, true, N, K, e) : operand(w, (int64_t)K * N, K, 1, false, N, K, e);
+    d.a = operand(a, a_g, lda, a_k, false, pb.B, K, sizeof(TA));
+    d.b = w_rc ? operand(w, (int64_t)K * N, 1, N, true, N, K, sizeof(TW)) : operand(w, (int64_t)K * N, K, 1, false, N, K, sizeof(TW));
     d.o = o;
     d.o_g = o_g;
     d.o_m = ldo;
@@ -567,7 +625,7 @@ int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t 
     d.tiles_n = (int)tiles(N, kTiles[cfg].n);
     d.k_chunk = K;
     deal(d, d.tiles_m, d.tiles_n * d.G);
-    return pb.dtype == 0 ? launch_op<float>(w_rc, cfg, d, st) : launch_op<bf16_t>(w_rc, cfg, d, st);
+    return launch_op<TA, TW, TO>(w_rc, cfg, d, st);
 }
 
 // Batch chunks of the weight-gradient contractions: about four workgroups per CU over both (768 -> 768 fp32: 131 us with
@@ -603,7 +661,7 @@ WgradPlan wgrad_plan(const Problem& pb)
     return pl;
 }
 
-size_t mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B > 0 ? pb.B : 1) * pb.kq() * pb.esize(), 256); }
+size_t mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B > 0 ? pb.B : 1) * pb.kq() * sizeof(float), 256); }
 
 // element strides of the vector between the factors: kept permuted (default reading) or in stage-1 order (PERM_B)
 struct Mid {
@@ -616,10 +674,26 @@ Mid mid(const Problem& pb)
     return Mid{pb.q, 1, 1, pb.k};
 }
 
+template <typename T>
 int stage1(const Problem& pb, const void* x, const void* R, void* U, hipStream_t st)
 {
     const Mid m = mid(pb);
-    return data_op(pb, x, pb.p, 1, pb.n_in, pb.p, R, false, pb.q, U, m.s1_g, m.s1_n, pb.kq(), nullptr, st);
+    return data_op<T, T, float>(pb, x, pb.p, 1, pb.n_in, pb.p, R, false, pb.q, U, m.s1_g, m.s1_n, pb.kq(), nullptr, st);
+}
+template <typename T>
+int fwd_typed(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* U, hipStream_t st)
+{
+    if (int rc = stage1<T>(pb, x, R, U, st)) return rc;
+    const Mid m = mid(pb);
+    return data_op<float, T, T>(pb, U, m.s2_g, m.s2_n, pb.kq(), pb.q, L, false, pb.s, y, 1, pb.k, pb.n_out(), pb.bias, st);
+}
+template <typename T>
+int fwd_t_typed(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* dU, hipStream_t st)
+{
+    // the vector between the factors in stage-1 order: written in short pieces once, read in long ones twice (dx, dR)
+    if (int rc = data_op<T, T, float>(pb, x, 1, pb.k, pb.n_out(), pb.s, L, true, pb.q, dU, 1, pb.k, pb.kq(), nullptr, st, !pb.perm_b()))
+        return rc;
+    return data_op<float, T, T>(pb, dU, pb.q, 1, pb.kq(), pb.q, R, true, pb.p, y, pb.p, 1, pb.n_in, nullptr, st);
 }
 
 }  // namespace
@@ -640,9 +714,7 @@ size_t ops_fwd_workspace(const Problem& pb) { return mid_bytes(pb); }
 // U: the vector between the factors (mid_bytes), left there for ops_bwd
 int ops_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* U, hipStream_t st)
 {
-    if (int rc = stage1(pb, x, R, U, st)) return rc;
-    const Mid m = mid(pb);
-    return data_op(pb, U, m.s2_g, m.s2_n, pb.kq(), pb.q, L, false, pb.s, y, 1, pb.k, pb.n_out(), pb.bias, st);
+    return pb.dtype == 0 ? fwd_typed<float>(pb, x, R, L, y, U, st) : fwd_typed<bf16_t>(pb, x, R, L, y, U, st);
 }
 
 size_t ops_fwd_t_workspace(const Problem& pb) { return mid_bytes(pb); }
@@ -650,9 +722,7 @@ size_t ops_fwd_t_workspace(const Problem& pb) { return mid_bytes(pb); }
 // y = x M: the dx path on its own
 int ops_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* dU, hipStream_t st)
 {
-    // the vector between the factors in stage-1 order: written in short pieces once, read in long ones twice (dx, dR)
-    if (int rc = data_op(pb, x, 1, pb.k, pb.n_out(), pb.s, L, true, pb.q, dU, 1, pb.k, pb.kq(), nullptr, st, !pb.perm_b())) return rc;
-    return data_op(pb, dU, pb.q, 1, pb.kq(), pb.q, R, true, pb.p, y, pb.p, 1, pb.n_in, nullptr, st);
+    return pb.dtype == 0 ? fwd_t_typed<float>(pb, x, R, L, y, dU, st) : fwd_t_typed<bf16_t>(pb, x, R, L, y, dU, st);
 }
 
 size_t ops_bwd_workspace(const Problem& pb)
@@ -680,7 +750,7 @@ int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, con
     char* w = static_cast<char*>(ws);
     const void* U = pb.saved;
     if (!U) {
-        if (int rc = stage1(pb, x, R, w, st)) return rc;
+        if (int rc = pb.dtype == 0 ? stage1<float>(pb, x, R, w, st) : stage1<bf16_t>(pb, x, R, w, st)) return rc;
         U = w;
     }
     void* dU = w + mid_bytes(pb);
@@ -691,8 +761,8 @@ int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, con
     float* P = reinterpret_cast<float*>(w + 2 * mid_bytes(pb));
     OpDesc d[2] = {};
     d[0].a = operand(dy, 1, pb.k, pb.n_out(), true, pb.s, pb.B, e);
-    d[0].b = operand(U, m.s2_g, m.s2_n, pb.kq(), true, pb.q, pb.B, e);
-    d[1].a = operand(dU, pb.q, 1, pb.kq(), true, pb.q, pb.B, e);
+    d[0].b = operand(U, m.s2_g, m.s2_n, pb.kq(), true, pb.q, pb.B, sizeof(float));
+    d[1].a = operand(dU, pb.q, 1, pb.kq(), true, pb.q, pb.B, sizeof(float));
     d[1].b = operand(x, pb.p, 1, pb.n_in, true, pb.p, pb.B, e);
     const int M[2] = {pb.s, pb.q}, N[2] = {pb.q, pb.p};
     for (int i = 0; i < 2; ++i) {

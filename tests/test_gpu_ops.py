@@ -81,3 +81,34 @@ def test_forward_with_bias_that_keeps_the_vector(case):
     for name, a, b, w in zip(("y", "dx", "dR", "dL", "dbias"), got, (out, xg.grad, layer.R.grad, layer.L.grad, layer.bias.grad), want):
         parity_util.check("%s.%s" % (sh.name, name), a.float().cpu().numpy(), w, TOL[dtype])
         parity_util.check("%s.layer.%s" % (sh.name, name), b.detach().float().cpu().numpy(), w, TOL[dtype])
+
+
+# bf16 layers hold the vector between the factors in 32 bits: a result is rounded to 16 bits once, when it is stored, which puts
+# every element within 2^-9 of its value (2e-5: sums of products in fp32).  With a 16-bit vector between them the whole is 2.3e-3 off.
+ONE_ROUNDING = 2.0 ** -9 + 2e-5
+
+
+@pytest.mark.parametrize("reading", [0, 1], ids=["reading_a", "reading_b"])
+@pytest.mark.parametrize("case", [(2000, 4, 49, 49, 64), (300, 2, 17, 16, 250), (640, 8, 101, 37, 16), (1100, 1, 64, 95, 128), (129, 3, 250, 97, 131)], ids=str)
+def test_vector_between_the_factors_keeps_32_bits(case, reading):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    sh = synth.Shape("bits_%s" % (case,), "bf16", *case, config=900 + parity_util.stable_seed(str(case)))
+    flags = B.MONARCH_FLAG_PERM_B if reading else 0
+    rd = oracle.READING_B if reading else oracle.READING_A
+    x, R, L, dy = synth.make_inputs(sh)
+    bias = synth.quantize(synth.normal(83, (sh.n_out,)), "bf16")
+    xd, Rd, Ld, dyd, bd = (_dev(a, "bf16") for a in (x, R, L, dy, bias))
+    want = oracle.bwd(dy, x, R, L, rd)
+    y, saved = B.monarch_fwd_bias_save(xd, Rd, Ld, bd, flags=flags)
+    got = [("y", B.monarch_fwd_ws(xd, Rd, Ld, flags=flags), oracle.fwd(x, R, L, rd)), ("y_bias", y, oracle.fwd_bias(x, R, L, bias, rd)),
+           ("xM", B.monarch_fwd_t(dyd, Rd, Ld, flags=flags), oracle.fwd_t(dy, R, L, rd))]
+    got += zip(("dx", "dR", "dL"), B.monarch_bwd(dyd, xd, Rd, Ld, flags=flags), want)
+    got += zip(("dx_saved", "dR_saved", "dL_saved"), B.monarch_bwd_saved(dyd, xd, saved, Rd, Ld, flags=flags)[:3], want)
+    for name, g, w in got:
+        err = parity_util.rel_fro(g.float().cpu().numpy(), w)
+        assert err <= ONE_ROUNDING, "%s.%s: %.3e" % (sh.name, name, err)
+    for name, g, w in zip(("dR32", "dL32"), B.monarch_bwd(dyd, xd, Rd, Ld, flags=flags | B.MONARCH_FLAG_WGRAD_F32)[1:], want[1:]):
+        err = parity_util.rel_fro(g.cpu().numpy(), w)
+        assert err <= 1e-5, "%s.%s: %.3e" % (sh.name, name, err)
