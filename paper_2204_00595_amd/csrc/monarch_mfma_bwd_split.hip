@@ -282,9 +282,11 @@ Plan make_plan(const Problem& pb)
 
 // Up to 2560 rows, 40 row tiles of the wide backward, which takes nearly the same time for any number of them (1024 -> 4096 -> 1024
 // training step: 200 rows 240 and 101 us, 2000 rows 292 and 229, 3000 rows 328 and 310; 768 -> 3072 -> 768: 213 and 174, 235 and 241
-// at 2000 and 3000 rows).  Where the other choice is the shape-generic kernel (width 384) up to 4096.
+// at 2000 and 3000 rows).  Where the other choice is the shape-generic bf16 kernel (width 384) up to 4096.  Not where it is the
+// shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors between the factors in fp32.
 bool bwd_split_preferred(const Problem& pb)
 {
+    if (!bwd_wide_supported(pb) && !tiled_bwd_supported(pb)) return false;
     return pb.dtype == 1 && pb.k == 4 && !pb.perm_b() && pb.p % 32 == 0 && pb.q % 32 == 0 && pb.s % 32 == 0 && pb.p <= 1024 &&
            pb.s <= 1024 && pb.q <= 256 && pb.B > 0 && pb.B <= (bwd_wide_supported(pb) ? 2560 : 4096) && make_plan(pb).ok;
 }

@@ -112,3 +112,17 @@ def test_vector_between_the_factors_keeps_32_bits(case, reading):
     for name, g, w in zip(("dR32", "dL32"), B.monarch_bwd(dyd, xd, Rd, Ld, flags=flags | B.MONARCH_FLAG_WGRAD_F32)[1:], want[1:]):
         err = parity_util.rel_fro(g.cpu().numpy(), w)
         assert err <= 1e-5, "%s.%s: %.3e" % (sh.name, name, err)
+
+
+# four-block shapes with a bf16 forward whose backward has no bf16 kernel: fp32 between the factors for short batches too
+@pytest.mark.parametrize("case", [(1, 4, 1024, 256, 1024), (200, 4, 32, 256, 1024), (2560, 4, 1024, 256, 32)], ids=str)
+def test_backward_keeps_32_bits_on_short_batches(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    sh = synth.Shape("bits_%s" % (case,), "bf16", *case, config=920 + parity_util.stable_seed(str(case)))
+    x, R, L, dy = synth.make_inputs(sh)
+    want = oracle.bwd(dy, x, R, L)
+    for name, g, w in zip(("dx", "dR", "dL"), B.monarch_bwd(*(_dev(a, "bf16") for a in (dy, x, R, L))), want):
+        err = parity_util.rel_fro(g.float().cpu().numpy(), w)
+        assert err <= ONE_ROUNDING, "%s.%s: %.3e" % (sh.name, name, err)
