@@ -141,3 +141,17 @@ def test_packed_weights_are_only_read(dims):
                                 ws.data_ptr(), ws.numel(), B.MONARCH_FLAG_WS_PACKED)
     assert rc == B.MONARCH_OK
     check("y_abi", y, oracle.fwd(x, R, L))
+
+
+# Up to 256 rows the chunks of the batch are summed in fp32: bf16 gradients are the fp32 ones, rounded once.
+@pytest.mark.parametrize("case", [(64, 64, 64, 64), (65, 192, 192, 768), (256, 256, 256, 1024), (256, 96, 96, 384), (200, 512, 128, 128)], ids=str)
+def test_short_batch_gradients_are_rounded_once(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, p, q, s = case
+    sh = synth.Shape("once_%s" % (case,), "bf16", rows, 4, p, q, s, config=840 + parity_util.stable_seed(str(case)))
+    x, R, L, dy = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in synth.make_inputs(sh))
+    narrow, wide = B.monarch_bwd(dy, x, R, L), B.monarch_bwd(dy, x, R, L, flags=B.MONARCH_FLAG_WGRAD_F32)
+    for name, a, b in zip(("dx", "dR", "dL"), narrow, wide):
+        assert torch.equal(a, b.to(torch.bfloat16)), name
