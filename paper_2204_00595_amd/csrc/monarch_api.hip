@@ -109,6 +109,23 @@ size_t bwd_need(const Problem& pb, Family fam)
     return bwd_kernel_need(pb, fam) + colsum_workspace(pb);
 }
 
+// The kernels' share of a backward workspace of `bytes` bytes, (size_t)-1 if that is too short.  The chunked weight gradients of short batches
+// and of the shape-generic contractions want more room for a short batch than for a long one; with less they take fewer chunks, so
+// that a workspace of the largest batch serves every smaller one (a trainer's last, shorter batch).  The SIMT kernels need next to
+// nothing and are the last resort.
+size_t bwd_kernel_room(const Problem& pb, Family& fam, size_t bytes)
+{
+    const size_t tail = colsum_workspace(pb), room = bytes < tail ? 0 : (bytes - tail) / 256 * 256;
+    const size_t least = align_up(fam == FAM_MFMA ? mfma_bwd_least(pb) : fam == FAM_OPS ? ops_bwd_least(pb) : bwd_kernel_need(pb, fam), 256);
+    if (bytes >= tail && room >= least) {
+        const size_t need = bwd_kernel_need(pb, fam);
+        return room < need ? room : need;
+    }
+    if (fam != FAM_OPS || !generic_bwd_supported(pb)) return (size_t)-1;
+    fam = FAM_GENERIC;
+    return bwd_kernel_room(pb, fam, bytes);
+}
+
 bool aligned(const void* p, size_t a) { return ((uintptr_t)p % a) == 0; }
 
 __global__ void empty_kernel() {}
@@ -209,7 +226,7 @@ int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* save
     if (!aligned(dy, 16) || !aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(dx, 16) ||
         !aligned(dR, 16) || !aligned(dL, 16) || !aligned(dbias, 16))
         return MONARCH_ERR_INVALID;
-    const Family fam = pick_bwd(pb);
+    Family fam = pick_bwd(pb);
     if (fam == FAM_NONE) return MONARCH_ERR_UNSUPPORTED;
     if (saved) {  // ignored by the kernel families that recompute
         const size_t sneed = monarch_saved_bytes(batch, n_in, k, q, s, dtype, flags);
@@ -218,11 +235,12 @@ int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* save
             pb.saved = const_cast<void*>(saved);
         }
     }
-    const size_t need = bwd_need(pb, fam);
-    if (!workspace || workspace_bytes < need || !aligned(workspace, 256)) return MONARCH_ERR_WORKSPACE;
+    if (!workspace || !aligned(workspace, 256)) return MONARCH_ERR_WORKSPACE;
+    pb.ws_bytes = bwd_kernel_room(pb, fam, workspace_bytes);
+    if (pb.ws_bytes == (size_t)-1) return MONARCH_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (dbias) {
-        void* cws = (char*)workspace + bwd_kernel_need(pb, fam);
+        void* cws = (char*)workspace + pb.ws_bytes;
         if (batch > 0 && (fam == FAM_OPS || (fam == FAM_MFMA && mfma_bwd_fuses_dbias(pb)))) {
             pb.dbias = dbias;  // computed with the backward's own launches
             pb.colsum_ws = cws;

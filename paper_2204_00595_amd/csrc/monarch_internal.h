@@ -17,7 +17,7 @@ struct Problem {
     void* colsum_ws = nullptr;   // backward only: colsum_workspace() bytes for the bias gradient's partial rows
     int act = 0;                 // forward only: 1 = the output is gelu(product + bias)
     void* y_pre = nullptr;       // forward with act: the value before the nonlinearity also goes here (may be null)
-    size_t ws_bytes = 0;         // forward with a workspace: its size
+    size_t ws_bytes = 0;         // forward with a workspace: its size; backward: bytes of the kernels' own area
     void* mid = nullptr;         // forward on packed weights, which it only reads: fwd_split_mid_bytes() of the call's own (may be null)
     const void* x_pre = nullptr; // backward only: the layer's input is gelu(x_pre); dx is returned with respect to x_pre
     int n_out() const { return k * s; }
@@ -60,6 +60,7 @@ int ops_fwd(const Problem& pb, const void* x, const void* R, const void* L, void
 size_t ops_fwd_t_workspace(const Problem& pb);
 int ops_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 size_t ops_bwd_workspace(const Problem& pb);
+size_t ops_bwd_least(const Problem& pb);  // what the call cannot do without; with less than the above it takes fewer batch chunks
 int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL,
             void* ws, hipStream_t st);  // pb.saved (may be null): U as ops_fwd left it
 
@@ -122,6 +123,7 @@ int launch_dft_factors(void* R, void* L, int m, int inverse, hipStream_t st);
 bool mfma_fwd_supported(const Problem& pb);
 bool mfma_bwd_supported(const Problem& pb);
 size_t mfma_bwd_workspace(const Problem& pb);
+size_t mfma_bwd_least(const Problem& pb);
 const char* mfma_fwd_name(const Problem& pb);
 const char* mfma_bwd_name(const Problem& pb);
 int mfma_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, hipStream_t st);
@@ -177,6 +179,7 @@ int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, co
 // the same on short batches, one launch per adjoint factor (monarch_mfma_bwd_split.hip); blocks that are multiples of 32
 bool bwd_split_preferred(const Problem& pb);
 size_t bwd_split_workspace(const Problem& pb);
+size_t bwd_split_least(const Problem& pb);  // as ops_bwd_least
 int bwd_split(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL,
               void* ws, hipStream_t st);
 

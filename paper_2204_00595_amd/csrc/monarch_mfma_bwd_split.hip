@@ -252,7 +252,8 @@ void fill_descs(const Problem& pb, WgradDesc& dl, WgradDesc& dr)
     dr.ldb = pb.n_in; dr.b_g = pb.p; dr.b_seg = 0; dr.seg_w = pb.p;
     dr.M = pb.q; dr.N = pb.p; dr.G = 4; dr.rows = pb.B;
 }
-Plan make_plan(const Problem& pb)
+// `room`: bytes there are; a plan with one chunk may need more
+Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 {
     Plan pl{};
     WgradDesc dl, dr;
@@ -264,18 +265,20 @@ Plan make_plan(const Problem& pb)
     const int64_t most = (pb.B + 63) / 64;
     z = z > most ? most : z;
     z = z < 1 ? 1 : z;
-    pl.rows_per_chunk = (int)(((pb.B + z - 1) / z + 63) / 64 * 64);
-    pl.nz = (int)((pb.B + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
     const size_t act = align_up((size_t)pb.B * pb.kq() * 2, 256);
-    size_t off = 0;
-    pl.y1 = off; off += act;
-    pl.du = off; off += act;
-    pl.lt = off; off += align_up(pb.n_L() * 2, 256);
-    pl.rt = off; off += align_up(pb.n_R() * 2, 256);
-    pl.partL = off; off += align_up((size_t)pl.nz * pb.n_L() * 4, 256);
-    pl.partR = off; off += align_up((size_t)pl.nz * pb.n_R() * 4, 256);
-    pl.total = off;
-    return pl;
+    for (;; z = pl.nz - 1) {
+        pl.rows_per_chunk = (int)(((pb.B + z - 1) / z + 63) / 64 * 64);
+        pl.nz = (int)((pb.B + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
+        size_t off = 0;
+        pl.y1 = off; off += act;
+        pl.du = off; off += act;
+        pl.lt = off; off += align_up(pb.n_L() * 2, 256);
+        pl.rt = off; off += align_up(pb.n_R() * 2, 256);
+        pl.partL = off; off += align_up((size_t)pl.nz * pb.n_L() * 4, 256);
+        pl.partR = off; off += align_up((size_t)pl.nz * pb.n_R() * 4, 256);
+        pl.total = off;
+        if (pl.total <= room || pl.nz == 1) return pl;
+    }
 }
 
 }  // namespace
@@ -292,11 +295,12 @@ bool bwd_split_preferred(const Problem& pb)
 }
 
 size_t bwd_split_workspace(const Problem& pb) { return make_plan(pb).total; }
+size_t bwd_split_least(const Problem& pb) { return make_plan(pb, 0).total; }
 
 int bwd_split(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL, void* ws,
               hipStream_t st)
 {
-    const Plan pl = make_plan(pb);
+    const Plan pl = make_plan(pb, pb.ws_bytes);
     if (!pl.ok) return -2;
     char* w = (char*)ws;
     uint16_t *Y1 = (uint16_t*)(w + pl.y1), *dU = (uint16_t*)(w + pl.du), *LT = (uint16_t*)(w + pl.lt), *RT = (uint16_t*)(w + pl.rt);

@@ -636,7 +636,8 @@ struct WgradPlan {
     int nz;
     int64_t rows;  // per chunk
 };
-WgradPlan wgrad_plan(const Problem& pb)
+size_t part_bytes(const Problem& pb, int nz) { return align_up((size_t)nz * (pb.n_R() + pb.n_L()) * 4, 256); }
+WgradPlan wgrad_plan(const Problem& pb, size_t room = SIZE_MAX)  // room: bytes for the partial sums; one chunk is the least
 {
     constexpr int KC = 32;
     const int M[2] = {pb.s, pb.q}, N[2] = {pb.q, pb.p};
@@ -656,9 +657,11 @@ WgradPlan wgrad_plan(const Problem& pb)
     int64_t nz = tiles(1024, (int)t);
     if (nz > 1) nz = tiles(nz, 8) * 8;  // whole sets of the eight XCDs
     nz = nz > most ? most : nz;
-    pl.rows = tiles(tiles(rows, (int)nz), KC) * KC;
-    pl.nz = (int)tiles(rows, (int)pl.rows);
-    return pl;
+    for (;; nz = pl.nz - 1) {
+        pl.rows = tiles(tiles(rows, (int)nz), KC) * KC;
+        pl.nz = (int)tiles(rows, (int)pl.rows);
+        if (part_bytes(pb, pl.nz) <= room || pl.nz == 1) return pl;
+    }
 }
 
 size_t mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B > 0 ? pb.B : 1) * pb.kq() * sizeof(float), 256); }
@@ -725,11 +728,8 @@ int ops_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, vo
     return pb.dtype == 0 ? fwd_t_typed<float>(pb, x, R, L, y, dU, st) : fwd_t_typed<bf16_t>(pb, x, R, L, y, dU, st);
 }
 
-size_t ops_bwd_workspace(const Problem& pb)
-{
-    const WgradPlan pl = wgrad_plan(pb);
-    return 2 * mid_bytes(pb) + align_up((size_t)pl.nz * (pb.n_R() + pb.n_L()) * 4, 256);
-}
+size_t ops_bwd_workspace(const Problem& pb) { return 2 * mid_bytes(pb) + part_bytes(pb, wgrad_plan(pb).nz); }
+size_t ops_bwd_least(const Problem& pb) { return 2 * mid_bytes(pb) + part_bytes(pb, 1); }
 
 int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL,
             void* ws, hipStream_t st)
@@ -740,7 +740,7 @@ int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, con
         if (rc) return rc;
         return f ? launch_fill_zero_f32((float*)dL, pb.n_L(), st) : launch_fill_zero_u16((uint16_t*)dL, pb.n_L(), st);
     }
-    const WgradPlan pl = wgrad_plan(pb);
+    const WgradPlan pl = wgrad_plan(pb, pb.ws_bytes - 2 * mid_bytes(pb));
     ColsumJob cj{};
     if (pb.dbias) {
         cj = make_colsum_job(pb, dy, pb.dbias, pb.colsum_ws);

@@ -126,3 +126,38 @@ def test_backward_keeps_32_bits_on_short_batches(case):
     for name, g, w in zip(("dx", "dR", "dL"), B.monarch_bwd(*(_dev(a, "bf16") for a in (dy, x, R, L))), want):
         err = parity_util.rel_fro(g.float().cpu().numpy(), w)
         assert err <= ONE_ROUNDING, "%s.%s: %.3e" % (sh.name, name, err)
+
+
+# A workspace of the largest batch serves a shorter last one, also where the shorter one asks for more: four-block layers on both
+# sides of the limits of the short-batch kernels (wide: 2560 rows, shape-generic bf16: 4096), the shape-generic contractions where a
+# longer batch has fewer chunks, and those with a workspace that only the SIMT kernels can use.
+LAST = [((128, 128, 512), 4, 2561, 2560, "bf16"), ((192, 192, 192), 4, 2600, 1500, "bf16"), ((96, 96, 96), 4, 4097, 4096, "bf16"),
+        ((192, 192, 768), 4, 2049, 2048, "f32"), ((101, 37, 16), 8, 6145, 6144, "bf16"), ((192, 192, 36), 4, 0, 3072, "bf16")]
+
+
+@pytest.mark.parametrize("case", LAST, ids=str)
+def test_workspace_of_the_largest_batch_serves_a_shorter_one(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    (p, q, s), k, most, rows, dtype = case
+    code = 0 if dtype == "f32" else 1
+    sh = synth.Shape("last_%s" % (case,), dtype, rows, k, p, q, s, config=940 + parity_util.stable_seed(str(case)))
+    size = B.monarch_bwd_workspace_bytes(rows, sh.n_in, k, q, s, code)
+    if most:
+        have = B.monarch_bwd_workspace_bytes(most, sh.n_in, k, q, s, code)
+    else:  # what the SIMT kernels ask for
+        have = B.monarch_bwd_workspace_bytes(rows, sh.n_in, k, q, s, code, B.MONARCH_FLAG_GENERIC)
+    assert have < size
+    x, R, L, dy = synth.make_inputs(sh)
+    want = oracle.bwd_bias(dy, x, R, L)
+    xd, Rd, Ld, dyd = (_dev(a, dtype) for a in (x, R, L, dy))
+    guard = 4096
+    ws = torch.full((have + guard,), 0xA5, dtype=torch.uint8, device="cuda")
+    got = B.monarch_bwd_bias(dyd, xd, Rd, Ld, workspace=ws[:have])
+    for name, g, w in zip(("dx", "dR", "dL", "dbias"), got, want):
+        parity_util.check("%s.%s" % (sh.name, name), g.float().cpu().numpy(), w, TOL[dtype])
+    assert bool((ws[have:] == 0xA5).all())
+    with pytest.raises(B.MonarchError) as e:  # not the partial rows of the bias gradient alone
+        B.monarch_bwd_bias(dyd, xd, Rd, Ld, workspace=ws[:256])
+    assert e.value.status == B.MONARCH_ERR_WORKSPACE
