@@ -602,7 +602,9 @@ MONARCH_CALL(py_linear, 5)
     const Tensor x = tensor_arg(a[0], "x"), R = tensor_arg(a[1], "R"), L = tensor_arg(a[2], "L");
     c10::optional<Tensor> bias;
     if (a[3] != Py_None) bias = tensor_arg(a[3], "bias");
-    const bool save = bool_arg(a[4]);
+    // nothing is kept where no backward follows (LinearFn::forward itself always runs without gradients)
+    const bool save = bool_arg(a[4]) && at::GradMode::is_enabled() &&
+                      (x.requires_grad() || R.requires_grad() || L.requires_grad() || (bias && bias->requires_grad()));
     return THPVariable_Wrap(unlocked([&] { return LinearFn::apply(x, R, L, bias, save); }));
 MONARCH_END
 

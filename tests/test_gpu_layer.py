@@ -1,0 +1,60 @@
+"""MonarchLinear and the binding's checks around it: what a call without gradients keeps."""
+import pytest
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+
+@pytest.fixture(scope="module")
+def B():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding
+    return binding
+
+
+def layer_of(p, q, s, k=4, dtype=torch.bfloat16, bias=True):
+    from paper_2204_00595_amd import autograd
+    torch.manual_seed(5)
+    layer = autograd.MonarchLinear(k * p, k * s, nblocks=k, q=q, bias=bias, device="cuda", dtype=dtype)
+    if bias:
+        torch.nn.init.normal_(layer.bias)
+    return layer
+
+
+# a shape with a packed forward, and one of the shape-generic contractions; both keep the vector in a training step
+@pytest.mark.parametrize("bias", [True, False], ids=["bias", "no_bias"])
+@pytest.mark.parametrize("dims", [(192, 192, 192), (49, 33, 64)], ids=str)
+def test_layer_without_gradients_keeps_nothing(B, dims, bias):
+    p, q, s = dims
+    rows = 3000
+    layer = layer_of(p, q, s, bias=bias)
+    x = torch.randn((rows, 4 * p), device="cuda").bfloat16()
+    saved = B.monarch_saved_bytes(rows, 4 * p, 4, q, s, B.MONARCH_BF16)
+    assert saved > 0
+    if bias:
+        want = B.monarch_fwd_bias(x, layer.R.detach(), layer.L.detach(), layer.bias.detach())
+    else:
+        want = B.monarch_fwd_ws(x, layer.R.detach(), layer.L.detach())
+
+    def peak():
+        torch.cuda.synchronize()
+        torch.cuda.reset_peak_memory_stats()
+        before = torch.cuda.memory_allocated()
+        y = layer(x)
+        torch.cuda.synchronize()
+        return y, torch.cuda.max_memory_allocated() - before
+
+    y, most = peak()   # a training step's forward: y and the vector
+    assert y.requires_grad and most >= y.numel() * 2 + saved
+    room = y.numel() * 2 + B.monarch_fwd_workspace_bytes(rows, 4 * p, 4, q, s, B.MONARCH_BF16) + 2048  # the allocator rounds up to 512
+    del y
+    for guard in (torch.no_grad, torch.inference_mode):
+        with guard():
+            y, most = peak()
+        assert torch.equal(y, want) and most <= room
+        del y
+    for par in layer.parameters():
+        par.requires_grad_(False)
+    y, most = peak()   # a frozen layer
+    assert not y.requires_grad and torch.equal(y, want) and most <= room
