@@ -411,10 +411,15 @@ struct LinearFn : torch::autograd::Function<LinearFn> {
         if (x.scalar_type() != at::kBFloat16 || R.size(0) != 4 || p % 64 || q % 64 || s % 64) return true;
         return rows > 2048 && (s <= p || rows <= 8192);
     }
+    // (rows, width) from any leading dimensions; their product must be the number of rows, else the last one is not `width`
     static Tensor rows_of(const Tensor& t, int64_t width)
     {
-        if (t.dim() == 2 && t.is_contiguous()) return t;
-        return t.reshape({-1, width}).contiguous();
+        if (t.dim() == 2 && t.size(1) == width && t.is_contiguous()) return t;
+        const Tensor rows = t.reshape({-1, width}).contiguous();
+        int64_t leading = 1;
+        for (int64_t d = 0; d + 1 < t.dim(); ++d) leading *= t.size(d);
+        TORCH_CHECK(rows.size(0) == leading, "the last dimension of the input must be ", width, ", got shape ", t.sizes());
+        return rows;
     }
     static Tensor forward(torch::autograd::AutogradContext* ctx, const Tensor& x, const Tensor& R, const Tensor& L,
                           const c10::optional<Tensor>& bias, bool save_intermediate)
@@ -431,6 +436,7 @@ struct LinearFn : torch::autograd::Function<LinearFn> {
         if (x.dim() == 2) return r.y;
         ctx->saved_data["shape"] = x.sizes().vec();
         std::vector<int64_t> shape = x.sizes().vec();
+        if (shape.empty()) shape.resize(1);
         shape.back() = r.y.size(1);
         return r.y.view(shape);
     }

@@ -58,3 +58,29 @@ def test_layer_without_gradients_keeps_nothing(B, dims, bias):
         par.requires_grad_(False)
     y, most = peak()   # a frozen layer
     assert not y.requires_grad and torch.equal(y, want) and most <= room
+
+
+# what is not (..., width) is refused, however it lies in memory
+@pytest.mark.parametrize("shape", [(10, 384), (384, 10), (10, 2, 384), (5, 2, 768, 1), (10, 769), (10, 1536)], ids=str)
+def test_layer_refuses_inputs_of_another_width(B, shape):
+    layer = layer_of(192, 192, 192)
+    x = torch.randn(shape, device="cuda").bfloat16()
+    for t in (x, x.transpose(0, 1).contiguous().transpose(0, 1), x.requires_grad_(True)):
+        assert tuple(t.shape) == shape
+        with pytest.raises((RuntimeError, ValueError)):
+            layer(t)
+
+
+def test_layer_takes_any_leading_dimensions_and_strides(B):
+    layer = layer_of(192, 192, 576)
+    x = torch.randn((6, 768), device="cuda").bfloat16()
+    want = layer(x)
+    views = [(x[:1].reshape(768), want[:1].reshape(2304)), (x.reshape(3, 2, 768), want.reshape(3, 2, 2304)),
+             (x.t().contiguous().t(), want), (x.reshape(2, 3, 768).transpose(0, 1), want.reshape(2, 3, 2304).transpose(0, 1)),
+             (x[:0], want[:0]), (x[:0].reshape(0, 5, 768), want[:0].reshape(0, 5, 2304))]
+    for view, y in views:
+        view = view.detach().requires_grad_(True)
+        out = layer(view)
+        assert out.shape == y.shape and torch.equal(out, y)
+        out.backward(torch.ones_like(out))
+        assert view.grad.shape == view.shape
