@@ -213,8 +213,15 @@ Layer fwd_layer(const char* name, const Tensor& x, const Tensor& R, const Tensor
     y = out(y, "y", {sh.B, sh.n_out()}, sh.dtype, sh.device);
     if (want_pre || y_pre.defined()) y_pre = out(y_pre, "y_pre", {sh.B, sh.n_out()}, sh.dtype, sh.device);
     if (!ws.defined()) {
+        if (flags & MONARCH_FLAG_WS_PACKED) {
+            // An empty batch asks whether the shape cannot do without a workspace; elsewhere the flag has nothing to refer to.
+            const int rc = monarch_fwd_ws(ptr(x), ptr(R), ptr(L), ptr(y), 0, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(),
+                                          w.stream(), nullptr, 0, flags);
+            TORCH_CHECK_VALUE(rc != MONARCH_ERR_WORKSPACE, "MONARCH_FLAG_WS_PACKED needs the workspace of the earlier call");
+            if (rc) raise_status(rc, name);
+            flags &= ~MONARCH_FLAG_WS_PACKED;
+        }
         const size_t need = monarch_fwd_workspace_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
-        TORCH_CHECK_VALUE(!need || !(flags & MONARCH_FLAG_WS_PACKED), "MONARCH_FLAG_WS_PACKED needs the workspace of the earlier call");
         if (need) ws = w.scratch(need);
     }
     const Bytes b(ws);
@@ -267,6 +274,7 @@ Saved fwd_save(const Tensor& x, const Tensor& R, const Tensor& L, const Tensor& 
     if (bias.defined()) check(bias, "bias", {sh.n_out()}, sh.dtype, sh.device);
     y = out(y, "y", {sh.B, sh.n_out()}, sh.dtype, sh.device);
     const size_t need = monarch_saved_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
+    if (flags & MONARCH_FLAG_WS_PACKED) raise_status(MONARCH_ERR_INVALID, "monarch_fwd_save");
     // nothing to save for this shape: the forward that has a workspace (fp32, k = 64 blocks of 64, 12000 rows: 6050 us without
     // one, which is the SIMT kernels there, 290 with)
     if (!need) return Saved{fwd_layer("monarch_fwd_save", x, R, L, bias, Act::none, {}, false, y, {}, flags, st).y, Tensor()};

@@ -84,3 +84,28 @@ def test_layer_takes_any_leading_dimensions_and_strides(B):
         assert out.shape == y.shape and torch.equal(out, y)
         out.backward(torch.ones_like(out))
         assert view.grad.shape == view.shape
+
+
+# dims (p, q, s), k, dtype: shapes whose calls never find packed weights take the flag without a workspace and ignore it
+@pytest.mark.parametrize("case", [((49, 33, 64), 4, "f32"), ((49, 33, 64), 4, "bf16"), ((96, 96, 384), 4, "bf16"), ((7, 5, 9), 3, "f32"),
+                                  ((16, 16, 16), 16, "f32")], ids=str)
+def test_packed_flag_without_a_workspace_is_ignored_where_it_means_nothing(B, case):
+    (p, q, s), k, dtype = case
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    layer = layer_of(p, q, s, k=k, dtype=dt)
+    x = torch.randn((33, k * p), device="cuda").to(dt)
+    R, L, bias = (t.detach() for t in (layer.R, layer.L, layer.bias))
+    assert torch.equal(B.monarch_fwd_ws(x, R, L, flags=B.MONARCH_FLAG_WS_PACKED), B.monarch_fwd_ws(x, R, L))
+    assert torch.equal(B.monarch_fwd_bias(x, R, L, bias, flags=B.MONARCH_FLAG_WS_PACKED), B.monarch_fwd_bias(x, R, L, bias))
+    with pytest.raises(B.MonarchError):
+        B.monarch_fwd_save(x, R, L, flags=B.MONARCH_FLAG_WS_PACKED)
+
+
+@pytest.mark.parametrize("case", [((192, 192, 192), 4, "bf16"), ((64, 64, 64), 64, "bf16"), ((32, 32, 32), 3, "f32")], ids=str)
+def test_packed_flag_without_a_workspace_is_refused_where_one_is_needed(B, case):
+    (p, q, s), k, dtype = case
+    dt = torch.float32 if dtype == "f32" else torch.bfloat16
+    layer = layer_of(p, q, s, k=k, dtype=dt)
+    x = torch.randn((33, k * p), device="cuda").to(dt)
+    with pytest.raises(ValueError):
+        B.monarch_fwd_ws(x, layer.R.detach(), layer.L.detach(), flags=B.MONARCH_FLAG_WS_PACKED)
