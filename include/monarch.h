@@ -378,7 +378,9 @@ int monarch_dft_factors(void* R, void* L, int m, int inverse, void* stream);
 
 /* Name of the kernel family the dispatcher picks for this problem: pass 0 = forward
  * (monarch_fwd / monarch_fwd_ex), 1 = backward, 2 = forward with workspace (monarch_fwd_ws),
- * 3 = transposed multiply (monarch_fwd_t).  Static string, never NULL ("invalid" / "unsupported" on bad input). */
+ * 3 = transposed multiply (monarch_fwd_t).  "generic_*" are the shape-generic kernels: with a workspace and blocks of 16 and
+ * more, contractions on the matrix cores, else the SIMT kernels.  Short batches of the bf16 four-block layers have kernels of
+ * their own, which are not named: the name is that of a long batch.  Static string, never NULL ("invalid" / "unsupported" on bad input). */
 const char* monarch_kernel_name(int pass, int n_in, int k, int q, int s,
                                 monarch_dtype dtype, unsigned flags);
 

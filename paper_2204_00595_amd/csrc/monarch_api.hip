@@ -611,7 +611,7 @@ int monarch_project(const void* A, void* R, void* L, int n, int m, monarch_dtype
 const char* monarch_kernel_name(int pass, int n_in, int k, int q, int s, monarch_dtype dtype, unsigned flags)
 {
     Problem pb;
-    int rc = make_problem(pb, 1, n_in, k, q, s, (int)dtype, flags);
+    int rc = make_problem(pb, 0, n_in, k, q, s, (int)dtype, flags);  // no batch: not the kernels of short ones
     if (rc == MONARCH_ERR_UNSUPPORTED) return "unsupported";
     if (rc || pass < 0 || pass > 3) return "invalid";
     if (pass == 3) {

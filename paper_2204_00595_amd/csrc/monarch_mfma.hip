@@ -41,7 +41,6 @@ bool mfma_fwd_keeps_packed(const Problem& pb) { return fwd_frag_supported(pb) ||
 const char* mfma_fwd_ws_name(const Problem& pb)
 {
     if (fwd_frag_supported(pb)) return "mfma_fwd_frag_bf16";
-    if (fwd_packed(pb)) return "mfma_fwd_split_bf16";
     if (sq64_supported(pb)) return "mfma_fwd_sq64_packed_bf16";
     if (real32_mfma_supported(pb)) return "mfma_fwd_stages_f32";
     return "unsupported";

@@ -538,3 +538,15 @@ def test_forward_on_shared_packed_weights_rejects_bad_arguments_without_a_gpu(bi
     assert call(ws_bytes=need - 1) == binding.MONARCH_ERR_WORKSPACE
     for shape in (dict(n_in=384, q=96, s=384), dict(dtype=0), dict(flags=binding.MONARCH_FLAG_PERM_B)):   # nothing is kept packed
         assert call(**shape) == binding.MONARCH_ERR_UNSUPPORTED
+
+
+def test_kernel_name_does_not_depend_on_the_kernels_of_short_batches(binding):
+    def names(n_in, k, q, s, dtype, flags=0):
+        return [binding.monarch_kernel_name(ps, n_in, k, q, s, dtype, flags) for ps in (0, 1, 2, 3)]
+
+    # width 384: a forward with packed weights for up to 8192 rows only
+    assert names(384, 4, 96, 384, 1) == ["mfma_fwd_tiled_bf16", "mfma_bwd_tiled_bf16", "mfma_fwd_tiled_bf16", "mfma_fwd_t_tiled_bf16"]
+    # a bf16 forward, but vectors too long for the bf16 backward
+    assert names(4096, 4, 256, 1024, 1) == ["mfma_fwd_tiled_bf16", "generic_bwd", "mfma_fwd_tiled_bf16", "generic_fwd_t"]
+    # the shape-generic kernels, with and without a workspace
+    assert names(196, 4, 49, 64, 1) == names(768, 4, 192, 192, 0) == ["generic_fwd", "generic_bwd", "generic_fwd", "generic_fwd_t"]
