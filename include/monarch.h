@@ -119,7 +119,8 @@ int monarch_fwd_ws(const void* x, const void* R, const void* L, void* y,
  * memory is an array inside the library that exists from program load: MONARCH_STATIC_WORKSPACE_BYTES
  * bytes per GPU, held by every GPU the library runs on until the process ends.  The call
  * allocates and frees nothing.  Shapes whose monarch_fwd_workspace_bytes(...) exceeds that limit
- * return MONARCH_ERR_WORKSPACE (every shape with a packed-weight kernel in this build fits);
+ * return MONARCH_ERR_WORKSPACE (every shape with a packed-weight kernel in this build fits), except that
+ * the shape-generic kernels run slices of the batch that fit, one after the other, with the same result;
  * MONARCH_FLAG_WS_PACKED is refused with MONARCH_ERR_INVALID, because the array belongs to no
  * caller between calls.  All calls on one GPU share the array and overwrite it: two calls that may
  * overlap in time on one GPU (different streams, different threads) race and must be serialised by

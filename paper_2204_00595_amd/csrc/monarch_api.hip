@@ -155,6 +155,24 @@ int static_workspace(void** out)
     return MONARCH_OK;
 }
 
+// monarch_fwd_static on the shape-generic contractions where the vector between the factors exceeds the array.  A row's result does
+// not depend on the rows beside it, so slices of the batch, one after the other on the stream, give what one call on the whole gives.
+int fwd_static_slices(Problem pb, const void* x, const void* R, const void* L, void* y, hipStream_t st)
+{
+    if (pb.flags & MONARCH_FLAG_WGRAD_F32) return MONARCH_ERR_INVALID;  // backward-only flag
+    if (!x || !R || !L || !y || !aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(y, 16)) return MONARCH_ERR_INVALID;
+    void* U = nullptr;
+    if (int rc = static_workspace(&U)) return rc;
+    const int64_t batch = pb.B, fit = (int64_t)(kStaticWorkspaceBytes / (pb.kq() * sizeof(float)));  // two rows at least (ops_supported)
+    const int64_t rows = fit >= 256 ? fit / 256 * 256 : fit;
+    for (int64_t b = 0; b < batch; b += rows) {
+        pb.B = batch - b < rows ? batch - b : rows;
+        const int rc = ops_fwd(pb, (const char*)x + (size_t)b * pb.n_in * pb.esize(), R, L, (char*)y + (size_t)b * pb.n_out() * pb.esize(), U, st);
+        if (rc) return rc;
+    }
+    return MONARCH_OK;
+}
+
 // The affine layer, optionally followed by the nonlinearity: y = act(x M^T + bias).  Whatever the chosen
 // kernel does not do in its own epilogue follows as a pass over y.
 int fwd_layer(const void* x, const void* R, const void* L, const void* bias, bool act, void* y_pre, void* y,
@@ -325,11 +343,11 @@ int monarch_fwd_static(const void* x, const void* R, const void* L, void* y, int
                        int q, int s, monarch_dtype dtype, void* stream, unsigned flags)
 {
     if (flags & MONARCH_FLAG_WS_PACKED) return MONARCH_ERR_INVALID;  // the shared array is nobody's to keep between calls
-    size_t need = monarch_fwd_workspace_bytes(batch, n_in, k, q, s, dtype, flags);
+    const size_t need = monarch_fwd_workspace_bytes(batch, n_in, k, q, s, dtype, flags);
     if (need > kStaticWorkspaceBytes) {
         Problem pb;
         if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags) || !fwd_uses_ops(pb)) return MONARCH_ERR_WORKSPACE;
-        need = 0;  // the shape-generic kernels can do without
+        return fwd_static_slices(pb, x, R, L, y, (hipStream_t)stream);
     }
     void* ws = nullptr;
     if (need > 0) {

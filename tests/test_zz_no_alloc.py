@@ -69,3 +69,21 @@ def test_static_workspace_forward_rejects_what_it_cannot_serve():
     with pytest.raises(binding.MonarchError) as e:
         binding.monarch_fwd_static(x, R, R, y, flags=binding.MONARCH_FLAG_WS_PACKED)
     assert e.value.status == binding.MONARCH_ERR_INVALID
+
+
+# the vector between the factors exceeds the array: slices of the batch (the last one short; with k q = 9045, of 231 rows whose bytes
+# are no multiple of 16)
+@pytest.mark.parametrize("case", [("f32", 3001, 4, 192, 192, 192), ("bf16", 20000, 4, 49, 49, 64), ("bf16", 500, 201, 17, 45, 16)], ids=str)
+def test_static_workspace_forward_in_slices_matches_the_workspace_forward(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding
+    dtype, rows, k, p, q, s = case
+    sh = synth.Shape("slices_%s" % (case,), dtype, rows, k, p, q, s, config=95)
+    x, R, L, _ = synth.make_inputs(sh)
+    xd, Rd, Ld = (_dev(a, dtype) for a in (x, R, L))
+    assert binding.monarch_fwd_workspace_bytes(rows, sh.n_in, k, q, s, 0 if dtype == "f32" else 1) > binding.MONARCH_STATIC_WORKSPACE_BYTES
+    y = torch.full((rows + 1, sh.n_out), float("nan"), dtype=xd.dtype, device="cuda")
+    binding.monarch_fwd_static(xd, Rd, Ld, y[:rows])
+    assert torch.equal(y[:rows], binding.monarch_fwd_ws(xd, Rd, Ld)) and bool(y[rows:].isnan().all())
+    parity_util.check(sh.name, y[:rows].float().cpu().numpy(), oracle.fwd(x, R, L), TOL[dtype])
