@@ -161,3 +161,18 @@ def test_workspace_of_the_largest_batch_serves_a_shorter_one(case):
     with pytest.raises(B.MonarchError) as e:  # not the partial rows of the bias gradient alone
         B.monarch_bwd_bias(dyd, xd, Rd, Ld, workspace=ws[:256])
     assert e.value.status == B.MONARCH_ERR_WORKSPACE
+
+
+# batches of one chunk or a few, where a chunk's own sum is what errs; the SIMT kernels add 16 rows at a time
+@pytest.mark.parametrize("case", [(302, 8, 43, 43, 66), (389, 3, 21, 21, 85), (363, 8, 154, 21, 21), (329, 4, 96, 96, 384)], ids=str)
+def test_fp32_weight_gradients_are_as_exact_as_the_simt_kernels(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    sh = synth.Shape("exact_%s" % (case,), "f32", *case, config=960 + parity_util.stable_seed(str(case)))
+    x, R, L, dy = synth.make_inputs(sh)
+    want = oracle.bwd(dy, x, R, L)
+    args = [_dev(a, "f32") for a in (dy, x, R, L)]
+    for name, g, simt, w in zip(("dx", "dR", "dL"), B.monarch_bwd(*args), B.monarch_bwd(*args, flags=B.MONARCH_FLAG_GENERIC), want):
+        ours, theirs = parity_util.rel_fro(g.cpu().numpy(), w), parity_util.rel_fro(simt.cpu().numpy(), w)
+        assert ours <= 1.05 * theirs, "%s.%s: %.3e and %.3e" % (sh.name, name, ours, theirs)   # 5 %: the order of the SIMT atomics varies
