@@ -3,7 +3,8 @@
 ``monarch_linear(x, R, L, bias)`` is differentiable: its forward is ``monarch_fwd_bias`` (or, with
 ``save_intermediate=True`` and where it pays, ``monarch_fwd_bias_save``), its backward ``monarch_bwd_bias`` /
 ``monarch_bwd_saved``.  ``MonarchLinear`` holds the two factors (and the bias) as parameters.  Leading
-dimensions of ``x`` are flattened into the batch.  The autograd node is native (``csrc/monarch_torch.cpp``).
+dimensions of ``x`` are flattened into the batch.  The autograd node is native (``csrc/monarch_torch.cpp``), except while
+``torch.jit.trace`` records, which sees Python nodes only.
 Everything runs in the HIP kernels; there is no fallback for CPU tensors.
 """
 from __future__ import annotations
@@ -15,9 +16,31 @@ import torch
 from . import binding
 
 
+class _MonarchLinearFn(torch.autograd.Function):
+    """The native node for ``torch.jit.trace``, which records this one as an operation; of the native call it would record the
+    allocation of the output and nothing else.  The backward recomputes the vector between the factors."""
+
+    @staticmethod
+    def forward(ctx, x, R, L, bias):
+        x2 = x.reshape(-1, R.shape[0] * R.shape[2]).contiguous()
+        y = binding.monarch_fwd_ws(x2, R, L) if bias is None else binding.monarch_fwd_bias(x2, R, L, bias)
+        ctx.save_for_backward(x2, R, L)
+        ctx.has_bias, ctx.x_shape = bias is not None, x.shape
+        return y.reshape(*x.shape[:-1], y.shape[-1])
+
+    @staticmethod
+    def backward(ctx, dy):
+        x2, R, L = ctx.saved_tensors
+        dy2 = dy.reshape(-1, L.shape[0] * L.shape[1]).contiguous()
+        dx, dR, dL, dbias = binding.monarch_bwd_saved(dy2, x2, None, R, L, want_dbias=ctx.has_bias)
+        return dx.reshape(ctx.x_shape), dR, dL, dbias
+
+
 def monarch_linear(x: torch.Tensor, R: torch.Tensor, L: torch.Tensor, bias: torch.Tensor | None = None,
                    save_intermediate: bool = True) -> torch.Tensor:
     """y = x M^T (+ bias) with M = P L P^T R; differentiable in x, R, L and bias."""
+    if torch.jit.is_tracing():
+        return _MonarchLinearFn.apply(x, R, L, bias)
     return binding._native_calls.linear(x, R, L, bias, save_intermediate)
 
 

@@ -109,3 +109,23 @@ def test_packed_flag_without_a_workspace_is_refused_where_one_is_needed(B, case)
     x = torch.randn((33, k * p), device="cuda").to(dt)
     with pytest.raises(ValueError):
         B.monarch_fwd_ws(x, layer.R.detach(), layer.L.detach(), flags=B.MONARCH_FLAG_WS_PACKED)
+
+
+@pytest.mark.parametrize("bias", [True, False], ids=["bias", "no_bias"])
+def test_traced_layer_computes(B, bias):
+    """torch.jit.trace records the multiply itself: the traced layer follows its input, its weights and their gradients."""
+    layer = layer_of(192, 192, 576, bias=bias)
+    x, other, dy = (torch.randn(shape, device="cuda").bfloat16() for shape in ((2, 5, 768), (2, 5, 768), (2, 5, 2304)))
+    traced = torch.jit.trace(layer, x)
+    with torch.no_grad():
+        layer.R.mul_(0.5)
+        tn = torch.jit.trace(layer, x)
+        assert torch.equal(tn(other), layer(other))
+    a, b = (other.clone().requires_grad_(True) for _ in range(2))
+    ya, yb = traced(a), layer(b)
+    assert torch.equal(ya, yb)
+    pars = list(layer.parameters())
+    for g, w in zip(torch.autograd.grad(ya, [a] + pars, dy), torch.autograd.grad(yb, [b] + pars, dy)):
+        assert torch.equal(g, w)
+    with pytest.raises((RuntimeError, ValueError)):
+        torch.jit.trace(layer, torch.randn((20, 384), device="cuda").bfloat16())
