@@ -410,9 +410,13 @@ Grads c64_bwd(bool with_ws, const Tensor& dy, const Tensor& x, const Tensor& R, 
 struct LinearFn : torch::autograd::Function<LinearFn> {
     // Where keeping the vector pays, by the GPU time of a training step with bias, recomputed and kept: fp32 and odd blocks always
     // (192 x 192, four blocks, fp32, 12608 rows: one contraction of 53 us of 400 less).  The bf16 layers of four blocks that are
-    // multiples of 64 have other forwards for the call that keeps nothing: short batches are faster on those (256 x 1024, 200 rows
-    // 49 and 73 us, 1000 rows 80 and 89; 2500 rows 153 and 126), and so are wide outputs over long batches (192 x 768: 7000 rows
-    // 115 and 112, 16384 rows 174 and 180; 768 x 192: 182 and 158).
+    // multiples of 64 have other forwards for the call that keeps nothing.  Those of short batches (256 x 1024: 200 rows 49 and 73
+    // us, 1000 rows 80 and 89) lose their lead between 1500 and 2500 rows, the wider the layer the sooner (192 x 192: 2000 rows 54
+    // and 57, 2500 rows 57 and 56; 192 x 768: 1500 rows 69 and 68, 2500 rows 80 and 72).  Over long batches the packed forward wins
+    // for wide outputs, by most in the widest layer, whose crossing is the line (256 x 1024: 8192 rows 159 and 150, 9000 rows 162
+    // and 176, 12000 rows 185 and 196).  192 x 768 crosses at 11000 rows (8192 rows 113 and 109, 10000 rows 127 and 126, 12000 rows
+    // 135 and 137), 192 x 576 and 128 x 512 not up to 16384 (12000 rows 121 and 117; 92 and 87), which the line costs 3 to 5 %;
+    // outputs no wider than the input gain at every length (768 x 192, 16384 rows: 176 and 150).
     static bool keeps(const Tensor& x, const Tensor& R, const Tensor& L)
     {
         const int64_t rows = x.size(0), p = R.size(2), q = R.size(1), s = L.size(1);
