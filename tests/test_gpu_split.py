@@ -39,7 +39,7 @@ def test_short_batch_forward(case):
     check("y", y, want)
     again = B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED)
     assert torch.equal(y, again)
-    check("y_long", B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws[:packed], flags=B.MONARCH_FLAG_WS_PACKED), want)  # no room: the fused kernel
+    check("y_long", B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws[:packed], flags=B.MONARCH_FLAG_WS_PACKED), want)  # no room behind the packed weights
     check("y_bias", B.monarch_fwd_bias(xd, Rd, Ld, bd, workspace=ws), oracle.fwd_bias(x, R, L, bias))
     pre, act = B.monarch_fwd_bias_gelu(xd, Rd, Ld, bd, workspace=ws)
     check("pre", pre, oracle.fwd_bias(x, R, L, bias))
