@@ -155,3 +155,24 @@ def test_short_batch_gradients_are_rounded_once(case):
     narrow, wide = B.monarch_bwd(dy, x, R, L), B.monarch_bwd(dy, x, R, L, flags=B.MONARCH_FLAG_WGRAD_F32)
     for name, a, b in zip(("dx", "dR", "dL"), narrow, wide):
         assert torch.equal(a, b.to(torch.bfloat16)), name
+
+
+def test_calls_on_two_streams_share_packed_weights():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    sh = synth.Shape("streams", "bf16", 3000, 4, 256, 256, 1024, config=860)
+    x, R, L, _ = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in synth.make_inputs(sh))
+    ws = torch.empty(B.monarch_fwd_workspace_bytes(0, sh.n_in, 4, 256, 1024, 1), dtype=torch.uint8, device="cuda")
+    B.monarch_fwd_ws(x[:8], R, L, workspace=ws)
+    parts = [x[:8], x[8:520], x[520:]]   # of several batch sizes
+    want = [B.monarch_fwd_ws(p, R, L) for p in parts]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    got = []
+    for i in range(24):
+        with torch.cuda.stream(streams[i % 2]):
+            got.append(B.monarch_fwd_ws(parts[i % 3], R, L, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED))
+    torch.cuda.synchronize()
+    for i, y in enumerate(got):
+        assert torch.equal(y, want[i % 3]), i
