@@ -32,8 +32,9 @@
  *   y, dy  (batch, k*s)         L, dL  (k, s, q)
  * Element type is `dtype` for all of them: MONARCH_F32 = IEEE binary32,
  * MONARCH_BF16 = the upper 16 bits of a binary32 stored as uint16_t.  Products
- * are accumulated in fp32; in the bf16 path the on-chip intermediate between
- * the two stages is rounded to bf16 (nearest even) and each output is rounded
+ * are accumulated in fp32; in the bf16 path the intermediate between
+ * the two stages is rounded to bf16 (nearest even) -- not in the kernels that serve
+ * any shape, whose intermediate is fp32 -- and each output is rounded
  * once on store.  With MONARCH_FLAG_WGRAD_F32, dR and dL are written as fp32
  * regardless of dtype.
  *
@@ -94,7 +95,10 @@ int monarch_fwd_ex(const void* x, const void* R, const void* L, void* y,
  * Section 3.3 steps 1-3).  For the shapes that have a packed-weight kernel (bf16: k = 4 wide
  * blocks, and the square m = 64 case) the call first re-lays R and L in matrix-core fragment order into `workspace` and then
  * runs the fused forward on the packed copies, which removes the weights from the LDS traffic of
- * the kernel.  fp32 layers with square blocks p = q = s of 32 or 64 (any k) run on the fp32 matrix cores, one
+ * the kernel; for k = 4 and up to 3072 rows it runs as one launch per factor instead, if the workspace also holds the vector
+ * between them (and both fit MONARCH_STATIC_WORKSPACE_BYTES).  The other bf16 shapes with k = 4 and blocks that are multiples of 32 (p: of 16; q up to 256, p up to 1024) have
+ * that form for up to 8192 rows; they pack in every call, the packed flag means nothing to them, and without a workspace, or with
+ * a short one, the call runs as monarch_fwd_ex.  fp32 layers with square blocks p = q = s of 32 or 64 (any k) run on the fp32 matrix cores, one
  * launch per block-diagonal factor with the vector between the factors kept in `workspace` (the packed flag
  * means nothing to them and is ignored).  Shapes that only the shape-generic kernels serve (p, q and s of 16 or more) run
  * on the matrix cores too, with the vector between the factors in `workspace`; for them the workspace is optional, and
@@ -137,8 +141,8 @@ int monarch_fwd_static(const void* x, const void* R, const void* L, void* y,
  * Arguments as monarch_fwd_ws (same workspace, same flags); `bias` (k*s elements of `dtype`, device
  * pointer, 16-byte aligned) may be NULL, and the call is then monarch_fwd_ws itself.  The bias is
  * added to the fp32 accumulator before the single rounding to `dtype` in the kernels that have a
- * bias epilogue (bf16 k = 4 wide blocks, fp32 m = 16, the shape-generic kernels); the bf16 m = 64
- * kernel has none, there a second in-place pass adds the bias to the rounded y (two roundings). */
+ * bias epilogue (bf16 k = 4 blocks, fp32 m = 16, the shape-generic kernels); the bf16 m = 64 kernel and the fp32 ones
+ * of square blocks of 32 / 64 have none, there a second in-place pass adds the bias to the rounded y (two roundings). */
 int monarch_fwd_bias(const void* x, const void* R, const void* L, const void* bias, void* y,
                      int64_t batch, int n_in, int k, int q, int s,
                      monarch_dtype dtype, void* stream,
@@ -175,7 +179,7 @@ size_t monarch_fwd_workspace_bytes(int64_t batch, int n_in, int k, int q, int s,
  * U is recomputed from x (no activation is saved by the forward call).  dx, dR
  * and dL are overwritten, never accumulated into.  The matrix-core kernels sum
  * per-chunk partial gradients in a fixed order (bit-reproducible); the SIMT
- * fallback (blocks below 16, MONARCH_FLAG_GENERIC) reduces dR/dL with fp32 atomics across
+ * fallback (blocks below 16, MONARCH_FLAG_GENERIC, a workspace too short for the others) reduces dR/dL with fp32 atomics across
  * workgroups, so its results are reproducible only up to fp32 summation order.  `workspace` must hold at least
  * monarch_bwd_workspace_bytes(...) bytes (device memory, 256-byte aligned);
  * its contents on entry are ignored and on exit are unspecified. */
@@ -210,8 +214,8 @@ int monarch_bwd_bias(const void* dy, const void* x, const void* R, const void* L
  *     y_pre[b][o] = (x M^T)[b][o] + bias[o],    y[b][o] = gelu(y_pre[b][o]).
  * Arguments as monarch_fwd_bias.  `bias` may be NULL (no bias).  `y_pre` (batch x k*s elements of
  * `dtype`, 16-byte aligned) receives the value before the nonlinearity, which the backward pass
- * needs; NULL skips it (inference).  In the kernels with the fused epilogue (bf16, k = 4 wide blocks,
- * with workspace) gelu is applied to the fp32 sum before its rounding to `dtype`; for every other
+ * needs; NULL skips it (inference).  In the kernels with the fused epilogue (bf16, k = 4, the packed-weight kernels of
+ * monarch_fwd_ws) gelu is applied to the fp32 sum before its rounding to `dtype`; for every other
  * shape y_pre is rounded to `dtype` first and a second pass computes y from it.
  *
  * monarch_bwd_bias_gelu_in (the block's second layer, whose input is x = gelu(x_pre)):
@@ -317,8 +321,8 @@ int monarch_to_dense(const void* R, const void* L, void* M,
  * dense-to-sparse step that precedes fine-tuning).  The sign of (u_1, v_1) is not fixed, and when the
  * two largest singular values of a slice coincide any leading pair is a valid answer; only the
  * products L*R are determined.  A zero slice gives zero factors.
- * The singular triple is computed in fp32 by a one-sided Jacobi iteration (at most 40 sweeps, pairs
- * orthogonal to 3e-7 relative).  A (n, n), R (m, m, m), L (m, m, m) are device pointers, 16-byte
+ * The singular triple is computed in fp32: v_1 by squaring the slice's Gram matrix until it is of rank one (32 times at most),
+ * u_1 from it.  Rounding leaves a slice's rank-1 part off by about 2^-24 sigma_1 (1 + sigma_1 / (sigma_1 - sigma_2)).  A (n, n), R (m, m, m), L (m, m, m) are device pointers, 16-byte
  * aligned, element type `dtype`; R and L are overwritten.  m <= 64; larger m returns
  * MONARCH_ERR_UNSUPPORTED; n != m*m or flags != 0 returns MONARCH_ERR_INVALID.  No workspace. */
 int monarch_project(const void* A, void* R, void* L, int n, int m,
@@ -347,7 +351,7 @@ int monarch_bwd_c64(const void* dy, const void* x, const void* R, const void* L,
 /* The same three operations with a workspace (device memory, 256-byte aligned, at least
  * monarch_c64_workspace_bytes(pass, ...) bytes with pass 0 = monarch_fwd_c64_ws, 1 = monarch_bwd_c64_ws,
  * 2 = monarch_fwd_h_c64_ws; contents ignored on entry, unspecified on exit).
- * Square blocks p = q = s in {16, 32, 64} (any k; the DFT-initialised matrices of the MRI model are of this
+ * Square blocks p = q = s that are a multiple of 8 from 16 to 64 (any k; the DFT-initialised matrices of the MRI model are of this
  * kind) run on the matrix cores: one launch per block-diagonal factor, the vector between the factors kept
  * in the workspace in a tiled order that makes the permutation between them long contiguous runs; the weight
  * gradients are contracted over the batch on the matrix cores too and their partial sums added in a fixed
