@@ -13,21 +13,25 @@
 // With MONARCH_FLAG_PERM_B the vector between the factors is kept in stage-1 order and the strides on either side of it
 // change places.  So there is one contraction, ops_gemm: O[g][m][n] = sum_k A[g][m][k] B[g][n][k].
 //
-// Precision: U and dU are fp32 for both types, as in the SIMT kernels, and a product with one of them runs on the fp32 matrix
-// cores, its bf16 operand widened on the way to LDS; bf16 layers are rounded once, when a result is stored.  The products of two
-// bf16 operands (step 1 and dU) are exact on the bf16 matrix cores.
+// Precision: U and dU are fp32 for both types, as in the SIMT kernels; bf16 layers are rounded once, when a result is stored.
+// Everything runs on the bf16 matrix cores, which are exact in the products and add them in fp32.  An fp32 operand is taken as three bf16
+// planes that add up to it exactly (split3), and a product of two such operands as the six products of planes above 2^-26 of
+// the whole (three where the other operand is bf16).  An accumulator takes one rounding per 16 contraction indices and product of planes, so
+// the results are closer to float64 than those of v_mfma_f32_32x32x2_f32 with one per 2 (normal operands, 192 indices: 2.0e-7 against
+// 2.5e-7; with the small products in a sum of their own, as the weight gradients have them, 0.8e-7).  What the planes cannot hold
+// (infinities, results below 2^-80) is found in the finished tile, which is then computed again in fp32 (op_doubtful, op_redo).
 //
-// What bounds it: fp32 layers the fp32 matrix cores (v_mfma_f32_32x32x2_f32, 154 TFLOP/s in a large product; a 128 x 128
-// tile needs 16 B/clk of LDS reads per CU, far below the 128 there are), small and odd bf16 layers the memory system (every
-// operand element is staged once per tile, element by element where it is strided, else in 16-byte pieces wherever they start) and,
-// in the products with U and dU, the fp32 matrix cores.  The intermediate goes
+// What bounds it: a product of two fp32 operands costs the matrix cores 6/14.4 of its time on the fp32 cores (2058 against
+// 143 TFLOP/s in a loop of MFMAs alone), and what is left is the vector work of splitting (5.5 instructions an element, once per tile that
+// takes it) and LDS.  Neither is near its rate: the chunks are a chain of load, split, barrier and multiply, and what hides it is the number of
+// workgroups on a CU.  So a chunk is 16 contraction indices, one MFMA deep: 64 x 64 tiles then take 30 KB of LDS, five
+// to a CU, where chunks of 32 leave two (4096 -> 1024 fp32, 8000 rows, whole step: 660 us on the fp32 matrix cores, 674 in planes with chunks of 32, 455 with
+// 16).  Small and odd bf16 layers are bound by the memory system.  The intermediate goes
 // through memory (for most shapes it stays in the last-level cache): a fused kernel would hold all k blocks of a row tile,
 // which leaves the large shapes one 16-row tile per CU.
-// Measured against the SIMT kernels: 768 -> 768 fp32, k = 4, 12608 rows: forward 741 -> 96 us, backward 3570 -> 255 us (one
-// contraction of 3.7 GFLOP takes 46 to 57 us, its matrix-core floor is 24: the cores are busy 62 % of the time of a busy CU,
-// and 2.3 rounds of workgroups leave a quarter of the launch on partly filled CUs); 196 -> 256 bf16, blocks of 49 and 64,
-// 32768 rows: forward 61 -> 39 us, backward 388 -> 90 us (U and dU in 16 bits: 26 and 67 us, but results 2.35e-3 off in place of
-// 1.65e-3); 4096 -> 1024 fp32, 16384 rows: 105 TFLOP/s in the data path, 92 in the weight gradients.
+// Measured, training step: 768 -> 768 fp32, k = 4, 12608 rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix cores, now 250 (one
+// contraction of 3.7 GFLOP takes 35 to 40 us, 50 where an operand is strided, the two weight gradients 74); 196 -> 256 bf16, blocks of 49 and 64,
+// 32768 rows: 458, 121, now 100 us; 2048 -> 512 fp32, 3000 rows: 137, now 112.
 #include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
@@ -41,14 +45,11 @@ constexpr int kThreads = 256;  // four waves
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
-template <typename T> struct OpType;
-template <> struct OpType<float> { static constexpr int KC = 32, KSTEP = 8; };   // contraction indices per chunk / per MFMA group
-template <> struct OpType<bf16_t> { static constexpr int KC = 32, KSTEP = 16; };
+constexpr int kStep = 16;  // contraction indices of an MFMA
 
 // How an operand is taken: kPieces16, 16-byte pieces along the contiguous index, all of them aligned and inside; kPiecesAny,
 // 16-byte pieces along it wherever they start (gfx950 loads from any address), a piece that crosses the limit being read from
-// the elements that end there and shifted into place on its way to LDS; kElements, single elements at any stride (fp32: a dword
-// per element; bf16: two 2-byte loads per dword, joined on the way to LDS so that nothing waits for them here).
+// the elements that end there and shifted into place on its way to LDS; kElements, single elements at any stride.
 enum Take { kElements, kPiecesAny, kPieces16 };
 
 // One operand: element (g, row, k) at p[g*g_s + row*r_s + k*k_s].
@@ -80,22 +81,53 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, kBufferBytes, 0x00020000);
 }
 
+template <typename T>
+struct TileDrop {
+    // v without its first n elements (zeros follow); a piece with nothing inside was loaded as zeros
+    static __device__ __forceinline__ u32x4 drop(u32x4 v, int n)
+    {
+        const int bytes = n * (int)sizeof(T);
+        if (bytes & 8) v = u32x4{v[2], v[3], 0u, 0u};
+        if (bytes & 4) v = u32x4{v[1], v[2], v[3], 0u};
+        if constexpr (sizeof(T) == 2) {
+            const uint32_t s = (bytes & 2) * 8;
+            v = u32x4{__builtin_amdgcn_alignbit(v[1], v[0], s), __builtin_amdgcn_alignbit(v[2], v[1], s),
+                      __builtin_amdgcn_alignbit(v[3], v[2], s), v[3] >> s};
+        }
+        return v;
+    }
+};
+
+// fp32 pair -> its three bf16 pairs: the value rounded, what that leaves rounded, and the rest, which fits.  The three add up to
+// the value exactly, except where the last one is below bf16's smallest number (values below 2^-110) or the value is not finite.
+__device__ __forceinline__ void split3(uint32_t a, uint32_t b, uint32_t out[3])
+{
+    float x = __uint_as_float(a), y = __uint_as_float(b);
+#pragma unroll
+    for (int w = 0; w < 3; ++w) {
+        out[w] = pack_bf16x2(x, y);
+        if (w < 2) {
+            x -= __uint_as_float(out[w] << 16);
+            y -= __uint_as_float(out[w] & 0xffff0000u);
+        }
+    }
+}
+
 // A C x O tile of an operand (C: extent along the index with the unit or smallest stride, O: along the other one) on
-// its way from memory (type T) to LDS [o][c] (type TL: T, or float for bf16), row stride LSTR elements.  Elements past the limits
-// read as zeros.
-template <typename T, typename TL, int C, int O, int LSTR, Take TAKE>
+// its way from memory to LDS [o][c], row stride LSTR elements: bf16 as it is, fp32 as three planes of SZ elements.  Elements past the
+// limits read as zeros.  Single elements are loaded with consecutive lanes on consecutive c (at a stride of 16 bytes a load takes the L1
+// 31 cycles, at 32 bytes 60), and neighbouring lanes exchange them so that each has two for a dword.
+template <typename T, int C, int O, int LSTR, Take TAKE, int SZ>
 struct OpTile {
-    static constexpr bool VEC = TAKE != kElements;
-    static constexpr bool kWiden = sizeof(TL) != sizeof(T);
-    static constexpr int EPD = 4 / (int)sizeof(T);                   // elements per dword
-    static constexpr int V = VEC ? 16 / (int)sizeof(T) : EPD;        // elements per piece
+    static constexpr bool VEC = TAKE != kElements, kSplit = sizeof(T) == 4;
+    static constexpr int V = VEC ? 16 / (int)sizeof(T) : 1;          // elements per piece
     static constexpr int PPO = C / V;                                // pieces per o
     static constexpr int kPieces = PPO * O;
     static constexpr int NP = (kPieces + kThreads - 1) / kThreads;   // per thread
-    static constexpr int kLoads = VEC ? 1 : EPD, kDwords = VEC ? 4 : EPD;
-    static_assert(C % V == 0 && LSTR * sizeof(TL) % 16 == 0, "tile");
-    static_assert(VEC || kPieces % kThreads == 0, "element-wise tiles divide over the threads");
+    static constexpr int kDwords = VEC ? 4 : 1;
+    static_assert(C % V == 0 && LSTR * 2 % 16 == 0, "tile");
     static constexpr bool kEven = kThreads % PPO == 0;  // a thread's pieces share c and step in o by a uniform amount
+    static_assert(VEC || (kEven && kPieces % kThreads == 0 && NP % 2 == 0), "element-wise tiles divide over the threads");
     uint32_t r[NP * kDwords];
     int over[TAKE == kPiecesAny ? (kEven ? 1 : NP) : 1];  // elements of a piece past the limit
 
@@ -112,76 +144,75 @@ struct OpTile {
             const int o = kEven ? o0 + n * (kThreads / PPO) : idx / PPO, c = kEven ? c0 : (idx % PPO) * V;
             uint32_t vo = kEven ? v0 : (o * os + c * cs) * (uint32_t)sizeof(T) + kBack;
             const uint32_t so = kEven ? n * (kThreads / PPO) * os * (uint32_t)sizeof(T) : 0u;
-            bool in = o < olim;
+            bool in = o < olim && c < clim;
             if constexpr (kPieces % kThreads != 0) in = in && idx < kPieces;
             if constexpr (TAKE == kPiecesAny) {
                 const int past = c + V > clim ? c + V - clim : 0;
                 over[kEven ? 0 : n] = past;
                 vo -= past * (uint32_t)sizeof(T);
             }
+            const uint32_t at = in ? vo : kNowhere;
+            if constexpr (VEC) {
+                const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, at, so, 0);
 #pragma unroll
-            for (int e = 0; e < kLoads; ++e) {
-                const uint32_t at = in && c + e < clim ? vo : kNowhere;
-                if constexpr (VEC) {
-                    const u32x4 v = __builtin_amdgcn_raw_buffer_load_b128(rs, at, so, 0);
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) r[4 * n + w] = v[w];
-                } else if constexpr (EPD == 1) {
-                    r[n] = __builtin_amdgcn_raw_buffer_load_b32(rs, at, so, 0);
-                } else {
-                    r[2 * n + e] = __builtin_amdgcn_raw_buffer_load_b16(rs, at, so + e * cs * (uint32_t)sizeof(T), 0);
-                }
+                for (int w = 0; w < 4; ++w) r[4 * n + w] = v[w];
+            } else if constexpr (sizeof(T) == 4) {
+                r[n] = __builtin_amdgcn_raw_buffer_load_b32(rs, at, so, 0);
+            } else {
+                r[n] = __builtin_amdgcn_raw_buffer_load_b16(rs, at, so, 0);
             }
         }
     }
-    // v without its first n elements (zeros follow); a piece with nothing inside was loaded as zeros
-    static __device__ __forceinline__ u32x4 drop(u32x4 v, int n)
+    __device__ __forceinline__ void store(bf16_t* lds, int tid) const
     {
-        const int bytes = n * (int)sizeof(T);
-        if (bytes & 8) v = u32x4{v[2], v[3], 0u, 0u};
-        if (bytes & 4) v = u32x4{v[1], v[2], v[3], 0u};
-        if constexpr (sizeof(T) == 2) {
-            const uint32_t s = (bytes & 2) * 8;
-            v = u32x4{__builtin_amdgcn_alignbit(v[1], v[0], s), __builtin_amdgcn_alignbit(v[2], v[1], s),
-                      __builtin_amdgcn_alignbit(v[3], v[2], s), v[3] >> s};
-        }
-        return v;
-    }
-    __device__ __forceinline__ void store(TL* lds, int tid) const
-    {
+        if constexpr (VEC) {
 #pragma unroll
-        for (int n = 0; n < NP; ++n) {
-            const int idx = tid + n * kThreads, o = idx / PPO, c = (idx % PPO) * V;
-            if constexpr (VEC) {
+            for (int n = 0; n < NP; ++n) {
+                const int idx = tid + n * kThreads, o = idx / PPO, c = (idx % PPO) * V;
                 u32x4 v = {r[4 * n], r[4 * n + 1], r[4 * n + 2], r[4 * n + 3]};
-                if constexpr (TAKE == kPiecesAny) v = drop(v, over[kEven ? 0 : n]);
+                if constexpr (TAKE == kPiecesAny) v = TileDrop<T>::drop(v, over[kEven ? 0 : n]);
                 if (kPieces % kThreads == 0 || idx < kPieces) {
-                    if constexpr (kWiden) {
+                    if constexpr (kSplit) {
+                        uint32_t lo[3], hi[3];
+                        split3(v[0], v[1], lo);
+                        split3(v[2], v[3], hi);
 #pragma unroll
-                        for (int w = 0; w < 4; w += 2)
-                            *reinterpret_cast<u32x4*>(lds + o * LSTR + c + 2 * w) =
-                                u32x4{v[w] << 16, v[w] & 0xffff0000u, v[w + 1] << 16, v[w + 1] & 0xffff0000u};
+                        for (int w = 0; w < 3; ++w) *reinterpret_cast<u32x2*>(lds + w * SZ + o * LSTR + c) = u32x2{lo[w], hi[w]};
                     } else {
                         *reinterpret_cast<u32x4*>(lds + o * LSTR + c) = v;
                     }
                 }
-            } else if constexpr (kWiden) {
-                *reinterpret_cast<u32x2*>(lds + o * LSTR + c) = u32x2{r[n * EPD] << 16, r[n * EPD + EPD - 1] << 16};
-            } else {
-                *reinterpret_cast<uint32_t*>(lds + o * LSTR + c) = EPD == 1 ? r[n] : (r[n * EPD] | (r[n * EPD + EPD - 1] << 16));
+            }
+        } else {
+            // of the elements n and n + 1 an even lane takes n of both lanes, an odd lane n + 1
+            const bool odd = tid & 1;
+            bf16_t* const to = lds + (tid / PPO + (odd ? kThreads / PPO : 0)) * LSTR + (tid % PPO & ~1);
+#pragma unroll
+            for (int n = 0; n < NP; n += 2) {
+                const uint32_t mine = odd ? r[n + 1] : r[n], give = odd ? r[n] : r[n + 1];
+                const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);  // lane ^ 1
+                const uint32_t a = odd ? got : mine, b = odd ? mine : got;
+                bf16_t* const p = to + n * (kThreads / PPO) * LSTR;
+                if constexpr (kSplit) {
+                    uint32_t v[3];
+                    split3(a, b, v);
+#pragma unroll
+                    for (int w = 0; w < 3; ++w) *reinterpret_cast<uint32_t*>(p + w * SZ) = v[w];
+                } else {
+                    *reinterpret_cast<uint32_t*>(p) = a | b << 16;
+                }
             }
         }
     }
 };
 
 // LDS row strides: contraction-contiguous tiles [row][KC] + 16 bytes (eight lanes of a b128 read then start in eight
-// different bank groups); row-contiguous tiles [k][rows]: fp32 + 16 bytes, bf16 odd multiples of 64 bytes, so that the
-// four rows a half wave of the transposing read touches fall on disjoint bank quarters.
-template <typename T, bool RC, int ROWS>
+// different bank groups); row-contiguous tiles [k][rows]: odd multiples of 64 bytes, so that the four rows a half wave of the
+// transposing read touches fall on disjoint bank quarters.
+template <bool RC, int ROWS, int KC>
 constexpr int op_lstr()
 {
-    if (!RC) return OpType<T>::KC + 16 / (int)sizeof(T);
-    if (sizeof(T) == 4) return ROWS + 4;
+    if (!RC) return KC + 8;
     return ROWS % 64 == 32 ? ROWS : ROWS + 32;
 }
 
@@ -191,52 +222,38 @@ __device__ __forceinline__ u32x2 op_lds_tr16(const bf16_t* p)
     return __builtin_bit_cast(u32x2, v);
 }
 
-// The MFMA operands of KSTEP contraction indices k0 .. k0 + KSTEP-1 for the 32 rows from r0: lane (row = lane % 32,
-// h = lane / 32) holds the indices k0 + (KSTEP/2)*h .. of its row (fp32: four values = four K = 2 steps).
-template <typename T, bool RC, int LSTR> struct OpFrag;
-template <bool RC, int LSTR>
-struct OpFrag<float, RC, LSTR> {
-    float v[4];
-    __device__ __forceinline__ void read(const float* lds, int r0, int k0, int lane)
-    {
-        const int row = r0 + (lane & 31), k = k0 + 4 * (lane >> 5);
-        if constexpr (!RC) {
-            const f32x4 t = *reinterpret_cast<const f32x4*>(lds + row * LSTR + k);
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = t[e];
-        } else {
-#pragma unroll
-            for (int e = 0; e < 4; ++e) v[e] = lds[(k + e) * LSTR + row];
-        }
-    }
-};
-template <bool RC, int LSTR>
-struct OpFrag<bf16_t, RC, LSTR> {
-    bf16x8 v;
+// The MFMA operands of the contraction indices k0 .. k0 + 15 for the 32 rows from r0, from PL planes of SZ elements: lane
+// (row = lane % 32, h = lane / 32) holds the indices k0 + 8 h .. of its row.
+template <bool RC, int LSTR, int PL, int SZ>
+struct OpFrag {
+    bf16x8 v[PL];
     __device__ __forceinline__ void read(const bf16_t* lds, int r0, int k0, int lane)
     {
-        if constexpr (!RC) {
-            v = as_bf16x8(lds128(lds + (r0 + (lane & 31)) * LSTR + k0 + 8 * (lane >> 5)));
-        } else {
-            // transposing read: within 16 lanes, lane i gets element i % 4 of lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4
-            const int G = lane >> 4, j = lane & 15;
-            const bf16_t* p = lds + (k0 + 8 * (G >> 1) + (j >> 2)) * LSTR + r0 + 16 * (G & 1) + 4 * (j & 3);
-            const u32x2 lo = op_lds_tr16(p), hi = op_lds_tr16(p + 4 * LSTR);
-            v = as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]});
+#pragma unroll
+        for (int w = 0; w < PL; ++w) {
+            if constexpr (!RC) {
+                v[w] = as_bf16x8(lds128(lds + w * SZ + (r0 + (lane & 31)) * LSTR + k0 + 8 * (lane >> 5)));
+            } else {
+                // transposing read: within 16 lanes, lane i gets element i % 4 of lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4
+                const int G = lane >> 4, j = lane & 15;
+                const bf16_t* p = lds + w * SZ + (k0 + 8 * (G >> 1) + (j >> 2)) * LSTR + r0 + 16 * (G & 1) + 4 * (j & 3);
+                const u32x2 lo = op_lds_tr16(p), hi = op_lds_tr16(p + 4 * LSTR);
+                v[w] = as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]});
+            }
         }
     }
 };
-template <bool RA, int LA, bool RB, int LB>
-__device__ __forceinline__ f32x16 op_mma(const OpFrag<float, RA, LA>& a, const OpFrag<float, RB, LB>& b, f32x16 c)
+// Products of the planes whose place values add up to less than 3; the others are below 2^-26 of the whole.  `big` takes the
+// product of the first planes, `small` the rest (they may be one).
+template <int PA, int PB>
+__device__ __forceinline__ void op_products(const bf16x8 (&a)[PA], const bf16x8 (&b)[PB], f32x16& big, f32x16& small)
 {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) c = __builtin_amdgcn_mfma_f32_32x32x2f32(a.v[e], b.v[e], c, 0, 0, 0);
-    return c;
-}
-template <bool RA, int LA, bool RB, int LB>
-__device__ __forceinline__ f32x16 op_mma(const OpFrag<bf16_t, RA, LA>& a, const OpFrag<bf16_t, RB, LB>& b, f32x16 c)
-{
-    return mfma32(a.v, b.v, c);
+    for (int w = 2; w > 0; --w)
+#pragma unroll
+        for (int u = 0; u <= w; ++u)
+            if (u < PA && w - u < PB) small = mfma32(a[u < PA ? u : 0], b[w - u < PB ? w - u : 0], small);
+    big = mfma32(a[0], b[0], big);
 }
 
 template <int WM_, int WN_, int MT_, int NT_>
@@ -245,135 +262,81 @@ struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32
     static constexpr int TM = WM * MT * 32, TN = WN * NT * 32;
 };
 
-// One workgroup, `bid` of d.blocks.  TA, TB, TO: element types of the operands and the output in memory; two bf16 operands are
-// multiplied as such, else as fp32.  RA / RB: the operand's row index (not the contraction) is the contiguous one.  PARTIAL: fp32
-// partial tiles of a split contraction instead of the output.
-// Workgroup order: the row tile (PARTIAL: the batch chunk) is dealt to the XCDs, and the blocks and column tiles of one
-// row tile follow each other on that XCD: strided operands and outputs of the k blocks share their cache lines, which
-// then meet in one L2.
-template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
-struct OpGemm {
-    using T = typename std::conditional<sizeof(TA) == 2 && sizeof(TB) == 2, bf16_t, float>::type;
-    static constexpr int KC = OpType<T>::KC, LA = op_lstr<T, RA, Cfg::TM>(), LB = op_lstr<T, RB, Cfg::TN>();
-    static constexpr int SZA = RA ? KC * LA : Cfg::TM * LA, SZB = RB ? KC * LB : Cfg::TN * LB;
-    static constexpr size_t kLds = 2 * sizeof(T) * (size_t)(SZA + SZB);
-    static __device__ void run(const OpDesc& d, int bid, unsigned char* op_lds);
-};
-template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
-__device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>::run(const OpDesc& d, int bid, unsigned char* op_lds)
+// Results of the split planes that are not what the fp32 matrix cores give: a value that is not finite (an infinity times the zero
+// planes of a number is no number) and one so small that planes below bf16's smallest number may have been lost.  Exact zeros
+// are right.  True if any lane of the wave holds such a value.
+template <int MT, int NT>
+__device__ __forceinline__ bool op_doubtful(const f32x16 (&acc)[MT][NT])
 {
-    constexpr int KC = OpType<T>::KC, KSTEP = OpType<T>::KSTEP, MT = Cfg::MT, NT = Cfg::NT, TM = Cfg::TM, TN = Cfg::TN;
-    using TileA = OpTile<TA, T, RA ? TM : KC, RA ? KC : TM, LA, AV>;
-    using TileB = OpTile<TB, T, RB ? TN : KC, RB ? KC : TN, LB, BV>;
-    T* const lds = reinterpret_cast<T*>(op_lds);
-
-    const int inner = d.G * d.tiles_n * (PARTIAL ? d.tiles_m : 1);
-    const int seq = d.deal ? bid >> 3 : bid;
-    const int outer = d.deal ? (seq / inner) * 8 + (bid & 7) : seq / inner;
-    if (outer >= d.nouter) return;
-    int in = seq % inner;
-    const int g = in % d.G;
-    in /= d.G;
-    const int tn = in % d.tiles_n;
-    const int tm = PARTIAL ? in / d.tiles_n : outer;
-    const int64_t m0 = (int64_t)tm * TM;
-    const int n0 = tn * TN;
-    const int64_t k_lo = PARTIAL ? (int64_t)outer * d.k_chunk : 0;
-    const int64_t k_len = PARTIAL ? (d.K - k_lo < d.k_chunk ? d.K - k_lo : d.k_chunk) : d.K;
-    const int mlim = d.M - m0 < TM ? (int)(d.M - m0) : TM, nlim = d.N - n0 < TN ? d.N - n0 : TN;
-
-    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-    const int wm = wave % Cfg::WM, wn = wave / Cfg::WM;
+    constexpr uint32_t kSmall = (127u - 80u) << 24, kWidth = (255u << 24) - kSmall;  // twice the bits of 2^-80, and from there to infinity
+    uint32_t worst = 0;
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t t = (__float_as_uint(acc[i][j][r]) << 1) - kSmall;
+                worst = t > worst ? t : worst;
+            }
+    if (!__any(worst >= kWidth)) return false;
+    bool off = false;  // most often these are the zeros of a ragged tile
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const uint32_t t = __float_as_uint(acc[i][j][r]) << 1;
+                off |= t != 0 && t - kSmall >= kWidth;
+            }
+    return __any(off);
+}
+// The wave's tile (32 MT rows from m0, 32 NT columns from n0) again on the fp32 matrix cores, straight from memory, sixteen
+// contraction indices to a partial sum.
+template <typename T>
+__device__ __forceinline__ float op_element(__amdgpu_buffer_rsrc_t rs, uint32_t at)
+{
+    if constexpr (sizeof(T) == 4) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, at, 0, 0));
+    else return bf16_to_f32((bf16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, at, 0, 0));
+}
+template <typename TA, typename TB, int MT, int NT>
+__device__ __forceinline__ void op_redo(const OpDesc& d, int g, int64_t m0, int n0, int mlim, int nlim, int64_t k_lo, int64_t k_len,
+                                        int lane, f32x16 (&acc)[MT][NT])
+{
     const TA* pa = static_cast<const TA*>(d.a.p) + g * d.a.g_s + m0 * d.a.r_s + k_lo * d.a.k_s;
     const TB* pb = static_cast<const TB*>(d.b.p) + g * d.b.g_s + (int64_t)n0 * d.b.r_s + k_lo * d.b.k_s;
-    const uint32_t a_o = (uint32_t)(RA ? d.a.k_s : d.a.r_s), a_c = (uint32_t)(RA ? d.a.r_s : d.a.k_s);
-    const uint32_t b_o = (uint32_t)(RB ? d.b.k_s : d.b.r_s), b_c = (uint32_t)(RB ? d.b.r_s : d.b.k_s);
-
-    // Partial tiles add their rows up in four sums that meet at the end: a single one over a chunk's rows left the fp32 weight
-    // gradients of some hundred rows up to 1.37 times as far off float64 as the SIMT kernels, which add up 16 rows at a time.
-    constexpr int SUMS = PARTIAL ? 4 : 1;
-    f32x16 sums[SUMS][MT][NT];
+    const int row = lane & 31, h = lane >> 5;
 #pragma unroll
-    for (int u = 0; u < SUMS; ++u)
+    for (int i = 0; i < MT; ++i)
 #pragma unroll
-        for (int i = 0; i < MT; ++i)
+        for (int j = 0; j < NT; ++j) {
+            const bool a_in = i * 32 + row < mlim, b_in = j * 32 + row < nlim;
+            f32x16 sum, all;
 #pragma unroll
-            for (int j = 0; j < NT; ++j)
+            for (int r = 0; r < 16; ++r) sum[r] = all[r] = 0.f;
+#pragma clang loop unroll(disable)
+            for (int64_t k = 0; k < k_len; k += 2) {
+                const bool k_in = k + h < k_len;
+                const float a = op_element<TA>(buffer_at(pa + k * d.a.k_s), a_in && k_in ? (uint32_t)((i * 32 + row) * (int)d.a.r_s + h * (int)d.a.k_s) * (uint32_t)sizeof(TA) : kNowhere);
+                const float b = op_element<TB>(buffer_at(pb + k * d.b.k_s), b_in && k_in ? (uint32_t)((j * 32 + row) * (int)d.b.r_s + h * (int)d.b.k_s) * (uint32_t)sizeof(TB) : kNowhere);
+                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, sum, 0, 0, 0);
+                if ((k & 15) == 14 || k + 2 >= k_len) {
 #pragma unroll
-                for (int r = 0; r < 16; ++r) sums[u][i][j][r] = 0.f;
-
-    // two chunks are on their way from memory while one is multiplied: with one, a chunk's time on the matrix cores
-    // (0.4 to 0.9 us) does not cover a load's
-    struct Stage {
-        TileA a;
-        TileB b;
-    };
-    Stage s0, s1;
-    auto fetch = [&](Stage& s, int64_t kk) {
-        const int64_t left = k_len - kk;
-        const int klim = left < KC ? (left > 0 ? (int)left : 0) : KC;
-        s.a.fetch(pa + kk * d.a.k_s, a_o, a_c, RA ? klim : mlim, RA ? mlim : klim, tid);
-        s.b.fetch(pb + kk * d.b.k_s, b_o, b_c, RB ? klim : nlim, RB ? nlim : klim, tid);
-        __builtin_amdgcn_sched_barrier(0);  // in this order: the wait for a chunk counts the loads behind it
-    };
-    auto put = [&](const Stage& s, int buf) {
-        s.a.store(lds + buf * (SZA + SZB), tid);
-        s.b.store(lds + buf * (SZA + SZB) + SZA, tid);
-    };
-    auto multiply = [&](auto which, int64_t kk) {
-        constexpr int buf = decltype(which)::value;
-        const T* la = lds + buf * (SZA + SZB);
-        const T* lb = la + SZA;
-        const int left = (int)(k_len - kk < KC ? k_len - kk : KC);
-#pragma unroll
-        for (int t = 0; t < KC / KSTEP; ++t) {
-            if (t * KSTEP < left) {
-                OpFrag<T, RA, LA> af[MT];
-                OpFrag<T, RB, LB> bf[NT];
-#pragma unroll
-                for (int i = 0; i < MT; ++i) af[i].read(la, (wm * MT + i) * 32, t * KSTEP, lane);
-#pragma unroll
-                for (int j = 0; j < NT; ++j) bf[j].read(lb, (wn * NT + j) * 32, t * KSTEP, lane);
-#pragma unroll
-                for (int i = 0; i < MT; ++i)
-#pragma unroll
-                    for (int j = 0; j < NT; ++j) {
-                        f32x16& acc = sums[(2 * buf + t % 2) % SUMS][i][j];
-                        acc = op_mma(af[i], bf[j], acc);
+                    for (int r = 0; r < 16; ++r) {
+                        all[r] += sum[r];
+                        sum[r] = 0.f;
                     }
+                }
             }
+            acc[i][j] = all;
         }
-    };
-    // chunk c is multiplied from LDS buffer c % 2; chunk c + 1 goes there from its registers at the end of step c, and
-    // chunk c + 3 is requested into the registers so freed
-    fetch(s0, 0);
-    fetch(s1, KC);
-    put(s0, 0);
-    fetch(s0, 2 * KC);
-    lds_barrier();
-    for (int64_t kk = 0; kk < k_len; kk += 2 * KC) {
-        multiply(std::integral_constant<int, 0>(), kk);
-        if (kk + KC >= k_len) break;
-        put(s1, 1);
-        fetch(s1, kk + 3 * KC);
-        lds_barrier();
-        multiply(std::integral_constant<int, 1>(), kk + KC);
-        if (kk + 2 * KC >= k_len) break;
-        put(s0, 0);
-        fetch(s0, kk + 4 * KC);
-        lds_barrier();
-    }
+}
 
-    auto& acc = sums[0];
-    if constexpr (SUMS == 4) {
-#pragma unroll
-        for (int i = 0; i < MT; ++i)
-#pragma unroll
-            for (int j = 0; j < NT; ++j)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) acc[i][j][r] = (sums[0][i][j][r] + sums[1][i][j][r]) + (sums[2][i][j][r] + sums[3][i][j][r]);
-    }
-
+template <typename TO, bool PARTIAL, int MT, int NT>
+__device__ __forceinline__ void op_store(const OpDesc& d, const f32x16 (&acc)[MT][NT], int outer, int g, int64_t m0, int n0,
+                                         int mlim, int nlim, int wm, int wn, int lane)
+{
     const int col = lane & 31, rh = 4 * (lane >> 5);
     using OT = typename std::conditional<PARTIAL, float, TO>::type;
     OT* O = static_cast<OT*>(d.o);
@@ -413,6 +376,143 @@ __device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>
                 else __builtin_amdgcn_raw_buffer_store_b16(f32_to_bf16(v), out, at, 0, 0);
             }
     }
+}
+
+// One workgroup, `bid` of d.blocks.  TA, TB, TO: element types of the operands and the output in memory.  RA / RB: the operand's
+// row index (not the contraction) is the contiguous one.  PARTIAL: fp32 partial tiles of a split contraction instead of the output.
+// Workgroup order: the row tile (PARTIAL: the batch chunk) is dealt to the XCDs, and the blocks and column tiles of one
+// row tile follow each other on that XCD: strided operands and outputs of the k blocks share their cache lines, which
+// then meet in one L2.
+template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
+struct OpGemm {
+    static constexpr bool kSplit = sizeof(TA) == 4 || sizeof(TB) == 4;
+    static constexpr int PA = sizeof(TA) == 2 ? 1 : 3, PB = sizeof(TB) == 2 ? 1 : 3;
+    static constexpr int KC = kSplit ? 16 : 32, LA = op_lstr<RA, Cfg::TM, KC>(), LB = op_lstr<RB, Cfg::TN, KC>();
+    static constexpr int SZA = RA ? KC * LA : Cfg::TM * LA, SZB = RB ? KC * LB : Cfg::TN * LB;
+    static constexpr int SZ = PA * SZA + PB * SZB;
+    static constexpr size_t kLds = 2 * sizeof(bf16_t) * (size_t)SZ;
+    static __device__ void run(const OpDesc& d, int bid, unsigned char* op_lds);
+};
+template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
+__device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>::run(const OpDesc& d, int bid, unsigned char* op_lds)
+{
+    constexpr int MT = Cfg::MT, NT = Cfg::NT, TM = Cfg::TM, TN = Cfg::TN;
+    using TileA = OpTile<TA, RA ? TM : KC, RA ? KC : TM, LA, AV, SZA>;
+    using TileB = OpTile<TB, RB ? TN : KC, RB ? KC : TN, LB, BV, SZB>;
+    bf16_t* const lds = reinterpret_cast<bf16_t*>(op_lds);
+
+    const int inner = d.G * d.tiles_n * (PARTIAL ? d.tiles_m : 1);
+    const int seq = d.deal ? bid >> 3 : bid;
+    const int outer = d.deal ? (seq / inner) * 8 + (bid & 7) : seq / inner;
+    if (outer >= d.nouter) return;
+    int in = seq % inner;
+    const int g = in % d.G;
+    in /= d.G;
+    const int tn = in % d.tiles_n;
+    const int tm = PARTIAL ? in / d.tiles_n : outer;
+    const int64_t m0 = (int64_t)tm * TM;
+    const int n0 = tn * TN;
+    const int64_t k_lo = PARTIAL ? (int64_t)outer * d.k_chunk : 0;
+    const int64_t k_len = PARTIAL ? (d.K - k_lo < d.k_chunk ? d.K - k_lo : d.k_chunk) : d.K;
+    const int mlim = d.M - m0 < TM ? (int)(d.M - m0) : TM, nlim = d.N - n0 < TN ? d.N - n0 : TN;
+
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    const int wm = wave % Cfg::WM, wn = wave / Cfg::WM;
+    const TA* pa = static_cast<const TA*>(d.a.p) + g * d.a.g_s + m0 * d.a.r_s + k_lo * d.a.k_s;
+    const TB* pb = static_cast<const TB*>(d.b.p) + g * d.b.g_s + (int64_t)n0 * d.b.r_s + k_lo * d.b.k_s;
+    const uint32_t a_o = (uint32_t)(RA ? d.a.k_s : d.a.r_s), a_c = (uint32_t)(RA ? d.a.r_s : d.a.k_s);
+    const uint32_t b_o = (uint32_t)(RB ? d.b.k_s : d.b.r_s), b_c = (uint32_t)(RB ? d.b.r_s : d.b.k_s);
+
+    // Partial tiles, whose sums run over hundreds of rows, keep the small products apart: a single sum left the fp32 weight
+    // gradients of some hundred rows further off float64 than the SIMT kernels, which add up 16 rows at a time.
+    constexpr int SUMS = PARTIAL && kSplit ? 2 : 1;
+    f32x16 sums[SUMS][MT][NT];
+#pragma unroll
+    for (int u = 0; u < SUMS; ++u)
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sums[u][i][j][r] = 0.f;
+
+    // two chunks are on their way from memory while one is multiplied: with one, a chunk's time on the matrix cores
+    // (0.4 to 0.9 us) does not cover a load's
+    struct Stage {
+        TileA a;
+        TileB b;
+    };
+    Stage s0, s1;
+    auto fetch = [&](Stage& s, int64_t kk) {
+        const int64_t left = k_len - kk;
+        const int klim = left < KC ? (left > 0 ? (int)left : 0) : KC;
+        s.a.fetch(pa + kk * d.a.k_s, a_o, a_c, RA ? klim : mlim, RA ? mlim : klim, tid);
+        s.b.fetch(pb + kk * d.b.k_s, b_o, b_c, RB ? klim : nlim, RB ? nlim : klim, tid);
+        __builtin_amdgcn_sched_barrier(0);  // in this order: the wait for a chunk counts the loads behind it
+    };
+    auto put = [&](const Stage& s, int buf) {
+        s.a.store(lds + buf * SZ, tid);
+        s.b.store(lds + buf * SZ + PA * SZA, tid);
+    };
+    auto multiply = [&](auto which, int64_t kk) {
+        constexpr int buf = decltype(which)::value;
+        const bf16_t* la = lds + buf * SZ;
+        const bf16_t* lb = la + PA * SZA;
+        const int left = (int)(k_len - kk < KC ? k_len - kk : KC);
+#pragma unroll
+        for (int t = 0; t < KC / kStep; ++t) {
+            if (t * kStep < left) {
+                OpFrag<RA, LA, PA, SZA> af[MT];
+                OpFrag<RB, LB, PB, SZB> bf[NT];
+#pragma unroll
+                for (int i = 0; i < MT; ++i) af[i].read(la, (wm * MT + i) * 32, t * kStep, lane);
+#pragma unroll
+                for (int j = 0; j < NT; ++j) bf[j].read(lb, (wn * NT + j) * 32, t * kStep, lane);
+#pragma unroll
+                for (int i = 0; i < MT; ++i)
+#pragma unroll
+                    for (int j = 0; j < NT; ++j) {
+                        op_products<PA, PB>(af[i].v, bf[j].v, sums[0][i][j], sums[SUMS - 1][i][j]);
+                    }
+            }
+        }
+    };
+    // chunk c is multiplied from LDS buffer c % 2; chunk c + 1 goes there from its registers at the end of step c, and
+    // chunk c + 3 is requested into the registers so freed
+    fetch(s0, 0);
+    fetch(s1, KC);
+    put(s0, 0);
+    fetch(s0, 2 * KC);
+    lds_barrier();
+    for (int64_t kk = 0; kk < k_len; kk += 2 * KC) {
+        multiply(std::integral_constant<int, 0>(), kk);
+        if (kk + KC >= k_len) break;
+        put(s1, 1);
+        fetch(s1, kk + 3 * KC);
+        lds_barrier();
+        multiply(std::integral_constant<int, 1>(), kk + KC);
+        if (kk + 2 * KC >= k_len) break;
+        put(s0, 0);
+        fetch(s0, kk + 4 * KC);
+        lds_barrier();
+    }
+
+    auto& acc = sums[0];
+    if constexpr (SUMS > 1) {
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int r = 0; r < 16; ++r) {
+                    acc[i][j][r] += sums[1][i][j][r];
+                }
+    }
+    if constexpr (kSplit) {
+        if (op_doubtful(acc))
+            op_redo<TA, TB>(d, g, m0 + wm * MT * 32, n0 + wn * NT * 32, mlim - wm * MT * 32, nlim - wn * NT * 32, k_lo, k_len, lane, acc);
+    }
+    op_store<TO, PARTIAL, MT, NT>(d, acc, outer, g, m0, n0, mlim, nlim, wm, wn, lane);
 }
 
 template <class G>
@@ -528,23 +628,26 @@ using Cfg128x128 = OpCfg<2, 2, 2, 2>;
 using Cfg128x96 = OpCfg<4, 1, 1, 3>;
 using Cfg128x64 = OpCfg<2, 2, 2, 1>;
 using Cfg64x64 = OpCfg<2, 2, 1, 1>;
+using Cfg64x128 = OpCfg<2, 2, 1, 2>;
 struct TileSize {
     int m, n;
 };
-constexpr int kTileSizes = 4;
-constexpr TileSize kTiles[kTileSizes] = {{128, 128}, {128, 96}, {128, 64}, {64, 64}};
+constexpr int kTileSizes = 5;
+constexpr TileSize kTiles[kTileSizes] = {{128, 128}, {128, 96}, {128, 64}, {64, 64}, {64, 128}};
 
 template <typename TA, typename TB, typename TO, bool RB, Take AV, Take BV>
 int launch_tile(int cfg, const OpDesc& d, hipStream_t st)
 {
     if constexpr (AV != kElements) {
-        if (cfg == 0) return launch_one<OpGemm<TA, TB, TO, Cfg128x128, false, RB, false, AV, BV>>(d, st);
-        if (cfg == 1) return launch_one<OpGemm<TA, TB, TO, Cfg128x96, false, RB, false, AV, BV>>(d, st);
+        switch (cfg) {
+            case 0: return launch_one<OpGemm<TA, TB, TO, Cfg128x128, false, RB, false, AV, BV>>(d, st);
+            case 1: return launch_one<OpGemm<TA, TB, TO, Cfg128x96, false, RB, false, AV, BV>>(d, st);
+            case 2: return launch_one<OpGemm<TA, TB, TO, Cfg128x64, false, RB, false, AV, BV>>(d, st);
+        }
+    } else if (cfg == 4) {
+        return launch_one<OpGemm<TA, TB, TO, Cfg64x128, false, RB, false, AV, BV>>(d, st);
     }
-    switch (cfg) {
-        case 2: return launch_one<OpGemm<TA, TB, TO, Cfg128x64, false, RB, false, AV, BV>>(d, st);
-        default: return launch_one<OpGemm<TA, TB, TO, Cfg64x64, false, RB, false, AV, BV>>(d, st);
-    }
+    return launch_one<OpGemm<TA, TB, TO, Cfg64x64, false, RB, false, AV, BV>>(d, st);
 }
 // The two kinds of contraction of the data path with the ways of taking that occur: both operands in aligned pieces, both in pieces
 // from anywhere, or A element by element (it is strided in the backward, and in the forward under MONARCH_FLAG_PERM_B).
@@ -565,34 +668,37 @@ int launch_op(bool w_rc, int cfg, const OpDesc& d, hipStream_t st)
                                             : launch_tile<TA, TB, TO, true, kPiecesAny, kPiecesAny>(cfg, d, st);
 }
 // dL from dy and U, dR from dU and x: T is the layer's type, U and dU are fp32
-template <typename T, Take BV>
+template <typename T, Take AV, Take BV>
 int launch_wgrad_take(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
 {
     if (cfg == 2)
         return launch_pair<OpGemm<T, float, float, Cfg128x64, true, true, true, kElements, BV>,
-                           OpGemm<float, T, float, Cfg128x64, true, true, true, kElements, BV>>(d0, d1, st);
+                           OpGemm<float, T, float, Cfg128x64, true, true, true, AV, BV>>(d0, d1, st);
     return launch_pair<OpGemm<T, float, float, Cfg64x64, true, true, true, kElements, BV>,
-                       OpGemm<float, T, float, Cfg64x64, true, true, true, kElements, BV>>(d0, d1, st);
+                       OpGemm<float, T, float, Cfg64x64, true, true, true, AV, BV>>(d0, d1, st);
 }
 template <typename T>
 int launch_wgrad(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
 {
     const Take b = d0.b.take < d1.b.take ? d0.b.take : d1.b.take;
-    return b == kPieces16    ? launch_wgrad_take<T, kPieces16>(cfg, d0, d1, st)
-           : b == kPiecesAny ? launch_wgrad_take<T, kPiecesAny>(cfg, d0, d1, st)
-                             : launch_wgrad_take<T, kElements>(cfg, d0, d1, st);
+    if (b == kElements) return launch_wgrad_take<T, kElements, kElements>(cfg, d0, d1, st);
+    return b == kPieces16 && d1.a.take == kPieces16 ? launch_wgrad_take<T, kPieces16, kPieces16>(cfg, d0, d1, st)
+                                                     : launch_wgrad_take<T, kPiecesAny, kPiecesAny>(cfg, d0, d1, st);
 }
 
 int64_t tiles(int64_t n, int t) { return (n + t - 1) / t; }
 
 // The tile that finishes first under a simple model: up to 256 workgroups run one per CU; beyond, rounds of two per CU
 // that share it.  A workgroup costs its (padded) tile plus a fixed share for filling and draining the pipeline.
-// Operands taken element by element need registers that the two largest tiles do not have.
+// Operands taken element by element keep to 64 rows, whose workgroups hold more of the strided loads in flight, and to 128 columns where
+// there are more than 64, since every column tile loads them again (1024 -> 4096 fp32, 8000 rows: step 559 us with 64 x 64,
+// 521 with 64 x 128, 560 with 128 x 64).
 int pick_tile(int64_t M, int N, int G, bool pieces)
 {
-    int best = kTileSizes - 1;
+    if (!pieces) return N > 64 ? 4 : 3;
+    int best = 3;
     double best_t = 1e30;
-    for (int c = pieces ? 0 : 2; c < kTileSizes; ++c) {
+    for (int c = 0; c < 4; ++c) {
         const double wgs = (double)tiles(M, kTiles[c].m) * tiles(N, kTiles[c].n) * G;
         const double pairs = wgs / 512, rounds = wgs <= 256 ? 0.5 : pairs < 4 ? (double)((int64_t)(pairs + 0.999)) : pairs;
         const double t = rounds * (kTiles[c].m * kTiles[c].n + 2048);
@@ -662,7 +768,7 @@ WgradPlan wgrad_plan(const Problem& pb, size_t room = SIZE_MAX)  // room: bytes 
     const int M[2] = {pb.s, pb.q}, N[2] = {pb.q, pb.p};
     WgradPlan pl{};
     double best = 1e30;
-    for (int c = 2; c < kTileSizes; ++c) {  // dy is taken element by element: the two smaller tiles; of them the smallest padded area, weighted by the larger tiles' better reuse
+    for (int c = 2; c < 4; ++c) {  // dy is taken element by element: the two smaller tiles; of them the smallest padded area, weighted by the larger tiles' better reuse
         double area = 0;
         for (int i = 0; i < 2; ++i) area += (double)tiles(M[i], kTiles[c].m) * tiles(N[i], kTiles[c].n) * (kTiles[c].m * kTiles[c].n + 2048);
         if (area < best) {

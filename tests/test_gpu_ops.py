@@ -176,3 +176,39 @@ def test_fp32_weight_gradients_are_as_exact_as_the_simt_kernels(case):
     for name, g, simt, w in zip(("dx", "dR", "dL"), B.monarch_bwd(*args), B.monarch_bwd(*args, flags=B.MONARCH_FLAG_GENERIC), want):
         ours, theirs = parity_util.rel_fro(g.cpu().numpy(), w), parity_util.rel_fro(simt.cpu().numpy(), w)
         assert ours <= 1.05 * theirs, "%s.%s: %.3e and %.3e" % (sh.name, name, ours, theirs)   # 5 %: the order of the SIMT atomics varies
+
+
+# What the bf16 planes of an fp32 operand cannot hold: infinities and NaN (their other planes are NaN), numbers that round to a bf16
+# infinity, and rows so small that planes fall below bf16's smallest number.  Those results are as in fp32, and the rest of the batch is too.
+@pytest.mark.parametrize("case", [(70, 4, 49, 33, 64, "f32"), (300, 4, 192, 192, 192, "f32"), (130, 3, 40, 128, 257, "f32"), (300, 4, 49, 49, 64, "bf16")], ids=str)
+def test_values_that_three_bf16_planes_cannot_hold(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    *dims, dtype = case
+    sh = synth.Shape("planes_%s" % (case,), dtype, *dims, config=980 + parity_util.stable_seed(str(case)))
+    x, R, L, dy = synth.make_inputs(sh)
+    inf = np.float32(np.inf)
+    for a in (x, dy):
+        a[0, 3], a[1, 5], a[2, 7] = inf, -inf, np.nan
+        a[5] *= np.float32(2.0 ** -100)
+        a[6] = 0
+        if dtype == "f32":
+            a[3, 2] = np.float32(3.4e38)   # rounds to infinity in bf16; the sums stay below it
+            a[4] *= np.float32(2.0 ** -115)
+    R[:, :, 2] *= np.float32(2.0 ** -6)
+    L[:, 2 // sh.k, :] *= np.float32(2.0 ** -6)
+    xd, Rd, Ld, dyd = (_dev(a, dtype) for a in (x, R, L, dy))
+    with np.errstate(all="ignore"):
+        want = dict(zip(("dx", "dR", "dL"), oracle.bwd(dy, x, R, L)), y=oracle.fwd(x, R, L))
+    got = dict(zip(("dx", "dR", "dL"), B.monarch_bwd(dyd, xd, Rd, Ld)), y=B.monarch_fwd_ws(xd, Rd, Ld))
+    limit = TOL[dtype]
+    for name in ("y", "dx"):
+        for row in range(sh.B):
+            g, w = got[name][row].float().cpu().numpy().astype(np.float64), want[name][row]
+            fine = np.isfinite(w)
+            assert np.array_equal(np.isnan(g), np.isnan(w)) and np.array_equal(g[~fine & ~np.isnan(w)], w[~fine & ~np.isnan(w)]), (sh.name, name, row)
+            size = np.linalg.norm(w[fine])
+            assert np.linalg.norm(g[fine] - w[fine]) <= limit * size, (sh.name, name, row)
+    for name in ("dR", "dL"):   # sums over rows with infinities, NaN and both: nothing finite may come of what is not
+        assert not np.isfinite(got[name].float().cpu().numpy()[~np.isfinite(want[name])]).any(), (sh.name, name)
