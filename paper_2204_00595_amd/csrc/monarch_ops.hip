@@ -19,7 +19,7 @@
 // the whole (three where the other operand is bf16).  An accumulator takes one rounding per 16 contraction indices and product of planes, so
 // the results are closer to float64 than those of v_mfma_f32_32x32x2_f32 with one per 2 (normal operands, 192 indices: 2.0e-7 against
 // 2.5e-7; with the small products in a sum of their own, as the weight gradients have them, 0.8e-7).  What the planes cannot hold
-// (infinities, results below 2^-80) is found in the finished tile, which is then computed again in fp32 (op_doubtful, op_redo).
+// (infinities, results below 2^-80) is found in the finished tile, which is then computed again in fp32 (planes_doubtful, op_redo).
 //
 // What bounds it: a product of two fp32 operands costs the matrix cores 6/14.4 of its time on the fp32 cores (2058 against
 // 143 TFLOP/s in a loop of MFMAs alone), and what is left is the vector work of splitting (5.5 instructions an element, once per tile that
@@ -37,6 +37,7 @@
 #include "monarch_device.h"
 #include "monarch_mfma_common.h"
 #include "monarch_colsum.h"
+#include "monarch_planes.h"
 
 namespace monarch {
 namespace {
@@ -97,21 +98,6 @@ struct TileDrop {
         return v;
     }
 };
-
-// fp32 pair -> its three bf16 pairs: the value rounded, what that leaves rounded, and the rest, which fits.  The three add up to
-// the value exactly, except where the last one is below bf16's smallest number (values below 2^-110) or the value is not finite.
-__device__ __forceinline__ void split3(uint32_t a, uint32_t b, uint32_t out[3])
-{
-    float x = __uint_as_float(a), y = __uint_as_float(b);
-#pragma unroll
-    for (int w = 0; w < 3; ++w) {
-        out[w] = pack_bf16x2(x, y);
-        if (w < 2) {
-            x -= __uint_as_float(out[w] << 16);
-            y -= __uint_as_float(out[w] & 0xffff0000u);
-        }
-    }
-}
 
 // A C x O tile of an operand (C: extent along the index with the unit or smallest stride, O: along the other one) on
 // its way from memory to LDS [o][c], row stride LSTR elements: bf16 as it is, fp32 as three planes of SZ elements.  Elements past the
@@ -243,55 +229,12 @@ struct OpFrag {
         }
     }
 };
-// Products of the planes whose place values add up to less than 3; the others are below 2^-26 of the whole.  `big` takes the
-// product of the first planes, `small` the rest (they may be one).
-template <int PA, int PB>
-__device__ __forceinline__ void op_products(const bf16x8 (&a)[PA], const bf16x8 (&b)[PB], f32x16& big, f32x16& small)
-{
-#pragma unroll
-    for (int w = 2; w > 0; --w)
-#pragma unroll
-        for (int u = 0; u <= w; ++u)
-            if (u < PA && w - u < PB) small = mfma32(a[u < PA ? u : 0], b[w - u < PB ? w - u : 0], small);
-    big = mfma32(a[0], b[0], big);
-}
-
 template <int WM_, int WN_, int MT_, int NT_>
 struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32
     static constexpr int WM = WM_, WN = WN_, MT = MT_, NT = NT_;
     static constexpr int TM = WM * MT * 32, TN = WN * NT * 32;
 };
 
-// Results of the split planes that are not what the fp32 matrix cores give: a value that is not finite (an infinity times the zero
-// planes of a number is no number) and one so small that planes below bf16's smallest number may have been lost.  Exact zeros
-// are right.  True if any lane of the wave holds such a value.
-template <int MT, int NT>
-__device__ __forceinline__ bool op_doubtful(const f32x16 (&acc)[MT][NT])
-{
-    constexpr uint32_t kSmall = (127u - 80u) << 24, kWidth = (255u << 24) - kSmall;  // twice the bits of 2^-80, and from there to infinity
-    uint32_t worst = 0;
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t t = (__float_as_uint(acc[i][j][r]) << 1) - kSmall;
-                worst = t > worst ? t : worst;
-            }
-    if (!__any(worst >= kWidth)) return false;
-    bool off = false;  // most often these are the zeros of a ragged tile
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t t = __float_as_uint(acc[i][j][r]) << 1;
-                off |= t != 0 && t - kSmall >= kWidth;
-            }
-    return __any(off);
-}
 // The wave's tile (32 MT rows from m0, 32 NT columns from n0) again on the fp32 matrix cores, straight from memory, sixteen
 // contraction indices to a partial sum.
 template <typename T>
@@ -472,7 +415,7 @@ __device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>
                 for (int i = 0; i < MT; ++i)
 #pragma unroll
                     for (int j = 0; j < NT; ++j) {
-                        op_products<PA, PB>(af[i].v, bf[j].v, sums[0][i][j], sums[SUMS - 1][i][j]);
+                        plane_products<PA, PB>(af[i].v, bf[j].v, sums[0][i][j], sums[SUMS - 1][i][j]);
                     }
             }
         }
@@ -509,7 +452,7 @@ __device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>
                 }
     }
     if constexpr (kSplit) {
-        if (op_doubtful(acc))
+        if (planes_doubtful(acc))
             op_redo<TA, TB>(d, g, m0 + wm * MT * 32, n0 + wn * NT * 32, mlim - wm * MT * 32, nlim - wn * NT * 32, k_lo, k_len, lane, acc);
     }
     op_store<TO, PARTIAL, MT, NT>(d, acc, outer, g, m0, n0, mlim, nlim, wm, wn, lane);

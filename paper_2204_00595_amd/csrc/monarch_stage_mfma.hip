@@ -9,9 +9,19 @@
 // One block-diagonal factor is one launch ("stage"), and the vector between the two factors goes through a
 // workspace: at n = 4096 a row of it takes 32 KiB, so a 32-row tile does not fit LDS next to anything else.  A
 // workgroup owns one block g and a share of the row tiles: its wave w keeps the expanded weights of 16 outputs
-// (32 real rows, the M extent of v_mfma_f32_32x32x2_f32) in registers for the whole launch and streams 32-row
-// activation tiles (the N extent) past them; a K = 2 step contracts one component of two complex inputs.
+// (32 real rows, the M extent of the MFMA) in registers for the whole launch and streams 32-row
+// activation tiles (the N extent) past them.
 //   D (32 x 32): acc[r] = D[8*(r/4) + 4*(lane/32) + r%4][lane%32]: a lane holds whole complex outputs of one row.
+//
+// The products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), both operands as three bf16 planes that add up to the fp32
+// values (monarch_planes.h): weights when they are loaded, activations on their way to LDS or, where a wave takes them from memory
+// itself, in its registers.  A step contracts eight complex inputs with six MFMAs in place of sixteen fp32 MFMAs of twice the cycles.
+// A tile with a result that planes cannot hold is computed again in fp32 (stage_redo).  On the fp32 cores the contiguous stages took 54 us
+// at 64 blocks of 64 and 2048 rows and were bound by them (69 to 74 % busy); they take 37 to 40 now, for 134 MB each, 26 us at the
+// rate of a copy.  What is left is one tile per workgroup in flight: the weights' planes take 96 registers, so two workgroups fit a CU.
+// A second tile in flight took a workgroup's registers to the limit and 6 us more, a third workgroup spilled (62 us).
+// Forward and backward together: 64 blocks of 64, 2048 rows: 389 -> 300 us; 48, 1500 rows: 212 -> 159; 32, 2048 rows: 103 -> 85; 64 real
+// blocks of 64, 12000 rows: 895 -> 730.
 //
 // The permutation between the factors is an 8-byte transposition, so it is done where the pieces can be made
 // long: the workspace holds the intermediate in tiles  T[row tile][block][index in block][32 rows]  (the
@@ -21,15 +31,17 @@
 // one L2.
 //
 // Weight gradients: dL[c] = dW[c]^T conj(U[c]),  dR[kk] = dY1[kk]^T conj(x[kk]),  contracted over the batch by the
-// same MFMA (K = two rows x one component); a workgroup owns one block and a share of the row tiles, the shares'
+// same MFMA (K = eight rows x two components); a workgroup owns one block and a share of the row tiles, the shares'
 // partial results go to the workspace and are summed in a fixed order (no atomics).
 //
 // Real fp32 layers with square blocks of 32 or 64 run on the same kernels (template flag REAL): a float2 is then two
 // consecutive values of a row, the activation side is unchanged, the weights are taken as stored and the
 // permutations move single values (see cstage_kernel).
+#include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
 #include "monarch_mfma_common.h"
+#include "monarch_planes.h"
 
 namespace monarch {
 namespace {
@@ -54,17 +66,89 @@ __device__ __forceinline__ int mid_src(int g, int k, int q, bool perm_b)
     return r * k + c;
 }
 
-__device__ __forceinline__ void lds_store_c2(float2* dst, u32x4 v)  // two complex values to an 8-byte aligned place
+// Element i of row `row` of a 32-row tile straight from memory, as the tiles below take it (zero past the end of the batch).
+template <int P, int IN, bool REAL>
+__device__ __forceinline__ float2 act_value(const float2* __restrict__ src, int64_t rt, int row, int g, int i, int k, int64_t ld, int64_t B)
 {
-    dst[0] = make_float2(__uint_as_float(v.x), __uint_as_float(v.y));
-    dst[1] = make_float2(__uint_as_float(v.z), __uint_as_float(v.w));
+    const int64_t r = rt * kRT + row;
+    if constexpr (IN == kInT) return src[(((size_t)rt * k + g) * P + i) * kRT + row];
+    if (r >= B) return make_float2(0.f, 0.f);
+    if constexpr (IN == kInNat) return src[r * ld + (size_t)g * P + i];
+    if constexpr (!REAL) return src[r * ld + (size_t)i * k + g];
+    const float* f = reinterpret_cast<const float*>(src) + r * (2 * ld) + g;
+    return make_float2(f[(size_t)(2 * i) * k], f[(size_t)(2 * i + 1) * k]);
+}
+
+// What lane (col, e = lane % 2) of the wave that owns M tile mt multiplies with input i of block g: its row of the expanded weights at
+// the two components.  CONJT: the conjugate transpose of the stored block; REAL: the weights as they are (CONJT: transposed).
+template <int P, int Q, bool CONJT, bool REAL>
+__device__ __forceinline__ float2 weight_value(const float2* __restrict__ W, int g, int mt, int col, int i)
+{
+    if constexpr (REAL) {
+        const float* Wf = reinterpret_cast<const float*>(W) + (size_t)g * (4 * P * Q);
+        const int nw = 32 * mt + col;
+        if constexpr (CONJT) return make_float2(Wf[(size_t)(2 * i) * (2 * Q) + nw], Wf[(size_t)(2 * i + 1) * (2 * Q) + nw]);
+        return *reinterpret_cast<const float2*>(Wf + (size_t)nw * (2 * P) + 2 * i);
+    } else {
+        const int e = col & 1;
+        int jw = 16 * mt + (col >> 1);
+        if (Q % 16 != 0 && jw >= Q) jw = Q - 1;  // an output that does not exist
+        const float2* Wg = W + (size_t)g * P * Q;
+        constexpr float sgn = CONJT ? -1.f : 1.f;
+        const float2 w = CONJT ? Wg[i * Q + jw] : Wg[jw * P + i];
+        return make_float2(e ? sgn * w.y : w.x, e ? w.x : -sgn * w.y);
+    }
+}
+
+// A lane's weights of an M tile as planes: step t contracts the inputs 8 t + 4 (lane / 32) .. + 3.
+template <int P, int Q, bool CONJT, bool REAL>
+__device__ __forceinline__ void load_weights(bf16x8 (&A)[P / 8][3], const float2* __restrict__ W, int g, int mt, int col, int kh)
+{
+#pragma unroll
+    for (int t = 0; t < P / 8; ++t) {
+        uint32_t w[4][3];
+#pragma unroll
+        for (int c = 0; c < 4; ++c) {
+            const float2 v = weight_value<P, Q, CONJT, REAL>(W, g, mt, col, 8 * t + 4 * kh + c);
+            split3(__float_as_uint(v.x), __float_as_uint(v.y), w[c]);
+        }
+#pragma unroll
+        for (int u = 0; u < 3; ++u) A[t][u] = as_bf16x8(u32x4{w[0][u], w[1][u], w[2][u], w[3][u]});
+    }
+}
+// four complex values (REAL: pairs) -> planes
+__device__ __forceinline__ void split_four(const float2 (&v)[4], bf16x8 (&b)[3])
+{
+    uint32_t w[4][3];
+#pragma unroll
+    for (int c = 0; c < 4; ++c) split3(__float_as_uint(v[c].x), __float_as_uint(v[c].y), w[c]);
+#pragma unroll
+    for (int u = 0; u < 3; ++u) b[u] = as_bf16x8(u32x4{w[0][u], w[1][u], w[2][u], w[3][u]});
+}
+
+// A tile whose planes do not hold it (planes_doubtful) again in fp32.
+template <int P, int Q, int IN, bool CONJT, bool REAL>
+__device__ __forceinline__ void stage_redo(f32x16& acc, const float2* __restrict__ in, const float2* __restrict__ W, int64_t rt, int g, int mt,
+                                           int k, int64_t ld, int64_t B, int lane)
+{
+    const int col = lane & 31, kh = lane >> 5;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma clang loop unroll(disable)
+    for (int u = 0; u < P / 2; ++u) {
+        const float2 w = weight_value<P, Q, CONJT, REAL>(W, g, mt, col, 2 * u + kh);
+        const float2 x = act_value<P, IN, REAL>(in, rt, col, g, 2 * u + kh, k, ld, B);
+        acc = mfma_f32(w.x, x.x, acc);
+        acc = mfma_f32(w.y, x.y, acc);
+    }
 }
 
 // A 32-row tile of one block's complex values, P per row, fetched into registers and later written to LDS.
-//   kInNat:    src[row][g*P + i]                          LDS [row][P + 1]
-//   kInGather: src[row][i*k + g]                          LDS [row][P + 1]
-//   kInT:      src tile (rt, g): [i][32 rows], contiguous LDS [i][32]
-// Rows past the end of the batch read as zeros (kInT: the producer wrote zeros there).
+//   kInNat:    src[row][g*P + i]
+//   kInGather: src[row][i*k + g]
+//   kInT:      src tile (rt, g): [i][32 rows], contiguous
+// LDS: three bf16 planes (monarch_planes.h) of [row][2 P + 8], a row's components in order; the 16 bytes of padding make a row an odd
+// number of 16-byte units, so that eight rows' pieces fall on different banks.  Rows past the end of the batch read as zeros (kInT: the producer wrote zeros there).
 // REAL (real fp32 data, two consecutive values per float2): only the gathering form differs, whose pieces are then
 // single floats, src[row][i'*k + g] for the 2P real indices i' of the block.
 template <int P, int NTHR, int IN, bool REAL = false>
@@ -72,8 +156,7 @@ struct ActTile {
     static constexpr int kAll = (IN == kInGather) ? kRT * P : kRT * P / 2;
     static constexpr int kPieces = (kAll + NTHR - 1) / NTHR;  // per thread
     static __device__ __forceinline__ bool has(int idx) { return kAll % NTHR == 0 || idx < kAll; }
-    static constexpr int kStride = (IN == kInT) ? kRT : P + 1;
-    static constexpr int kLen = (IN == kInT) ? P * kRT : kRT * (P + 1);
+    static constexpr int kStride = 2 * P + 8, kPlane = kRT * kStride, kLen = 3 * kPlane;  // bf16 values
     static_assert(!REAL || kAll % NTHR == 0, "tile does not divide over the threads");
     u32x4 v[IN == kInGather ? (kPieces + 1) / 2 : kPieces];
 
@@ -112,40 +195,62 @@ struct ActTile {
         }
     }
 
-    __device__ __forceinline__ void to_lds(float2* act, int tid) const
+    __device__ __forceinline__ void to_lds(bf16_t* act, int tid) const
     {
         if constexpr (IN == kInNat) {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / (P / 2), c2 = idx - row * (P / 2);
-                if (has(idx)) lds_store_c2(act + row * kStride + 2 * c2, v[n]);
+                uint32_t a[3], b[3];
+                split3(v[n].x, v[n].y, a);
+                split3(v[n].z, v[n].w, b);
+                if (!has(idx)) continue;
+#pragma unroll
+                for (int u = 0; u < 3; ++u) *reinterpret_cast<u32x2*>(act + u * kPlane + row * kStride + 4 * c2) = u32x2{a[u], b[u]};
             }
         } else if constexpr (IN == kInGather && REAL) {
-            float* actf = reinterpret_cast<float*>(act);
 #pragma unroll
             for (int n = 0; n < 2 * kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / (2 * P), i = idx - row * (2 * P);
-                actf[row * (2 * kStride) + i] = __uint_as_float(v[n / 4][n % 4]);
+                uint32_t a[3];
+                split3(v[n / 4][n % 4], 0u, a);
+#pragma unroll
+                for (int u = 0; u < 3; ++u) act[u * kPlane + row * kStride + i] = (bf16_t)a[u];
             }
         } else if constexpr (IN == kInGather) {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
                 const int idx = tid + n * NTHR, row = idx / P, i = idx - row * P;
                 const u32x4 w = v[n / 2];
-                if (has(idx)) act[row * kStride + i] = (n & 1) ? make_float2(__uint_as_float(w.z), __uint_as_float(w.w))
-                                                 : make_float2(__uint_as_float(w.x), __uint_as_float(w.y));
+                uint32_t a[3];
+                if (n & 1) split3(w.z, w.w, a);
+                else split3(w.x, w.y, a);
+                if (!has(idx)) continue;
+#pragma unroll
+                for (int u = 0; u < 3; ++u) *reinterpret_cast<uint32_t*>(act + u * kPlane + row * kStride + 2 * i) = a[u];
             }
         } else {
 #pragma unroll
-            for (int n = 0; n < kPieces; ++n)
-                if (has(tid + n * NTHR)) *reinterpret_cast<u32x4*>(act + 2 * (tid + n * NTHR)) = v[n];
+            for (int n = 0; n < kPieces; ++n) {
+                const int idx = tid + n * NTHR, i = idx / (kRT / 2), row = 2 * (idx - i * (kRT / 2));
+                uint32_t a[3], b[3];
+                split3(v[n].x, v[n].y, a);
+                split3(v[n].z, v[n].w, b);
+                if (!has(idx)) continue;
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    *reinterpret_cast<uint32_t*>(act + u * kPlane + row * kStride + 2 * i) = a[u];
+                    *reinterpret_cast<uint32_t*>(act + u * kPlane + (row + 1) * kStride + 2 * i) = b[u];
+                }
+            }
         }
     }
 
-    // element i of row `row`
-    static __device__ __forceinline__ float2 at(const float2* act, int i, int row)
+    // the MFMA operand of step t: lane (row, h) the components 16 t + 8 h ..
+    static __device__ __forceinline__ void read(bf16x8 (&b)[3], const bf16_t* act, int t, int lane)
     {
-        return (IN == kInT) ? act[i * kRT + row] : act[row * kStride + i];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) b[u] = as_bf16x8(lds128(act + u * kPlane + (lane & 31) * kStride + 16 * t + 8 * (lane >> 5)));
     }
 };
 
@@ -162,7 +267,7 @@ struct ActTile {
 // (CONJT: transposed), and since the permutations move single values, the two values of a result pair go to their
 // places separately (in the tiled workspace, to the pair slot [index / 2][row][index % 2] of the consumer's block).
 template <int P, int Q, int IN, int OUT, bool CONJT, bool REAL = false>
-__global__ void __launch_bounds__(kTileWaves<Q> * 64)
+__global__ void __launch_bounds__(kTileWaves<Q> * 64, P >= 56 || IN == kInGather ? 2 : 3)
 cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float2* __restrict__ out, int64_t B,
               int k, int nsplit, int perm_b)
 {
@@ -170,46 +275,33 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
     constexpr bool kWhole = Q % 16 == 0;  // else the last wave has outputs that do not exist
     using Tile = ActTile<P, NTHR, IN, REAL>;
     constexpr int OSTR = Q + 1;
-    __shared__ __align__(16) float2 act[2][Tile::kLen];
+    // kOutNat: the barrier before the results leave LDS also frees the tile, so one buffer will do
+    constexpr int kBufs = OUT == kOutNat ? 1 : 2;
+    __shared__ __align__(16) bf16_t act[kBufs][Tile::kLen];
     __shared__ __align__(16) float2 ost[OUT == kOutNat ? kRT * OSTR : 1];
 
     const int g = (int)blockIdx.x / nsplit, split = (int)blockIdx.x - g * nsplit;
     const int tid = threadIdx.x, lane = tid & 63, mt = tid >> 6;
-    const int col = lane & 31, kh = lane >> 5, e = lane & 1;
+    const int col = lane & 31, kh = lane >> 5;
     const int64_t ntiles = (B + kRT - 1) / kRT;
     const int64_t ld_in = (int64_t)k * P, ld_out = (int64_t)k * Q;
     const bool pb = perm_b != 0;
 
-    // this lane's rows of the expanded weights: real row 2*jw + e, for the inputs i = 2u + kh
-    float A0[P / 2], A1[P / 2];
-    {
-        if constexpr (REAL) {
-            const int nw = 32 * mt + col;  // this lane's output of the block
-            const float* Wf = reinterpret_cast<const float*>(W) + (size_t)g * (4 * P * Q);
+    bf16x8 A[P / 8][3];
+    load_weights<P, Q, CONJT, REAL>(A, W, g, mt, col, kh);
+
+    // where this lane's results go within a tile of the workspace: 32-bit offsets, which leave a third workgroup room
+    constexpr bool kTiled = OUT == kOutTFwd || OUT == kOutTBwd;
+    constexpr int kOuts = kTiled ? (REAL ? 16 : 8) : 1;
+    uint32_t off[kOuts];
+    if constexpr (kTiled) {
 #pragma unroll
-            for (int u = 0; u < P / 2; ++u) {
-                const int i = 2 * u + kh;  // inputs 2i and 2i + 1
-                if constexpr (CONJT) {
-                    A0[u] = Wf[(size_t)(2 * i) * (2 * Q) + nw];
-                    A1[u] = Wf[(size_t)(2 * i + 1) * (2 * Q) + nw];
-                } else {
-                    const float2 w = *reinterpret_cast<const float2*>(Wf + (size_t)nw * (2 * P) + 2 * i);
-                    A0[u] = w.x;
-                    A1[u] = w.y;
-                }
-            }
-        } else {
-            int jw = 16 * mt + (col >> 1);
-            if (!kWhole && jw >= Q) jw = Q - 1;
-            const float2* Wg = W + (size_t)g * P * Q;
-            constexpr float sgn = CONJT ? -1.f : 1.f;
-#pragma unroll
-            for (int u = 0; u < P / 2; ++u) {
-                const int i = 2 * u + kh;
-                const float2 w = CONJT ? Wg[i * Q + jw] : Wg[jw * P + i];
-                A0[u] = e ? sgn * w.y : w.x;
-                A1[u] = e ? w.x : -sgn * w.y;
-            }
+        for (int o = 0; o < kOuts; ++o) {
+            constexpr int E = REAL ? 2 : 1;  // values per float2 of the output
+            const int j = 16 * mt + 4 * (o / (2 * E)) + 2 * kh + o / E % 2, n = E * j + o % E;
+            const int d = (OUT == kOutTFwd) ? mid_dest(g * E * Q + n, k, E * Q, pb) : mid_src(g * E * Q + n, k, E * Q, pb);
+            const int blk = d / (E * Q), idx = d - blk * (E * Q);
+            off[o] = (uint32_t)(((blk * Q + idx / E) * kRT + col) * E + idx % E) * (uint32_t)(8 / E);
         }
     }
 
@@ -217,7 +309,7 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
     int64_t rt = split;
     if (rt < ntiles) pre.fetch(in, rt, g, k, ld_in, B, tid);
     for (int it = 0; rt < ntiles; rt += nsplit, ++it) {
-        float2* a = act[it & 1];
+        bf16_t* a = act[kBufs == 2 ? it & 1 : 0];
         pre.to_lds(a, tid);
         lds_barrier();
         if (rt + nsplit < ntiles) pre.fetch(in, rt + nsplit, g, k, ld_in, B, tid);
@@ -226,11 +318,12 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
 #pragma unroll
         for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-        for (int u = 0; u < P / 2; ++u) {
-            const float2 xv = Tile::at(a, 2 * u + kh, col);
-            acc = mfma_f32(A0[u], xv.x, acc);
-            acc = mfma_f32(A1[u], xv.y, acc);
+        for (int t = 0; t < P / 8; ++t) {
+            bf16x8 xv[3];
+            Tile::read(xv, a, t, lane);
+            plane_products<3, 3>(A[t], xv, acc, acc);
         }
+        if (planes_doubtful(acc)) stage_redo<P, Q, IN, CONJT, REAL>(acc, in, W, rt, g, mt, k, ld_in, B, lane);
 
         const int64_t row = rt * kRT + col;
         if constexpr (OUT == kOutNat) {
@@ -250,61 +343,44 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
                 if (rt * kRT + r < B)
                     *reinterpret_cast<f32x4*>(out + (rt * kRT + r) * ld_out + (size_t)g * Q + 2 * c2) = f32x4{v0.x, v0.y, v1.x, v1.y};
             }
+        } else if constexpr (kTiled) {
+            char* const to = reinterpret_cast<char*>(out + (size_t)rt * k * (Q * kRT));
+#pragma unroll
+            for (int o = 0; o < kOuts; ++o) {
+                if (!kWhole && 16 * mt + 4 * (o / 2) + 2 * kh + o % 2 >= Q) continue;
+                if constexpr (REAL) *reinterpret_cast<float*>(to + off[o]) = acc[o];
+                else *reinterpret_cast<float2*>(to + off[o]) = make_float2(acc[2 * o], acc[2 * o + 1]);
+            }
         } else {
 #pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int j = 16 * mt + 4 * q4 + 2 * kh + h;
-                    if (!kWhole && j >= Q) continue;
-                    const float2 v = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
-                    if constexpr (REAL) {
-                        float* outf = reinterpret_cast<float*>(out);
-#pragma unroll
-                        for (int t = 0; t < 2; ++t) {
-                            const int n = 2 * j + t;  // output of the block, 0 .. 2Q-1
-                            const float val = t ? v.y : v.x;
-                            if constexpr (OUT == kOutScatter) {
-                                if (row < B) outf[row * (2 * ld_out) + (size_t)n * k + g] = val;
-                            } else {
-                                const int d = (OUT == kOutTFwd) ? mid_dest(g * 2 * Q + n, k, 2 * Q, pb) : mid_src(g * 2 * Q + n, k, 2 * Q, pb);
-                                const int blk = d / (2 * Q), idx = d - blk * (2 * Q);
-                                outf[((((size_t)rt * k + blk) * Q + (idx >> 1)) * kRT + col) * 2 + (idx & 1)] = val;
-                            }
-                        }
-                    } else if constexpr (OUT == kOutScatter) {
-                        if (row < B) out[row * ld_out + (size_t)j * k + g] = v;
-                    } else {
-                        const int d = (OUT == kOutTFwd) ? mid_dest(g * Q + j, k, Q, pb) : mid_src(g * Q + j, k, Q, pb);
-                        const int blk = d / Q, idx = d - blk * Q;
-                        out[(((size_t)rt * k + blk) * Q + idx) * kRT + col] = v;
-                    }
+            for (int o = 0; o < 8; ++o) {
+                const int j = 16 * mt + 4 * (o / 2) + 2 * kh + o % 2;
+                if (!kWhole && j >= Q) continue;
+                if (row >= B) continue;
+                if constexpr (REAL) {
+                    float* outf = reinterpret_cast<float*>(out) + row * (2 * ld_out) + g;
+                    outf[(size_t)(2 * j) * k] = acc[2 * o];
+                    outf[(size_t)(2 * j + 1) * k] = acc[2 * o + 1];
+                } else {
+                    out[row * ld_out + (size_t)j * k + g] = make_float2(acc[2 * o], acc[2 * o + 1]);
                 }
+            }
         }
     }
 }
 
 // The two stages that touch the outer permutation (y[b][l*k + c] written, dy read the same way), for k a multiple
-// of 8: eight blocks per workgroup, wave w = block 8*oct + w, every wave the same MTW M tiles (16 outputs each) of its
+// of 8: eight blocks per workgroup, wave w = block 8*oct + w, every wave the same M tile (16 outputs) of its
 // own block, so that the pieces of the permuted side are the eight blocks' values of one (row, l): 64 contiguous bytes
-// instead of 8.  Workgroups that differ only in their M tiles read the same activations (they sit on one XCD); where
-// that re-reading costs more than the lost occupancy a wave takes two M tiles (measured: the scattering stage at blocks
-// of 64, four M tiles; the gathering stage at blocks of 32).
+// instead of 8.  Workgroups that differ only in their M tile read the same activations (they sit on one XCD) and split them
+// again, which costs less than the registers of a second M tile.
 //
 // cscatter8_kernel: tiled workspace -> y.  The activations of a wave's block are MFMA operands exactly as they lie
 // in the workspace (lane = row, 512 contiguous bytes per wave load), so they go from global memory to registers
 // directly, ahead of the MFMAs; the results are exchanged through LDS as [row][l][block].
-template <int P>
-constexpr int kMTilesPerWave = P >= 64 ? 2 : 1;
-// the gathering stage has less room (its chunk staging registers): two M tiles per wave would spill at blocks of 64,
-// and only pay at the batch sizes of the real fp32 layers with blocks of 64 (P = 32 pairs)
-template <int P, bool REAL>
-constexpr int kMTilesPerWaveGather = (REAL && P == 32) ? 2 : 1;
-
 template <int P, int Q>
 struct Scatter8 {
-    static constexpr int MTW = kMTilesPerWave<Q>;
-    static constexpr int kRow = 16 * MTW * 8 + 1;  // values per row of the exchange buffer
+    static constexpr int kRow = 16 * 8 + 1;  // values per row of the exchange buffer
     static constexpr size_t kLds = 2 * (size_t)kRT * kRow * sizeof(float2);
 };
 
@@ -314,125 +390,111 @@ __global__ void __launch_bounds__(512)
 cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, float2* __restrict__ out, int64_t B, int k,
                  int nsplit)
 {
-    constexpr int MTW = Scatter8<P, Q>::MTW;
-    constexpr int MTG = kTileWaves<Q> / MTW;  // groups of M tiles = workgroups per (block octet, split)
-    constexpr int NCH = MTW == 1 ? 1 : 4;  // pieces a tile's activations are fetched in
-    constexpr int CH = P / 2 / NCH;        // input pairs per piece
+    constexpr int MTG = kTileWaves<Q>;  // workgroups per (block octet, split)
+    constexpr int STEPS = P / 8, NCH = STEPS >= 6 ? 2 : 1;  // pieces a tile's activations are fetched in
+    constexpr int CH = (STEPS + NCH - 1) / NCH;              // steps of the first piece
     constexpr int OROW = Scatter8<P, Q>::kRow;
     extern __shared__ __align__(16) float2 ost8[];
 
     int bid = (int)blockIdx.x;
     const int split = bid % nsplit;
     bid /= nsplit;
-    const int mt0 = (bid % MTG) * MTW, oct = bid / MTG;
+    const int mt = bid % MTG, oct = bid / MTG;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int g = 8 * oct + w;
-    const int col = lane & 31, kh = lane >> 5, e = lane & 1;
+    const int col = lane & 31, kh = lane >> 5;
     const int64_t ntiles = (B + kRT - 1) / kRT;
     const int64_t ld_out = (int64_t)k * Q;
 
-    float A0[MTW][P / 2], A1[MTW][P / 2];
+    bf16x8 A[STEPS][3];
+    load_weights<P, Q, false, REAL>(A, W, g, mt, col, kh);
+    auto load = [&](float2 (&buf)[CH][4], int64_t rt, int part) {
+        const float2* src = T + ((size_t)rt * k + g) * (P * kRT) + (size_t)(8 * part * CH + 4 * kh) * kRT + col;
 #pragma unroll
-    for (int m = 0; m < MTW; ++m) {
-        if constexpr (REAL) {
-            const float* Wf = reinterpret_cast<const float*>(W) + (size_t)g * (4 * P * Q) + (size_t)(32 * (mt0 + m) + col) * (2 * P);
+        for (int t = 0; t < CH; ++t)
+            if (part * CH + t < STEPS) {
 #pragma unroll
-            for (int u = 0; u < P / 2; ++u) {
-                const float2 wv = *reinterpret_cast<const float2*>(Wf + 2 * (2 * u + kh));
-                A0[m][u] = wv.x;
-                A1[m][u] = wv.y;
+                for (int c = 0; c < 4; ++c) buf[t][c] = src[(8 * t + c) * kRT];
             }
-        } else {
-            int jw = 16 * (mt0 + m) + (col >> 1);
-            if (Q % 16 != 0 && jw >= Q) jw = Q - 1;  // an output that does not exist
-            const float2* Wg = W + (size_t)g * P * Q;
-#pragma unroll
-            for (int u = 0; u < P / 2; ++u) {
-                const float2 wv = Wg[jw * P + 2 * u + kh];
-                A0[m][u] = e ? wv.y : wv.x;
-                A1[m][u] = e ? wv.x : -wv.y;
-            }
-        }
-    }
-    auto load = [&](float2 (&buf)[CH], int64_t rt, int part) {
-        const float2* src = T + ((size_t)rt * k + g) * (P * kRT) + (size_t)(2 * part * CH + kh) * kRT + col;
-#pragma unroll
-        for (int u = 0; u < CH; ++u) buf[u] = src[2 * u * kRT];
     };
-    f32x16 acc[MTW];
+    f32x16 acc;
     auto zero = [&]() {
 #pragma unroll
-        for (int m = 0; m < MTW; ++m)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
     };
-    auto mma = [&](const float2 (&buf)[CH], int part) {
+    auto mma = [&](const float2 (&buf)[CH][4], auto which) {
+        constexpr int part = decltype(which)::value;
 #pragma unroll
-        for (int u = 0; u < CH; ++u)
-#pragma unroll
-            for (int m = 0; m < MTW; ++m) {
-                acc[m] = mfma_f32(A0[m][part * CH + u], buf[u].x, acc[m]);
-                acc[m] = mfma_f32(A1[m][part * CH + u], buf[u].y, acc[m]);
+        for (int t = 0; t < CH; ++t)
+            if constexpr (part * CH < STEPS) {
+                if (part * CH + t < STEPS) {
+                    bf16x8 b[3];
+                    split_four(buf[t], b);
+                    plane_products<3, 3>(A[part * CH + t], b, acc, acc);
+                }
             }
+    };
+    auto mend = [&](int64_t rt) {
+        if (planes_doubtful(acc)) stage_redo<P, Q, kInT, false, REAL>(acc, T, W, rt, g, mt, k, 0, B, lane);
     };
     // the results of one tile: exchange through LDS buffer it & 1 (one barrier per tile), then the 64-byte (REAL:
     // 32-byte) pieces of y
     auto emit = [&](int64_t rt, int it) {
         float2* o = ost8 + (it & 1) * (kRT * OROW);
         if constexpr (REAL) {
-            // [row][32 * MTW outputs][8 blocks] floats in the same space; acc[m][r] is output 8*(r/4) + 4*kh + r%4 of M tile m
+            // [row][32 outputs][8 blocks] floats in the same space; acc[r] is output 8*(r/4) + 4*kh + r%4
             float* of = reinterpret_cast<float*>(o);
 #pragma unroll
-            for (int m = 0; m < MTW; ++m)
-#pragma unroll
-                for (int r = 0; r < 16; ++r) of[col * (2 * OROW) + (32 * m + 8 * (r / 4) + 4 * kh + (r % 4)) * 8 + w] = acc[m][r];
+            for (int r = 0; r < 16; ++r) of[col * (2 * OROW) + (8 * (r / 4) + 4 * kh + (r % 4)) * 8 + w] = acc[r];
             lds_barrier();
             float* outf = reinterpret_cast<float*>(out);
 #pragma unroll
-            for (int n = 0; n < 4 * MTW; ++n) {  // 32 rows x 32 * MTW outputs x 2 halves of the eight blocks, 16 bytes each
-                const int idx = tid + n * 512, part = idx & 1, nl = (idx >> 1) % (32 * MTW), r = idx / (64 * MTW);
+            for (int n = 0; n < 4; ++n) {  // 32 rows x 32 outputs x 2 halves of the eight blocks, 16 bytes each
+                const int idx = tid + n * 512, part = idx & 1, nl = (idx >> 1) & 31, r = idx >> 6;
                 const float2 v0 = *reinterpret_cast<const float2*>(of + r * (2 * OROW) + nl * 8 + 4 * part);
                 const float2 v1 = *reinterpret_cast<const float2*>(of + r * (2 * OROW) + nl * 8 + 4 * part + 2);
                 if (rt * kRT + r < B)
-                    *reinterpret_cast<f32x4*>(outf + (rt * kRT + r) * (2 * ld_out) + (size_t)(32 * mt0 + nl) * k + 8 * oct + 4 * part) =
+                    *reinterpret_cast<f32x4*>(outf + (rt * kRT + r) * (2 * ld_out) + (size_t)(32 * mt + nl) * k + 8 * oct + 4 * part) =
                         f32x4{v0.x, v0.y, v1.x, v1.y};
             }
         } else {
 #pragma unroll
-            for (int m = 0; m < MTW; ++m)
+            for (int q4 = 0; q4 < 4; ++q4)
 #pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h)
-                        o[col * OROW + (16 * m + 4 * q4 + 2 * kh + h) * 8 + w] = make_float2(acc[m][4 * q4 + 2 * h], acc[m][4 * q4 + 2 * h + 1]);
+                for (int h = 0; h < 2; ++h)
+                    o[col * OROW + (4 * q4 + 2 * kh + h) * 8 + w] = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
             lds_barrier();
 #pragma unroll
-            for (int n = 0; n < 4 * MTW; ++n) {  // 32 rows x 16 * MTW outputs x 4 pairs of blocks, 16 bytes each
-                const int idx = tid + n * 512, c2 = idx & 3, ll = (idx >> 2) % (16 * MTW), r = idx / (64 * MTW);
+            for (int n = 0; n < 4; ++n) {  // 32 rows x 16 outputs x 4 pairs of blocks, 16 bytes each
+                const int idx = tid + n * 512, c2 = idx & 3, ll = (idx >> 2) & 15, r = idx >> 6;
                 const float2 v0 = o[r * OROW + ll * 8 + 2 * c2], v1 = o[r * OROW + ll * 8 + 2 * c2 + 1];
-                if (rt * kRT + r < B && (Q % 16 == 0 || 16 * mt0 + ll < Q))
-                    *reinterpret_cast<f32x4*>(out + (rt * kRT + r) * ld_out + (size_t)(16 * mt0 + ll) * k + 8 * oct + 2 * c2) =
+                if (rt * kRT + r < B && (Q % 16 == 0 || 16 * mt + ll < Q))
+                    *reinterpret_cast<f32x4*>(out + (rt * kRT + r) * ld_out + (size_t)(16 * mt + ll) * k + 8 * oct + 2 * c2) =
                         f32x4{v0.x, v0.y, v1.x, v1.y};
             }
         }
     };
 
-    // two register sets: the next piece of the activations (a whole tile, or a quarter where the weights of two M
-    // tiles leave less room) is on its way while the current one is multiplied
-    float2 xa[CH], xb[CH];
+    // two register sets: the next piece of the activations (a whole tile, or half of one where the weights leave less room) is on
+    // its way while the current one is multiplied
+    typedef std::integral_constant<int, 0> First;
+    typedef std::integral_constant<int, 1> Second;
+    float2 xa[CH][4], xb[CH][4];
     int64_t rt = split;
     if (rt < ntiles) load(xa, rt, 0);
     if constexpr (NCH == 1) {
         for (int it = 0; rt < ntiles; it += 2) {
             if (rt + nsplit < ntiles) load(xb, rt + nsplit, 0);
             zero();
-            mma(xa, 0);
+            mma(xa, First());
+            mend(rt);
             emit(rt, it);
             rt += nsplit;
             if (rt >= ntiles) break;
             if (rt + nsplit < ntiles) load(xa, rt + nsplit, 0);
             zero();
-            mma(xb, 0);
+            mma(xb, First());
+            mend(rt);
             emit(rt, it + 1);
             rt += nsplit;
         }
@@ -440,13 +502,10 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
         for (int it = 0; rt < ntiles; rt += nsplit, ++it) {
             zero();
             load(xb, rt, 1);
-            mma(xa, 0);
-            load(xa, rt, 2);
-            mma(xb, 1);
-            load(xb, rt, 3);
-            mma(xa, 2);
+            mma(xa, First());
             if (rt + nsplit < ntiles) load(xa, rt + nsplit, 0);
-            mma(xb, 3);
+            mma(xb, Second());
+            mend(rt);
             emit(rt, it);
         }
     }
@@ -454,14 +513,13 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
 
 // cgather8_kernel: dy (read through the outer permutation) -> tiled workspace, weights conj(L[c])^T.  The eight
 // blocks' values of 32 rows x 16 inputs come in as 64-byte pieces and are laid out in LDS as one plane per block,
-// [row][16 + 1]; a wave takes its operands from its own plane.  Four (P = 64) such chunks make a tile; the next
-// chunk is fetched into registers while the current one is multiplied.  A wave takes kMTilesPerWaveGather M tiles (see
-// cscatter8_kernel).  EMIT: the workgroups of M tile 0 also write
+// [row][16 + 2]; a wave takes its operands from its own plane.  Four (P = 64) such chunks make a tile; the next
+// chunk is fetched into registers while the current one is multiplied.  EMIT: the workgroups of M tile 0 also write
 // the chunk to the workspace in the tiled order (dW[row tile][block][l][32 rows]), the operand of the weight-gradient
 // kernel, which then does not have to gather dy again.
 template <int P>
 struct Gather8 {
-    static constexpr int kPlane = kRT * 17 + 1;
+    static constexpr int kPlane = kRT * 18 + 2;
     static constexpr size_t kLds = 2 * (size_t)8 * kPlane * sizeof(float2);
 };
 
@@ -472,8 +530,7 @@ __global__ void __launch_bounds__(512)
 cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float2* __restrict__ out,
                 float2* __restrict__ dwt, int64_t B, int k, int nsplit, int perm_b)
 {
-    constexpr int MTW = kMTilesPerWaveGather<Q, REAL>;
-    constexpr int MTG = kTileWaves<Q> / MTW;
+    constexpr int MTG = kTileWaves<Q>;
     constexpr int NCHUNK = (P + 15) / 16;
     constexpr int PLANE = Gather8<P>::kPlane;
     extern __shared__ __align__(16) float2 gat8[];
@@ -481,36 +538,16 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
     int bid = (int)blockIdx.x;
     const int split = bid % nsplit;
     bid /= nsplit;
-    const int mt0 = (bid % MTG) * MTW, oct = bid / MTG;
+    const int mt = bid % MTG, oct = bid / MTG;
     const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
     const int g = 8 * oct + w;
-    const int col = lane & 31, kh = lane >> 5, e = lane & 1;
+    const int col = lane & 31, kh = lane >> 5;
     const int64_t ntiles = (B + kRT - 1) / kRT;
     const int64_t ld_in = (int64_t)k * P;
     const bool pb = perm_b != 0;
 
-    float A0[MTW][P / 2], A1[MTW][P / 2];
-#pragma unroll
-    for (int m = 0; m < MTW; ++m) {
-        if constexpr (REAL) {
-            const float* Wf = reinterpret_cast<const float*>(W) + (size_t)g * (4 * P * Q) + 32 * (mt0 + m) + col;
-#pragma unroll
-            for (int u = 0; u < P / 2; ++u) {
-                A0[m][u] = Wf[(size_t)(2 * (2 * u + kh)) * (2 * Q)];
-                A1[m][u] = Wf[(size_t)(2 * (2 * u + kh) + 1) * (2 * Q)];
-            }
-        } else {
-            int jw = 16 * (mt0 + m) + (col >> 1);
-            if (Q % 16 != 0 && jw >= Q) jw = Q - 1;
-            const float2* Wg = W + (size_t)g * P * Q;
-#pragma unroll
-            for (int u = 0; u < P / 2; ++u) {
-                const float2 wv = Wg[(2 * u + kh) * Q + jw];
-                A0[m][u] = e ? -wv.y : wv.x;
-                A1[m][u] = e ? wv.x : wv.y;
-            }
-        }
-    }
+    bf16x8 A[P / 8][3];
+    load_weights<P, Q, true, REAL>(A, W, g, mt, col, kh);
     u32x4 pre[4];
     auto fetch = [&](int64_t rt, int ch) {
 #pragma unroll
@@ -536,11 +573,11 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
                 const int part = idx & 1, il = (idx >> 1) & 31;
                 float* bf = reinterpret_cast<float*>(buf);
 #pragma unroll
-                for (int t = 0; t < 4; ++t) bf[(4 * part + t) * (2 * PLANE) + r * 34 + il] = __uint_as_float(pre[n][t]);
+                for (int t = 0; t < 4; ++t) bf[(4 * part + t) * (2 * PLANE) + r * 36 + il] = __uint_as_float(pre[n][t]);
             } else {
                 const int c2 = idx & 3, ll = (idx >> 2) & 15;
-                buf[(2 * c2) * PLANE + r * 17 + ll] = make_float2(__uint_as_float(pre[n].x), __uint_as_float(pre[n].y));
-                buf[(2 * c2 + 1) * PLANE + r * 17 + ll] = make_float2(__uint_as_float(pre[n].z), __uint_as_float(pre[n].w));
+                buf[(2 * c2) * PLANE + r * 18 + ll] = make_float2(__uint_as_float(pre[n].x), __uint_as_float(pre[n].y));
+                buf[(2 * c2 + 1) * PLANE + r * 18 + ll] = make_float2(__uint_as_float(pre[n].z), __uint_as_float(pre[n].w));
             }
         }
     };
@@ -549,11 +586,9 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
     if (rt < ntiles) fetch(rt, 0);
     int cnt = 0;
     for (; rt < ntiles; rt += nsplit) {
-        f32x16 acc[MTW];
+        f32x16 acc;
 #pragma unroll
-        for (int m = 0; m < MTW; ++m)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[m][r] = 0.f;
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
         for (int ch = 0; ch < NCHUNK; ++ch, ++cnt) {
             float2* buf = gat8 + (cnt & 1) * (8 * PLANE);
@@ -563,66 +598,132 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
             else if (rt + nsplit < ntiles) fetch(rt + nsplit, 0);
             const float2* mine = buf + w * PLANE;
 #pragma unroll
-            for (int u = 0; u < 8; ++u) {
-                if (ch * 8 + u >= P / 2) continue;  // the last chunk of a block that is no multiple of 16
-                const float2 xv = mine[col * 17 + 2 * u + kh];
+            for (int u = 0; u < 2; ++u) {
+                if (2 * ch + u >= P / 8) continue;  // the last chunk of a block that is no multiple of 16
+                float2 xv[4];
 #pragma unroll
-                for (int m = 0; m < MTW; ++m) {
-                    acc[m] = mfma_f32(A0[m][ch * 8 + u], xv.x, acc[m]);
-                    acc[m] = mfma_f32(A1[m][ch * 8 + u], xv.y, acc[m]);
+                for (int c = 0; c < 4; c += 2) {
+                    const f32x4 v = *reinterpret_cast<const f32x4*>(mine + col * 18 + 8 * u + 4 * kh + c);
+                    xv[c] = make_float2(v.x, v.y);
+                    xv[c + 1] = make_float2(v.z, v.w);
                 }
+                bf16x8 b[3];
+                split_four(xv, b);
+                plane_products<3, 3>(A[2 * ch + u], b, acc, acc);
             }
             if constexpr (EMIT) {
-                if (mt0 == 0) {
+                if (mt == 0) {
                     float2* dst = dwt + (((size_t)rt * k + g) * P + 16 * ch) * kRT;
 #pragma unroll
                     for (int n = 0; n < 8; ++n)
-                        if (16 * ch + 2 * n < P) dst[(2 * n + kh) * kRT + col] = mine[col * 17 + 2 * n + kh];
+                        if (16 * ch + 2 * n < P) dst[(2 * n + kh) * kRT + col] = mine[col * 18 + 2 * n + kh];
                 }
             }
         }
+        if (planes_doubtful(acc)) stage_redo<P, Q, kInGather, true, REAL>(acc, in, W, rt, g, mt, k, ld_in, B, lane);
+        if constexpr (REAL) {
+            float* outf = reinterpret_cast<float*>(out);
 #pragma unroll
-        for (int m = 0; m < MTW; ++m) {
-            if constexpr (REAL) {
-                float* outf = reinterpret_cast<float*>(out);
-#pragma unroll
-                for (int r = 0; r < 16; ++r) {
-                    const int n = 32 * (mt0 + m) + 8 * (r / 4) + 4 * kh + (r % 4);
-                    const int d = mid_src(g * 2 * Q + n, k, 2 * Q, pb);
-                    const int blk = d / (2 * Q), idx = d - blk * (2 * Q);
-                    outf[((((size_t)rt * k + blk) * Q + (idx >> 1)) * kRT + col) * 2 + (idx & 1)] = acc[m][r];
-                }
-            } else {
-#pragma unroll
-                for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-                    for (int h = 0; h < 2; ++h) {
-                        const int j = 16 * (mt0 + m) + 4 * q4 + 2 * kh + h;
-                        if (Q % 16 != 0 && j >= Q) continue;
-                        const int d = mid_src(g * Q + j, k, Q, pb);
-                        const int blk = d / Q, idx = d - blk * Q;
-                        out[(((size_t)rt * k + blk) * Q + idx) * kRT + col] =
-                            make_float2(acc[m][4 * q4 + 2 * h], acc[m][4 * q4 + 2 * h + 1]);
-                    }
+            for (int r = 0; r < 16; ++r) {
+                const int n = 32 * mt + 8 * (r / 4) + 4 * kh + (r % 4);
+                const int d = mid_src(g * 2 * Q + n, k, 2 * Q, pb);
+                const int blk = d / (2 * Q), idx = d - blk * (2 * Q);
+                outf[((((size_t)rt * k + blk) * Q + (idx >> 1)) * kRT + col) * 2 + (idx & 1)] = acc[r];
             }
+        } else {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+                for (int h = 0; h < 2; ++h) {
+                    const int j = 16 * mt + 4 * q4 + 2 * kh + h;
+                    if (Q % 16 != 0 && j >= Q) continue;
+                    const int d = mid_src(g * Q + j, k, Q, pb);
+                    const int blk = d / Q, idx = d - blk * Q;
+                    out[(((size_t)rt * k + blk) * Q + idx) * kRT + col] = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
+                }
         }
     }
 }
 
+// dy, read through the outer permutation, in tiles dW[row tile][block][l][32 rows]: the operand of the stage that makes dY1 and of the
+// weight gradient.  A workgroup moves 64 consecutive values of 32 rows through LDS (REAL: the 64 blocks from g0 of one pair of
+// inputs, 2 x 64 floats), reading 512 bytes (2 x 256) of a row and writing runs of 256 bytes.  Bound by memory (2048 x 4096
+// complex values: 28 us, 4.8 TB/s).
+template <bool REAL>
+__global__ void __launch_bounds__(256)
+ctile_kernel(const float2* __restrict__ in, float2* __restrict__ out, int64_t B, int k, int P, int chunks)
+{
+    constexpr int kRow = 65;  // float2 (REAL: two rows of 65 floats, the first and the second input)
+    __shared__ float2 buf[kRT * kRow];
+    const int64_t rt = blockIdx.x / chunks;
+    const int ch = (int)(blockIdx.x - rt * chunks), tid = threadIdx.x;
+    const int per = (k + 63) / 64, pair = REAL ? ch / per : 0, g0 = REAL ? (ch - pair * per) * 64 : 0;
+    const int j0 = 64 * ch, n = k * P;  // complex: flat position l * k + c
+    u32x4 v[4];
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int idx = tid + 256 * u, row = idx >> 5, c = idx & 31;
+        const int64_t r = rt * kRT + row;
+        bool in_row;
+        size_t at;
+        if constexpr (REAL) {
+            in_row = g0 + 4 * (c & 15) < k;
+            at = (size_t)r * (2 * n) + (size_t)(2 * pair + (c >> 4)) * k + g0 + 4 * (c & 15);
+        } else {
+            in_row = j0 + 2 * c < n;
+            at = (size_t)r * (2 * n) + 2 * (j0 + 2 * c);
+        }
+        v[u] = r < B && in_row ? ldg128(reinterpret_cast<const float*>(in) + at) : u32x4{0, 0, 0, 0};
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int idx = tid + 256 * u, row = idx >> 5, c = idx & 31;
+        if constexpr (REAL) {
+            float* b = reinterpret_cast<float*>(buf) + row * (2 * kRow) + (c >> 4) * kRow + 4 * (c & 15);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) b[e] = __uint_as_float(v[u][e]);
+        } else {
+            buf[row * kRow + 2 * c] = make_float2(__uint_as_float(v[u].x), __uint_as_float(v[u].y));
+            buf[row * kRow + 2 * c + 1] = make_float2(__uint_as_float(v[u].z), __uint_as_float(v[u].w));
+        }
+    }
+    lds_barrier();
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+        const int idx = tid + 256 * u, row = 2 * (idx & 15), j = idx >> 4;
+        float2 a, b;
+        size_t at;
+        if constexpr (REAL) {
+            if (g0 + j >= k) continue;
+            const float* f = reinterpret_cast<const float*>(buf) + row * (2 * kRow) + j;
+            a = make_float2(f[0], f[kRow]);
+            b = make_float2(f[2 * kRow], f[3 * kRow]);
+            at = (((size_t)rt * k + g0 + j) * P + pair) * kRT + row;
+        } else {
+            if (j0 + j >= n) continue;
+            const int l = (j0 + j) / k, c = j0 + j - l * k;
+            a = buf[row * kRow + j];
+            b = buf[(row + 1) * kRow + j];
+            at = (((size_t)rt * k + c) * P + l) * kRT + row;
+        }
+        *reinterpret_cast<f32x4*>(out + at) = f32x4{a.x, a.y, b.x, b.y};
+    }
+}
+
 // part[z][g][ma][nb] = sum over the rows b of the tiles z, z + Z, ... of  A[b][g][ma] * conj(Bv[b][g][nb])
-// A: dW (kInGather from dy) or dY1 (kInT);  Bv: U (kInT) or x (kInNat).  M = 2*MA real rows (re and im of the
+// A: dW or dY1 (kInT);  Bv: U (kInT) or x (kInNat).  M = 2*MA real rows (re and im of the
 // result), N = NB columns, K = (row, component): with B'[(b,t)][nb] = component t of Bv[b][nb],
 //   A'[2ma][(b,0)] = ar,  A'[2ma][(b,1)] = ai,  A'[2ma+1][(b,0)] = ai,  A'[2ma+1][(b,1)] = -ar.
-// Wave w owns the 16 values ma = 16w .. 16w+15 and every column.  LDS holds each operand so that the lanes of a
-// wave read consecutive addresses for one row: [row][len] for row-major sources, [idx][32 + 1] for the tiled ones.
+// Wave w owns the 16 values ma = 16w .. 16w+15 and every column.  LDS holds each operand as three bf16 planes (monarch_planes.h)
+// [idx][32 rows x 2 components + 8], the layout of an MFMA operand; the A rows 2ma+1 are made from 2ma on the way out of LDS.
 template <int LEN, int NTHR, int MODE, bool REAL = false>
 struct WgTile {
-    static constexpr int kAll = (MODE == kInGather) ? kRT * LEN : kRT * LEN / 2;
+    static constexpr int kAll = kRT * LEN / 2;
     static constexpr int kPieces = (kAll + NTHR - 1) / NTHR;
     static __device__ __forceinline__ bool has(int idx) { return kAll % NTHR == 0 || idx < kAll; }
     static_assert(!REAL || kAll % NTHR == 0, "tile does not divide over the threads");
-    static constexpr int kLen = (MODE == kInT) ? LEN * (kRT + 1) : kRT * LEN;
-    u32x4 v[MODE == kInGather ? (kPieces + 1) / 2 : kPieces];
+    static constexpr int kStride = REAL ? kRT + 8 : 2 * kRT + 8, kPlane = (REAL ? 2 : 1) * LEN * kStride, kLen = 3 * kPlane;  // bf16 values
+    u32x4 v[kPieces];
 
     __device__ __forceinline__ void fetch(const float2* __restrict__ src, int64_t rt, int g, int k, int64_t ld, int64_t B, int tid)
     {
@@ -630,26 +731,9 @@ struct WgTile {
         if constexpr (MODE == kInNat) {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
-                const int idx = tid + n * NTHR, row = idx / (LEN / 2), c2 = idx - row * (LEN / 2);
+                const int idx = tid + n * NTHR;
+                const int row = REAL ? 2 * (idx / LEN) + (idx & 1) : idx / (LEN / 2), c2 = REAL ? (idx % LEN) >> 1 : idx % (LEN / 2);
                 v[n] = (has(idx) && row0 + row < B) ? ldg128(src + (row0 + row) * ld + (size_t)g * LEN + 2 * c2) : u32x4{0, 0, 0, 0};
-            }
-        } else if constexpr (MODE == kInGather && REAL) {
-            const float* srcf = reinterpret_cast<const float*>(src);
-#pragma unroll
-            for (int n = 0; n < 2 * kPieces; ++n) {
-                const int idx = tid + n * NTHR, row = idx / (2 * LEN), i = idx - row * (2 * LEN);
-                float t = 0.f;
-                if (row0 + row < B) t = srcf[(row0 + row) * (2 * ld) + (size_t)i * k + g];
-                v[n / 4][n % 4] = __float_as_uint(t);
-            }
-        } else if constexpr (MODE == kInGather) {
-#pragma unroll
-            for (int n = 0; n < kPieces; ++n) {
-                const int idx = tid + n * NTHR, row = idx / LEN, i = idx - row * LEN;
-                float2 t = make_float2(0.f, 0.f);
-                if (has(idx) && row0 + row < B) t = src[(row0 + row) * ld + (size_t)i * k + g];
-                if (n & 1) { v[n / 2].z = __float_as_uint(t.x); v[n / 2].w = __float_as_uint(t.y); }
-                else { v[n / 2].x = __float_as_uint(t.x); v[n / 2].y = __float_as_uint(t.y); }
             }
         } else {
             const float2* tile = src + ((size_t)rt * k + g) * (LEN * kRT);
@@ -659,35 +743,69 @@ struct WgTile {
         }
     }
 
-    __device__ __forceinline__ void to_lds(float2* t, int tid) const
+    // one dword (two values next to each other in a row of LDS) to its place in each plane
+    static __device__ __forceinline__ void put(bf16_t* p, uint32_t x, uint32_t y)
     {
-        if constexpr (MODE == kInNat) {
+        uint32_t w[3];
+        split3(x, y, w);
 #pragma unroll
-            for (int n = 0; n < kPieces; ++n)
-                if (has(tid + n * NTHR)) *reinterpret_cast<u32x4*>(t + 2 * (tid + n * NTHR)) = v[n];
-        } else if constexpr (MODE == kInGather && REAL) {
-            float* tf = reinterpret_cast<float*>(t);
+        for (int u = 0; u < 3; ++u) *reinterpret_cast<uint32_t*>(p + u * kPlane) = w[u];
+    }
+    static __device__ __forceinline__ void put2(bf16_t* p, uint32_t x, uint32_t y, uint32_t z, uint32_t w)
+    {
+        uint32_t a[3], b[3];
+        split3(x, y, a);
+        split3(z, w, b);
 #pragma unroll
-            for (int n = 0; n < 2 * kPieces; ++n) tf[tid + n * NTHR] = __uint_as_float(v[n / 4][n % 4]);
-        } else if constexpr (MODE == kInGather) {
+        for (int u = 0; u < 3; ++u) *reinterpret_cast<u32x2*>(p + u * kPlane) = u32x2{a[u], b[u]};
+    }
+    __device__ __forceinline__ void to_lds(bf16_t* t, int tid) const
+    {
+        if constexpr (MODE == kInNat && REAL) {
+            // of the four values of a piece an even lane takes two, an odd lane the other two, each of both lanes' rows
+            const bool odd = tid & 1;
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
-                const u32x4 w = v[n / 2];
-                if (has(tid + n * NTHR)) t[tid + n * NTHR] = (n & 1) ? make_float2(__uint_as_float(w.z), __uint_as_float(w.w))
-                                            : make_float2(__uint_as_float(w.x), __uint_as_float(w.y));
+                const int idx = tid + n * NTHR, row = 2 * (idx / LEN), c2 = (idx % LEN) >> 1;
+                uint32_t a[2], b[2];
+#pragma unroll
+                for (int c = 0; c < 2; ++c) {
+                    const uint32_t mine = odd ? v[n][2 + c] : v[n][c], give = odd ? v[n][c] : v[n][2 + c];
+                    const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);  // lane ^ 1
+                    a[c] = odd ? got : mine;
+                    b[c] = odd ? mine : got;
+                }
+#pragma unroll
+                for (int c = 0; c < 2; ++c) put(t + (4 * c2 + 2 * odd + c) * kStride + row, a[c], b[c]);
+            }
+        } else if constexpr (MODE == kInNat) {
+#pragma unroll
+            for (int n = 0; n < kPieces; ++n) {
+                const int idx = tid + n * NTHR, row = idx / (LEN / 2), c2 = idx - row * (LEN / 2);
+                if (!has(idx)) continue;
+                put(t + 2 * c2 * kStride + 2 * row, v[n].x, v[n].y);
+                put(t + (2 * c2 + 1) * kStride + 2 * row, v[n].z, v[n].w);
             }
         } else {
 #pragma unroll
             for (int n = 0; n < kPieces; ++n) {
-                const int idx = tid + n * NTHR, i = idx / (kRT / 2), rp = idx - i * (kRT / 2);
-                if (has(idx)) lds_store_c2(t + i * (kRT + 1) + 2 * rp, v[n]);
+                const int idx = tid + n * NTHR, i = idx / (kRT / 2), row = 2 * (idx - i * (kRT / 2));
+                if (!has(idx)) continue;
+                if constexpr (REAL) {
+                    put(t + 2 * i * kStride + row, v[n].x, v[n].z);
+                    put(t + (2 * i + 1) * kStride + row, v[n].y, v[n].w);
+                } else {
+                    put2(t + i * kStride + 2 * row, v[n].x, v[n].y, v[n].z, v[n].w);
+                }
             }
         }
     }
 
-    static __device__ __forceinline__ float2 at(const float2* t, int idx, int row)
+    // the MFMA operand of step s: lane half h the values 16 s + 8 h .. of its row idx
+    static __device__ __forceinline__ void read(bf16x8 (&b)[3], const bf16_t* t, int idx, int s, int h)
     {
-        return (MODE == kInT) ? t[idx * (kRT + 1) + row] : t[row * LEN + idx];
+#pragma unroll
+        for (int u = 0; u < 3; ++u) b[u] = as_bf16x8(lds128(t + u * kPlane + idx * kStride + 16 * s + 8 * h));
     }
 };
 
@@ -702,7 +820,7 @@ cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float
     constexpr int NTN = REAL ? (2 * NB + 31) / 32 : (NB + 31) / 32;
     using TA = WgTile<MA, NTHR, AMODE, REAL>;
     using TB = WgTile<NB, NTHR, BMODE, REAL>;
-    extern __shared__ __align__(16) float2 wg_lds[];  // two buffers of each operand: 2 * (TA::kLen + TB::kLen) values
+    extern __shared__ __align__(16) bf16_t wg_lds[];  // TA::kLen + TB::kLen values: one buffer, two workgroups of a CU take turns
 
     const int g = (int)blockIdx.x / Z, z = (int)blockIdx.x - g * Z;
     const int tid = threadIdx.x, lane = tid & 63, mt = tid >> 6;
@@ -724,9 +842,11 @@ cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float
         pa.fetch(A, rt, g, k, lda, B, tid);
         pbv.fetch(Bv, rt, g, k, ldb, B, tid);
     }
-    for (int it = 0; rt < ntiles; rt += Z, ++it) {
-        float2* ta = wg_lds + (it & 1) * TA::kLen;
-        float2* tb = wg_lds + 2 * TA::kLen + (it & 1) * TB::kLen;
+    bf16_t* const ta = wg_lds;
+    bf16_t* const tb = wg_lds + TA::kLen;
+    const uint32_t turn = e ? 0x01000302u : 0x03020100u, flip = e ? 0x80000000u : 0u;  // (ar, ai) or (ai, -ar)
+    for (; rt < ntiles; rt += Z) {
+        lds_barrier();
         pa.to_lds(ta, tid);
         pbv.to_lds(tb, tid);
         lds_barrier();
@@ -735,28 +855,47 @@ cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float
             pbv.fetch(Bv, rt + Z, g, k, ldb, B, tid);
         }
 #pragma unroll
-        for (int u = 0; u < kRT / 2; ++u) {
-            const int b = 2 * u + kh;
-            const float2 av = TA::at(ta, ma, b);
-            if constexpr (REAL) {
-                const float as = e ? av.y : av.x;
+        for (int s = 0; s < (REAL ? 2 : 4); ++s) {
+            bf16x8 av[3];
+            TA::read(av, ta, REAL ? 32 * mt + col : ma, s, kh);
+            if constexpr (!REAL) {
 #pragma unroll
-                for (int nt = 0; nt < NTN; ++nt) {
-                    const int nbp = 16 * nt + (col >> 1);  // the pair holding real column 32*nt + col
-                    const float2 bv = (NB % 16 == 0 || nbp < NB) ? TB::at(tb, nbp, b) : make_float2(0.f, 0.f);
-                    acc[nt] = mfma_f32(as, e ? bv.y : bv.x, acc[nt]);
-                }
-            } else {
-                const float a0 = e ? av.y : av.x;
-                const float a1 = e ? -av.x : av.y;
+                for (int u = 0; u < 3; ++u) {
+                    u32x4 w = __builtin_bit_cast(u32x4, av[u]);
 #pragma unroll
-                for (int nt = 0; nt < NTN; ++nt) {
-                    const int nb = 32 * nt + col;
-                    const float2 bv = (NB % 32 == 0 || nb < NB) ? TB::at(tb, nb, b) : make_float2(0.f, 0.f);
-                    acc[nt] = mfma_f32(a0, bv.x, acc[nt]);
-                    acc[nt] = mfma_f32(a1, bv.y, acc[nt]);
+                    for (int c = 0; c < 4; ++c) w[c] = __builtin_amdgcn_perm(w[c], w[c], turn) ^ flip;
+                    av[u] = as_bf16x8(w);
                 }
             }
+#pragma unroll
+            for (int nt = 0; nt < NTN; ++nt) {
+                int nb = 32 * nt + col;
+                if (!REAL && NB % 32 != 0 && nb >= NB) nb = NB - 1;  // a column that does not exist
+                bf16x8 bv[3];
+                TB::read(bv, tb, nb, s, kh);
+                plane_products<3, 3>(av, bv, acc[nt], acc[nt]);
+            }
+        }
+    }
+    if (planes_doubtful(acc)) {
+#pragma unroll
+        for (int nt = 0; nt < NTN; ++nt) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[nt][r] = 0.f;
+            int nb = REAL ? 16 * nt + (col >> 1) : 32 * nt + col;
+            if (nb >= NB) nb = NB - 1;
+            for (int64_t t = z; t < ntiles; t += Z)
+#pragma clang loop unroll(disable)
+                for (int u = 0; u < kRT / 2; ++u) {
+                    const float2 av = act_value<MA, AMODE, REAL>(A, t, 2 * u + kh, g, ma, k, lda, B);
+                    const float2 bv = act_value<NB, BMODE, REAL>(Bv, t, 2 * u + kh, g, nb, k, ldb, B);
+                    if constexpr (REAL) {
+                        acc[nt] = mfma_f32(e ? av.y : av.x, e ? bv.y : bv.x, acc[nt]);
+                    } else {
+                        acc[nt] = mfma_f32(e ? av.y : av.x, bv.x, acc[nt]);
+                        acc[nt] = mfma_f32(e ? -av.x : av.y, bv.y, acc[nt]);
+                    }
+                }
         }
     }
     if constexpr (REAL) {
@@ -806,7 +945,10 @@ __global__ void __launch_bounds__(256) csum_kernel(const f32x4* __restrict__ par
 int64_t tiles_of(const Problem& pb) { return (pb.B + kRT - 1) / kRT; }
 size_t t_bytes(const Problem& pb) { return align_up((size_t)tiles_of(pb) * kRT * pb.kq() * sizeof(float2), 256); }
 
-// workgroups of one block: enough for about sixteen waves per CU in all, a multiple of 8, at most one per tile
+// workgroups of one block: about `target_waves` in all, a multiple of 8, at most one per tile.  A workgroup loads and splits a block's
+// weights before its first tile, so there are no more of them than stay resident: eight waves a CU (64 complex blocks of 64, 2048
+// rows, forward and backward: 317 us with sixteen, 302 with eight), four for real layers, whose batches are the long ones (64
+// real blocks of 64, 12000 rows: 834 with sixteen, 807 with eight, 745 with four)
 int splits_for(const Problem& pb, int waves_per_wg, int target_waves)
 {
     int64_t n = (target_waves / waves_per_wg + pb.k - 1) / pb.k;
@@ -828,7 +970,7 @@ int wgrad_chunks(const Problem& pb)
 template <int M, int IN, int OUT, bool CONJT, bool REAL = false>
 int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hipStream_t st)
 {
-    const int nsplit = splits_for(pb, kTileWaves<M>, 4096);
+    const int nsplit = splits_for(pb, kTileWaves<M>, REAL ? 1024 : 2048);
     const int64_t grid = (int64_t)pb.k * nsplit;
     if (grid > 0x7fffffffLL) return -2;
     hipLaunchKernelGGL((cstage_kernel<M, M, IN, OUT, CONJT, REAL>), dim3((unsigned)grid), dim3(64 * kTileWaves<M>), 0, st, (const float2*)in,
@@ -836,10 +978,11 @@ int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hi
     return hip_status(hipGetLastError());
 }
 
-// the eight-blocks-per-workgroup stages: about two workgroups per CU, a multiple of 8 per (block octet, M tile)
+// the eight-blocks-per-workgroup stages: about one workgroup per CU, a multiple of 8 per (block octet, M tile); their weights
+// take 12 registers a step of 8 inputs (32 real blocks of 32, 8000 rows, forward and backward: 144 us with two, 133 with one)
 int splits8_for(const Problem& pb, int mtiles)
 {
-    int64_t n = (512 + (pb.k / 8) * mtiles - 1) / ((pb.k / 8) * mtiles);
+    int64_t n = (256 + (pb.k / 8) * mtiles - 1) / ((pb.k / 8) * mtiles);
     n = (n + 7) / 8 * 8;
     const int64_t t = tiles_of(pb);
     if (n > t) n = t;
@@ -849,7 +992,7 @@ int splits8_for(const Problem& pb, int mtiles)
 template <int M, bool REAL = false>
 int launch_scatter8(const Problem& pb, const void* T, const void* W, void* out, hipStream_t st)
 {
-    constexpr int MTG = kTileWaves<M> / Scatter8<M, M>::MTW;
+    constexpr int MTG = kTileWaves<M>;
     const int nsplit = splits8_for(pb, MTG);
     const int64_t grid = (int64_t)(pb.k / 8) * MTG * nsplit;
     if (grid > 0x7fffffffLL) return -2;
@@ -864,7 +1007,7 @@ int launch_scatter8(const Problem& pb, const void* T, const void* W, void* out, 
 template <int M, bool EMIT, bool REAL = false>
 int launch_gather8(const Problem& pb, const void* in, const void* W, void* out, void* dwt, hipStream_t st)
 {
-    constexpr int MTG = kTileWaves<M> / kMTilesPerWaveGather<M, REAL>;
+    constexpr int MTG = kTileWaves<M>;
     const int nsplit = splits8_for(pb, MTG);
     const int64_t grid = (int64_t)(pb.k / 8) * MTG * nsplit;
     if (grid > 0x7fffffffLL) return -2;
@@ -886,7 +1029,7 @@ int launch_wgrad(const Problem& pb, const void* A, const void* Bv, void* out, vo
     if (grid > 0x7fffffffLL) return -2;
     float2* dst = Z == 1 ? (float2*)out : (float2*)part;
     auto kern = cwgrad_kernel<M, M, AMODE, BMODE, REAL>;
-    const size_t lds = 2 * (size_t)(WgTile<M, 64 * kTileWaves<M>, AMODE, REAL>::kLen + WgTile<M, 64 * kTileWaves<M>, BMODE, REAL>::kLen) * sizeof(float2);
+    const size_t lds = (size_t)(WgTile<M, 64 * kTileWaves<M>, AMODE, REAL>::kLen + WgTile<M, 64 * kTileWaves<M>, BMODE, REAL>::kLen) * sizeof(bf16_t);
     if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess) return -4;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kTileWaves<M>), lds, st, (const float2*)A, (const float2*)Bv, dst, pb.B,
                        pb.k, Z, lda, ldb);
@@ -894,6 +1037,22 @@ int launch_wgrad(const Problem& pb, const void* A, const void* Bv, void* out, vo
     if (rc || Z == 1) return rc;
     const size_t n4 = (size_t)pb.k * M * M / (REAL ? 1 : 2);  // float4s of one gradient: (2M)^2 floats, or M^2 complex values, per block
     hipLaunchKernelGGL(csum_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, (const f32x4*)part, (f32x4*)out, n4, Z);
+    return hip_status(hipGetLastError());
+}
+
+// Whether dy is re-laid by a launch of its own or by the stage that gathers it, which reads it and lays it out once per M tile (four
+// M tiles, 2048 rows: 28 + 40 us against 87; two: 8 + 13 against 14; two of a real layer, 12000 rows, whose dy is larger than the caches: 69 + 107
+// against 232).  Other block counts than multiples of eight have no gathering stage.
+template <int M, bool REAL = false>
+constexpr bool kRelay = REAL ? M == 32 : M >= 56;
+
+template <int M, bool REAL = false>
+int launch_tile(const Problem& pb, const void* in, void* out, hipStream_t st)
+{
+    const int chunks = REAL ? M * ((pb.k + 63) / 64) : (pb.k * M + 63) / 64;
+    const int64_t grid = tiles_of(pb) * chunks;
+    if (grid > 0x7fffffffLL) return -2;
+    hipLaunchKernelGGL(ctile_kernel<REAL>, dim3((unsigned)grid), dim3(256), 0, st, (const float2*)in, (float2*)out, pb.B, pb.k, M, chunks);
     return hip_status(hipGetLastError());
 }
 
@@ -924,15 +1083,18 @@ int run_bwd(const Problem& pb, const void* dy, const void* x, const void* R, con
     void* dY1t = w + t_bytes(pb);
     void* dWt = w + 2 * t_bytes(pb);
     void* part = w + 3 * t_bytes(pb);
-    const bool eight = pb.k % 8 == 0;
     int rc = launch_stage<M, kInNat, kOutTFwd, false>(pb, x, R, Ut, st);
     if (rc) return rc;
-    rc = eight ? launch_gather8<M, true>(pb, dy, L, dY1t, dWt, st) : launch_stage<M, kInGather, kOutTBwd, true>(pb, dy, L, dY1t, st);
+    if (!kRelay<M> && pb.k % 8 == 0) {
+        rc = launch_gather8<M, true>(pb, dy, L, dY1t, dWt, st);
+    } else {
+        rc = launch_tile<M>(pb, dy, dWt, st);
+        if (!rc) rc = launch_stage<M, kInT, kOutTBwd, true>(pb, dWt, L, dY1t, st);
+    }
     if (rc) return rc;
     rc = launch_stage<M, kInT, kOutNat, true>(pb, dY1t, R, dx, st);
     if (rc) return rc;
-    rc = eight ? launch_wgrad<M, kInT, kInT>(pb, dWt, Ut, dL, part, 0, 0, st)
-               : launch_wgrad<M, kInGather, kInT>(pb, dy, Ut, dL, part, pb.n_out(), 0, st);
+    rc = launch_wgrad<M, kInT, kInT>(pb, dWt, Ut, dL, part, 0, 0, st);
     if (rc) return rc;
     return launch_wgrad<M, kInT, kInNat>(pb, dY1t, x, dR, part, 0, pb.n_in, st);
 }
@@ -967,16 +1129,18 @@ int run_real_bwd(const Problem& pb, const void* dy, const void* x, const void* R
     void* dY1t = w + rt_bytes(pb);
     void* dWt = w + 2 * rt_bytes(pb);
     void* part = w + 3 * rt_bytes(pb);
-    const bool eight = pb.k % 8 == 0;
     int rc = launch_stage<M, kInNat, kOutTFwd, false, true>(pb, x, R, Ut, st);
     if (rc) return rc;
-    rc = eight ? launch_gather8<M, true, true>(pb, dy, L, dY1t, dWt, st)
-               : launch_stage<M, kInGather, kOutTBwd, true, true>(pb, dy, L, dY1t, st);
+    if (!kRelay<M, true> && pb.k % 8 == 0) {
+        rc = launch_gather8<M, true, true>(pb, dy, L, dY1t, dWt, st);
+    } else {
+        rc = launch_tile<M, true>(pb, dy, dWt, st);
+        if (!rc) rc = launch_stage<M, kInT, kOutTBwd, true, true>(pb, dWt, L, dY1t, st);
+    }
     if (rc) return rc;
     rc = launch_stage<M, kInT, kOutNat, true, true>(pb, dY1t, R, dx, st);
     if (rc) return rc;
-    rc = eight ? launch_wgrad<M, kInT, kInT, true>(pb, dWt, Ut, dL, part, 0, 0, st)
-               : launch_wgrad<M, kInGather, kInT, true>(pb, dy, Ut, dL, part, pb.n_out() / 2, 0, st);
+    rc = launch_wgrad<M, kInT, kInT, true>(pb, dWt, Ut, dL, part, 0, 0, st);
     if (rc) return rc;
     return launch_wgrad<M, kInT, kInNat, true>(pb, dY1t, x, dR, part, 0, pb.n_in / 2, st);
 }

@@ -33,3 +33,54 @@ def test_blocks_between_the_tiles(case, reading):
         rel = np.linalg.norm((g - w).reshape(g.shape[0], -1), axis=1) / np.linalg.norm(w.reshape(g.shape[0], -1), axis=1)
         assert float(rel.max()) <= 4e-5, (name, int(rel.argmax()), float(rel.max()))   # no row, no block of a gradient
         assert np.linalg.norm(g - w) / np.linalg.norm(w) <= 1e-5, name
+
+
+# Infinities, NaN, numbers that round to a bf16 infinity and tiny ones do not fit the bf16 planes: what comes of them is what
+# the SIMT kernels give, element by element, and the rest of the batch is not touched.
+@pytest.mark.parametrize("case", [(70, 16, 16), (40, 24, 8), (65, 64, 8), (33, 40, 5), (100, 64, 64)], ids=str)
+def test_values_that_three_bf16_planes_cannot_hold(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, m, k = case
+    x, R, L, dy = (_normal(8900 + 10 * i, shp, std) for i, (shp, std) in enumerate(
+        (((rows, k * m), 1.0), ((k, m, m), m ** -0.5), ((k, m, m), m ** -0.5), ((rows, k * m), 1.0))))
+    for a in (x, dy):
+        a[0, 3], a[1, 5], a[2, 7] = np.inf, complex(0, -np.inf), np.nan
+        a[3, 9] = 3.4e38 / 64 * 1j
+        a[4] *= np.float32(2.0 ** -110)
+        a[6] = 0
+    xd, Rd, Ld, dyd = (torch.from_numpy(a).cuda() for a in (x, R, L, dy))
+    got = [B.monarch_fwd_c64_ws(xd, Rd, Ld), B.monarch_fwd_h_c64_ws(dyd, Rd, Ld), *B.monarch_bwd_c64_ws(dyd, xd, Rd, Ld)]
+    want = [B.monarch_fwd_c64(xd, Rd, Ld), B.monarch_fwd_h_c64(dyd, Rd, Ld), *B.monarch_bwd_c64(dyd, xd, Rd, Ld)]
+    for name, g, w in zip(("y", "xMh", "dx", "dR", "dL"), got, want):
+        g, w = (torch.view_as_real(t).cpu().double().numpy() for t in (g, w))
+        fine = np.isfinite(w)
+        assert np.array_equal(fine, np.isfinite(g)), name
+        for row in range(len(w)):
+            a, b = g[row][fine[row]], w[row][fine[row]]
+            assert np.linalg.norm(a - b) <= 4e-5 * np.linalg.norm(b), (name, row)
+
+
+@pytest.mark.parametrize("case", [(70, 32, 32), (100, 64, 64), (40, 64, 5)], ids=str)
+def test_real_layers_with_values_that_three_bf16_planes_cannot_hold(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, m, k = case
+    x, R, L, dy = (synth.normal(8950 + i, shp, std).astype(np.float32) for i, (shp, std) in enumerate(
+        (((rows, k * m), 1.0), ((k, m, m), m ** -0.5), ((k, m, m), m ** -0.5), ((rows, k * m), 1.0))))
+    for a in (x, dy):
+        a[0, 3], a[1, 5], a[2, 7], a[3, 9], a[6] = np.inf, -np.inf, np.nan, 3.4e38 / 64, 0
+        a[4] *= np.float32(2.0 ** -110)
+    xd, Rd, Ld, dyd = (torch.from_numpy(a).cuda() for a in (x, R, L, dy))
+    generic = B.MONARCH_FLAG_GENERIC
+    got = [B.monarch_fwd_ws(xd, Rd, Ld), B.monarch_fwd_t(dyd, Rd, Ld), *B.monarch_bwd(dyd, xd, Rd, Ld)]
+    want = [B.monarch_fwd(xd, Rd, Ld, flags=generic), B.monarch_fwd_t(dyd, Rd, Ld, flags=generic), *B.monarch_bwd(dyd, xd, Rd, Ld, flags=generic)]
+    for name, g, w in zip(("y", "xM", "dx", "dR", "dL"), got, want):
+        g, w = (t.cpu().double().numpy() for t in (g, w))
+        fine = np.isfinite(w)
+        assert np.array_equal(fine, np.isfinite(g)), name
+        for row in range(len(w)):
+            a, b = g[row][fine[row]], w[row][fine[row]]
+            assert np.linalg.norm(a - b) <= 4e-5 * np.linalg.norm(b), (name, row)
