@@ -17,8 +17,9 @@
 // Fragments:  WT[g][nt][t][lane][e] = W[g][16t + 4*(e/2) + 2*(lane/32) + e%2][32*nt + lane%32]: lane half h holds, of the 16 m of
 // a step, the pairs that its 16-byte pieces 2i + h of the line bring.
 //
-// What bounds it: latency for a few row tiles (three launches of about 6 us), the address path of the L1 above (see
-// monarch_mfma_fwd_split.hip).  Measured, GPU time of a training step: 256 -> 256 -> 1024 blocks, 200 rows 86 -> 57 us; the feed-forward
+// What bounds it: latency for a few row tiles (three launches of about 6 us), the address path of the L1 above; the rows come in whole
+// lines that change places through LDS (RowPieces; training step of the feed-forward block of width 1024, 2000 rows: 224 -> 196 us, of width 768
+// 169 -> 150, 200 rows 106 -> 99).  Measured, GPU time of a training step: 256 -> 256 -> 1024 blocks, 200 rows 86 -> 57 us; the feed-forward
 // block of width 1024 240 -> 101 us at 200 rows, 262 -> 153 at 1000; of width 384 119 -> 69 and 134 -> 88.
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
@@ -58,7 +59,7 @@ bwd_split_prep_kernel(const BwdPrep w, int64_t B, SplitGrid gr, ColsumJob cj)
     extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
     int bid = (int)blockIdx.x;
     if (bid < w.y1_blocks) {
-        split_stage1<1, NT, NG, 4 / NT, true, true>(w.x, w.R, w.Y1, B, w.P, w.Q, gr, bid, reinterpret_cast<f32x4*>(split_lds));
+        split_stage1<1, NT, NG, 4 / NT, true, true, (NT > 1)>(w.x, w.R, w.Y1, B, w.P, w.Q, gr, bid, reinterpret_cast<f32x4*>(split_lds));
         return;
     }
     bid -= w.y1_blocks;
@@ -89,7 +90,7 @@ adjoint_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ WT,
     const int rows = B - b0 < 32 ? (int)(B - b0) : 32;
 
     const auto ra = buffer_at(in + b0 * 4 * M), rw = buffer_at(WT);
-    const uint32_t a_at = ln < rows ? (uint32_t)(ln * 8 * M + lo * 128 + h * 16) : kNowhere;
+    uint16_t* const turn = reinterpret_cast<uint16_t*>(split_lds) + wave * (int)(kTurnBytes / 2);
     uint32_t w_at[NT];
 #pragma unroll
     for (int j = 0; j < NT; ++j) w_at[j] = nt0 + j < NTT ? (uint32_t)(((nt0 + j) * T + lo) * 1024 + lane * 16) : kNowhere;
@@ -103,11 +104,10 @@ adjoint_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ WT,
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[g][j][r] = 0.f;
 
-    u32x4 af[BUF][4], wf[BUF][4][NT];
+    RowPieces af[BUF];
+    u32x4 wf[BUF][4][NT];
     auto load = [&](int t, int buf) {
-        const uint32_t a = t < steps ? a_at : kNowhere;
-#pragma unroll
-        for (int i = 0; i < 4; ++i) af[buf][i] = __builtin_amdgcn_raw_buffer_load_b128(ra, a, t * 128 + i * 32, 0);
+        af[buf].fetch(ra, (uint32_t)((lo + t) * 128), (uint32_t)(8 * M), rows, t < steps ? 8 : 0, lane);
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
             const uint32_t w = t < steps ? w_at[j] : kNowhere;
@@ -120,7 +120,8 @@ adjoint_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ WT,
     for (int t = 0; t < BUF; ++t) load(t, t);
 #pragma unroll
     for (int t = 0; t < NS; ++t) {
-        const u32x4(&a)[4] = af[t % BUF];
+        af[t % BUF].turn(turn, lane);
+        const u32x4(&a)[4] = af[t % BUF].v;
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
             // a piece holds m0: c0 c1 | c2 c3, m1: c0 c1 | c2 c3
@@ -134,6 +135,7 @@ adjoint_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ WT,
         if (t + BUF < NS) load(t + BUF, t % BUF);
     }
 
+    lds_barrier();  // the sums take the place of the rows
     // the waves' sums: wave w hands two blocks to wave w ^ 2, then one to wave w ^ 1, and keeps block w
     auto slot = [&](int owner, int g, int j, int q4) { return (((owner * 2 + g) * NT + j) * 4 + q4) * 64 + lane; };
 #pragma unroll
@@ -225,7 +227,7 @@ int adjoint(const uint16_t* in, const uint16_t* WT, uint16_t* out, const void* x
 template <int NT>
 int launch_prep(const BwdPrep& w, int64_t B, const SplitGrid& gr, const ColsumJob& cj, unsigned blocks, hipStream_t st)
 {
-    constexpr size_t lds = (size_t)4 * NT * 4096;
+    constexpr size_t lds = split_stage1_lds<1, NT, (NT > 1)>();
     const int ng = ((w.P / 16 + 3) / 4 + 3) / 4;
     auto kern = ng == 1 ? bwd_split_prep_kernel<NT, 1> : ng == 2 ? bwd_split_prep_kernel<NT, 2>
               : ng == 3 ? bwd_split_prep_kernel<NT, 3> : bwd_split_prep_kernel<NT, 4>;

@@ -1,19 +1,20 @@
 // bf16 forward of the four-block layers on packed weights, for batches too short to fill the chip with 64-row tiles of the
 // fused kernel (monarch_mfma_fwd_frag.hip): one launch per block-diagonal factor, so that the weights are spread over all CUs
-// instead of passing through the few that have a row tile.  The vector between the factors goes through the workspace, in
-// the order the packed L contracts it: U[b][j/4][kk][j%4] (16 elements = one K-step of block c = (j/4) / (Q/16)).
+// instead of passing through the few that have a row tile.  The vector between the factors goes through the workspace in the MFMA
+// fragments of the second stage: K-step j/4 contracts the 16 elements (kk, j%4), and block c = (j/4) / (Q/16) is a run of them.
 //
 //   stage 1   workgroup = (row tile, block kk, NT column tiles of 32): the four waves share out the contraction, so that every
 //             byte of x and R the workgroup needs is loaded once, and add up their tiles through LDS
 //   stage 2   workgroup = (row tile, NT column tiles of 32): wave c computes block c (again nothing is loaded twice);
 //             the four blocks of an output row are interleaved through LDS and leave in whole rows
 //
-// Operands come straight from memory to registers: x and U in 16-byte pieces (a K-step is 32 contiguous bytes of a row),
-// weights in 1 KiB fragments.
-// What bounds it: latency for one row tile (two launches of about 3.5 us), above that the address path of the L1 (an x or U
-// load touches 32 lines, 27 clocks, for MFMAs of 32 clocks on four SIMDs).  Staging x and U in LDS instead (whole lines per
-// load) measured no better: the 64 KiB it takes per workgroup cost more overlap than the shorter loads gain.
-// Measured, 1024 -> 4096 -> 1024 with bias and GELU: 8 rows 54 -> 14.5 us, 256 rows 66 -> 20 us, 1531 rows 69 -> 39 us.
+// U and the weights come in 1 KiB fragments straight from memory to registers; the rows of x do too where there are few tiles, and
+// else in whole lines that change places through LDS (RowPieces).
+// What bounds it: latency for one row tile (two launches of about 3.5 us), above that the address path of the L1: 20 cycles a fragment
+// for MFMAs of 32 cycles on four SIMDs.  With U in rows, a fragment of it took 62 cycles, and so did one of x (1531 rows: the stages of
+// 1024 -> 4096 5.8 + 16.4 -> 5.2 + 15.5 us, the second one now bound by the nonlinearity, of 4096 -> 1024 12.8 + 7.6 -> 10.4 + 5.2).
+// Measured, 1024 -> 4096 -> 1024 with bias and GELU, against the fused kernel alone and against U in rows: 8 rows 54, 14.4 and 14.5 us, 256 rows
+// 66, 19.9 and 18.6, 1531 rows 69, 40.1 and 32.7; 768 -> 3072 -> 768, 1531 rows: 33.0 and 25.6.
 #include "../../include/monarch.h"
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
@@ -32,7 +33,7 @@ struct SplitPack {
 
 // PACK: R is read as it is, and further workgroups of the launch build the packed copies of R and L, for the second stage and for
 // later calls.
-template <int NB, int NT, int NG, int AHEAD, bool PACK>
+template <int NB, int NT, int NG, int AHEAD, bool PACK, bool TURN>
 __global__ void __launch_bounds__(256)
 split_stage1_kernel(const uint16_t* __restrict__ x, const SplitPack w, uint16_t* __restrict__ U, int64_t B, int P, int Q, SplitGrid gr)
 {
@@ -43,7 +44,7 @@ split_stage1_kernel(const uint16_t* __restrict__ x, const SplitPack w, uint16_t*
             return;
         }
     }
-    split_stage1<NB, NT, NG, AHEAD, PACK, false>(x, PACK ? w.R : w.RF1, U, B, P, Q, gr, (int)blockIdx.x, reinterpret_cast<f32x4*>(split_lds));
+    split_stage1<NB, NT, NG, AHEAD, PACK, false, TURN>(x, PACK ? w.R : w.RF1, U, B, P, Q, gr, (int)blockIdx.x, reinterpret_cast<f32x4*>(split_lds));
 }
 
 template <int NB, int NT, int NG, int AHEAD, bool ACT>
@@ -71,10 +72,11 @@ split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) a_at[i] = i * 32 + ln < rows ? (uint32_t)(((i * 32 + ln) * 4 * Q + 8 * g) * 2) : kNowhere;
+    for (int i = 0; i < NB; ++i) a_at[i] = i * 32 < rows ? (uint32_t)(i * (Q / 4) * 1024 + lane * 16) : kNowhere;
 #pragma unroll
     for (int j = 0; j < NT; ++j) w_at[j] = lt0 + j < LT ? (uint32_t)((lt0 + j) * KS * 1024 + lane * 16) : kNowhere;
-    tile_product<NB, NT, NG, AHEAD, false>(U + b0 * 4 * Q + c * Q, a_at, LF2 + (size_t)c * LT * KS * 512, w_at, 1024u, KS, acc);
+    tile_product<NB, NT, NG, AHEAD, false, false>(U + (b0 / 32 * (Q / 4) + c * KS) * 512, a_at, 1024u, LF2 + (size_t)c * LT * KS * 512, w_at,
+                                                  1024u, KS, acc, 0u, 0, nullptr);
 
 #pragma unroll
     for (int j = 0; j < NT; ++j) {
@@ -119,8 +121,9 @@ int launch_stage(const Problem& pb, int stage, const SplitArgs& a, hipStream_t s
     unsigned blocks;
     if (stage == 1) {
         const SplitGrid gr = split_grid(pb.B, 32 * NB, 4 * ((pb.q / 32 + NT - 1) / NT), &blocks);
-        constexpr size_t lds = (size_t)4 * NB * NT * 4096;
-        auto kern = pb.ws_packed() ? split_stage1_kernel<NB, NT, NG, AHEAD, false> : split_stage1_kernel<NB, NT, NG, AHEAD, true>;
+        constexpr bool kTurn = NT > 1;  // many tiles: launch_factor
+        constexpr size_t lds = split_stage1_lds<NB, NT, kTurn>();
+        auto kern = pb.ws_packed() ? split_stage1_kernel<NB, NT, NG, AHEAD, false, kTurn> : split_stage1_kernel<NB, NT, NG, AHEAD, true, kTurn>;
         SplitPack w = a.w;
         w.blocks = (int)blocks;
         if (!pb.ws_packed()) blocks += (unsigned)((w.pieces + 255) / 256);
@@ -167,8 +170,8 @@ bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
 }
 
 // Where there is a fused kernel, up to 3072 rows (48 of its row tiles; it takes the same time for any number of them): 1024 -> 4096
-// -> 1024, both layers, 2048 rows 69 and 47 us, 3000 rows 71 and 62, 4096 rows 73 and 81; 512 -> 2048 -> 512 3000 rows 36 and 28,
-// 4096 rows 34 and 34.  Where the other choice is the shape-generic kernel (width 384: 47 us for 300 rows, 60 for 8000), up to
+// -> 1024, both layers with the nonlinearity, 2600 rows 70 and 46 us; 768 -> 3072 alone 3500 rows 17.4 and 21.3, 3072 -> 768 28.0 and 27.0; 512 -> 2048
+// alone 13.2 and 15.3, 2048 -> 512 17.1 and 15.2.  Where the other choice is the shape-generic kernel (width 384: 47 us for 300 rows, 60 for 8000), up to
 // 8192.  And only where it all fits the static workspace, so that monarch_fwd_static runs the same kernels as monarch_fwd_ws.
 bool fwd_split_preferred(const Problem& pb)
 {
@@ -176,7 +179,7 @@ bool fwd_split_preferred(const Problem& pb)
            fwd_frag_packed(pb) + fwd_split_mid_bytes(pb) <= MONARCH_STATIC_WORKSPACE_BYTES;
 }
 
-size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)pb.B * pb.kq() * 2, 256); }
+size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B + 31) / 32 * 32 * pb.kq() * 2, 256); }
 
 int fwd_split(const Problem& pb, const void* x, const void* R, const void* L, uint16_t* RF1, uint16_t* LF2, void* y, void* U,
               hipStream_t st)

@@ -176,3 +176,20 @@ def test_calls_on_two_streams_share_packed_weights():
     torch.cuda.synchronize()
     for i, y in enumerate(got):
         assert torch.equal(y, want[i % 3]), i
+
+
+# the vector between the factors is kept in whole tiles of 32 rows: the workspace and the scratch that the queries name hold them
+@pytest.mark.parametrize("case", [(1, 64, 64, 64), (33, 128, 64, 64), (545, 256, 256, 768), (2817, 128, 128, 128)], ids=str)
+def test_whole_tiles_stay_inside_the_workspace(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, p, q, s = case
+    sh = synth.Shape("guard_%s" % (case,), "bf16", rows, 4, p, q, s, config=560 + parity_util.stable_seed(str(case)))
+    x, R, L, _ = synth.make_inputs(sh)
+    xd, Rd, Ld = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L))
+    need = B.monarch_fwd_workspace_bytes(rows, sh.n_in, 4, q, s, 1)
+    ws = torch.full((need + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+    y = B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws[:need])
+    parity_util.check(sh.name, y.float().cpu().numpy(), oracle.fwd(x, R, L), 2e-2)
+    assert bool((ws[need:] == 0xA5).all())
