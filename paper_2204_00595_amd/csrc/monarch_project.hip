@@ -13,9 +13,11 @@
 // contraction step r.  Tiles below the diagonal are transposes of those above, by way of LDS.
 //
 // What bounds it: the matrix cores, 32 clocks for each of the NT^2 (NT + 1) / 2 * 4 steps of a squaring (m = 32: 768 clocks, one
-// wave per SIMD; m = 64: 5120, four).  The one-sided Jacobi SVD that was here before (all m triples, three cross-lane
+// wave per SIMD; m = 64: 5120, four), then the transposition through LDS.  Sums over the lanes stay in the vector registers and run
+// beside the products (m = 32, 1024 slices: 15.8 us with shuffles between them, 13.3 now; the four lanes of a column meet by row swaps).  The one-sided Jacobi SVD that was here before (all m triples, three cross-lane
 // shuffles per element and rotation) took 784 us for m = 32 and 5.8 ms for m = 64, and was less accurate (products
 // 2e-5 off at m = 64, here 5e-7).
+#include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
 #include "monarch_mfma_common.h"
@@ -27,12 +29,35 @@ constexpr int kMaxSquarings = 32;     // relative gaps down to 1e-8, below fp32
 constexpr float kRankOne = 1e-4f;     // 1 - |S|_F^2 at trace 1, about twice the second eigenvalue; one squaring more follows
 constexpr int kWavesPerBlock = 4;     // slices of neighbouring k: their rows of A lie next to each other
 
-__device__ __forceinline__ float wave_sum(float v)
+// Reductions over the wave inside the vector registers: a shuffle goes through LDS, and six of them in a row took as long as the
+// squaring beside them.
+template <int CTRL>
+__device__ __forceinline__ float lane_move(float v)
 {
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) v += __shfl_xor(v, d);
-    return v;
+    return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true));
 }
+// over the four lanes of a column of a tile: 16 and 32 apart
+template <typename Op>
+__device__ __forceinline__ float column_reduce(float v, Op op)
+{
+    const uint32_t a = __float_as_uint(v);
+    const auto p = __builtin_amdgcn_permlane16_swap(a, a, false, false);
+    const uint32_t b = __float_as_uint(op(__uint_as_float(p[0]), __uint_as_float(p[1])));
+    const auto q = __builtin_amdgcn_permlane32_swap(b, b, false, false);
+    return op(__uint_as_float(q[0]), __uint_as_float(q[1]));
+}
+template <typename Op>
+__device__ __forceinline__ float wave_reduce(float v, Op op)
+{
+    v = op(v, lane_move<0xB1>(v));   // the neighbour, the pair next to it, the other four, the other eight of a row of 16
+    v = op(v, lane_move<0x4E>(v));
+    v = op(v, lane_move<0x141>(v));
+    v = op(v, lane_move<0x140>(v));
+    return column_reduce(v, op);
+}
+__device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float column_sum(float v) { return column_reduce(v, [](float a, float b) { return a + b; }); }
+__device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); }); }
 
 // NT x NT tiles of 16 x 16
 template <typename T, int NT>
@@ -64,8 +89,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
     for (int t = 0; t < GT; ++t)
 #pragma unroll
         for (int a = 0; a < NT; ++a) big = fmaxf(big, fabsf(g[a][t]));
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) big = fmaxf(big, __shfl_xor(big, d));
+    big = wave_max(big);
     // a power of two brings the largest entry near one: the squares neither overflow nor vanish
     int ex = 0;
     if (big > 0.f) (void)frexpf(big, &ex);
@@ -93,9 +117,11 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
 #pragma unroll
             for (int b = 0; b < NT; ++b) S[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[a][t], g[b][t], S[a][b], 0, 0, 0);
 
-    // S = S^2
+    // S = S^2 at trace 1; returns the trace before, |S|_F^2, which is 1 exactly when S, at trace 1 itself, is of rank one.  The sum over
+    // the lanes runs beside the products.
     auto square = [&]() {
         f32x4 Q[NT][NT];
+        float norm2 = 0.f;
 #pragma unroll
         for (int a = 0; a < NT; ++a)
 #pragma unroll
@@ -110,6 +136,20 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
                 for (int a = 0; a < NT; ++a)
 #pragma unroll
                     for (int b = a; b < NT; ++b) Q[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(S[e][a][r], S[e][b][r], Q[a][b], 0, 0, 0);
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = 0; b < NT; ++b)
+#pragma unroll
+                for (int r = 0; r < NA; ++r) norm2 = fmaf(S[a][b][r], S[a][b][r], norm2);
+        norm2 = wave_sum(norm2);
+        const float inv = norm2 > 0.f ? 1.f / norm2 : 0.f;
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = a; b < NT; ++b)
+#pragma unroll
+                for (int r = 0; r < NA; ++r) Q[a][b][r] *= inv;
         int at = 0;
 #pragma unroll
         for (int a = 0; a < NT; ++a)
@@ -129,23 +169,19 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
         for (int a = 0; a < NT; ++a)
 #pragma unroll
             for (int b = 0; b < NT; ++b) S[a][b] = Q[a][b];
+        return norm2;
     };
-    for (int it = 0; it < kMaxSquarings; ++it) {
+    {
         const float inv = trace > 0.f ? 1.f / trace : 0.f;
-        float norm2 = 0.f;  // |S|_F^2 at trace 1: the trace of the square, and 1 exactly when S is of rank one
 #pragma unroll
         for (int a = 0; a < NT; ++a)
 #pragma unroll
             for (int b = 0; b < NT; ++b)
 #pragma unroll
-                for (int r = 0; r < NA; ++r) {
-                    S[a][b][r] *= inv;
-                    norm2 = fmaf(S[a][b][r], S[a][b][r], norm2);
-                }
-        trace = wave_sum(norm2);
-        square();
-        if (!(1.f - trace > kRankOne)) break;  // NaN ends it too
+                for (int r = 0; r < NA; ++r) S[a][b][r] *= inv;
     }
+    for (int it = 0; it < kMaxSquarings; ++it)
+        if (!(1.f - square() > kRankOne)) break;  // NaN ends it too
 
     // v_1 is every column of S up to scale: the row with the largest diagonal entry
     float best = -1.f;
@@ -160,14 +196,9 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
                 who = TS * a + c;
             }
         }
-#pragma unroll
-    for (int d = 32; d >= 1; d >>= 1) {
-        const float ob = __shfl_xor(best, d);
-        const int ow = __shfl_xor(who, d);
-        if (ob > best || (ob == best && ow < who)) {
-            best = ob;
-            who = ow;
-        }
+    {
+        const float top = wave_max(best);
+        who = -(int)wave_max(best == top ? -(float)who : -1e9f);  // the first of equal ones
     }
     float v[NT];
 #pragma unroll
@@ -178,9 +209,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
 #pragma unroll
             for (int r = 0; r < NA; ++r)
                 if (TS * e + 4 * h + r == who) v[a] = S[e][a][r];
-        // one of the H lanes of a column has it, the others zero
-#pragma unroll
-        for (int d = TS; d < 64; d <<= 1) v[a] += __shfl_xor(v[a], d);
+        v[a] = column_sum(v[a]);  // one of the H lanes of a column has it, the others zero
     }
 
     // Twice u = G v, with one step v = G^T u in between: what rounding left of the other vectors shrinks with their singular
@@ -204,25 +233,28 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
 #pragma unroll
                 for (int a = 0; a < NT; ++a) w[t] = fmaf(g[a][t], v[a], w[t]);
         }
-        // sum over the TS lanes of a row, each lane keeping half of its values at every step while it has more than one
-        int left = GP, t0 = 0;
-#pragma unroll
-        for (int d = TS / 2; d >= 1; d >>= 1) {
-            if (left > 1) {
-                left >>= 1;
+        // sum over the TS lanes of a row, each lane keeping half of its values at every step while it has more than one; the partners are
+        // the lanes 15 - c, 7 - c of eight, c ^ 2 and c ^ 1, which differ in the bit d
+        int t0 = 0;
+        auto halve = [&](auto ctrl, auto count, int d) {
+            constexpr int CTRL = decltype(ctrl)::value, left = decltype(count)::value / 2;
+            if constexpr (left > 0) {
                 const bool upper = (lane & d) != 0;
                 t0 = 2 * t0 + (upper ? 1 : 0);
 #pragma unroll
-                for (int t = 0; t < GP / 2; ++t)
-                    if (t < left) {
-                        const float give = upper ? w[t] : w[t + left];
-                        const float keep = upper ? w[t + left] : w[t];
-                        w[t] = keep + __shfl_xor(give, d);
-                    }
+                for (int t = 0; t < left; ++t) {
+                    const float give = upper ? w[t] : w[t + left];
+                    const float keep = upper ? w[t + left] : w[t];
+                    w[t] = keep + lane_move<CTRL>(give);
+                }
             } else {
-                w[0] += __shfl_xor(w[0], d);
+                w[0] += lane_move<CTRL>(w[0]);
             }
-        }
+        };
+        halve(std::integral_constant<int, 0x140>(), std::integral_constant<int, GP>(), 8);
+        halve(std::integral_constant<int, 0x141>(), std::integral_constant<int, GP / 2>(), 4);
+        halve(std::integral_constant<int, 0x4E>(), std::integral_constant<int, GP / 4>(), 2);
+        halve(std::integral_constant<int, 0xB1>(), std::integral_constant<int, GP / 8>(), 1);
         u = w[0];
         l = H * t0 + h;
         constexpr int kHeld = TS / GP;  // lanes that hold the same element
@@ -240,9 +272,7 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
                 for (int a = 0; a < NT; ++a) v[a] = fmaf(g[a][t], ut, v[a]);
             }
 #pragma unroll
-            for (int a = 0; a < NT; ++a)
-#pragma unroll
-                for (int d = TS; d < 64; d <<= 1) v[a] += __shfl_xor(v[a], d);
+            for (int a = 0; a < NT; ++a) v[a] = column_sum(v[a]);
         }
     }
     const float sigma = sqrtf(sigma2);
