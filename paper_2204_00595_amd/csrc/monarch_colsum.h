@@ -68,7 +68,8 @@ struct ColsumJob {
 };
 
 static inline int colsum_partial_blocks(const ColsumJob& cj) { return cj.col_tiles * cj.chunks; }
-static inline int colsum_final_blocks(const ColsumJob& cj) { return (cj.n_out + 63) / 64; }
+constexpr int kFinalCols = 16;  // columns of a workgroup of the second pass
+static inline int colsum_final_blocks(const ColsumJob& cj) { return (cj.n_out + kFinalCols - 1) / kFinalCols; }
 
 // Pass 1, workgroup `block` of colsum_partial_blocks (256 threads): each wave adds its rows of the
 // chunk in fp32, the four waves meet in LDS, wave 0 adds them in wave order and writes one fp32 partial
@@ -126,18 +127,22 @@ __device__ __forceinline__ void colsum_partial_body(const ColsumJob& cj, int blo
     for (int e = 0; e < CW; ++e) cj.part[(size_t)ch * n_out + col + e] = sum[e];
 }
 
-// Pass 2, workgroup `block` of colsum_final_blocks (64 * NL threads): the workgroup owns 64 columns;
-// NL groups of lanes each add every NL-th chunk partial, the NL sums meet in LDS and are added in
-// order; one rounding to the output type.  Every thread of the workgroup must call it.
-template <typename TO, int NL>
+// Pass 2, workgroup `block` of colsum_final_blocks (THREADS threads): the workgroup owns 16 columns; THREADS / 16 groups of
+// lanes each add every (THREADS / 16)-th chunk partial, eight in flight, the sums of the groups meet in LDS and are added in
+// order; one rounding to the output type.  Every thread of the workgroup must call it.  Bound by the latency of a thread's chain
+// of loads: with 64 columns a workgroup (4 groups of 256 threads, four loads in flight) the reduction it rides on took 9.0 us at
+// 768 columns in 341 chunks and 14.1 at 4096 columns in 64, now 7.0 and 9.5 (as a launch of
+// its own, which had 1024 threads: 4.7 and 4.9).
+template <typename TO, int THREADS>
 __device__ __forceinline__ void colsum_final_body(const ColsumJob& cj, int block)
 {
-    __shared__ float red[NL][64];
-    const int tx = threadIdx.x & 63, ty = threadIdx.x >> 6;
-    const int o = block * 64 + tx;
+    constexpr int NL = THREADS / kFinalCols;
+    __shared__ float red[NL][kFinalCols];
+    const int tx = threadIdx.x % kFinalCols, ty = threadIdx.x / kFinalCols;
+    const int o = block * kFinalCols + tx;
     float acc = 0.f;
     if (o < cj.n_out) {
-#pragma unroll 4
+#pragma unroll 8
         for (int ch = ty; ch < cj.chunks; ch += NL) acc += cj.part[(size_t)ch * cj.n_out + o];
     }
     red[ty][tx] = acc;

@@ -293,9 +293,9 @@ __global__ void __launch_bounds__(64 * ROWCOL_WAVES) colsum_partial_kernel(Colsu
 }
 
 template <typename TO>
-__global__ void __launch_bounds__(1024) colsum_final_kernel(ColsumJob cj)
+__global__ void __launch_bounds__(256) colsum_final_kernel(ColsumJob cj)
 {
-    colsum_final_body<TO, 16>(cj, (int)blockIdx.x);
+    colsum_final_body<TO, 256>(cj, (int)blockIdx.x);
 }
 
 ColsumJob make_colsum_job(const Problem& pb, const void* dy, void* dbias, void* ws)
@@ -323,8 +323,8 @@ int launch_colsum(const Problem& pb, const void* dy, void* dbias, void* ws, hipS
     const ColsumJob cj = make_colsum_job(pb, dy, dbias, ws);
     if (int rc = launch_colsum_partial(pb, cj, st)) return rc;
     const dim3 g2((unsigned)colsum_final_blocks(cj));
-    if (cj.out_f32) hipLaunchKernelGGL(colsum_final_kernel<float>, g2, dim3(1024), 0, st, cj);
-    else hipLaunchKernelGGL(colsum_final_kernel<bf16_t>, g2, dim3(1024), 0, st, cj);
+    if (cj.out_f32) hipLaunchKernelGGL(colsum_final_kernel<float>, g2, dim3(256), 0, st, cj);
+    else hipLaunchKernelGGL(colsum_final_kernel<bf16_t>, g2, dim3(256), 0, st, cj);
     return hip_status(hipGetLastError());
 }
 

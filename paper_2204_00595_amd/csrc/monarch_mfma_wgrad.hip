@@ -324,8 +324,8 @@ __global__ void __launch_bounds__(256)
 wgrad_reduce_kernel(WgradDesc d0, WgradDesc d1, int blocks0, int nz, ColsumJob cj, int blocks01)
 {
     if ((int)blockIdx.x >= blocks01) {
-        if (OUT_F32) colsum_final_body<float, 4>(cj, (int)blockIdx.x - blocks01);
-        else colsum_final_body<bf16_t, 4>(cj, (int)blockIdx.x - blocks01);
+        if (OUT_F32) colsum_final_body<float, 256>(cj, (int)blockIdx.x - blocks01);
+        else colsum_final_body<bf16_t, 256>(cj, (int)blockIdx.x - blocks01);
         return;
     }
     const bool first = (int)blockIdx.x < blocks0;

@@ -486,7 +486,7 @@ ops_gemm_pair_kernel(const OpDesc d0, const OpDesc d1)
 // chunks: a workgroup owns 64 elements, wave w adds the chunks w, w + WAVES, ..., the sums of the waves are added in order, and
 // workgroups from `blocks01` on run the second pass of the bias gradient.
 // Bound by latency: the 128 chunks of blocks of 49 x 49 and 64 x 49 took 11.7 us with a thread per element and the bias pass
-// 6.7 us in a launch of its own, together now 8.0; at 16 chunks of 192 x 192 a thread per element takes 5.1 us, 16 waves 13.
+// 6.7 us in a launch of its own, together 5.3; at 16 chunks of 192 x 192 a thread per element takes 5.1 us, 16 waves 13.
 constexpr int kSumWaves = 16, kManyChunks = 32;
 struct OpSum {
     const float* P;
@@ -501,7 +501,7 @@ ops_sum_kernel(OpSum s0, OpSum s1, int64_t blocks0, int64_t blocks01, ColsumJob 
     constexpr int kOwn = WAVES > 1 ? 64 : 256;  // elements of a workgroup
     if constexpr (WAVES > 1) {
         if ((int64_t)blockIdx.x >= blocks01) {
-            colsum_final_body<OT, WAVES>(cj, (int)((int64_t)blockIdx.x - blocks01));
+            colsum_final_body<OT, WAVES * 64>(cj, (int)((int64_t)blockIdx.x - blocks01));
             return;
         }
     }
