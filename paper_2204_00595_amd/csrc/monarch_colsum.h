@@ -1,6 +1,7 @@
 // Column sums of the upstream gradient (the bias gradient dbias[o] = sum_b dy[b][o]) as device
-// bodies, so that the two passes can run either as kernels of their own or as extra workgroups at the
-// tail of launches the backward makes anyway (the weight re-layout and the weight-gradient reduction).
+// bodies: two passes, of which the second can run as a kernel of its own or as extra workgroups at the tail of a reduction the
+// backward makes anyway.  The bf16 four-block layers take the first pass's sums from their weight-gradient products
+// (monarch_mfma_wgrad.hip).
 #pragma once
 #include "monarch_device.h"
 
@@ -129,7 +130,7 @@ __device__ __forceinline__ void colsum_partial_body(const ColsumJob& cj, int blo
 
 // Pass 2, workgroup `block` of colsum_final_blocks (THREADS threads): the workgroup owns 16 columns; THREADS / 16 groups of
 // lanes each add every (THREADS / 16)-th chunk partial, eight in flight, the sums of the groups meet in LDS and are added in
-// order; one rounding to the output type.  Every thread of the workgroup must call it.  Bound by the latency of a thread's chain
+// order, in 64 bits (the largest sums of all are made here), then rounded to the output type.  Every thread of the workgroup must call it.  Bound by the latency of a thread's chain
 // of loads: with 64 columns a workgroup (4 groups of 256 threads, four loads in flight) the reduction it rides on took 9.0 us at
 // 768 columns in 341 chunks and 14.1 at 4096 columns in 64, now 7.0 and 9.5 (as a launch of
 // its own, which had 1024 threads: 4.7 and 4.9).
@@ -137,10 +138,10 @@ template <typename TO, int THREADS>
 __device__ __forceinline__ void colsum_final_body(const ColsumJob& cj, int block)
 {
     constexpr int NL = THREADS / kFinalCols;
-    __shared__ float red[NL][kFinalCols];
+    __shared__ double red[NL][kFinalCols];
     const int tx = threadIdx.x % kFinalCols, ty = threadIdx.x / kFinalCols;
     const int o = block * kFinalCols + tx;
-    float acc = 0.f;
+    double acc = 0.;
     if (o < cj.n_out) {
 #pragma unroll 8
         for (int ch = ty; ch < cj.chunks; ch += NL) acc += cj.part[(size_t)ch * cj.n_out + o];
@@ -148,10 +149,10 @@ __device__ __forceinline__ void colsum_final_body(const ColsumJob& cj, int block
     red[ty][tx] = acc;
     __syncthreads();
     if (ty > 0 || o >= cj.n_out) return;
-    acc = 0.f;
+    acc = 0.;
 #pragma unroll
     for (int w = 0; w < NL; ++w) acc += red[w][tx];
-    Elem<TO>::store((TO*)cj.dbias + o, acc);
+    Elem<TO>::store((TO*)cj.dbias + o, (float)acc);
 }
 
 }  // namespace monarch

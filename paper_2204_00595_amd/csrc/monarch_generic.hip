@@ -279,8 +279,7 @@ int launch_bias_add(const Problem& pb, void* y, hipStream_t st)
     return hip_status(hipGetLastError());
 }
 
-// dbias[o] = sum_b dy[b][o] as two kernels of its own (bodies in monarch_colsum.h); the k = 4 matrix-core
-// backward runs the same bodies at the tail of two of its own launches instead.
+// dbias[o] = sum_b dy[b][o] as two kernels of its own (bodies in monarch_colsum.h).
 size_t colsum_workspace(const Problem& pb)
 {
     return align_up((size_t)rowcol_chunks(pb.B, pb.n_out()) * pb.n_out() * sizeof(float), 256);

@@ -242,6 +242,7 @@ struct WgradDesc {
     int64_t rows;
     int rows_per_chunk;
     int deint;       // A holds the four groups interleaved
+    float* colsum;   // deint only, may be null: row z receives the column sums of A over chunk z (lda floats)
     void* out;       // reduced result [g][m][col(n)], col(n) = (n % seg_w) * (N / seg_w) + n / seg_w
 };
 bool wgrad_tile_ok(int M, int N, int seg_w, int* tm, int* tn);
@@ -249,6 +250,8 @@ int wgrad_tiles(const WgradDesc& d);  // workgroups per batch chunk (0: shape no
 // both GEMMs over the same nz batch chunks (one launch when their tile shapes agree), then
 // one launch that sums the chunks of both and writes `out` (fp32 or bf16)
 int wgrad_gemm_pair(const WgradDesc& d0, const WgradDesc& d1, int nz, hipStream_t st);
+// the bias gradient from a GEMM over nz chunks whose deint operand is dy: the job whose `part` is that GEMM's `colsum`
+ColsumJob wgrad_colsum_job(const Problem& pb, int nz);
 // `cj` (may be null): the second pass of the bias gradient runs as extra workgroups of the same launch
 int wgrad_reduce_pair(const WgradDesc& d0, const WgradDesc& d1, bool out_f32, int nz, hipStream_t st,
                       const ColsumJob* cj = nullptr);

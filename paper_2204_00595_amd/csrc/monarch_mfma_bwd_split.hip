@@ -7,8 +7,8 @@
 //   dU from dy:  W = L (m = l, n = r; g*N + n = c*q + r is the permuted position)
 //   dx from dU:  W = R (m = j, n = i)
 //
-//   prep     transposed fragments of L and R (below), the recomputed Y1 (split_stage1, which reads R as it is) and the first pass
-//            of the bias gradient, as workgroups of one launch
+//   prep     transposed fragments of L and R (below), the recomputed Y1 (split_stage1, which reads R as it is), as workgroups
+//            of one launch
 //   adjoint  workgroup = (32 rows, NT column tiles of 32 of all four blocks): the waves share out the contraction, a K-step of
 //            16 m is one whole 128-byte line per row, picked apart in registers; the waves' tiles are added up through LDS,
 //            wave g keeps block g
@@ -34,7 +34,7 @@ struct BwdPrep {
     const uint16_t *x, *R, *L;
     uint16_t *Y1, *LT, *RT;
     int P, Q, S;
-    int y1_blocks, pack_blocks;  // workgroups of the recompute (none where the forward saved the vector), then of the packing
+    int y1_blocks;  // workgroups of the recompute (none where the forward saved the vector), then those of the packing
 };
 
 // one 16-byte piece of the transposed fragments of W (4 blocks of M x N)
@@ -54,7 +54,7 @@ __device__ __forceinline__ void pack_adjoint_piece(const uint16_t* __restrict__ 
 
 template <int NT, int NG>
 __global__ void __launch_bounds__(256)
-bwd_split_prep_kernel(const BwdPrep w, int64_t B, SplitGrid gr, ColsumJob cj)
+bwd_split_prep_kernel(const BwdPrep w, int64_t B, SplitGrid gr)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
     int bid = (int)blockIdx.x;
@@ -63,13 +63,9 @@ bwd_split_prep_kernel(const BwdPrep w, int64_t B, SplitGrid gr, ColsumJob cj)
         return;
     }
     bid -= w.y1_blocks;
-    if (bid < w.pack_blocks) {
-        const int nL = 4 * w.S * w.Q / 8, nR = 4 * w.Q * w.P / 8, pc = bid * 256 + (int)threadIdx.x;
-        if (pc < nL) pack_adjoint_piece(w.L, w.LT, w.S, w.Q, pc);
-        else if (pc < nL + nR) pack_adjoint_piece(w.R, w.RT, w.Q, w.P, pc - nL);
-        return;
-    }
-    colsum_partial_body<bf16_t, 4>(cj, bid - w.pack_blocks);
+    const int nL = 4 * w.S * w.Q / 8, nR = 4 * w.Q * w.P / 8, pc = bid * 256 + (int)threadIdx.x;
+    if (pc < nL) pack_adjoint_piece(w.L, w.LT, w.S, w.Q, pc);
+    else if (pc < nL + nR) pack_adjoint_piece(w.R, w.RT, w.Q, w.P, pc - nL);
 }
 
 // NS: K-steps of a wave, at most (see tile_product).  ACT: the result is multiplied by gelu'(x_pre).
@@ -225,14 +221,14 @@ int adjoint(const uint16_t* in, const uint16_t* WT, uint16_t* out, const void* x
 }
 
 template <int NT>
-int launch_prep(const BwdPrep& w, int64_t B, const SplitGrid& gr, const ColsumJob& cj, unsigned blocks, hipStream_t st)
+int launch_prep(const BwdPrep& w, int64_t B, const SplitGrid& gr, unsigned blocks, hipStream_t st)
 {
     constexpr size_t lds = split_stage1_lds<1, NT, (NT > 1)>();
     const int ng = ((w.P / 16 + 3) / 4 + 3) / 4;
     auto kern = ng == 1 ? bwd_split_prep_kernel<NT, 1> : ng == 2 ? bwd_split_prep_kernel<NT, 2>
               : ng == 3 ? bwd_split_prep_kernel<NT, 3> : bwd_split_prep_kernel<NT, 4>;
     if (hipError_t e = allow_dynamic_lds((const void*)kern, lds)) return hip_status(e);
-    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, w, B, gr, cj);
+    hipLaunchKernelGGL(kern, dim3(blocks), dim3(256), lds, st, w, B, gr);
     return hip_status(hipGetLastError());
 }
 
@@ -306,16 +302,13 @@ int bwd_split(const Problem& pb, const void* dy, const void* x, const void* R, c
     if (!pl.ok) return -2;
     char* w = (char*)ws;
     uint16_t *Y1 = (uint16_t*)(w + pl.y1), *dU = (uint16_t*)(w + pl.du), *LT = (uint16_t*)(w + pl.lt), *RT = (uint16_t*)(w + pl.rt);
-    ColsumJob cj{};
-    if (pb.dbias) cj = make_colsum_job(pb, dy, pb.dbias, pb.colsum_ws);
     const int nt = (pb.B + 31) / 32 * (pb.kq() / 32) <= 512 ? 1 : 2;
     unsigned blocks = 0;
     SplitGrid gr{};
     if (!pb.saved) gr = split_grid(pb.B, 32, 4 * ((pb.q / 32 + nt - 1) / nt), &blocks);
-    BwdPrep pr{(const uint16_t*)x, (const uint16_t*)R, (const uint16_t*)L, Y1, LT, RT, pb.p, pb.q, pb.s, (int)blocks,
-               (int)(((pb.n_R() + pb.n_L()) / 8 + 255) / 256)};
-    blocks += (unsigned)pr.pack_blocks + (pb.dbias ? (unsigned)colsum_partial_blocks(cj) : 0u);
-    int rc = nt == 1 ? launch_prep<1>(pr, pb.B, gr, cj, blocks, st) : launch_prep<2>(pr, pb.B, gr, cj, blocks, st);
+    BwdPrep pr{(const uint16_t*)x, (const uint16_t*)R, (const uint16_t*)L, Y1, LT, RT, pb.p, pb.q, pb.s, (int)blocks};
+    blocks += (unsigned)(((pb.n_R() + pb.n_L()) / 8 + 255) / 256);
+    int rc = nt == 1 ? launch_prep<1>(pr, pb.B, gr, blocks, st) : launch_prep<2>(pr, pb.B, gr, blocks, st);
     if (!rc) rc = adjoint((const uint16_t*)dy, LT, dU, nullptr, pb.B, pb.s, pb.q, st);
     if (!rc) rc = adjoint(dU, RT, (uint16_t*)dx, pb.x_pre, pb.B, pb.q, pb.p, st);
     if (rc) return rc;
@@ -333,6 +326,11 @@ int bwd_split(const Problem& pb, const void* dy, const void* x, const void* R, c
     // would add a rounding (200 rows: dR and dL 2.34e-3 off float64 with fp32 sums, 2.88e-3 without; from 257 rows on 2.88e-3
     // against 2.94e-3 in the chunks of 256)
     dl.p_bf16 = dr.p_bf16 = pb.wgrad_f32() || pb.B <= 256 ? 0 : 1;
+    ColsumJob cj{};
+    if (pb.dbias) {
+        cj = wgrad_colsum_job(pb, pl.nz);
+        dl.colsum = cj.part;
+    }
     rc = wgrad_gemm_pair(dl, dr, pl.nz, st);
     return rc ? rc : wgrad_reduce_pair(dl, dr, pb.wgrad_f32(), pl.nz, st, pb.dbias ? &cj : nullptr);
 }

@@ -41,14 +41,8 @@ namespace {
 //       (dx stage, 16x16x32: R transposed, K-slots in the order the chained accumulators hold dY1)
 __global__ void __launch_bounds__(256)
 prep_frag_kernel(const uint16_t* __restrict__ L, const uint16_t* __restrict__ R, uint16_t* __restrict__ XF,
-                 uint16_t* __restrict__ LF, uint16_t* __restrict__ RF, int P, int Q, int S, int JG, int IG,
-                 ColsumJob cj, int nprep)
+                 uint16_t* __restrict__ LF, uint16_t* __restrict__ RF, int P, int Q, int S, int JG, int IG)
 {
-    // workgroups past the re-layout run the first pass of the bias gradient (column sums of dy)
-    if ((int)blockIdx.x >= nprep) {
-        colsum_partial_body<bf16_t, 4>(cj, (int)blockIdx.x - nprep);
-        return;
-    }
     const int nR = 4 * Q * P / 8, nL = 4 * S * Q / 8;  // pieces per array
     int pc = blockIdx.x * 256 + threadIdx.x;
     uint16_t v[8];
@@ -543,7 +537,7 @@ int fwd_t_wide(const Problem& pb, const void* x, const void* R, const void* L, v
     const size_t pieces = (2 * pb.n_R() + pb.n_L()) / 8;
     const int nprep = (int)((pieces + 255) / 256);
     hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)nprep), dim3(256), 0, st, (const uint16_t*)L, (const uint16_t*)R,
-                       XF, LF, RF, pb.p, pb.q, pb.s, e->jg, e->ig, ColsumJob{}, nprep);
+                       XF, LF, RF, pb.p, pb.q, pb.s, e->jg, e->ig);
     if (hipGetLastError() != hipSuccess) return -4;
     return e->fn(pb, x, nullptr, XF, LF, RF, y, nullptr, nullptr, st);
 }
@@ -570,11 +564,8 @@ int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, co
     }
     const size_t pieces = (2 * pb.n_R() + pb.n_L()) / 8;
     const int nprep = (int)((pieces + 255) / 256);
-    ColsumJob cj{};
-    const bool want_db = pb.dbias != nullptr;
-    if (want_db) cj = make_colsum_job(pb, dy, pb.dbias, pb.colsum_ws);
-    hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)(nprep + (want_db ? colsum_partial_blocks(cj) : 0))), dim3(256), 0,
-                       st, (const uint16_t*)L, (const uint16_t*)R, XF, LF, RF, pb.p, pb.q, pb.s, e->jg, e->ig, cj, nprep);
+    hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)nprep), dim3(256), 0, st, (const uint16_t*)L, (const uint16_t*)R,
+                       XF, LF, RF, pb.p, pb.q, pb.s, e->jg, e->ig);
     if (hipGetLastError() != hipSuccess) return -4;
     // Step 1 (Y1, for dL) is recomputed either by the data kernel itself or, for the shapes that have it, by a
     // GEMM of its own with four times the rows per workgroup (monarch_mfma_y1.hip); not at all when the forward saved it.
@@ -598,9 +589,14 @@ int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, co
     dr.A = dY1ws; dr.Bm = (const uint16_t*)x; dr.P = (float*)(w + pl.off_partR); dr.out = dR;
     dl.rows_per_chunk = dr.rows_per_chunk = pl.rows_per_chunk;
     dl.p_bf16 = dr.p_bf16 = f32out ? 0 : 1;  // bf16 gradients: bf16 partial tiles
+    ColsumJob cj{};
+    if (pb.dbias) {
+        cj = wgrad_colsum_job(pb, pl.nz);
+        dl.colsum = cj.part;
+    }
     rc = wgrad_gemm_pair(dl, dr, pl.nz, st);
     if (rc) return rc;
-    return wgrad_reduce_pair(dl, dr, f32out, pl.nz, st, want_db ? &cj : nullptr);
+    return wgrad_reduce_pair(dl, dr, f32out, pl.nz, st, pb.dbias ? &cj : nullptr);
 }
 
 }  // namespace monarch

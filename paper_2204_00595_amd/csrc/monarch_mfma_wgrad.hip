@@ -15,6 +15,12 @@
 // each group's output; the batch is split into chunks whose fp32 partial tiles are summed by
 // `wgrad_reduce_kernel`, which also undoes the column order used for dL and converts to the
 // output type.
+//
+// The bias gradient, the column sums of dy, comes with dL: a wave adds up the fragments of dy it multiplies (v_dot2 against ones,
+// five instructions for eight rows), in the tiles of the first columns n alone.  A pass of its own over dy cost more than the
+// products slow down (GPU time of the training step of the feed-forward block of width 1024, 16384 rows: 583 -> 565 us; the launch
+// that did it beside the weights' re-layout 26.9 + 11.6 -> 6.0 + 5.6, the two launches of products 153 -> 160; 768 -> 768, 12608
+// rows: 6.3 -> 3.0 against 24.2 -> 24.8).  The sums are off float64 by 2.8e-8 (12608 rows), those of that pass were by 6.3e-8.
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
 #include "monarch_colsum.h"
@@ -66,7 +72,7 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* T, int stride, int k0,
 // MSPLIT = true (large tiles): they split the tile's rows m instead, each taking both K-steps of a pipeline step on
 // its own half of the accumulators -- 128 x 128 per group in 2 x 128 accumulator registers, which halves the operand
 // bytes fetched per flop against the 64 x 128 tile.
-template <int TM, int TN, bool DEINT, bool MSPLIT>
+template <int TM, int TN, bool DEINT, bool SUMS, bool MSPLIT>
 __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int tile, const int zi)
 {
     // register stages of the operand loads (rows fetched NSTG steps before they are stored): two for the 128 x 128 tile (feed-forward
@@ -176,6 +182,20 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
         for (int t = 0; t < B_PER; ++t) *reinterpret_cast<u32x4*>(buf + lb[t]) = breg[stg][t];
     };
 
+    // column sums of A from the fragments of the products: eight rows of a feature per lane, a chain for each parity of the step
+    float cs[2][MTW] = {};
+    auto add_rows = [&](float& s, const bf16x8& f) {
+        typedef __attribute__((ext_vector_type(2))) __bf16 bf16x2;
+        const u32x4 v = __builtin_bit_cast(u32x4, f);
+        float t = 0.f;
+#pragma unroll
+        for (int w = 0; w < 4; ++w) {
+            const uint32_t pair = v[w];  // (a bit cast of the element itself takes element 0)
+            t = __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), bf16x2{(__bf16)1.f, (__bf16)1.f}, t, false);
+        }
+        s += t;
+    };
+
     f32x16 acc[MTW * NT];
 #pragma unroll
     for (int t = 0; t < MTW * NT; ++t)
@@ -222,6 +242,9 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
             for (int mt = 0; mt < MTW; ++mt)
 #pragma unroll
                 for (int nt = 0; nt < NT; ++nt) acc[mt * NT + nt] = mfma32(af[mt], bfr[nt], acc[mt * NT + nt]);
+            if constexpr (SUMS)
+#pragma unroll
+                for (int mt = 0; mt < MTW; ++mt) add_rows(cs[k][mt], af[mt]);
             if constexpr (MSPLIT) {
                 // second K-step of the pipeline step (rows 16 .. 31 of the buffer)
 #pragma unroll
@@ -232,9 +255,23 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
                 for (int mt = 0; mt < MTW; ++mt)
 #pragma unroll
                     for (int nt = 0; nt < NT; ++nt) acc[mt * NT + nt] = mfma32(af[mt], bfr[nt], acc[mt * NT + nt]);
+                if constexpr (SUMS)
+#pragma unroll
+                    for (int mt = 0; mt < MTW; ++mt) add_rows(cs[k][mt], af[mt]);
             }
         }
     }
+    }
+    auto store_sums = [&](int mt, float v) {
+        if (lane < 32) d.colsum[(size_t)zi * d.lda + 4 * (m0 + (MSPLIT ? kh * MTW * 32 : 0) + mt * 32 + lane) + grp] = v;
+    };
+    if constexpr (SUMS) {
+#pragma unroll
+        for (int mt = 0; mt < MTW; ++mt) {
+            cs[0][mt] += cs[1][mt];
+            cs[0][mt] += __shfl_xor(cs[0][mt], 32);  // the other eight rows of the K-steps
+            if constexpr (MSPLIT) store_sums(mt, cs[0][mt]);
+        }
     }
 
     // sum the two K halves of every group through LDS (fp32, in two rounds of at most R1 tiles per
@@ -243,10 +280,16 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
         constexpr int NTILE = MT * NT, R1 = (NTILE + 1) / 2;
         static_assert((size_t)4 * R1 * 4096 <= (size_t)2 * BUF * 2, "reduction staging fits the pipeline buffers");
         float* red = reinterpret_cast<float*>(lds) + (size_t)grp * R1 * 1024 + lane;
+        float* redc = reinterpret_cast<float*>(lds) + (size_t)4 * R1 * 1024 + grp * MT * 32 + (lane & 31);
+        static_assert(!SUMS || (size_t)4 * R1 * 4096 + 4 * MT * 128 <= (size_t)2 * BUF * 2, "and so do the column sums");
 #pragma unroll
         for (int t0 = 0; t0 < NTILE; t0 += R1) {
             __syncthreads();  // the buffers (or the previous round) are no longer read
             if (kh == 1) {
+                if constexpr (SUMS)
+                    if (t0 == 0)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) redc[mt * 32] = cs[0][mt];
 #pragma unroll
                 for (int t = t0; t < t0 + R1 && t < NTILE; ++t)
 #pragma unroll
@@ -254,6 +297,10 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
             }
             __syncthreads();
             if (kh == 0) {
+                if constexpr (SUMS)
+                    if (t0 == 0)
+#pragma unroll
+                        for (int mt = 0; mt < MT; ++mt) store_sums(mt, cs[0][mt] + redc[mt * 32]);
 #pragma unroll
                 for (int t = t0; t < t0 + R1 && t < NTILE; ++t)
 #pragma unroll
@@ -307,11 +354,12 @@ wgrad_gemm_kernel(WgradDesc d0, WgradDesc d1, int tiles0, int tiles)
     const int t = v % tiles, zi = v / tiles;
     constexpr bool MSPLIT = (TM / 32) * (TN / 32) > 9;  // more accumulators than one wave of a pair can hold
     if (t < tiles0) {
-        if (d0.deint) wgrad_gemm_body<TM, TN, true, MSPLIT>(d0, t, zi);
-        else wgrad_gemm_body<TM, TN, false, MSPLIT>(d0, t, zi);
+        if (d0.colsum && t % (d0.N / TN) == 0) wgrad_gemm_body<TM, TN, true, true, MSPLIT>(d0, t, zi);
+        else if (d0.deint) wgrad_gemm_body<TM, TN, true, false, MSPLIT>(d0, t, zi);
+        else wgrad_gemm_body<TM, TN, false, false, MSPLIT>(d0, t, zi);
     } else {
-        if (d1.deint) wgrad_gemm_body<TM, TN, true, MSPLIT>(d1, t - tiles0, zi);
-        else wgrad_gemm_body<TM, TN, false, MSPLIT>(d1, t - tiles0, zi);
+        if (d1.deint) wgrad_gemm_body<TM, TN, true, false, MSPLIT>(d1, t - tiles0, zi);
+        else wgrad_gemm_body<TM, TN, false, false, MSPLIT>(d1, t - tiles0, zi);
     }
 }
 
@@ -463,6 +511,13 @@ int wgrad_gemm_pair(const WgradDesc& d0, const WgradDesc& d1, int nz, hipStream_
     if (tm0 == tm1 && tn0 == tn1) return launch_gemm_tile(tm0, tn0, d0, &d1, nz, st);
     const int rc = launch_gemm_tile(tm0, tn0, d0, nullptr, nz, st);
     return rc ? rc : launch_gemm_tile(tm1, tn1, d1, nullptr, nz, st);
+}
+
+ColsumJob wgrad_colsum_job(const Problem& pb, int nz)
+{
+    ColsumJob cj = make_colsum_job(pb, nullptr, pb.dbias, pb.colsum_ws);
+    cj.chunks = nz;  // no more than it was: chunks of at least 64 rows against 16, and of 256 / tiles against 1024 / (s / 64)
+    return cj;
 }
 
 int wgrad_reduce_pair(const WgradDesc& d0, const WgradDesc& d1, bool out_f32, int nz, hipStream_t st, const ColsumJob* cj)
