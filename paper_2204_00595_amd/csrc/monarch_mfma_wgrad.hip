@@ -6,9 +6,9 @@
 //   dR[kk][j][i] = sum_b dY1[b][kk][j] * x[b][kk*p + i]  A = dY1,                  Bm = x
 //
 // (the adjoints of steps 2 and 1 of Section 3.3).  Both operands are stored batch-major, i.e.
-// the contraction index is the slow one, so they are staged row-major in LDS with 16-byte
-// writes and read back with the transposing LDS load of gfx950 (ds_read_b64_tr_b16), which
-// hands every lane four consecutive batch rows of one feature: exactly the MFMA operand layout.
+// the contraction index is the slow one, so they are staged row-major in LDS and read back with
+// the transposing LDS load of gfx950 (ds_read_b64_tr_b16), which hands every lane four consecutive
+// batch rows of one feature: exactly the MFMA operand layout.
 //
 // One workgroup = four groups g, two waves per group (each takes every other 16-row K-step on its own
 // accumulators: two waves per SIMD hide each other's staging and LDS latencies), a TM x TN tile of
@@ -16,22 +16,31 @@
 // `wgrad_reduce_kernel`, which also undoes the column order used for dL and converts to the
 // output type.
 //
+// What bounds it: memory.  A further step of 32 rows costs what its rows take at 4 to 5 TB/s (768 -> 768: 1.1 us; from 50000 rows
+// on the launch reads at 4.7 TB/s), and 9 us are the launch, the first rows' latency and the partial tiles, which all workgroups
+// write at the same time.  To get there the work of a step is dealt out between its MFMAs (`multiply`), B goes into LDS without
+// passing through registers, and the rows of the interleaved operand are read in whole lines (each wave load of its runs of 64
+// bytes held the L1 up three times as long): rows staged by way of registers before the products, with fragments read in between,
+// took 31.2 us where this takes 29.7 (768 -> 3072, 8192 rows; whole training step 101.4 -> 99.2), 80.4 + 76.3 where this takes
+// 77.8 + 72.8 (feed-forward block of width 1024, 16384 rows; 551 -> 546).
+//
 // The bias gradient, the column sums of dy, comes with dL: a wave adds up the fragments of dy it multiplies (v_dot2 against ones,
 // five instructions for eight rows), in the tiles of the first columns n alone.  A pass of its own over dy cost more than the
 // products slow down (GPU time of the training step of the feed-forward block of width 1024, 16384 rows: 583 -> 565 us; the launch
 // that did it beside the weights' re-layout 26.9 + 11.6 -> 6.0 + 5.6, the two launches of products 153 -> 160; 768 -> 768, 12608
 // rows: 6.3 -> 3.0 against 24.2 -> 24.8).  The sums are off float64 by 2.8e-8 (12608 rows), those of that pass were by 6.3e-8.
+#include <type_traits>
+#include <utility>
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
+#include "monarch_mfma_stage1.h"
 #include "monarch_colsum.h"
 
 namespace monarch {
 
 namespace {
 
-typedef __attribute__((ext_vector_type(4))) short s16x4;
-
-constexpr int KB = 32;    // batch rows per pipeline step (two 16-row K-steps, one per wave of a group)
+constexpr int KB = 32;    // batch rows per pipeline step (two 16-row K-steps)
 constexpr int NTHR = 512;  // eight waves per workgroup
 
 // A load at this offset (past the end of the buffer, whatever is added to it) reads zeros; make_problem keeps KB rows of any
@@ -42,31 +51,58 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffffu, 0x00020000);
 }
 
-// Padding of the LDS rows (bf16 elements).  A half wave of a transposing read touches four consecutive rows,
-// 64 bytes (16 banks) of each: with a row stride of an odd multiple of 64 bytes the four rows fall on disjoint
-// quarters of the 64 banks.  Strides: 128 -> 160, 96 -> 96, 64 -> 96, 32 -> 32 elements.  (The 16-byte writes stay
-// conflict-free: 16 lanes write 256 bytes that are either contiguous or in two disjoint bank ranges.)
-constexpr int lds_pad(int tile) { return (tile == 128 || tile == 64) ? 32 : 0; }
-
-// Transposing LDS read: within each 16 lanes, lane i receives element (i % 4) of lanes
-// i/4, 4 + i/4, 8 + i/4, 12 + i/4.
-__device__ __forceinline__ u32x2 lds_tr16(const uint16_t* p)
+// A row of TW features of one group is TW / 32 runs of 64 bytes in LDS, unpadded.  Half a wave of a transposing read touches one run
+// of four consecutive rows, which must fall on disjoint quarters of the 64 banks: the runs of a row change places by the row (strides
+// of one or three runs do it by themselves).
+template <int TW>
+__device__ __forceinline__ constexpr int run_key(int row)
 {
-    s16x4 v = __builtin_amdgcn_ds_read_tr16_b64_v4i16(
-        (s16x4 __attribute__((address_space(3)))*)(const_cast<uint16_t*>(p)));
-    return __builtin_bit_cast(u32x2, v);
+    return TW == 128 ? row & 3 : TW == 64 ? (row >> 1) & 1 : 0;
 }
-
-// MFMA operand (32 features x 16 batch rows) from a row-major LDS tile T[row][col]:
-// lane (f = lane % 32, h = lane / 32) gets T[k0 + 8h .. 8h+7][c0 + f].
-__device__ __forceinline__ bf16x8 frag_tr(const uint16_t* T, int stride, int k0, int c0, int lane)
+// The LDS accesses of the pipeline are written out, and the wave waits for them by itself (lgkm_wait): the compiler puts a wait for
+// everything that is on its way into LDS (buffer_load ... lds) before a transposing read it knows of.
+// Transposing read: within each 16 lanes, lane i receives element (i % 4) of lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4.
+template <int OFF>
+__device__ __forceinline__ u32x2 lds_tr16(uint32_t at)
 {
-    const int G = lane >> 4, j = lane & 15;
-    const uint16_t* p = T + (size_t)(k0 + 8 * (G >> 1) + (j >> 2)) * stride + c0 + 16 * (G & 1) + 4 * (j & 3);
-    const u32x2 lo = lds_tr16(p), hi = lds_tr16(p + 4 * stride);
-    const u32x4 v = {lo[0], lo[1], hi[0], hi[1]};
-    return as_bf16x8(v);
+    static_assert(OFF >= 0 && OFF < 65536, "offset field");
+    u32x2 v;
+    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(at), "n"(OFF));
+    return v;
 }
+template <int OFF>
+__device__ __forceinline__ void lds_put32(uint32_t at, uint32_t v)
+{
+    static_assert(OFF >= 0 && OFF < 65536, "offset field");
+    asm volatile("ds_write_b32 %0, %1 offset:%2" : : "v"(at), "v"(v), "n"(OFF));
+}
+template <int OFF>
+__device__ __forceinline__ void lds_put128(uint32_t at, const u32x4& v)
+{
+    static_assert(OFF >= 0 && OFF < 65536, "offset field");
+    asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(at), "v"(v), "n"(OFF));
+}
+// An MFMA operand (32 features x 16 batch rows) on its way from LDS: lane (f = lane % 32, h = lane / 32) gets rows 8h .. 8h+7 of
+// feature f, four of them in each half.
+struct Frag {
+    u32x2 lo, hi;
+    __device__ __forceinline__ bf16x8 operand() const { return as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]}); }
+};
+template <int N>
+__device__ __forceinline__ void lgkm_wait(Frag (&f)[N])
+{
+    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+#pragma unroll
+    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i].lo), "+v"(f[i].hi));
+}
+template <int... I, typename F>
+__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, F f)
+{
+    (f(std::integral_constant<int, I>{}), ...);
+}
+// f(0) .. f(N - 1), the numbers as constants
+template <int N, typename F>
+__device__ __forceinline__ void each(F f) { each_of(std::make_integer_sequence<int, N>{}, f); }
 
 // MSPLIT = false: the two waves of a group split the K-steps (each keeps the whole TM x TN tile, summed at the end);
 // MSPLIT = true (large tiles): they split the tile's rows m instead, each taking both K-steps of a pipeline step on
@@ -75,20 +111,16 @@ __device__ __forceinline__ bf16x8 frag_tr(const uint16_t* T, int stride, int k0,
 template <int TM, int TN, bool DEINT, bool SUMS, bool MSPLIT>
 __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int tile, const int zi)
 {
-    // register stages of the operand loads (rows fetched NSTG steps before they are stored): two for the 128 x 128 tile (feed-forward
-    // block of width 1024, 16384 rows: 82 -> 77 us in each layer); the smaller ones measured no faster with two
-    constexpr int NSTG = MSPLIT ? 2 : 1;
     constexpr int MT = TM / 32, NT = TN / 32;
     constexpr int MTW = MSPLIT ? MT / 2 : MT;  // m tiles of one wave
     static_assert(!MSPLIT || MT % 2 == 0, "row split");
-    constexpr int SA = TM + lds_pad(TM), SB = TN + lds_pad(TN);  // LDS row strides (bf16 elements)
-    constexpr int BUF = 4 * KB * (SA + SB);  // one pipeline buffer: As [4][KB][SA], then Bs [4][KB][SB]
+    constexpr int ABUF = 4 * KB * TM * 2, BBUF = 4 * KB * TN * 2;  // bytes of a step's rows [4][KB][T]: two buffers of A, then three of B
     extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
 
     // eight waves: wave = (group g, half kh); the two waves of a group each take one 16-row K-step of every
     // 32-row pipeline step on their own accumulators, which are summed through LDS at the end (MSPLIT: each
     // takes half of the tile's rows m over both K-steps, and nothing is summed)
-    const int tid = threadIdx.x, wave = tid >> 6, lane = tid & 63;
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
     const int grp = wave & 3, kh = wave >> 2;
     const int tiles_n = d.N / TN;
     const int tiles_mn = (d.M / TM) * tiles_n;
@@ -99,87 +131,92 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
     if (row_hi > d.rows) row_hi = d.rows;
     const int64_t nrows = row_hi > row_lo ? row_hi - row_lo : 0;
 
-    // ---- per-thread load tasks (16-byte pieces; DEINT A: 64-byte runs holding 8 m x 4 groups) ----
+    // ---- per-thread load tasks (pieces of 16 bytes, side by side in a row) ----
     // Addresses are fixed for the whole chunk: byte offsets from the (uniform) first row of a step, LDS offsets inside a
-    // buffer, and the row of the task inside a step.
-    constexpr int A_TASKS = DEINT ? (KB * TM / 8) : (4 * KB * TM / 8);
-    constexpr int B_TASKS = 4 * KB * TN / 8;
-    static_assert(B_TASKS % NTHR == 0 && (DEINT || A_TASKS % NTHR == 0), "only de-interleaving leaves threads without a task");
-    constexpr int A_PER = (A_TASKS + NTHR - 1) / NTHR, B_PER = (B_TASKS + NTHR - 1) / NTHR;
-    u32x4 areg[NSTG][A_PER][DEINT ? 4 : 1], breg[NSTG][B_PER];
-    uint32_t pa[A_PER], pb[B_PER];
-    int ra[A_PER], rb[B_PER], la[A_PER], lb[B_PER];
+    // buffer, and the row of the task inside a step.  B goes straight into LDS, 64 pieces side by side per wave; A by way of
+    // registers, where a piece of the interleaved operand (two m of four groups) is picked apart.
+    constexpr int A_PER = 4 * KB * TM / 8 / NTHR, B_PER = 4 * KB * TN / 8 / NTHR;
+    static_assert(A_PER * NTHR * 8 == 4 * KB * TM && B_PER * NTHR * 8 == 4 * KB * TN, "every thread has the same tasks");
+    u32x4 areg[2][A_PER];
+    uint32_t pa[A_PER], pb[B_PER], la[A_PER];
+    int ra[A_PER], rb[B_PER];
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)lds;
 #pragma unroll
     for (int t = 0; t < A_PER; ++t) {
-        // a thread without a task in this slot repeats task 0 (its loads are unconditional and must
-        // stay in bounds; it stores nothing)
-        const int task = tid + t * NTHR < A_TASKS ? tid + t * NTHR : 0;
+        const int task = tid + t * NTHR;
         if (DEINT) {
-            const int r = task / (TM / 8), u = task % (TM / 8);
-            ra[t] = tid + t * NTHR < A_TASKS ? r : (1 << 30);
-            pa[t] = (uint32_t)(r * d.lda + (m0 + 8 * u) * 4 + g0) * 2;
-            la[t] = r * SA + 8 * u;
+            const int r = task / (TM / 2), u = task % (TM / 2);  // m = 2u, 2u + 1
+            ra[t] = r;
+            pa[t] = (uint32_t)(r * d.lda + m0 * 4 + g0 + 8 * u) * 2;
+            la[t] = lds0 + r * TM * 2 + ((u >> 4) ^ run_key<TM>(r)) * 64 + (u & 15) * 4;
         } else {
             const int g = task / (KB * TM / 8), rem = task % (KB * TM / 8);
             const int r = rem / (TM / 8), u = rem % (TM / 8);
-            ra[t] = tid + t * NTHR < A_TASKS && g0 + g < d.G ? r : (1 << 30);  // a group past the last one: zeros
+            ra[t] = g0 + g < d.G ? r : (1 << 30);  // a group past the last one: zeros
             pa[t] = (uint32_t)(r * d.lda + (g0 + g) * d.a_g + m0 + 8 * u) * 2;
-            la[t] = (g * KB + r) * SA + 8 * u;
+            la[t] = lds0 + (g * KB + r) * TM * 2 + ((u >> 2) ^ run_key<TM>(r)) * 64 + (u & 3) * 16;
         }
     }
 #pragma unroll
     for (int t = 0; t < B_PER; ++t) {
-        const int task = tid + t * NTHR < B_TASKS ? tid + t * NTHR : 0;
+        const int task = tid + t * NTHR;  // its place in LDS; the piece that belongs there:
         const int g = task / (KB * TN / 8), rem = task % (KB * TN / 8);
-        const int r = rem / (TN / 8), u = rem % (TN / 8);
+        const int r = rem / (TN / 8), u = ((rem % (TN / 8) >> 2) ^ run_key<TN>(r)) * 4 + (rem & 3);
         const int n = n0 + 8 * u;
-        rb[t] = tid + t * NTHR < B_TASKS && g0 + g < d.G ? r : (1 << 30);
+        rb[t] = g0 + g < d.G ? r : (1 << 30);
         pb[t] = (uint32_t)(r * d.ldb + (g0 + g) * d.b_g + (n / d.seg_w) * d.b_seg + (n % d.seg_w)) * 2;
-        lb[t] = 4 * KB * SA + (g * KB + r) * SB + 8 * u;
     }
 
-    // rows r0 .. r0+KB-1 of the chunk -> register stage `stg`; rows past the end of the chunk (and the
-    // slots of threads without a task) load nothing and read as zeros: a buffer load at an offset past the
-    // buffer's end.  A branch around each load instead makes the compiler lose count of the loads in flight
-    // and wait for all of them, which leaves no second stage.
-    auto load_step = [&](int64_t r0, int stg) {
-        const auto bufa = buffer_at(d.A + (row_lo + r0) * d.lda), bufb = buffer_at(d.Bm + (row_lo + r0) * d.ldb);
-        const int left = nrows - r0 < KB ? (int)(nrows - r0) : KB;
-#pragma unroll
-        for (int t = 0; t < A_PER; ++t) {
-            const uint32_t at = ra[t] < left ? pa[t] : kNowhere;
-#pragma unroll
-            for (int w = 0; w < (DEINT ? 4 : 1); ++w) areg[stg][t][w] = __builtin_amdgcn_raw_buffer_load_b128(bufa, at, 16 * w, 0);
-        }
-#pragma unroll
-        for (int t = 0; t < B_PER; ++t)
-            breg[stg][t] = __builtin_amdgcn_raw_buffer_load_b128(bufb, rb[t] < left ? pb[t] : kNowhere, 0, 0);
+    // Rows r0 .. r0+KB-1 of the chunk; rows past its end load nothing and read as zeros: a buffer load at an offset past the buffer's end.  A branch around each load instead makes the compiler lose
+    // count of the loads in flight and wait for all of them.
+    auto rows_left = [&](int64_t r0) { return nrows - r0 < KB ? (int)(nrows - r0) : KB; };
+    auto load_a = [&](int64_t r0, int stg, int t) {
+        const auto buf = buffer_at(d.A + (row_lo + r0) * d.lda);
+        areg[stg][t] = __builtin_amdgcn_raw_buffer_load_b128(buf, ra[t] < rows_left(r0) ? pa[t] : kNowhere, 0, 0);
     };
-    // register stage -> LDS buffer
-    auto store_step = [&](int64_t, int stg, uint16_t* buf) {
-#pragma unroll
-        for (int t = 0; t < A_PER; ++t) {
-            uint16_t* to = buf + la[t];
-            if constexpr (A_TASKS % NTHR != 0)  // no branch here either: without a task the zeros go past the buffers
-                to = tid + t * NTHR < A_TASKS ? to : lds + 2 * BUF + 8 * lane;
-            if (DEINT) {
-                // the run holds elements e = 4*m' + c (m' = 0..7); gather the 8 m' of each group c
-#pragma unroll
-                for (int c = 0; c < 4; ++c) {
-                    u32x4 v;
-#pragma unroll
-                    for (int w = 0; w < 4; ++w) {
-                        const uint32_t lo = areg[stg][t][w][c >> 1], hi = areg[stg][t][w][2 + (c >> 1)];
-                        v[w] = (c & 1) ? pick_hi16(lo, hi) : pick_lo16(lo, hi);
-                    }
-                    *reinterpret_cast<u32x4*>(to + c * KB * SA) = v;
-                }
-            } else {
-                *reinterpret_cast<u32x4*>(to) = areg[stg][t][0];
-            }
+    auto load_b = [&](int64_t r0, int bsel, int t) {
+        const auto buf = buffer_at(d.Bm + (row_lo + r0) * d.ldb);
+        auto to = (__attribute__((address_space(3))) unsigned char*)lds + 2 * ABUF + bsel * BBUF + (t * NTHR + wave * 64) * 16;
+        __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)to, 16,
+                                                 rb[t] < rows_left(r0) ? pb[t] : kNowhere, 0, 0, 0);
+    };
+    // register stage -> buffer BUF of A; of an interleaved piece the two m of group c, side by side with the other lanes'
+    auto store_a = [&](auto buf, int stg, int t, auto c) {
+        constexpr int C = decltype(c)::value, OFF = decltype(buf)::value * ABUF;
+        const u32x4& v = areg[stg][t];
+        if constexpr (DEINT) {
+            const uint32_t lo = v[C >> 1], hi = v[2 + (C >> 1)];
+            lds_put32<OFF + C * KB * TM * 2>(la[t], (C & 1) ? pick_hi16(lo, hi) : pick_lo16(lo, hi));
+        } else {
+            lds_put128<OFF>(la[t], v);
         }
+    };
+
+    // ---- fragments ----
+    // lane's address of run t of a row: the first row of a K-step is a multiple of 8, so the key depends on the lane alone
+    uint32_t aat[MTW], bat[NT];
+    {
+        const int G = lane >> 4, j = lane & 15, row = (MSPLIT ? 0 : 16 * kh) + 8 * (G >> 1) + (j >> 2);
+        const int in_run = 32 * (G & 1) + 8 * (j & 3);
 #pragma unroll
-        for (int t = 0; t < B_PER; ++t) *reinterpret_cast<u32x4*>(buf + lb[t]) = breg[stg][t];
+        for (int t = 0; t < MTW; ++t)
+            aat[t] = lds0 + (grp * KB + row) * TM * 2 + (((MSPLIT ? kh * MTW : 0) + t) ^ run_key<TM>(j >> 2)) * 64 + in_run;
+#pragma unroll
+        for (int t = 0; t < NT; ++t) bat[t] = lds0 + 2 * ABUF + (grp * KB + row) * TN * 2 + (t ^ run_key<TN>(j >> 2)) * 64 + in_run;
+    }
+    Frag fr[2][MTW + NT];
+    // half H of fragment I (MTW of A, then NT of B) of K-step K from buffer BUF of A and buffer `bsel` of B
+    auto read_half = [&](Frag (&f)[MTW + NT], auto buf, int bsel, auto kstep, auto i, auto half) {
+        constexpr int I = decltype(i)::value, H = decltype(half)::value, ROW = 16 * decltype(kstep)::value + 4 * H;
+        u32x2 v;
+        if constexpr (I < MTW) v = lds_tr16<decltype(buf)::value * ABUF + ROW * TM * 2>(aat[I]);
+        else v = lds_tr16<ROW * TN * 2>(bat[I - MTW] + bsel * BBUF);
+        (H ? f[I].hi : f[I].lo) = v;
+    };
+    constexpr int READS = 2 * (MTW + NT);
+    auto read = [&](Frag (&f)[MTW + NT], auto buf, int bsel, auto kstep, auto o) {
+        constexpr int O = decltype(o)::value;
+        read_half(f, buf, bsel, kstep, std::integral_constant<int, O / 2>{}, std::integral_constant<int, O % 2>{});
     };
 
     // column sums of A from the fragments of the products: eight rows of a feature per lane, a chain for each parity of the step
@@ -202,65 +239,88 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
 #pragma unroll
         for (int i = 0; i < 16; ++i) acc[t][i] = 0.f;
 
-    // Pipeline (one workgroup barrier per 32-row step, two LDS buffers, one register stage):
-    // in step s the MFMAs read buffer s%2 while the rows of step s+1 go from registers to buffer
-    // (s+1)%2 and the rows of step s+1+NSTG are fetched into the registers just freed.  A wave reads the
-    // fragments of its own K-step (rows 16*kh .. 16*kh+15 of the step) before the staging work, so that
-    // their LDS latency hides behind it.  The loop body has no branches (a step past the end of the
-    // chunk works on zeros): control flow here makes the compiler shuffle the accumulators between blocks.
-    if (nrows > 0) {  // (uniform) an empty chunk touches no memory and yields a zero partial tile
-    load_step(0, 0);
-    store_step(0, 0, lds);
-    load_step(KB, 1 % NSTG);
-    if constexpr (NSTG == 2) load_step(2 * KB, 0);
-    const int woff_a = grp * KB * SA, woff_b = 4 * KB * SA + grp * KB * SB;
-    for (int64_t r0 = 0; r0 < nrows; r0 += 2 * KB) {
-#pragma unroll
-        for (int k = 0; k < 2; ++k) {
-            const uint16_t* cur = lds + k * BUF;
-            uint16_t* nxt = lds + (k ^ 1) * BUF;
-            __syncthreads();
-            bf16x8 af[MTW], bfr[NT];
-            const int krow = MSPLIT ? 0 : 16 * kh, mcol = MSPLIT ? kh * MTW * 32 : 0;
-            if constexpr (MSPLIT) {
-                // large tiles: the next rows are requested first, so that they travel during the fragment reads too
-                store_step(r0 + (k + 1) * KB, (k + 1) % NSTG, nxt);
-                load_step(r0 + (k + 1 + NSTG) * KB, (k + 1) % NSTG);
-                __builtin_amdgcn_sched_barrier(0);
-            }
-#pragma unroll
-            for (int mt = 0; mt < MTW; ++mt) af[mt] = frag_tr(cur + woff_a, SA, krow, mcol + mt * 32, lane);
-#pragma unroll
-            for (int nt = 0; nt < NT; ++nt) bfr[nt] = frag_tr(cur + woff_b, SB, krow, nt * 32, lane);
+    // products of one K-step, with `count` other operations dealt out between them: an MFMA takes 32 cycles, in which the wave
+    // requests what comes next
+    auto multiply = [&](const Frag (&f)[MTW + NT], int k, auto count, auto op) {
+        constexpr int OPS = decltype(count)::value, TILES = MTW * NT;
+        each<TILES>([&](auto tile_no) {
+            constexpr int T = decltype(tile_no)::value;
+            acc[T] = mfma32(f[MTW + T % NT].operand(), f[T / NT].operand(), acc[T]);  // (transposed: a lane holds runs of n of one m)
+            if constexpr (SUMS && T % NT == 0) add_rows(cs[k][T / NT], f[T / NT].operand());
+            each<(T + 1) * OPS / TILES - T * OPS / TILES>([&](auto o) { op(std::integral_constant<int, decltype(o)::value + T * OPS / TILES>{}); });
             __builtin_amdgcn_sched_barrier(0);
-            if constexpr (!MSPLIT) {
-                store_step(r0 + (k + 1) * KB, (k + 1) % NSTG, nxt);
-                load_step(r0 + (k + 1 + NSTG) * KB, (k + 1) % NSTG);
-                __builtin_amdgcn_sched_barrier(0);
-            }
+        });
+    };
+
+    // Pipeline, one workgroup barrier per 32-row step s: past it the rows of step s+1 are in LDS for all waves and nobody reads
+    // those of step s any more.  While the products of step s run, the fragments of step s+1 are read, its A buffer's
+    // predecessor takes the rows of step s+2 from the registers, the B rows of step s+3 are requested into the buffer that B(s)
+    // left, and the A rows of step s+4 into the registers just freed: two steps for memory to answer.  (MSPLIT: a step is two
+    // K-steps, the fragments of the second are read during the products of the first, before the barrier.)  The loop body has
+    // no branches (a step past the end of the chunk works on zeros): control flow here makes the compiler shuffle the
+    // accumulators between blocks.
+    constexpr int AN = A_PER, BN = B_PER;  // load instructions of a step
+    constexpr int AW = DEINT ? 4 : 1;      // stores of a piece
+    using Zero = std::integral_constant<int, 0>;
+    using One = std::integral_constant<int, 1>;
+    if (nrows > 0) {  // (uniform) an empty chunk touches no memory and yields a zero partial tile
+    auto load_a_all = [&](int64_t r0, int stg) {
 #pragma unroll
-            for (int mt = 0; mt < MTW; ++mt)
+        for (int t = 0; t < A_PER; ++t) load_a(r0, stg, t);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto load_b_all = [&](int64_t r0, int bsel) {
 #pragma unroll
-                for (int nt = 0; nt < NT; ++nt) acc[mt * NT + nt] = mfma32(af[mt], bfr[nt], acc[mt * NT + nt]);
-            if constexpr (SUMS)
-#pragma unroll
-                for (int mt = 0; mt < MTW; ++mt) add_rows(cs[k][mt], af[mt]);
-            if constexpr (MSPLIT) {
-                // second K-step of the pipeline step (rows 16 .. 31 of the buffer)
-#pragma unroll
-                for (int mt = 0; mt < MTW; ++mt) af[mt] = frag_tr(cur + woff_a, SA, 16, mcol + mt * 32, lane);
-#pragma unroll
-                for (int nt = 0; nt < NT; ++nt) bfr[nt] = frag_tr(cur + woff_b, SB, 16, nt * 32, lane);
-#pragma unroll
-                for (int mt = 0; mt < MTW; ++mt)
-#pragma unroll
-                    for (int nt = 0; nt < NT; ++nt) acc[mt * NT + nt] = mfma32(af[mt], bfr[nt], acc[mt * NT + nt]);
-                if constexpr (SUMS)
-#pragma unroll
-                    for (int mt = 0; mt < MTW; ++mt) add_rows(cs[k][mt], af[mt]);
-            }
+        for (int t = 0; t < B_PER; ++t) load_b(r0, bsel, t);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto store_a_all = [&](auto buf, int stg) {
+        each<AN * AW>([&](auto o) { store_a(buf, stg, decltype(o)::value / AW, std::integral_constant<int, decltype(o)::value % AW>{}); });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load_a_all(0, 0);
+    load_b_all(0, 0);
+    load_a_all(KB, 1);
+    load_b_all(KB, 1);
+    store_a_all(Zero{}, 0);
+    load_a_all(2 * KB, 0);
+    load_b_all(2 * KB, 2);  // in the order of the loop, or the compiler waits there for too much
+    store_a_all(One{}, 1);
+    load_a_all(3 * KB, 1);
+    wait_vmcnt<3 * AN + 2 * BN>();  // B rows of step 0
+    lds_barrier();
+    each<READS>([&](auto o) { read(fr[0], Zero{}, 0, Zero{}, o); });
+    lgkm_wait(fr[0]);
+    int bsel = 0;  // buffer of the B rows of the step
+    auto step = [&](int64_t r0, auto par) {
+        constexpr int K = decltype(par)::value;
+        using Next = std::integral_constant<int, K ^ 1>;
+        const int bnext = bsel == 2 ? 0 : bsel + 1;
+        Frag (&now)[MTW + NT] = fr[MSPLIT ? 1 : K];        // multiplied past the barrier
+        Frag (&then)[MTW + NT] = fr[MSPLIT ? 0 : K ^ 1];   // read there
+        if constexpr (MSPLIT) {
+            multiply(then, K, std::integral_constant<int, READS>{}, [&](auto o) { read(now, par, bsel, One{}, o); });
+            lgkm_wait(now);
         }
+        // what was requested after the B rows of step s+1
+        wait_vmcnt<2 * AN + BN>();
+        lds_barrier();
+        multiply(now, K, std::integral_constant<int, READS + AN * AW + AN + BN>{}, [&](auto o) {
+            constexpr int O = decltype(o)::value, S = O - READS, L = S - AN * AW - BN;
+            if constexpr (S < 0) read(then, Next{}, bnext, Zero{}, o);
+            else if constexpr (S < AN * AW) store_a(par, K, S / AW, std::integral_constant<int, S % AW>{});
+            else if constexpr (L < 0) load_b(r0 + 3 * KB, bsel, S - AN * AW);
+            else load_a(r0 + 4 * KB, K, L);
+            __builtin_amdgcn_sched_barrier(0);
+        });
+        lgkm_wait(then);
+        bsel = bnext;
+    };
+    for (int64_t r0 = 0; r0 < nrows; r0 += 2 * KB) {
+        step(r0, Zero{});
+        step(r0 + KB, One{});
     }
+    wait_vmcnt<0>();  // nothing is on its way into LDS any more
     }
     auto store_sums = [&](int mt, float v) {
         if (lane < 32) d.colsum[(size_t)zi * d.lda + 4 * (m0 + (MSPLIT ? kh * MTW * 32 : 0) + mt * 32 + lane) + grp] = v;
@@ -274,71 +334,93 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
         }
     }
 
-    // sum the two K halves of every group through LDS (fp32, in two rounds of at most R1 tiles per
-    // wave: the staging buffers hold 4 x R1 tiles), then the kh = 0 wave owns the group's partial tile
-    if constexpr (!MSPLIT) {
-        constexpr int NTILE = MT * NT, R1 = (NTILE + 1) / 2;
-        static_assert((size_t)4 * R1 * 4096 <= (size_t)2 * BUF * 2, "reduction staging fits the pipeline buffers");
-        float* red = reinterpret_cast<float*>(lds) + (size_t)grp * R1 * 1024 + lane;
-        float* redc = reinterpret_cast<float*>(lds) + (size_t)4 * R1 * 1024 + grp * MT * 32 + (lane & 31);
-        static_assert(!SUMS || (size_t)4 * R1 * 4096 + 4 * MT * 128 <= (size_t)2 * BUF * 2, "and so do the column sums");
+    // Partial tiles P[z][g][m][n].  A lane holds, of each 32 x 32 tile, the m = lane % 32 and four n of every eight: the wave turns
+    // the tile through its own piece of LDS (4 KB) into rows of whole 16-byte stores.  (A 2-byte store per element instead: 0.8 us more at
+    // 768 -> 768, 12608 rows.)
+    const bool live = g0 + grp < d.G;  // (the group count need not be a multiple of four)
+    const int ln = lane & 31, h = lane >> 5;
+    const size_t pbase = (((size_t)zi * d.G + g0 + grp) * d.M) * d.N;
+    auto store_tile = [&](int mt, int nt, const f32x16& a, unsigned char* turn) {
+        const size_t at = pbase + (size_t)(m0 + (MSPLIT ? kh * MTW * 32 : 0) + mt * 32) * d.N + n0 + nt * 32;
+        if (d.p_bf16) {
 #pragma unroll
-        for (int t0 = 0; t0 < NTILE; t0 += R1) {
-            __syncthreads();  // the buffers (or the previous round) are no longer read
-            if (kh == 1) {
-                if constexpr (SUMS)
-                    if (t0 == 0)
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<u32x2*>(turn + ln * 80 + q * 16 + h * 8) =
+                    u32x2{pack_bf16x2(a[4 * q], a[4 * q + 1]), pack_bf16x2(a[4 * q + 2], a[4 * q + 3])};
+            __builtin_amdgcn_wave_barrier();
+            uint16_t* to = reinterpret_cast<uint16_t*>(d.P) + at + (size_t)(lane >> 2) * d.N + (lane & 3) * 8;
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) redc[mt * 32] = cs[0][mt];
-#pragma unroll
-                for (int t = t0; t < t0 + R1 && t < NTILE; ++t)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) red[(t - t0) * 1024 + i * 64] = acc[t][i];
+            for (int u = 0; u < 2; ++u) {
+                const u32x4 v = *reinterpret_cast<const u32x4*>(turn + ((lane >> 2) + 16 * u) * 80 + (lane & 3) * 16);
+                if (live) *reinterpret_cast<u32x4*>(to + (size_t)16 * u * d.N) = v;
             }
-            __syncthreads();
-            if (kh == 0) {
-                if constexpr (SUMS)
-                    if (t0 == 0)
+        } else {
 #pragma unroll
-                        for (int mt = 0; mt < MT; ++mt) store_sums(mt, cs[0][mt] + redc[mt * 32]);
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4*>(turn + ln * 128 + ((2 * q + h) ^ (ln & 7)) * 16) =
+                    f32x4{a[4 * q], a[4 * q + 1], a[4 * q + 2], a[4 * q + 3]};
+            __builtin_amdgcn_wave_barrier();
+            float* to = d.P + at + (size_t)(lane >> 3) * d.N + (lane & 7) * 4;
 #pragma unroll
-                for (int t = t0; t < t0 + R1 && t < NTILE; ++t)
-#pragma unroll
-                    for (int i = 0; i < 16; ++i) acc[t][i] += red[(t - t0) * 1024 + i * 64];
+            for (int u = 0; u < 4; ++u) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(turn + ((lane >> 3) + 8 * u) * 128 + ((lane & 7) ^ (lane >> 3)) * 16);
+                if (live) *reinterpret_cast<f32x4*>(to + (size_t)8 * u * d.N) = v;
             }
         }
-        if (kh != 0) return;
-    }
-    if (g0 + grp >= d.G) return;  // (the group count need not be a multiple of four)
-
-    // partial tile: P[z][g][m][n]
-    const int ln = lane & 31, h = lane >> 5;
-    const int mw = m0 + (MSPLIT ? kh * MTW * 32 : 0);  // first row of this wave's accumulators
-    const size_t pbase = (((size_t)zi * d.G + g0 + grp) * d.M) * d.N;
-    if (d.p_bf16) {
-        uint16_t* Pg = reinterpret_cast<uint16_t*>(d.P) + pbase;
+        __builtin_amdgcn_wave_barrier();
+    };
+    __syncthreads();  // the buffers are no longer read
+    if constexpr (MSPLIT) {
 #pragma unroll
-        for (int mt = 0; mt < MTW; ++mt)
+        for (int t = 0; t < MTW * NT; ++t)
+            store_tile(t / NT, t % NT, acc[t], reinterpret_cast<unsigned char*>(lds) + (wave * 2 + t % 2) * 4096);
+    } else {
+        // the two waves of a group hand each other half of their tiles (fp32), add and store the other half
+        constexpr int NTILE = MT * NT, R1 = (NTILE + 1) / 2;
+        float* red = reinterpret_cast<float*>(lds) + (size_t)grp * NTILE * 1024;
+        float* redc = reinterpret_cast<float*>(lds) + (size_t)4 * NTILE * 1024 + grp * MT * 32 + ln;
+        auto hand = [&](int t) {
 #pragma unroll
-            for (int nt = 0; nt < NT; ++nt)
+            for (int q = 0; q < 4; ++q)
+                *reinterpret_cast<f32x4*>(red + t * 1024 + q * 256 + lane * 4) =
+                    f32x4{acc[t][4 * q], acc[t][4 * q + 1], acc[t][4 * q + 2], acc[t][4 * q + 3]};
+        };
+        auto finish = [&](int t) {
 #pragma unroll
-                for (int i = 0; i < 16; ++i) {
-                    const int m = mw + mt * 32 + 8 * (i / 4) + 4 * h + (i % 4);
-                    Pg[(size_t)m * d.N + n0 + nt * 32 + ln] = (uint16_t)(pack_bf16x2(acc[mt * NT + nt][i], 0.f) & 0xffffu);
-                }
-        return;
-    }
-    float* Pg = d.P + pbase;
+            for (int q = 0; q < 4; ++q) {
+                const f32x4 v = *reinterpret_cast<const f32x4*>(red + t * 1024 + q * 256 + lane * 4);
 #pragma unroll
-    for (int mt = 0; mt < MTW; ++mt)
-#pragma unroll
-        for (int nt = 0; nt < NT; ++nt)
-#pragma unroll
-            for (int i = 0; i < 16; ++i) {
-                const int m = mw + mt * 32 + 8 * (i / 4) + 4 * h + (i % 4);
-                Pg[(size_t)m * d.N + n0 + nt * 32 + ln] = acc[mt * NT + nt][i];
+                for (int i = 0; i < 4; ++i) acc[t][4 * q + i] += v[i];
             }
+            __builtin_amdgcn_wave_barrier();
+            store_tile(t / NT, t % NT, acc[t], reinterpret_cast<unsigned char*>(red + t * 1024));
+        };
+        if (kh == 1) {
+            if constexpr (SUMS)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) redc[mt * 32] = cs[0][mt];
+#pragma unroll
+            for (int t = 0; t < R1; ++t) hand(t);
+        } else {
+#pragma unroll
+            for (int t = R1; t < NTILE; ++t) hand(t);
+        }
+        __syncthreads();
+        if (kh == 0) {
+            if constexpr (SUMS)
+#pragma unroll
+                for (int mt = 0; mt < MT; ++mt) store_sums(mt, cs[0][mt] + redc[mt * 32]);
+#pragma unroll
+            for (int t = 0; t < R1; ++t) finish(t);
+        } else {
+#pragma unroll
+            for (int t = R1; t < NTILE; ++t) finish(t);
+        }
+    }
 }
+
+// more accumulators than one wave of a pair can hold
+constexpr bool msplit(int tm, int tn) { return (tm / 32) * (tn / 32) > 9; }
 
 // One launch for up to two GEMMs over the same batch chunks.  Workgroups are handed to the
 // eight XCDs round-robin by linear id; the id is remapped so that each XCD owns a contiguous
@@ -352,7 +434,7 @@ wgrad_gemm_kernel(WgradDesc d0, WgradDesc d1, int tiles0, int tiles)
     const int per = nwg >> 3, rem = nwg & 7;
     const int v = xcd * per + (xcd < rem ? xcd : rem) + slot;
     const int t = v % tiles, zi = v / tiles;
-    constexpr bool MSPLIT = (TM / 32) * (TN / 32) > 9;  // more accumulators than one wave of a pair can hold
+    constexpr bool MSPLIT = msplit(TM, TN);
     if (t < tiles0) {
         if (d0.colsum && t % (d0.N / TN) == 0) wgrad_gemm_body<TM, TN, true, true, MSPLIT>(d0, t, zi);
         else if (d0.deint) wgrad_gemm_body<TM, TN, true, false, MSPLIT>(d0, t, zi);
@@ -454,9 +536,10 @@ int tiles_of(const WgradDesc& d, int tm, int tn) { return (d.M / tm) * (d.N / tn
 template <int TM, int TN>
 int launch_gemm(const WgradDesc& d0, const WgradDesc* d1, int nz, hipStream_t st)
 {
-    // two pipeline buffers; where not every thread has an A task, what the others store (four groups, 16 bytes per lane)
-    constexpr size_t surplus = KB * TM / 8 % NTHR != 0 ? (size_t)(3 * KB * (TM + lds_pad(TM)) + 512) * 2 : 0;
-    constexpr size_t lds = (size_t)2 * 4 * KB * (TM + lds_pad(TM) + TN + lds_pad(TN)) * 2 + surplus;
+    // two buffers of A, three of B; in their place at the end the tiles that two waves add up, and the column sums
+    constexpr size_t pipeline = (size_t)4 * KB * (2 * TM + 3 * TN) * 2;
+    constexpr size_t sums = msplit(TM, TN) ? 0 : (size_t)4 * ((TM / 32) * (TN / 32) * 4096 + TM * 4);
+    constexpr size_t lds = pipeline > sums ? pipeline : sums;
     static_assert(lds <= kMaxLdsBytes, "LDS");
     auto kern = wgrad_gemm_kernel<TM, TN>;
     if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess)
