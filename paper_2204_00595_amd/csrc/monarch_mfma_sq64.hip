@@ -25,16 +25,18 @@
 //
 // Backward (adjoints of steps 3, 2, P^T, 1; the paper leaves them to automatic differentiation,
 // Section 4):
-//   transpose   dW[b][c][l] = dy[b][l*64 + c]  (adjoint of step 3, a pure permutation) and the
-//               transposed weights LT[c][r][l], RT[kk][i][j]: batched 64 x 64 transposes.
-//   data        block stage (x, R) -> U to the workspace (dL needs it);
-//               block stage (dW, LT) -> dU[b][c][r] = dY1[b][r][c], exchanged like the forward
-//               intermediate and also copied to the workspace (dR needs it);
-//               column stage (RT) -> dx.
-//   wgrad       dL = sum_b dW (x) U and dR = sum_b dY1 (x) x as batch-contracted GEMMs with 64
-//               groups (monarch_mfma_wgrad.hip).
+//   u           block stage (x, R) -> U to the workspace (dL needs it)
+//   stage L     dy, U -> dU (to the workspace) and dL's partial sums
+//   stage R     dU, x -> dx and dR's partial sums        (both: bwd_sq64_stage_kernel)
+//   reduce      the sums over the batch chunks (monarch_mfma_wgrad.hip)
+// What bounds it: memory.  U, dU and the inputs are read and written 8 times in all (1.07 GB at 16384 rows); the transposed dy, dY1
+// and separate weight-gradient products that this replaced moved 1.47 GB (training step, 16384 rows: 379 -> 325 us; the backward
+// alone 311 -> 260, at 1000 rows 61 -> 52, at 64 rows 51 -> 43).
+// The transposed multiply transposes its input rows and runs both adjoint steps in one kernel.
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
+#include "monarch_mfma_stage1.h"
+#include "monarch_lds_tr.h"
 
 namespace monarch {
 
@@ -358,39 +360,21 @@ transpose64_kernel(const uint16_t* __restrict__ src, uint16_t* __restrict__ dst)
     }
 }
 
-// DX_ONLY: the transposed multiply y = x M on its own (dW is then the transposed input of that
-// product): no recompute of step 1, no workspace copies of the intermediates.
-template <bool DX_ONLY>
+// The transposed multiply y = x M on its own: both adjoint steps in one kernel (no copies of the vector between them).
 __global__ void __launch_bounds__(512)
-bwd_sq64_data_kernel(const uint16_t* __restrict__ dW, const uint16_t* __restrict__ x,
-                     const uint16_t* __restrict__ R /* packed */, const uint16_t* __restrict__ LT /* packed L^T */,
-                     const uint16_t* __restrict__ RT /* packed R^T */, uint16_t* __restrict__ dx,
-                     uint16_t* __restrict__ Uws, uint16_t* __restrict__ dY1ws, int64_t B)
+fwd_t_sq64_kernel(const uint16_t* __restrict__ dW, const uint16_t* __restrict__ LT /* packed L^T */,
+                  const uint16_t* __restrict__ RT /* packed R^T */, uint16_t* __restrict__ dx, int64_t B)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char ldsb[];
     const Lane t = make_lane();
-    const int ln = t.ln, g = t.g;
     const int64_t b0 = (int64_t)blockIdx.x * SQ_BM;
-    int64_t row = b0 + ln;
+    int64_t row = b0 + t.ln;
     row = row < B ? row : B - 1;
-
     u32x4 pk1[16];  // pk1[i][t]: one 16-byte exchange piece per i, filled component by component
-    // ---- recompute step 1; the exchange layout T[b][j][kk] is U[b][c = j][r = kk]: to the workspace
-    if constexpr (!DX_ONLY) {
-        block_stage<true>(t, x + row * N64 + 32 * g, R, ldsb, pk1);
-        __syncthreads();
-        copy_out<false>(t, ldsb, Uws, b0, B, 0);
-        __syncthreads();
-        exchange_write(t, ldsb, pk1);
-        __syncthreads();
-        copy_out<false>(t, ldsb, Uws, b0, B, 32);
-        __syncthreads();
-    }
 
     // ---- adjoint of step 2: dU[b][c][r] = sum_l LT[c][r][l] dW[b][c][l]; as dY1[b][kk = r][j = c]
-    // the exchange layout T[b][r][c] is dY1[b][kk][j]: operand order of the next stage, and the
-    // layout of the workspace copy
-    block_stage<true>(t, dW + row * N64 + 32 * g, LT, ldsb, pk1);
+    // the exchange layout T[b][r][c] is dY1[b][kk][j]: operand order of the next stage
+    block_stage<true>(t, dW + row * N64 + 32 * t.g, LT, ldsb, pk1);
 
     // ---- adjoint of step 1: dx[b][kk*64 + i] = sum_j RT[kk][i][j] dY1[b][kk][j], written over the dY1 lines (see
     // column_stage_inplace): line (b, kk) of the buffer becomes dx[b][kk*64 ..], which is also the layout of dx itself
@@ -398,10 +382,6 @@ bwd_sq64_data_kernel(const uint16_t* __restrict__ dW, const uint16_t* __restrict
     for (int h = 0; h < 2; ++h) {
         if (h) exchange_write(t, ldsb, pk1);
         __syncthreads();
-        if constexpr (!DX_ONLY) {
-            copy_out<false>(t, ldsb, dY1ws, b0, B, 32 * h);
-            __syncthreads();  // every wave has copied its share of the dY1 half before lines are overwritten
-        }
         column_stage_inplace(t, RT, ldsb, h);
         __syncthreads();
         copy_out<false, true>(t, ldsb, dx, b0, B, 32 * h);
@@ -409,47 +389,254 @@ bwd_sq64_data_kernel(const uint16_t* __restrict__ dW, const uint16_t* __restrict
     }
 }
 
-// batch chunks of the two weight-gradient GEMMs (64 groups each): about one workgroup per CU
-struct Plan64 {
-    size_t off_u, off_dy1, off_dw, off_lt, off_rt, off_rp, off_partL, off_partR, total;
-    int nz, rows_per_chunk;
-    bool ok;
-};
-
-void fill_descs64(const Problem& pb, WgradDesc& dl, WgradDesc& dr)
+// The vector between the factors for the backward: U[b][c][r] = Y1[b][kk = r][j = c], the exchange layout as it is.
+__global__ void __launch_bounds__(512)
+u_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R /* packed */, uint16_t* __restrict__ U, int64_t B)
 {
-    // dL[c][l][r] = sum_b dW[b][c][l] * U[b][c][r];   dR[kk][j][i] = sum_b dY1[b][kk][j] * x[b][kk][i]
-    dl = WgradDesc{};
-    dl.lda = N64; dl.a_g = M64; dl.deint = 0;
-    dl.ldb = N64; dl.b_g = M64; dl.b_seg = 0; dl.seg_w = M64;
-    dl.M = M64; dl.N = M64; dl.G = M64; dl.rows = pb.B;
-    dr = dl;
+    extern __shared__ __attribute__((aligned(16))) unsigned char ldsb[];
+    const Lane t = make_lane();
+    const int64_t b0 = (int64_t)blockIdx.x * SQ_BM;
+    int64_t row = b0 + t.ln;
+    row = row < B ? row : B - 1;
+    u32x4 pk1[16];
+    block_stage<true>(t, x + row * N64 + 32 * t.g, R, ldsb, pk1);
+    __syncthreads();
+    copy_out<false>(t, ldsb, U, b0, B, 0);
+    __syncthreads();
+    exchange_write(t, ldsb, pk1);
+    __syncthreads();
+    copy_out<false>(t, ldsb, U, b0, B, 32);
 }
+
+// One factor of the backward, the gradients of its input and of its weights together: with its 64 blocks W[c] (64 x 64),
+//     out[b][64 c + r] = sum_l in[b][64 l + c] W[c][l][r],     dW[c][l][r] = sum_b in[b][64 l + c] other[b][64 c + r].
+//   L:  in = dy, other = U (as u_sq64_kernel leaves it), out = dU
+//   R:  in = dU, other = x, out = dx  (dU[b][64 j + kk] is dY1[b][kk][j]: the permutation between the factors is again a
+//       column of every block, so that both launches are the same kernel on what the one before wrote)
+// Workgroup = eight blocks c0 .. c0+7 and every nz-th 32 rows of the batch, wave = one block: W[c] in registers as the operand of the first
+// product, dW[c] in registers as the sum of the second.  A step is 32 rows.  `in` comes in pieces of eight c (16 bytes of every
+// 128-byte line; the workgroups of the other c read the rest of the lines at about the same time on the same XCD), is turned to
+// [c][row][l] in registers and LDS and read twice, as rows for `out` and transposed for dW; the wave's columns of `other` travel
+// straight into an LDS ring of its own.  One barrier per step, rows requested two (in) and three (other) steps ahead.
+// At 16384 rows 95 us, 402 MB at 4.2 TB/s; the pieces of `in` cost eight times their bytes between L2 and L1, which is why
+// eight blocks share a workgroup and not fewer.  All workgroups walk the batch together, the first launch from its end, so that each
+// finds in the memory-side cache what the launch before wrote last (both stages with chunks of consecutive rows: 334 us against 325
+// for the training step).
+constexpr int ST_ROWS = 32;
+constexpr int ST_IN = 8 * ST_ROWS * 128;     // bytes of a step's `in`: two buffers
+constexpr int ST_RING = 3 * ST_ROWS * 128;   // a wave's ring of `other`
+constexpr size_t ST_LDS = 2 * ST_IN + 8 * ST_RING;
+static_assert(ST_LDS <= kMaxLdsBytes, "LDS");
+struct Stage64 {
+    const uint16_t *in, *W, *other;
+    uint16_t* out;
+    void* P;  // partial dW[chunk][c][l][r], fp32 or bf16
+    int p_bf16, nz, steps, down;
+    int64_t B;
+};
+__global__ void __launch_bounds__(512)
+bwd_sq64_stage_kernel(const Stage64 a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char ldsb[];
+    const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
+    // a chunk's eight workgroups on one XCD (workgroups go to the eight XCDs in turn)
+    const int nwg = gridDim.x, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per = nwg >> 3;  // (a multiple of eight)
+    const int v = xcd * per + slot, zi = v >> 3, cg = v & 7, c = cg * 8 + wave;
+    const uint32_t lds0 = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) void*)ldsb;
+    const uint32_t ring = lds0 + 2 * ST_IN + wave * ST_RING;
+
+    // the rows of a step: reads past the last one give zeros, writes are dropped (their offsets, all in the lane's
+    // own, which is what the range check looks at, lie past the buffer's end)
+    auto rows_at = [&](const uint16_t* p, int s) {
+        const int64_t row = ((int64_t)(a.down ? a.steps - 1 - s : s) * a.nz + zi) * ST_ROWS;
+        const int n = s >= a.steps || row >= a.B ? 0 : a.B - row < ST_ROWS ? (int)(a.B - row) : ST_ROWS;
+        return __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(p) + row * N64, 0, n * N64 * 2, 0x00020000);
+    };
+    // `in`: thread = (row, l = 4 quad ..), four pieces of eight c
+    const int irow = tid >> 4, quad = tid & 15;
+    const uint32_t in_at = (uint32_t)(irow * N64 * 2 + quad * 512 + cg * 16);
+    const uint32_t in_put = lds0 + irow * 128 + ((quad >> 3) ^ run_key<64>(irow)) * 64 + (quad & 7) * 8;
+    u32x4 stage[2][4];
+    auto load_in = [&](int s, int stg) {
+        const auto buf = rows_at(a.in, s);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) stage[stg][e] = __builtin_amdgcn_raw_buffer_load_b128(buf, in_at + e * 128, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto store_in = [&](auto par) {
+        constexpr int K = decltype(par)::value;
+        const u32x4(&p)[4] = stage[K];
+        each<8>([&](auto cc) {
+            constexpr int C = decltype(cc)::value, w = C >> 1;
+            u32x2 d;
+            if constexpr (C & 1) d = u32x2{pick_hi16(p[0][w], p[1][w]), pick_hi16(p[2][w], p[3][w])};
+            else d = u32x2{pick_lo16(p[0][w], p[1][w]), pick_lo16(p[2][w], p[3][w])};
+            lds_put64<K * ST_IN + C * ST_ROWS * 128>(in_put, d);
+        });
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // rows of 64 features: eight lanes a row; what a lane's place holds of the row (8 rows further: the same)
+    const int prow = lane >> 3, piece = (((lane & 7) >> 2) ^ run_key<64>(prow)) * 4 + (lane & 3);
+    const uint32_t other_at = (uint32_t)(prow * N64 * 2 + c * 128 + piece * 16);
+    auto load_other = [&](int s, int rsel) {
+        const auto buf = rows_at(a.other, s);
+        auto to = (__attribute__((address_space(3))) unsigned char*)ldsb + 2 * ST_IN + wave * ST_RING + rsel * (ST_ROWS * 128);
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(buf, (__attribute__((address_space(3))) void*)(to + n * 1024), 16,
+                                                     other_at + n * 8 * N64 * 2, 0, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // transposed operands: lane's address of run t of a row (see monarch_lds_tr.h)
+    const int G = lane >> 4, j = lane & 15;
+    const uint32_t tr = (8 * (G >> 1) + (j >> 2)) * 128 + 32 * (G & 1) + 8 * (j & 3);
+    const uint32_t tr_at[2] = {tr + run_key<64>(j >> 2) * 64, tr + (1 ^ run_key<64>(j >> 2)) * 64};
+    const uint32_t in_line = lds0 + wave * (ST_ROWS * 128) + ln * 128;
+    const uint32_t in_rd[2] = {in_line + run_key<64>(ln) * 64 + h * 16, in_line + (1 ^ run_key<64>(ln)) * 64 + h * 16};
+
+    load_other(0, 0);
+    load_in(0, 0);
+    load_other(1, 1);
+    load_in(1, 1);
+    load_other(2, 2);
+    // W[c], turned by way of the wave's eighth of the `in` buffers: operand [r][l], r = 32 t + lane % 32, K-step u
+    Frag wf[8];
+    {
+        const uint32_t at = lds0 + wave * 8192;
+        u32x4 g[8];
+#pragma unroll
+        for (int n = 0; n < 8; ++n) g[n] = ldg128(a.W + (size_t)c * 4096 + (n * 8 + prow) * 64 + piece * 8);
+        each<8>([&](auto n) { lds_put128<decltype(n)::value * 1024>(at + lane * 16, g[decltype(n)::value]); });
+        each<16>([&](auto o) {
+            constexpr int O = decltype(o)::value, T = O >> 3, U = (O >> 1) & 3, H = O & 1;
+            const u32x2 d = lds_tr16<U * 2048 + H * 512>(at + tr_at[T]);
+            (H ? wf[T * 4 + U].hi : wf[T * 4 + U].lo) = d;
+        });
+        lgkm_wait(wf);
+    }
+    lds_barrier();
+
+    f32x16 dw[2][2];
+#pragma unroll
+    for (int t = 0; t < 4; ++t)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) dw[t >> 1][t & 1][i] = 0.f;
+    int rsel = 0;  // ring place of the step's `other`
+    auto step = [&](int s, auto par) {
+        constexpr int K = decltype(par)::value;
+        store_in(par);
+        load_in(s + 2, K);
+        // the step's `other` was requested before its `in`, which is in the registers stored above
+        wait_vmcnt<24>();
+        lds_barrier();
+        const uint32_t oat = ring + rsel * (ST_ROWS * 128);
+        u32x4 rows[4];
+        Frag it[4], ot[4];  // [tile of 32 features][K-step]
+        each<4>([&](auto u) {
+            constexpr int U = decltype(u)::value;
+            rows[U] = lds_get128<K * ST_IN + (U & 1) * 32>(in_rd[U >> 1]);
+        });
+        each<8>([&](auto o) {
+            constexpr int O = decltype(o)::value, T = O >> 2, U = (O >> 1) & 1, H = O & 1;
+            const u32x2 d = lds_tr16<K * ST_IN + U * 2048 + H * 512>(lds0 + wave * (ST_ROWS * 128) + tr_at[T]);
+            const u32x2 e = lds_tr16<U * 2048 + H * 512>(oat + tr_at[T]);
+            (H ? it[T * 2 + U].hi : it[T * 2 + U].lo) = d;
+            (H ? ot[T * 2 + U].hi : ot[T * 2 + U].lo) = e;
+        });
+        lgkm_wait(rows);
+        lgkm_wait(it);
+        lgkm_wait(ot);
+        __builtin_amdgcn_sched_barrier(0);
+        f32x16 o2[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+#pragma unroll
+            for (int i = 0; i < 16; ++i) o2[t][i] = 0.f;
+#pragma unroll
+            for (int u = 0; u < 4; ++u) o2[t] = mfma32(wf[t * 4 + u].operand(), as_bf16x8(rows[u]), o2[t]);
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u)
+#pragma unroll
+            for (int t = 0; t < 4; ++t)
+                dw[t >> 1][t & 1] = mfma32(ot[(t & 1) * 2 + u].operand(), it[(t >> 1) * 2 + u].operand(), dw[t >> 1][t & 1]);
+        // out: lane = row, runs of four r; turned to whole lines in the ring place that was just read
+        each<8>([&](auto o) {
+            constexpr int T = decltype(o)::value >> 2, Q = decltype(o)::value & 3;
+            lds_put64<0>(oat + ln * 128 + (((4 * T + Q) ^ (ln & 7)) * 16) + h * 8,
+                         u32x2{pack_bf16x2(o2[T][4 * Q], o2[T][4 * Q + 1]), pack_bf16x2(o2[T][4 * Q + 2], o2[T][4 * Q + 3])});
+        });
+        u32x4 line[4];
+        each<4>([&](auto n) {
+            constexpr int N = decltype(n)::value;
+            line[N] = lds_get128<N * 1024>(oat + prow * 128 + (((lane & 7) ^ prow) * 16));
+        });
+        lgkm_wait(line);
+        const auto buf = rows_at(a.out, s);
+#pragma unroll
+        for (int n = 0; n < 4; ++n)
+            __builtin_amdgcn_raw_buffer_store_b128(line[n], buf, (uint32_t)((prow + 8 * n) * N64 * 2 + c * 128 + (lane & 7) * 16), 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+        load_other(s + 3, rsel);
+        rsel = rsel == 2 ? 0 : rsel + 1;
+    };
+    for (int s = 0; s < a.steps; s += 2) {
+        step(s, std::integral_constant<int, 0>{});
+        step(s + 1, std::integral_constant<int, 1>{});
+    }
+    wait_vmcnt<0>();  // nothing is on its way into LDS any more
+
+    // partial dW: lane = l, runs of four r; the wave turns its 32 x 32 tiles in its ring
+    const size_t base = ((size_t)zi * 64 + c) * 4096;
+    each<4>([&](auto t4) {
+        constexpr int T = decltype(t4)::value;
+        const f32x16& d = dw[T >> 1][T & 1];
+        const uint32_t at = ring + (T & 1) * 4096;
+        const size_t tile = base + (T >> 1) * 32 * 64 + (T & 1) * 32;
+        if (a.p_bf16) {
+            u32x4 line[2];
+            each<4>([&](auto q) {
+                constexpr int Q = decltype(q)::value;
+                lds_put64<Q * 16>(at + ln * 80 + h * 8, u32x2{pack_bf16x2(d[4 * Q], d[4 * Q + 1]), pack_bf16x2(d[4 * Q + 2], d[4 * Q + 3])});
+            });
+            each<2>([&](auto n) { line[decltype(n)::value] = lds_get128<decltype(n)::value * 16 * 80>(at + (lane >> 2) * 80 + (lane & 3) * 16); });
+            lgkm_wait(line);
+            uint16_t* to = (uint16_t*)a.P + tile + (lane >> 2) * 64 + (lane & 3) * 8;
+#pragma unroll
+            for (int n = 0; n < 2; ++n) *reinterpret_cast<u32x4*>(to + n * 16 * 64) = line[n];
+        } else {
+            u32x4 line[4];
+            each<4>([&](auto q) {
+                constexpr int Q = decltype(q)::value;
+                lds_put128<0>(at + ln * 128 + ((2 * Q + h) ^ (ln & 7)) * 16,
+                              __builtin_bit_cast(u32x4, f32x4{d[4 * Q], d[4 * Q + 1], d[4 * Q + 2], d[4 * Q + 3]}));
+            });
+            each<4>([&](auto n) { line[decltype(n)::value] = lds_get128<decltype(n)::value * 1024>(at + prow * 128 + (((lane & 7) ^ prow) * 16)); });
+            lgkm_wait(line);
+            float* to = (float*)a.P + tile + prow * 64 + (lane & 7) * 4;
+#pragma unroll
+            for (int n = 0; n < 4; ++n) *reinterpret_cast<u32x4*>(to + n * 8 * 64) = line[n];
+        }
+    });
+}
+
+// Batch chunks of the two stages: with the eight workgroups of a chunk about one per CU, at least two steps of 32 rows each.
+struct Plan64 {
+    size_t off_u, off_du, off_rp, off_partL, off_partR, total;
+    int nz, steps;
+};
 
 Plan64 make_plan64(const Problem& pb)
 {
     Plan64 pl{};
-    WgradDesc dl, dr;
-    fill_descs64(pb, dl, dr);
-    const int tiles = wgrad_tiles(dl) + wgrad_tiles(dr);
-    pl.ok = wgrad_tiles(dl) > 0 && wgrad_tiles(dr) > 0;
-    if (!pl.ok) return pl;
-    int64_t z = 256 / tiles;  // at most one workgroup per CU: its two LDS buffers leave room for one only
-    const int64_t maxz = (pb.B + 255) / 256;
-    if (z > maxz) z = maxz;
-    if (z < 1) z = 1;
-    const int64_t rpc = ((pb.B + z - 1) / z + 63) / 64 * 64;  // whole pipeline rounds (two 32-row steps)
-    pl.rows_per_chunk = (int)(rpc > 0 ? rpc : 32);
-    pl.nz = (int)((pb.B + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
-    if (pl.nz < 1) pl.nz = 1;
+    const int64_t steps = (pb.B + ST_ROWS - 1) / ST_ROWS;
+    pl.nz = (int)(steps > 64 ? 32 : steps > 2 ? steps / 2 : 1);
+    pl.steps = (int)((steps + pl.nz - 1) / pl.nz);
     size_t off = 0;
     const size_t act = align_up((size_t)(pb.B > 0 ? pb.B : 1) * N64 * 2, 256);
-    pl.off_u = off;   off += act;
-    pl.off_dy1 = off; off += act;
-    pl.off_dw = off;  off += act;
-    pl.off_lt = off;  off += align_up(pb.n_L() * 2, 256);
-    pl.off_rt = off;  off += align_up(pb.n_R() * 2, 256);
-    pl.off_rp = off;  off += align_up(pb.n_R() * 2, 256);
+    pl.off_u = off;  off += act;
+    pl.off_du = off; off += act;
+    pl.off_rp = off; off += align_up(pb.n_R() * 2, 256);
     pl.off_partL = off; off += align_up((size_t)pl.nz * pb.n_L() * 4, 256);
     pl.off_partR = off; off += align_up((size_t)pl.nz * pb.n_R() * 4, 256);
     pl.total = off;
@@ -499,7 +686,7 @@ int fwd_sq64_ws(const Problem& pb, const void* x, const void* R, const void* L, 
     return hip_status(hipGetLastError());
 }
 
-bool bwd_sq64_supported(const Problem& pb) { return sq64_supported(pb) && make_plan64(pb).ok; }
+bool bwd_sq64_supported(const Problem& pb) { return sq64_supported(pb); }
 
 // Transposed multiply: input rows re-laid [c][l] (one pass), L^T and R^T packed, then the dx stages.
 size_t fwd_t_sq64_workspace(const Problem& pb)
@@ -520,11 +707,9 @@ int fwd_t_sq64(const Problem& pb, const void* x, const void* R, const void* L, v
     hipLaunchKernelGGL(pack64_kernel, dim3(2 * 128), dim3(256), 0, st, jlt, jrt, jrt);
     hipLaunchKernelGGL(transpose64_kernel, dim3((unsigned)pb.B), dim3(256), 0, st, (const uint16_t*)x, xT);
     if (hipGetLastError() != hipSuccess) return -4;
-    auto kern = bwd_sq64_data_kernel<true>;
-    if (allow_dynamic_lds((const void*)kern, SQ_LDS) != hipSuccess)
+    if (allow_dynamic_lds((const void*)fwd_t_sq64_kernel, SQ_LDS) != hipSuccess)
         return -4;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), SQ_LDS, st, xT, (const uint16_t*)nullptr,
-                       (const uint16_t*)nullptr, LT, RT, (uint16_t*)y, (uint16_t*)nullptr, (uint16_t*)nullptr, pb.B);
+    hipLaunchKernelGGL(fwd_t_sq64_kernel, dim3((unsigned)grid), dim3(512), SQ_LDS, st, xT, LT, RT, (uint16_t*)y, pb.B);
     return hip_status(hipGetLastError());
 }
 
@@ -535,7 +720,6 @@ int bwd_sq64(const Problem& pb, const void* dy, const void* x, const void* R, co
 {
     if (!sq64_supported(pb)) return -2;
     const Plan64 pl = make_plan64(pb);
-    if (!pl.ok) return -2;
     const bool f32out = pb.wgrad_f32();
     if (pb.B == 0) {
         int rc = f32out ? launch_fill_zero_f32((float*)dR, pb.n_R(), st) : launch_fill_zero_u16((uint16_t*)dR, pb.n_R(), st);
@@ -545,31 +729,28 @@ int bwd_sq64(const Problem& pb, const void* dy, const void* x, const void* R, co
     const int64_t grid = (pb.B + SQ_BM - 1) / SQ_BM;
     if (grid > 0x7fffffffLL || pb.B > 0x7fffffffLL) return -2;
     char* w = (char*)ws;
-    uint16_t* Uws = (uint16_t*)(w + pl.off_u);
-    uint16_t* dY1ws = (uint16_t*)(w + pl.off_dy1);
-    uint16_t* dWws = (uint16_t*)(w + pl.off_dw);
-    uint16_t* LT = (uint16_t*)(w + pl.off_lt);
-    uint16_t* RT = (uint16_t*)(w + pl.off_rt);
+    uint16_t* U = (uint16_t*)(w + pl.off_u);
+    uint16_t* dU = (uint16_t*)(w + pl.off_du);
     uint16_t* Rp = (uint16_t*)(w + pl.off_rp);
-    const Pack64Job jr{(const uint16_t*)R, Rp, 0}, jlt{(const uint16_t*)L, LT, 1}, jrt{(const uint16_t*)R, RT, 1};
-    hipLaunchKernelGGL(pack64_kernel, dim3(3 * 128), dim3(256), 0, st, jr, jlt, jrt);
-    hipLaunchKernelGGL(transpose64_kernel, dim3((unsigned)pb.B), dim3(256), 0, st, (const uint16_t*)dy, dWws);
-    if (hipGetLastError() != hipSuccess) return -4;
-    auto kern = bwd_sq64_data_kernel<false>;
-    if (allow_dynamic_lds((const void*)kern, SQ_LDS) != hipSuccess)
+    if (allow_dynamic_lds((const void*)u_sq64_kernel, SQ_LDS) != hipSuccess ||
+        allow_dynamic_lds((const void*)bwd_sq64_stage_kernel, ST_LDS) != hipSuccess)
         return -4;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), SQ_LDS, st, dWws, (const uint16_t*)x, Rp, LT, RT,
-                       (uint16_t*)dx, Uws, dY1ws, pb.B);
+    const Pack64Job jr{(const uint16_t*)R, Rp, 0};
+    hipLaunchKernelGGL(pack64_kernel, dim3(128), dim3(256), 0, st, jr, jr, jr);
+    hipLaunchKernelGGL(u_sq64_kernel, dim3((unsigned)grid), dim3(512), SQ_LDS, st, (const uint16_t*)x, Rp, U, pb.B);
     if (hipGetLastError() != hipSuccess) return -4;
-
-    WgradDesc dl, dr;
-    fill_descs64(pb, dl, dr);
-    dl.A = dWws; dl.Bm = Uws; dl.P = (float*)(w + pl.off_partL); dl.out = dL;
-    dr.A = dY1ws; dr.Bm = (const uint16_t*)x; dr.P = (float*)(w + pl.off_partR); dr.out = dR;
-    dl.rows_per_chunk = dr.rows_per_chunk = pl.rows_per_chunk;
-    dl.p_bf16 = dr.p_bf16 = f32out ? 0 : 1;  // bf16 gradients: bf16 partial tiles
-    int rc = wgrad_gemm_pair(dl, dr, pl.nz, st);
-    if (rc) return rc;
+    WgradDesc dl{}, dr{};
+    dl.M = dl.N = dl.G = M64; dl.seg_w = M64;
+    // bf16 gradients: bf16 partial sums, but beyond 256 rows only (up to there the chunks of 64 rows would add a rounding)
+    dl.p_bf16 = f32out || pb.B <= 256 ? 0 : 1;
+    dr = dl;
+    dl.P = (float*)(w + pl.off_partL); dl.out = dL;
+    dr.P = (float*)(w + pl.off_partR); dr.out = dR;
+    const Stage64 sl{(const uint16_t*)dy, (const uint16_t*)L, U, dU, dl.P, dl.p_bf16, pl.nz, pl.steps, 1, pb.B};
+    const Stage64 sr{dU, (const uint16_t*)R, (const uint16_t*)x, (uint16_t*)dx, dr.P, dr.p_bf16, pl.nz, pl.steps, 0, pb.B};
+    hipLaunchKernelGGL(bwd_sq64_stage_kernel, dim3((unsigned)(8 * pl.nz)), dim3(512), ST_LDS, st, sl);
+    hipLaunchKernelGGL(bwd_sq64_stage_kernel, dim3((unsigned)(8 * pl.nz)), dim3(512), ST_LDS, st, sr);
+    if (hipGetLastError() != hipSuccess) return -4;
     return wgrad_reduce_pair(dl, dr, f32out, pl.nz, st);
 }
 

@@ -30,10 +30,10 @@
 // that did it beside the weights' re-layout 26.9 + 11.6 -> 6.0 + 5.6, the two launches of products 153 -> 160; 768 -> 768, 12608
 // rows: 6.3 -> 3.0 against 24.2 -> 24.8).  The sums are off float64 by 2.8e-8 (12608 rows), those of that pass were by 6.3e-8.
 #include <type_traits>
-#include <utility>
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
 #include "monarch_mfma_stage1.h"
+#include "monarch_lds_tr.h"
 #include "monarch_colsum.h"
 
 namespace monarch {
@@ -50,59 +50,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
 {
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffffu, 0x00020000);
 }
-
-// A row of TW features of one group is TW / 32 runs of 64 bytes in LDS, unpadded.  Half a wave of a transposing read touches one run
-// of four consecutive rows, which must fall on disjoint quarters of the 64 banks: the runs of a row change places by the row (strides
-// of one or three runs do it by themselves).
-template <int TW>
-__device__ __forceinline__ constexpr int run_key(int row)
-{
-    return TW == 128 ? row & 3 : TW == 64 ? (row >> 1) & 1 : 0;
-}
-// The LDS accesses of the pipeline are written out, and the wave waits for them by itself (lgkm_wait): the compiler puts a wait for
-// everything that is on its way into LDS (buffer_load ... lds) before a transposing read it knows of.
-// Transposing read: within each 16 lanes, lane i receives element (i % 4) of lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4.
-template <int OFF>
-__device__ __forceinline__ u32x2 lds_tr16(uint32_t at)
-{
-    static_assert(OFF >= 0 && OFF < 65536, "offset field");
-    u32x2 v;
-    asm volatile("ds_read_b64_tr_b16 %0, %1 offset:%2" : "=v"(v) : "v"(at), "n"(OFF));
-    return v;
-}
-template <int OFF>
-__device__ __forceinline__ void lds_put32(uint32_t at, uint32_t v)
-{
-    static_assert(OFF >= 0 && OFF < 65536, "offset field");
-    asm volatile("ds_write_b32 %0, %1 offset:%2" : : "v"(at), "v"(v), "n"(OFF));
-}
-template <int OFF>
-__device__ __forceinline__ void lds_put128(uint32_t at, const u32x4& v)
-{
-    static_assert(OFF >= 0 && OFF < 65536, "offset field");
-    asm volatile("ds_write_b128 %0, %1 offset:%2" : : "v"(at), "v"(v), "n"(OFF));
-}
-// An MFMA operand (32 features x 16 batch rows) on its way from LDS: lane (f = lane % 32, h = lane / 32) gets rows 8h .. 8h+7 of
-// feature f, four of them in each half.
-struct Frag {
-    u32x2 lo, hi;
-    __device__ __forceinline__ bf16x8 operand() const { return as_bf16x8(u32x4{lo[0], lo[1], hi[0], hi[1]}); }
-};
-template <int N>
-__device__ __forceinline__ void lgkm_wait(Frag (&f)[N])
-{
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-#pragma unroll
-    for (int i = 0; i < N; ++i) asm volatile("" : "+v"(f[i].lo), "+v"(f[i].hi));
-}
-template <int... I, typename F>
-__device__ __forceinline__ void each_of(std::integer_sequence<int, I...>, F f)
-{
-    (f(std::integral_constant<int, I>{}), ...);
-}
-// f(0) .. f(N - 1), the numbers as constants
-template <int N, typename F>
-__device__ __forceinline__ void each(F f) { each_of(std::make_integer_sequence<int, N>{}, f); }
 
 // MSPLIT = false: the two waves of a group split the K-steps (each keeps the whole TM x TN tile, summed at the end);
 // MSPLIT = true (large tiles): they split the tile's rows m instead, each taking both K-steps of a pipeline step on
@@ -445,9 +392,22 @@ wgrad_gemm_kernel(WgradDesc d0, WgradDesc d1, int tiles0, int tiles)
     }
 }
 
+// add(z, count) over 0 .. nz-1, eight at a time, then four, then one
+template <typename F>
+__device__ __forceinline__ void for_chunks(int nz, F add)
+{
+    int z = 0;
+    for (; z + 8 <= nz; z += 8) add(z, std::integral_constant<int, 8>{});
+    if (z + 4 <= nz) {
+        add(z, std::integral_constant<int, 4>{});
+        z += 4;
+    }
+    for (; z < nz; ++z) add(z, std::integral_constant<int, 1>{});
+}
+
 // out[g][m][col(n)] = sum_z P[z][g][m][n];  col(n) = (n % seg_w) * (N / seg_w) + n / seg_w
 // (identity when seg_w == N).  Blocks [0, blocks0) reduce d0, the rest d1; eight consecutive elements per
-// thread (16-byte loads of bf16 partial tiles, two 16-byte loads of fp32 ones), four chunks in flight.
+// thread (16-byte loads of bf16 partial tiles, two 16-byte loads of fp32 ones), eight chunks in flight.
 // Blocks from `blocks01` on (when cj.part is set) run the second pass of the bias gradient instead.
 template <bool OUT_F32>
 __global__ void __launch_bounds__(256)
@@ -464,46 +424,36 @@ wgrad_reduce_kernel(WgradDesc d0, WgradDesc d1, int blocks0, int nz, ColsumJob c
     const size_t e = ((size_t)(blockIdx.x - (first ? 0 : blocks0)) * 256 + threadIdx.x) * 8;
     if (e >= total) return;
     float s[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-    int z = 0;
     if (d.p_bf16) {
         const uint16_t* P = reinterpret_cast<const uint16_t*>(d.P) + e;
-        for (; z + 4 <= nz; z += 4) {
-            u32x4 v[4];
+        auto add = [&](int z, auto count) {
+            u32x4 v[decltype(count)::value];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) v[u] = ldg128(P + (size_t)(z + u) * total);
+            for (int u = 0; u < decltype(count)::value; ++u) v[u] = ldg128(P + (size_t)(z + u) * total);
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < decltype(count)::value; ++u)
 #pragma unroll
                 for (int w = 0; w < 4; ++w) {
                     s[2 * w] += __uint_as_float(v[u][w] << 16);
                     s[2 * w + 1] += __uint_as_float(v[u][w] & 0xffff0000u);
                 }
-        }
-        for (; z < nz; ++z) {
-            const u32x4 v = ldg128(P + (size_t)z * total);
-#pragma unroll
-            for (int w = 0; w < 4; ++w) {
-                s[2 * w] += __uint_as_float(v[w] << 16);
-                s[2 * w + 1] += __uint_as_float(v[w] & 0xffff0000u);
-            }
-        }
+        };
+        for_chunks(nz, add);
     } else {
         const float* P = d.P + e;
-        for (; z + 4 <= nz; z += 4) {
-            f32x4 v[4][2];
+        auto add = [&](int z, auto count) {
+            f32x4 v[decltype(count)::value][2];
 #pragma unroll
-            for (int u = 0; u < 4; ++u) {
+            for (int u = 0; u < decltype(count)::value; ++u) {
                 v[u][0] = *reinterpret_cast<const f32x4*>(P + (size_t)(z + u) * total);
                 v[u][1] = *reinterpret_cast<const f32x4*>(P + (size_t)(z + u) * total + 4);
             }
 #pragma unroll
-            for (int u = 0; u < 4; ++u)
+            for (int u = 0; u < decltype(count)::value; ++u)
 #pragma unroll
                 for (int w = 0; w < 8; ++w) s[w] += v[u][w >> 2][w & 3];
-        }
-        for (; z < nz; ++z)
-#pragma unroll
-            for (int w = 0; w < 8; ++w) s[w] += P[(size_t)z * total + w];
+        };
+        for_chunks(nz, add);
     }
     // the eight elements share a row and (seg_w being a multiple of 8) a segment: their outputs are nseg apart
     const int nseg = d.N / d.seg_w;
