@@ -38,10 +38,11 @@ namespace {
 //   LF[kk][c][kt][jt][lane][e]   = L[c][32*kt + 8*(lane/16) + e][4*(16*jt + lane%16) + kk]
 //       (dY1 stage, 16x16x32: L transposed, rows picked as the mid permutation scatters them)
 //   RF[kk][ig][u][it][lane][e]   = R[kk][32*u + 16*(e/4) + 4*(lane/16) + e%4][16*(ig*IG + it) + lane%16]
-//       (dx stage, 16x16x32: R transposed, K-slots in the order the chained accumulators hold dY1)
+//       (dx stage, 16x16x32: R transposed, K-slots in the order the chained accumulators hold dY1; for the kernel that reads dY1
+//       from LDS in the natural order, R[kk][32*u + 8*(lane/16) + e][..])
 __global__ void __launch_bounds__(256)
 prep_frag_kernel(const uint16_t* __restrict__ L, const uint16_t* __restrict__ R, uint16_t* __restrict__ XF,
-                 uint16_t* __restrict__ LF, uint16_t* __restrict__ RF, int P, int Q, int S, int JG, int IG)
+                 uint16_t* __restrict__ LF, uint16_t* __restrict__ RF, int P, int Q, int S, int IG, bool chained)
 {
     const int nR = 4 * Q * P / 8, nL = 4 * S * Q / 8;  // pieces per array
     int pc = blockIdx.x * 256 + threadIdx.x;
@@ -79,9 +80,10 @@ prep_frag_kernel(const uint16_t* __restrict__ L, const uint16_t* __restrict__ R,
         const int u = rest % U; rest /= U;
         const int nig = P / 16 / IG;
         const int ig = rest % nig, kk = rest / nig;
-        const uint16_t* src = R + ((size_t)kk * Q + 32 * u + 4 * (lane >> 4)) * P + 16 * (ig * IG + it) + (lane & 15);
+        const int step = chained ? 4 : 8, gap = chained ? 16 : 4;  // rows from lane / 16 to the next; from e to e + 4
+        const uint16_t* src = R + ((size_t)kk * Q + 32 * u + step * (lane >> 4)) * P + 16 * (ig * IG + it) + (lane & 15);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) v[e] = src[(size_t)(16 * (e >> 2) + (e & 3)) * P];
+        for (int e = 0; e < 8; ++e) v[e] = src[(size_t)(gap * (e >> 2) + (e & 3)) * P];
         dst = RF + (size_t)pc * 8;
     } else {
         return;
@@ -415,47 +417,325 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
     }
 }
 
-template <typename C>
-int launch_data(const Problem& pb, const void* dy, const void* x, const uint16_t* XF, const uint16_t* LF,
-                const uint16_t* RF, void* dx, uint16_t* Y1ws, uint16_t* dY1ws, hipStream_t st)
+// The same stages for two of the four blocks kk per workgroup, two waves per block: half of the accumulators per wave, two waves per
+// SIMD and two workgroups per CU, and the two workgroups of a row tile on two CUs where the tiles alone would leave CUs idle.
+//   X  half of the columns j per wave
+//   A  two of the four c per wave; dy comes through a DMA-filled LDS ring as it is and is picked apart where it is read
+//   B  from the dY1 tile in LDS (as bf16, which is also what goes to the workspace for dR), half of the columns i, or of the rows
+//      where the column tiles do not come out even, per wave
+// What bounds it: between L2 and L1 the weights pass once per 64 rows and dy twice, 8 to 16 TB/s in all.  Measured, this kernel
+// against the one above: 768 -> 3072, 8192 rows, 30.8 and 36.9 us; blocks of 256 x 1024, 16384 rows, 106.8 + 96.0 and 117.5 + 97.6.
+// More chunks of dy or of fragments on the way change nothing; 128 rows per workgroup (43.5; 109.4 + 100.5) and all four blocks in
+// eight waves (the whole training step 516 us against 518, but 300 against 287 at 192 x 768 and 40000 rows) do not pay.
+template <int P_, int Q_, int S_>
+struct BwdPair {
+    static constexpr int K = 4, P = P_, Q = Q_, S = S_, IG = 4;
+    static constexpr int BM = 64, NBT = 4;           // rows of a workgroup, in stages A and B as 16-row tiles
+    static constexpr int QK = Q / K, KQ = K * Q;
+    static constexpr int N_IN = K * P, N_OUT = K * S;
+    static constexpr int JT = QK / 16;               // 16-wide j tiles per (kk, c)
+    static constexpr int T_STRIDE = 2 * Q + 8;       // LDS tile [64][two blocks of Q]
+    static constexpr int DX_COLS = IG * 16;          // dx columns of a tile of stage B
+    static constexpr int DX_STRIDE = DX_COLS + 8;
+    // stage B: the two waves of a block take every other tile of columns, or 32 rows each where the tiles do not come out even
+    static constexpr bool BY_COLS = P / DX_COLS % 2 == 0;
+    static constexpr int BT = BY_COLS ? NBT : NBT / 2, TILES = BY_COLS ? P / DX_COLS / 2 : P / DX_COLS;
+    static constexpr size_t LDS_TILE = (size_t)BM * T_STRIDE * 2;
+    static constexpr size_t LDS_DX = (size_t)4 * 16 * DX_STRIDE * 2;
+    static constexpr int RING = 4;                   // stage A: chunks of 32 l of dy in LDS, 256 bytes a row
+    static constexpr size_t LDS_DY = (size_t)RING * BM * 256;
+    // step-1 recompute, half of a block's columns per wave (x through an LDS ring, packed R fragments)
+    using S1 = Stage1<P_, Q_ / 2, Q_ / 32, 2>;
+    static constexpr size_t max2(size_t a, size_t b) { return a > b ? a : b; }
+    static constexpr size_t LDS_BYTES = max2(LDS_TILE + LDS_DX, max2(LDS_DY, S1::LDS_X));
+    static_assert(P % DX_COLS == 0 && Q % 64 == 0 && S % 64 == 0, "tile shapes");
+    static_assert(2 * LDS_BYTES <= kMaxLdsBytes, "two workgroups per CU");
+};
+
+// MODE and ACT as above (no mode 1).
+template <typename C, int MODE, bool ACT>
+__device__ __forceinline__ void
+bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, const uint16_t* __restrict__ XF,
+              const uint16_t* __restrict__ LF, const uint16_t* __restrict__ RF, uint16_t* __restrict__ dx,
+              uint16_t* __restrict__ Y1ws, uint16_t* __restrict__ dY1ws, const uint16_t* __restrict__ x_pre, int64_t B)
 {
-    // no workspace for dY1: dx only; dY1 but no Y1 workspace: the forward saved that vector
-    // (the nonlinearity's factor is applied here only by the recomputing backward)
-    auto kern = !dY1ws ? bwd_wide_data_kernel<C, 1, false>
-                       : (Y1ws ? (pb.x_pre ? bwd_wide_data_kernel<C, 0, true> : bwd_wide_data_kernel<C, 0, false>)
-                               : (pb.x_pre ? bwd_wide_data_kernel<C, 2, true> : bwd_wide_data_kernel<C, 2, false>));
-    if (pb.x_pre && !dY1ws) return -2;
-    if (allow_dynamic_lds((const void*)kern, C::LDS_BYTES) != hipSuccess)
+    extern __shared__ __attribute__((aligned(16))) uint16_t lds[];
+    const int tid = threadIdx.x;
+    const int wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63;
+    // the two workgroups of a row tile follow one another on one XCD (workgroups go to the eight XCDs in turn)
+    const int slot = blockIdx.x >> 3, kp = slot & 1;
+    const int64_t b0 = ((int64_t)(slot >> 1) * 8 + (blockIdx.x & 7)) * C::BM;
+    if (b0 >= B) return;  // (uniform)
+    const int kl = wave >> 1, half = wave & 1, kk = 2 * kp + kl;
+
+    // ------------------------------------------------- X: recompute step 1 -> workspace ----
+    if constexpr (MODE == 0) {
+        using S1 = typename C::S1;
+        const int ln = lane & 31, g = lane >> 5;
+        f32x16 acc[S1::QT * S1::NB];
+        stage1_block<S1>(x, XF, b0, B, kk, lane, lds + (size_t)wave * S1::XR * 4096, acc, half * S1::QT);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();  // every wave is done with its x ring: the space becomes the Y1 tile
+        // lane holds D^T[j][b] for b = nb*32 + ln and j = half*Q/2 + jt*32 + 8*(i/4) + 4*g + i%4
+#pragma unroll
+        for (int jt = 0; jt < S1::QT; ++jt)
+#pragma unroll
+            for (int nb = 0; nb < S1::NB; ++nb)
+#pragma unroll
+                for (int i4 = 0; i4 < 4; ++i4) {
+                    const f32x16& a = acc[jt * S1::NB + nb];
+                    u32x2 v = {pack_bf16x2(a[4 * i4 + 0], a[4 * i4 + 1]), pack_bf16x2(a[4 * i4 + 2], a[4 * i4 + 3])};
+                    const int j = half * (C::Q / 2) + jt * 32 + 8 * i4 + 4 * g;
+                    *reinterpret_cast<u32x2*>(lds + (size_t)(nb * 32 + ln) * C::T_STRIDE + kl * C::Q + j) = v;
+                }
+        __syncthreads();
+        copy_out_tile<2 * C::Q, 256, false>(lds, C::T_STRIDE, Y1ws + kp * 2 * C::Q, C::KQ, b0, B, tid);
+        __syncthreads();
+    }
+
+    // 16 x 16 tile coordinates for stages A and B
+    const int l16 = lane & 15, h = lane >> 4;
+
+    // ------------------------------------------------- A: dY1 (accumulators) ----
+    // accA[(ci*JT + jt)*NBT + bt][e] = dY1[b = bt*16 + l16][kk][j = c*QK + jt*16 + 4*h + e], c = 2*half + ci
+    f32x4 accA[2 * C::JT * C::NBT];
+#pragma unroll
+    for (int t = 0; t < 2 * C::JT * C::NBT; ++t) accA[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+
+    // dy arrives in chunks of 32 l, as it is, through an LDS ring filled in whole 256-byte pieces of its rows, three chunks ahead.
+    // 16-byte piece u of a row (l = 2u, 2u + 1 of all four c) lies in place u ^ (row % 16): the reads of 16 rows are conflict-free.
+    constexpr int NC = C::S / 32, DPT = C::BM * 16 / 256;  // chunks; requests of a thread per chunk
+    const int64_t rows = B - b0 < C::BM ? B - b0 : C::BM;  // rows past the end read as zeros
+    const auto dyb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(dy) + b0 * C::N_OUT, 0, (int)rows * C::N_OUT * 2, 0x00020000);
+    const uint32_t dy_at = (uint32_t)((tid >> 4) * C::N_OUT * 2 + 16 * ((tid & 15) ^ ((tid >> 4) & 15)));
+    auto issue_dy = [&](int n) {
+        const int m = n < NC ? n : NC - 1;  // past the last chunk: again the last one, for the count of the requests
+        auto to = (__attribute__((address_space(3))) unsigned char*)lds + (n % C::RING) * C::BM * 256 + wave * 1024;
+#pragma unroll
+        for (int i = 0; i < DPT; ++i)
+            __builtin_amdgcn_raw_ptr_buffer_load_lds(dyb, (__attribute__((address_space(3))) void*)(to + i * 256 * 16), 16,
+                                                     dy_at + i * 16 * C::N_OUT * 2, m * 256, 0, 0);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    // A operand: fragments (c, chunk, jt) of LF (rows kk*QK + jt*16 + l16 of L^T), c = 2 * half + ci, one chunk ahead
+    const uint16_t* Lk = LF + (((size_t)kk * 4 + 2 * half) * NC * C::JT * 64 + lane) * 8;
+    u32x4 lf[2][2][C::JT];
+    auto issue_l = [&](int n, int at) {
+        const int m = n < NC ? n : NC - 1;
+#pragma unroll
+        for (int ci = 0; ci < 2; ++ci)
+#pragma unroll
+            for (int jt = 0; jt < C::JT; ++jt) lf[at][ci][jt] = ldg128(Lk + ((size_t)(ci * NC + m) * C::JT + jt) * 512);
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    issue_dy(0);
+    issue_dy(1);
+    issue_l(0, 0);
+    issue_dy(2);
+    for (int n0 = 0; n0 < NC; n0 += 2) {
+#pragma unroll
+        for (int par = 0; par < 2; ++par) {
+            const int n = n0 + par;
+            __builtin_amdgcn_sched_barrier(0);
+            // chunk n has landed once only what was requested after it is outstanding: the two chunks behind it, a chunk's fragments
+            wait_vmcnt<2 * DPT + 2 * C::JT>();
+            lds_barrier();  // ... for every wave, and nobody reads chunk n-1 any more
+            issue_l(n + 1, par ^ 1);
+            issue_dy(n + 3);
+            const uint16_t* chunk = lds + (size_t)(n % C::RING) * C::BM * 128 + (size_t)l16 * 128;
+            uint32_t lo[2][4], hi[2][4];  // l = 8h + 2w and the next one, c = 2 * half (low 16 bits) and the next one
+            auto read = [&](int bt, int at) {
+#pragma unroll
+                for (int w = 0; w < 4; ++w) {
+                    const uint32_t* piece = reinterpret_cast<const uint32_t*>(chunk + bt * 16 * 128 + 8 * ((4 * h + w) ^ l16)) + half;
+                    lo[at][w] = piece[0];
+                    hi[at][w] = piece[2];
+                }
+            };
+            read(0, 0);
+#pragma unroll
+            for (int bt = 0; bt < C::NBT; ++bt) {
+                __builtin_amdgcn_sched_barrier(0);
+                if (bt + 1 < C::NBT) read(bt + 1, (bt + 1) & 1);
+                __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+                for (int ci = 0; ci < 2; ++ci) {
+                    u32x4 v;
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) v[w] = ci ? pick_hi16(lo[bt & 1][w], hi[bt & 1][w]) : pick_lo16(lo[bt & 1][w], hi[bt & 1][w]);
+#pragma unroll
+                    for (int jt = 0; jt < C::JT; ++jt)
+                        accA[(ci * C::JT + jt) * C::NBT + bt] =
+                            mfma16(as_bf16x8(lf[par][ci][jt]), as_bf16x8(v), accA[(ci * C::JT + jt) * C::NBT + bt]);
+                }
+            }
+        }
+    }
+    wait_vmcnt<0>();  // nothing is on its way into LDS any more
+    __syncthreads();
+    // dY1 of the two blocks as bf16 in LDS: [b][kl*Q + j], the operand of stage B and the layout of the workspace copy
+#pragma unroll
+    for (int J = 0; J < 2 * C::JT; ++J)
+#pragma unroll
+        for (int bt = 0; bt < C::NBT; ++bt) {
+            const f32x4& a = accA[J * C::NBT + bt];
+            *reinterpret_cast<u32x2*>(lds + (size_t)(bt * 16 + l16) * C::T_STRIDE + kl * C::Q + (2 * half * C::JT + J) * 16 + 4 * h) =
+                u32x2{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3])};
+        }
+
+    // ------------------------------------------------- B: dx ----
+    constexpr int U = C::Q / 32;
+    const uint16_t* Rt = RF + ((size_t)kk * (C::P / C::DX_COLS) * U * C::IG * 64 + lane) * 8;
+    // The fragments run through a ring of NSB steps that continues across the tiles (U % NSB == 0 keeps the slot numbers static).
+    constexpr int NSB = (U % 4 == 0) ? 4 : ((U % 3 == 0) ? 3 : 2);
+    static_assert(U % NSB == 0, "ring");
+    const auto column_tile = [&](int n) { return C::BY_COLS ? 2 * n + half : n; };
+    u32x4 af[NSB][C::IG];
+    auto issue = [&](int n, int u, int at) {
+#pragma unroll
+        for (int it = 0; it < C::IG; ++it) af[at][it] = ldg128(Rt + ((size_t)(column_tile(n) * U + u) * C::IG + it) * 512);
+    };
+#pragma unroll
+    for (int d = 0; d < NSB - 1; ++d) issue(0, d, d);
+    // what a lane stores of a 16-row tile: two pieces of 16 bytes, eight lanes a row
+    const int row0 = C::BY_COLS ? 0 : 32 * half;
+    uint16_t* stage = lds + C::LDS_TILE / 2 + (size_t)wave * 16 * C::DX_STRIDE;
+    const auto row_at = [&](int bt, int i) { return b0 + row0 + bt * 16 + i * 8 + (lane >> 3); };
+    u32x4 hp[ACT ? 2 * C::BT : 1];
+    const auto load_pre = [&](int n, int bt, int i) {
+        int64_t row = row_at(bt, i);
+        row = row < B ? row : B - 1;  // rows past the end are read from a valid row and never stored
+        hp[bt * 2 + i] = ldg128_nt(x_pre + row * C::N_IN + kk * C::P + column_tile(n) * C::DX_COLS + 8 * (lane & 7));
+    };
+    if constexpr (ACT) {
+#pragma unroll
+        for (int i = 0; i < 2 * C::BT; ++i) load_pre(0, i >> 1, i & 1);
+    }
+    __syncthreads();  // the tile is complete; nothing below writes it
+    copy_out_tile<2 * C::Q, 256, false>(lds, C::T_STRIDE, dY1ws + kp * 2 * C::Q, C::KQ, b0, B, tid);
+
+    for (int n = 0; n < C::TILES; ++n) {
+        f32x4 acc[C::IG * C::BT];
+#pragma unroll
+        for (int t = 0; t < C::IG * C::BT; ++t) acc[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            __builtin_amdgcn_sched_barrier(0);
+            if (u + NSB - 1 < U) issue(n, u + NSB - 1, (u + NSB - 1) % NSB);
+            else if (n + 1 < C::TILES) issue(n + 1, u + NSB - 1 - U, (u + NSB - 1) % NSB);
+            __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+            for (int bt = 0; bt < C::BT; ++bt) {
+                const bf16x8 bfr = as_bf16x8(lds128(lds + (size_t)(row0 + bt * 16 + l16) * C::T_STRIDE + kl * C::Q + 32 * u + 8 * h));
+#pragma unroll
+                for (int it = 0; it < C::IG; ++it)
+                    acc[it * C::BT + bt] = mfma16(as_bf16x8(af[u % NSB][it]), bfr, acc[it * C::BT + bt]);
+            }
+        }
+        // D^T[i][b]: lane holds i = it*16 + 4*h + 0..3 for row b = bt*16 + l16; 16 rows at a time leave by way of the wave's
+        // staging tile (private to the wave: no workgroup barrier)
+#pragma unroll
+        for (int bt = 0; bt < C::BT; ++bt) {
+#pragma unroll
+            for (int it = 0; it < C::IG; ++it) {
+                const f32x4& a = acc[it * C::BT + bt];
+                *reinterpret_cast<u32x2*>(stage + (size_t)l16 * C::DX_STRIDE + it * 16 + 4 * h) =
+                    u32x2{pack_bf16x2(a[0], a[1]), pack_bf16x2(a[2], a[3])};
+            }
+            wave_fence();
+#pragma unroll
+            for (int i = 0; i < 2; ++i) {
+                u32x4 v = lds128(stage + (size_t)(i * 8 + (lane >> 3)) * C::DX_STRIDE + 8 * (lane & 7));
+                if constexpr (ACT) {
+                    const u32x4 hv = hp[bt * 2 + i];
+                    if (n + 1 < C::TILES) load_pre(n + 1, bt, i);
+#pragma unroll
+                    for (int w = 0; w < 4; ++w) {
+                        const float g0 = __uint_as_float(v[w] << 16), g1 = __uint_as_float(v[w] & 0xffff0000u);
+                        const float h0 = __uint_as_float(hv[w] << 16), h1 = __uint_as_float(hv[w] & 0xffff0000u);
+                        v[w] = pack_bf16x2(g0 * gelu_grad_f(h0), g1 * gelu_grad_f(h1));
+                    }
+                }
+                const int64_t row = row_at(bt, i);
+                if (row < B) stg128_nt(dx + row * C::N_IN + kk * C::P + column_tile(n) * C::DX_COLS + 8 * (lane & 7), v);
+            }
+            wave_fence();
+        }
+    }
+}
+
+template <typename C, int MODE, bool ACT>
+__global__ void __launch_bounds__(256, 2)
+bwd_pair_data_kernel(const uint16_t* dy, const uint16_t* x, const uint16_t* XF, const uint16_t* LF, const uint16_t* RF, uint16_t* dx,
+                     uint16_t* Y1ws, uint16_t* dY1ws, const uint16_t* x_pre, int64_t B)
+{
+    bwd_pair_data<C, MODE, ACT>(dy, x, XF, LF, RF, dx, Y1ws, dY1ws, x_pre, B);
+}
+
+// Where two workgroups share a row tile (bwd_pair_data_kernel), whole backward at 6000, 12000 and 40000 rows, with it and without:
+// blocks of 192 and more always (192 x 768: 65 and 73 us, 94 and 94, 286 and 300; 256 x 1024: 85 and 98, 126 and 126, 380 and 403;
+// 1024 x 256: 100 and 111, 140 and 144, 442 and 462); smaller ones up to 128 tiles, which alone would leave CUs idle (128 x 512: 46
+// and 50 us, 65 and 62, 148 and 151; 512 x 128: 47 and 53, 65 and 65, 180 and 168).
+bool pairs(const Problem& pb) { return pb.q > 128 || (pb.B + 63) / 64 <= 128; }
+
+template <typename K>
+int launch_data_on(K kern, size_t lds, int64_t grid, const Problem& pb, const void* dy, const void* x, const uint16_t* XF,
+                   const uint16_t* LF, const uint16_t* RF, void* dx, uint16_t* Y1ws, uint16_t* dY1ws, hipStream_t st)
+{
+    if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess)
         return -4;
-    const int64_t grid = (pb.B + C::BM - 1) / C::BM;
     if (grid > 0x7fffffffLL) return -2;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), C::LDS_BYTES, st, (const uint16_t*)dy,
-                       (const uint16_t*)x, XF, LF, RF, (uint16_t*)dx, Y1ws, dY1ws, (const uint16_t*)pb.x_pre, pb.B);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(256), lds, st, (const uint16_t*)dy, (const uint16_t*)x, XF, LF, RF,
+                       (uint16_t*)dx, Y1ws, dY1ws, (const uint16_t*)pb.x_pre, pb.B);
     return hip_status(hipGetLastError());
 }
 
+// no workspace for dY1: dx only; dY1 but no Y1 workspace: the forward saved that vector, or it is made elsewhere
+template <int P, int Q, int S, int JG, int LC, int IG>
+int launch_data(const Problem& pb, const void* dy, const void* x, const uint16_t* XF, const uint16_t* LF,
+                const uint16_t* RF, void* dx, uint16_t* Y1ws, uint16_t* dY1ws, hipStream_t st)
+{
+    using C = BwdWide<P, Q, S, JG, LC, IG>;
+    const int64_t tiles = (pb.B + 63) / 64;
+    auto run = [&](auto kern) { return launch_data_on(kern, C::LDS_BYTES, tiles, pb, dy, x, XF, LF, RF, dx, Y1ws, dY1ws, st); };
+    if (!dY1ws) return pb.x_pre ? -2 : run(bwd_wide_data_kernel<C, 1, false>);
+    if (pairs(pb)) {
+        using D = BwdPair<P, Q, S>;
+        auto run2 = [&](auto kern) {  // two workgroups for each row tile, whole sets of eight tiles
+            return launch_data_on(kern, D::LDS_BYTES, (tiles + 7) / 8 * 16, pb, dy, x, XF, LF, RF, dx, Y1ws, dY1ws, st);
+        };
+        if (Y1ws) return pb.x_pre ? run2(bwd_pair_data_kernel<D, 0, true>) : run2(bwd_pair_data_kernel<D, 0, false>);
+        return pb.x_pre ? run2(bwd_pair_data_kernel<D, 2, true>) : run2(bwd_pair_data_kernel<D, 2, false>);
+    }
+    if constexpr (Q <= 128) {
+        if (Y1ws) return pb.x_pre ? run(bwd_wide_data_kernel<C, 0, true>) : run(bwd_wide_data_kernel<C, 0, false>);
+        return pb.x_pre ? run(bwd_wide_data_kernel<C, 2, true>) : run(bwd_wide_data_kernel<C, 2, false>);
+    }
+    return -2;
+}
+
 struct Entry {
-    int p, q, s, jg, ig;  // jg, ig: the data kernel's loop splits, which fix the fragment order of the weights
+    int p, q, s, ig;  // ig: a loop split of the data kernels that fixes the fragment order of the weights
     int (*fn)(const Problem&, const void*, const void*, const uint16_t*, const uint16_t*, const uint16_t*, void*,
               uint16_t*, uint16_t*, hipStream_t);
 };
 
 //                                 P     Q     S   JG   LC  IG
 const Entry kTable[] = {
-    {192, 192, 192, 6, 4, launch_data<BwdWide<192, 192, 192, 6, 192, 4>>},
-    {192, 192, 768, 6, 4, launch_data<BwdWide<192, 192, 768, 6, 192, 4>>},
-    {256, 256, 1024, 4, 4, launch_data<BwdWide<256, 256, 1024, 4, 128, 4>>},
-    {1024, 256, 256, 4, 4, launch_data<BwdWide<1024, 256, 256, 4, 128, 4>>},
-    {768, 192, 192, 6, 4, launch_data<BwdWide<768, 192, 192, 6, 192, 4>>},
-    {256, 256, 256, 4, 4, launch_data<BwdWide<256, 256, 256, 4, 128, 4>>},
-    {192, 192, 576, 6, 4, launch_data<BwdWide<192, 192, 576, 6, 192, 4>>},
-    {256, 256, 768, 4, 4, launch_data<BwdWide<256, 256, 768, 4, 128, 4>>},
-    {128, 128, 128, 4, 4, launch_data<BwdWide<128, 128, 128, 4, 128, 4>>},
-    {128, 128, 512, 4, 4, launch_data<BwdWide<128, 128, 512, 4, 128, 4>>},
-    {512, 128, 128, 4, 4, launch_data<BwdWide<512, 128, 128, 4, 128, 4>>},
-    {64, 64, 64, 2, 4, launch_data<BwdWide<64, 64, 64, 2, 64, 4>>},
-    {64, 64, 128, 2, 4, launch_data<BwdWide<64, 64, 128, 2, 64, 4>>},
-    {128, 64, 64, 2, 4, launch_data<BwdWide<128, 64, 64, 2, 64, 4>>},
+    {192, 192, 192, 4, launch_data<192, 192, 192, 6, 192, 4>},
+    {192, 192, 768, 4, launch_data<192, 192, 768, 6, 192, 4>},
+    {256, 256, 1024, 4, launch_data<256, 256, 1024, 4, 128, 4>},
+    {1024, 256, 256, 4, launch_data<1024, 256, 256, 4, 128, 4>},
+    {768, 192, 192, 4, launch_data<768, 192, 192, 6, 192, 4>},
+    {256, 256, 256, 4, launch_data<256, 256, 256, 4, 128, 4>},
+    {192, 192, 576, 4, launch_data<192, 192, 576, 6, 192, 4>},
+    {256, 256, 768, 4, launch_data<256, 256, 768, 4, 128, 4>},
+    {128, 128, 128, 4, launch_data<128, 128, 128, 4, 128, 4>},
+    {128, 128, 512, 4, launch_data<128, 128, 512, 4, 128, 4>},
+    {512, 128, 128, 4, launch_data<512, 128, 128, 4, 128, 4>},
+    {64, 64, 64, 4, launch_data<64, 64, 64, 2, 64, 4>},
+    {64, 64, 128, 4, launch_data<64, 64, 128, 2, 64, 4>},
+    {128, 64, 64, 4, launch_data<128, 64, 64, 2, 64, 4>},
 };
 
 const Entry* find(const Problem& pb)
@@ -537,7 +817,7 @@ int fwd_t_wide(const Problem& pb, const void* x, const void* R, const void* L, v
     const size_t pieces = (2 * pb.n_R() + pb.n_L()) / 8;
     const int nprep = (int)((pieces + 255) / 256);
     hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)nprep), dim3(256), 0, st, (const uint16_t*)L, (const uint16_t*)R,
-                       XF, LF, RF, pb.p, pb.q, pb.s, e->jg, e->ig);
+                       XF, LF, RF, pb.p, pb.q, pb.s, e->ig, true);
     if (hipGetLastError() != hipSuccess) return -4;
     return e->fn(pb, x, nullptr, XF, LF, RF, y, nullptr, nullptr, st);
 }
@@ -565,7 +845,7 @@ int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, co
     const size_t pieces = (2 * pb.n_R() + pb.n_L()) / 8;
     const int nprep = (int)((pieces + 255) / 256);
     hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)nprep), dim3(256), 0, st, (const uint16_t*)L, (const uint16_t*)R,
-                       XF, LF, RF, pb.p, pb.q, pb.s, e->jg, e->ig);
+                       XF, LF, RF, pb.p, pb.q, pb.s, e->ig, !pairs(pb));
     if (hipGetLastError() != hipSuccess) return -4;
     // Step 1 (Y1, for dL) is recomputed either by the data kernel itself or, for the shapes that have it, by a
     // GEMM of its own with four times the rows per workgroup (monarch_mfma_y1.hip); not at all when the forward saved it.
