@@ -329,7 +329,7 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
     for (int d = 0; d < NSB - 1; ++d) issue(d, d);
     // ACT: what leaves is multiplied by gelu'(x_pre), which costs the vector units two to three times what the tile costs the
     // matrix cores, and a wave is alone on its SIMD: so the pieces of tile ig - 1 leave between the MFMAs of tile ig
-    // (1024 x 256, 16384 rows: 128 -> 117 us).  hp[i] holds the x_pre piece that task i multiplies by; it is replaced by the one
+    // (measured where it mattered most, 1024 x 256 blocks, 16384 rows: 128 -> 117 us).  hp[i] holds the x_pre piece that task i multiplies by; it is replaced by the one
     // of the next tile as soon as it is used.
     constexpr int PIECES = C::DX_COLS / 8;
     const auto pre_at = [&](int ig, int i) {

@@ -13,7 +13,7 @@
 // What bounds it: latency for one row tile (two launches of about 3.5 us), above that the address path of the L1: 20 cycles a fragment
 // for MFMAs of 32 cycles on four SIMDs.  With U in rows, a fragment of it took 62 cycles, and so did one of x (1531 rows: the stages of
 // 1024 -> 4096 5.8 + 16.4 -> 5.2 + 15.5 us, the second one now bound by the nonlinearity, of 4096 -> 1024 12.8 + 7.6 -> 10.4 + 5.2).
-// Measured, 1024 -> 4096 -> 1024 with bias and GELU, against the fused kernel alone and against U in rows: 8 rows 54, 14.4 and 14.5 us, 256 rows
+// Measured, 1024 -> 4096 -> 1024 with bias and GELU, against the fused kernel alone and against U in rows: 8 rows 54, 15.7 and 13.9 us, 256 rows
 // 66, 19.9 and 18.6, 1531 rows 69, 40.1 and 32.7; 768 -> 3072 -> 768, 1531 rows: 33.0 and 25.6.
 #include "../../include/monarch.h"
 #include "monarch_internal.h"
@@ -72,10 +72,11 @@ split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
 #pragma unroll
-    for (int i = 0; i < NB; ++i) a_at[i] = i * 32 < rows ? (uint32_t)(i * (Q / 4) * 1024 + lane * 16) : kNowhere;
+    for (int i = 0; i < NB; ++i) a_at[i] = ln < rows ? (uint32_t)((g * rows + ln) * 16) : kNowhere;
 #pragma unroll
     for (int j = 0; j < NT; ++j) w_at[j] = lt0 + j < LT ? (uint32_t)((lt0 + j) * KS * 1024 + lane * 16) : kNowhere;
-    tile_product<NB, NT, NG, AHEAD, false, false>(U + (b0 / 32 * (Q / 4) + c * KS) * 512, a_at, 1024u, LF2 + (size_t)c * LT * KS * 512, w_at,
+    static_assert(NB == 1, "a tile of U has the rows of the workgroup");
+    tile_product<NB, NT, NG, AHEAD, false, false>(U + b0 * 4 * Q + c * KS * rows * 16, a_at, (uint32_t)rows * 32, LF2 + (size_t)c * LT * KS * 512, w_at,
                                                   1024u, KS, acc, 0u, 0, nullptr);
 
 #pragma unroll
@@ -179,7 +180,7 @@ bool fwd_split_preferred(const Problem& pb)
            fwd_frag_packed(pb) + fwd_split_mid_bytes(pb) <= MONARCH_STATIC_WORKSPACE_BYTES;
 }
 
-size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B + 31) / 32 * 32 * pb.kq() * 2, 256); }
+size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)pb.B * pb.kq() * 2, 256); }
 
 int fwd_split(const Problem& pb, const void* x, const void* R, const void* L, uint16_t* RF1, uint16_t* LF2, void* y, void* U,
               hipStream_t st)

@@ -105,8 +105,8 @@ __device__ __forceinline__ bool split_index(const SplitGrid& gr, int bid, int& r
 // Step 1 for one workgroup: Y1 of 32 * NB rows, block kk, NT column tiles of 32.  The four waves share out the contraction, so that
 // every byte of x and R the workgroup needs is loaded once, and add up their tiles through LDS (split_stage1_lds bytes).
 // DIRECT: W is R as it is (read in 16-byte pieces of its rows, like x), else the packed copy RF1.  NATURAL: out[b][kk*Q + j], else
-// the order the packed L contracts, (j/4, kk, j%4), in MFMA fragments: out[b/32][j/4][lane][e] = element 8 (lane / 32) + e of the 16
-// (kk, j%4) of row lane % 32, whole tiles of 32 rows.
+// the order the packed L contracts, (j/4, kk, j%4), in MFMA fragments: out[b/32][j/4][h][row][e] = element 8 h + e of the 16
+// (kk, j%4) of row b % 32, with no more rows in the last tile than there are.
 template <int NB, int NT, bool TURN>
 constexpr size_t split_stage1_lds() { return (size_t)4 * NB * NT * 4096 + (TURN ? 4 * kTurnBytes : 0); }
 template <int NB, int NT, int NG, int AHEAD, bool DIRECT, bool NATURAL, bool TURN>
@@ -166,8 +166,9 @@ __device__ __forceinline__ void split_stage1(const uint16_t* __restrict__ x, con
             const u32x2 o = {pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
             if constexpr (NATURAL) {
                 if (row < rows && jt0 + j < QT) *reinterpret_cast<u32x2*>(U + (b0 + row) * 4 * Q + kk * Q + col) = o;
-            } else if (i * 32 < rows && jt0 + j < QT) {
-                *reinterpret_cast<u32x2*>(U + ((b0 / 32 + i) * (Q / 4) + (col >> 2)) * 512 + ((kk >> 1) * 32 + ln) * 8 + (kk & 1) * 4) = o;
+            } else if (row < rows && jt0 + j < QT) {
+                const int tall = rows - i * 32 < 32 ? rows - i * 32 : 32;  // rows of the tile
+                *reinterpret_cast<u32x2*>(U + (b0 + i * 32) * 4 * Q + (((col >> 2) * 2 + (kk >> 1)) * tall + ln) * 8 + (kk & 1) * 4) = o;
             }
         }
 }

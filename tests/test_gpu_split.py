@@ -178,9 +178,9 @@ def test_calls_on_two_streams_share_packed_weights():
         assert torch.equal(y, want[i % 3]), i
 
 
-# the vector between the factors is kept in whole tiles of 32 rows: the workspace and the scratch that the queries name hold them
+# the vector between the factors is kept in tiles of 32 rows, the last one no longer than it is: nothing past what the queries name
 @pytest.mark.parametrize("case", [(1, 64, 64, 64), (33, 128, 64, 64), (545, 256, 256, 768), (2817, 128, 128, 128)], ids=str)
-def test_whole_tiles_stay_inside_the_workspace(case):
+def test_tiles_stay_inside_the_workspace(case):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2204_00595_amd import binding as B
