@@ -648,7 +648,8 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
 // dy, read through the outer permutation, in tiles dW[row tile][block][l][32 rows]: the operand of the stage that makes dY1 and of the
 // weight gradient.  A workgroup moves 64 consecutive values of 32 rows through LDS (REAL: the 64 blocks from g0 of one pair of
 // inputs, 2 x 64 floats), reading 512 bytes (2 x 256) of a row and writing runs of 256 bytes.  Bound by memory (2048 x 4096
-// complex values: 28 us, 4.8 TB/s).
+// complex values: 28 us, 4.8 TB/s).  REAL with a number of blocks that is no multiple of four loads single values: a piece of four
+// would start anywhere, and the last one of the last row would end past the tensor.
 template <bool REAL>
 __global__ void __launch_bounds__(256)
 ctile_kernel(const float2* __restrict__ in, float2* __restrict__ out, int64_t B, int k, int P, int chunks)
@@ -673,7 +674,13 @@ ctile_kernel(const float2* __restrict__ in, float2* __restrict__ out, int64_t B,
             in_row = j0 + 2 * c < n;
             at = (size_t)r * (2 * n) + 2 * (j0 + 2 * c);
         }
-        v[u] = r < B && in_row ? ldg128(reinterpret_cast<const float*>(in) + at) : u32x4{0, 0, 0, 0};
+        const float* p = reinterpret_cast<const float*>(in) + at;
+        if (!REAL || k % 4 == 0) {
+            v[u] = r < B && in_row ? ldg128(p) : u32x4{0, 0, 0, 0};
+        } else {
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[u][e] = r < B && g0 + 4 * (c & 15) + e < k ? __float_as_uint(p[e]) : 0u;
+        }
     }
 #pragma unroll
     for (int u = 0; u < 4; ++u) {

@@ -84,3 +84,30 @@ def test_real_layers_with_values_that_three_bf16_planes_cannot_hold(case):
         for row in range(len(w)):
             a, b = g[row][fine[row]], w[row][fine[row]]
             assert np.linalg.norm(a - b) <= 4e-5 * np.linalg.norm(b), (name, row)
+
+
+# Real layers of blocks of 32 and 64 read dy in the order of the outer permutation, in pieces of four where the block count allows: for every
+# remainder by four, dy as the last bytes of a mapping, and with NaN behind it.
+@pytest.mark.parametrize("case", [(33, 32, 3), (64, 32, 5), (5, 32, 66), (33, 64, 1), (32, 64, 2), (65, 64, 67), (40, 64, 4), (31, 32, 12)], ids=str)
+def test_real_layers_read_nothing_behind_dy(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, m, k = case
+    x, R, L, dy = (synth.normal(8970 + i, shp, std).astype(np.float32) for i, (shp, std) in enumerate(
+        (((rows, k * m), 1.0), ((k, m, m), m ** -0.5), ((k, m, m), m ** -0.5), ((rows, k * m), 1.0))))
+    xd, Rd, Ld = (torch.from_numpy(a).cuda() for a in (x, R, L))
+    flat = torch.from_numpy(dy).cuda().reshape(-1)
+    room = torch.full((8 << 20,), float("nan"), device="cuda")   # 32 MiB: a mapping of its own
+    lead = (room.numel() - flat.numel()) % 4                     # a tensor starts at a multiple of 16 bytes
+    results = []
+    for start in (0, room.numel() - flat.numel() - lead):
+        view = room[start:start + flat.numel()]
+        view.copy_(flat)
+        results.append(B.monarch_bwd(view.view(rows, k * m), xd, Rd, Ld))
+        view.fill_(float("nan"))
+    plain = B.monarch_bwd(flat.view(rows, k * m), xd, Rd, Ld)
+    simt = B.monarch_bwd(flat.view(rows, k * m), xd, Rd, Ld, flags=B.MONARCH_FLAG_GENERIC)
+    for name, first, last, g, w in zip(("dx", "dR", "dL"), *results, plain, simt):
+        assert torch.equal(first, g) and torch.equal(last, g), name
+        assert float((g - w).double().norm()) <= 1e-5 * float(w.double().norm()), name
