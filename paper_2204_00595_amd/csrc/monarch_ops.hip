@@ -15,11 +15,11 @@
 //
 // Precision: U and dU are fp32 for both types, as in the SIMT kernels; bf16 layers are rounded once, when a result is stored.
 // Everything runs on the bf16 matrix cores, which are exact in the products and add them in fp32.  An fp32 operand is taken as three bf16
-// planes that add up to it exactly (split3), and a product of two such operands as the six products of planes above 2^-26 of
-// the whole (three where the other operand is bf16).  An accumulator takes one rounding per 16 contraction indices and product of planes, so
+// planes that add up to it exactly (split3), and a product of two such operands as the six largest products of planes (three where the
+// other operand is bf16).  An accumulator takes one rounding per 16 contraction indices and product of planes, so
 // the results are closer to float64 than those of v_mfma_f32_32x32x2_f32 with one per 2 (normal operands, 192 indices: 2.0e-7 against
 // 2.5e-7; with the small products in a sum of their own, as the weight gradients have them, 0.8e-7).  What the planes cannot hold
-// (infinities, results below 2^-80) is found in the finished tile, which is then computed again in fp32 (planes_doubtful, op_redo).
+// (infinities, operands from 2^104 and results from 2^80 on) is found in the finished tile, which is then computed again in fp32 (op_redo).
 //
 // What bounds it: a product of two fp32 operands costs the matrix cores 6/14.4 of its time on the fp32 cores (2058 against
 // 143 TFLOP/s in a loop of MFMAs alone), and what is left is the vector work of splitting (5.5 instructions an element, once per tile that
@@ -452,7 +452,12 @@ __device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>
                 }
     }
     if constexpr (kSplit) {
-        if (planes_doubtful(acc))
+        const bool off = planes_overflowed(acc);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] *= kPlaneUnscale<PA / 3 + PB / 3>;
+        if (off)
             op_redo<TA, TB>(d, g, m0 + wm * MT * 32, n0 + wn * NT * 32, mlim - wm * MT * 32, nlim - wn * NT * 32, k_lo, k_len, lane, acc);
     }
     op_store<TO, PARTIAL, MT, NT>(d, acc, outer, g, m0, n0, mlim, nlim, wm, wn, lane);

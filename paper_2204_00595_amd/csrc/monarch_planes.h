@@ -4,11 +4,18 @@
 
 namespace monarch {
 
-// fp32 pair -> its three bf16 pairs: the value rounded, what that leaves rounded, and the rest, which fits.  The three add up to
-// the value exactly, except where the last one is below bf16's smallest number (values below 2^-110) or the value is not finite.
+// Operands are scaled up before they are split: every bit of an fp32 number, the denormal ones too, is then a multiple of 2^-125, so that
+// each plane is a normal bf16 number or zero and nothing is lost at the lower end, whatever the other operand.  Numbers from 2^104 and
+// results from 2^80 on become infinite, which the finished tile shows (planes_overflowed).
+constexpr float kPlaneScale = 0x1p24f;
+template <int SPLIT>  // operands that were split: 1 or 2
+constexpr float kPlaneUnscale = SPLIT == 2 ? 0x1p-48f : 0x1p-24f;
+
+// fp32 pair -> its three bf16 pairs: the (scaled) value rounded, what that leaves rounded, and the rest, which fits.  The three add up to
+// the value exactly.
 __device__ __forceinline__ void split3(uint32_t a, uint32_t b, uint32_t out[3])
 {
-    float x = __uint_as_float(a), y = __uint_as_float(b);
+    float x = __uint_as_float(a) * kPlaneScale, y = __uint_as_float(b) * kPlaneScale;
 #pragma unroll
     for (int w = 0; w < 3; ++w) {
         out[w] = pack_bf16x2(x, y);
@@ -19,8 +26,8 @@ __device__ __forceinline__ void split3(uint32_t a, uint32_t b, uint32_t out[3])
     }
 }
 
-// Products of the planes whose place values add up to less than 3; the others are below 2^-26 of the whole.  `big` takes the
-// product of the first planes, `small` the rest (they may be one).
+// Products of the planes whose place values add up to less than 3; what the others add up to is at most 2^-24 of the product (2^-27.5 root
+// mean square, where one rounding to fp32 is 2^-25.3).  `big` takes the product of the first planes, `small` the rest (they may be one).
 template <int PA, int PB>
 __device__ __forceinline__ void plane_products(const bf16x8 (&a)[PA], const bf16x8 (&b)[PB], f32x16& big, f32x16& small)
 {
@@ -32,13 +39,11 @@ __device__ __forceinline__ void plane_products(const bf16x8 (&a)[PA], const bf16
     big = mfma32(a[0], b[0], big);
 }
 
-// Results of the split planes that are not what the fp32 matrix cores give: a value that is not finite (an infinity times the zero
-// planes of a number is no number) and one so small that planes below bf16's smallest number may have been lost.  Exact zeros
-// are right.  True if any lane of the wave holds such a value.
+// Whether a lane of the wave holds a result that is not finite: an infinity or NaN among the operands (an infinity times the zero planes of
+// a number is no number), or something that the scale made infinite.
 template <int MT, int NT>
-__device__ __forceinline__ bool planes_doubtful(const f32x16 (&acc)[MT][NT])
+__device__ __forceinline__ bool planes_overflowed(const f32x16 (&acc)[MT][NT])
 {
-    constexpr uint32_t kSmall = (127u - 80u) << 24, kWidth = (255u << 24) - kSmall;  // twice the bits of 2^-80, and from there to infinity
     uint32_t worst = 0;
 #pragma unroll
     for (int i = 0; i < MT; ++i)
@@ -46,31 +51,19 @@ __device__ __forceinline__ bool planes_doubtful(const f32x16 (&acc)[MT][NT])
         for (int j = 0; j < NT; ++j)
 #pragma unroll
             for (int r = 0; r < 16; ++r) {
-                const uint32_t t = (__float_as_uint(acc[i][j][r]) << 1) - kSmall;
+                const uint32_t t = __float_as_uint(acc[i][j][r]) << 1;
                 worst = t > worst ? t : worst;
             }
-    if (!__any(worst >= kWidth)) return false;
-    bool off = false;  // most often these are the zeros of a ragged tile
-#pragma unroll
-    for (int i = 0; i < MT; ++i)
-#pragma unroll
-        for (int j = 0; j < NT; ++j)
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const uint32_t t = __float_as_uint(acc[i][j][r]) << 1;
-                off |= t != 0 && t - kSmall >= kWidth;
-            }
-    return __any(off);
-}
-
-__device__ __forceinline__ bool planes_doubtful(const f32x16& acc)
-{
-    return planes_doubtful(reinterpret_cast<const f32x16(&)[1][1]>(acc));
+    return __any(worst >= (255u << 24));
 }
 template <int NT>
-__device__ __forceinline__ bool planes_doubtful(const f32x16 (&acc)[NT])
+__device__ __forceinline__ bool planes_overflowed(const f32x16 (&acc)[NT])
 {
-    return planes_doubtful(reinterpret_cast<const f32x16(&)[1][NT]>(acc));
+    return planes_overflowed(reinterpret_cast<const f32x16(&)[1][NT]>(acc));
+}
+__device__ __forceinline__ bool planes_overflowed(const f32x16& acc)
+{
+    return planes_overflowed(reinterpret_cast<const f32x16(&)[1][1]>(acc));
 }
 
 }  // namespace monarch

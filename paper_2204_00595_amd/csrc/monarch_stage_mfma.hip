@@ -16,7 +16,7 @@
 // The products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), both operands as three bf16 planes that add up to the fp32
 // values (monarch_planes.h): weights when they are loaded, activations on their way to LDS or, where a wave takes them from memory
 // itself, in its registers.  A step contracts eight complex inputs with six MFMAs in place of sixteen fp32 MFMAs of twice the cycles.
-// A tile with a result that planes cannot hold is computed again in fp32 (stage_redo).  On the fp32 cores the contiguous stages took 54 us
+// A tile with results that are not finite is computed again in fp32 (stage_finish).  On the fp32 cores the contiguous stages took 54 us
 // at 64 blocks of 64 and 2048 rows and were bound by them (69 to 74 % busy); they take 37 to 40 now, for 134 MB each, 26 us at the
 // rate of a copy.  What is left is one tile per workgroup in flight: the weights' planes take 96 registers, so two workgroups fit a CU.
 // A second tile in flight took a workgroup's registers to the limit and 6 us more, a third workgroup spilled (62 us).
@@ -126,11 +126,14 @@ __device__ __forceinline__ void split_four(const float2 (&v)[4], bf16x8 (&b)[3])
     for (int u = 0; u < 3; ++u) b[u] = as_bf16x8(u32x4{w[0][u], w[1][u], w[2][u], w[3][u]});
 }
 
-// A tile whose planes do not hold it (planes_doubtful) again in fp32.
+// A finished tile: the planes' scale comes off; one with something not finite is computed again in fp32.
 template <int P, int Q, int IN, bool CONJT, bool REAL>
-__device__ __forceinline__ void stage_redo(f32x16& acc, const float2* __restrict__ in, const float2* __restrict__ W, int64_t rt, int g, int mt,
+__device__ __forceinline__ void stage_finish(f32x16& acc, const float2* __restrict__ in, const float2* __restrict__ W, int64_t rt, int g, int mt,
                                            int k, int64_t ld, int64_t B, int lane)
 {
+    const bool off = planes_overflowed(acc);
+    acc *= kPlaneUnscale<2>;
+    if (!off) return;
     const int col = lane & 31, kh = lane >> 5;
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
@@ -323,7 +326,7 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
             Tile::read(xv, a, t, lane);
             plane_products<3, 3>(A[t], xv, acc, acc);
         }
-        if (planes_doubtful(acc)) stage_redo<P, Q, IN, CONJT, REAL>(acc, in, W, rt, g, mt, k, ld_in, B, lane);
+        stage_finish<P, Q, IN, CONJT, REAL>(acc, in, W, rt, g, mt, k, ld_in, B, lane);
 
         const int64_t row = rt * kRT + col;
         if constexpr (OUT == kOutNat) {
@@ -434,9 +437,7 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
                 }
             }
     };
-    auto mend = [&](int64_t rt) {
-        if (planes_doubtful(acc)) stage_redo<P, Q, kInT, false, REAL>(acc, T, W, rt, g, mt, k, 0, B, lane);
-    };
+    auto finish = [&](int64_t rt) { stage_finish<P, Q, kInT, false, REAL>(acc, T, W, rt, g, mt, k, 0, B, lane); };
     // the results of one tile: exchange through LDS buffer it & 1 (one barrier per tile), then the 64-byte (REAL:
     // 32-byte) pieces of y
     auto emit = [&](int64_t rt, int it) {
@@ -487,14 +488,14 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
             if (rt + nsplit < ntiles) load(xb, rt + nsplit, 0);
             zero();
             mma(xa, First());
-            mend(rt);
+            finish(rt);
             emit(rt, it);
             rt += nsplit;
             if (rt >= ntiles) break;
             if (rt + nsplit < ntiles) load(xa, rt + nsplit, 0);
             zero();
             mma(xb, First());
-            mend(rt);
+            finish(rt);
             emit(rt, it + 1);
             rt += nsplit;
         }
@@ -505,7 +506,7 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
             mma(xa, First());
             if (rt + nsplit < ntiles) load(xa, rt + nsplit, 0);
             mma(xb, Second());
-            mend(rt);
+            finish(rt);
             emit(rt, it);
         }
     }
@@ -620,7 +621,7 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
                 }
             }
         }
-        if (planes_doubtful(acc)) stage_redo<P, Q, kInGather, true, REAL>(acc, in, W, rt, g, mt, k, ld_in, B, lane);
+        stage_finish<P, Q, kInGather, true, REAL>(acc, in, W, rt, g, mt, k, ld_in, B, lane);
         if constexpr (REAL) {
             float* outf = reinterpret_cast<float*>(out);
 #pragma unroll
@@ -884,7 +885,10 @@ cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float
             }
         }
     }
-    if (planes_doubtful(acc)) {
+    const bool off = planes_overflowed(acc);
+#pragma unroll
+    for (int nt = 0; nt < NTN; ++nt) acc[nt] *= kPlaneUnscale<2>;
+    if (off) {
 #pragma unroll
         for (int nt = 0; nt < NTN; ++nt) {
 #pragma unroll

@@ -1,0 +1,118 @@
+"""fp32 products in three bf16 planes (shape-generic contractions, stage kernels of the complex multiply and of real fp32 blocks of 32 and 64):
+operands at both ends of the range of fp32, rows beside others that hold infinities, weight gradients of such batches."""
+import numpy as np
+import pytest
+
+import oracle
+from oracle import complex_ref
+from paper_2204_00595_amd import synth
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+# rows, k, p, q, s, type: shape-generic fp32 in all tile sizes and ways of taking an operand, bf16; real blocks with and without eight
+# blocks to a workgroup; complex blocks likewise
+SHAPES = [(70, 4, 48, 48, 48, "f32"), (130, 3, 40, 128, 257, "f32"), (300, 4, 192, 192, 192, "f32"), (70, 4, 49, 33, 64, "bf16"),
+          (70, 32, 32, 32, 32, "f32"), (40, 5, 64, 64, 64, "f32"), (70, 8, 64, 64, 64, "f32"),
+          (70, 16, 16, 16, 16, "c64"), (40, 5, 40, 40, 40, "c64"), (65, 8, 64, 64, 64, "c64")]
+
+
+def _inputs(shape, seed):
+    rows, k, p, q, s, dtype = shape
+    sizes = ((rows, k * p), 1.0), ((k, q, p), p ** -0.5), ((k, s, q), q ** -0.5), ((rows, k * s), 1.0)
+    out = []
+    for i, (size, std) in enumerate(sizes):
+        a = synth.normal(seed + 10 * i, size, std).astype(np.float32)
+        if dtype == "c64":
+            a = (a + 1j * synth.normal(seed + 10 * i + 5, size, std)).astype(np.complex64)
+        out.append(synth.quantize(a, "bf16") if dtype == "bf16" else a)
+    return out  # x, R, L, dy
+
+
+def _dev(a, dtype):
+    return torch.from_numpy(np.ascontiguousarray(a)).cuda().to({"f32": torch.float32, "bf16": torch.bfloat16, "c64": torch.complex64}[dtype])
+
+
+def _calls(B, x, R, L, dy):
+    """y and x M (complex: x M^H) with a workspace, dx, dR, dL."""
+    if x.is_complex():
+        return dict(zip(("y", "xM", "dx", "dR", "dL"), (B.monarch_fwd_c64_ws(x, R, L), B.monarch_fwd_h_c64_ws(dy, R, L), *B.monarch_bwd_c64_ws(dy, x, R, L))))
+    return dict(zip(("y", "xM", "dx", "dR", "dL"), (B.monarch_fwd_ws(x, R, L), B.monarch_fwd_t(dy, R, L), *B.monarch_bwd(dy, x, R, L))))
+
+
+def _exact(x, R, L, dy, dtype):
+    with np.errstate(all="ignore"):
+        if dtype == "c64":
+            return dict(zip(("y", "xM", "dx", "dR", "dL"), (complex_ref.fwd(x, R, L, 0), complex_ref.fwd_h(dy, R, L, 0), *complex_ref.bwd(dy, x, R, L, 0))))
+        return dict(zip(("y", "xM", "dx", "dR", "dL"), (oracle.fwd(x, R, L), oracle.fwd_t(dy, R, L), *oracle.bwd(dy, x, R, L))))
+
+
+def _wide(t):
+    t = t.detach().cpu()
+    return t.to(torch.complex128).numpy() if t.is_complex() else t.double().numpy()
+
+
+def _times(a, power):
+    """a * 2^power in two steps: the power itself may be beyond fp32."""
+    half = power // 2
+    return (a * a.dtype.type(2.0 ** half) * a.dtype.type(2.0 ** (power - half))).astype(a.dtype)
+
+
+# The scales of the activations and of both factors.  The products are ordinary numbers, or at least normal ones; the operands are where
+# the planes would end without their scale (2^-110), among the denormal numbers (2^-132 keeps 17 bits, which the reference is given
+# too), and far above one.  A bf16 layer holds the vector between the factors in fp32: there it is that vector that is tiny or large.
+SCALES = {"f32": [(-112, 40, 0), (-126, 60, 0), (-132, 90, 0), (60, -126, 40), (0, -60, 110), (-60, -60, 100), (100, -100, 0), (-30, -60, -20), (90, 0, -60)],
+          "bf16": [(-66, -66, 100), (-60, -60, 100), (90, 0, -128), (0, 90, -100), (-30, -60, -20)]}
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_operands_at_both_ends_of_the_range(shape):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    dtype = shape[-1]
+    x, R, L, dy = _inputs(shape, 9100)
+    for scale in SCALES["bf16" if dtype == "bf16" else "f32"]:
+        xs, Rs, Ls = (_times(a, e) for a, e in zip((x, R, L), scale))
+        if dtype == "bf16":
+            xs, Rs, Ls = (synth.quantize(a, "bf16") for a in (xs, Rs, Ls))
+        xd, Rd, Ld = (_dev(a, dtype) for a in (xs, Rs, Ls))
+        y = B.monarch_fwd_c64_ws(xd, Rd, Ld) if dtype == "c64" else B.monarch_fwd_ws(xd, Rd, Ld)
+        want = complex_ref.fwd(xs, Rs, Ls, 0) if dtype == "c64" else oracle.fwd(xs, Rs, Ls)
+        got = _wide(y)
+        # between the factors there is fp32: where that vector is denormal, 2^-150 of rounding to each of its elements, against its size
+        mid = scale[0] + scale[1]
+        limit = (2e-2 if dtype == "bf16" else 1e-5) + (2.0 ** (-148 - mid) if mid < -126 else 0)
+        rel = np.linalg.norm(got - want, axis=1) / np.linalg.norm(want, axis=1)
+        print(shape, scale, "%.2e" % rel.max(), flush=True)
+        assert float(rel.max()) <= limit, (scale, float(rel.max()))
+
+
+# Blocks of the weight gradients that meet what is not finite are computed again in fp32: their finite elements are checked one column of a
+# gradient at a time, since an infinity in x takes one column of dR, and one in dy one row of dL.
+@pytest.mark.parametrize("shape", SHAPES + [(1100, 4, 96, 64, 160, "f32"), (3000, 4, 49, 49, 64, "bf16")], ids=str)
+def test_weight_gradients_of_a_batch_with_infinities(shape):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, k, p, q, s, dtype = shape
+    x, R, L, dy = _inputs(shape, 9400)
+    x[3, 5], x[rows - 1, p] = np.inf, 3e38 if dtype != "bf16" else 2.0 ** 120   # block 0; block 1
+    got = _calls(B, *(_dev(a, dtype) for a in (x, R, L, dy)))
+    want = _exact(x, R, L, dy, dtype)
+    limit = 2e-2 if dtype == "bf16" else 4e-5
+    finite = redone = 0
+    for name in ("dR", "dL"):
+        g, w = _wide(got[name]), want[name]
+        big = np.finfo(np.float32).max
+        fine = np.isfinite(w) & (np.abs(w) < big / 2)
+        assert not np.isfinite(g[~np.isfinite(w)]).any(), name
+        assert np.isfinite(g[fine]).all(), name
+        scale = np.abs(w[fine & (np.abs(w) < 1e6)]).max()
+        small = fine & (np.abs(w) < 1e6)   # beside the columns that meet 3e38
+        err = np.abs(g[small] - w[small]).max() / scale
+        print(shape, name, "%.2e of %d finite, %d not" % (err, small.sum(), (~np.isfinite(w)).sum()), flush=True)
+        assert err <= limit, (name, err)
+        finite += int(small.sum())
+        redone += int((~np.isfinite(w)).sum())
+    assert finite and redone
