@@ -19,7 +19,9 @@
 // other operand is bf16).  An accumulator takes one rounding per 16 contraction indices and product of planes, so
 // the results are closer to float64 than those of v_mfma_f32_32x32x2_f32 with one per 2 (normal operands, 192 indices: 2.0e-7 against
 // 2.5e-7; with the small products in a sum of their own, as the weight gradients have them, 0.8e-7).  What the planes cannot hold
-// (infinities, operands from 2^104 and results from 2^80 on) is found in the finished tile, which is then computed again in fp32 (op_redo).
+// (infinities, operands from 2^104 and results from 2^80 on) is found in the finished tile; those rows of it are then computed again in fp32
+// (op_redo).  With an infinity in one of every 32 rows that costs: 768 -> 768 fp32, 12608 rows, forward 82 -> 322 us and backward 230 -> 539,
+// 1024 -> 4096 fp32, 8000 rows, 169 -> 832 and 409 -> 1187.
 //
 // What bounds it: a product of two fp32 operands costs the matrix cores 6/14.4 of its time on the fp32 cores (2058 against
 // 143 TFLOP/s in a loop of MFMAs alone), and what is left is the vector work of splitting (5.5 instructions an element, once per tile that
@@ -235,44 +237,71 @@ struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32
     static constexpr int TM = WM * MT * 32, TN = WN * NT * 32;
 };
 
-// The wave's tile (32 MT rows from m0, 32 NT columns from n0) again on the fp32 matrix cores, straight from memory, sixteen
-// contraction indices to a partial sum.
+// Rows of wave (wm, wn)'s 32 x 32 tiles that hold something not finite, again on the fp32 matrix cores, straight
+// from memory, sixteen contraction indices to a partial sum.  The other rows keep their results: their operand is zero here (a weight
+// that is not finite leaves no other rows).  All tile sizes have the same groups of 32 columns, so that a row's result depends neither on
+// the rows beside it nor on the tile that was picked for the batch.
 template <typename T>
-__device__ __forceinline__ float op_element(__amdgpu_buffer_rsrc_t rs, uint32_t at)
+__device__ __forceinline__ float op_element(__amdgpu_buffer_rsrc_t rs, uint32_t at, uint32_t scalar)
 {
-    if constexpr (sizeof(T) == 4) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, at, 0, 0));
-    else return bf16_to_f32((bf16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, at, 0, 0));
+    if constexpr (sizeof(T) == 4) return __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rs, at, scalar, 0));
+    else return bf16_to_f32((bf16_t)__builtin_amdgcn_raw_buffer_load_b16(rs, at, scalar, 0));
 }
 template <typename TA, typename TB, int MT, int NT>
-__device__ __forceinline__ void op_redo(const OpDesc& d, int g, int64_t m0, int n0, int mlim, int nlim, int64_t k_lo, int64_t k_len,
+__device__ __forceinline__ void op_redo(const OpDesc& d, int g, int64_t m0, int n0, int mlim, int nlim, int wm, int wn, int64_t k_lo, int64_t k_len,
                                         int lane, f32x16 (&acc)[MT][NT])
 {
-    const TA* pa = static_cast<const TA*>(d.a.p) + g * d.a.g_s + m0 * d.a.r_s + k_lo * d.a.k_s;
-    const TB* pb = static_cast<const TB*>(d.b.p) + g * d.b.g_s + (int64_t)n0 * d.b.r_s + k_lo * d.b.k_s;
+    wm = __builtin_amdgcn_readfirstlane(wm) * (MT * 32);  // uniform, for the addresses to be
+    wn = __builtin_amdgcn_readfirstlane(wn) * (NT * 32);
+    mlim -= wm;
+    nlim -= wn;
+    const TA* pa = static_cast<const TA*>(d.a.p) + g * d.a.g_s + (m0 + wm) * d.a.r_s + k_lo * d.a.k_s;
+    const TB* pb = static_cast<const TB*>(d.b.p) + g * d.b.g_s + (int64_t)(n0 + wn) * d.b.r_s + k_lo * d.b.k_s;
     const int row = lane & 31, h = lane >> 5;
+    const uint32_t a_2k = 2u * (uint32_t)d.a.k_s * (uint32_t)sizeof(TA), b_2k = 2u * (uint32_t)d.b.k_s * (uint32_t)sizeof(TB);
 #pragma unroll
     for (int i = 0; i < MT; ++i)
 #pragma unroll
         for (int j = 0; j < NT; ++j) {
-            const bool a_in = i * 32 + row < mlim, b_in = j * 32 + row < nlim;
-            f32x16 sum, all;
+            uint32_t bad = 0;  // rows
 #pragma unroll
-            for (int r = 0; r < 16; ++r) sum[r] = all[r] = 0.f;
-#pragma clang loop unroll(disable)
-            for (int64_t k = 0; k < k_len; k += 2) {
-                const bool k_in = k + h < k_len;
-                const float a = op_element<TA>(buffer_at(pa + k * d.a.k_s), a_in && k_in ? (uint32_t)((i * 32 + row) * (int)d.a.r_s + h * (int)d.a.k_s) * (uint32_t)sizeof(TA) : kNowhere);
-                const float b = op_element<TB>(buffer_at(pb + k * d.b.k_s), b_in && k_in ? (uint32_t)((j * 32 + row) * (int)d.b.r_s + h * (int)d.b.k_s) * (uint32_t)sizeof(TB) : kNowhere);
-                sum = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, sum, 0, 0, 0);
-                if ((k & 15) == 14 || k + 2 >= k_len) {
-#pragma unroll
-                    for (int r = 0; r < 16; ++r) {
-                        all[r] += sum[r];
-                        sum[r] = 0.f;
-                    }
-                }
+            for (int r = 0; r < 16; ++r) {
+                const float v = acc[i][j][r];
+                const uint64_t off = __ballot(planes_bad(v));
+                if ((uint32_t)off) bad |= 1u << (8 * (r / 4) + r % 4);
+                if ((uint32_t)(off >> 32)) bad |= 1u << (8 * (r / 4) + 4 + r % 4);
             }
-            acc[i][j] = all;
+            if (!bad) continue;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+                const float v = acc[i][j][r];
+                acc[i][j][r] = bad >> (8 * (r / 4) + 4 * h + r % 4) & 1 ? 0.f : v;
+            }
+            const bool a_in = i * 32 + row < mlim && (bad >> row & 1), b_in = j * 32 + row < nlim;
+            const uint32_t a_at = (uint32_t)((i * 32 + row) * (int)d.a.r_s + h * (int)d.a.k_s) * (uint32_t)sizeof(TA);
+            const uint32_t b_at = (uint32_t)((j * 32 + row) * (int)d.b.r_s + h * (int)d.b.k_s) * (uint32_t)sizeof(TB);
+#pragma clang loop unroll(disable)
+            for (int64_t k = 0; k < k_len; k += 16) {
+                const auto ra = buffer_at(pa + k * d.a.k_s), rb = buffer_at(pb + k * d.b.k_s);
+                const int left = k_len - k < 16 ? (int)(k_len - k) : 16;
+                f32x16 sum;
+#pragma unroll
+                for (int r = 0; r < 16; ++r) sum[r] = 0.f;
+#pragma clang loop unroll(disable)
+                for (int u0 = 0; u0 < 8; u0 += 4) {
+                    float a[4], b[4];
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) {
+                        const bool in = 2 * (u0 + u) + h < left;
+                        a[u] = op_element<TA>(ra, a_in && in ? a_at : kNowhere, (u0 + u) * a_2k);
+                        b[u] = op_element<TB>(rb, b_in && in ? b_at : kNowhere, (u0 + u) * b_2k);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 4; ++u) sum = __builtin_amdgcn_mfma_f32_32x32x2f32(a[u], b[u], sum, 0, 0, 0);
+                }
+#pragma unroll
+                for (int r = 0; r < 16; ++r) acc[i][j][r] += sum[r];
+            }
         }
 }
 
@@ -457,8 +486,7 @@ __device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>
         for (int i = 0; i < MT; ++i)
 #pragma unroll
             for (int j = 0; j < NT; ++j) acc[i][j] *= kPlaneUnscale<PA / 3 + PB / 3>;
-        if (off)
-            op_redo<TA, TB>(d, g, m0 + wm * MT * 32, n0 + wn * NT * 32, mlim - wm * MT * 32, nlim - wn * NT * 32, k_lo, k_len, lane, acc);
+        if (off) op_redo<TA, TB>(d, g, m0, n0, mlim, nlim, wm, wn, k_lo, k_len, lane, acc);
     }
     op_store<TO, PARTIAL, MT, NT>(d, acc, outer, g, m0, n0, mlim, nlim, wm, wn, lane);
 }

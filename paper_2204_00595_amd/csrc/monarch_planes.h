@@ -39,8 +39,12 @@ __device__ __forceinline__ void plane_products(const bf16x8 (&a)[PA], const bf16
     big = mfma32(a[0], b[0], big);
 }
 
-// Whether a lane of the wave holds a result that is not finite: an infinity or NaN among the operands (an infinity times the zero planes of
-// a number is no number), or something that the scale made infinite.
+// A result that is not finite: an infinity or NaN among the operands (an infinity times the zero planes of a number is no number), or
+// something that the scale made infinite.
+__device__ __forceinline__ bool planes_bad(float v) { return (__float_as_uint(v) << 1) >= (255u << 24); }
+
+// Whether a lane of the wave holds one.  What is computed again then has to be chosen by rows of the batch: a row's result must not
+// depend on the rows beside it.
 template <int MT, int NT>
 __device__ __forceinline__ bool planes_overflowed(const f32x16 (&acc)[MT][NT])
 {
@@ -64,6 +68,26 @@ __device__ __forceinline__ bool planes_overflowed(const f32x16 (&acc)[NT])
 __device__ __forceinline__ bool planes_overflowed(const f32x16& acc)
 {
     return planes_overflowed(reinterpret_cast<const f32x16(&)[1][1]>(acc));
+}
+
+// Tiles with a column (lane % 32) for each row of the batch: the results of the rows that hold something not finite become zero, for
+// fp32 products to be added to them.  True in the lanes of these rows; the others keep their results and add products with zero.
+__device__ __forceinline__ bool planes_clear(f32x16& acc)
+{
+    bool off = false;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const float v = acc[r];
+        off |= planes_bad(v);
+    }
+    const uint64_t m = __ballot(off);
+    off = ((uint32_t)m | (uint32_t)(m >> 32)) >> (__lane_id() & 31) & 1;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const float v = acc[r];
+        acc[r] = off ? 0.f : v;
+    }
+    return off;
 }
 
 }  // namespace monarch

@@ -16,9 +16,10 @@
 // The products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), both operands as three bf16 planes that add up to the fp32
 // values (monarch_planes.h): weights when they are loaded, activations on their way to LDS or, where a wave takes them from memory
 // itself, in its registers.  A step contracts eight complex inputs with six MFMAs in place of sixteen fp32 MFMAs of twice the cycles.
-// A tile with results that are not finite is computed again in fp32 (stage_finish).  On the fp32 cores the contiguous stages took 54 us
-// at 64 blocks of 64 and 2048 rows and were bound by them (69 to 74 % busy); they take 37 to 40 now, for 134 MB each, 26 us at the
-// rate of a copy.  What is left is one tile per workgroup in flight: the weights' planes take 96 registers, so two workgroups fit a CU.
+// Rows with results that are not finite are computed again in fp32 (stage_finish; an infinity in one of every 32 rows, 64 complex blocks of
+// 64, 2048 rows: forward 73 -> 210 us, backward 223 -> 525; 64 real blocks of 64, 12000 rows: 191 -> 405 and 557 -> 2467).
+// On the fp32 cores the contiguous stages took 54 us at 64 blocks of 64 and 2048 rows and were bound by them (69 to 74 % busy); they
+// take 37 to 40 now, for 134 MB each, 26 us at the rate of a copy.  What is left is one tile per workgroup in flight: the weights' planes take 96 registers, so two workgroups fit a CU.
 // A second tile in flight took a workgroup's registers to the limit and 6 us more, a third workgroup spilled (62 us).
 // Forward and backward together: 64 blocks of 64, 2048 rows: 389 -> 300 us; 48, 1500 rows: 212 -> 159; 32, 2048 rows: 103 -> 85; 64 real
 // blocks of 64, 12000 rows: 895 -> 730.
@@ -70,13 +71,18 @@ __device__ __forceinline__ int mid_src(int g, int k, int q, bool perm_b)
 template <int P, int IN, bool REAL>
 __device__ __forceinline__ float2 act_value(const float2* __restrict__ src, int64_t rt, int row, int g, int i, int k, int64_t ld, int64_t B)
 {
-    const int64_t r = rt * kRT + row;
     if constexpr (IN == kInT) return src[(((size_t)rt * k + g) * P + i) * kRT + row];
-    if (r >= B) return make_float2(0.f, 0.f);
-    if constexpr (IN == kInNat) return src[r * ld + (size_t)g * P + i];
-    if constexpr (!REAL) return src[r * ld + (size_t)i * k + g];
-    const float* f = reinterpret_cast<const float*>(src) + r * (2 * ld) + g;
-    return make_float2(f[(size_t)(2 * i) * k], f[(size_t)(2 * i + 1) * k]);
+    const int64_t at = rt * kRT + row, r = at < B ? at : B - 1;
+    float2 v;
+    if constexpr (IN == kInNat) {
+        v = src[r * ld + (size_t)g * P + i];
+    } else if constexpr (!REAL) {
+        v = src[r * ld + (size_t)i * k + g];
+    } else {
+        const float* f = reinterpret_cast<const float*>(src) + r * (2 * ld) + g;
+        v = make_float2(f[(size_t)(2 * i) * k], f[(size_t)(2 * i + 1) * k]);
+    }
+    return at < B ? v : make_float2(0.f, 0.f);
 }
 
 // What lane (col, e = lane % 2) of the wave that owns M tile mt multiplies with input i of block g: its row of the expanded weights at
@@ -126,23 +132,30 @@ __device__ __forceinline__ void split_four(const float2 (&v)[4], bf16x8 (&b)[3])
     for (int u = 0; u < 3; ++u) b[u] = as_bf16x8(u32x4{w[0][u], w[1][u], w[2][u], w[3][u]});
 }
 
-// A finished tile: the planes' scale comes off; one with something not finite is computed again in fp32.
+// A finished tile: the planes' scale comes off, and rows with something not finite are computed again in fp32.
 template <int P, int Q, int IN, bool CONJT, bool REAL>
 __device__ __forceinline__ void stage_finish(f32x16& acc, const float2* __restrict__ in, const float2* __restrict__ W, int64_t rt, int g, int mt,
-                                           int k, int64_t ld, int64_t B, int lane)
+                                             int k, int64_t ld, int64_t B, int lane)
 {
     const bool off = planes_overflowed(acc);
     acc *= kPlaneUnscale<2>;
     if (!off) return;
+    const bool mine = planes_clear(acc);
     const int col = lane & 31, kh = lane >> 5;
-#pragma unroll
-    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+    constexpr int U = P >= 48 ? 1 : 2;  // what the weights leave room for
 #pragma clang loop unroll(disable)
-    for (int u = 0; u < P / 2; ++u) {
-        const float2 w = weight_value<P, Q, CONJT, REAL>(W, g, mt, col, 2 * u + kh);
-        const float2 x = act_value<P, IN, REAL>(in, rt, col, g, 2 * u + kh, k, ld, B);
-        acc = mfma_f32(w.x, x.x, acc);
-        acc = mfma_f32(w.y, x.y, acc);
+    for (int u0 = 0; u0 < P / 2; u0 += U) {
+        float2 w[U], x[U];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            w[u] = weight_value<P, Q, CONJT, REAL>(W, g, mt, col, 2 * (u0 + u) + kh);
+            x[u] = act_value<P, IN, REAL>(in, rt, col, g, 2 * (u0 + u) + kh, k, ld, B);
+        }
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            acc = mfma_f32(w[u].x, mine ? x[u].x : 0.f, acc);
+            acc = mfma_f32(w[u].y, mine ? x[u].y : 0.f, acc);
+        }
     }
 }
 
@@ -891,20 +904,29 @@ cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float
     if (off) {
 #pragma unroll
         for (int nt = 0; nt < NTN; ++nt) {
-#pragma unroll
-            for (int r = 0; r < 16; ++r) acc[nt][r] = 0.f;
+            if (!planes_overflowed(acc[nt])) continue;
+            const bool mine = planes_clear(acc[nt]);
             int nb = REAL ? 16 * nt + (col >> 1) : 32 * nt + col;
             if (nb >= NB) nb = NB - 1;
+#pragma clang loop unroll(disable)
             for (int64_t t = z; t < ntiles; t += Z)
 #pragma clang loop unroll(disable)
-                for (int u = 0; u < kRT / 2; ++u) {
-                    const float2 av = act_value<MA, AMODE, REAL>(A, t, 2 * u + kh, g, ma, k, lda, B);
-                    const float2 bv = act_value<NB, BMODE, REAL>(Bv, t, 2 * u + kh, g, nb, k, ldb, B);
-                    if constexpr (REAL) {
-                        acc[nt] = mfma_f32(e ? av.y : av.x, e ? bv.y : bv.x, acc[nt]);
-                    } else {
-                        acc[nt] = mfma_f32(e ? av.y : av.x, bv.x, acc[nt]);
-                        acc[nt] = mfma_f32(e ? -av.x : av.y, bv.y, acc[nt]);
+                for (int u0 = 0; u0 < kRT / 2; u0 += 2) {
+                    float2 av[2], bv[2];
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        av[u] = act_value<MA, AMODE, REAL>(A, t, 2 * (u0 + u) + kh, g, ma, k, lda, B);
+                        bv[u] = act_value<NB, BMODE, REAL>(Bv, t, 2 * (u0 + u) + kh, g, nb, k, ldb, B);
+                        if (!mine) bv[u] = make_float2(0.f, 0.f);
+                    }
+#pragma unroll
+                    for (int u = 0; u < 2; ++u) {
+                        if constexpr (REAL) {
+                            acc[nt] = mfma_f32(e ? av[u].y : av[u].x, e ? bv[u].y : bv[u].x, acc[nt]);
+                        } else {
+                            acc[nt] = mfma_f32(e ? av[u].y : av[u].x, bv[u].x, acc[nt]);
+                            acc[nt] = mfma_f32(e ? -av[u].x : av[u].y, bv[u].y, acc[nt]);
+                        }
                     }
                 }
         }

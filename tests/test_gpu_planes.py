@@ -88,6 +88,47 @@ def test_operands_at_both_ends_of_the_range(shape):
         assert float(rel.max()) <= limit, (scale, float(rel.max()))
 
 
+def _hurt(a):
+    """Rows 3, 35 and the last one with something not finite, or too large for the planes."""
+    a = a.copy()
+    a[3, 5], a[35, 1], a[-1, 2] = np.inf, 3e38, np.nan
+    return a, [3, 35, a.shape[0] - 1]
+
+
+@pytest.mark.parametrize("shape", SHAPES, ids=str)
+def test_a_row_does_not_depend_on_the_rows_beside_it(shape):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    dtype = shape[-1]
+    x, R, L, dy = _inputs(shape, 9200)
+    plain = _calls(B, *(_dev(a, dtype) for a in (x, R, L, dy)))
+    x, rows = _hurt(x)
+    dy, _ = _hurt(dy)
+    hurt = _calls(B, *(_dev(a, dtype) for a in (x, R, L, dy)))
+    keep = [i for i in range(shape[0]) if i not in rows]
+    for name in ("y", "xM", "dx"):
+        assert torch.equal(plain[name][keep], hurt[name][keep]), name
+
+
+# more rows than the array of the call without a workspace holds: slices of 512 and of 2560 rows
+@pytest.mark.parametrize("shape", [(1300, 8, 64, 512, 64, "f32"), (3000, 4, 192, 192, 192, "f32"), (1300, 8, 33, 512, 50, "bf16")], ids=str)
+def test_slices_with_infinities_give_what_one_call_gives(shape):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    dtype = shape[-1]
+    x, R, L, _ = _inputs(shape, 9300)
+    for row, value in ((0, np.inf), (40, -np.inf), (600, 3e38), (1299, np.nan)):
+        x[row, 7] = value
+    xd, Rd, Ld = (_dev(a, dtype) for a in (x, R, L))
+    one = B.monarch_fwd_ws(xd, Rd, Ld)
+    slices = torch.empty_like(one)
+    B.monarch_fwd_static(xd, Rd, Ld, slices)
+    same = (one == slices) | (one.isnan() & slices.isnan())
+    assert bool(same.all()), (~same).nonzero()[:4]
+
+
 # Blocks of the weight gradients that meet what is not finite are computed again in fp32: their finite elements are checked one column of a
 # gradient at a time, since an infinity in x takes one column of dR, and one in dy one row of dL.
 @pytest.mark.parametrize("shape", SHAPES + [(1100, 4, 96, 64, 160, "f32"), (3000, 4, 49, 49, 64, "bf16")], ids=str)
