@@ -201,6 +201,7 @@ size_t fwd_t_sq64_workspace(const Problem& pb);  // transposed multiply y = x M
 int fwd_t_sq64(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 bool bwd_sq64_supported(const Problem& pb);
 size_t bwd_sq64_workspace(const Problem& pb);
+size_t bwd_sq64_least(const Problem& pb);  // as ops_bwd_least
 int bwd_sq64(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx,
              void* dR, void* dL, void* ws, hipStream_t st);
 

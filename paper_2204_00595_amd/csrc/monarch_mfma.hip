@@ -116,7 +116,11 @@ size_t mfma_bwd_workspace(const Problem& pb)
     if (real32_mfma_supported(pb)) return real32_mfma_workspace(pb, 1);
     return 0;
 }
-size_t mfma_bwd_least(const Problem& pb) { return bwd_split_preferred(pb) ? bwd_split_least(pb) : mfma_bwd_workspace(pb); }
+size_t mfma_bwd_least(const Problem& pb)
+{
+    if (bwd_split_preferred(pb)) return bwd_split_least(pb);
+    return !bwd_wide_supported(pb) && bwd_sq64_supported(pb) ? bwd_sq64_least(pb) : mfma_bwd_workspace(pb);
+}
 const char* mfma_bwd_name(const Problem& pb)
 {
     if (bwd_wide_supported(pb)) return "mfma_bwd_wide_bf16";

@@ -620,25 +620,30 @@ bwd_sq64_stage_kernel(const Stage64 a)
     });
 }
 
-// Batch chunks of the two stages: with the eight workgroups of a chunk about one per CU, at least two steps of 32 rows each.
+// Batch chunks of the two stages: with the eight workgroups of a chunk about one per CU, at least two steps of 32 rows each, and no more
+// than fit the workspace (`room`; one chunk is the least).  bf16 gradients have bf16 partial sums, but beyond 256 rows only: up to there
+// the chunks of 64 rows would add a rounding.
 struct Plan64 {
     size_t off_u, off_du, off_rp, off_partL, off_partR, total;
-    int nz, steps;
+    int nz, steps, p_bf16;
 };
 
-Plan64 make_plan64(const Problem& pb)
+Plan64 make_plan64(const Problem& pb, size_t room = SIZE_MAX)
 {
     Plan64 pl{};
     const int64_t steps = (pb.B + ST_ROWS - 1) / ST_ROWS;
-    pl.nz = (int)(steps > 64 ? 32 : steps > 2 ? steps / 2 : 1);
-    pl.steps = (int)((steps + pl.nz - 1) / pl.nz);
+    pl.p_bf16 = pb.wgrad_f32() || pb.B <= 256 ? 0 : 1;
     size_t off = 0;
     const size_t act = align_up((size_t)(pb.B > 0 ? pb.B : 1) * N64 * 2, 256);
     pl.off_u = off;  off += act;
     pl.off_du = off; off += act;
     pl.off_rp = off; off += align_up(pb.n_R() * 2, 256);
-    pl.off_partL = off; off += align_up((size_t)pl.nz * pb.n_L() * 4, 256);
-    pl.off_partR = off; off += align_up((size_t)pl.nz * pb.n_R() * 4, 256);
+    const size_t chunk = (size_t)M64 * M64 * M64 * (pl.p_bf16 ? 2 : 4), fit = room > off ? (room - off) / (2 * chunk) : 0;
+    pl.nz = (int)(steps > 64 ? 32 : steps > 2 ? steps / 2 : 1);
+    if ((size_t)pl.nz > fit) pl.nz = fit > 1 ? (int)fit : 1;
+    pl.steps = (int)((steps + pl.nz - 1) / pl.nz);
+    pl.off_partL = off; off += pl.nz * chunk;
+    pl.off_partR = off; off += pl.nz * chunk;
     pl.total = off;
     return pl;
 }
@@ -714,12 +719,13 @@ int fwd_t_sq64(const Problem& pb, const void* x, const void* R, const void* L, v
 }
 
 size_t bwd_sq64_workspace(const Problem& pb) { return make_plan64(pb).total; }
+size_t bwd_sq64_least(const Problem& pb) { return make_plan64(pb, 0).total; }
 
 int bwd_sq64(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx,
              void* dR, void* dL, void* ws, hipStream_t st)
 {
     if (!sq64_supported(pb)) return -2;
-    const Plan64 pl = make_plan64(pb);
+    const Plan64 pl = make_plan64(pb, pb.ws_bytes);
     const bool f32out = pb.wgrad_f32();
     if (pb.B == 0) {
         int rc = f32out ? launch_fill_zero_f32((float*)dR, pb.n_R(), st) : launch_fill_zero_u16((uint16_t*)dR, pb.n_R(), st);
@@ -741,8 +747,7 @@ int bwd_sq64(const Problem& pb, const void* dy, const void* x, const void* R, co
     if (hipGetLastError() != hipSuccess) return -4;
     WgradDesc dl{}, dr{};
     dl.M = dl.N = dl.G = M64; dl.seg_w = M64;
-    // bf16 gradients: bf16 partial sums, but beyond 256 rows only (up to there the chunks of 64 rows would add a rounding)
-    dl.p_bf16 = f32out || pb.B <= 256 ? 0 : 1;
+    dl.p_bf16 = pl.p_bf16;
     dr = dl;
     dl.P = (float*)(w + pl.off_partL); dl.out = dL;
     dr.P = (float*)(w + pl.off_partR); dr.out = dR;

@@ -132,7 +132,8 @@ def test_backward_keeps_32_bits_on_short_batches(case):
 # sides of the limits of the short-batch kernels (wide: 2560 rows, shape-generic bf16: 4096), the shape-generic contractions where a
 # longer batch has fewer chunks, and those with a workspace that only the SIMT kernels can use.
 LAST = [((128, 128, 512), 4, 2561, 2560, "bf16"), ((192, 192, 192), 4, 2600, 1500, "bf16"), ((96, 96, 96), 4, 4097, 4096, "bf16"),
-        ((192, 192, 768), 4, 2049, 2048, "f32"), ((101, 37, 16), 8, 6145, 6144, "bf16"), ((192, 192, 36), 4, 0, 3072, "bf16")]
+        ((192, 192, 768), 4, 2049, 2048, "f32"), ((101, 37, 16), 8, 6145, 6144, "bf16"), ((192, 192, 36), 4, 0, 3072, "bf16"),
+        ((64, 64, 64), 64, 257, 256, "bf16")]
 
 
 @pytest.mark.parametrize("case", LAST, ids=str)
@@ -161,6 +162,26 @@ def test_workspace_of_the_largest_batch_serves_a_shorter_one(case):
     with pytest.raises(B.MonarchError) as e:  # not the partial rows of the bias gradient alone
         B.monarch_bwd_bias(dyd, xd, Rd, Ld, workspace=ws[:256])
     assert e.value.status == B.MONARCH_ERR_WORKSPACE
+
+
+# 64 blocks of 64: fp32 gradients in the room that bf16 ones ask for, and in that of a batch half as long (fewer chunks, down to one)
+@pytest.mark.parametrize("rows, room_of", [(2100, 2100), (700, 700), (300, 300), (300, 150), (257, 257)])
+def test_workspace_of_bf16_gradients_serves_fp32_ones(rows, room_of):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    sh = synth.Shape("room_%d_%d" % (rows, room_of), "bf16", rows, 64, 64, 64, 64, config=950)
+    activations = 2 * 2 * 4096
+    have = B.monarch_bwd_workspace_bytes(room_of, 4096, 64, 64, 64, 1) + activations * (rows - room_of)
+    assert have < B.monarch_bwd_workspace_bytes(rows, 4096, 64, 64, 64, 1, B.MONARCH_FLAG_WGRAD_F32)
+    x, R, L, dy = synth.make_inputs(sh)
+    want = oracle.bwd(dy, x, R, L)
+    xd, Rd, Ld, dyd = (_dev(a, "bf16") for a in (x, R, L, dy))
+    ws = torch.full((have + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    got = B.monarch_bwd(dyd, xd, Rd, Ld, workspace=ws[:have], flags=B.MONARCH_FLAG_WGRAD_F32)
+    for name, g, w in zip(("dx", "dR", "dL"), got, want):
+        parity_util.check("%s.%s" % (sh.name, name), g.float().cpu().numpy(), w, TOL["bf16"])
+    assert bool((ws[have:] == 0xA5).all())
 
 
 # batches of one chunk or a few, where a chunk's own sum is what errs; the SIMT kernels add 16 rows at a time

@@ -107,6 +107,16 @@ def test_forward_with_workspace_rejects_bad_arguments_without_a_gpu(binding):
     assert call(ws=None, ws_bytes=0, flags=binding.MONARCH_FLAG_GENERIC) == binding.MONARCH_OK
 
 
+def test_backward_workspace_of_64_blocks_of_64(binding):
+    """Beyond 256 rows no more than three copies of the activations, three of the factors and fp32 partial sums over
+    chunks of 256 rows, eight at most, beside the partial rows of the bias gradient; growing from there on."""
+    last = 0
+    for rows in (257, 288, 300, 511, 700, 1000, 1500, 2047, 2048, 2049, 3000, 4096, 16384):
+        need = binding.monarch_bwd_workspace_bytes(rows, 4096, 64, 64, 64, 1)
+        assert last <= need <= 3 * rows * 8192 + 3 * 2 * 64 ** 3 + min(8, -(-rows // 256)) * 2 * 4 * 64 ** 3 + 64 * 4096 * 4, rows
+        last = need
+
+
 def test_dense_form_rejects_bad_arguments_without_a_gpu(binding):
     L = binding.lib()
     p = 4096  # never dereferenced: every case below is refused before any launch
