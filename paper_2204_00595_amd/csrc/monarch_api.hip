@@ -109,10 +109,10 @@ size_t bwd_need(const Problem& pb, Family fam)
     return bwd_kernel_need(pb, fam) + colsum_workspace(pb);
 }
 
-// The kernels' share of a backward workspace of `bytes` bytes, (size_t)-1 if that is too short.  The chunked weight gradients of short batches
-// and of the shape-generic contractions want more room for a short batch than for a long one; with less they take fewer chunks, so
-// that a workspace of the largest batch serves every smaller one (a trainer's last, shorter batch).  The SIMT kernels need next to
-// nothing and are the last resort.
+// The kernels' share of a backward workspace of `bytes` bytes, (size_t)-1 if that is too short.  The chunked weight
+// gradients of short batches and of the shape-generic contractions want more room for a short batch than for a long
+// one; with less they take fewer chunks, so that a workspace of the largest batch serves every smaller one (a trainer's
+// last, shorter batch).  The SIMT kernels need next to nothing and are the last resort.
 size_t bwd_kernel_room(const Problem& pb, Family& fam, size_t bytes)
 {
     const size_t tail = colsum_workspace(pb), room = bytes < tail ? 0 : (bytes - tail) / 256 * 256;
@@ -155,8 +155,9 @@ int static_workspace(void** out)
     return MONARCH_OK;
 }
 
-// monarch_fwd_static on the shape-generic contractions where the vector between the factors exceeds the array.  A row's result does
-// not depend on the rows beside it, so slices of the batch, one after the other on the stream, give what one call on the whole gives.
+// monarch_fwd_static on the shape-generic contractions where the vector between the factors exceeds the array.  A row's
+// result does not depend on the rows beside it, so slices of the batch, one after the other on the stream, give what
+// one call on the whole gives.
 int fwd_static_slices(Problem pb, const void* x, const void* R, const void* L, void* y, hipStream_t st)
 {
     if (pb.flags & MONARCH_FLAG_WGRAD_F32) return MONARCH_ERR_INVALID;  // backward-only flag

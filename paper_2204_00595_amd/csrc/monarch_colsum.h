@@ -128,12 +128,12 @@ __device__ __forceinline__ void colsum_partial_body(const ColsumJob& cj, int blo
     for (int e = 0; e < CW; ++e) cj.part[(size_t)ch * n_out + col + e] = sum[e];
 }
 
-// Pass 2, workgroup `block` of colsum_final_blocks (THREADS threads): the workgroup owns 16 columns; THREADS / 16 groups of
-// lanes each add every (THREADS / 16)-th chunk partial, eight in flight, the sums of the groups meet in LDS and are added in
-// order, in 64 bits (the largest sums of all are made here), then rounded to the output type.  Every thread of the workgroup must call it.  Bound by the latency of a thread's chain
-// of loads: with 64 columns a workgroup (4 groups of 256 threads, four loads in flight) the reduction it rides on took 9.0 us at
-// 768 columns in 341 chunks and 14.1 at 4096 columns in 64, now 7.0 and 9.5 (as a launch of
-// its own, which had 1024 threads: 4.7 and 4.9).
+// Pass 2, workgroup `block` of colsum_final_blocks (THREADS threads): the workgroup owns 16 columns; THREADS / 16
+// groups of lanes each add every (THREADS / 16)-th chunk partial, eight in flight, the sums of the groups meet in LDS
+// and are added in order, in 64 bits (the largest sums of all are made here), then rounded to the output type.  Every
+// thread of the workgroup must call it.  Bound by the latency of a thread's chain of loads: with 64 columns a workgroup
+// (4 groups of 256 threads, four loads in flight) the reduction it rides on took 9.0 us at 768 columns in 341 chunks
+// and 14.1 at 4096 columns in 64, now 7.0 and 9.5 (as a launch of its own, which had 1024 threads: 4.7 and 4.9).
 template <typename TO, int THREADS>
 __device__ __forceinline__ void colsum_final_body(const ColsumJob& cj, int block)
 {

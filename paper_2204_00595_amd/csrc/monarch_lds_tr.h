@@ -7,16 +7,16 @@
 
 namespace monarch {
 
-// A row of TW features of one group is TW / 32 runs of 64 bytes in LDS, unpadded.  Half a wave of a transposing read touches one run
-// of four consecutive rows, which must fall on disjoint quarters of the 64 banks: the runs of a row change places by the row (strides
-// of one or three runs do it by themselves).
+// A row of TW features of one group is TW / 32 runs of 64 bytes in LDS, unpadded.  Half a wave of a transposing read
+// touches one run of four consecutive rows, which must fall on disjoint quarters of the 64 banks: the runs of a row
+// change places by the row (strides of one or three runs do it by themselves).
 template <int TW>
 __device__ __forceinline__ constexpr int run_key(int row)
 {
     return TW == 128 ? row & 3 : TW == 64 ? (row >> 1) & 1 : 0;
 }
-// The LDS accesses of the pipeline are written out, and the wave waits for them by itself (lgkm_wait): the compiler puts a wait for
-// everything that is on its way into LDS (buffer_load ... lds) before a transposing read it knows of.
+// The LDS accesses of the pipeline are written out, and the wave waits for them by itself (lgkm_wait): the compiler
+// puts a wait for everything that is on its way into LDS (buffer_load ... lds) before a transposing read it knows of.
 // Transposing read: within each 16 lanes, lane i receives element (i % 4) of lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4.
 template <int OFF>
 __device__ __forceinline__ u32x2 lds_tr16(uint32_t at)

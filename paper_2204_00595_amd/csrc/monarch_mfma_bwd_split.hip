@@ -17,10 +17,11 @@
 // Fragments:  WT[g][nt][t][lane][e] = W[g][16t + 4*(e/2) + 2*(lane/32) + e%2][32*nt + lane%32]: lane half h holds, of the 16 m of
 // a step, the pairs that its 16-byte pieces 2i + h of the line bring.
 //
-// What bounds it: latency for a few row tiles (three launches of about 6 us), the address path of the L1 above; the rows come in whole
-// lines that change places through LDS (RowPieces; training step of the feed-forward block of width 1024, 2000 rows: 224 -> 196 us, of width 768
-// 169 -> 150, 200 rows 106 -> 99).  Measured, GPU time of a training step: 256 -> 256 -> 1024 blocks, 200 rows 86 -> 57 us; the feed-forward
-// block of width 1024 240 -> 101 us at 200 rows, 262 -> 153 at 1000; of width 384 119 -> 69 and 134 -> 88.
+// What bounds it: latency for a few row tiles (three launches of about 6 us), the address path of the L1 above; the
+// rows come in whole lines that change places through LDS (RowPieces; training step of the feed-forward block of width
+// 1024, 2000 rows: 224 -> 196 us, of width 768 169 -> 150, 200 rows 106 -> 99).  Measured, GPU time of a training step:
+// 256 -> 256 -> 1024 blocks, 200 rows 86 -> 57 us; the feed-forward block of width 1024 240 -> 101 us at 200 rows, 262
+// -> 153 at 1000; of width 384 119 -> 69 and 134 -> 88.
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
 #include "monarch_mfma_split.h"
@@ -281,10 +282,11 @@ Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 
 }  // namespace
 
-// Up to 2560 rows, 40 row tiles of the wide backward, which takes nearly the same time for any number of them (1024 -> 4096 -> 1024
-// training step: 200 rows 240 and 101 us, 2000 rows 292 and 229, 3000 rows 328 and 310; 768 -> 3072 -> 768: 213 and 174, 235 and 241
-// at 2000 and 3000 rows).  Where the other choice is the shape-generic bf16 kernel (width 384) up to 4096.  Not where it is the
-// shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors between the factors in fp32.
+// Up to 2560 rows, 40 row tiles of the wide backward, which takes nearly the same time for any number of them (1024 ->
+// 4096 -> 1024 training step: 200 rows 240 and 101 us, 2000 rows 292 and 229, 3000 rows 328 and 310; 768 -> 3072 ->
+// 768: 213 and 174, 235 and 241 at 2000 and 3000 rows).  Where the other choice is the shape-generic bf16 kernel (width
+// 384) up to 4096.  Not where it is the shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors
+// between the factors in fp32.
 bool bwd_split_preferred(const Problem& pb)
 {
     if (!bwd_wide_supported(pb) && !tiled_bwd_supported(pb)) return false;
@@ -322,9 +324,9 @@ int bwd_split(const Problem& pb, const void* dy, const void* x, const void* R, c
     }
     dr.A = dU; dr.Bm = (const uint16_t*)x; dr.P = (float*)(w + pl.partR); dr.out = dR;
     dl.rows_per_chunk = dr.rows_per_chunk = pl.rows_per_chunk;
-    // bf16 partial sums only where the kernels of long batches have several too, beyond 256 rows: up to there the chunks of 64 rows
-    // would add a rounding (200 rows: dR and dL 2.34e-3 off float64 with fp32 sums, 2.88e-3 without; from 257 rows on 2.88e-3
-    // against 2.94e-3 in the chunks of 256)
+    // bf16 partial sums only where the kernels of long batches have several too, beyond 256 rows: up to there the
+    // chunks of 64 rows would add a rounding (200 rows: dR and dL 2.34e-3 off float64 with fp32 sums, 2.88e-3 without;
+    // from 257 rows on 2.88e-3 against 2.94e-3 in the chunks of 256)
     dl.p_bf16 = dr.p_bf16 = pb.wgrad_f32() || pb.B <= 256 ? 0 : 1;
     ColsumJob cj{};
     if (pb.dbias) {

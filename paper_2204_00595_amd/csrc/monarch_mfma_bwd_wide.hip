@@ -96,9 +96,9 @@ prep_frag_kernel(const uint16_t* __restrict__ L, const uint16_t* __restrict__ R,
 
 // ------------------------------------------------------------------------ data ----
 
-template <int P_, int Q_, int S_, int JG_, int LC_, int IG_>
+template <int P_, int Q_, int S_, int LC_, int IG_>
 struct BwdWide {
-    static constexpr int K = 4, P = P_, Q = Q_, S = S_, JG = JG_, LC = LC_, IG = IG_;
+    static constexpr int K = 4, P = P_, Q = Q_, S = S_, LC = LC_, IG = IG_;
     static constexpr int BM = 64, NB = 2;   // stage X uses 32 x 32 tiles (2 row tiles)
     static constexpr int NBT = 4;           // stages A, B use 16 x 16 tiles (4 row tiles)
     static constexpr int QK = Q / K, QT = Q / 32, KQ = K * Q;
@@ -115,7 +115,7 @@ struct BwdWide {
     static constexpr size_t max2(size_t a, size_t b) { return a > b ? a : b; }
     static constexpr size_t LDS_BYTES = max2(max2(LDS_Y1, LDS_DW), max2(LDS_DX, S1::LDS_X));
     static_assert(P % 64 == 0 && Q % 32 == 0 && S % 32 == 0 && QK % 16 == 0, "tile shapes");
-    static_assert(QT % JG == 0 && S % LC == 0 && LC % 32 == 0 && (P / 16) % IG == 0, "loop splits");
+    static_assert(S % LC == 0 && LC % 32 == 0 && (P / 16) % IG == 0, "loop splits");
     static_assert(DX_COLS % 8 == 0 && (64 % (DX_COLS / 8) == 0), "dx staging copy-out");
     static_assert(LDS_BYTES <= kMaxLdsBytes, "LDS");
 };
@@ -327,10 +327,10 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
     };
 #pragma unroll
     for (int d = 0; d < NSB - 1; ++d) issue(d, d);
-    // ACT: what leaves is multiplied by gelu'(x_pre), which costs the vector units two to three times what the tile costs the
-    // matrix cores, and a wave is alone on its SIMD: so the pieces of tile ig - 1 leave between the MFMAs of tile ig
-    // (measured where it mattered most, 1024 x 256 blocks, 16384 rows: 128 -> 117 us).  hp[i] holds the x_pre piece that task i multiplies by; it is replaced by the one
-    // of the next tile as soon as it is used.
+    // ACT: what leaves is multiplied by gelu'(x_pre), which costs the vector units two to three times what the tile
+    // costs the matrix cores, and a wave is alone on its SIMD: so the pieces of tile ig - 1 leave between the MFMAs of
+    // tile ig (measured where it mattered most, 1024 x 256 blocks, 16384 rows: 128 -> 117 us).  hp[i] holds the x_pre
+    // piece that task i multiplies by; it is replaced by the one of the next tile as soon as it is used.
     constexpr int PIECES = C::DX_COLS / 8;
     const auto pre_at = [&](int ig, int i) {
         const int t = lane + i * 64;
@@ -417,16 +417,19 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
     }
 }
 
-// The same stages for two of the four blocks kk per workgroup, two waves per block: half of the accumulators per wave, two waves per
-// SIMD and two workgroups per CU, and the two workgroups of a row tile on two CUs where the tiles alone would leave CUs idle.
+// The same stages for two of the four blocks kk per workgroup, two waves per block: half of the accumulators per wave,
+// two waves per SIMD and two workgroups per CU, and the two workgroups of a row tile on two CUs where the tiles alone
+// would leave CUs idle.
 //   X  half of the columns j per wave
 //   A  two of the four c per wave; dy comes through a DMA-filled LDS ring as it is and is picked apart where it is read
 //   B  from the dY1 tile in LDS (as bf16, which is also what goes to the workspace for dR), half of the columns i, or of the rows
 //      where the column tiles do not come out even, per wave
-// What bounds it: between L2 and L1 the weights pass once per 64 rows and dy twice, 8 to 16 TB/s in all.  Measured, this kernel
-// against the one above: 768 -> 3072, 8192 rows, 30.8 and 36.9 us; blocks of 256 x 1024, 16384 rows, 106.8 + 96.0 and 117.5 + 97.6.
-// More chunks of dy or of fragments on the way change nothing; 128 rows per workgroup (43.5; 109.4 + 100.5) and all four blocks in
-// eight waves (the whole training step 516 us against 518, but 300 against 287 at 192 x 768 and 40000 rows) do not pay.
+// What bounds it: between L2 and L1 the weights pass once per 64 rows and dy twice, 8 to 16 TB/s in all.  Measured,
+// this kernel against the one above: 768 -> 3072, 8192 rows, 30.8 and 36.9 us; blocks of 256 x 1024, 16384 rows, 106.8
+// + 96.0 and 117.5 + 97.6.
+// More chunks of dy or of fragments on the way change nothing; 128 rows per workgroup (43.5; 109.4 + 100.5) and all
+// four blocks in eight waves (the whole training step 516 us against 518, but 300 against 287 at 192 x 768 and 40000
+// rows) do not pay.
 template <int P_, int Q_, int S_>
 struct BwdPair {
     static constexpr int K = 4, P = P_, Q = Q_, S = S_, IG = 4;
@@ -502,8 +505,9 @@ bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, c
 #pragma unroll
     for (int t = 0; t < 2 * C::JT * C::NBT; ++t) accA[t] = f32x4{0.f, 0.f, 0.f, 0.f};
 
-    // dy arrives in chunks of 32 l, as it is, through an LDS ring filled in whole 256-byte pieces of its rows, three chunks ahead.
-    // 16-byte piece u of a row (l = 2u, 2u + 1 of all four c) lies in place u ^ (row % 16): the reads of 16 rows are conflict-free.
+    // dy arrives in chunks of 32 l, as it is, through an LDS ring filled in whole 256-byte pieces of its rows, three
+    // chunks ahead. 16-byte piece u of a row (l = 2u, 2u + 1 of all four c) lies in place u ^ (row % 16): the reads of
+    // 16 rows are conflict-free.
     constexpr int NC = C::S / 32, DPT = C::BM * 16 / 256;  // chunks; requests of a thread per chunk
     const int64_t rows = B - b0 < C::BM ? B - b0 : C::BM;  // rows past the end read as zeros
     const auto dyb = __builtin_amdgcn_make_buffer_rsrc(const_cast<uint16_t*>(dy) + b0 * C::N_OUT, 0, (int)rows * C::N_OUT * 2, 0x00020000);
@@ -537,7 +541,8 @@ bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, c
         for (int par = 0; par < 2; ++par) {
             const int n = n0 + par;
             __builtin_amdgcn_sched_barrier(0);
-            // chunk n has landed once only what was requested after it is outstanding: the two chunks behind it, a chunk's fragments
+            // chunk n has landed once only what was requested after it is outstanding: the two chunks behind it, a
+            // chunk's fragments
             wait_vmcnt<2 * DPT + 2 * C::JT>();
             lds_barrier();  // ... for every wave, and nobody reads chunk n-1 any more
             issue_l(n + 1, par ^ 1);
@@ -672,10 +677,11 @@ bwd_pair_data_kernel(const uint16_t* dy, const uint16_t* x, const uint16_t* XF, 
     bwd_pair_data<C, MODE, ACT>(dy, x, XF, LF, RF, dx, Y1ws, dY1ws, x_pre, B);
 }
 
-// Where two workgroups share a row tile (bwd_pair_data_kernel), whole backward at 6000, 12000 and 40000 rows, with it and without:
-// blocks of 192 and more always (192 x 768: 65 and 73 us, 94 and 94, 286 and 300; 256 x 1024: 85 and 98, 126 and 126, 380 and 403;
-// 1024 x 256: 100 and 111, 140 and 144, 442 and 462); smaller ones up to 128 tiles, which alone would leave CUs idle (128 x 512: 46
-// and 50 us, 65 and 62, 148 and 151; 512 x 128: 47 and 53, 65 and 65, 180 and 168).
+// Where two workgroups share a row tile (bwd_pair_data_kernel), whole backward at 6000, 12000 and 40000 rows, with it
+// and without: blocks of 192 and more always (192 x 768: 65 and 73 us, 94 and 94, 286 and 300; 256 x 1024: 85 and 98,
+// 126 and 126, 380 and 403; 1024 x 256: 100 and 111, 140 and 144, 442 and 462); smaller ones up to 128 tiles, which
+// alone would leave CUs idle (128 x 512: 46 and 50 us, 65 and 62, 148 and 151; 512 x 128: 47 and 53, 65 and 65, 180 and
+// 168).
 bool pairs(const Problem& pb) { return pb.q > 128 || (pb.B + 63) / 64 <= 128; }
 
 template <typename K>
@@ -691,11 +697,11 @@ int launch_data_on(K kern, size_t lds, int64_t grid, const Problem& pb, const vo
 }
 
 // no workspace for dY1: dx only; dY1 but no Y1 workspace: the forward saved that vector, or it is made elsewhere
-template <int P, int Q, int S, int JG, int LC, int IG>
+template <int P, int Q, int S, int LC, int IG>
 int launch_data(const Problem& pb, const void* dy, const void* x, const uint16_t* XF, const uint16_t* LF,
                 const uint16_t* RF, void* dx, uint16_t* Y1ws, uint16_t* dY1ws, hipStream_t st)
 {
-    using C = BwdWide<P, Q, S, JG, LC, IG>;
+    using C = BwdWide<P, Q, S, LC, IG>;
     const int64_t tiles = (pb.B + 63) / 64;
     auto run = [&](auto kern) { return launch_data_on(kern, C::LDS_BYTES, tiles, pb, dy, x, XF, LF, RF, dx, Y1ws, dY1ws, st); };
     if (!dY1ws) return pb.x_pre ? -2 : run(bwd_wide_data_kernel<C, 1, false>);
@@ -720,22 +726,22 @@ struct Entry {
               uint16_t*, uint16_t*, hipStream_t);
 };
 
-//                                 P     Q     S   JG   LC  IG
+//                                    P    Q    S   LC  IG
 const Entry kTable[] = {
-    {192, 192, 192, 4, launch_data<192, 192, 192, 6, 192, 4>},
-    {192, 192, 768, 4, launch_data<192, 192, 768, 6, 192, 4>},
-    {256, 256, 1024, 4, launch_data<256, 256, 1024, 4, 128, 4>},
-    {1024, 256, 256, 4, launch_data<1024, 256, 256, 4, 128, 4>},
-    {768, 192, 192, 4, launch_data<768, 192, 192, 6, 192, 4>},
-    {256, 256, 256, 4, launch_data<256, 256, 256, 4, 128, 4>},
-    {192, 192, 576, 4, launch_data<192, 192, 576, 6, 192, 4>},
-    {256, 256, 768, 4, launch_data<256, 256, 768, 4, 128, 4>},
-    {128, 128, 128, 4, launch_data<128, 128, 128, 4, 128, 4>},
-    {128, 128, 512, 4, launch_data<128, 128, 512, 4, 128, 4>},
-    {512, 128, 128, 4, launch_data<512, 128, 128, 4, 128, 4>},
-    {64, 64, 64, 4, launch_data<64, 64, 64, 2, 64, 4>},
-    {64, 64, 128, 4, launch_data<64, 64, 128, 2, 64, 4>},
-    {128, 64, 64, 4, launch_data<128, 64, 64, 2, 64, 4>},
+    {192, 192, 192, 4, launch_data<192, 192, 192, 192, 4>},
+    {192, 192, 768, 4, launch_data<192, 192, 768, 192, 4>},
+    {256, 256, 1024, 4, launch_data<256, 256, 1024, 128, 4>},
+    {1024, 256, 256, 4, launch_data<1024, 256, 256, 128, 4>},
+    {768, 192, 192, 4, launch_data<768, 192, 192, 192, 4>},
+    {256, 256, 256, 4, launch_data<256, 256, 256, 128, 4>},
+    {192, 192, 576, 4, launch_data<192, 192, 576, 192, 4>},
+    {256, 256, 768, 4, launch_data<256, 256, 768, 128, 4>},
+    {128, 128, 128, 4, launch_data<128, 128, 128, 128, 4>},
+    {128, 128, 512, 4, launch_data<128, 128, 512, 128, 4>},
+    {512, 128, 128, 4, launch_data<512, 128, 128, 128, 4>},
+    {64, 64, 64, 4, launch_data<64, 64, 64, 64, 4>},
+    {64, 64, 128, 4, launch_data<64, 64, 128, 64, 4>},
+    {128, 64, 64, 4, launch_data<128, 64, 64, 64, 4>},
 };
 
 const Entry* find(const Problem& pb)

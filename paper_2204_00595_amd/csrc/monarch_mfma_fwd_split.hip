@@ -8,13 +8,15 @@
 //   stage 2   workgroup = (row tile, NT column tiles of 32): wave c computes block c (again nothing is loaded twice);
 //             the four blocks of an output row are interleaved through LDS and leave in whole rows
 //
-// U and the weights come in 1 KiB fragments straight from memory to registers; the rows of x do too where there are few tiles, and
-// else in whole lines that change places through LDS (RowPieces).
-// What bounds it: latency for one row tile (two launches of about 3.5 us), above that the address path of the L1: 20 cycles a fragment
-// for MFMAs of 32 cycles on four SIMDs.  With U in rows, a fragment of it took 62 cycles, and so did one of x (1531 rows: the stages of
-// 1024 -> 4096 5.8 + 16.4 -> 5.2 + 15.5 us, the second one now bound by the nonlinearity, of 4096 -> 1024 12.8 + 7.6 -> 10.4 + 5.2).
-// Measured, 1024 -> 4096 -> 1024 with bias and GELU, against the fused kernel alone and against U in rows: 8 rows 54, 15.7 and 13.9 us, 256 rows
-// 66, 19.9 and 18.6, 1531 rows 69, 40.1 and 32.7; 768 -> 3072 -> 768, 1531 rows: 33.0 and 25.6.
+// U and the weights come in 1 KiB fragments straight from memory to registers; the rows of x do too where there are few
+// tiles, and else in whole lines that change places through LDS (RowPieces).
+// What bounds it: latency for one row tile (two launches of about 3.5 us), above that the address path of the L1: 20
+// cycles a fragment for MFMAs of 32 cycles on four SIMDs.  With U in rows, a fragment of it took 62 cycles, and so did
+// one of x (1531 rows: the stages of 1024 -> 4096 5.8 + 16.4 -> 5.2 + 15.5 us, the second one now bound by the
+// nonlinearity, of 4096 -> 1024 12.8 + 7.6 -> 10.4 + 5.2).
+// Measured, 1024 -> 4096 -> 1024 with bias and GELU, against the fused kernel alone and against U in rows: 8 rows 54,
+// 15.7 and 13.9 us, 256 rows 66, 19.9 and 18.6, 1531 rows 69, 40.1 and 32.7; 768 -> 3072 -> 768, 1531 rows: 33.0 and
+// 25.6.
 #include "../../include/monarch.h"
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
@@ -170,10 +172,11 @@ bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
            pb.q <= 256;
 }
 
-// Where there is a fused kernel, up to 3072 rows (48 of its row tiles; it takes the same time for any number of them): 1024 -> 4096
-// -> 1024, both layers with the nonlinearity, 2600 rows 70 and 46 us; 768 -> 3072 alone 3500 rows 17.4 and 21.3, 3072 -> 768 28.0 and 27.0; 512 -> 2048
-// alone 13.2 and 15.3, 2048 -> 512 17.1 and 15.2.  Where the other choice is the shape-generic kernel (width 384: 47 us for 300 rows, 60 for 8000), up to
-// 8192.  And only where it all fits the static workspace, so that monarch_fwd_static runs the same kernels as monarch_fwd_ws.
+// Where there is a fused kernel, up to 3072 rows (48 of its row tiles; it takes the same time for any number of them):
+// 1024 -> 4096 -> 1024, both layers with the nonlinearity, 2600 rows 70 and 46 us; 768 -> 3072 alone 3500 rows 17.4 and
+// 21.3, 3072 -> 768 28.0 and 27.0; 512 -> 2048 alone 13.2 and 15.3, 2048 -> 512 17.1 and 15.2.  Where the other choice
+// is the shape-generic kernel (width 384: 47 us for 300 rows, 60 for 8000), up to 8192.  And only where it all fits the
+// static workspace, so that monarch_fwd_static runs the same kernels as monarch_fwd_ws.
 bool fwd_split_preferred(const Problem& pb)
 {
     return fwd_split_supported(pb) && pb.B > 0 && pb.B <= (fwd_frag_supported(pb) ? 3072 : 8192) &&

@@ -13,14 +13,16 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<void*>(p), 0, 0x7fffffffu, 0x00020000);
 }
 
-// 32 rows x 128 bytes of a matrix in memory -> a lane's four 16-byte pieces 2 i + lane / 32 of row lane % 32, which is how the MFMAs
-// want them.  Loaded like that a load touches 32 rows and takes the L1 62 cycles (rows of 1024, 2048 or 3072 bytes); with eight lanes
-// on the 128 bytes of a row it takes 20, and the pieces change places through LDS that the wave owns.
+// 32 rows x 128 bytes of a matrix in memory -> a lane's four 16-byte pieces 2 i + lane / 32 of row lane % 32, which is
+// how the MFMAs want them.  Loaded like that a load touches 32 rows and takes the L1 62 cycles (rows of 1024, 2048 or
+// 3072 bytes); with eight lanes on the 128 bytes of a row it takes 20, and the pieces change places through LDS that
+// the wave owns.
 constexpr int kTurnRow = 72;                            // bf16 values of a row there: an odd number of 16-byte units
 constexpr size_t kTurnBytes = 32 * kTurnRow * 2;        // per wave
 struct RowPieces {
     u32x4 v[4];
-    // at: byte offset of the first row's 128 bytes; ld: bytes of a row; rows: rows there are; pieces: 16-byte pieces there are (even)
+    // at: byte offset of the first row's 128 bytes; ld: bytes of a row; rows: rows there are; pieces: 16-byte pieces
+    // there are (even)
     __device__ __forceinline__ void fetch(__amdgpu_buffer_rsrc_t rs, uint32_t at, uint32_t ld, int rows, int pieces, int lane)
     {
         const uint32_t mine = at + (uint32_t)(lane >> 3) * ld + (lane & 7) * 16;
@@ -41,10 +43,11 @@ struct RowPieces {
     }
 };
 
-// acc[nb][nt] += (32 rows nb) x (32 columns nt) over `steps` K-steps, at most 4 * NG.  a_at / w_at: byte offsets of this lane's
-// first piece (kNowhere: a row or tile that does not exist), a_step / w_step: from one K-step to the next; W_FIRST: the weights are the first MFMA operand (the result is
-// transposed).  Loads are issued four K-steps at a time, `AHEAD` such groups
-// ahead; the trip count is a template parameter because loads past the end, even of nothing, cost as much as real ones.
+// acc[nb][nt] += (32 rows nb) x (32 columns nt) over `steps` K-steps, at most 4 * NG.  a_at / w_at: byte offsets of
+// this lane's first piece (kNowhere: a row or tile that does not exist), a_step / w_step: from one K-step to the next;
+// W_FIRST: the weights are the first MFMA operand (the result is transposed).  Loads are issued four K-steps at a time,
+// `AHEAD` such groups ahead; the trip count is a template parameter because loads past the end, even of nothing, cost
+// as much as real ones.
 // TURN (NB = 1): the rows, of a_ld bytes, are read in whole lines (RowPieces); a_at is the uniform offset of the first.
 template <int NB, int NT, int NG, int AHEAD, bool W_FIRST, bool TURN>
 __device__ __forceinline__ void tile_product(const void* a, const uint32_t (&a_at)[NB], uint32_t a_step, const void* w, const uint32_t (&w_at)[NT],
@@ -102,11 +105,12 @@ __device__ __forceinline__ bool split_index(const SplitGrid& gr, int bid, int& r
     return rt < gr.row_tiles;
 }
 
-// Step 1 for one workgroup: Y1 of 32 * NB rows, block kk, NT column tiles of 32.  The four waves share out the contraction, so that
-// every byte of x and R the workgroup needs is loaded once, and add up their tiles through LDS (split_stage1_lds bytes).
-// DIRECT: W is R as it is (read in 16-byte pieces of its rows, like x), else the packed copy RF1.  NATURAL: out[b][kk*Q + j], else
-// the order the packed L contracts, (j/4, kk, j%4), in MFMA fragments: out[b/32][j/4][h][row][e] = element 8 h + e of the 16
-// (kk, j%4) of row b % 32, with no more rows in the last tile than there are.
+// Step 1 for one workgroup: Y1 of 32 * NB rows, block kk, NT column tiles of 32.  The four waves share out the
+// contraction, so that every byte of x and R the workgroup needs is loaded once, and add up their tiles through LDS
+// (split_stage1_lds bytes).
+// DIRECT: W is R as it is (read in 16-byte pieces of its rows, like x), else the packed copy RF1.  NATURAL: out[b][kk*Q
+// + j], else the order the packed L contracts, (j/4, kk, j%4), in MFMA fragments: out[b/32][j/4][h][row][e] = element 8
+// h + e of the 16 (kk, j%4) of row b % 32, with no more rows in the last tile than there are.
 template <int NB, int NT, bool TURN>
 constexpr size_t split_stage1_lds() { return (size_t)4 * NB * NT * 4096 + (TURN ? 4 * kTurnBytes : 0); }
 template <int NB, int NT, int NG, int AHEAD, bool DIRECT, bool NATURAL, bool TURN>

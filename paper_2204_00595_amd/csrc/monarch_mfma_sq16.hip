@@ -352,7 +352,8 @@ bwd_sq16_kernel(const float* __restrict__ dy, const float* __restrict__ x, const
 #pragma unroll
         for (int v = 0; v < 16; ++v) dya[v] = *reinterpret_cast<const f32x4*>(p + 4 * v) * m;
     };
-    // daq[cq][u] = dy[b0 + 4h + u][16*bl + 4cq .. +3]: the same rows "down the batch" for the dL product (read back from the tile)
+    // daq[cq][u] = dy[b0 + 4h + u][16*bl + 4cq .. +3]: the same rows "down the batch" for the dL product (read back
+    // from the tile)
     f32x4 xa[16], dya[16], daq[4][4];
     if (tile < ntiles) {  // in flight while the weights are staged
         load_x(tile, xa);
@@ -629,12 +630,14 @@ reduce_sq16_kernel(const float* __restrict__ P, float* __restrict__ dR, float* _
     }
 }
 
-// The shortest batches: one launch without partial gradients.  With m = k = 16 a block of either gradient needs one column of the other
-// factor only (dY1[b][kk][j] = sum_l L[j][l][kk] dy[b][16l + j], U[b][c][r] = sum_i R[r][c][i] x[b][16r + i]), so sixteen workgroups own a
-// block kk of dR and of dx, sixteen a block c of dL, each over the whole batch, and together they do the work once.  The sums are short
-// and strided: fused multiply-adds, 64 rows at a time, thread (row, four columns), then thread (row, column) of the gradient's block.
-// Bound by latency: a chunk is one round of loads, two passes through LDS and a sum over its rows, 1.7 us each.  Forward and backward
-// of 64 rows 10.8 -> 7.7 us, 128 rows 11.0 -> 8.8, 192 rows 11.1 -> 10.5, 256 rows 11.2 and 12.3: up to 192 rows.
+// The shortest batches: one launch without partial gradients.  With m = k = 16 a block of either gradient needs one
+// column of the other factor only (dY1[b][kk][j] = sum_l L[j][l][kk] dy[b][16l + j], U[b][c][r] = sum_i R[r][c][i]
+// x[b][16r + i]), so sixteen workgroups own a block kk of dR and of dx, sixteen a block c of dL, each over the whole
+// batch, and together they do the work once.  The sums are short and strided: fused multiply-adds, 64 rows at a time,
+// thread (row, four columns), then thread (row, column) of the gradient's block.
+// Bound by latency: a chunk is one round of loads, two passes through LDS and a sum over its rows, 1.7 us each.
+// Forward and backward of 64 rows 10.8 -> 7.7 us, 128 rows 11.0 -> 8.8, 192 rows 11.1 -> 10.5, 256 rows 11.2 and 12.3:
+// up to 192 rows.
 constexpr int64_t kBlockRows = 192;
 __global__ void __launch_bounds__(256)
 bwd_sq16_block_kernel(const float* __restrict__ dy, const float* __restrict__ x, const float* __restrict__ R, const float* __restrict__ L,

@@ -29,9 +29,9 @@
 //   stage L     dy, U -> dU (to the workspace) and dL's partial sums
 //   stage R     dU, x -> dx and dR's partial sums        (both: bwd_sq64_stage_kernel)
 //   reduce      the sums over the batch chunks (monarch_mfma_wgrad.hip)
-// What bounds it: memory.  U, dU and the inputs are read and written 8 times in all (1.07 GB at 16384 rows); the transposed dy, dY1
-// and separate weight-gradient products that this replaced moved 1.47 GB (training step, 16384 rows: 379 -> 325 us; the backward
-// alone 311 -> 260, at 1000 rows 61 -> 52, at 64 rows 51 -> 43).
+// What bounds it: memory.  U, dU and the inputs are read and written 8 times in all (1.07 GB at 16384 rows); the
+// transposed dy, dY1 and separate weight-gradient products that this replaced moved 1.47 GB (training step, 16384 rows:
+// 379 -> 325 us; the backward alone 311 -> 260, at 1000 rows 61 -> 52, at 64 rows 51 -> 43).
 // The transposed multiply transposes its input rows and runs both adjoint steps in one kernel.
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
@@ -305,16 +305,15 @@ fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R,
 
 // ------------------------------------------------------------------------ pack ----
 
-// A 64-block factor W[blk][out][in] (64 x 64 each) in MFMA fragment order, for up to three factors in
+// A 64-block factor W[blk][out][in] (64 x 64 each) in MFMA fragment order, for one or two factors in
 // one launch:  dst[blk][t2][u][lane][e] = W'[blk][32*t2 + lane%32][32*(lane/32) + 8*u + e], where W' = W,
-// or W' = W^T per block (tr: the backward multiplies by the transposed factors).  One thread = one
+// or W' = W^T per block (tr: the transposed multiply takes the transposed factors).  One thread = one
 // 16-byte piece; 32768 pieces per factor.
 struct Pack64Job { const uint16_t* src; uint16_t* dst; int tr; };
 __global__ void __launch_bounds__(256)
-pack64_kernel(Pack64Job j0, Pack64Job j1, Pack64Job j2)
+pack64_kernel(Pack64Job j0, Pack64Job j1)
 {
-    const int which = blockIdx.x >> 7;  // 128 blocks of 256 pieces per factor
-    const Pack64Job& j = which == 0 ? j0 : (which == 1 ? j1 : j2);
+    const Pack64Job& j = blockIdx.x >> 7 ? j1 : j0;  // 128 workgroups of 256 pieces per factor
     const int pc = (blockIdx.x & 127) * 256 + threadIdx.x;
     const int lane = pc & 63, ln = lane & 31, g = lane >> 5;
     const int rest = pc >> 6, u = rest & 3, t2 = (rest >> 2) & 1, blk = rest >> 3;
@@ -413,15 +412,16 @@ u_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R /* 
 //   L:  in = dy, other = U (as u_sq64_kernel leaves it), out = dU
 //   R:  in = dU, other = x, out = dx  (dU[b][64 j + kk] is dY1[b][kk][j]: the permutation between the factors is again a
 //       column of every block, so that both launches are the same kernel on what the one before wrote)
-// Workgroup = eight blocks c0 .. c0+7 and every nz-th 32 rows of the batch, wave = one block: W[c] in registers as the operand of the first
-// product, dW[c] in registers as the sum of the second.  A step is 32 rows.  `in` comes in pieces of eight c (16 bytes of every
-// 128-byte line; the workgroups of the other c read the rest of the lines at about the same time on the same XCD), is turned to
-// [c][row][l] in registers and LDS and read twice, as rows for `out` and transposed for dW; the wave's columns of `other` travel
-// straight into an LDS ring of its own.  One barrier per step, rows requested two (in) and three (other) steps ahead.
-// At 16384 rows 95 us, 402 MB at 4.2 TB/s; the pieces of `in` cost eight times their bytes between L2 and L1, which is why
-// eight blocks share a workgroup and not fewer.  All workgroups walk the batch together, the first launch from its end, so that each
-// finds in the memory-side cache what the launch before wrote last (both stages with chunks of consecutive rows: 334 us against 325
-// for the training step).
+// Workgroup = eight blocks c0 .. c0+7 and every nz-th 32 rows of the batch, wave = one block: W[c] in registers as the
+// operand of the first product, dW[c] in registers as the sum of the second.  A step is 32 rows.  `in` comes in pieces
+// of eight c (16 bytes of every 128-byte line; the workgroups of the other c read the rest of the lines at about the
+// same time on the same XCD), is turned to [c][row][l] in registers and LDS and read twice, as rows for `out` and
+// transposed for dW; the wave's columns of `other` travel straight into an LDS ring of its own.  One barrier per step,
+// rows requested two (in) and three (other) steps ahead.
+// At 16384 rows 95 us, 402 MB at 4.2 TB/s; the pieces of `in` cost eight times their bytes between L2 and L1, which is
+// why eight blocks share a workgroup and not fewer.  All workgroups walk the batch together, the first launch from its
+// end, so that each finds in the memory-side cache what the launch before wrote last (both stages with chunks of
+// consecutive rows: 334 us against 325 for the training step).
 constexpr int ST_ROWS = 32;
 constexpr int ST_IN = 8 * ST_ROWS * 128;     // bytes of a step's `in`: two buffers
 constexpr int ST_RING = 3 * ST_ROWS * 128;   // a wave's ring of `other`
@@ -620,9 +620,9 @@ bwd_sq64_stage_kernel(const Stage64 a)
     });
 }
 
-// Batch chunks of the two stages: with the eight workgroups of a chunk about one per CU, at least two steps of 32 rows each, and no more
-// than fit the workspace (`room`; one chunk is the least).  bf16 gradients have bf16 partial sums, but beyond 256 rows only: up to there
-// the chunks of 64 rows would add a rounding.
+// Batch chunks of the two stages: with the eight workgroups of a chunk about one per CU, at least two steps of 32 rows
+// each, and no more than fit the workspace (`room`; one chunk is the least).  bf16 gradients have bf16 partial sums,
+// but beyond 256 rows only: up to there the chunks of 64 rows would add a rounding.
 struct Plan64 {
     size_t off_u, off_du, off_rp, off_partL, off_partR, total;
     int nz, steps, p_bf16;
@@ -679,7 +679,7 @@ int fwd_sq64_ws(const Problem& pb, const void* x, const void* R, const void* L, 
     uint16_t* Lp = (uint16_t*)((char*)ws + align_up(pb.n_R() * 2, 256));
     if (!pb.ws_packed()) {
         const Pack64Job jr{(const uint16_t*)R, Rp, 0}, jl{(const uint16_t*)L, Lp, 0};
-        hipLaunchKernelGGL(pack64_kernel, dim3(2 * 128), dim3(256), 0, st, jr, jl, jl);
+        hipLaunchKernelGGL(pack64_kernel, dim3(2 * 128), dim3(256), 0, st, jr, jl);
         if (hipGetLastError() != hipSuccess) return -4;
     }
     auto kern = fwd_sq64_kernel<true>;
@@ -709,7 +709,7 @@ int fwd_t_sq64(const Problem& pb, const void* x, const void* R, const void* L, v
     uint16_t* LT = (uint16_t*)(w + align_up((size_t)pb.B * N64 * 2, 256));
     uint16_t* RT = LT + align_up((size_t)M64 * M64 * M64 * 2, 256) / 2;
     const Pack64Job jlt{(const uint16_t*)L, LT, 1}, jrt{(const uint16_t*)R, RT, 1};
-    hipLaunchKernelGGL(pack64_kernel, dim3(2 * 128), dim3(256), 0, st, jlt, jrt, jrt);
+    hipLaunchKernelGGL(pack64_kernel, dim3(2 * 128), dim3(256), 0, st, jlt, jrt);
     hipLaunchKernelGGL(transpose64_kernel, dim3((unsigned)pb.B), dim3(256), 0, st, (const uint16_t*)x, xT);
     if (hipGetLastError() != hipSuccess) return -4;
     if (allow_dynamic_lds((const void*)fwd_t_sq64_kernel, SQ_LDS) != hipSuccess)
@@ -742,7 +742,7 @@ int bwd_sq64(const Problem& pb, const void* dy, const void* x, const void* R, co
         allow_dynamic_lds((const void*)bwd_sq64_stage_kernel, ST_LDS) != hipSuccess)
         return -4;
     const Pack64Job jr{(const uint16_t*)R, Rp, 0};
-    hipLaunchKernelGGL(pack64_kernel, dim3(128), dim3(256), 0, st, jr, jr, jr);
+    hipLaunchKernelGGL(pack64_kernel, dim3(128), dim3(256), 0, st, jr, jr);
     hipLaunchKernelGGL(u_sq64_kernel, dim3((unsigned)grid), dim3(512), SQ_LDS, st, (const uint16_t*)x, Rp, U, pb.B);
     if (hipGetLastError() != hipSuccess) return -4;
     WgradDesc dl{}, dr{};

@@ -24,11 +24,12 @@
 // took 31.2 us where this takes 29.7 (768 -> 3072, 8192 rows; whole training step 101.4 -> 99.2), 80.4 + 76.3 where this takes
 // 77.8 + 72.8 (feed-forward block of width 1024, 16384 rows; 551 -> 546).
 //
-// The bias gradient, the column sums of dy, comes with dL: a wave adds up the fragments of dy it multiplies (v_dot2 against ones,
-// five instructions for eight rows), in the tiles of the first columns n alone.  A pass of its own over dy cost more than the
-// products slow down (GPU time of the training step of the feed-forward block of width 1024, 16384 rows: 583 -> 565 us; the launch
-// that did it beside the weights' re-layout 26.9 + 11.6 -> 6.0 + 5.6, the two launches of products 153 -> 160; 768 -> 768, 12608
-// rows: 6.3 -> 3.0 against 24.2 -> 24.8).  The sums are off float64 by 2.8e-8 (12608 rows), those of that pass were by 6.3e-8.
+// The bias gradient, the column sums of dy, comes with dL: a wave adds up the fragments of dy it multiplies (v_dot2
+// against ones, five instructions for eight rows), in the tiles of the first columns n alone.  A pass of its own over
+// dy cost more than the products slow down (GPU time of the training step of the feed-forward block of width 1024,
+// 16384 rows: 583 -> 565 us; the launch that did it beside the weights' re-layout 26.9 + 11.6 -> 6.0 + 5.6, the two
+// launches of products 153 -> 160; 768 -> 768, 12608 rows: 6.3 -> 3.0 against 24.2 -> 24.8).  The sums are off float64
+// by 2.8e-8 (12608 rows), those of that pass were by 6.3e-8.
 #include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
@@ -114,8 +115,9 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
         pb[t] = (uint32_t)(r * d.ldb + (g0 + g) * d.b_g + (n / d.seg_w) * d.b_seg + (n % d.seg_w)) * 2;
     }
 
-    // Rows r0 .. r0+KB-1 of the chunk; rows past its end load nothing and read as zeros: a buffer load at an offset past the buffer's end.  A branch around each load instead makes the compiler lose
-    // count of the loads in flight and wait for all of them.
+    // Rows r0 .. r0+KB-1 of the chunk; rows past its end load nothing and read as zeros: a buffer load at an offset
+    // past the buffer's end.  A branch around each load instead makes the compiler lose count of the loads in flight
+    // and wait for all of them.
     auto rows_left = [&](int64_t r0) { return nrows - r0 < KB ? (int)(nrows - r0) : KB; };
     auto load_a = [&](int64_t r0, int stg, int t) {
         const auto buf = buffer_at(d.A + (row_lo + r0) * d.lda);
@@ -281,9 +283,9 @@ __device__ __forceinline__ void wgrad_gemm_body(const WgradDesc& d, const int ti
         }
     }
 
-    // Partial tiles P[z][g][m][n].  A lane holds, of each 32 x 32 tile, the m = lane % 32 and four n of every eight: the wave turns
-    // the tile through its own piece of LDS (4 KB) into rows of whole 16-byte stores.  (A 2-byte store per element instead: 0.8 us more at
-    // 768 -> 768, 12608 rows.)
+    // Partial tiles P[z][g][m][n].  A lane holds, of each 32 x 32 tile, the m = lane % 32 and four n of every eight:
+    // the wave turns the tile through its own piece of LDS (4 KB) into rows of whole 16-byte stores.  (A 2-byte store
+    // per element instead: 0.8 us more at 768 -> 768, 12608 rows.)
     const bool live = g0 + grp < d.G;  // (the group count need not be a multiple of four)
     const int ln = lane & 31, h = lane >> 5;
     const size_t pbase = (((size_t)zi * d.G + g0 + grp) * d.M) * d.N;

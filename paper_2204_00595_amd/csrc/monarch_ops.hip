@@ -13,27 +13,31 @@
 // With MONARCH_FLAG_PERM_B the vector between the factors is kept in stage-1 order and the strides on either side of it
 // change places.  So there is one contraction, ops_gemm: O[g][m][n] = sum_k A[g][m][k] B[g][n][k].
 //
-// Precision: U and dU are fp32 for both types, as in the SIMT kernels; bf16 layers are rounded once, when a result is stored.
-// Everything runs on the bf16 matrix cores, which are exact in the products and add them in fp32.  An fp32 operand is taken as three bf16
-// planes that add up to it exactly (split3), and a product of two such operands as the six largest products of planes (three where the
-// other operand is bf16).  An accumulator takes one rounding per 16 contraction indices and product of planes, so
-// the results are closer to float64 than those of v_mfma_f32_32x32x2_f32 with one per 2 (normal operands, 192 indices: 2.0e-7 against
-// 2.5e-7; with the small products in a sum of their own, as the weight gradients have them, 0.8e-7).  What the planes cannot hold
-// (infinities, operands from 2^104 and results from 2^80 on) is found in the finished tile; those rows of it are then computed again in fp32
-// (op_redo).  With an infinity in one of every 32 rows that costs: 768 -> 768 fp32, 12608 rows, forward 82 -> 322 us and backward 230 -> 539,
-// 1024 -> 4096 fp32, 8000 rows, 169 -> 832 and 409 -> 1187.
+// Precision: U and dU are fp32 for both types, as in the SIMT kernels; bf16 layers are rounded once, when a result is
+// stored.
+// Everything runs on the bf16 matrix cores, which are exact in the products and add them in fp32.  An fp32 operand is
+// taken as three bf16 planes that add up to it exactly (split3), and a product of two such operands as the six largest
+// products of planes (three where the other operand is bf16).  An accumulator takes one rounding per 16 contraction
+// indices and product of planes, so the results are closer to float64 than those of v_mfma_f32_32x32x2_f32 with one per
+// 2 (normal operands, 192 indices: 2.0e-7 against 2.5e-7; with the small products in a sum of their own, as the weight
+// gradients have them, 0.8e-7).  What the planes cannot hold (infinities, operands from 2^104 and results from 2^80 on)
+// is found in the finished tile; those rows of it are then computed again in fp32 (op_redo).  With an infinity in one
+// of every 32 rows that costs: 768 -> 768 fp32, 12608 rows, forward 82 -> 322 us and backward 230 -> 539, 1024 -> 4096
+// fp32, 8000 rows, 169 -> 832 and 409 -> 1187.
 //
-// What bounds it: a product of two fp32 operands costs the matrix cores 6/14.4 of its time on the fp32 cores (2058 against
-// 143 TFLOP/s in a loop of MFMAs alone), and what is left is the vector work of splitting (5.5 instructions an element, once per tile that
-// takes it) and LDS.  Neither is near its rate: the chunks are a chain of load, split, barrier and multiply, and what hides it is the number of
-// workgroups on a CU.  So a chunk is 16 contraction indices, one MFMA deep: 64 x 64 tiles then take 30 KB of LDS, five
-// to a CU, where chunks of 32 leave two (4096 -> 1024 fp32, 8000 rows, whole step: 660 us on the fp32 matrix cores, 674 in planes with chunks of 32, 455 with
-// 16).  Small and odd bf16 layers are bound by the memory system.  The intermediate goes
-// through memory (for most shapes it stays in the last-level cache): a fused kernel would hold all k blocks of a row tile,
-// which leaves the large shapes one 16-row tile per CU.
-// Measured, training step: 768 -> 768 fp32, k = 4, 12608 rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix cores, now 250 (one
-// contraction of 3.7 GFLOP takes 35 to 40 us, 50 where an operand is strided, the two weight gradients 74); 196 -> 256 bf16, blocks of 49 and 64,
-// 32768 rows: 458, 121, now 100 us; 2048 -> 512 fp32, 3000 rows: 137, now 112.
+// What bounds it: a product of two fp32 operands costs the matrix cores 6/14.4 of its time on the fp32 cores (2058
+// against 143 TFLOP/s in a loop of MFMAs alone), and what is left is the vector work of splitting (5.5 instructions an
+// element, once per tile that takes it) and LDS.  Neither is near its rate: the chunks are a chain of load, split,
+// barrier and multiply, and what hides it is the number of workgroups on a CU.  So a chunk is 16 contraction indices,
+// one MFMA deep: 64 x 64 tiles then take 30 KB of LDS, five to a CU, where chunks of 32 leave two (4096 -> 1024 fp32,
+// 8000 rows, whole step: 660 us on the fp32 matrix cores, 674 in planes with chunks of 32, 455 with 16).  Small and odd
+// bf16 layers are bound by the memory system.  The intermediate goes through memory (for most shapes it stays in the
+// last-level cache): a fused kernel would hold all k blocks of a row tile, which leaves the large shapes one 16-row
+// tile per CU.
+// Measured, training step: 768 -> 768 fp32, k = 4, 12608 rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix
+// cores, now 250 (one contraction of 3.7 GFLOP takes 35 to 40 us, 50 where an operand is strided, the two weight
+// gradients 74); 196 -> 256 bf16, blocks of 49 and 64, 32768 rows: 458, 121, now 100 us; 2048 -> 512 fp32, 3000 rows:
+// 137, now 112.
 #include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
@@ -102,9 +106,10 @@ struct TileDrop {
 };
 
 // A C x O tile of an operand (C: extent along the index with the unit or smallest stride, O: along the other one) on
-// its way from memory to LDS [o][c], row stride LSTR elements: bf16 as it is, fp32 as three planes of SZ elements.  Elements past the
-// limits read as zeros.  Single elements are loaded with consecutive lanes on consecutive c (at a stride of 16 bytes a load takes the L1
-// 31 cycles, at 32 bytes 60), and neighbouring lanes exchange them so that each has two for a dword.
+// its way from memory to LDS [o][c], row stride LSTR elements: bf16 as it is, fp32 as three planes of SZ elements.
+// Elements past the limits read as zeros.  Single elements are loaded with consecutive lanes on consecutive c (at a
+// stride of 16 bytes a load takes the L1 31 cycles, at 32 bytes 60), and neighbouring lanes exchange them so that each
+// has two for a dword.
 template <typename T, int C, int O, int LSTR, Take TAKE, int SZ>
 struct OpTile {
     static constexpr bool VEC = TAKE != kElements, kSplit = sizeof(T) == 4;
@@ -237,10 +242,10 @@ struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32
     static constexpr int TM = WM * MT * 32, TN = WN * NT * 32;
 };
 
-// Rows of wave (wm, wn)'s 32 x 32 tiles that hold something not finite, again on the fp32 matrix cores, straight
-// from memory, sixteen contraction indices to a partial sum.  The other rows keep their results: their operand is zero here (a weight
-// that is not finite leaves no other rows).  All tile sizes have the same groups of 32 columns, so that a row's result depends neither on
-// the rows beside it nor on the tile that was picked for the batch.
+// Rows of wave (wm, wn)'s 32 x 32 tiles that hold something not finite, again on the fp32 matrix cores, straight from
+// memory, sixteen contraction indices to a partial sum.  The other rows keep their results: their operand is zero here
+// (a weight that is not finite leaves no other rows).  All tile sizes have the same groups of 32 columns, so that a
+// row's result depends neither on the rows beside it nor on the tile that was picked for the batch.
 template <typename T>
 __device__ __forceinline__ float op_element(__amdgpu_buffer_rsrc_t rs, uint32_t at, uint32_t scalar)
 {
@@ -350,8 +355,9 @@ __device__ __forceinline__ void op_store(const OpDesc& d, const f32x16 (&acc)[MT
     }
 }
 
-// One workgroup, `bid` of d.blocks.  TA, TB, TO: element types of the operands and the output in memory.  RA / RB: the operand's
-// row index (not the contraction) is the contiguous one.  PARTIAL: fp32 partial tiles of a split contraction instead of the output.
+// One workgroup, `bid` of d.blocks.  TA, TB, TO: element types of the operands and the output in memory.  RA / RB: the
+// operand's row index (not the contraction) is the contiguous one.  PARTIAL: fp32 partial tiles of a split contraction
+// instead of the output.
 // Workgroup order: the row tile (PARTIAL: the batch chunk) is dealt to the XCDs, and the blocks and column tiles of one
 // row tile follow each other on that XCD: strided operands and outputs of the k blocks share their cache lines, which
 // then meet in one L2.
@@ -625,8 +631,9 @@ int launch_tile(int cfg, const OpDesc& d, hipStream_t st)
     }
     return launch_one<OpGemm<TA, TB, TO, Cfg64x64, false, RB, false, AV, BV>>(d, st);
 }
-// The two kinds of contraction of the data path with the ways of taking that occur: both operands in aligned pieces, both in pieces
-// from anywhere, or A element by element (it is strided in the backward, and in the forward under MONARCH_FLAG_PERM_B).
+// The two kinds of contraction of the data path with the ways of taking that occur: both operands in aligned pieces,
+// both in pieces from anywhere, or A element by element (it is strided in the backward, and in the forward under
+// MONARCH_FLAG_PERM_B).
 template <typename TA, typename TB, typename TO>
 int launch_op(bool w_rc, int cfg, const OpDesc& d, hipStream_t st)
 {
@@ -666,9 +673,9 @@ int64_t tiles(int64_t n, int t) { return (n + t - 1) / t; }
 
 // The tile that finishes first under a simple model: up to 256 workgroups run one per CU; beyond, rounds of two per CU
 // that share it.  A workgroup costs its (padded) tile plus a fixed share for filling and draining the pipeline.
-// Operands taken element by element keep to 64 rows, whose workgroups hold more of the strided loads in flight, and to 128 columns where
-// there are more than 64, since every column tile loads them again (1024 -> 4096 fp32, 8000 rows: step 559 us with 64 x 64,
-// 521 with 64 x 128, 560 with 128 x 64).
+// Operands taken element by element keep to 64 rows, whose workgroups hold more of the strided loads in flight, and to
+// 128 columns where there are more than 64, since every column tile loads them again (1024 -> 4096 fp32, 8000 rows:
+// step 559 us with 64 x 64, 521 with 64 x 128, 560 with 128 x 64).
 int pick_tile(int64_t M, int N, int G, bool pieces)
 {
     if (!pieces) return N > 64 ? 4 : 3;

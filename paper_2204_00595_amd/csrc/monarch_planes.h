@@ -4,15 +4,16 @@
 
 namespace monarch {
 
-// Operands are scaled up before they are split: every bit of an fp32 number, the denormal ones too, is then a multiple of 2^-125, so that
-// each plane is a normal bf16 number or zero and nothing is lost at the lower end, whatever the other operand.  Numbers from 2^104 and
-// results from 2^80 on become infinite, which the finished tile shows (planes_overflowed).
+// Operands are scaled up before they are split: every bit of an fp32 number, the denormal ones too, is then a multiple
+// of 2^-125, so that each plane is a normal bf16 number or zero and nothing is lost at the lower end, whatever the
+// other operand.  Numbers from 2^104 and results from 2^80 on become infinite, which the finished tile shows
+// (planes_overflowed).
 constexpr float kPlaneScale = 0x1p24f;
 template <int SPLIT>  // operands that were split: 1 or 2
 constexpr float kPlaneUnscale = SPLIT == 2 ? 0x1p-48f : 0x1p-24f;
 
-// fp32 pair -> its three bf16 pairs: the (scaled) value rounded, what that leaves rounded, and the rest, which fits.  The three add up to
-// the value exactly.
+// fp32 pair -> its three bf16 pairs: the (scaled) value rounded, what that leaves rounded, and the rest, which fits.
+// The three add up to the value exactly.
 __device__ __forceinline__ void split3(uint32_t a, uint32_t b, uint32_t out[3])
 {
     float x = __uint_as_float(a) * kPlaneScale, y = __uint_as_float(b) * kPlaneScale;
@@ -26,8 +27,9 @@ __device__ __forceinline__ void split3(uint32_t a, uint32_t b, uint32_t out[3])
     }
 }
 
-// Products of the planes whose place values add up to less than 3; what the others add up to is at most 2^-24 of the product (2^-27.5 root
-// mean square, where one rounding to fp32 is 2^-25.3).  `big` takes the product of the first planes, `small` the rest (they may be one).
+// Products of the planes whose place values add up to less than 3; what the others add up to is at most 2^-24 of the
+// product (2^-27.5 root mean square, where one rounding to fp32 is 2^-25.3).  `big` takes the product of the first
+// planes, `small` the rest (they may be one).
 template <int PA, int PB>
 __device__ __forceinline__ void plane_products(const bf16x8 (&a)[PA], const bf16x8 (&b)[PB], f32x16& big, f32x16& small)
 {
@@ -39,12 +41,12 @@ __device__ __forceinline__ void plane_products(const bf16x8 (&a)[PA], const bf16
     big = mfma32(a[0], b[0], big);
 }
 
-// A result that is not finite: an infinity or NaN among the operands (an infinity times the zero planes of a number is no number), or
-// something that the scale made infinite.
+// A result that is not finite: an infinity or NaN among the operands (an infinity times the zero planes of a number is
+// no number), or something that the scale made infinite.
 __device__ __forceinline__ bool planes_bad(float v) { return (__float_as_uint(v) << 1) >= (255u << 24); }
 
-// Whether a lane of the wave holds one.  What is computed again then has to be chosen by rows of the batch: a row's result must not
-// depend on the rows beside it.
+// Whether a lane of the wave holds one.  What is computed again then has to be chosen by rows of the batch: a row's
+// result must not depend on the rows beside it.
 template <int MT, int NT>
 __device__ __forceinline__ bool planes_overflowed(const f32x16 (&acc)[MT][NT])
 {
@@ -70,8 +72,9 @@ __device__ __forceinline__ bool planes_overflowed(const f32x16& acc)
     return planes_overflowed(reinterpret_cast<const f32x16(&)[1][1]>(acc));
 }
 
-// Tiles with a column (lane % 32) for each row of the batch: the results of the rows that hold something not finite become zero, for
-// fp32 products to be added to them.  True in the lanes of these rows; the others keep their results and add products with zero.
+// Tiles with a column (lane % 32) for each row of the batch: the results of the rows that hold something not finite
+// become zero, for fp32 products to be added to them.  True in the lanes of these rows; the others keep their results
+// and add products with zero.
 __device__ __forceinline__ bool planes_clear(f32x16& acc)
 {
     bool off = false;

@@ -12,11 +12,12 @@
 // accumulator tile holds S[4h + r][c] = S[c][4h + r], which is what the same lane has to bring as either operand of
 // contraction step r.  Tiles below the diagonal are transposes of those above, by way of LDS.
 //
-// What bounds it: the matrix cores, 32 clocks for each of the NT^2 (NT + 1) / 2 * 4 steps of a squaring (m = 32: 768 clocks, one
-// wave per SIMD; m = 64: 5120, four), then the transposition through LDS.  Sums over the lanes stay in the vector registers and run
-// beside the products (m = 32, 1024 slices: 15.8 us with shuffles between them, 13.3 now; the four lanes of a column meet by row swaps).  The one-sided Jacobi SVD that was here before (all m triples, three cross-lane
-// shuffles per element and rotation) took 784 us for m = 32 and 5.8 ms for m = 64, and was less accurate (products
-// 2e-5 off at m = 64, here 5e-7).
+// What bounds it: the matrix cores, 32 clocks for each of the NT^2 (NT + 1) / 2 * 4 steps of a squaring (m = 32: 768
+// clocks, one wave per SIMD; m = 64: 5120, four), then the transposition through LDS.  Sums over the lanes stay in the
+// vector registers and run beside the products (m = 32, 1024 slices: 15.8 us with shuffles between them, 13.3 now; the
+// four lanes of a column meet by row swaps).  The one-sided Jacobi SVD that was here before (all m triples, three
+// cross-lane shuffles per element and rotation) took 784 us for m = 32 and 5.8 ms for m = 64, and was less accurate
+// (products 2e-5 off at m = 64, here 5e-7).
 #include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
@@ -117,8 +118,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
 #pragma unroll
             for (int b = 0; b < NT; ++b) S[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[a][t], g[b][t], S[a][b], 0, 0, 0);
 
-    // S = S^2 at trace 1; returns the trace before, |S|_F^2, which is 1 exactly when S, at trace 1 itself, is of rank one.  The sum over
-    // the lanes runs beside the products.
+    // S = S^2 at trace 1; returns the trace before, |S|_F^2, which is 1 exactly when S, at trace 1 itself, is of rank
+    // one.  The sum over the lanes runs beside the products.
     auto square = [&]() {
         f32x4 Q[NT][NT];
         float norm2 = 0.f;
@@ -233,8 +234,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
 #pragma unroll
                 for (int a = 0; a < NT; ++a) w[t] = fmaf(g[a][t], v[a], w[t]);
         }
-        // sum over the TS lanes of a row, each lane keeping half of its values at every step while it has more than one; the partners are
-        // the lanes 15 - c, 7 - c of eight, c ^ 2 and c ^ 1, which differ in the bit d
+        // sum over the TS lanes of a row, each lane keeping half of its values at every step while it has more than
+        // one; the partners are the lanes 15 - c, 7 - c of eight, c ^ 2 and c ^ 1, which differ in the bit d
         int t0 = 0;
         auto halve = [&](auto ctrl, auto count, int d) {
             constexpr int CTRL = decltype(ctrl)::value, left = decltype(count)::value / 2;

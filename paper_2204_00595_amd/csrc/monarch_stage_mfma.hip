@@ -13,16 +13,19 @@
 // activation tiles (the N extent) past them.
 //   D (32 x 32): acc[r] = D[8*(r/4) + 4*(lane/32) + r%4][lane%32]: a lane holds whole complex outputs of one row.
 //
-// The products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), both operands as three bf16 planes that add up to the fp32
-// values (monarch_planes.h): weights when they are loaded, activations on their way to LDS or, where a wave takes them from memory
-// itself, in its registers.  A step contracts eight complex inputs with six MFMAs in place of sixteen fp32 MFMAs of twice the cycles.
-// Rows with results that are not finite are computed again in fp32 (stage_finish; an infinity in one of every 32 rows, 64 complex blocks of
-// 64, 2048 rows: forward 73 -> 210 us, backward 223 -> 525; 64 real blocks of 64, 12000 rows: 191 -> 405 and 557 -> 2467).
-// On the fp32 cores the contiguous stages took 54 us at 64 blocks of 64 and 2048 rows and were bound by them (69 to 74 % busy); they
-// take 37 to 40 now, for 134 MB each, 26 us at the rate of a copy.  What is left is one tile per workgroup in flight: the weights' planes take 96 registers, so two workgroups fit a CU.
+// The products run on the bf16 matrix cores (v_mfma_f32_32x32x16_bf16), both operands as three bf16 planes that add up
+// to the fp32 values (monarch_planes.h): weights when they are loaded, activations on their way to LDS or, where a wave
+// takes them from memory itself, in its registers.  A step contracts eight complex inputs with six MFMAs in place of
+// sixteen fp32 MFMAs of twice the cycles.
+// Rows with results that are not finite are computed again in fp32 (stage_finish; an infinity in one of every 32 rows,
+// 64 complex blocks of 64, 2048 rows: forward 73 -> 210 us, backward 223 -> 525; 64 real blocks of 64, 12000 rows: 191
+// -> 405 and 557 -> 2467).
+// On the fp32 cores the contiguous stages took 54 us at 64 blocks of 64 and 2048 rows and were bound by them (69 to 74
+// % busy); they take 37 to 40 now, for 134 MB each, 26 us at the rate of a copy.  What is left is one tile per
+// workgroup in flight: the weights' planes take 96 registers, so two workgroups fit a CU.
 // A second tile in flight took a workgroup's registers to the limit and 6 us more, a third workgroup spilled (62 us).
-// Forward and backward together: 64 blocks of 64, 2048 rows: 389 -> 300 us; 48, 1500 rows: 212 -> 159; 32, 2048 rows: 103 -> 85; 64 real
-// blocks of 64, 12000 rows: 895 -> 730.
+// Forward and backward together: 64 blocks of 64, 2048 rows: 389 -> 300 us; 48, 1500 rows: 212 -> 159; 32, 2048 rows:
+// 103 -> 85; 64 real blocks of 64, 12000 rows: 895 -> 730.
 //
 // The permutation between the factors is an 8-byte transposition, so it is done where the pieces can be made
 // long: the workspace holds the intermediate in tiles  T[row tile][block][index in block][32 rows]  (the
@@ -85,8 +88,9 @@ __device__ __forceinline__ float2 act_value(const float2* __restrict__ src, int6
     return at < B ? v : make_float2(0.f, 0.f);
 }
 
-// What lane (col, e = lane % 2) of the wave that owns M tile mt multiplies with input i of block g: its row of the expanded weights at
-// the two components.  CONJT: the conjugate transpose of the stored block; REAL: the weights as they are (CONJT: transposed).
+// What lane (col, e = lane % 2) of the wave that owns M tile mt multiplies with input i of block g: its row of the
+// expanded weights at the two components.  CONJT: the conjugate transpose of the stored block; REAL: the weights as
+// they are (CONJT: transposed).
 template <int P, int Q, bool CONJT, bool REAL>
 __device__ __forceinline__ float2 weight_value(const float2* __restrict__ W, int g, int mt, int col, int i)
 {
@@ -163,8 +167,9 @@ __device__ __forceinline__ void stage_finish(f32x16& acc, const float2* __restri
 //   kInNat:    src[row][g*P + i]
 //   kInGather: src[row][i*k + g]
 //   kInT:      src tile (rt, g): [i][32 rows], contiguous
-// LDS: three bf16 planes (monarch_planes.h) of [row][2 P + 8], a row's components in order; the 16 bytes of padding make a row an odd
-// number of 16-byte units, so that eight rows' pieces fall on different banks.  Rows past the end of the batch read as zeros (kInT: the producer wrote zeros there).
+// LDS: three bf16 planes (monarch_planes.h) of [row][2 P + 8], a row's components in order; the 16 bytes of padding
+// make a row an odd number of 16-byte units, so that eight rows' pieces fall on different banks.  Rows past the end of
+// the batch read as zeros (kInT: the producer wrote zeros there).
 // REAL (real fp32 data, two consecutive values per float2): only the gathering form differs, whose pieces are then
 // single floats, src[row][i'*k + g] for the 2P real indices i' of the block.
 template <int P, int NTHR, int IN, bool REAL = false>
@@ -659,11 +664,12 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
     }
 }
 
-// dy, read through the outer permutation, in tiles dW[row tile][block][l][32 rows]: the operand of the stage that makes dY1 and of the
-// weight gradient.  A workgroup moves 64 consecutive values of 32 rows through LDS (REAL: the 64 blocks from g0 of one pair of
-// inputs, 2 x 64 floats), reading 512 bytes (2 x 256) of a row and writing runs of 256 bytes.  Bound by memory (2048 x 4096
-// complex values: 28 us, 4.8 TB/s).  REAL with a number of blocks that is no multiple of four loads single values: a piece of four
-// would start anywhere, and the last one of the last row would end past the tensor.
+// dy, read through the outer permutation, in tiles dW[row tile][block][l][32 rows]: the operand of the stage that makes
+// dY1 and of the weight gradient.  A workgroup moves 64 consecutive values of 32 rows through LDS (REAL: the 64 blocks
+// from g0 of one pair of inputs, 2 x 64 floats), reading 512 bytes (2 x 256) of a row and writing runs of 256 bytes.
+// Bound by memory (2048 x 4096 complex values: 28 us, 4.8 TB/s).  REAL with a number of blocks that is no multiple of
+// four loads single values: a piece of four would start anywhere, and the last one of the last row would end past the
+// tensor.
 template <bool REAL>
 __global__ void __launch_bounds__(256)
 ctile_kernel(const float2* __restrict__ in, float2* __restrict__ out, int64_t B, int k, int P, int chunks)
@@ -978,10 +984,10 @@ __global__ void __launch_bounds__(256) csum_kernel(const f32x4* __restrict__ par
 int64_t tiles_of(const Problem& pb) { return (pb.B + kRT - 1) / kRT; }
 size_t t_bytes(const Problem& pb) { return align_up((size_t)tiles_of(pb) * kRT * pb.kq() * sizeof(float2), 256); }
 
-// workgroups of one block: about `target_waves` in all, a multiple of 8, at most one per tile.  A workgroup loads and splits a block's
-// weights before its first tile, so there are no more of them than stay resident: eight waves a CU (64 complex blocks of 64, 2048
-// rows, forward and backward: 317 us with sixteen, 302 with eight), four for real layers, whose batches are the long ones (64
-// real blocks of 64, 12000 rows: 834 with sixteen, 807 with eight, 745 with four)
+// workgroups of one block: about `target_waves` in all, a multiple of 8, at most one per tile.  A workgroup loads and
+// splits a block's weights before its first tile, so there are no more of them than stay resident: eight waves a CU (64
+// complex blocks of 64, 2048 rows, forward and backward: 317 us with sixteen, 302 with eight), four for real layers,
+// whose batches are the long ones (64 real blocks of 64, 12000 rows: 834 with sixteen, 807 with eight, 745 with four)
 int splits_for(const Problem& pb, int waves_per_wg, int target_waves)
 {
     int64_t n = (target_waves / waves_per_wg + pb.k - 1) / pb.k;
@@ -1073,9 +1079,10 @@ int launch_wgrad(const Problem& pb, const void* A, const void* Bv, void* out, vo
     return hip_status(hipGetLastError());
 }
 
-// Whether dy is re-laid by a launch of its own or by the stage that gathers it, which reads it and lays it out once per M tile (four
-// M tiles, 2048 rows: 28 + 40 us against 87; two: 8 + 13 against 14; two of a real layer, 12000 rows, whose dy is larger than the caches: 69 + 107
-// against 232).  Other block counts than multiples of eight have no gathering stage.
+// Whether dy is re-laid by a launch of its own or by the stage that gathers it, which reads it and lays it out once per
+// M tile (four M tiles, 2048 rows: 28 + 40 us against 87; two: 8 + 13 against 14; two of a real layer, 12000 rows,
+// whose dy is larger than the caches: 69 + 107 against 232).  Other block counts than multiples of eight have no
+// gathering stage.
 template <int M, bool REAL = false>
 constexpr bool kRelay = REAL ? M == 32 : M >= 56;
 
