@@ -30,8 +30,8 @@
 // element, once per tile that takes it) and LDS.  Neither is near its rate: the chunks are a chain of load, split,
 // barrier and multiply, and what hides it is the number of workgroups on a CU.  So a chunk is 16 contraction indices,
 // one MFMA deep: 64 x 64 tiles then take 30 KB of LDS, five to a CU, where chunks of 32 leave two (4096 -> 1024 fp32,
-// 8000 rows, whole step: 660 us on the fp32 matrix cores, 674 in planes with chunks of 32, 455 with 16).  Small and odd
-// bf16 layers are bound by the memory system.  The intermediate goes through memory (for most shapes it stays in the
+// 8000 rows, whole step: 660 us on the fp32 matrix cores, 674 in planes with chunks of 32, 455 with 16); few workgroups
+// take chunks of 32 (launch_chunks).  Small and odd bf16 layers are bound by the memory system.  The intermediate goes through memory (for most shapes it stays in the
 // last-level cache): a fused kernel would hold all k blocks of a row tile, which leaves the large shapes one 16-row
 // tile per CU.
 // Measured, training step: 768 -> 768 fp32, k = 4, 12608 rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix
@@ -49,6 +49,7 @@ namespace monarch {
 namespace {
 
 constexpr int kThreads = 256;  // four waves
+constexpr int kCUs = 256;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
 
@@ -236,9 +237,9 @@ struct OpFrag {
         }
     }
 };
-template <int WM_, int WN_, int MT_, int NT_>
-struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32
-    static constexpr int WM = WM_, WN = WN_, MT = MT_, NT = NT_;
+template <int WM_, int WN_, int MT_, int NT_, int CHUNK_ = 16>
+struct OpCfg {  // WM x WN waves, each MT x NT tiles of 32 x 32; CHUNK: contraction indices of a chunk where planes are multiplied
+    static constexpr int WM = WM_, WN = WN_, MT = MT_, NT = NT_, CHUNK = CHUNK_;
     static constexpr int TM = WM * MT * 32, TN = WN * NT * 32;
 };
 
@@ -365,7 +366,7 @@ template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bo
 struct OpGemm {
     static constexpr bool kSplit = sizeof(TA) == 4 || sizeof(TB) == 4;
     static constexpr int PA = sizeof(TA) == 2 ? 1 : 3, PB = sizeof(TB) == 2 ? 1 : 3;
-    static constexpr int KC = kSplit ? 16 : 32, LA = op_lstr<RA, Cfg::TM, KC>(), LB = op_lstr<RB, Cfg::TN, KC>();
+    static constexpr int KC = kSplit ? Cfg::CHUNK : 32, LA = op_lstr<RA, Cfg::TM, KC>(), LB = op_lstr<RB, Cfg::TN, KC>();
     static constexpr int SZA = RA ? KC * LA : Cfg::TM * LA, SZB = RB ? KC * LB : Cfg::TN * LB;
     static constexpr int SZ = PA * SZA + PB * SZB;
     static constexpr size_t kLds = 2 * sizeof(bf16_t) * (size_t)SZ;
@@ -617,19 +618,33 @@ struct TileSize {
 constexpr int kTileSizes = 5;
 constexpr TileSize kTiles[kTileSizes] = {{128, 128}, {128, 96}, {128, 64}, {64, 64}, {64, 128}};
 
+// Chunks of 32 indices where planes are multiplied by no more workgroups than then run at the same time, one or two to a CU: nothing
+// but the next chunks hides a chunk's way from memory there, and half as many take less time, with the same results bit for bit.
+// x M in fp32, blocks of 256 and 1024, chunks of 16 and 32: 3000 rows 114.5 and 76.4 us; x M^T, 40 rows 20.7 and 17.4, 2000 rows
+// 51.2 and 49.1.  Beyond, chunks of 16 leave room for more workgroups (blocks of 40 x 128 and 128 x 257, k = 3, 8000 rows, x M: 31.0
+// and 43.6 us).
+template <typename TA, typename TB, typename TO, class Cfg, bool RB, Take AV, Take BV>
+int launch_chunks(const OpDesc& d, hipStream_t st)
+{
+    if constexpr (sizeof(TA) == 4 || sizeof(TB) == 4) {
+        using Few = OpGemm<TA, TB, TO, OpCfg<Cfg::WM, Cfg::WN, Cfg::MT, Cfg::NT, 32>, false, RB, false, AV, BV>;
+        if (d.blocks <= kCUs * (kMaxLdsBytes / 2 >= Few::kLds ? 2 : 1)) return launch_one<Few>(d, st);
+    }
+    return launch_one<OpGemm<TA, TB, TO, Cfg, false, RB, false, AV, BV>>(d, st);
+}
 template <typename TA, typename TB, typename TO, bool RB, Take AV, Take BV>
 int launch_tile(int cfg, const OpDesc& d, hipStream_t st)
 {
     if constexpr (AV != kElements) {
         switch (cfg) {
-            case 0: return launch_one<OpGemm<TA, TB, TO, Cfg128x128, false, RB, false, AV, BV>>(d, st);
-            case 1: return launch_one<OpGemm<TA, TB, TO, Cfg128x96, false, RB, false, AV, BV>>(d, st);
-            case 2: return launch_one<OpGemm<TA, TB, TO, Cfg128x64, false, RB, false, AV, BV>>(d, st);
+            case 0: return launch_chunks<TA, TB, TO, Cfg128x128, RB, AV, BV>(d, st);
+            case 1: return launch_chunks<TA, TB, TO, Cfg128x96, RB, AV, BV>(d, st);
+            case 2: return launch_chunks<TA, TB, TO, Cfg128x64, RB, AV, BV>(d, st);
         }
     } else if (cfg == 4) {
-        return launch_one<OpGemm<TA, TB, TO, Cfg64x128, false, RB, false, AV, BV>>(d, st);
+        return launch_chunks<TA, TB, TO, Cfg64x128, RB, AV, BV>(d, st);
     }
-    return launch_one<OpGemm<TA, TB, TO, Cfg64x64, false, RB, false, AV, BV>>(d, st);
+    return launch_chunks<TA, TB, TO, Cfg64x64, RB, AV, BV>(d, st);
 }
 // The two kinds of contraction of the data path with the ways of taking that occur: both operands in aligned pieces,
 // both in pieces from anywhere, or A element by element (it is strided in the backward, and in the forward under
@@ -673,12 +688,14 @@ int64_t tiles(int64_t n, int t) { return (n + t - 1) / t; }
 
 // The tile that finishes first under a simple model: up to 256 workgroups run one per CU; beyond, rounds of two per CU
 // that share it.  A workgroup costs its (padded) tile plus a fixed share for filling and draining the pipeline.
-// Operands taken element by element keep to 64 rows, whose workgroups hold more of the strided loads in flight, and to
-// 128 columns where there are more than 64, since every column tile loads them again (1024 -> 4096 fp32, 8000 rows:
-// step 559 us with 64 x 64, 521 with 64 x 128, 560 with 128 x 64).
+// Operands taken element by element keep to 64 rows, whose workgroups hold more of the strided loads in flight, and to 128 columns
+// where there are more than 64, since every column tile loads them again (1024 -> 4096 fp32, 8000 rows: step 559 us with 64 x 64,
+// 521 with 64 x 128, 560 with 128 x 64).  Not where 128 columns would leave half of the CUs idle (x M, blocks of 256 and 1024, 40 rows:
+// 55.2 us with 64 x 128, 41.6 with 64 x 64; from there up to a workgroup per CU it depends: 192 of them, blocks of 256 and 1024, 60.0 and
+// 54.3 us, blocks of 96 19.1 and 21.3).
 int pick_tile(int64_t M, int N, int G, bool pieces)
 {
-    if (!pieces) return N > 64 ? 4 : 3;
+    if (!pieces) return N > 64 && tiles(M, 64) * tiles(N, 128) * G > kCUs / 2 ? 4 : 3;
     int best = 3;
     double best_t = 1e30;
     for (int c = 0; c < 4; ++c) {

@@ -111,6 +111,23 @@ def test_a_row_does_not_depend_on_the_rows_beside_it(shape):
         assert torch.equal(plain[name][keep], hurt[name][keep]), name
 
 
+# Tiles and chunk lengths go by the size of the batch: the first rows of a long one, alone, give the same bits.  Fewer and more than 64
+# columns, contractions that end within a chunk, operands in pieces and element by element.
+@pytest.mark.parametrize("reading", (0, 1))
+@pytest.mark.parametrize("shape", [(9000, 3, 40, 128, 257, "f32"), (9000, 4, 192, 192, 192, "f32"), (5000, 4, 33, 70, 300, "f32"),
+                                   (20000, 4, 49, 49, 64, "bf16"), (9000, 8, 101, 99, 17, "bf16")], ids=str)
+def test_a_short_batch_gives_the_rows_of_a_long_one(shape, reading):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    x, R, L, dy = (_dev(a, shape[-1]) for a in _inputs(shape, 9600))
+    flags = B.MONARCH_FLAG_PERM_B if reading else 0
+    y, xM = B.monarch_fwd_ws(x, R, L, flags=flags), B.monarch_fwd_t(dy, R, L, flags=flags)
+    for rows in (1, 40, 700, 1300, 2500, 4100):
+        assert torch.equal(B.monarch_fwd_ws(x[:rows], R, L, flags=flags), y[:rows]), ("y", rows)
+        assert torch.equal(B.monarch_fwd_t(dy[:rows], R, L, flags=flags), xM[:rows]), ("xM", rows)
+
+
 # more rows than the array of the call without a workspace holds: slices of 512 and of 2560 rows
 @pytest.mark.parametrize("shape", [(1300, 8, 64, 512, 64, "f32"), (3000, 4, 192, 192, 192, "f32"), (1300, 8, 33, 512, 50, "bf16")], ids=str)
 def test_slices_with_infinities_give_what_one_call_gives(shape):
