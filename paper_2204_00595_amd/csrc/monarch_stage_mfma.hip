@@ -543,13 +543,13 @@ struct Gather8 {
 };
 
 // REAL (see cstage_kernel): the pieces of dy are 32 bytes (eight blocks' values of one (row, input)), a chunk is
-// 32 inputs = 16 pairs, and the weights are L[c]^T as stored.
-template <int P, int Q, bool EMIT, bool REAL = false>
+// 32 inputs = 16 pairs, and the weights are L[c]^T as stored.  MTW: M tiles of a wave (launch_gather8).
+template <int P, int Q, bool EMIT, bool REAL, int MTW>
 __global__ void __launch_bounds__(512)
 cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float2* __restrict__ out,
                 float2* __restrict__ dwt, int64_t B, int k, int nsplit, int perm_b)
 {
-    constexpr int MTG = kTileWaves<Q>;
+    constexpr int MTG = kTileWaves<Q> / MTW;
     constexpr int NCHUNK = (P + 15) / 16;
     constexpr int PLANE = Gather8<P>::kPlane;
     extern __shared__ __align__(16) float2 gat8[];
@@ -557,16 +557,25 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
     int bid = (int)blockIdx.x;
     const int split = bid % nsplit;
     bid /= nsplit;
-    const int mt = bid % MTG, oct = bid / MTG;
-    const int tid = threadIdx.x, lane = tid & 63, w = tid >> 6;
+    const int mt0 = bid % MTG * MTW, oct = bid / MTG;
+    const int tid = threadIdx.x, lane = tid & 63, w = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int g = 8 * oct + w;
     const int col = lane & 31, kh = lane >> 5;
     const int64_t ntiles = (B + kRT - 1) / kRT;
     const int64_t ld_in = (int64_t)k * P;
     const bool pb = perm_b != 0;
 
-    bf16x8 A[P / 8][3];
-    load_weights<P, Q, true, REAL>(A, W, g, mt, col, kh);
+    bf16x8 A[MTW][P / 8][3];
+#pragma unroll
+    for (int m = 0; m < MTW; ++m) load_weights<P, Q, true, REAL>(A[m], W, g, mt0 + m, col, kh);
+    constexpr int kOuts = REAL ? 16 : 8, E = REAL ? 2 : 1;  // as in cstage_kernel
+    uint32_t off[MTW][kOuts];
+#pragma unroll
+    for (int o = 0; o < MTW * kOuts; ++o) {
+        const int j = 16 * (mt0 + o / kOuts) + 4 * (o % kOuts / (2 * E)) + 2 * kh + o / E % 2;
+        const int d = mid_src(g * E * Q + E * j + o % E, k, E * Q, pb), blk = d / (E * Q), idx = d - blk * (E * Q);
+        off[o / kOuts][o % kOuts] = (uint32_t)(((blk * Q + idx / E) * kRT + col) * E + idx % E) * (uint32_t)(8 / E);
+    }
     u32x4 pre[4];
     auto fetch = [&](int64_t rt, int ch) {
 #pragma unroll
@@ -605,9 +614,9 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
     if (rt < ntiles) fetch(rt, 0);
     int cnt = 0;
     for (; rt < ntiles; rt += nsplit) {
-        f32x16 acc;
+        f32x16 acc[MTW];
 #pragma unroll
-        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+        for (int r = 0; r < MTW * 16; ++r) acc[r / 16][r % 16] = 0.f;
 #pragma unroll
         for (int ch = 0; ch < NCHUNK; ++ch, ++cnt) {
             float2* buf = gat8 + (cnt & 1) * (8 * PLANE);
@@ -628,10 +637,11 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
                 }
                 bf16x8 b[3];
                 split_four(xv, b);
-                plane_products<3, 3>(A[2 * ch + u], b, acc, acc);
+#pragma unroll
+                for (int m = 0; m < MTW; ++m) plane_products<3, 3>(A[m][2 * ch + u], b, acc[m], acc[m]);
             }
             if constexpr (EMIT) {
-                if (mt == 0) {
+                if (mt0 == 0) {
                     float2* dst = dwt + (((size_t)rt * k + g) * P + 16 * ch) * kRT;
 #pragma unroll
                     for (int n = 0; n < 8; ++n)
@@ -639,27 +649,16 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
                 }
             }
         }
-        stage_finish<P, Q, kInGather, true, REAL>(acc, in, W, rt, g, mt, k, ld_in, B, lane);
-        if constexpr (REAL) {
-            float* outf = reinterpret_cast<float*>(out);
+        char* const to = reinterpret_cast<char*>(out + (size_t)rt * k * (Q * kRT));
 #pragma unroll
-            for (int r = 0; r < 16; ++r) {
-                const int n = 32 * mt + 8 * (r / 4) + 4 * kh + (r % 4);
-                const int d = mid_src(g * 2 * Q + n, k, 2 * Q, pb);
-                const int blk = d / (2 * Q), idx = d - blk * (2 * Q);
-                outf[((((size_t)rt * k + blk) * Q + (idx >> 1)) * kRT + col) * 2 + (idx & 1)] = acc[r];
+        for (int m = 0; m < MTW; ++m) {
+            stage_finish<P, Q, kInGather, true, REAL>(acc[m], in, W, rt, g, mt0 + m, k, ld_in, B, lane);
+#pragma unroll
+            for (int o = 0; o < kOuts; ++o) {
+                if (!REAL && Q % 16 != 0 && 16 * (mt0 + m) + 4 * (o / 2) + 2 * kh + o % 2 >= Q) continue;
+                if constexpr (REAL) *reinterpret_cast<float*>(to + off[m][o]) = acc[m][o];
+                else *reinterpret_cast<float2*>(to + off[m][o]) = make_float2(acc[m][2 * o], acc[m][2 * o + 1]);
             }
-        } else {
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-                for (int h = 0; h < 2; ++h) {
-                    const int j = 16 * mt + 4 * q4 + 2 * kh + h;
-                    if (Q % 16 != 0 && j >= Q) continue;
-                    const int d = mid_src(g * Q + j, k, Q, pb);
-                    const int blk = d / Q, idx = d - blk * Q;
-                    out[(((size_t)rt * k + blk) * Q + idx) * kRT + col] = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
-                }
         }
     }
 }
@@ -1043,19 +1042,31 @@ int launch_scatter8(const Problem& pb, const void* T, const void* W, void* out, 
     return hip_status(hipGetLastError());
 }
 
-template <int M, bool EMIT, bool REAL = false>
-int launch_gather8(const Problem& pb, const void* in, const void* W, void* out, void* dwt, hipStream_t st)
+template <int M, bool EMIT, bool REAL, int MTW>
+int launch_gather8_tiles(const Problem& pb, const void* in, const void* W, void* out, void* dwt, hipStream_t st)
 {
-    constexpr int MTG = kTileWaves<M>;
+    constexpr int MTG = kTileWaves<M> / MTW;
     const int nsplit = splits8_for(pb, MTG);
     const int64_t grid = (int64_t)(pb.k / 8) * MTG * nsplit;
     if (grid > 0x7fffffffLL) return -2;
-    auto kern = cgather8_kernel<M, M, EMIT, REAL>;
+    auto kern = cgather8_kernel<M, M, EMIT, REAL, MTW>;
     constexpr size_t lds = Gather8<M>::kLds;
     if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess) return -4;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), lds, st, (const float2*)in, (const float2*)W,
                        (float2*)out, (float2*)dwt, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0);
     return hip_status(hipGetLastError());
+}
+
+// One M tile a wave, whose workgroups read the same rows once for each; two, with all the registers there are, for the real layers with
+// blocks of 64 whose rows take more than 64 MB, so that they come from memory once (x M, 64 blocks: 2000 rows, 33 MB, 39 us with
+// one and 43 with two; 6000 rows 128 and 106, 30000 rows 616 and 485; 32 blocks, 6000 rows, 49 MB, 52 and 53, 12000 rows 122 and 100).
+template <int M, bool EMIT, bool REAL = false>
+int launch_gather8(const Problem& pb, const void* in, const void* W, void* out, void* dwt, hipStream_t st)
+{
+    if constexpr (REAL && M == 32 && !EMIT) {
+        if (pb.B * pb.n_out() * (int64_t)sizeof(float) > (64LL << 20)) return launch_gather8_tiles<M, EMIT, REAL, 2>(pb, in, W, out, dwt, st);
+    }
+    return launch_gather8_tiles<M, EMIT, REAL, 1>(pb, in, W, out, dwt, st);
 }
 
 // lda, ldb: row lengths of row-major operands in float2 units

@@ -112,10 +112,11 @@ def test_a_row_does_not_depend_on_the_rows_beside_it(shape):
 
 
 # Tiles and chunk lengths go by the size of the batch: the first rows of a long one, alone, give the same bits.  Fewer and more than 64
-# columns, contractions that end within a chunk, operands in pieces and element by element.
+# columns, contractions that end within a chunk, operands in pieces and element by element; real blocks of 64 whose rows take more than
+# 64 MB and less.
 @pytest.mark.parametrize("reading", (0, 1))
 @pytest.mark.parametrize("shape", [(9000, 3, 40, 128, 257, "f32"), (9000, 4, 192, 192, 192, "f32"), (5000, 4, 33, 70, 300, "f32"),
-                                   (20000, 4, 49, 49, 64, "bf16"), (9000, 8, 101, 99, 17, "bf16")], ids=str)
+                                   (20000, 4, 49, 49, 64, "bf16"), (9000, 8, 101, 99, 17, "bf16"), (4101, 64, 64, 64, 64, "f32")], ids=str)
 def test_a_short_batch_gives_the_rows_of_a_long_one(shape, reading):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
