@@ -216,6 +216,24 @@ struct ActTile {
         }
     }
 
+    // kInGather: the tile as it is, in the order of a kInT source
+    __device__ __forceinline__ void to_tile(float2* __restrict__ tile, int tid) const
+    {
+#pragma unroll
+        for (int n = 0; n < (REAL ? 2 : 1) * kPieces; ++n) {
+            const int idx = tid + n * NTHR;
+            if constexpr (REAL) {
+                const int row = idx / (2 * P), i = idx - row * (2 * P);
+                reinterpret_cast<float*>(tile)[((i >> 1) * kRT + row) * 2 + (i & 1)] = __uint_as_float(v[n / 4][n % 4]);
+            } else {
+                const int row = idx / P, i = idx - row * P;
+                const u32x4 w = v[n / 2];
+                if (has(idx)) tile[i * kRT + row] = (n & 1) ? make_float2(__uint_as_float(w.z), __uint_as_float(w.w))
+                                                           : make_float2(__uint_as_float(w.x), __uint_as_float(w.y));
+            }
+        }
+    }
+
     __device__ __forceinline__ void to_lds(bf16_t* act, int tid) const
     {
         if constexpr (IN == kInNat) {
@@ -287,10 +305,11 @@ struct ActTile {
 // is what one pair of K = 2 steps contracts, so the activation side is unchanged; the weights are used as they are
 // (CONJT: transposed), and since the permutations move single values, the two values of a result pair go to their
 // places separately (in the tiled workspace, to the pair slot [index / 2][row][index % 2] of the consumer's block).
+// kInGather: `tiles`, if given, receives the input as it is gathered, in the order of a kInT source.
 template <int P, int Q, int IN, int OUT, bool CONJT, bool REAL = false>
 __global__ void __launch_bounds__(kTileWaves<Q> * 64, P >= 56 || IN == kInGather ? 2 : 3)
 cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float2* __restrict__ out, int64_t B,
-              int k, int nsplit, int perm_b)
+              int k, int nsplit, int perm_b, float2* __restrict__ tiles)
 {
     constexpr int NTHR = kTileWaves<Q> * 64;
     constexpr bool kWhole = Q % 16 == 0;  // else the last wave has outputs that do not exist
@@ -332,6 +351,9 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
     for (int it = 0; rt < ntiles; rt += nsplit, ++it) {
         bf16_t* a = act[kBufs == 2 ? it & 1 : 0];
         pre.to_lds(a, tid);
+        if constexpr (IN == kInGather) {
+            if (tiles) pre.to_tile(tiles + ((size_t)rt * k + g) * (P * kRT), tid);
+        }
         lds_barrier();
         if (rt + nsplit < ntiles) pre.fetch(in, rt + nsplit, g, k, ld_in, B, tid);
 
@@ -986,7 +1008,8 @@ size_t t_bytes(const Problem& pb) { return align_up((size_t)tiles_of(pb) * kRT *
 // workgroups of one block: about `target_waves` in all, a multiple of 8, at most one per tile.  A workgroup loads and
 // splits a block's weights before its first tile, so there are no more of them than stay resident: eight waves a CU (64
 // complex blocks of 64, 2048 rows, forward and backward: 317 us with sixteen, 302 with eight), four for real layers,
-// whose batches are the long ones (64 real blocks of 64, 12000 rows: 834 with sixteen, 807 with eight, 745 with four)
+// whose batches are the long ones (64 real blocks of 64, 12000 rows: 834 with sixteen, 807 with eight, 745 with four),
+// but eight where single values are gathered (x M, 2 blocks of 64, 12000 rows: 17.5 us with four, 16.3 with eight)
 int splits_for(const Problem& pb, int waves_per_wg, int target_waves)
 {
     int64_t n = (target_waves / waves_per_wg + pb.k - 1) / pb.k;
@@ -1006,13 +1029,13 @@ int wgrad_chunks(const Problem& pb)
 }
 
 template <int M, int IN, int OUT, bool CONJT, bool REAL = false>
-int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hipStream_t st)
+int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hipStream_t st, void* tiles = nullptr)
 {
-    const int nsplit = splits_for(pb, kTileWaves<M>, REAL ? 1024 : 2048);
+    const int nsplit = splits_for(pb, kTileWaves<M>, REAL && IN != kInGather ? 1024 : 2048);
     const int64_t grid = (int64_t)pb.k * nsplit;
     if (grid > 0x7fffffffLL) return -2;
     hipLaunchKernelGGL((cstage_kernel<M, M, IN, OUT, CONJT, REAL>), dim3((unsigned)grid), dim3(64 * kTileWaves<M>), 0, st, (const float2*)in,
-                       (const float2*)W, (float2*)out, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0);
+                       (const float2*)W, (float2*)out, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0, (float2*)tiles);
     return hip_status(hipGetLastError());
 }
 
@@ -1090,12 +1113,21 @@ int launch_wgrad(const Problem& pb, const void* A, const void* Bv, void* out, vo
     return hip_status(hipGetLastError());
 }
 
-// Whether dy is re-laid by a launch of its own or by the stage that gathers it, which reads it and lays it out once per
-// M tile (four M tiles, 2048 rows: 28 + 40 us against 87; two: 8 + 13 against 14; two of a real layer, 12000 rows,
-// whose dy is larger than the caches: 69 + 107 against 232).  Other block counts than multiples of eight have no
-// gathering stage.
+// How dy gets into tiles: by a launch of its own (ctile_kernel), or by a stage that gathers it.
+//
+// The stage that gathers eight blocks side by side (multiples of eight) reads dy and lays it out once per M tile: not for complex blocks
+// with four M tiles (2048 rows: 28 + 40 us with the launch, 87 without; two: 8 + 13 against 14), nor for real blocks of 64 (12000 rows,
+// dy larger than the caches: 69 + 107 against 232).
 template <int M, bool REAL = false>
 constexpr bool kRelay = REAL ? M == 32 : M >= 56;
+// The stage that gathers one block does it where the launch would cost more than it saves: up to 3 MB, and up to seven blocks, which
+// leave ctile_kernel's lanes little to do.  Whole backward with the launch and without: 7 real blocks of 32, 200 rows 26.5 and 24.2 us, 12000
+// rows 68.6 and 63.5; 20 blocks, 2000 rows 45.2 and 46.5, 12000 rows 96.6 and 112; 1 block of 64, 30000 rows 124 and 98; 33 blocks, 500
+// rows 48.1 and 48.0, 2000 rows 79.7 and 93.0; 12 complex blocks of 32, 1000 rows 38.6 and 35.9, 8000 rows 85.8 and 87.6.
+bool lays_out(const Problem& pb, size_t value)
+{
+    return pb.k < 8 || (size_t)pb.B * pb.n_out() * value <= (3u << 20);
+}
 
 template <int M, bool REAL = false>
 int launch_tile(const Problem& pb, const void* in, void* out, hipStream_t st)
@@ -1138,6 +1170,8 @@ int run_bwd(const Problem& pb, const void* dy, const void* x, const void* R, con
     if (rc) return rc;
     if (!kRelay<M> && pb.k % 8 == 0) {
         rc = launch_gather8<M, true>(pb, dy, L, dY1t, dWt, st);
+    } else if (lays_out(pb, sizeof(float2))) {
+        rc = launch_stage<M, kInGather, kOutTBwd, true>(pb, dy, L, dY1t, st, dWt);
     } else {
         rc = launch_tile<M>(pb, dy, dWt, st);
         if (!rc) rc = launch_stage<M, kInT, kOutTBwd, true>(pb, dWt, L, dY1t, st);
@@ -1184,6 +1218,8 @@ int run_real_bwd(const Problem& pb, const void* dy, const void* x, const void* R
     if (rc) return rc;
     if (!kRelay<M, true> && pb.k % 8 == 0) {
         rc = launch_gather8<M, true, true>(pb, dy, L, dY1t, dWt, st);
+    } else if (lays_out(pb, sizeof(float))) {
+        rc = launch_stage<M, kInGather, kOutTBwd, true, true>(pb, dy, L, dY1t, st, dWt);
     } else {
         rc = launch_tile<M, true>(pb, dy, dWt, st);
         if (!rc) rc = launch_stage<M, kInT, kOutTBwd, true, true>(pb, dWt, L, dY1t, st);

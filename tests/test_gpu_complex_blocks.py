@@ -35,8 +35,8 @@ def test_blocks_between_the_tiles(case, reading):
         assert np.linalg.norm(g - w) / np.linalg.norm(w) <= 1e-5, name
 
 
-# Infinities, NaN, numbers that round to a bf16 infinity and tiny ones do not fit the bf16 planes: what comes of them is what
-# the SIMT kernels give, element by element, and the rest of the batch is not touched.
+# Infinities, NaN and numbers that the scale of the planes makes infinite (5.3e36 2^24) do not fit them: what comes of them is what
+# the SIMT kernels give, element by element, and the rest of the batch is not touched.  A row of tiny numbers fits.
 @pytest.mark.parametrize("case", [(70, 16, 16), (40, 24, 8), (65, 64, 8), (33, 40, 5), (100, 64, 64)], ids=str)
 def test_values_that_three_bf16_planes_cannot_hold(case):
     if not torch.cuda.is_available():
@@ -88,7 +88,8 @@ def test_real_layers_with_values_that_three_bf16_planes_cannot_hold(case):
 
 # Real layers of blocks of 32 and 64 read dy in the order of the outer permutation, in pieces of four where the block count allows: for every
 # remainder by four, dy as the last bytes of a mapping, and with NaN behind it.
-@pytest.mark.parametrize("case", [(33, 32, 3), (64, 32, 5), (5, 32, 66), (33, 64, 1), (32, 64, 2), (65, 64, 67), (40, 64, 4), (31, 32, 12)], ids=str)
+@pytest.mark.parametrize("case", [(33, 32, 3), (64, 32, 5), (5, 32, 66), (33, 64, 1), (32, 64, 2), (65, 64, 67), (40, 64, 4), (31, 32, 12),
+                                  (1801, 32, 19), (1001, 64, 18)], ids=str)
 def test_real_layers_read_nothing_behind_dy(case):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -111,3 +112,31 @@ def test_real_layers_read_nothing_behind_dy(case):
     for name, first, last, g, w in zip(("dx", "dR", "dL"), *results, plain, simt):
         assert torch.equal(first, g) and torch.equal(last, g), name
         assert float((g - w).double().norm()) <= 1e-5 * float(w.double().norm()), name
+
+
+# The backward lays dy out in tiles in one of three ways (by block count and size of dy): (rows, block, blocks, real layer?) on either
+# side of the rules, ragged rows.
+LAYOUTS = [(77, 32, 11, True), (2501, 64, 7, True), (1801, 32, 19, True), (1001, 64, 18, True), (33, 64, 64, True), (300, 16, 9, False),
+           (1501, 24, 12, False), (901, 32, 7, False), (40, 64, 16, False)]
+
+
+@pytest.mark.parametrize("reading", [0, 1], ids=["reading_a", "reading_b"])
+@pytest.mark.parametrize("case", LAYOUTS, ids=str)
+def test_layouts_of_dy(case, reading):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, m, k, real = case
+    draw = (lambda *a: synth.normal(*a).astype(np.float32)) if real else _normal
+    x, R, L, dy = (torch.from_numpy(draw(8990 + 10 * i, shp, std)).cuda() for i, (shp, std) in enumerate(
+        (((rows, k * m), 1.0), ((k, m, m), m ** -0.5), ((k, m, m), m ** -0.5), ((rows, k * m), 1.0))))
+    flags = B.MONARCH_FLAG_PERM_B if reading else 0
+    if real:
+        got, want = B.monarch_bwd(dy, x, R, L, flags=flags), B.monarch_bwd(dy, x, R, L, flags=flags | B.MONARCH_FLAG_GENERIC)
+    else:
+        got, want = B.monarch_bwd_c64_ws(dy, x, R, L, flags=flags), B.monarch_bwd_c64(dy, x, R, L, flags=flags)
+    for name, g, w in zip(("dx", "dR", "dL"), got, want):
+        # two sums of at most `rows` fp32 products in different orders; per row of dx and per block of a gradient
+        g, w = (t.reshape(t.shape[0], -1).to(torch.complex128) for t in (g, w))
+        rel = torch.linalg.norm(g - w, dim=1) / torch.linalg.norm(w, dim=1)
+        assert float(rel.max()) <= 1e-5, (name, float(rel.max()))
