@@ -267,9 +267,8 @@ int monarch_bwd_saved(const void* dy, const void* x, const void* saved, size_t s
                       void* workspace, size_t workspace_bytes, unsigned flags);
 
 /* Bytes of device scratch with which monarch_bwd and monarch_bwd_bias run best (never 0 for a valid problem; 0 on invalid
- * arguments).  bf16 layers of four blocks with up to 4096 rows and of 64 blocks of 64 with up to 256, and shapes that only the
- * shape-generic kernels serve, may ask for more than a longer batch does, but accept less: a workspace sized for a longer batch serves
- * them (with fewer partial sums of the weight gradients, added up in another order).  MONARCH_FLAG_WGRAD_F32 may ask for more too. */
+ * arguments).  A batch may ask for more than a longer one does, but accepts less: a workspace sized for the longer batch serves
+ * it (with fewer partial sums of the weight gradients, added up in another order).  MONARCH_FLAG_WGRAD_F32 may ask for more too. */
 size_t monarch_bwd_workspace_bytes(int64_t batch, int n_in, int k, int q, int s,
                                    monarch_dtype dtype, unsigned flags);
 

@@ -173,6 +173,7 @@ bool saved_supported(const Problem& pb);
 // bf16, k = 4, wide blocks: backward (monarch_mfma_bwd_wide.hip)
 bool bwd_wide_supported(const Problem& pb);
 size_t bwd_wide_workspace(const Problem& pb);
+size_t bwd_wide_least(const Problem& pb);  // as ops_bwd_least
 int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx,
              void* dR, void* dL, void* ws, hipStream_t st);
 
@@ -219,6 +220,7 @@ bool tiled_fwd_supported(const Problem& pb);
 int tiled_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, hipStream_t st);
 bool tiled_bwd_supported(const Problem& pb);
 size_t tiled_bwd_workspace(const Problem& pb);
+size_t tiled_bwd_least(const Problem& pb);  // as ops_bwd_least
 int tiled_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR,
               void* dL, void* ws, hipStream_t st);
 bool tiled_fwd_t_supported(const Problem& pb);

@@ -119,7 +119,9 @@ size_t mfma_bwd_workspace(const Problem& pb)
 size_t mfma_bwd_least(const Problem& pb)
 {
     if (bwd_split_preferred(pb)) return bwd_split_least(pb);
-    return !bwd_wide_supported(pb) && bwd_sq64_supported(pb) ? bwd_sq64_least(pb) : mfma_bwd_workspace(pb);
+    if (bwd_wide_supported(pb)) return bwd_wide_least(pb);
+    if (bwd_sq64_supported(pb)) return bwd_sq64_least(pb);
+    return !sq16_supported(pb) && tiled_bwd_supported(pb) ? tiled_bwd_least(pb) : mfma_bwd_workspace(pb);
 }
 const char* mfma_bwd_name(const Problem& pb)
 {

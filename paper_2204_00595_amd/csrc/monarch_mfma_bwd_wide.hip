@@ -775,7 +775,9 @@ void fill_descs(const Problem& pb, WgradDesc& dl, WgradDesc& dr)
     dr.M = pb.q; dr.N = pb.p; dr.G = 4; dr.rows = pb.B;
 }
 
-Plan make_plan(const Problem& pb)
+// `room`: bytes there are; a plan with one chunk may need more.  (Chunks are whole 64 rows, so that a batch just below a multiple can
+// have more of them than a longer one.)
+Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 {
     Plan pl{};
     WgradDesc dl, dr;
@@ -787,21 +789,23 @@ Plan make_plan(const Problem& pb)
     const int64_t maxz = (pb.B + 255) / 256;
     if (z > maxz) z = maxz;
     if (z < 1) z = 1;
-    const int64_t rpc = ((pb.B + z - 1) / z + 63) / 64 * 64;  // whole pipeline rounds (two 32-row steps)
-    pl.rows_per_chunk = (int)(rpc > 0 ? rpc : 32);
-    pl.nz = (int)((pb.B + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
-    if (pl.nz < 1) pl.nz = 1;
-    size_t off = 0;
     const size_t act = align_up((size_t)(pb.B > 0 ? pb.B : 1) * pb.kq() * 2, 256);
-    pl.off_y1 = off;  off += act;
-    pl.off_dy1 = off; off += act;
-    pl.off_xf = off; off += align_up(pb.n_R() * 2, 256);
-    pl.off_lf = off; off += align_up(pb.n_L() * 2, 256);
-    pl.off_rf = off; off += align_up(pb.n_R() * 2, 256);
-    pl.off_partL = off; off += align_up((size_t)pl.nz * pb.n_L() * 4, 256);
-    pl.off_partR = off; off += align_up((size_t)pl.nz * pb.n_R() * 4, 256);
-    pl.total = off;
-    return pl;
+    for (;; z = pl.nz - 1) {
+        const int64_t rpc = ((pb.B + z - 1) / z + 63) / 64 * 64;  // whole pipeline rounds (two 32-row steps)
+        pl.rows_per_chunk = (int)(rpc > 0 ? rpc : 32);
+        pl.nz = (int)((pb.B + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
+        if (pl.nz < 1) pl.nz = 1;
+        size_t off = 0;
+        pl.off_y1 = off;  off += act;
+        pl.off_dy1 = off; off += act;
+        pl.off_xf = off; off += align_up(pb.n_R() * 2, 256);
+        pl.off_lf = off; off += align_up(pb.n_L() * 2, 256);
+        pl.off_rf = off; off += align_up(pb.n_R() * 2, 256);
+        pl.off_partL = off; off += align_up((size_t)pl.nz * pb.n_L() * 4, 256);
+        pl.off_partR = off; off += align_up((size_t)pl.nz * pb.n_R() * 4, 256);
+        pl.total = off;
+        if (pl.total <= room || pl.nz == 1) return pl;
+    }
 }
 
 }  // namespace
@@ -829,12 +833,13 @@ int fwd_t_wide(const Problem& pb, const void* x, const void* R, const void* L, v
 }
 
 size_t bwd_wide_workspace(const Problem& pb) { return make_plan(pb).total; }
+size_t bwd_wide_least(const Problem& pb) { return make_plan(pb, 0).total; }
 
 int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx,
              void* dR, void* dL, void* ws, hipStream_t st)
 {
     const Entry* e = find(pb);
-    const Plan pl = make_plan(pb);
+    const Plan pl = make_plan(pb, pb.ws_bytes);
     if (!e || !pl.ok) return -2;
     char* w = (char*)ws;
     uint16_t* Y1ws = (uint16_t*)(w + pl.off_y1);

@@ -449,7 +449,9 @@ void fill_descs_tiled(const Problem& pb, WgradDesc& dl, WgradDesc& dr)
     dr.M = pb.q; dr.N = pb.p; dr.G = pb.k; dr.rows = pb.B;
 }
 
-TiledPlan make_plan_tiled(const Problem& pb)
+// `room`: bytes there are; a plan with one chunk may need more.  (Chunks are whole 64 rows, so that a batch just below a multiple can
+// have more of them than a longer one.)
+TiledPlan make_plan_tiled(const Problem& pb, size_t room = SIZE_MAX)
 {
     TiledPlan pl{};
     WgradDesc dl, dr;
@@ -461,21 +463,23 @@ TiledPlan make_plan_tiled(const Problem& pb)
     const int64_t maxz = (pb.B + 255) / 256;
     if (z > maxz) z = maxz;
     if (z < 1) z = 1;
-    const int64_t rpc = ((pb.B + z - 1) / z + 63) / 64 * 64;
-    pl.rows_per_chunk = (int)(rpc > 0 ? rpc : 64);
-    pl.nz = (int)((pb.B + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
-    if (pl.nz < 1) pl.nz = 1;
     const size_t rows = (size_t)(pb.B > 0 ? pb.B : 1);
-    size_t off = 0;
-    pl.off_u = off;   off += align_up(rows * pb.kq() * 2, 256);
-    pl.off_dw = off;  off += align_up(rows * pb.n_out() * 2, 256);
-    pl.off_dy1 = off; off += align_up(rows * pb.kq() * 2, 256);
-    pl.off_lt = off;  off += align_up(pb.n_L() * 2, 256);
-    pl.off_rt = off;  off += align_up(pb.n_R() * 2, 256);
-    pl.off_partL = off; off += align_up((size_t)pl.nz * pb.n_L() * 4, 256);
-    pl.off_partR = off; off += align_up((size_t)pl.nz * pb.n_R() * 4, 256);
-    pl.total = off;
-    return pl;
+    for (;; z = pl.nz - 1) {
+        const int64_t rpc = ((pb.B + z - 1) / z + 63) / 64 * 64;
+        pl.rows_per_chunk = (int)(rpc > 0 ? rpc : 64);
+        pl.nz = (int)((pb.B + pl.rows_per_chunk - 1) / pl.rows_per_chunk);
+        if (pl.nz < 1) pl.nz = 1;
+        size_t off = 0;
+        pl.off_u = off;   off += align_up(rows * pb.kq() * 2, 256);
+        pl.off_dw = off;  off += align_up(rows * pb.n_out() * 2, 256);
+        pl.off_dy1 = off; off += align_up(rows * pb.kq() * 2, 256);
+        pl.off_lt = off;  off += align_up(pb.n_L() * 2, 256);
+        pl.off_rt = off;  off += align_up(pb.n_R() * 2, 256);
+        pl.off_partL = off; off += align_up((size_t)pl.nz * pb.n_L() * 4, 256);
+        pl.off_partR = off; off += align_up((size_t)pl.nz * pb.n_R() * 4, 256);
+        pl.total = off;
+        if (pl.total <= room || pl.nz == 1) return pl;
+    }
 }
 
 template <int RT, bool DX_ONLY>
@@ -537,12 +541,13 @@ bool tiled_bwd_supported(const Problem& pb)
 }
 
 size_t tiled_bwd_workspace(const Problem& pb) { return make_plan_tiled(pb).total; }
+size_t tiled_bwd_least(const Problem& pb) { return make_plan_tiled(pb, 0).total; }
 
 int tiled_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR,
               void* dL, void* ws, hipStream_t st)
 {
     if (!tiled_bwd_supported(pb)) return -2;
-    const TiledPlan pl = make_plan_tiled(pb);
+    const TiledPlan pl = make_plan_tiled(pb, pb.ws_bytes);
     const bool f32out = pb.wgrad_f32();
     if (pb.B == 0) {
         int rc = f32out ? launch_fill_zero_f32((float*)dR, pb.n_R(), st) : launch_fill_zero_u16((uint16_t*)dR, pb.n_R(), st);

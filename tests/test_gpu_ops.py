@@ -129,11 +129,12 @@ def test_backward_keeps_32_bits_on_short_batches(case):
 
 
 # A workspace of the largest batch serves a shorter last one, also where the shorter one asks for more: four-block layers on both
-# sides of the limits of the short-batch kernels (wide: 2560 rows, shape-generic bf16: 4096), the shape-generic contractions where a
-# longer batch has fewer chunks, and those with a workspace that only the SIMT kernels can use.
+# sides of the limits of the short-batch kernels (wide: 2560 rows, shape-generic bf16: 4096), batches with one chunk more than a
+# slightly longer one, and those with a workspace that only the SIMT kernels can use.
 LAST = [((128, 128, 512), 4, 2561, 2560, "bf16"), ((192, 192, 192), 4, 2600, 1500, "bf16"), ((96, 96, 96), 4, 4097, 4096, "bf16"),
         ((192, 192, 768), 4, 2049, 2048, "f32"), ((101, 37, 16), 8, 6145, 6144, "bf16"), ((192, 192, 36), 4, 0, 3072, "bf16"),
-        ((64, 64, 64), 64, 257, 256, "bf16")]
+        ((64, 64, 64), 64, 257, 256, "bf16"), ((256, 256, 1024), 4, 3073, 3072, "bf16"), ((192, 192, 192), 4, 8193, 8192, "bf16"),
+        ((64, 96, 96), 2, 9217, 9216, "bf16"), ((32, 32, 32), 32, 4097, 4096, "bf16"), ((16, 16, 16), 16, 4097, 4096, "bf16")]
 
 
 @pytest.mark.parametrize("case", LAST, ids=str)
