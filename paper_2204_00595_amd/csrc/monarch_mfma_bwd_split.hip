@@ -282,16 +282,21 @@ Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 
 }  // namespace
 
-// Up to 2560 rows, 40 row tiles of the wide backward, which takes nearly the same time for any number of them (1024 ->
-// 4096 -> 1024 training step: 200 rows 240 and 101 us, 2000 rows 292 and 229, 3000 rows 328 and 310; 768 -> 3072 ->
-// 768: 213 and 174, 235 and 241 at 2000 and 3000 rows).  Where the other choice is the shape-generic bf16 kernel (width
-// 384) up to 4096.  Not where it is the shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors
-// between the factors in fp32.
+// Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows, 2048 where the output is no wider
+// than the input and 1536 where it is narrower (dx is then the larger product and each workgroup has a share of the rows of dU again), and
+// no more than 2^19 / q, where `adjoint` runs out of workgroups of one column tile.  Whole backward with bias on these kernels and on the wide
+// one: blocks of 256 and 1024, 300 rows 36 and 63 us, 2000 rows 54 and 68, 2500 rows 73 and 69; of 192 and 768, 2500 rows 48 and 55, 3000
+// rows 64 and 55; of 192, 2000 rows 37 and 39, 3000 rows 52 and 40; of 256, 2000 rows 42 and 46, 2500 rows 55 and 46; of 1024 and 256, 1500 rows
+// 65 and 70, 2000 rows 77 and 71; of 768 and 192, 1200 rows 46 and 54, 1536 rows 56 and 55.  Not for blocks of 64 alone (8 rows 19 and
+// 18, 1000 rows 22 and 21).  Where the other choice is the shape-generic bf16 kernel (width 384) up to 4096.  Not where it is
+// the shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors between the factors in fp32.
 bool bwd_split_preferred(const Problem& pb)
 {
-    if (!bwd_wide_supported(pb) && !tiled_bwd_supported(pb)) return false;
+    const bool wide = bwd_wide_supported(pb);
+    if (!wide && !tiled_bwd_supported(pb)) return false;
+    if (wide && (pb.B * pb.q > (1 << 19) || pb.B > (pb.s > pb.p ? 2560 : pb.s == pb.p ? 2048 : 1536) || (pb.p == 64 && pb.s == 64))) return false;
     return pb.dtype == 1 && pb.k == 4 && !pb.perm_b() && pb.p % 32 == 0 && pb.q % 32 == 0 && pb.s % 32 == 0 && pb.p <= 1024 &&
-           pb.s <= 1024 && pb.q <= 256 && pb.B > 0 && pb.B <= (bwd_wide_supported(pb) ? 2560 : 4096) && make_plan(pb).ok;
+           pb.s <= 1024 && pb.q <= 256 && pb.B > 0 && pb.B <= 4096 && make_plan(pb).ok;
 }
 
 size_t bwd_split_workspace(const Problem& pb) { return make_plan(pb).total; }

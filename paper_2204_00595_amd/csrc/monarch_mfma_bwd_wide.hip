@@ -5,7 +5,8 @@
 //             weight operand below is then one contiguous, fully coalesced 1 KiB read per wave.
 //             L is transposed with its rows picked in the order the mid permutation scatters them,
 //             R is transposed with its K-slots in the order the chained accumulators of `data` hold dY1.
-//   data      one workgroup per 64 batch rows, wave w <-> R block kk = w:
+//   data      blocks of 192 and more, and short batches: two workgroups per 64 batch rows, two waves for an R block (bwd_pair_data,
+//             which passes dY1 through LDS); else, and for the transposed multiply, one workgroup, wave w <-> R block kk = w:
 //               X) recompute step 1, Y1[b][kk][j] (x through a DMA-filled LDS ring, packed R fragments
 //                  straight into registers), and write it to the workspace (dL needs U);
 //               A) dY1[b][kk][c*Q/4 + r1] = sum_l dy[b][4*l + c] * L[c][l][4*r1 + kk]
@@ -429,7 +430,9 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
 // + 96.0 and 117.5 + 97.6.
 // More chunks of dy or of fragments on the way change nothing; 128 rows per workgroup (43.5; 109.4 + 100.5) and all
 // four blocks in eight waves (the whole training step 516 us against 518, but 300 against 287 at 192 x 768 and 40000
-// rows) do not pay.
+// rows) do not pay.  With q = 256 the form that recomputes step 1 has 10 to 18 registers too few for two workgroups and spills them; step 1
+// in a launch of its own instead (monarch_mfma_y1.hip) is no better up to 12000 rows (256 x 1024, whole backward: 8192 rows 96 and 99 us, 12000
+// rows 120 and 118, 16384 rows 149 and 143).
 template <int P_, int Q_, int S_>
 struct BwdPair {
     static constexpr int K = 4, P = P_, Q = Q_, S = S_, IG = 4;
@@ -858,8 +861,8 @@ int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, co
     hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)nprep), dim3(256), 0, st, (const uint16_t*)L, (const uint16_t*)R,
                        XF, LF, RF, pb.p, pb.q, pb.s, e->ig, !pairs(pb));
     if (hipGetLastError() != hipSuccess) return -4;
-    // Step 1 (Y1, for dL) is recomputed either by the data kernel itself or, for the shapes that have it, by a
-    // GEMM of its own with four times the rows per workgroup (monarch_mfma_y1.hip); not at all when the forward saved it.
+    // Step 1 (Y1, for dL) is recomputed either by the data kernel itself or, for long batches of the shapes that have it, by
+    // a GEMM of its own with four times the rows per workgroup (monarch_mfma_y1.hip); not at all when the forward saved it.
     const bool y1_apart = !pb.saved && y1_gemm_supported(pb);
     int rc = 0;
     if (y1_apart) {

@@ -419,13 +419,13 @@ Grads c64_bwd(bool with_ws, const Tensor& dy, const Tensor& x, const Tensor& R, 
 struct LinearFn : torch::autograd::Function<LinearFn> {
     // Where keeping the vector pays, by the GPU time of a training step with bias, recomputed and kept: fp32 and odd blocks always
     // (192 x 192, four blocks, fp32, 12608 rows: one contraction of 53 us of 400 less).  The bf16 layers of four blocks that are
-    // multiples of 64 have other forwards for the call that keeps nothing.  Those of short batches (256 x 1024: 200 rows 49 and 73
-    // us, 1000 rows 80 and 89) lose their lead between 1500 and 2500 rows, the wider the layer the sooner (192 x 192: 2000 rows 54
-    // and 57, 2500 rows 57 and 56; 192 x 768: 1500 rows 69 and 68, 2500 rows 80 and 72).  Over long batches the packed forward wins
-    // for wide outputs, by most in the widest layer, whose crossing is the line (256 x 1024: 8192 rows 159 and 150, 9000 rows 162
-    // and 176, 12000 rows 185 and 196).  192 x 768 crosses at 11000 rows (8192 rows 113 and 109, 10000 rows 127 and 126, 12000 rows
-    // 135 and 137), 192 x 576 and 128 x 512 not up to 16384 (12000 rows 121 and 117; 92 and 87), which the line costs 3 to 5 %;
-    // outputs no wider than the input gain at every length (768 x 192, 16384 rows: 176 and 150).
+    // multiples of 64 have other forwards for the call that keeps nothing.  Those of short batches (256 x 1024: 300 rows 47 and 54
+    // us, 1000 rows 58 and 59) lose their lead between 1500 and 3500 rows (256 x 1024: 2000 rows 76 and 73; 192 x 768: 2000 rows 60 and
+    // 62, 2500 rows 66 and 63; 192 x 192: 2500 rows 50 and 52, 3500 rows 57 and 55; 1024 x 256: 1500 rows 87 and 92, 2500 rows 103
+    // and 95).  Over long batches the packed forward wins for wide outputs, by most in the widest layer (256 x 1024: 4500 rows 107 and 103,
+    // 8192 rows 131 and 136, 12000 rows 169 and 179); 192 x 768 crosses at 5000 rows (8192 rows 95 and 97, 12000 rows 121 and 129),
+    // 256 x 768 at 8192 (12000 rows 143 and 150), 192 x 576 and 128 x 512 not up to 12000 (108 and 108; 82 and 80): the line between
+    // them costs up to 4 % on either side.  Outputs no wider than the input gain at every length (768 x 192, 16384 rows: 166 and 142).
     static bool keeps(const Tensor& x, const Tensor& R, const Tensor& L)
     {
         const int64_t rows = x.size(0), p = R.size(2), q = R.size(1), s = L.size(1);

@@ -193,3 +193,38 @@ def test_tiles_stay_inside_the_workspace(case):
     y = B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws[:need])
     parity_util.check(sh.name, y.float().cpu().numpy(), oracle.fwd(x, R, L), 2e-2)
     assert bool((ws[need:] == 0xA5).all())
+
+
+# The backward on either side of its row limits: short-batch kernels up to them (2048, 1536, 2560 rows; none for blocks of 64), and the
+# recomputed vector from a product of its own beyond 8192 rows.
+LINES = [(256, 256, 1024, 2048), (192, 192, 192, 2048), (128, 128, 512, 2560), (512, 128, 128, 1536), (1024, 256, 256, 1536), (64, 64, 64, 40),
+         (1024, 256, 256, 8192), (768, 192, 192, 8192)]
+
+
+@pytest.mark.parametrize("past", [0, 1])
+@pytest.mark.parametrize("case", LINES, ids=str)
+def test_backward_at_its_row_limits(case, past):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    p, q, s, rows = case
+    rows += past
+    gen = torch.Generator(device="cuda").manual_seed(rows + p)
+    x, R, L, dy = (torch.randn(shp, generator=gen, device="cuda").mul_(std).to(torch.bfloat16) for shp, std in (
+        ((rows, 4 * p), 1.0), ((4, q, p), p ** -0.5), ((4, s, q), q ** -0.5), ((rows, 4 * s), 1.0)))
+    dx, dR, dL, db = B.monarch_bwd_bias(dy, x, R, L)
+    xd, Rd, Ld, dyd = (t.double() for t in (x, R, L, dy))
+    # y[b][l*4 + c] = sum_r L[c][l][r] U[b][c][r], and U[b][c][r] is Y1 at the flat position c*q + r of (j, kk)
+    Y1 = torch.stack([xd[:, kk * p:(kk + 1) * p] @ Rd[kk].T for kk in range(4)], 2).reshape(rows, 4, q)
+    dW = dyd.reshape(rows, s, 4)
+    dU = torch.stack([dW[:, :, c] @ Ld[c] for c in range(4)], 1)
+    dY1 = dU.reshape(rows, q, 4)
+    want = (torch.cat([dY1[:, :, kk] @ Rd[kk] for kk in range(4)], 1),
+            torch.stack([dY1[:, :, kk].T @ xd[:, kk * p:(kk + 1) * p] for kk in range(4)]),
+            torch.stack([dW[:, :, c].T @ Y1[:, c] for c in range(4)]), dyd.sum(0))
+    for name, g, w in zip(("dx", "dR", "dL", "dbias"), (dx, dR, dL, db), want):
+        # bf16 roundings of 2^-9 / sqrt(3) root mean square each: the vector, a partial sum, the result; a third more for the largest
+        err = float(torch.linalg.norm(g.double() - w) / torch.linalg.norm(w))
+        assert err <= 4e-3, (name, err)
+    rel = torch.linalg.norm(dx.double() - want[0], dim=1) / torch.linalg.norm(want[0], dim=1)
+    assert float(rel.max()) <= 6e-3   # no row: twice the root mean square
