@@ -7,7 +7,7 @@
 `traffic` scales the FETCH_SIZE / WRITE_SIZE readings (KiB per dispatch) by what the same counter
 shows for the library's plain copy kernel (stream_copy_kernel, N bytes read and N bytes written per
 dispatch), and reports HBM bytes per launch for every kernel of the library, plus the totals per
-C-ABI call (monarch_fwd = the forward kernel, monarch_fwd_ws = the pack kernel + the packed-weight
+C-ABI call (every kernel as often as the call launches it; monarch_fwd = the forward kernel, monarch_fwd_ws = the pack kernel + the packed-weight
 forward, monarch_bwd = every other kernel of the library; the m = 64 pack kernel serves both
 monarch_fwd_ws and monarch_bwd and is counted with the latter).
 """
@@ -68,20 +68,22 @@ def cmd_traffic(args):
     print("%-60s %6s %14s %14s" % ("kernel", "calls", "fetch_MB", "write_MB"))
     calls = {"monarch_fwd": [0.0, 0.0], "monarch_fwd_ws": [0.0, 0.0], "monarch_bwd": [0.0, 0.0]}
     per_kernel = {}
+    picked = []
     for k in sorted(fetch):
-        if k == COPY_KERNEL or not any(t in k for t in ("fwd_", "bwd_", "wgrad_", "prep_", "y1_gemm", "pack64", "transpose64", "transpose_blocks", "reduce_sq16", "generic_", "fill_zero", "f32_to_bf16")):
+        if k == COPY_KERNEL or not any(t in k for t in ("fwd_", "bwd_", "wgrad_", "prep_", "y1_gemm", "pack64", "u_sq64", "transpose64", "transpose_blocks", "reduce_sq16", "generic_", "fill_zero", "f32_to_bf16")):
             continue
         fb, wb = fetch[k] * f_scale * 1024.0, write.get(k, 0.0) * w_scale * 1024.0
         per_kernel[k] = {"fetch_bytes": fb, "write_bytes": wb}
+        picked.append((k, fb, wb))
         print("%-60s %6d %14.2f %14.2f" % (k[:60], nf[k], fb / 1e6, wb / 1e6))
-        if k.startswith("fwd_frag") or k.startswith("pack_fwd") or k.startswith("fwd_sq64_kernel<true>"):
-            call = "monarch_fwd_ws"
-        elif k.startswith("fwd_") or k.startswith("generic_fwd") or k.startswith("tiled_fwd"):
-            call = "monarch_fwd"
-        else:
-            call = "monarch_bwd"
-        calls[call][0] += fb
-        calls[call][1] += wb
+    call_of = {k: "monarch_fwd_ws" if k.startswith(("fwd_frag", "pack_fwd", "fwd_sq64_kernel<true>")) else
+               "monarch_fwd" if k.startswith(("fwd_", "generic_fwd", "tiled_fwd")) else "monarch_bwd" for k, _, _ in picked}
+    for k, fb, wb in picked:
+        call = call_of[k]
+        # a kernel that a call launches twice: a whole multiple of its rarest kernel's launches
+        per_call = max(1, int(nf[k] / min(nf[o] for o, c in call_of.items() if c == call) + 0.2)) if call == "monarch_bwd" else 1
+        calls[call][0] += fb * per_call
+        calls[call][1] += wb * per_call
     for c, (fb, wb) in calls.items():
         print("%-60s %6s %14.2f %14.2f   total %.2f MB per call" % (c, "", fb / 1e6, wb / 1e6, (fb + wb) / 1e6))
     if args.json:
