@@ -408,7 +408,7 @@ def measure_extras(ly: Layer, calls: int):
             ex["f32_fwd_kernel"] = binding.monarch_kernel_name(2, sh.n_in, sh.k, sh.q, sh.s, 0)
             ex["f32_fwd_tflops"] = sh.fwd_flops() / (ex["f32_fwd_ms"] * 1e-3) / 1e12
             del fx, fy, fdx, fws2
-        # Algorithm 1 on a dense Gaussian n x n matrix: one Jacobi SVD per slice
+        # Algorithm 1 on a dense Gaussian n x n matrix: the leading singular pair of every slice
         Adense = torch.from_numpy(synth.quantize(synth.normal(4343, (sh.n_in, sh.n_in)), sh.dtype)).to(dev).to(dt)
         Rp, Lp = torch.empty_like(Rd), torch.empty_like(Ld)
         ex["project_ms"] = timed_runs(lambda i: binding.monarch_project(Adense, Rp, Lp), 20, 2)[0]

@@ -1,8 +1,8 @@
 // bf16 backward of the four-block layers on batches too short to fill the chip with 64-row tiles of the data kernel of
 // monarch_mfma_bwd_wide.hip: one launch per adjoint factor, so that the weights are spread over all CUs.
 //
-// With the vector between the factors kept in its permuted order, dU[b][4j + kk] = dY1[b][kk][j], both adjoint steps are one
-// operation: the input has its four blocks interleaved, the output has them one after the other,
+// With the vector between the factors kept in its permuted order, dU[b][4j + kk] = dY1[b][kk][j], both adjoint steps
+// are one operation: the input has its four blocks interleaved, the output has them one after the other,
 //     out[b][g*N + n] = sum_m in[b][4m + g] W[g][m][n]
 //   dU from dy:  W = L (m = l, n = r; g*N + n = c*q + r is the permuted position)
 //   dx from dU:  W = R (m = j, n = i)
@@ -14,8 +14,8 @@
 //            wave g keeps block g
 //   wgrad    as in the wide backward (monarch_mfma_wgrad.hip), with dU as the interleaved operand of dR
 //
-// Fragments:  WT[g][nt][t][lane][e] = W[g][16t + 4*(e/2) + 2*(lane/32) + e%2][32*nt + lane%32]: lane half h holds, of the 16 m of
-// a step, the pairs that its 16-byte pieces 2i + h of the line bring.
+// Fragments: WT[g][nt][t][lane][e] = W[g][16t + 4*(e/2) + 2*(lane/32) + e%2][32*nt + lane%32]: lane half h holds, of
+// the 16 m of a step, the pairs that its 16-byte pieces 2i + h of the line bring.
 //
 // What bounds it: latency for a few row tiles (three launches of about 6 us), the address path of the L1 above; the
 // rows come in whole lines that change places through LDS (RowPieces; training step of the feed-forward block of width
@@ -282,14 +282,16 @@ Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 
 }  // namespace
 
-// Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows, 2048 where the output is no wider
-// than the input and 1536 where it is narrower (dx is then the larger product and each workgroup has a share of the rows of dU again), and
-// no more than 2^19 / q, where `adjoint` runs out of workgroups of one column tile.  Whole backward with bias on these kernels and on the wide
-// one: blocks of 256 and 1024, 300 rows 36 and 63 us, 2000 rows 54 and 68, 2500 rows 73 and 69; of 192 and 768, 2500 rows 48 and 55, 3000
-// rows 64 and 55; of 192, 2000 rows 37 and 39, 3000 rows 52 and 40; of 256, 2000 rows 42 and 46, 2500 rows 55 and 46; of 1024 and 256, 1500 rows
-// 65 and 70, 2000 rows 77 and 71; of 768 and 192, 1200 rows 46 and 54, 1536 rows 56 and 55.  Not for blocks of 64 alone (8 rows 19 and
-// 18, 1000 rows 22 and 21).  Where the other choice is the shape-generic bf16 kernel (width 384) up to 4096.  Not where it is
-// the shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors between the factors in fp32.
+// Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows, 2048 where
+// the output is no wider than the input and 1536 where it is narrower (dx is then the larger product and each
+// workgroup has a share of the rows of dU again), and no more than 2^19 / q, where `adjoint` runs out of workgroups
+// of one column tile.  Whole backward with bias on these kernels and on the wide one: blocks of 256 and 1024, 300
+// rows 36 and 63 us, 2000 rows 54 and 68, 2500 rows 73 and 69; of 192 and 768, 2500 rows 48 and 55, 3000 rows 64 and
+// 55; of 192, 2000 rows 37 and 39, 3000 rows 52 and 40; of 256, 2000 rows 42 and 46, 2500 rows 55 and 46; of 1024 and
+// 256, 1500 rows 65 and 70, 2000 rows 77 and 71; of 768 and 192, 1200 rows 46 and 54, 1536 rows 56 and 55.  Not for
+// blocks of 64 alone (8 rows 19 and 18, 1000 rows 22 and 21).  Where the other choice is the shape-generic bf16
+// kernel (width 384) up to 4096.  Not where it is the shape-generic contractions (q = 256 with p or s = 1024), which
+// hold the vectors between the factors in fp32.
 bool bwd_split_preferred(const Problem& pb)
 {
     const bool wide = bwd_wide_supported(pb);

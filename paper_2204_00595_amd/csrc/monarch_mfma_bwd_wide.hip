@@ -430,9 +430,9 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
 // + 96.0 and 117.5 + 97.6.
 // More chunks of dy or of fragments on the way change nothing; 128 rows per workgroup (43.5; 109.4 + 100.5) and all
 // four blocks in eight waves (the whole training step 516 us against 518, but 300 against 287 at 192 x 768 and 40000
-// rows) do not pay.  With q = 256 the form that recomputes step 1 has 10 to 18 registers too few for two workgroups and spills them; step 1
-// in a launch of its own instead (monarch_mfma_y1.hip) is no better up to 12000 rows (256 x 1024, whole backward: 8192 rows 96 and 99 us, 12000
-// rows 120 and 118, 16384 rows 149 and 143).
+// rows) do not pay.  With q = 256 the form that recomputes step 1 has 10 to 18 registers too few for two workgroups
+// and spills them; step 1 in a launch of its own instead (monarch_mfma_y1.hip) is no better up to 12000 rows (256 x
+// 1024, whole backward: 8192 rows 96 and 99 us, 12000 rows 120 and 118, 16384 rows 149 and 143).
 template <int P_, int Q_, int S_>
 struct BwdPair {
     static constexpr int K = 4, P = P_, Q = Q_, S = S_, IG = 4;
@@ -443,7 +443,8 @@ struct BwdPair {
     static constexpr int T_STRIDE = 2 * Q + 8;       // LDS tile [64][two blocks of Q]
     static constexpr int DX_COLS = IG * 16;          // dx columns of a tile of stage B
     static constexpr int DX_STRIDE = DX_COLS + 8;
-    // stage B: the two waves of a block take every other tile of columns, or 32 rows each where the tiles do not come out even
+    // stage B: the two waves of a block take every other tile of columns, or 32 rows each where the tiles do not come
+    // out even
     static constexpr bool BY_COLS = P / DX_COLS % 2 == 0;
     static constexpr int BT = BY_COLS ? NBT : NBT / 2, TILES = BY_COLS ? P / DX_COLS / 2 : P / DX_COLS;
     static constexpr size_t LDS_TILE = (size_t)BM * T_STRIDE * 2;
@@ -594,7 +595,8 @@ bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, c
     // ------------------------------------------------- B: dx ----
     constexpr int U = C::Q / 32;
     const uint16_t* Rt = RF + ((size_t)kk * (C::P / C::DX_COLS) * U * C::IG * 64 + lane) * 8;
-    // The fragments run through a ring of NSB steps that continues across the tiles (U % NSB == 0 keeps the slot numbers static).
+    // The fragments run through a ring of NSB steps that continues across the tiles (U % NSB == 0 keeps the slot
+    // numbers static).
     constexpr int NSB = (U % 4 == 0) ? 4 : ((U % 3 == 0) ? 3 : 2);
     static_assert(U % NSB == 0, "ring");
     const auto column_tile = [&](int n) { return C::BY_COLS ? 2 * n + half : n; };
@@ -640,8 +642,8 @@ bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, c
                     acc[it * C::BT + bt] = mfma16(as_bf16x8(af[u % NSB][it]), bfr, acc[it * C::BT + bt]);
             }
         }
-        // D^T[i][b]: lane holds i = it*16 + 4*h + 0..3 for row b = bt*16 + l16; 16 rows at a time leave by way of the wave's
-        // staging tile (private to the wave: no workgroup barrier)
+        // D^T[i][b]: lane holds i = it*16 + 4*h + 0..3 for row b = bt*16 + l16; 16 rows at a time leave by way of the
+        // wave's staging tile (private to the wave: no workgroup barrier)
 #pragma unroll
         for (int bt = 0; bt < C::BT; ++bt) {
 #pragma unroll
@@ -778,8 +780,8 @@ void fill_descs(const Problem& pb, WgradDesc& dl, WgradDesc& dr)
     dr.M = pb.q; dr.N = pb.p; dr.G = 4; dr.rows = pb.B;
 }
 
-// `room`: bytes there are; a plan with one chunk may need more.  (Chunks are whole 64 rows, so that a batch just below a multiple can
-// have more of them than a longer one.)
+// `room`: bytes there are; a plan with one chunk may need more.  (Chunks are whole 64 rows, so that a batch just
+// below a multiple can have more of them than a longer one.)
 Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 {
     Plan pl{};
@@ -861,8 +863,9 @@ int bwd_wide(const Problem& pb, const void* dy, const void* x, const void* R, co
     hipLaunchKernelGGL(prep_frag_kernel, dim3((unsigned)nprep), dim3(256), 0, st, (const uint16_t*)L, (const uint16_t*)R,
                        XF, LF, RF, pb.p, pb.q, pb.s, e->ig, !pairs(pb));
     if (hipGetLastError() != hipSuccess) return -4;
-    // Step 1 (Y1, for dL) is recomputed either by the data kernel itself or, for long batches of the shapes that have it, by
-    // a GEMM of its own with four times the rows per workgroup (monarch_mfma_y1.hip); not at all when the forward saved it.
+    // Step 1 (Y1, for dL) is recomputed either by the data kernel itself or, for long batches of the shapes that have
+    // it, by a GEMM of its own with four times the rows per workgroup (monarch_mfma_y1.hip); not at all when the
+    // forward saved it.
     const bool y1_apart = !pb.saved && y1_gemm_supported(pb);
     int rc = 0;
     if (y1_apart) {

@@ -14,8 +14,8 @@
 // cycles a fragment for MFMAs of 32 cycles on four SIMDs.  With U in rows, a fragment of it took 62 cycles, and so did
 // one of x (1531 rows: the stages of 1024 -> 4096 5.8 + 16.4 -> 5.2 + 15.5 us, the second one now bound by the
 // nonlinearity, of 4096 -> 1024 12.8 + 7.6 -> 10.4 + 5.2).
-// Measured, 1024 -> 4096 -> 1024 with bias and GELU, against the fused kernel alone and against U in rows: 8 rows 54,
-// 15.7 and 13.9 us, 256 rows 66, 19.9 and 18.6, 1531 rows 69, 40.1 and 32.7; 768 -> 3072 -> 768, 1531 rows: 33.0 and
+// Measured, 1024 -> 4096 -> 1024 with bias and GELU, against the fused kernel alone and against U in rows: 8 rows 54
+// us and 16 for both, 256 rows 66, 19.9 and 18.6, 1531 rows 69, 40.1 and 32.7; 768 -> 3072 -> 768, 1531 rows: 33.0 and
 // 25.6.
 #include "../../include/monarch.h"
 #include "monarch_internal.h"

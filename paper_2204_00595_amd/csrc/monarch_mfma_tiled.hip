@@ -449,8 +449,8 @@ void fill_descs_tiled(const Problem& pb, WgradDesc& dl, WgradDesc& dr)
     dr.M = pb.q; dr.N = pb.p; dr.G = pb.k; dr.rows = pb.B;
 }
 
-// `room`: bytes there are; a plan with one chunk may need more.  (Chunks are whole 64 rows, so that a batch just below a multiple can
-// have more of them than a longer one.)
+// `room`: bytes there are; a plan with one chunk may need more.  (Chunks are whole 64 rows, so that a batch just
+// below a multiple can have more of them than a longer one.)
 TiledPlan make_plan_tiled(const Problem& pb, size_t room = SIZE_MAX)
 {
     TiledPlan pl{};

@@ -6,7 +6,8 @@
 // workgroup streams the whole of R through its CU's L1 for 64 rows, and for layers with long blocks
 // (p = 1024: R is 2 MB) that stream is the larger half of the kernel.  Y1 has to go through the
 // workspace anyway, so nothing ties this product to 64-row tiles: here a workgroup takes 256 rows of
-// one block (192 for q = 192), so R passes each L1 a quarter as often.  Used for p >= 768 and long batches (see the table below).
+// one block (192 for q = 192), so R passes each L1 a quarter as often.  Used for p >= 768 and long batches (see the
+// table below).
 //
 //   workgroup  = (row tile of BM = 32 * NW rows, block kk); NW = 8 waves (6 for q = 192)
 //   x          travels in 64-column chunks through an LDS ring of XR = 4 slots filled by
@@ -183,11 +184,12 @@ struct Entry {
     int (*fn)(const Problem&, const void*, const uint16_t*, uint16_t*, hipStream_t);
 };
 
-// Only the layers with long blocks gain, and only over long batches: the data kernel that recomputes step 1 itself (two workgroups for
-// each row tile, monarch_mfma_bwd_wide.hip) is faster up to 8192 rows.  Whole backward with this kernel and without: 4096 -> 1024, 2000 rows
-// 82 and 71 us, 8192 rows 112 and 100, 10000 rows 128 and 136, 16384 rows 172 and 185; 3072 -> 768, 8192 rows 78 and 75, 10000 rows
-// 92 and 94, 16384 rows 129 and 117.  Blocks p = 256 (1024 -> 4096): 8192 rows 99 and 96, 16384 rows 143 and 149; 1024 -> 1024: 62 and
-// 59, 86 and 83; for short blocks the extra launch, and the copy-out that nothing overlaps, cost more than the R stream saved.
+// Only the layers with long blocks gain, and only over long batches: the data kernel that recomputes step 1 itself
+// (two workgroups for each row tile, monarch_mfma_bwd_wide.hip) is faster up to 8192 rows.  Whole backward with this
+// kernel and without: 4096 -> 1024, 2000 rows 82 and 71 us, 8192 rows 112 and 100, 10000 rows 128 and 136, 16384 rows
+// 172 and 185; 3072 -> 768, 8192 rows 78 and 75, 10000 rows 92 and 94, 16384 rows 129 and 117.  Blocks p = 256 (1024
+// -> 4096): 8192 rows 99 and 96, 16384 rows 143 and 149; 1024 -> 1024: 62 and 59, 86 and 83; for short blocks the
+// extra launch, and the copy-out that nothing overlaps, cost more than the R stream saved.
 constexpr int64_t kRowsApart = 8192;
 const Entry kTable[] = {
     {768, 192, launch<Y1Gemm<768, 192>>},    // GPT-2 small fc2 3072 -> 768

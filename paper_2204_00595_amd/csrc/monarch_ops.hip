@@ -1,7 +1,7 @@
-// Shape-generic multiply on the matrix cores, fp32 and bf16: any k, any block sizes from 16 up, both readings of the mid
-// permutation.  It serves the calls that bring a workspace on every shape without a kernel of its own (fp32 Transformer
-// layers, block sizes that are multiples of nothing); without a workspace, or below 16, the SIMT kernels of
-// monarch_generic.hip run.
+// Shape-generic multiply on the matrix cores, fp32 and bf16: any k, any block sizes from 16 up, both readings of the
+// mid permutation.  It serves the calls that bring a workspace on every shape without a kernel of its own (fp32
+// Transformer layers, block sizes that are multiples of nothing); without a workspace, or below 16, the SIMT kernels
+// of monarch_generic.hip run.
 //
 // Every step of Section 3.3 and every adjoint of one is a batched contraction whose operands lie in memory with three
 // element strides each (block, row, contraction index), and the permutations are nothing but such strides:
@@ -31,13 +31,12 @@
 // barrier and multiply, and what hides it is the number of workgroups on a CU.  So a chunk is 16 contraction indices,
 // one MFMA deep: 64 x 64 tiles then take 30 KB of LDS, five to a CU, where chunks of 32 leave two (4096 -> 1024 fp32,
 // 8000 rows, whole step: 660 us on the fp32 matrix cores, 674 in planes with chunks of 32, 455 with 16); few workgroups
-// take chunks of 32 (launch_chunks).  Small and odd bf16 layers are bound by the memory system.  The intermediate goes through memory (for most shapes it stays in the
-// last-level cache): a fused kernel would hold all k blocks of a row tile, which leaves the large shapes one 16-row
-// tile per CU.
-// Measured, training step: 768 -> 768 fp32, k = 4, 12608 rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix
-// cores, now 250 (one contraction of 3.7 GFLOP takes 35 to 40 us, 50 where an operand is strided, the two weight
-// gradients 74); 196 -> 256 bf16, blocks of 49 and 64, 32768 rows: 458, 121, now 100 us; 2048 -> 512 fp32, 3000 rows:
-// 137, now 112.
+// take chunks of 32 (launch_chunks).  Small and odd bf16 layers are bound by the memory system.  The intermediate
+// goes through memory (for most shapes it stays in the last-level cache): a fused kernel would hold all k blocks of a
+// row tile, which leaves the large shapes one 16-row tile per CU. Measured, training step: 768 -> 768 fp32, k = 4,
+// 12608 rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix cores, now 256 (one contraction of 3.7 GFLOP takes
+// 35 to 40 us, 50 where an operand is strided, the two weight gradients 74); 196 -> 256 bf16, blocks of 49 and 64,
+// 32768 rows: 458, 121, now 96 us; 2048 -> 512 fp32, 3000 rows: 137, now 112.
 #include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
@@ -55,9 +54,10 @@ typedef __attribute__((ext_vector_type(4))) short s16x4;
 
 constexpr int kStep = 16;  // contraction indices of an MFMA
 
-// How an operand is taken: kPieces16, 16-byte pieces along the contiguous index, all of them aligned and inside; kPiecesAny,
-// 16-byte pieces along it wherever they start (gfx950 loads from any address), a piece that crosses the limit being read from
-// the elements that end there and shifted into place on its way to LDS; kElements, single elements at any stride.
+// How an operand is taken: kPieces16, 16-byte pieces along the contiguous index, all of them aligned and inside;
+// kPiecesAny, 16-byte pieces along it wherever they start (gfx950 loads from any address), a piece that crosses the
+// limit being read from the elements that end there and shifted into place on its way to LDS; kElements, single
+// elements at any stride.
 enum Take { kElements, kPiecesAny, kPieces16 };
 
 // One operand: element (g, row, k) at p[g*g_s + row*r_s + k*k_s].
@@ -81,8 +81,8 @@ struct OpDesc {
 };
 
 // Buffer accesses: the base is uniform, a lane adds a 32-bit offset, and a lane whose offset is kNowhere reads zero or
-// writes nothing.  So a ragged tile needs no branch around a load -- with branches the compiler cannot count the loads in
-// flight and waits for all of them at the first use, which undoes the prefetching.
+// writes nothing.  So a ragged tile needs no branch around a load -- with branches the compiler cannot count the
+// loads in flight and waits for all of them at the first use, which undoes the prefetching.
 constexpr uint32_t kNowhere = 0xffffffffu, kBufferBytes = 0x7fffffffu;  // ops_supported keeps a tile's extent below 2 GiB
 __device__ __forceinline__ __amdgpu_buffer_rsrc_t buffer_at(const void* p)
 {
@@ -201,8 +201,8 @@ struct OpTile {
 };
 
 // LDS row strides: contraction-contiguous tiles [row][KC] + 16 bytes (eight lanes of a b128 read then start in eight
-// different bank groups); row-contiguous tiles [k][rows]: odd multiples of 64 bytes, so that the four rows a half wave of the
-// transposing read touches fall on disjoint bank quarters.
+// different bank groups); row-contiguous tiles [k][rows]: odd multiples of 64 bytes, so that the four rows a half
+// wave of the transposing read touches fall on disjoint bank quarters.
 template <bool RC, int ROWS, int KC>
 constexpr int op_lstr()
 {
@@ -216,8 +216,8 @@ __device__ __forceinline__ u32x2 op_lds_tr16(const bf16_t* p)
     return __builtin_bit_cast(u32x2, v);
 }
 
-// The MFMA operands of the contraction indices k0 .. k0 + 15 for the 32 rows from r0, from PL planes of SZ elements: lane
-// (row = lane % 32, h = lane / 32) holds the indices k0 + 8 h .. of its row.
+// The MFMA operands of the contraction indices k0 .. k0 + 15 for the 32 rows from r0, from PL planes of SZ elements:
+// lane (row = lane % 32, h = lane / 32) holds the indices k0 + 8 h .. of its row.
 template <bool RC, int LSTR, int PL, int SZ>
 struct OpFrag {
     bf16x8 v[PL];
@@ -402,8 +402,9 @@ __device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>
     const uint32_t a_o = (uint32_t)(RA ? d.a.k_s : d.a.r_s), a_c = (uint32_t)(RA ? d.a.r_s : d.a.k_s);
     const uint32_t b_o = (uint32_t)(RB ? d.b.k_s : d.b.r_s), b_c = (uint32_t)(RB ? d.b.r_s : d.b.k_s);
 
-    // Partial tiles, whose sums run over hundreds of rows, keep the small products apart: a single sum left the fp32 weight
-    // gradients of some hundred rows further off float64 than the SIMT kernels, which add up 16 rows at a time.
+    // Partial tiles, whose sums run over hundreds of rows, keep the small products apart: a single sum left the fp32
+    // weight gradients of some hundred rows further off float64 than the SIMT kernels, which add up 16 rows at a
+    // time.
     constexpr int SUMS = PARTIAL && kSplit ? 2 : 1;
     f32x16 sums[SUMS][MT][NT];
 #pragma unroll
@@ -522,11 +523,11 @@ ops_gemm_pair_kernel(const OpDesc d0, const OpDesc d1)
     }
 }
 
-// out[e] = sum over the batch chunks of P[z][e], for both gradients.  WAVES = 1: a thread per element.  WAVES > 1, for many
-// chunks: a workgroup owns 64 elements, wave w adds the chunks w, w + WAVES, ..., the sums of the waves are added in order, and
-// workgroups from `blocks01` on run the second pass of the bias gradient.
-// Bound by latency: the 128 chunks of blocks of 49 x 49 and 64 x 49 took 11.7 us with a thread per element and the bias pass
-// 6.7 us in a launch of its own, together 5.3; at 16 chunks of 192 x 192 a thread per element takes 5.1 us, 16 waves 13.
+// out[e] = sum over the batch chunks of P[z][e], for both gradients.  WAVES = 1: a thread per element.  WAVES > 1,
+// for many chunks: a workgroup owns 64 elements, wave w adds the chunks w, w + WAVES, ..., the sums of the waves are
+// added in order, and workgroups from `blocks01` on run the second pass of the bias gradient. Bound by latency: the
+// 128 chunks of blocks of 49 x 49 and 64 x 49 took 11.7 us with a thread per element and the bias pass 6.7 us in a
+// launch of its own, together 5.3; at 16 chunks of 192 x 192 a thread per element takes 5.1 us, 16 waves 13.
 constexpr int kSumWaves = 16, kManyChunks = 32;
 struct OpSum {
     const float* P;
@@ -580,8 +581,9 @@ int launch_sum(const OpSum& s0, const OpSum& s1, const ColsumJob* cj, hipStream_
 
 // ---- host side ----
 
-// 16-byte pieces along the contiguous index need every other stride, the extent and the base to be multiples of a piece.
-// Otherwise they are taken wherever they start (no extent is shorter than a piece: blocks have at least 16 elements).
+// 16-byte pieces along the contiguous index need every other stride, the extent and the base to be multiples of a
+// piece. Otherwise they are taken wherever they start (no extent is shorter than a piece: blocks have at least 16
+// elements).
 Take take_of(const void* p, int64_t s1, int64_t s2, int64_t contiguous_stride, int64_t extent, int esize)
 {
     const int v = 16 / esize;
@@ -618,11 +620,11 @@ struct TileSize {
 constexpr int kTileSizes = 5;
 constexpr TileSize kTiles[kTileSizes] = {{128, 128}, {128, 96}, {128, 64}, {64, 64}, {64, 128}};
 
-// Chunks of 32 indices where planes are multiplied by no more workgroups than then run at the same time, one or two to a CU: nothing
-// but the next chunks hides a chunk's way from memory there, and half as many take less time, with the same results bit for bit.
-// x M in fp32, blocks of 256 and 1024, chunks of 16 and 32: 3000 rows 114.5 and 76.4 us; x M^T, 40 rows 20.7 and 17.4, 2000 rows
-// 51.2 and 49.1.  Beyond, chunks of 16 leave room for more workgroups (blocks of 40 x 128 and 128 x 257, k = 3, 8000 rows, x M: 31.0
-// and 43.6 us).
+// Chunks of 32 indices where planes are multiplied by no more workgroups than then run at the same time, one or two
+// to a CU: nothing but the next chunks hides a chunk's way from memory there, and half as many take less time, with
+// the same results bit for bit. x M in fp32, blocks of 256 and 1024, chunks of 16 and 32: 3000 rows 114.5 and 76.4
+// us; x M^T, 40 rows 20.7 and 17.4, 2000 rows 51.2 and 49.1.  Beyond, chunks of 16 leave room for more workgroups
+// (blocks of 40 x 128 and 128 x 257, k = 3, 8000 rows, x M: 31.0 and 43.6 us).
 template <typename TA, typename TB, typename TO, class Cfg, bool RB, Take AV, Take BV>
 int launch_chunks(const OpDesc& d, hipStream_t st)
 {
@@ -688,11 +690,11 @@ int64_t tiles(int64_t n, int t) { return (n + t - 1) / t; }
 
 // The tile that finishes first under a simple model: up to 256 workgroups run one per CU; beyond, rounds of two per CU
 // that share it.  A workgroup costs its (padded) tile plus a fixed share for filling and draining the pipeline.
-// Operands taken element by element keep to 64 rows, whose workgroups hold more of the strided loads in flight, and to 128 columns
-// where there are more than 64, since every column tile loads them again (1024 -> 4096 fp32, 8000 rows: step 559 us with 64 x 64,
-// 521 with 64 x 128, 560 with 128 x 64).  Not where 128 columns would leave half of the CUs idle (x M, blocks of 256 and 1024, 40 rows:
-// 55.2 us with 64 x 128, 41.6 with 64 x 64; from there up to a workgroup per CU it depends: 192 of them, blocks of 256 and 1024, 60.0 and
-// 54.3 us, blocks of 96 19.1 and 21.3).
+// Operands taken element by element keep to 64 rows, whose workgroups hold more of the strided loads in flight, and
+// to 128 columns where there are more than 64, since every column tile loads them again (1024 -> 4096 fp32, 8000
+// rows: step 559 us with 64 x 64, 521 with 64 x 128, 560 with 128 x 64).  Not where 128 columns would leave half of
+// the CUs idle (x M, blocks of 256 and 1024, 40 rows: 55.2 us with 64 x 128, 41.6 with 64 x 64; from there up to a
+// workgroup per CU it depends: 192 of them, blocks of 256 and 1024, 60.0 and 54.3 us, blocks of 96 19.1 and 21.3).
 int pick_tile(int64_t M, int N, int G, bool pieces)
 {
     if (!pieces) return N > 64 && tiles(M, 64) * tiles(N, 128) * G > kCUs / 2 ? 4 : 3;
@@ -753,9 +755,9 @@ int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t 
     return launch_op<TA, TW, TO>(w_rc, cfg, d, st);
 }
 
-// Batch chunks of the weight-gradient contractions: about four workgroups per CU over both (768 -> 768 fp32: 131 us with
-// two, 104 with four), at least four pipeline chunks of rows each, and whole sets of eight, since a chunk belongs to an XCD
-// (4096 -> 1024 fp32 with three chunks: three XCDs busy, 1088 us; with eight 465 us).
+// Batch chunks of the weight-gradient contractions: about four workgroups per CU over both (768 -> 768 fp32: 131 us
+// with two, 104 with four), at least four pipeline chunks of rows each, and whole sets of eight, since a chunk
+// belongs to an XCD (4096 -> 1024 fp32 with three chunks: three XCDs busy, 1088 us; with eight 465 us).
 struct WgradPlan {
     int cfg;
     int nz;

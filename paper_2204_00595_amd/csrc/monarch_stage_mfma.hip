@@ -1,6 +1,6 @@
 // Complex-valued Monarch multiply on the matrix cores (complex64, fp32 arithmetic), for square blocks
-// p = q = s, a multiple of 8 from 16 to 64, and any k.  The paper's results hold over C (Notation Review); the steps are
-// those of Section 3.3 with the permutations of Definition 3.1, the gradients those of monarch_complex.hip.
+// p = q = s, a multiple of 8 from 16 to 64, and any k.  The paper's results hold over C (Notation Review); the steps
+// are those of Section 3.3 with the permutations of Definition 3.1, the gradients those of monarch_complex.hip.
 //
 // A complex product is a real product of twice the size: with a vector stored as interleaved (re, im) pairs,
 // y = W x over C is  y' = W' x'  over R, where W'[2j+e][2i+t] = (Wr, -Wi; Wi, Wr)[e][t].  The activations are
@@ -70,7 +70,8 @@ __device__ __forceinline__ int mid_src(int g, int k, int q, bool perm_b)
     return r * k + c;
 }
 
-// Element i of row `row` of a 32-row tile straight from memory, as the tiles below take it (zero past the end of the batch).
+// Element i of row `row` of a 32-row tile straight from memory, as the tiles below take it (zero past the end of the
+// batch).
 template <int P, int IN, bool REAL>
 __device__ __forceinline__ float2 act_value(const float2* __restrict__ src, int64_t rt, int row, int g, int i, int k, int64_t ld, int64_t B)
 {
@@ -415,8 +416,8 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
 // The two stages that touch the outer permutation (y[b][l*k + c] written, dy read the same way), for k a multiple
 // of 8: eight blocks per workgroup, wave w = block 8*oct + w, every wave the same M tile (16 outputs) of its
 // own block, so that the pieces of the permuted side are the eight blocks' values of one (row, l): 64 contiguous bytes
-// instead of 8.  Workgroups that differ only in their M tile read the same activations (they sit on one XCD) and split them
-// again, which costs less than the registers of a second M tile.
+// instead of 8.  Workgroups that differ only in their M tile read the same activations (they sit on one XCD) and
+// split them again, which costs less than the registers of a second M tile.
 //
 // cscatter8_kernel: tiled workspace -> y.  The activations of a wave's block are MFMA operands exactly as they lie
 // in the workspace (lane = row, 512 contiguous bytes per wave load), so they go from global memory to registers
@@ -516,8 +517,8 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
         }
     };
 
-    // two register sets: the next piece of the activations (a whole tile, or half of one where the weights leave less room) is on
-    // its way while the current one is multiplied
+    // two register sets: the next piece of the activations (a whole tile, or half of one where the weights leave less
+    // room) is on its way while the current one is multiplied
     typedef std::integral_constant<int, 0> First;
     typedef std::integral_constant<int, 1> Second;
     float2 xa[CH][4], xb[CH][4];
@@ -762,8 +763,9 @@ ctile_kernel(const float2* __restrict__ in, float2* __restrict__ out, int64_t B,
 // A: dW or dY1 (kInT);  Bv: U (kInT) or x (kInNat).  M = 2*MA real rows (re and im of the
 // result), N = NB columns, K = (row, component): with B'[(b,t)][nb] = component t of Bv[b][nb],
 //   A'[2ma][(b,0)] = ar,  A'[2ma][(b,1)] = ai,  A'[2ma+1][(b,0)] = ai,  A'[2ma+1][(b,1)] = -ar.
-// Wave w owns the 16 values ma = 16w .. 16w+15 and every column.  LDS holds each operand as three bf16 planes (monarch_planes.h)
-// [idx][32 rows x 2 components + 8], the layout of an MFMA operand; the A rows 2ma+1 are made from 2ma on the way out of LDS.
+// Wave w owns the 16 values ma = 16w .. 16w+15 and every column.  LDS holds each operand as three bf16 planes
+// (monarch_planes.h) [idx][32 rows x 2 components + 8], the layout of an MFMA operand; the A rows 2ma+1 are made from
+// 2ma on the way out of LDS.
 template <int LEN, int NTHR, int MODE, bool REAL = false>
 struct WgTile {
     static constexpr int kAll = kRT * LEN / 2;
@@ -857,8 +859,9 @@ struct WgTile {
     }
 };
 
-// REAL: real fp32 operands, two consecutive values per float2: out[g][ma'][nb'] = sum_b A[b][g][ma'] * Bv[b][g][nb'] for
-// the 2*MA x 2*NB real indices; a K = 2 step contracts two batch rows, each lane picking its component of the pair.
+// REAL: real fp32 operands, two consecutive values per float2: out[g][ma'][nb'] = sum_b A[b][g][ma'] * Bv[b][g][nb']
+// for the 2*MA x 2*NB real indices; a K = 2 step contracts two batch rows, each lane picking its component of the
+// pair.
 template <int MA, int NB, int AMODE, int BMODE, bool REAL = false>
 __global__ void __launch_bounds__(kTileWaves<MA> * 64)
 cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float2* __restrict__ part, int64_t B, int k,
@@ -1039,8 +1042,9 @@ int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hi
     return hip_status(hipGetLastError());
 }
 
-// the eight-blocks-per-workgroup stages: about one workgroup per CU, a multiple of 8 per (block octet, M tile); their weights
-// take 12 registers a step of 8 inputs (32 real blocks of 32, 8000 rows, forward and backward: 144 us with two, 133 with one)
+// the eight-blocks-per-workgroup stages: about one workgroup per CU, a multiple of 8 per (block octet, M tile); their
+// weights take 12 registers a step of 8 inputs (32 real blocks of 32, 8000 rows, forward and backward: 144 us with
+// two, 133 with one)
 int splits8_for(const Problem& pb, int mtiles)
 {
     int64_t n = (256 + (pb.k / 8) * mtiles - 1) / ((pb.k / 8) * mtiles);
@@ -1080,9 +1084,10 @@ int launch_gather8_tiles(const Problem& pb, const void* in, const void* W, void*
     return hip_status(hipGetLastError());
 }
 
-// One M tile a wave, whose workgroups read the same rows once for each; two, with all the registers there are, for the real layers with
-// blocks of 64 whose rows take more than 64 MB, so that they come from memory once (x M, 64 blocks: 2000 rows, 33 MB, 39 us with
-// one and 43 with two; 6000 rows 128 and 106, 30000 rows 616 and 485; 32 blocks, 6000 rows, 49 MB, 52 and 53, 12000 rows 122 and 100).
+// One M tile a wave, whose workgroups read the same rows once for each; two, with all the registers there are, for
+// the real layers with blocks of 64 whose rows take more than 64 MB, so that they come from memory once (x M, 64
+// blocks: 2000 rows, 33 MB, 39 us with one and 43 with two; 6000 rows 128 and 106, 30000 rows 616 and 485; 32 blocks,
+// 6000 rows, 49 MB, 52 and 53, 12000 rows 122 and 100).
 template <int M, bool EMIT, bool REAL = false>
 int launch_gather8(const Problem& pb, const void* in, const void* W, void* out, void* dwt, hipStream_t st)
 {
@@ -1115,15 +1120,16 @@ int launch_wgrad(const Problem& pb, const void* A, const void* Bv, void* out, vo
 
 // How dy gets into tiles: by a launch of its own (ctile_kernel), or by a stage that gathers it.
 //
-// The stage that gathers eight blocks side by side (multiples of eight) reads dy and lays it out once per M tile: not for complex blocks
-// with four M tiles (2048 rows: 28 + 40 us with the launch, 87 without; two: 8 + 13 against 14), nor for real blocks of 64 (12000 rows,
-// dy larger than the caches: 69 + 107 against 232).
+// The stage that gathers eight blocks side by side (multiples of eight) reads dy and lays it out once per M tile: not
+// for complex blocks with four M tiles (2048 rows: 28 + 40 us with the launch, 87 without; two: 8 + 13 against 14),
+// nor for real blocks of 64 (12000 rows, dy larger than the caches: 69 + 107 against 232).
 template <int M, bool REAL = false>
 constexpr bool kRelay = REAL ? M == 32 : M >= 56;
-// The stage that gathers one block does it where the launch would cost more than it saves: up to 3 MB, and up to seven blocks, which
-// leave ctile_kernel's lanes little to do.  Whole backward with the launch and without: 7 real blocks of 32, 200 rows 26.5 and 24.2 us, 12000
-// rows 68.6 and 63.5; 20 blocks, 2000 rows 45.2 and 46.5, 12000 rows 96.6 and 112; 1 block of 64, 30000 rows 124 and 98; 33 blocks, 500
-// rows 48.1 and 48.0, 2000 rows 79.7 and 93.0; 12 complex blocks of 32, 1000 rows 38.6 and 35.9, 8000 rows 85.8 and 87.6.
+// The stage that gathers one block does it where the launch would cost more than it saves: up to 3 MB, and up to
+// seven blocks, which leave ctile_kernel's lanes little to do.  Whole backward with the launch and without: 7 real
+// blocks of 32, 200 rows 26.5 and 24.2 us, 12000 rows 68.6 and 63.5; 20 blocks, 2000 rows 45.2 and 46.5, 12000 rows
+// 96.6 and 112; 1 block of 64, 30000 rows 124 and 98; 33 blocks, 500 rows 48.1 and 48.0, 2000 rows 79.7 and 93.0; 12
+// complex blocks of 32, 1000 rows 38.6 and 35.9, 8000 rows 85.8 and 87.6.
 bool lays_out(const Problem& pb, size_t value)
 {
     return pb.k < 8 || (size_t)pb.B * pb.n_out() * value <= (3u << 20);

@@ -1,9 +1,9 @@
-// Host path of the Python binding: argument checks, output and scratch allocation, the stream, the call into the C ABI, and
-// the autograd node, in one native module (_native.so).  No arithmetic and no kernels here.
+// Host path of the Python binding: argument checks, output and scratch allocation, the stream, the call into the C
+// ABI, and the autograd node, in one native module (_native.so).  No arithmetic and no kernels here.
 //
-// Why native: a training step of one layer enqueues six kernels of 3 to 30 us; with the marshalling in Python (ctypes, a
-// torch.autograd.Function, a dozen torch calls) the host needed 200 us for it, more than the GPU for every batch up to
-// about 32768 rows of 768 features.
+// Why native: a training step of one layer enqueues six kernels of 3 to 30 us; with the marshalling in Python
+// (ctypes, a torch.autograd.Function, a dozen torch calls) the host needed 200 us for it, more than the GPU for every
+// batch up to about 32768 rows of 768 features.
 #include <Python.h>
 
 #include <ATen/ATen.h>
@@ -134,8 +134,8 @@ Tensor out(Tensor t, const char* name, at::IntArrayRef shape, at::ScalarType dty
     return t;
 }
 
-// Where a call runs: its device made current, the raw stream.  Scratch the call allocates itself belongs to that stream (the
-// caching allocator hands its block, once released, only to later work of that same stream).
+// Where a call runs: its device made current, the raw stream.  Scratch the call allocates itself belongs to that
+// stream (the caching allocator hands its block, once released, only to later work of that same stream).
 struct Where {
     at::AutoDispatchBelowADInplaceOrView below;
     c10::DeviceGuard guard;
@@ -155,7 +155,8 @@ struct Where {
         c10::StreamGuard on(*st.torch);
         return make({(int64_t)bytes}, at::kByte, guard.current_device());
     }
-    // the same memory without a tensor around it, for the calls whose host time counts (8 rows of a packed forward: 1 us less)
+    // the same memory without a tensor around it, for the calls whose host time counts (8 rows of a packed forward: 1
+    // us less)
     c10::DataPtr block(size_t bytes) const
     {
         if (!bytes) return {};
@@ -223,7 +224,8 @@ Layer fwd_layer(const char* name, const Tensor& x, const Tensor& R, const Tensor
     if (want_pre || y_pre.defined()) y_pre = out(y_pre, "y_pre", {sh.B, sh.n_out()}, sh.dtype, sh.device);
     if (!ws.defined()) {
         if (flags & MONARCH_FLAG_WS_PACKED) {
-            // An empty batch asks whether the shape cannot do without a workspace; elsewhere the flag has nothing to refer to.
+            // An empty batch asks whether the shape cannot do without a workspace; elsewhere the flag has nothing to
+            // refer to.
             const int rc = monarch_fwd_ws(ptr(x), ptr(R), ptr(L), ptr(y), 0, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(),
                                           w.stream(), nullptr, 0, flags);
             TORCH_CHECK_VALUE(rc != MONARCH_ERR_WORKSPACE, "MONARCH_FLAG_WS_PACKED needs the workspace of the earlier call");
@@ -234,8 +236,8 @@ Layer fwd_layer(const char* name, const Tensor& x, const Tensor& R, const Tensor
         if (need) ws = w.scratch(need);
     }
     const Bytes b(ws);
-    // a workspace of packed weights is only read (other streams may be using it): the vector between the factors of a short batch
-    // goes to memory of this call
+    // a workspace of packed weights is only read (other streams may be using it): the vector between the factors of a
+    // short batch goes to memory of this call
     const size_t mid = flags & MONARCH_FLAG_WS_PACKED ? monarch_fwd_packed_scratch_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q,
                                                                                         (int)sh.s, sh.code(), flags)
                                                       : 0;
@@ -284,8 +286,8 @@ Saved fwd_save(const Tensor& x, const Tensor& R, const Tensor& L, const Tensor& 
     y = out(y, "y", {sh.B, sh.n_out()}, sh.dtype, sh.device);
     const size_t need = monarch_saved_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
     if (flags & MONARCH_FLAG_WS_PACKED) raise_status(MONARCH_ERR_INVALID, "monarch_fwd_save");
-    // nothing to save for this shape: the forward that has a workspace (fp32, k = 64 blocks of 64, 12000 rows: 6050 us without
-    // one, which is the SIMT kernels there, 290 with)
+    // nothing to save for this shape: the forward that has a workspace (fp32, k = 64 blocks of 64, 12000 rows: 6050
+    // us without one, which is the SIMT kernels there, 290 with)
     if (!need) return Saved{fwd_layer("monarch_fwd_save", x, R, L, bias, Act::none, {}, false, y, {}, flags, st).y, Tensor()};
     if (!saved.defined()) saved = make({(int64_t)need}, at::kByte, sh.device);
     const Bytes b(saved);
@@ -295,7 +297,8 @@ Saved fwd_save(const Tensor& x, const Tensor& R, const Tensor& L, const Tensor& 
     return Saved{y, saved};
 }
 
-// Every backward: `x_pre` (the layer's input is gelu(x_pre)) and `saved` (the vector between the factors) may be missing.
+// Every backward: `x_pre` (the layer's input is gelu(x_pre)) and `saved` (the vector between the factors) may be
+// missing.
 struct Grads {
     Tensor dx, dR, dL, dbias;
 };
@@ -414,25 +417,28 @@ Grads c64_bwd(bool with_ws, const Tensor& dy, const Tensor& x, const Tensor& R, 
 
 // ---- autograd ----
 
-// y = x M^T (+ bias).  The forward can keep the vector between the factors for the backward (save_intermediate), else the
-// backward recomputes it.
+// y = x M^T (+ bias).  The forward can keep the vector between the factors for the backward (save_intermediate), else
+// the backward recomputes it.
 struct LinearFn : torch::autograd::Function<LinearFn> {
-    // Where keeping the vector pays, by the GPU time of a training step with bias, recomputed and kept: fp32 and odd blocks always
-    // (192 x 192, four blocks, fp32, 12608 rows: one contraction of 53 us of 400 less).  The bf16 layers of four blocks that are
-    // multiples of 64 have other forwards for the call that keeps nothing.  Those of short batches (256 x 1024: 300 rows 47 and 54
-    // us, 1000 rows 58 and 59) lose their lead between 1500 and 3500 rows (256 x 1024: 2000 rows 76 and 73; 192 x 768: 2000 rows 60 and
-    // 62, 2500 rows 66 and 63; 192 x 192: 2500 rows 50 and 52, 3500 rows 57 and 55; 1024 x 256: 1500 rows 87 and 92, 2500 rows 103
-    // and 95).  Over long batches the packed forward wins for wide outputs, by most in the widest layer (256 x 1024: 4500 rows 107 and 103,
-    // 8192 rows 131 and 136, 12000 rows 169 and 179); 192 x 768 crosses at 5000 rows (8192 rows 95 and 97, 12000 rows 121 and 129),
-    // 256 x 768 at 8192 (12000 rows 143 and 150), 192 x 576 and 128 x 512 not up to 12000 (108 and 108; 82 and 80): the line between
-    // them costs up to 4 % on either side.  Outputs no wider than the input gain at every length (768 x 192, 16384 rows: 166 and 142).
+    // Where keeping the vector pays, by the GPU time of a training step with bias, recomputed and kept: fp32 and odd
+    // blocks always (192 x 192, four blocks, fp32, 12608 rows: one contraction of 53 us of 400 less).  The bf16
+    // layers of four blocks that are multiples of 64 have other forwards for the call that keeps nothing.  Those of
+    // short batches (256 x 1024: 300 rows 47 and 54 us, 1000 rows 58 and 59) lose their lead between 1500 and 3500
+    // rows (256 x 1024: 2000 rows 76 and 73; 192 x 768: 2000 rows 60 and 62, 2500 rows 66 and 63; 192 x 192: 2500
+    // rows 50 and 52, 3500 rows 57 and 55; 1024 x 256: 1500 rows 87 and 92, 2500 rows 103 and 95).  Over long batches
+    // the packed forward wins for wide outputs, by most in the widest layer (256 x 1024: 4500 rows 107 and 103, 8192
+    // rows 131 and 136, 12000 rows 169 and 179); 192 x 768 crosses at 5000 rows (8192 rows 95 and 97, 12000 rows 121
+    // and 129), 256 x 768 at 8192 (12000 rows 143 and 150), 192 x 576 and 128 x 512 not up to 12000 (108 and 108; 82
+    // and 80): the line between them costs up to 4 % on either side.  Outputs no wider than the input gain at every
+    // length (768 x 192, 16384 rows: 166 and 142).
     static bool keeps(const Tensor& x, const Tensor& R, const Tensor& L)
     {
         const int64_t rows = x.size(0), p = R.size(2), q = R.size(1), s = L.size(1);
         if (x.scalar_type() != at::kBFloat16 || R.size(0) != 4 || p % 64 || q % 64 || s % 64) return true;
         return rows > 2048 && (s <= p || rows <= 8192);
     }
-    // (rows, width) from any leading dimensions; their product must be the number of rows, else the last one is not `width`
+    // (rows, width) from any leading dimensions; their product must be the number of rows, else the last one is not
+    // `width`
     static Tensor rows_of(const Tensor& t, int64_t width)
     {
         if (t.dim() == 2 && t.size(1) == width && t.is_contiguous()) return t;

@@ -1008,7 +1008,7 @@ def test_dft_factors_make_the_monarch_matrix_a_fourier_transform(B, m):
 
 # ------------------------------------------------------ projection (Algorithm 1) ----
 # Only the products L[j][l][k] * R[k][j][i] are determined (sign and scaling of a singular pair are
-# free), so the Monarch matrix is compared, not the factors.  fp32 Jacobi against the fp64 SVD: the
+# free), so the Monarch matrix is compared, not the factors.  fp32 squarings against the fp64 SVD: the
 # leading singular pair of a slice is conditioned by its relative gap (about 1e-2 for 64 x 64 Gaussian
 # slices), hence 1e-4; the objective itself is insensitive to that and is held to 1e-5.
 PROJ_TOL = {"f32": 1e-4, "bf16": 2e-2}
