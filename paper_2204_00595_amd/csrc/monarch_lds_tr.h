@@ -17,6 +17,9 @@ __device__ __forceinline__ constexpr int run_key(int row)
 }
 // The LDS accesses of the pipeline are written out, and the wave waits for them by itself (lgkm_wait): the compiler
 // puts a wait for everything that is on its way into LDS (buffer_load ... lds) before a transposing read it knows of.
+// It takes the registers of such a read as written at once, so what it makes must not touch them, nor pass a branch,
+// before the wait: every read is handed to lgkm_wait within its basic block, none is left unused, and a test
+// (test_lds_reads_in_flight.py) reads the assembly of the sources that include this file.
 // Transposing read: within each 16 lanes, lane i receives element (i % 4) of lanes i/4, 4 + i/4, 8 + i/4, 12 + i/4.
 template <int OFF>
 __device__ __forceinline__ u32x2 lds_tr16(uint32_t at)
