@@ -282,21 +282,21 @@ Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 
 }  // namespace
 
-// Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows, 2048 where
-// the output is no wider than the input and 1536 where it is narrower (dx is then the larger product and each
-// workgroup has a share of the rows of dU again), and no more than 2^19 / q, where `adjoint` runs out of workgroups
-// of one column tile.  Whole backward with bias on these kernels and on the wide one: blocks of 256 and 1024, 300
-// rows 36 and 63 us, 2000 rows 54 and 68, 2500 rows 73 and 69; of 192 and 768, 2500 rows 48 and 55, 3000 rows 64 and
-// 55; of 192, 2000 rows 37 and 39, 3000 rows 52 and 40; of 256, 2000 rows 42 and 46, 2500 rows 55 and 46; of 1024 and
-// 256, 1500 rows 65 and 70, 2000 rows 77 and 71; of 768 and 192, 1200 rows 46 and 54, 1536 rows 56 and 55.  Not for
-// blocks of 64 alone (8 rows 19 and 18, 1000 rows 22 and 21).  Where the other choice is the shape-generic bf16
-// kernel (width 384) up to 4096.  Not where it is the shape-generic contractions (q = 256 with p or s = 1024), which
-// hold the vectors between the factors in fp32.
+// Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows, 2048 where the
+// output is narrower than the input (dx is then the larger product, and every workgroup reads the rows of dU again), and
+// no more than 2^19 / q, where `adjoint` runs out of workgroups of one column tile.  Whole backward with bias on these
+// kernels and on the wide one, in brackets with the nonlinearity's factor: blocks of 256 and 1024, 300 rows 36 and 63 us,
+// 2000 rows 54 and 68 (55 and 74), 2300 rows 72 and 69; of 192 and 768, 2500 rows 48 and 55, 3000 rows 64 and 55; of 192,
+// 2500 rows 39 and 40 (40 and 44), 3000 rows 52 and 40; of 256, 2000 rows 42 and 46, 2300 rows 55 and 46; of 1024 and 256,
+// 1500 rows 66 and 70 (69 and 94), 2000 rows 77 and 71 (81 and 95), 2300 rows 93 and 72 (98 and 97); of 768 and 192, 1500
+// rows 56 and 54 (60 and 71), 2300 rows 66 and 55 (71 and 72).  Not for blocks of 64 alone (8 rows 19 and 18, 1000 rows 22
+// and 21).  Where the other choice is the shape-generic bf16 kernel (width 384) up to 4096.  Not where it is the
+// shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors between the factors in fp32.
 bool bwd_split_preferred(const Problem& pb)
 {
     const bool wide = bwd_wide_supported(pb);
     if (!wide && !tiled_bwd_supported(pb)) return false;
-    if (wide && (pb.B * pb.q > (1 << 19) || pb.B > (pb.s > pb.p ? 2560 : pb.s == pb.p ? 2048 : 1536) || (pb.p == 64 && pb.s == 64))) return false;
+    if (wide && (pb.B * pb.q > (1 << 19) || pb.B > (pb.s < pb.p ? 2048 : 2560) || (pb.p == 64 && pb.s == 64))) return false;
     return pb.dtype == 1 && pb.k == 4 && !pb.perm_b() && pb.p % 32 == 0 && pb.q % 32 == 0 && pb.s % 32 == 0 && pb.p <= 1024 &&
            pb.s <= 1024 && pb.q <= 256 && pb.B > 0 && pb.B <= 4096 && make_plan(pb).ok;
 }

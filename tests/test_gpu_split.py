@@ -195,9 +195,9 @@ def test_tiles_stay_inside_the_workspace(case):
     assert bool((ws[need:] == 0xA5).all())
 
 
-# The backward on either side of its row limits: short-batch kernels up to them (2048, 1536, 2560 rows; none for blocks of 64), and the
+# The backward on either side of its row limits: short-batch kernels up to them (2048, 2560 rows; none for blocks of 64), and the
 # recomputed vector from a product of its own beyond 8192 rows.
-LINES = [(256, 256, 1024, 2048), (192, 192, 192, 2048), (128, 128, 512, 2560), (512, 128, 128, 1536), (1024, 256, 256, 1536), (64, 64, 64, 40),
+LINES = [(256, 256, 1024, 2048), (192, 192, 192, 2560), (128, 128, 512, 2560), (512, 128, 128, 2048), (1024, 256, 256, 2048), (64, 64, 64, 40),
          (1024, 256, 256, 8192), (768, 192, 192, 8192)]
 
 
