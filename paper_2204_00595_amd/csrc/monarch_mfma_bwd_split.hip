@@ -283,15 +283,16 @@ Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 }  // namespace
 
 // Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows, 2048 where the
-// output is narrower than the input (dx is then the larger product, and every workgroup reads the rows of dU again), and
-// no more than 2^19 / q, where `adjoint` runs out of workgroups of one column tile.  Whole backward with bias on these
-// kernels and on the wide one, in brackets with the nonlinearity's factor: blocks of 256 and 1024, 300 rows 36 and 63 us,
-// 2000 rows 54 and 68 (55 and 74), 2300 rows 72 and 69; of 192 and 768, 2500 rows 48 and 55, 3000 rows 64 and 55; of 192,
-// 2500 rows 39 and 40 (40 and 44), 3000 rows 52 and 40; of 256, 2000 rows 42 and 46, 2300 rows 55 and 46; of 1024 and 256,
-// 1500 rows 66 and 70 (69 and 94), 2000 rows 77 and 71 (81 and 95), 2300 rows 93 and 72 (98 and 97); of 768 and 192, 1500
-// rows 56 and 54 (60 and 71), 2300 rows 66 and 55 (71 and 72).  Not for blocks of 64 alone (8 rows 19 and 18, 1000 rows 22
-// and 21).  Where the other choice is the shape-generic bf16 kernel (width 384) up to 4096.  Not where it is the
-// shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors between the factors in fp32.
+// output is narrower than the input (dx is then the larger product, and every workgroup reads the rows of dU again),
+// and no more than 2^19 / q, where `adjoint` runs out of workgroups of one column tile.  Whole backward with bias on
+// these kernels and on the wide one, in brackets with the nonlinearity's factor: blocks of 256 and 1024, 300 rows 36
+// and 63 us, 2000 rows 54 and 68 (55 and 74), 2300 rows 72 and 69; of 192 and 768, 2500 rows 48 and 55, 3000 rows 64
+// and 55; of 192, 2500 rows 39 and 40 (40 and 44), 3000 rows 52 and 40; of 256, 2000 rows 42 and 46, 2300 rows 55 and
+// 46; of 1024 and 256, 1500 rows 66 and 70 (69 and 94), 2000 rows 77 and 71 (81 and 95), 2300 rows 93 and 72 (98 and
+// 97); of 768 and 192, 1500 rows 56 and 54 (60 and 71), 2300 rows 66 and 55 (71 and 72).  Not for blocks of 64 alone
+// (8 rows 19 and 18, 1000 rows 22 and 21).  Where the other choice is the shape-generic bf16 kernel (width 384) up to
+// 4096.  Not where it is the shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors between
+// the factors in fp32.
 bool bwd_split_preferred(const Problem& pb)
 {
     const bool wide = bwd_wide_supported(pb);
