@@ -86,6 +86,15 @@ bool fwd_uses_ops(const Problem& pb)
 {
     return !(pb.flags & MONARCH_FLAG_GENERIC) && !mfma_fwd_ws_supported(pb) && !mfma_fwd_supported(pb) && ops_supported(pb);
 }
+// What a kept vector between the factors takes up, 0 where none is kept (monarch_saved_bytes: and what the forward that
+// keeps it lays out beside it).
+size_t saved_least(const Problem& pb)
+{
+    if (pb.flags & MONARCH_FLAG_GENERIC) return 0;
+    if (saved_supported(pb)) return align_up((size_t)(pb.B > 0 ? pb.B : 1) * pb.kq() * pb.esize(), 256);
+    return fwd_uses_ops(pb) && pick_bwd(pb) == FAM_OPS ? ops_fwd_least(pb) : 0;
+}
+
 bool room_for(const void* workspace, size_t bytes, size_t need)
 {
     return workspace && bytes >= need && (uintptr_t)workspace % 256 == 0;
@@ -166,6 +175,7 @@ int fwd_static_slices(Problem pb, const void* x, const void* R, const void* L, v
     if (int rc = static_workspace(&U)) return rc;
     const int64_t batch = pb.B, fit = (int64_t)(kStaticWorkspaceBytes / (pb.kq() * sizeof(float)));  // two rows at least (ops_supported)
     const int64_t rows = fit >= 256 ? fit / 256 * 256 : fit;
+    pb.ws_bytes = kStaticWorkspaceBytes;
     for (int64_t b = 0; b < batch; b += rows) {
         pb.B = batch - b < rows ? batch - b : rows;
         const int rc = ops_fwd(pb, (const char*)x + (size_t)b * pb.n_in * pb.esize(), R, L, (char*)y + (size_t)b * pb.n_out() * pb.esize(), U, st);
@@ -205,8 +215,9 @@ int fwd_layer(const void* x, const void* R, const void* L, const void* bias, boo
         pb.mid = mid;
         rc = mfma_fwd_ws(pb, x, R, L, y, workspace, st);
         bias_done = bias_done || mfma_fwd_fuses_bias(pb, true);
-    } else if (fwd_uses_ops(pb) && (batch == 0 || room_for(workspace, workspace_bytes, ops_fwd_workspace(pb)))) {
+    } else if (fwd_uses_ops(pb) && (batch == 0 || room_for(workspace, workspace_bytes, ops_fwd_least(pb)))) {
         if (batch == 0) return MONARCH_OK;
+        pb.ws_bytes = workspace_bytes;
         rc = ops_fwd(pb, x, R, L, y, workspace, st);
         bias_done = true;
     } else {
@@ -248,7 +259,7 @@ int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* save
     Family fam = pick_bwd(pb);
     if (fam == FAM_NONE) return MONARCH_ERR_UNSUPPORTED;
     if (saved) {  // ignored by the kernel families that recompute
-        const size_t sneed = monarch_saved_bytes(batch, n_in, k, q, s, dtype, flags);
+        const size_t sneed = saved_least(pb);
         if (sneed > 0) {
             if (saved_bytes < sneed || !aligned(saved, 16)) return MONARCH_ERR_WORKSPACE;
             pb.saved = const_cast<void*>(saved);
@@ -326,17 +337,17 @@ int monarch_fwd_ws(const void* x, const void* R, const void* L, void* y, int64_t
     Problem pb;
     int rc = make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags);
     if (rc) return rc;
-    const bool ops = fwd_uses_ops(pb) && room_for(workspace, workspace_bytes, ops_fwd_workspace(pb));
+    const bool ops = fwd_uses_ops(pb) && room_for(workspace, workspace_bytes, ops_fwd_least(pb));
     if (!fwd_uses_ws(pb, workspace, workspace_bytes) && !ops)
         return monarch_fwd_ex(x, R, L, y, batch, n_in, k, q, s, dtype, stream, flags & ~MONARCH_FLAG_WS_PACKED);
     if (flags & MONARCH_FLAG_WGRAD_F32) return MONARCH_ERR_INVALID;  // backward-only flag
     if (!R || !L || ((!x || !y) && batch > 0)) return MONARCH_ERR_INVALID;
     if (!aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(y, 16)) return MONARCH_ERR_INVALID;
+    pb.ws_bytes = workspace_bytes;
     if (ops) return batch == 0 ? MONARCH_OK : ops_fwd(pb, x, R, L, y, workspace, (hipStream_t)stream);
     if (!workspace || workspace_bytes < mfma_fwd_ws_least(pb) || !aligned(workspace, 256))
         return MONARCH_ERR_WORKSPACE;
     if (batch == 0) return MONARCH_OK;
-    pb.ws_bytes = workspace_bytes;
     return mfma_fwd_ws(pb, x, R, L, y, workspace, (hipStream_t)stream);
 }
 
@@ -398,9 +409,8 @@ size_t monarch_saved_bytes(int64_t batch, int n_in, int k, int q, int s, monarch
 {
     Problem pb;
     if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags)) return 0;
-    if (flags & MONARCH_FLAG_GENERIC) return 0;
-    if (saved_supported(pb)) return align_up((size_t)(batch > 0 ? batch : 1) * pb.kq() * pb.esize(), 256);
-    return fwd_uses_ops(pb) && pick_bwd(pb) == FAM_OPS ? ops_fwd_workspace(pb) : 0;
+    const size_t least = saved_least(pb);
+    return least && !saved_supported(pb) ? ops_fwd_workspace(pb) : least;
 }
 
 int monarch_fwd_save(const void* x, const void* R, const void* L, void* y, void* saved, size_t saved_bytes,
@@ -422,9 +432,10 @@ int monarch_fwd_bias_save(const void* x, const void* R, const void* L, const voi
     if (!aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(y, 16)) return MONARCH_ERR_INVALID;
     if (!aligned(bias, 16)) return MONARCH_ERR_INVALID;
     if (need == 0) return MONARCH_ERR_UNSUPPORTED;
-    if (!saved || saved_bytes < need || !aligned(saved, 16)) return MONARCH_ERR_WORKSPACE;
+    if (!saved || saved_bytes < saved_least(pb) || !aligned(saved, 16)) return MONARCH_ERR_WORKSPACE;
     if (batch == 0) return MONARCH_OK;
     pb.bias = bias;
+    pb.ws_bytes = saved_bytes;
     if (fwd_uses_ops(pb)) return ops_fwd(pb, x, R, L, y, saved, (hipStream_t)stream);
     pb.saved = saved;
     return mfma_fwd(pb, x, R, L, y, (hipStream_t)stream);
@@ -498,7 +509,8 @@ int monarch_fwd_t(const void* x, const void* R, const void* L, void* y, int64_t 
         if (batch == 0) return MONARCH_OK;
         return mfma_fwd_t(pb, x, R, L, y, workspace, st);
     }
-    if (batch > 0 && ops_supported(pb) && room_for(workspace, workspace_bytes, ops_fwd_t_workspace(pb)))
+    pb.ws_bytes = workspace_bytes;
+    if (batch > 0 && ops_supported(pb) && room_for(workspace, workspace_bytes, ops_fwd_t_least(pb)))
         return ops_fwd_t(pb, x, R, L, y, workspace, st);
     if (!generic_fwd_t_supported(pb)) return MONARCH_ERR_UNSUPPORTED;
     if (batch == 0) return MONARCH_OK;

@@ -53,11 +53,14 @@ int generic_bwd(const Problem& pb, const void* dy, const void* x, const void* R,
                 void* dx, void* dR, void* dL, void* ws, hipStream_t st);
 
 // ---- shape-generic multiply on the matrix cores, one launch per contraction (monarch_ops.hip): blocks of 16 and more, both
-// dtypes and readings; `U` / the workspaces hold the vector between the factors ----
+// dtypes and readings; `U` / the workspaces (pb.ws_bytes) hold the vector between the factors, and the weights as planes where there
+// is room beyond the `least` ----
 bool ops_supported(const Problem& pb);
 size_t ops_fwd_workspace(const Problem& pb);
+size_t ops_fwd_least(const Problem& pb);
 int ops_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* U, hipStream_t st);
 size_t ops_fwd_t_workspace(const Problem& pb);
+size_t ops_fwd_t_least(const Problem& pb);
 int ops_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 size_t ops_bwd_workspace(const Problem& pb);
 size_t ops_bwd_least(const Problem& pb);  // what the call cannot do without; with less than the above it takes fewer batch chunks

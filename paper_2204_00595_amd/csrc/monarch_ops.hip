@@ -37,6 +37,7 @@
 // 12608 rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix cores, now 256 (one contraction of 3.7 GFLOP takes
 // 35 to 40 us, 50 where an operand is strided, the two weight gradients 74); 196 -> 256 bf16, blocks of 49 and 64,
 // 32768 rows: 458, 121, now 96 us; 2048 -> 512 fp32, 3000 rows: 137, now 112.
+#include <algorithm>
 #include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
@@ -71,6 +72,7 @@ struct OpDesc {
     void* o;           // output, or the partial tiles [split][g][m][n] (fp32)
     int64_t o_g, o_m, o_n;  // element (g, m, n) goes to g*o_g + m*o_m + n*o_n ...
     int o_mid;         // ... or, 1: to the stage-1 position of element g*N + n of the permuted vector (default reading)
+    int o_turn;        // long batches: how a result's neighbours in memory are found (RowsStore)
     const void* bias;  // added to o at the offset g*o_g + n*o_n (may be null)
     int64_t M, K;
     int N, G;
@@ -111,17 +113,17 @@ struct TileDrop {
 // Elements past the limits read as zeros.  Single elements are loaded with consecutive lanes on consecutive c (at a
 // stride of 16 bytes a load takes the L1 31 cycles, at 32 bytes 60), and neighbouring lanes exchange them so that each
 // has two for a dword.
-template <typename T, int C, int O, int LSTR, Take TAKE, int SZ>
+template <typename T, int C, int O, int LSTR, Take TAKE, int SZ, int THREADS = kThreads>
 struct OpTile {
     static constexpr bool VEC = TAKE != kElements, kSplit = sizeof(T) == 4;
     static constexpr int V = VEC ? 16 / (int)sizeof(T) : 1;          // elements per piece
     static constexpr int PPO = C / V;                                // pieces per o
     static constexpr int kPieces = PPO * O;
-    static constexpr int NP = (kPieces + kThreads - 1) / kThreads;   // per thread
+    static constexpr int NP = (kPieces + THREADS - 1) / THREADS;   // per thread
     static constexpr int kDwords = VEC ? 4 : 1;
     static_assert(C % V == 0 && LSTR * 2 % 16 == 0, "tile");
-    static constexpr bool kEven = kThreads % PPO == 0;  // a thread's pieces share c and step in o by a uniform amount
-    static_assert(VEC || (kEven && kPieces % kThreads == 0 && NP % 2 == 0), "element-wise tiles divide over the threads");
+    static constexpr bool kEven = THREADS % PPO == 0;  // a thread's pieces share c and step in o by a uniform amount
+    static_assert(VEC || (kEven && kPieces % THREADS == 0 && NP % 2 == 0), "element-wise tiles divide over the threads");
     uint32_t r[NP * kDwords];
     int over[TAKE == kPiecesAny ? (kEven ? 1 : NP) : 1];  // elements of a piece past the limit
 
@@ -134,12 +136,12 @@ struct OpTile {
         const uint32_t v0 = (o0 * os + c0 * cs) * (uint32_t)sizeof(T) + kBack;
 #pragma unroll
         for (int n = 0; n < NP; ++n) {
-            const int idx = tid + n * kThreads;
-            const int o = kEven ? o0 + n * (kThreads / PPO) : idx / PPO, c = kEven ? c0 : (idx % PPO) * V;
+            const int idx = tid + n * THREADS;
+            const int o = kEven ? o0 + n * (THREADS / PPO) : idx / PPO, c = kEven ? c0 : (idx % PPO) * V;
             uint32_t vo = kEven ? v0 : (o * os + c * cs) * (uint32_t)sizeof(T) + kBack;
-            const uint32_t so = kEven ? n * (kThreads / PPO) * os * (uint32_t)sizeof(T) : 0u;
+            const uint32_t so = kEven ? n * (THREADS / PPO) * os * (uint32_t)sizeof(T) : 0u;
             bool in = o < olim && c < clim;
-            if constexpr (kPieces % kThreads != 0) in = in && idx < kPieces;
+            if constexpr (kPieces % THREADS != 0) in = in && idx < kPieces;
             if constexpr (TAKE == kPiecesAny) {
                 const int past = c + V > clim ? c + V - clim : 0;
                 over[kEven ? 0 : n] = past;
@@ -162,10 +164,10 @@ struct OpTile {
         if constexpr (VEC) {
 #pragma unroll
             for (int n = 0; n < NP; ++n) {
-                const int idx = tid + n * kThreads, o = idx / PPO, c = (idx % PPO) * V;
+                const int idx = tid + n * THREADS, o = idx / PPO, c = (idx % PPO) * V;
                 u32x4 v = {r[4 * n], r[4 * n + 1], r[4 * n + 2], r[4 * n + 3]};
                 if constexpr (TAKE == kPiecesAny) v = TileDrop<T>::drop(v, over[kEven ? 0 : n]);
-                if (kPieces % kThreads == 0 || idx < kPieces) {
+                if (kPieces % THREADS == 0 || idx < kPieces) {
                     if constexpr (kSplit) {
                         uint32_t lo[3], hi[3];
                         split3(v[0], v[1], lo);
@@ -180,13 +182,13 @@ struct OpTile {
         } else {
             // of the elements n and n + 1 an even lane takes n of both lanes, an odd lane n + 1
             const bool odd = tid & 1;
-            bf16_t* const to = lds + (tid / PPO + (odd ? kThreads / PPO : 0)) * LSTR + (tid % PPO & ~1);
+            bf16_t* const to = lds + (tid / PPO + (odd ? THREADS / PPO : 0)) * LSTR + (tid % PPO & ~1);
 #pragma unroll
             for (int n = 0; n < NP; n += 2) {
                 const uint32_t mine = odd ? r[n + 1] : r[n], give = odd ? r[n] : r[n + 1];
                 const uint32_t got = (uint32_t)__builtin_amdgcn_mov_dpp((int)give, 0xB1, 0xf, 0xf, true);  // lane ^ 1
                 const uint32_t a = odd ? got : mine, b = odd ? mine : got;
-                bf16_t* const p = to + n * (kThreads / PPO) * LSTR;
+                bf16_t* const p = to + n * (THREADS / PPO) * LSTR;
                 if constexpr (kSplit) {
                     uint32_t v[3];
                     split3(a, b, v);
@@ -523,9 +525,343 @@ ops_gemm_pair_kernel(const OpDesc d0, const OpDesc d1)
     }
 }
 
+// ---- long batches: the weights as planes, laid out once per call ----
+//
+// A workgroup has 64 rows of four neighbouring blocks, two waves a block, each with half of the columns of its tile (64
+// NT).  The rows are split on their way into LDS, once for all columns of the tile, and interleaved blocks are read and
+// written in whole lines; the weights come as planes in fragment order (ops_planes_kernel) straight into registers, a
+// K-step ahead, so that nothing but the rows is split in the loop and nothing but the rows passes through LDS.  The sums
+// are those of OpGemm, in the same order: a call that takes this kernel gives the same bits.
+// 768 -> 768 fp32, 12608 rows, per contraction: 42 to 50 us in 64 x 64 tiles, 33 here (37 with interleaved rows).  Of
+// these the matrix cores alone take 16 (six products, 197 of 256 CUs, the clock that ordinary numbers leave them), storing
+// the results, which nothing overlaps with one workgroup to a CU, 9, the first rows and the launch 5.
+struct PlaneJob {
+    const void* src;
+    bf16_t* dst;    // [g][tile of 32 rows n][K-step][plane][lane][8]
+    int N, K, n_s, k_s;  // element (g, n, k) at g*N*K + n*n_s + k*k_s
+    int tiles_n, steps, blocks;
+};
+// CW > 0: workgroups behind those of the weights run the first pass of the bias gradient, CW columns to a lane
+template <typename T, int CW>
+__global__ void __launch_bounds__(256)
+ops_planes_kernel(const PlaneJob j0, const PlaneJob j1, const PlaneJob j2, int G, const ColsumJob cj)
+{
+    constexpr int PL = sizeof(T) == 4 ? 3 : 1;
+    const int b01 = j0.blocks + j1.blocks, b012 = b01 + j2.blocks, block = (int)blockIdx.x;
+    if constexpr (CW > 0) {
+        if (block >= b012) {
+            colsum_partial_body<T, CW>(cj, block - b012);
+            return;
+        }
+    }
+    const PlaneJob j = block < j0.blocks ? j0 : block < b01 ? j1 : j2;
+    const int bid = block < j0.blocks ? block : block < b01 ? block - j0.blocks : block - b01;
+    const int idx = bid * 256 + (int)threadIdx.x, lane = idx & 63, tile = idx >> 6;
+    const int ks = tile % j.steps, nt = tile / j.steps % j.tiles_n, g = tile / j.steps / j.tiles_n;
+    if (g >= G) return;
+    const int n = nt * 32 + (lane & 31), k0 = ks * kStep + 8 * (lane >> 5);
+    const T* const p = static_cast<const T*>(j.src) + (size_t)g * j.N * j.K + (size_t)n * j.n_s + (size_t)k0 * j.k_s;
+    T v[8];
+#pragma unroll
+    for (int e = 0; e < 8; ++e) v[e] = n < j.N && k0 + e < j.K ? p[(size_t)e * j.k_s] : T(0);
+    bf16_t* const to = j.dst + ((size_t)tile * PL * 64 + lane) * 8;
+    u32x4 o[PL];
+#pragma unroll
+    for (int w = 0; w < 4; ++w) {
+        if constexpr (PL == 3) {
+            uint32_t s[3];
+            split3(__float_as_uint(v[2 * w]), __float_as_uint(v[2 * w + 1]), s);
+#pragma unroll
+            for (int u = 0; u < 3; ++u) o[u][w] = s[u];
+        } else {
+            o[0][w] = (uint32_t)v[2 * w] | (uint32_t)v[2 * w + 1] << 16;
+        }
+    }
+#pragma unroll
+    for (int u = 0; u < PL; ++u) *reinterpret_cast<u32x4*>(to + (size_t)u * 512) = o[u];
+}
+
+constexpr int kRows = 64, kRowsThreads = 512;
+// 64 rows x 32 of an operand whose blocks are interleaved (element (g, k) at k*G + g), on their way to LDS: a thread has
+// four k of a row for four neighbouring blocks, in pieces of four elements, and turns them in registers.
+template <typename T, int LSTR, int SZ>
+struct QuadTile {
+    static constexpr int kWords = sizeof(T);  // dwords of a piece
+    u32x4 r[sizeof(T)];  // fp32: a piece each; bf16: two
+    __device__ __forceinline__ void fetch(const T* base, uint32_t os, uint32_t cs, int olim, int clim, int tid)
+    {
+        const int o = tid >> 3, c = (tid & 7) * 4;
+        const auto rs = buffer_at(base);
+#pragma unroll
+        for (int n = 0; n < 4; ++n) {
+            const uint32_t at = o < olim && c + n < clim ? (o * os + (c + n) * cs) * (uint32_t)sizeof(T) : kNowhere;
+            if constexpr (sizeof(T) == 4) {
+                r[n] = __builtin_amdgcn_raw_buffer_load_b128(rs, at, 0, 0);
+            } else {
+                const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(rs, at, 0, 0);
+                r[n >> 1][2 * (n & 1)] = v[0];
+                r[n >> 1][2 * (n & 1) + 1] = v[1];
+            }
+        }
+    }
+    // lds: the first of four slots, `slot` elements apart
+    __device__ __forceinline__ void store(bf16_t* lds, int slot, int tid) const
+    {
+        bf16_t* const to = lds + (tid >> 3) * LSTR + (tid & 7) * 4;
+#pragma unroll
+        for (int g = 0; g < 4; ++g) {
+            if constexpr (sizeof(T) == 4) {
+                uint32_t lo[3], hi[3];
+                split3(r[0][g], r[1][g], lo);
+                split3(r[2][g], r[3][g], hi);
+#pragma unroll
+                for (int w = 0; w < 3; ++w) *reinterpret_cast<u32x2*>(to + g * slot + w * SZ) = u32x2{lo[w], hi[w]};
+            } else {
+                const uint32_t a = r[0][g >> 1], b = r[0][2 + (g >> 1)], c = r[1][g >> 1], e = r[1][2 + (g >> 1)];
+                *reinterpret_cast<u32x2*>(to + g * slot) = g & 1 ? u32x2{pick_hi16(a, b), pick_hi16(c, e)} : u32x2{pick_lo16(a, b), pick_lo16(c, e)};
+            }
+        }
+    }
+};
+
+// A finished workgroup's results, eight rows of its four blocks at a time, by way of LDS, so that what lies side by side
+// in memory leaves together: kTurnNone, four columns of a block; kTurnBlocks, the four blocks of a column (element (g, n)
+// at n*G + g); kTurnMid, four columns G apart of a block (the stage-1 position of the permuted vector), kTurnMidAny, one
+// of them, a lane the next.  Straight from the accumulators (kTurnDirect) single elements leave, G or more apart: 768 ->
+// 768 fp32, 12608 rows, 44 to 50 us for a contraction that takes 34 this way.
+enum Turn { kTurnDirect, kTurnNone, kTurnBlocks, kTurnMid, kTurnMidAny };
+template <typename TO, int NT>
+struct RowsStore {
+    static constexpr int NW = 64 * NT, STR = NW + 4, TILE = 8 * 4 * STR;
+    static constexpr size_t kLds = 2 * sizeof(float) * (size_t)TILE;
+    // E: elements of a piece
+    template <int E>
+    static __device__ __forceinline__ void run(const OpDesc& d, const f32x16 (&acc)[2][NT], int g0, int tn, int64_t m0, int mlim, int slot, int half,
+                                               int tid, int lane, float* lds)
+    {
+        constexpr int U = 4 * NT / E, PB = NW / E;  // pieces of a thread and of a block's eight rows / 8
+        const int col = half * (NT * 32) + (lane & 31), h = lane >> 5, G = d.G, step = d.o_turn == kTurnBlocks ? STR : d.o_turn == kTurnMid ? G : 1;
+        const auto out = buffer_at(static_cast<TO*>(d.o) + m0 * d.o_m), bias = buffer_at(d.bias);
+        int from[U], row[U];  // place in LDS; row of the eight (kRows: a piece that does not exist)
+        uint32_t to[U];
+        float add[U][E];
+#pragma unroll
+        for (int u = 0; u < U; ++u) {
+            const int idx = tid + u * kRowsThreads, r = idx / (4 * PB), rest = idx % (4 * PB);
+            int c = rest / PB, n = rest % PB * E;
+            if (d.o_turn == kTurnBlocks) {
+                c = 0;
+                n = rest;
+            } else if (d.o_turn != kTurnNone) {
+                const int w = NW / G / E, t = rest % PB;
+                n = t % w * (E * G) + t / w;
+            }
+            const int g = g0 + c, at = tn * NW + n;
+            from[u] = (r * 4 + c) * STR + n;
+            row[u] = at < d.N ? r : kRows;
+            if (d.o_turn >= kTurnMid) {
+                const uint32_t f = (uint32_t)(g * d.N + at);
+                to[u] = f % (uint32_t)G * (uint32_t)d.N + f / (uint32_t)G;
+            } else {
+                to[u] = (uint32_t)g * (uint32_t)d.o_g + (uint32_t)at * (uint32_t)d.o_n;
+            }
+#pragma unroll
+            for (int e = 0; e < E; ++e) add[u][e] = 0.f;
+            if (E == 4 && d.bias) {
+                const uint32_t b = row[u] < kRows ? to[u] * (uint32_t)sizeof(TO) : kNowhere;
+                if constexpr (sizeof(TO) == 4) {
+                    const f32x4 v = __builtin_bit_cast(f32x4, __builtin_amdgcn_raw_buffer_load_b128(bias, b, 0, 0));
+#pragma unroll
+                    for (int e = 0; e < E; ++e) add[u][e] = v[e];
+                } else {
+                    const u32x2 v = __builtin_amdgcn_raw_buffer_load_b64(bias, b, 0, 0);
+#pragma unroll
+                    for (int e = 0; e < E; ++e) add[u][e] = __uint_as_float(e & 1 ? v[e >> 1] & 0xffff0000u : v[e >> 1] << 16);
+                }
+            }
+        }
+        lds_barrier();  // the last chunk has been read
+#pragma unroll
+        for (int s = 0; s < 8; ++s) {
+            float* const tile = lds + (s & 1) * TILE;
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int e = 0; e < 4; ++e) tile[((4 * h + e) * 4 + slot) * STR + col + j * 32] = acc[s >> 2][j][4 * (s & 3) + e];
+            lds_barrier();
+#pragma unroll
+            for (int u = 0; u < U; ++u) {
+                const float* const p = tile + from[u];
+                const int m = s * 8 + row[u];
+                const uint32_t at = m < mlim ? ((uint32_t)m * (uint32_t)d.o_m + to[u]) * (uint32_t)sizeof(TO) : kNowhere;
+                if constexpr (E == 1) {
+                    static_assert(E != 1 || sizeof(TO) == 4, "between the factors");
+                    __builtin_amdgcn_raw_buffer_store_b32(__float_as_uint(p[0]), out, at, 0, 0);
+                } else {
+                    f32x4 v;
+#pragma unroll
+                    for (int e = 0; e < E; ++e) v[e] = p[e * step] + add[u][e];
+                    if constexpr (sizeof(TO) == 4) __builtin_amdgcn_raw_buffer_store_b128(__builtin_bit_cast(u32x4, v), out, at, 0, 0);
+                    else __builtin_amdgcn_raw_buffer_store_b64(u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])}, out, at, 0, 0);
+                }
+            }
+        }
+    }
+};
+
+template <typename TA, typename TB, typename TO, int NT, Take AV, bool QUAD>
+struct RowsGemm {
+    static constexpr bool kSplit = sizeof(TA) == 4 || sizeof(TB) == 4;
+    static constexpr int PA = sizeof(TA) == 2 ? 1 : 3, PB = sizeof(TB) == 2 ? 1 : 3;
+    // chunks of 16 indices where that lets a second workgroup on the CU (49 x 49 blocks bf16, 32768 rows: 17 and 15 us)
+    static constexpr int KC = PA == 3 && NT == 1 && !QUAD ? 16 : 32, LSTR = KC + 8, SZ = kRows * LSTR, SLOT = PA * SZ, BUF = 4 * SLOT;
+    static constexpr size_t kLds = std::max(2 * sizeof(bf16_t) * (size_t)BUF, RowsStore<TO, NT>::kLds);
+};
+template <typename TA, typename TB, typename TO, int NT, Take AV, bool QUAD>
+__global__ void __launch_bounds__(kRowsThreads, 2)
+ops_rows_kernel(const OpDesc d, const bf16_t* __restrict__ planes, int steps)
+{
+    using S = RowsGemm<TA, TB, TO, NT, AV, QUAD>;
+    constexpr int PA = S::PA, PB = S::PB, KC = S::KC, MT = 2, NF = NT * PB;
+    static_assert(!QUAD || KC == 32, "the tile of QuadTile");
+    using TileA = std::conditional_t<QUAD, QuadTile<TA, S::LSTR, S::SZ>, OpTile<TA, KC, kRows, S::LSTR, AV, S::SZ, 128>>;
+    extern __shared__ __align__(16) unsigned char op_lds[];
+    bf16_t* const lds = reinterpret_cast<bf16_t*>(op_lds);
+
+    const int inner = d.G / 4 * d.tiles_n, bid = (int)blockIdx.x, seq = d.deal ? bid >> 3 : bid;
+    const int tm = d.deal ? (seq / inner) * 8 + (bid & 7) : seq / inner;
+    if (tm >= d.nouter) return;
+    const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), slot = wave >> 1, half = wave & 1;
+    const int g0 = seq % inner % (d.G / 4) * 4, g = g0 + slot, tn = seq % inner / (d.G / 4);
+    const int64_t m0 = (int64_t)tm * kRows;
+    const int n0 = tn * (64 * NT), K = (int)d.K;
+    const int mlim = d.M - m0 < kRows ? (int)(d.M - m0) : kRows, nlim = d.N - n0 < 64 * NT ? d.N - n0 : 64 * NT;
+
+    // rows: the 128 threads of a slot have its block; QUAD: all threads have the four blocks of the workgroup
+    const TA* pa = static_cast<const TA*>(d.a.p) + (QUAD ? g0 : g) * d.a.g_s + m0 * d.a.r_s;
+    TileA s0, s1;
+    // requests stay where they are written: moved to their use, as the compiler would, they are waited for at once
+    auto pin = [] {
+        asm volatile("" ::: "memory");
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    auto fetch = [&](TileA& s, int kk) {
+        const int left = K - kk, klim = left < KC ? (left > 0 ? left : 0) : KC;
+        s.fetch(pa + (int64_t)kk * d.a.k_s, (uint32_t)d.a.r_s, QUAD ? (uint32_t)d.a.k_s : 1u, mlim, klim, QUAD ? tid : tid & 127);
+        pin();
+    };
+    auto put = [&](const TileA& s, int buf) {
+        if constexpr (QUAD) s.store(lds + buf * S::BUF, S::SLOT, tid);
+        else s.store(lds + buf * S::BUF + slot * S::SLOT, tid & 127);
+    };
+    // fragments of a K-step: tiles past the last column take the last one's
+    const int nt_all = (d.N + 31) / 32;
+    uint32_t w_at[NT];
+#pragma unroll
+    for (int j = 0; j < NT; ++j) {
+        const int nt = tn * 2 * NT + half * NT + j, in = nt < nt_all ? nt : nt_all - 1;
+        w_at[j] = (uint32_t)(((g * nt_all + in) * steps) * PB) * 1024u;
+    }
+    const auto rw = buffer_at(planes);
+    u32x4 w0[NF], w1[NF];
+    auto load = [&](u32x4 (&w)[NF], int ks) {
+        const uint32_t at = (uint32_t)(ks < steps ? ks : steps - 1) * (PB * 1024u);
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int u = 0; u < PB; ++u) w[j * PB + u] = __builtin_amdgcn_raw_buffer_load_b128(rw, lane * 16u, w_at[j] + at + u * 1024u, 0);
+        pin();
+    };
+
+    f32x16 acc[MT][NT];
+#pragma unroll
+    for (int i = 0; i < MT; ++i)
+#pragma unroll
+        for (int j = 0; j < NT; ++j)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[i][j][r] = 0.f;
+    auto multiply = [&](const u32x4 (&w)[NF], int buf, int t) {
+        OpFrag<false, S::LSTR, PA, S::SZ> af[MT];
+#pragma unroll
+        for (int i = 0; i < MT; ++i) af[i].read(lds + buf * S::BUF + slot * S::SLOT, i * 32, t * kStep, lane);
+        // the order of plane_products in every tile
+#pragma unroll
+        for (int v = 2; v >= 0; --v)
+#pragma unroll
+            for (int u = 0; u <= v; ++u)
+                if (u < PA && v - u < PB) {
+#pragma unroll
+                    for (int i = 0; i < MT; ++i)
+#pragma unroll
+                        for (int j = 0; j < NT; ++j)
+                            acc[i][j] = mfma32(af[i].v[u < PA ? u : 0], as_bf16x8(w[j * PB + (v - u < PB ? v - u : 0)]), acc[i][j]);
+                }
+        __builtin_amdgcn_sched_barrier(0);
+    };
+    load(w0, 0);
+    fetch(s0, 0);
+    fetch(s1, KC);
+    put(s0, 0);
+    lds_barrier();
+    // a chunk that is not the last one; fragments of the next K-step, then rows, whose wait leaves them in flight
+    auto chunk = [&](auto which, TileA& mine, const TileA& next, u32x4 (&even)[NF], u32x4 (&odd)[NF], int kk) {
+        constexpr int buf = decltype(which)::value;
+        load(odd, kk / kStep + 1);
+        fetch(mine, kk + 2 * KC);
+        multiply(even, buf, 0);
+        if constexpr (KC > kStep) {
+            load(even, kk / kStep + 2);
+            multiply(odd, buf, 1);
+        }
+        put(next, buf ^ 1);
+        lds_barrier();
+    };
+    auto& w2 = KC > kStep ? w0 : w1;  // fragments of the second chunk of two
+    auto& w3 = KC > kStep ? w1 : w0;
+    int kk = 0, buf = 0;
+    for (; kk + 2 * KC < K; kk += 2 * KC) {
+        chunk(std::integral_constant<int, 0>(), s0, s1, w0, w1, kk);
+        chunk(std::integral_constant<int, 1>(), s1, s0, w2, w3, kk + KC);
+    }
+    if (kk + KC < K) {
+        chunk(std::integral_constant<int, 0>(), s0, s1, w0, w1, kk);
+        kk += KC;
+        buf = 1;
+    }
+    if constexpr (KC > kStep) {
+        load(w1, kk / kStep + 1);
+        multiply(w0, buf, 0);
+        if (kStep < K - kk) multiply(w1, buf, 1);
+    } else if (buf) {
+        multiply(w1, 1, 0);
+    } else {
+        multiply(w0, 0, 0);
+    }
+    if constexpr (S::kSplit) {
+        const bool off = planes_overflowed(acc);
+#pragma unroll
+        for (int i = 0; i < MT; ++i)
+#pragma unroll
+            for (int j = 0; j < NT; ++j) acc[i][j] *= kPlaneUnscale<PA / 3 + PB / 3>;
+        if (off) op_redo<TA, TB>(d, g, m0, n0, mlim, nlim, 0, half, 0, K, lane, acc);
+    }
+    float* const turn = reinterpret_cast<float*>(op_lds);
+    if (d.o_turn == kTurnDirect) {
+        op_store<TO, false, MT, NT>(d, acc, tm, g, m0, n0, mlim, nlim, 0, half, lane);
+        return;
+    }
+    if constexpr (sizeof(TO) == 4) {
+        if (d.o_turn == kTurnMidAny) {
+            RowsStore<TO, NT>::template run<1>(d, acc, g0, tn, m0, mlim, slot, half, tid, lane, turn);
+            return;
+        }
+    }
+    RowsStore<TO, NT>::template run<4>(d, acc, g0, tn, m0, mlim, slot, half, tid, lane, turn);
+}
+
 // out[e] = sum over the batch chunks of P[z][e], for both gradients.  WAVES = 1: a thread per element.  WAVES > 1,
 // for many chunks: a workgroup owns 64 elements, wave w adds the chunks w, w + WAVES, ..., the sums of the waves are
-// added in order, and workgroups from `blocks01` on run the second pass of the bias gradient. Bound by latency: the
+// added in order.  Workgroups from `blocks01` on run the second pass of the bias gradient.  Bound by latency: the
 // 128 chunks of blocks of 49 x 49 and 64 x 49 took 11.7 us with a thread per element and the bias pass 6.7 us in a
 // launch of its own, together 5.3; at 16 chunks of 192 x 192 a thread per element takes 5.1 us, 16 waves 13.
 constexpr int kSumWaves = 16, kManyChunks = 32;
@@ -540,11 +876,9 @@ __global__ void __launch_bounds__(WAVES > 1 ? WAVES * 64 : 256)
 ops_sum_kernel(OpSum s0, OpSum s1, int64_t blocks0, int64_t blocks01, ColsumJob cj)
 {
     constexpr int kOwn = WAVES > 1 ? 64 : 256;  // elements of a workgroup
-    if constexpr (WAVES > 1) {
-        if ((int64_t)blockIdx.x >= blocks01) {
-            colsum_final_body<OT, WAVES * 64>(cj, (int)((int64_t)blockIdx.x - blocks01));
-            return;
-        }
+    if ((int64_t)blockIdx.x >= blocks01) {
+        colsum_final_body<OT, (WAVES > 1 ? WAVES * 64 : 256)>(cj, (int)((int64_t)blockIdx.x - blocks01));
+        return;
     }
     const bool second = (int64_t)blockIdx.x >= blocks0;
     const OpSum& s = second ? s1 : s0;
@@ -571,11 +905,10 @@ int launch_sum(const OpSum& s0, const OpSum& s1, const ColsumJob* cj, hipStream_
 {
     const bool many = s0.nz >= kManyChunks;
     const int64_t own = many ? 64 : 256, b0 = (s0.n + own - 1) / own, b01 = b0 + (s1.n + own - 1) / own;
-    if (many)
-        hipLaunchKernelGGL((ops_sum_kernel<OT, kSumWaves>), dim3((unsigned)(b01 + (cj ? colsum_final_blocks(*cj) : 0))),
-                           dim3(kSumWaves * 64), 0, st, s0, s1, b0, b01, cj ? *cj : ColsumJob{});
-    else
-        hipLaunchKernelGGL((ops_sum_kernel<OT, 1>), dim3((unsigned)b01), dim3(256), 0, st, s0, s1, b0, b01, ColsumJob{});
+    const dim3 grid((unsigned)(b01 + (cj ? colsum_final_blocks(*cj) : 0)));
+    const ColsumJob job = cj ? *cj : ColsumJob{};
+    if (many) hipLaunchKernelGGL((ops_sum_kernel<OT, kSumWaves>), grid, dim3(kSumWaves * 64), 0, st, s0, s1, b0, b01, job);
+    else hipLaunchKernelGGL((ops_sum_kernel<OT, 1>), grid, dim3(256), 0, st, s0, s1, b0, b01, job);
     return hip_status(hipGetLastError());
 }
 
@@ -712,6 +1045,94 @@ int pick_tile(int64_t M, int N, int G, bool pieces)
     return best;
 }
 
+// What a contraction reads and writes: the rows of the blocks interleaved on the way in or out, or on neither side.
+enum Sides { kPlain, kSpreadOut, kSpreadIn };
+// Columns per wave (NT tiles of 32) of the kernel with the weights laid out as planes, 0: not there.  It gains where a side
+// is interleaved, which it reads and writes in whole lines, and where splitting a row once instead of once per 64 columns
+// tells; its workgroups run one to a CU, so that it loses where the last round of them is far from full, and it pays 3 to 5
+// us for the weights.  us, contractions of 64-column tiles first: 768 -> 768 fp32 x M^T 12608 rows 80 and 67, 8192 rows
+// (half a round) 47 and 58; x M 83 and 73; 768 -> 3072 12608 rows 166 and 155, x M 182 and 140; 1024 -> 1024 fp32 x M^T
+// 16384 rows (two rounds of 128 columns) 133 and 126, 8192 rows and 1024 -> 4096 at 2048 (one round) 70 and 67, 50 and
+// 55; the plain contraction of 3072 -> 768 x M, four column tiles, 12608 rows: 146 and 163; with 96 of 128 columns: 384 ->
+// 384 16384 rows 36 and 45; 40 x 33 blocks, k = 8, bf16, 16384 rows 29 and 20, x M 35 and 25; in fp32 x M 22 and 26 at
+// 8192 rows; 49 x 49 bf16, 32768 rows 31 and 27; 20 x 20, k = 4, 16384 rows 12.2 and 13.5.
+int rows_tile(const Problem& pb, int N, Sides sides)
+{
+    if (pb.k % 4) return 0;
+    const int nt = N <= 64 ? 1 : tiles(N, 192) * 192 <= tiles(N, 128) * 128 ? 3 : 2;
+    const int64_t cols = tiles(N, 64 * nt), wgs = tiles(pb.B, kRows) * (pb.k / 4) * cols, slots = tiles(wgs, kCUs) * kCUs;
+    if (sides == kPlain && !(nt == 3 && cols == 1) && !(nt == 1 && pb.dtype == 1)) return 0;
+    if (nt == 3) return 4 * wgs >= 3 * slots ? nt : 0;
+    if (10 * wgs < 9 * slots) return 0;
+    if (nt == 1) return (N > 48 || pb.k > 4) && !(sides == kSpreadIn && pb.dtype == 0) ? nt : 0;
+    return slots > kCUs && 5 * N >= 4 * 128 * cols ? nt : 0;
+}
+// a weight (k blocks, N x K) as planes, bytes
+size_t plane_bytes(const Problem& pb, int N, int K)
+{
+    return (size_t)pb.k * (size_t)tiles(N, 32) * (size_t)tiles(K, kStep) * (pb.dtype == 0 ? 3 : 1) * 1024;
+}
+struct Planes {  // of the weights of one call, in its workspace; those the call has no use for are null
+    bf16_t* w[3] = {nullptr, nullptr, nullptr};
+    PlaneJob job[3] = {};
+    int n = 0;
+    size_t bytes = 0;
+    // the next weight, element (g, n, k) at g*N*K + n*n_s + k*k_s
+    void add(const Problem& pb, const void* src, int N, int K, int n_s, int k_s, Sides sides)
+    {
+        const size_t b = plane_bytes(pb, N, K);
+        if (rows_tile(pb, N, sides) && b < (1u << 30)) {
+            PlaneJob& j = job[n];
+            j = PlaneJob{src, reinterpret_cast<bf16_t*>(bytes), N, K, n_s, k_s, (int)tiles(N, 32), (int)tiles(K, kStep), 0};
+            j.blocks = (int)tiles((int64_t)pb.k * j.tiles_n * j.steps, 4);
+            bytes += b;
+        }
+        ++n;
+    }
+    // `at`: room for them, or null; cj (may be null): the first pass of the bias gradient with them
+    int launch(const Problem& pb, void* at, const ColsumJob* cj, hipStream_t st)
+    {
+        const int blocks = at ? job[0].blocks + job[1].blocks + job[2].blocks : 0;
+        if (!blocks) return cj ? launch_colsum_partial(pb, *cj, st) : 0;
+        for (int i = 0; i < n; ++i)
+            if (job[i].blocks) w[i] = job[i].dst = reinterpret_cast<bf16_t*>(static_cast<char*>(at) + reinterpret_cast<size_t>(job[i].dst));
+        const int cw = cj ? rowcol_cw(cj->n_out) : 0;
+        auto kernel = pb.dtype == 0 ? (cw == 4 ? ops_planes_kernel<float, 4> : cw ? ops_planes_kernel<float, 1> : ops_planes_kernel<float, 0>)
+                                    : (cw == 4 ? ops_planes_kernel<bf16_t, 4> : cw ? ops_planes_kernel<bf16_t, 1> : ops_planes_kernel<bf16_t, 0>);
+        hipLaunchKernelGGL(kernel, dim3((unsigned)(blocks + (cj ? colsum_partial_blocks(*cj) : 0))), dim3(256), 0, st, job[0], job[1], job[2], pb.k,
+                           cj ? *cj : ColsumJob{});
+        return hip_status(hipGetLastError());
+    }
+};
+
+template <typename TA, typename TB, typename TO, int NT, Take AV, bool QUAD>
+int launch_rows_one(const OpDesc& d, const bf16_t* planes, hipStream_t st)
+{
+    auto kernel = ops_rows_kernel<TA, TB, TO, NT, AV, QUAD>;
+    constexpr size_t lds = RowsGemm<TA, TB, TO, NT, AV, QUAD>::kLds;
+    if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds)) return hip_status(e);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)d.blocks), dim3(kRowsThreads), lds, st, d, planes, (int)tiles(d.K, kStep));
+    return hip_status(hipGetLastError());
+}
+template <typename TA, typename TB, typename TO, int NT>
+int launch_rows_take(const OpDesc& d, const bf16_t* planes, hipStream_t st)
+{
+    switch (d.a.take) {
+        case kElements: return launch_rows_one<TA, TB, TO, NT, kElements, true>(d, planes, st);
+        case kPiecesAny: return launch_rows_one<TA, TB, TO, NT, kPiecesAny, false>(d, planes, st);
+        default: return launch_rows_one<TA, TB, TO, NT, kPieces16, false>(d, planes, st);
+    }
+}
+template <typename TA, typename TB, typename TO>
+int launch_rows(int nt, const OpDesc& d, const bf16_t* planes, hipStream_t st)
+{
+    switch (nt) {
+        case 1: return launch_rows_take<TA, TB, TO, 1>(d, planes, st);
+        case 2: return launch_rows_take<TA, TB, TO, 2>(d, planes, st);
+        default: return launch_rows_take<TA, TB, TO, 3>(d, planes, st);
+    }
+}
+
 // Where the row tiles (batch chunks) do not come out even over the eight XCDs, whole ones per XCD would leave some of
 // them idle: the workgroups are then numbered straight through.
 void deal(OpDesc& d, int nouter, int inner)
@@ -732,7 +1153,7 @@ OpOperand operand(const void* p, int64_t g_s, int64_t r_s, int64_t k_s, bool rc,
 // One step of the data path: O (rows x blocks x N) = A x W per block; W, and one of A and O, are of the layer's type.
 template <typename TA, typename TW, typename TO>
 int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t lda, int K, const void* w, bool w_rc, int N,
-            void* o, int64_t o_g, int64_t o_n, int64_t ldo, const void* bias, hipStream_t st, bool o_mid = false)
+            const bf16_t* planes, void* o, int64_t o_g, int64_t o_n, int64_t ldo, const void* bias, hipStream_t st, bool o_mid = false)
 {
     OpDesc d{};
     d.a = operand(a, a_g, lda, a_k, false, pb.B, K, sizeof(TA));
@@ -747,10 +1168,20 @@ int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t 
     d.K = K;
     d.N = N;
     d.G = pb.k;
+    d.k_chunk = K;
+    if (planes) {
+        const int nt = rows_tile(pb, N, d.a.take == kElements ? kSpreadIn : o_n == 1 ? kPlain : kSpreadOut);
+        d.tiles_n = (int)tiles(N, 64 * nt);
+        const bool whole = N % 4 == 0 && ldo % 4 == 0;  // pieces of four elements begin at multiples of their size
+        if (o_mid) d.o_turn = whole && N % (4 * d.G) == 0 && 64 * nt % (4 * d.G) == 0 ? kTurnMid : 64 * nt % d.G == 0 ? kTurnMidAny : kTurnDirect;
+        else if (o_n == 1) d.o_turn = whole && o_g % 4 == 0 ? kTurnNone : kTurnDirect;
+        else d.o_turn = o_g == 1 && o_n == d.G && d.G % 4 == 0 ? kTurnBlocks : kTurnDirect;
+        deal(d, (int)tiles(d.M, kRows), d.G / 4 * d.tiles_n);
+        return launch_rows<TA, TW, TO>(nt, d, planes, st);
+    }
     const int cfg = pick_tile(d.M, N, d.G, d.a.take != kElements);
     d.tiles_m = (int)tiles(d.M, kTiles[cfg].m);
     d.tiles_n = (int)tiles(N, kTiles[cfg].n);
-    d.k_chunk = K;
     deal(d, d.tiles_m, d.tiles_n * d.G);
     return launch_op<TA, TW, TO>(w_rc, cfg, d, st);
 }
@@ -805,25 +1236,46 @@ Mid mid(const Problem& pb)
 }
 
 template <typename T>
-int stage1(const Problem& pb, const void* x, const void* R, void* U, hipStream_t st)
+int stage1(const Problem& pb, const void* x, const void* R, const bf16_t* planes, void* U, hipStream_t st)
 {
     const Mid m = mid(pb);
-    return data_op<T, T, float>(pb, x, pb.p, 1, pb.n_in, pb.p, R, false, pb.q, U, m.s1_g, m.s1_n, pb.kq(), nullptr, st);
+    return data_op<T, T, float>(pb, x, pb.p, 1, pb.n_in, pb.p, R, false, pb.q, planes, U, m.s1_g, m.s1_n, pb.kq(), nullptr, st);
 }
 template <typename T>
-int fwd_typed(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* U, hipStream_t st)
+int fwd_typed(const Problem& pb, const void* x, const void* R, const void* L, const Planes& pl, void* y, void* U, hipStream_t st)
 {
-    if (int rc = stage1<T>(pb, x, R, U, st)) return rc;
+    if (int rc = stage1<T>(pb, x, R, pl.w[0], U, st)) return rc;
     const Mid m = mid(pb);
-    return data_op<float, T, T>(pb, U, m.s2_g, m.s2_n, pb.kq(), pb.q, L, false, pb.s, y, 1, pb.k, pb.n_out(), pb.bias, st);
+    return data_op<float, T, T>(pb, U, m.s2_g, m.s2_n, pb.kq(), pb.q, L, false, pb.s, pl.w[1], y, 1, pb.k, pb.n_out(), pb.bias, st);
 }
 template <typename T>
-int fwd_t_typed(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* dU, hipStream_t st)
+int fwd_t_typed(const Problem& pb, const void* x, const void* R, const void* L, const Planes& pl, void* y, void* dU, hipStream_t st)
 {
     // the vector between the factors in stage-1 order: written in short pieces once, read in long ones twice (dx, dR)
-    if (int rc = data_op<T, T, float>(pb, x, 1, pb.k, pb.n_out(), pb.s, L, true, pb.q, dU, 1, pb.k, pb.kq(), nullptr, st, !pb.perm_b()))
+    if (int rc = data_op<T, T, float>(pb, x, 1, pb.k, pb.n_out(), pb.s, L, true, pb.q, pl.w[0], dU, 1, pb.k, pb.kq(), nullptr, st, !pb.perm_b()))
         return rc;
-    return data_op<float, T, T>(pb, dU, pb.q, 1, pb.kq(), pb.q, R, true, pb.p, y, pb.p, 1, pb.n_in, nullptr, st);
+    return data_op<float, T, T>(pb, dU, pb.q, 1, pb.kq(), pb.q, R, true, pb.p, pl.w[1], y, pb.p, 1, pb.n_in, nullptr, st);
+}
+
+// The weights that the forward and the data path of the backward (recompute: with step 1 again) want as planes.
+Planes fwd_planes(const Problem& pb, const void* R, const void* L)
+{
+    Planes pl;
+    pl.add(pb, R, pb.q, pb.p, pb.p, 1, pb.perm_b() ? kPlain : kSpreadOut);
+    pl.add(pb, L, pb.s, pb.q, pb.q, 1, pb.perm_b() ? kSpreadIn : kSpreadOut);
+    return pl;
+}
+Planes fwd_t_planes(const Problem& pb, const void* R, const void* L, bool recompute)
+{
+    Planes pl;
+    pl.add(pb, L, pb.q, pb.s, 1, pb.q, kSpreadIn);
+    pl.add(pb, R, pb.p, pb.q, 1, pb.p, kPlain);
+    if (recompute) pl.add(pb, R, pb.q, pb.p, pb.p, 1, pb.perm_b() ? kPlain : kSpreadOut);
+    return pl;
+}
+int run_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, const Planes& pl, void* y, void* dU, hipStream_t st)
+{
+    return pb.dtype == 0 ? fwd_t_typed<float>(pb, x, R, L, pl, y, dU, st) : fwd_t_typed<bf16_t>(pb, x, R, L, pl, y, dU, st);
 }
 
 }  // namespace
@@ -839,23 +1291,36 @@ bool ops_supported(const Problem& pb)
     return (tiles(rows, 64) + 8) * tiles(widest, 32) * pb.k < (1LL << 30);
 }
 
-size_t ops_fwd_workspace(const Problem& pb) { return mid_bytes(pb); }
+// The vector between the factors, then the weights as planes; with room for the vector alone (`least`) the weights are
+// taken as they are, which gives the same bits.
+size_t ops_fwd_workspace(const Problem& pb) { return mid_bytes(pb) + fwd_planes(pb, nullptr, nullptr).bytes; }
+size_t ops_fwd_least(const Problem& pb) { return mid_bytes(pb); }
 
-// U: the vector between the factors (mid_bytes), left there for ops_bwd
+// U: the vector between the factors (mid_bytes), left there for ops_bwd; pb.ws_bytes from there on
 int ops_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* U, hipStream_t st)
 {
-    return pb.dtype == 0 ? fwd_typed<float>(pb, x, R, L, y, U, st) : fwd_typed<bf16_t>(pb, x, R, L, y, U, st);
+    Planes pl = fwd_planes(pb, R, L);
+    if (int rc = pl.launch(pb, pb.ws_bytes >= mid_bytes(pb) + pl.bytes ? static_cast<char*>(U) + mid_bytes(pb) : nullptr, nullptr, st)) return rc;
+    return pb.dtype == 0 ? fwd_typed<float>(pb, x, R, L, pl, y, U, st) : fwd_typed<bf16_t>(pb, x, R, L, pl, y, U, st);
 }
 
-size_t ops_fwd_t_workspace(const Problem& pb) { return mid_bytes(pb); }
+size_t ops_fwd_t_workspace(const Problem& pb) { return mid_bytes(pb) + fwd_t_planes(pb, nullptr, nullptr, false).bytes; }
+size_t ops_fwd_t_least(const Problem& pb) { return mid_bytes(pb); }
 
 // y = x M: the dx path on its own
 int ops_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* dU, hipStream_t st)
 {
-    return pb.dtype == 0 ? fwd_t_typed<float>(pb, x, R, L, y, dU, st) : fwd_t_typed<bf16_t>(pb, x, R, L, y, dU, st);
+    Planes pl = fwd_t_planes(pb, R, L, false);
+    if (int rc = pl.launch(pb, pb.ws_bytes >= mid_bytes(pb) + pl.bytes ? static_cast<char*>(dU) + mid_bytes(pb) : nullptr, nullptr, st)) return rc;
+    return run_fwd_t(pb, x, R, L, pl, y, dU, st);
 }
 
-size_t ops_bwd_workspace(const Problem& pb) { return 2 * mid_bytes(pb) + part_bytes(pb, wgrad_plan(pb).nz); }
+// U, dU, then the weights as planes, over which the partial sums of the weight gradients are written afterwards
+size_t ops_bwd_workspace(const Problem& pb)
+{
+    const size_t part = part_bytes(pb, wgrad_plan(pb).nz), planes = fwd_t_planes(pb, nullptr, nullptr, true).bytes;
+    return 2 * mid_bytes(pb) + (part > planes ? part : planes);
+}
 size_t ops_bwd_least(const Problem& pb) { return 2 * mid_bytes(pb) + part_bytes(pb, 1); }
 
 int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL,
@@ -868,20 +1333,19 @@ int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, con
         return f ? launch_fill_zero_f32((float*)dL, pb.n_L(), st) : launch_fill_zero_u16((uint16_t*)dL, pb.n_L(), st);
     }
     const WgradPlan pl = wgrad_plan(pb, pb.ws_bytes - 2 * mid_bytes(pb));
+    Planes planes = fwd_t_planes(pb, R, L, !pb.saved);
     ColsumJob cj{};
-    if (pb.dbias) {
-        cj = make_colsum_job(pb, dy, pb.dbias, pb.colsum_ws);
-        const int rc = pl.nz >= kManyChunks ? launch_colsum_partial(pb, cj, st) : launch_colsum(pb, dy, pb.dbias, pb.colsum_ws, st);
-        if (rc) return rc;
-    }
+    if (pb.dbias) cj = make_colsum_job(pb, dy, pb.dbias, pb.colsum_ws);
+    const ColsumJob* bias_sum = pb.dbias ? &cj : nullptr;
     char* w = static_cast<char*>(ws);
     const void* U = pb.saved;
+    if (int rc = planes.launch(pb, pb.ws_bytes >= 2 * mid_bytes(pb) + planes.bytes ? w + 2 * mid_bytes(pb) : nullptr, bias_sum, st)) return rc;
     if (!U) {
-        if (int rc = pb.dtype == 0 ? stage1<float>(pb, x, R, w, st) : stage1<bf16_t>(pb, x, R, w, st)) return rc;
+        if (int rc = pb.dtype == 0 ? stage1<float>(pb, x, R, planes.w[2], w, st) : stage1<bf16_t>(pb, x, R, planes.w[2], w, st)) return rc;
         U = w;
     }
     void* dU = w + mid_bytes(pb);
-    if (int rc = ops_fwd_t(pb, dy, R, L, dx, dU, st)) return rc;
+    if (int rc = run_fwd_t(pb, dy, R, L, planes, dx, dU, st)) return rc;
 
     const Mid m = mid(pb);
     const int e = (int)pb.esize();
@@ -906,8 +1370,7 @@ int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, con
     const int rc = pb.dtype == 0 ? launch_wgrad<float>(pl.cfg, d[0], d[1], st) : launch_wgrad<bf16_t>(pl.cfg, d[0], d[1], st);
     if (rc) return rc;
     const OpSum s0{P, dL, (int64_t)pb.n_L(), pl.nz}, s1{P + (size_t)pl.nz * pb.n_L(), dR, (int64_t)pb.n_R(), pl.nz};
-    const ColsumJob* second_pass = pb.dbias && pl.nz >= kManyChunks ? &cj : nullptr;
-    return pb.wgrad_f32() ? launch_sum<float>(s0, s1, second_pass, st) : launch_sum<bf16_t>(s0, s1, second_pass, st);
+    return pb.wgrad_f32() ? launch_sum<float>(s0, s1, bias_sum, st) : launch_sum<bf16_t>(s0, s1, bias_sum, st);
 }
 
 }  // namespace monarch

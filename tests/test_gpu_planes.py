@@ -175,3 +175,40 @@ def test_weight_gradients_of_a_batch_with_infinities(shape):
         finite += int(small.sum())
         redone += int((~np.isfinite(w)).sum())
     assert finite and redone
+
+
+# Batches whose contractions take the kernel with the weights laid out as planes (64 rows of four blocks; 64, 128 and 192 columns),
+# and the same call with room for the vector between the factors alone, which takes the weights as they are: the same bits.  Contractions
+# that end in the first and the second half of a chunk, pieces that start anywhere, blocks that leave whole pieces of four and not, block
+# counts of 4, 8, 12 and 16; rows that hold something not finite.
+@pytest.mark.parametrize("reading", (0, 1))
+@pytest.mark.parametrize("shape", [(12500, 4, 192, 192, 192, "f32"), (12500, 4, 50, 180, 179, "f32"), (15041, 4, 250, 256, 250, "f32"),
+                                   (16329, 8, 40, 33, 63, "f32"), (5400, 12, 32, 24, 20, "f32"), (12300, 4, 400, 192, 384, "f32"),
+                                   (16301, 4, 49, 49, 64, "bf16"), (32703, 4, 16, 64, 49, "bf16"), (4070, 16, 17, 31, 33, "bf16"),
+                                   (16300, 4, 130, 128, 120, "bf16"), (12500, 4, 70, 190, 190, "bf16")], ids=str)
+def test_weights_as_planes_give_the_same_bits(shape, reading):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, k, p, q, s, dtype = shape
+    x, R, L, dy = (torch.randn(size, generator=torch.Generator("cuda").manual_seed(9400 + i), device="cuda") * std
+                   for i, (size, std) in enumerate((((rows, k * p), 1.0), ((k, q, p), p ** -0.5), ((k, s, q), q ** -0.5), ((rows, k * s), 1.0))))
+    x[3, 5], x[rows - 1, 2], dy[35, 1], dy[rows - 2, 0] = float("inf"), float("nan"), 3e38, float("-inf")
+    if dtype == "bf16":
+        x, R, L, dy = (t.to(torch.bfloat16) for t in (x, R, L, dy))
+    flags, code = (B.MONARCH_FLAG_PERM_B if reading else 0), B.MONARCH_F32 if dtype == "f32" else B.MONARCH_BF16
+    vector = (rows * k * q * 4 + 255) // 256 * 256
+    assert reading or max(f(rows, k * p, k, q, s, code, flags) for f in (B.monarch_fwd_workspace_bytes, B.monarch_fwd_t_workspace_bytes)) > vector
+    bare = torch.empty(vector, dtype=torch.uint8, device="cuda")
+    for name, call, args in (("y", B.monarch_fwd_ws, (x, R, L)), ("xM", B.monarch_fwd_t, (dy, R, L))):
+        a, b = call(*args, flags=flags), call(*args, workspace=bare, flags=flags)
+        assert torch.equal(torch.nan_to_num(a), torch.nan_to_num(b)), name
+        assert torch.equal(torch.isnan(a), torch.isnan(b)), name
+    bias = torch.randn(k * s, generator=torch.Generator("cuda").manual_seed(9410), device="cuda").to(x.dtype)
+    y, saved = B.monarch_fwd_bias_save(x, R, L, bias, flags=flags)
+    b, kept = B.monarch_fwd_bias_save(x, R, L, bias, saved=bare, flags=flags)
+    assert torch.equal(torch.nan_to_num(y), torch.nan_to_num(b))
+    for part, again in zip(B.monarch_bwd_saved(dy, x, saved, R, L, flags=flags, want_dbias=True),
+                           B.monarch_bwd_saved(dy, x, bare, R, L, flags=flags, want_dbias=True)):
+        assert torch.equal(torch.nan_to_num(part), torch.nan_to_num(again))
+    assert torch.equal(torch.nan_to_num(B.monarch_bwd(dy, x, R, L, flags=flags)[0]), torch.nan_to_num(B.monarch_fwd_t(dy, R, L, workspace=bare, flags=flags)))
