@@ -48,7 +48,6 @@
 namespace monarch {
 namespace {
 
-constexpr int kThreads = 256;  // four waves
 constexpr int kCUs = 256;
 
 typedef __attribute__((ext_vector_type(4))) short s16x4;
@@ -113,7 +112,7 @@ struct TileDrop {
 // Elements past the limits read as zeros.  Single elements are loaded with consecutive lanes on consecutive c (at a
 // stride of 16 bytes a load takes the L1 31 cycles, at 32 bytes 60), and neighbouring lanes exchange them so that each
 // has two for a dword.
-template <typename T, int C, int O, int LSTR, Take TAKE, int SZ, int THREADS = kThreads>
+template <typename T, int C, int O, int LSTR, Take TAKE, int SZ, int THREADS>
 struct OpTile {
     static constexpr bool VEC = TAKE != kElements, kSplit = sizeof(T) == 4;
     static constexpr int V = VEC ? 16 / (int)sizeof(T) : 1;          // elements per piece
@@ -367,7 +366,7 @@ __device__ __forceinline__ void op_store(const OpDesc& d, const f32x16 (&acc)[MT
 template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bool PARTIAL, Take AV, Take BV>
 struct OpGemm {
     static constexpr bool kSplit = sizeof(TA) == 4 || sizeof(TB) == 4;
-    static constexpr int PA = sizeof(TA) == 2 ? 1 : 3, PB = sizeof(TB) == 2 ? 1 : 3;
+    static constexpr int PA = sizeof(TA) == 2 ? 1 : 3, PB = sizeof(TB) == 2 ? 1 : 3, kThreads = Cfg::WM * Cfg::WN * 64;
     static constexpr int KC = kSplit ? Cfg::CHUNK : 32, LA = op_lstr<RA, Cfg::TM, KC>(), LB = op_lstr<RB, Cfg::TN, KC>();
     static constexpr int SZA = RA ? KC * LA : Cfg::TM * LA, SZB = RB ? KC * LB : Cfg::TN * LB;
     static constexpr int SZ = PA * SZA + PB * SZB;
@@ -378,8 +377,8 @@ template <typename TA, typename TB, typename TO, class Cfg, bool RA, bool RB, bo
 __device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>::run(const OpDesc& d, int bid, unsigned char* op_lds)
 {
     constexpr int MT = Cfg::MT, NT = Cfg::NT, TM = Cfg::TM, TN = Cfg::TN;
-    using TileA = OpTile<TA, RA ? TM : KC, RA ? KC : TM, LA, AV, SZA>;
-    using TileB = OpTile<TB, RB ? TN : KC, RB ? KC : TN, LB, BV, SZB>;
+    using TileA = OpTile<TA, RA ? TM : KC, RA ? KC : TM, LA, AV, SZA, kThreads>;
+    using TileB = OpTile<TB, RB ? TN : KC, RB ? KC : TN, LB, BV, SZB, kThreads>;
     bf16_t* const lds = reinterpret_cast<bf16_t*>(op_lds);
 
     const int inner = d.G * d.tiles_n * (PARTIAL ? d.tiles_m : 1);
@@ -502,7 +501,7 @@ __device__ __forceinline__ void OpGemm<TA, TB, TO, Cfg, RA, RB, PARTIAL, AV, BV>
 }
 
 template <class G>
-__global__ void __launch_bounds__(kThreads, 2)
+__global__ void __launch_bounds__(G::kThreads, 2)
 ops_gemm_kernel(const OpDesc d)
 {
     extern __shared__ __align__(16) unsigned char op_lds[];
@@ -510,7 +509,7 @@ ops_gemm_kernel(const OpDesc d)
 }
 // two contractions, the workgroups of the second behind those of the first
 template <class G0, class G1>
-__global__ void __launch_bounds__(kThreads, 2)
+__global__ void __launch_bounds__(G0::kThreads, 2)
 ops_gemm_pair_kernel(const OpDesc d0, const OpDesc d1)
 {
     extern __shared__ __align__(16) unsigned char op_lds[];
@@ -929,7 +928,7 @@ int launch_one(const OpDesc& d, hipStream_t st)
 {
     auto kernel = ops_gemm_kernel<G>;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), G::kLds)) return hip_status(e);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)d.blocks), dim3(kThreads), G::kLds, st, d);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)d.blocks), dim3(G::kThreads), G::kLds, st, d);
     return hip_status(hipGetLastError());
 }
 template <class G0, class G1>
@@ -938,7 +937,7 @@ int launch_pair(const OpDesc& d0, const OpDesc& d1, hipStream_t st)
     constexpr size_t lds = G0::kLds > G1::kLds ? G0::kLds : G1::kLds;
     auto kernel = ops_gemm_pair_kernel<G0, G1>;
     if (hipError_t e = allow_dynamic_lds(reinterpret_cast<const void*>(kernel), lds)) return hip_status(e);
-    hipLaunchKernelGGL(kernel, dim3((unsigned)(d0.blocks + d1.blocks)), dim3(kThreads), lds, st, d0, d1);
+    hipLaunchKernelGGL(kernel, dim3((unsigned)(d0.blocks + d1.blocks)), dim3(G0::kThreads), lds, st, d0, d1);
     return hip_status(hipGetLastError());
 }
 
@@ -947,6 +946,7 @@ using Cfg128x96 = OpCfg<4, 1, 1, 3>;
 using Cfg128x64 = OpCfg<2, 2, 2, 1>;
 using Cfg64x64 = OpCfg<2, 2, 1, 1>;
 using Cfg64x128 = OpCfg<2, 2, 1, 2>;
+using Cfg192x192 = OpCfg<6, 2, 1, 3>;  // twelve waves
 struct TileSize {
     int m, n;
 };
@@ -1001,14 +1001,19 @@ int launch_op(bool w_rc, int cfg, const OpDesc& d, hipStream_t st)
                                             : launch_tile<TA, TB, TO, true, kPiecesAny, kPiecesAny>(cfg, d, st);
 }
 // dL from dy and U, dR from dU and x: T is the layer's type, U and dU are fp32
+template <typename T, class Cfg, Take AV, Take BV>
+int launch_wgrad_tile(const OpDesc& d0, const OpDesc& d1, hipStream_t st)
+{
+    return launch_pair<OpGemm<T, float, float, Cfg, true, true, true, kElements, BV>, OpGemm<float, T, float, Cfg, true, true, true, AV, BV>>(d0, d1, st);
+}
 template <typename T, Take AV, Take BV>
 int launch_wgrad_take(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
 {
-    if (cfg == 2)
-        return launch_pair<OpGemm<T, float, float, Cfg128x64, true, true, true, kElements, BV>,
-                           OpGemm<float, T, float, Cfg128x64, true, true, true, AV, BV>>(d0, d1, st);
-    return launch_pair<OpGemm<T, float, float, Cfg64x64, true, true, true, kElements, BV>,
-                       OpGemm<float, T, float, Cfg64x64, true, true, true, AV, BV>>(d0, d1, st);
+    switch (cfg) {
+        case 0: return launch_wgrad_tile<T, Cfg64x64, AV, BV>(d0, d1, st);
+        case 1: return launch_wgrad_tile<T, Cfg128x128, AV, BV>(d0, d1, st);
+        default: return launch_wgrad_tile<T, Cfg192x192, AV, BV>(d0, d1, st);
+    }
 }
 template <typename T>
 int launch_wgrad(int cfg, const OpDesc& d0, const OpDesc& d1, hipStream_t st)
@@ -1186,37 +1191,42 @@ int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t 
     return launch_op<TA, TW, TO>(w_rc, cfg, d, st);
 }
 
-// Batch chunks of the weight-gradient contractions: about four workgroups per CU over both (768 -> 768 fp32: 131 us
-// with two, 104 with four), at least four pipeline chunks of rows each, and whole sets of eight, since a chunk
+// Tiles and batch chunks of the weight-gradient contractions.  64 x 64, about four workgroups per CU over both contractions
+// (768 -> 768 fp32: 131 us with two, 104 with four; 128 x 64 gained nothing anywhere: 96 x 384 blocks, 4096 rows, backward
+// 64 us and 73).  Larger tiles, 128 x 128 two to a CU and 192 x 192 (twelve waves) one to a CU, where they cover no more
+// than the small ones and their chunks still have 256 rows: every value is split half or a third as often (768 -> 768 fp32,
+// 12608 rows, both contractions 77 us in 64 x 64 tiles, 53 in 192 x 192, of which the matrix cores alone take 30; backward
+// 176 and 152, at 1024 rows 41 and 48; 1024 -> 4096 in 128 x 128 tiles, 12608 rows 617 and 564, 4096 rows 212 and 201; 128
+// x 512 blocks, 4096 rows 83 and 94).  At least 128 rows each, and whole sets of eight, since a chunk
 // belongs to an XCD (4096 -> 1024 fp32 with three chunks: three XCDs busy, 1088 us; with eight 465 us).
 struct WgradPlan {
     int cfg;
     int nz;
     int64_t rows;  // per chunk
 };
+constexpr int kWgradTiles[] = {64, 128, 192}, kWgradGroups[] = {4 * kCUs, 2 * kCUs, kCUs};
 size_t part_bytes(const Problem& pb, int nz) { return align_up((size_t)nz * (pb.n_R() + pb.n_L()) * 4, 256); }
 WgradPlan wgrad_plan(const Problem& pb, size_t room = SIZE_MAX)  // room: bytes for the partial sums; one chunk is the least
 {
-    constexpr int KC = 32;
     const int M[2] = {pb.s, pb.q}, N[2] = {pb.q, pb.p};
+    const int64_t rows = pb.B > 0 ? pb.B : 1, most = tiles(rows, 128);
     WgradPlan pl{};
-    double best = 1e30;
-    for (int c = 2; c < 4; ++c) {  // dy is taken element by element: the two smaller tiles; of them the smallest padded area, weighted by the larger tiles' better reuse
-        double area = 0;
-        for (int i = 0; i < 2; ++i) area += (double)tiles(M[i], kTiles[c].m) * tiles(N[i], kTiles[c].n) * (kTiles[c].m * kTiles[c].n + 2048);
-        if (area < best) {
-            best = area;
-            pl.cfg = c;
-        }
+    int64_t z = 1, least = 0;  // batch chunks; what the small tiles cover
+    for (int c = 0; c < 3; ++c) {
+        const int t = kWgradTiles[c];
+        int64_t count = 0;
+        for (int i = 0; i < 2; ++i) count += tiles(M[i], t) * tiles(N[i], t);
+        int64_t nz = tiles(kWgradGroups[c], (int)(count * pb.k));
+        if (nz > 1) nz = tiles(nz, 8) * 8;  // whole sets of the eight XCDs
+        nz = std::min(nz, most);
+        if (c == 0) least = count * t * t;
+        if (c > 0 && (10 * count * t * t > 11 * least || rows < 256 * nz)) continue;
+        pl.cfg = c;
+        z = nz;
     }
-    int64_t t = 0;
-    for (int i = 0; i < 2; ++i) t += tiles(M[i], kTiles[pl.cfg].m) * tiles(N[i], kTiles[pl.cfg].n) * pb.k;
-    const int64_t rows = pb.B > 0 ? pb.B : 1, most = tiles(rows, 4 * KC);
-    int64_t nz = tiles(1024, (int)t);
-    if (nz > 1) nz = tiles(nz, 8) * 8;  // whole sets of the eight XCDs
-    nz = nz > most ? most : nz;
-    for (;; nz = pl.nz - 1) {
-        pl.rows = tiles(tiles(rows, (int)nz), KC) * KC;
+    for (;; z = pl.nz - 1) {
+        const int step = pl.cfg == 0 ? 64 : 32;
+        pl.rows = tiles(tiles(rows, (int)z), step) * step;
         pl.nz = (int)tiles(rows, (int)pl.rows);
         if (part_bytes(pb, pl.nz) <= room || pl.nz == 1) return pl;
     }
@@ -1362,8 +1372,8 @@ int ops_bwd(const Problem& pb, const void* dy, const void* x, const void* R, con
         d[i].N = N[i];
         d[i].K = pb.B;
         d[i].G = pb.k;
-        d[i].tiles_m = (int)tiles(M[i], kTiles[pl.cfg].m);
-        d[i].tiles_n = (int)tiles(N[i], kTiles[pl.cfg].n);
+        d[i].tiles_m = (int)tiles(M[i], kWgradTiles[pl.cfg]);
+        d[i].tiles_n = (int)tiles(N[i], kWgradTiles[pl.cfg]);
         d[i].k_chunk = pl.rows;
         deal(d[i], pl.nz, d[i].tiles_m * d[i].tiles_n * pb.k);
     }

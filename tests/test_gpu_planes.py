@@ -212,3 +212,22 @@ def test_weights_as_planes_give_the_same_bits(shape, reading):
                            B.monarch_bwd_saved(dy, x, bare, R, L, flags=flags, want_dbias=True)):
         assert torch.equal(torch.nan_to_num(part), torch.nan_to_num(again))
     assert torch.equal(torch.nan_to_num(B.monarch_bwd(dy, x, R, L, flags=flags)[0]), torch.nan_to_num(B.monarch_fwd_t(dy, R, L, workspace=bare, flags=flags)))
+
+
+# Weight gradients of long batches in tiles of 128 x 128 and 192 x 192, at and below the edges of a tile, dy in single elements and U from
+# anywhere, an odd last chunk; against 64 bits.  A sum over the batch leaves an error of its own size times some 2^-24 and the square root
+# of the rows of a chunk at most: 1e-6 of the norm.
+@pytest.mark.parametrize("reading", (0, 1))
+@pytest.mark.parametrize("shape", [(8321, 4, 192, 192, 192, "f32"), (8500, 4, 179, 191, 180, "f32"), (4099, 4, 256, 256, 251, "f32"),
+                                   (8200, 3, 128, 121, 128, "f32"), (8700, 4, 180, 190, 186, "bf16"), (4500, 5, 125, 120, 127, "bf16")], ids=str)
+def test_weight_gradients_in_large_tiles(shape, reading):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    x, R, L, dy = _inputs(shape, 9500)
+    flags, rd = (B.MONARCH_FLAG_PERM_B, oracle.READING_B) if reading else (0, oracle.READING_A)
+    got = B.monarch_bwd(*(_dev(a, shape[-1]) for a in (dy, x, R, L)), flags=flags | B.MONARCH_FLAG_WGRAD_F32)[1:]
+    for name, g, w in zip(("dR", "dL"), got, oracle.bwd(dy, x, R, L, rd)[1:]):
+        error = np.linalg.norm(_wide(g) - w) / np.linalg.norm(w)
+        print(shape, name, "%.2e" % error, flush=True)
+        assert error <= 1e-6, (name, error)
