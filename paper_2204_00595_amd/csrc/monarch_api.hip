@@ -95,6 +95,10 @@ size_t saved_least(const Problem& pb)
     return fwd_uses_ops(pb) && pick_bwd(pb) == FAM_OPS ? ops_fwd_least(pb) : 0;
 }
 
+// The same for a layer in training (monarch_fwd_keep), which keeps it also where monarch_fwd_save recomputes.
+bool keeps_sq64(const Problem& pb) { return !(pb.flags & MONARCH_FLAG_GENERIC) && pick_bwd(pb) == FAM_MFMA && sq64_supported(pb); }
+size_t kept_least(const Problem& pb) { return keeps_sq64(pb) ? sq64_mid_bytes(pb) : saved_least(pb); }
+
 bool room_for(const void* workspace, size_t bytes, size_t need)
 {
     return workspace && bytes >= need && (uintptr_t)workspace % 256 == 0;
@@ -242,9 +246,10 @@ int fwd_layer(const void* x, const void* R, const void* L, const void* bias, boo
     return rc;
 }
 
-// Backward of the affine layer; `saved` (may be null): the vector between the factors kept by monarch_fwd_save;
+// Backward of the affine layer; `saved` (may be null): the vector between the factors kept by monarch_fwd_save, `kept`: by
+// monarch_fwd_keep;
 // `x_pre` (may be null): the layer's input is gelu(x_pre) and dx is wanted with respect to x_pre.
-int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* saved, size_t saved_bytes, const void* R,
+int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* saved, size_t saved_bytes, bool kept, const void* R,
               const void* L, void* dx, void* dR, void* dL, void* dbias, int64_t batch, int n_in, int k, int q,
               int s, monarch_dtype dtype, void* stream, void* workspace, size_t workspace_bytes, unsigned flags)
 {
@@ -259,7 +264,7 @@ int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* save
     Family fam = pick_bwd(pb);
     if (fam == FAM_NONE) return MONARCH_ERR_UNSUPPORTED;
     if (saved) {  // ignored by the kernel families that recompute
-        const size_t sneed = saved_least(pb);
+        const size_t sneed = kept ? kept_least(pb) : saved_least(pb);
         if (sneed > 0) {
             if (saved_bytes < sneed || !aligned(saved, 16)) return MONARCH_ERR_WORKSPACE;
             pb.saved = const_cast<void*>(saved);
@@ -441,6 +446,37 @@ int monarch_fwd_bias_save(const void* x, const void* R, const void* L, const voi
     return mfma_fwd(pb, x, R, L, y, (hipStream_t)stream);
 }
 
+size_t monarch_kept_bytes(int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, unsigned flags)
+{
+    Problem pb;
+    if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags)) return 0;
+    return keeps_sq64(pb) ? sq64_kept_bytes(pb) : monarch_saved_bytes(batch, n_in, k, q, s, dtype, flags);
+}
+
+int monarch_fwd_keep(const void* x, const void* R, const void* L, const void* bias, void* y, void* kept, size_t kept_bytes,
+                     int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, void* stream, unsigned flags)
+{
+    Problem pb;
+    int rc = make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags);
+    if (rc) return rc;
+    if (!keeps_sq64(pb)) return monarch_fwd_bias_save(x, R, L, bias, y, kept, kept_bytes, batch, n_in, k, q, s, dtype, stream, flags);
+    if (flags & (MONARCH_FLAG_WGRAD_F32 | MONARCH_FLAG_WS_PACKED)) return MONARCH_ERR_INVALID;
+    if (!R || !L || ((!x || !y) && batch > 0)) return MONARCH_ERR_INVALID;
+    if (!aligned(x, 16) || !aligned(R, 16) || !aligned(L, 16) || !aligned(y, 16) || !aligned(bias, 16)) return MONARCH_ERR_INVALID;
+    if (!kept || kept_bytes < sq64_kept_bytes(pb) || !aligned(kept, 16)) return MONARCH_ERR_WORKSPACE;
+    if (batch == 0) return MONARCH_OK;
+    pb.bias = bias;
+    return fwd_sq64_keep(pb, x, R, L, y, kept, (hipStream_t)stream);
+}
+
+int monarch_bwd_kept(const void* dy, const void* x, const void* kept, size_t kept_bytes, const void* R, const void* L, void* dx, void* dR,
+                     void* dL, void* dbias, int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, void* stream,
+                     void* workspace, size_t workspace_bytes, unsigned flags)
+{
+    return bwd_layer(dy, x, nullptr, kept, kept_bytes, true, R, L, dx, dR, dL, dbias, batch, n_in, k, q, s, dtype, stream, workspace,
+                     workspace_bytes, flags);
+}
+
 size_t monarch_bwd_workspace_bytes(int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype,
                                    unsigned flags)
 {
@@ -470,7 +506,7 @@ int monarch_bwd_saved(const void* dy, const void* x, const void* saved, size_t s
                       const void* L, void* dx, void* dR, void* dL, void* dbias, int64_t batch, int n_in, int k, int q,
                       int s, monarch_dtype dtype, void* stream, void* workspace, size_t workspace_bytes, unsigned flags)
 {
-    return bwd_layer(dy, x, nullptr, saved, saved_bytes, R, L, dx, dR, dL, dbias, batch, n_in, k, q, s, dtype, stream,
+    return bwd_layer(dy, x, nullptr, saved, saved_bytes, false, R, L, dx, dR, dL, dbias, batch, n_in, k, q, s, dtype, stream,
                      workspace, workspace_bytes, flags);
 }
 
@@ -480,7 +516,7 @@ int monarch_bwd_bias_gelu_in(const void* dy, const void* x, const void* x_pre, c
 {
     if (!x_pre && batch > 0) return MONARCH_ERR_INVALID;
     if (!aligned(x_pre, 16) || (x_pre && x_pre == dx_pre)) return MONARCH_ERR_INVALID;
-    return bwd_layer(dy, x, x_pre, nullptr, 0, R, L, dx_pre, dR, dL, dbias, batch, n_in, k, q, s, dtype, stream,
+    return bwd_layer(dy, x, x_pre, nullptr, 0, false, R, L, dx_pre, dR, dL, dbias, batch, n_in, k, q, s, dtype, stream,
                      workspace, workspace_bytes, flags);
 }
 

@@ -201,6 +201,9 @@ bool sq64_supported(const Problem& pb);
 int fwd_sq64(const Problem& pb, const void* x, const void* R, const void* L, void* y, hipStream_t st);
 size_t fwd_sq64_workspace(const Problem& pb);  // forward on factors packed in fragment order
 int fwd_sq64_ws(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
+size_t sq64_mid_bytes(const Problem& pb);   // the vector between the factors
+size_t sq64_kept_bytes(const Problem& pb);  // ... and what the forward that keeps it lays out beside it
+int fwd_sq64_keep(Problem pb, const void* x, const void* R, const void* L, void* y, void* kept, hipStream_t st);
 size_t fwd_t_sq64_workspace(const Problem& pb);  // transposed multiply y = x M
 int fwd_t_sq64(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 bool bwd_sq64_supported(const Problem& pb);

@@ -90,12 +90,11 @@ int mfma_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, v
 bool mfma_fwd_fuses_bias(const Problem& pb, bool with_ws)
 {
     if (with_ws && fwd_packed(pb)) return true;
-    if (with_ws && sq64_supported(pb)) return false;
-    // of mfma_fwd's kernels all but sq64 have a bias epilogue
-    return fwd_wide_supported(pb) || (!sq64_supported(pb) && (sq16_supported(pb) || tiled_fwd_supported(pb)));
+    // all of mfma_fwd's kernels have a bias epilogue
+    return fwd_wide_supported(pb) || sq64_supported(pb) || sq16_supported(pb) || tiled_fwd_supported(pb);
 }
 
-bool mfma_bwd_fuses_dbias(const Problem& pb) { return bwd_split_preferred(pb) || bwd_wide_supported(pb); }
+bool mfma_bwd_fuses_dbias(const Problem& pb) { return bwd_split_preferred(pb) || bwd_wide_supported(pb) || bwd_sq64_supported(pb); }
 
 // The nonlinearity of the feed-forward block: applied in the epilogue of the packed-weight forward for the
 // four-block layer shapes, and in the dx epilogue of their (recomputing) backward.

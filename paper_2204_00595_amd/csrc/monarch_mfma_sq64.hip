@@ -25,8 +25,8 @@
 //
 // Backward (adjoints of steps 3, 2, P^T, 1; the paper leaves them to automatic differentiation,
 // Section 4):
-//   u           block stage (x, R) -> U to the workspace (dL needs it)
-//   stage L     dy, U -> dU (to the workspace) and dL's partial sums
+//   u           block stage (x, R) -> U to the workspace (dL needs it), unless the forward kept it
+//   stage L     dy, U -> dU (to the workspace), dL's partial sums and the bias gradient's
 //   stage R     dU, x -> dx and dR's partial sums        (both: bwd_sq64_stage_kernel)
 //   reduce      the sums over the batch chunks (monarch_mfma_wgrad.hip)
 // What bounds it: memory.  U, dU and the inputs are read and written 8 times in all (1.07 GB at 16384 rows); the
@@ -37,6 +37,7 @@
 #include "monarch_mfma_common.h"
 #include "monarch_mfma_stage1.h"
 #include "monarch_lds_tr.h"
+#include "monarch_colsum.h"
 
 namespace monarch {
 
@@ -210,9 +211,10 @@ __device__ __forceinline__ void column_stage_inplace(const Lane& t_, const uint1
 // 128 lines, eight per instruction (1 KiB contiguous).  Line (b, jl) goes to
 // dst[(b0 + b) * 4096 + (col0 + jl) * 64 ..].  SWZ: tile rows are 4096 bytes and the 16-byte piece
 // index is XOR-ed with b % 8; otherwise rows are SQ_ROWB bytes, pieces in order.
+// bias (may be null): added to the bf16 results, 64 values a line.
 template <bool SWZ, bool NT = SWZ>
 __device__ __forceinline__ void copy_out(const Lane& t_, const unsigned char* ldsb, uint16_t* __restrict__ dst,
-                                         int64_t b0, int64_t B, int col0)
+                                         int64_t b0, int64_t B, int col0, const uint16_t* __restrict__ bias = nullptr)
 {
 #pragma unroll
     for (int k2 = 0; k2 < 16; ++k2) {
@@ -220,7 +222,14 @@ __device__ __forceinline__ void copy_out(const Lane& t_, const unsigned char* ld
         const int b = 4 * t_.wave + (line >> 5), jl = line & 31;
         const unsigned char* src = SWZ ? ldsb + (size_t)b * 4096 + jl * 128 + ((pc ^ (b & 7)) * 16)
                                        : ldsb + (size_t)b * SQ_ROWB + jl * 128 + pc * 16;
-        const u32x4 v = *reinterpret_cast<const u32x4*>(src);
+        u32x4 v = *reinterpret_cast<const u32x4*>(src);
+        if (bias) {
+            const u32x4 a = ldg128(bias + (size_t)(col0 + jl) * M64 + 8 * pc);
+#pragma unroll
+            for (int w = 0; w < 4; ++w)
+                v[w] = pack_bf16x2(__uint_as_float(v[w] << 16) + __uint_as_float(a[w] << 16),
+                                   __uint_as_float(v[w] & 0xffff0000u) + __uint_as_float(a[w] & 0xffff0000u));
+        }
         if (b0 + b < B) {
             uint16_t* p = dst + (b0 + b) * N64 + (size_t)(col0 + jl) * M64 + 8 * pc;
             if (NT) stg128_nt(p, v);  // final outputs: streamed; workspace copies stay cacheable for the next kernel
@@ -242,10 +251,12 @@ __device__ __forceinline__ Lane make_lane()
 
 // ------------------------------------------------------------------------ forward ----
 
+// U (may be null): the vector between the factors also goes there, in the exchange layout, which is the one the backward
+// reads.
 template <bool PACKED>
 __global__ void __launch_bounds__(512)
-fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R,
-                const uint16_t* __restrict__ L, uint16_t* __restrict__ y, int64_t B)
+fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R, const uint16_t* __restrict__ L,
+                const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, uint16_t* __restrict__ U, int64_t B)
 {
     extern __shared__ __attribute__((aligned(16))) unsigned char ldsb[];
     const Lane t = make_lane();
@@ -270,6 +281,7 @@ fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R,
             exchange_write(t, ldsb, pk1);
         }
         __syncthreads();
+        if (U) copy_out<false>(t, ldsb, U, b0, B, 32 * h);
         f32x16 ev;
         column_stage<PACKED>(t, L, ldsb, h, [&](int cc, const f32x16& acc) {
             if ((cc & 1) == 0) {
@@ -299,7 +311,7 @@ fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R,
                 }
         }
         __syncthreads();
-        copy_out<true>(t, ldsb, y, b0, B, 32 * rnd);
+        copy_out<true>(t, ldsb, y, b0, B, 32 * rnd, bias);
     }
 }
 
@@ -431,13 +443,14 @@ struct Stage64 {
     const uint16_t *in, *W, *other;
     uint16_t* out;
     void* P;  // partial dW[chunk][c][l][r], fp32 or bf16
+    float* colsum;  // SUMS: row zi receives the column sums of `in` over the chunk
     int p_bf16, nz, steps, down;
     int64_t B;
 };
-__global__ void __launch_bounds__(512)
-bwd_sq64_stage_kernel(const Stage64 a)
+// SUMS: and the sums of the columns of `in` (the bias gradient), by adding up the fragments that dW is multiplied from.
+template <bool SUMS>
+__device__ __forceinline__ void bwd_sq64_stage(const Stage64& a, unsigned char* ldsb)
 {
-    extern __shared__ __attribute__((aligned(16))) unsigned char ldsb[];
     const int tid = threadIdx.x, wave = __builtin_amdgcn_readfirstlane(tid >> 6), lane = tid & 63, ln = lane & 31, h = lane >> 5;
     // a chunk's eight workgroups on one XCD (workgroups go to the eight XCDs in turn)
     const int nwg = gridDim.x, xcd = blockIdx.x & 7, slot = blockIdx.x >> 3, per = nwg >> 3;  // (a multiple of eight)
@@ -521,6 +534,7 @@ bwd_sq64_stage_kernel(const Stage64 a)
     for (int t = 0; t < 4; ++t)
 #pragma unroll
         for (int i = 0; i < 16; ++i) dw[t >> 1][t & 1][i] = 0.f;
+    float sums[2] = {0.f, 0.f};  // column l = 32 t + lane % 32 of block c, half of the rows
     int rsel = 0;  // ring place of the step's `other`
     auto step = [&](int s, auto par) {
         constexpr int K = decltype(par)::value;
@@ -547,6 +561,14 @@ bwd_sq64_stage_kernel(const Stage64 a)
         lgkm_wait(it);
         lgkm_wait(ot);
         __builtin_amdgcn_sched_barrier(0);
+        if constexpr (SUMS) {
+            auto add_pair = [](uint32_t pair, float sum) {
+                return __builtin_amdgcn_fdot2_f32_bf16(__builtin_bit_cast(bf16x2, pair), bf16x2{(__bf16)1.f, (__bf16)1.f}, sum, false);
+            };
+#pragma unroll
+            for (int o = 0; o < 4; ++o)
+                sums[o >> 1] += add_pair(it[o].lo[0], add_pair(it[o].lo[1], add_pair(it[o].hi[0], add_pair(it[o].hi[1], 0.f))));
+        }
         f32x16 o2[2];
 #pragma unroll
         for (int t = 0; t < 2; ++t) {
@@ -585,6 +607,13 @@ bwd_sq64_stage_kernel(const Stage64 a)
         step(s + 1, std::integral_constant<int, 1>{});
     }
     wait_vmcnt<0>();  // nothing is on its way into LDS any more
+    if constexpr (SUMS) {
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+            const float v = sums[t] + __shfl_xor(sums[t], 32);
+            if (h == 0) a.colsum[(size_t)zi * N64 + (32 * t + ln) * 64 + c] = v;
+        }
+    }
 
     // partial dW: lane = l, runs of four r; the wave turns its 32 x 32 tiles in its ring
     const size_t base = ((size_t)zi * 64 + c) * 4096;
@@ -618,6 +647,14 @@ bwd_sq64_stage_kernel(const Stage64 a)
             for (int n = 0; n < 4; ++n) *reinterpret_cast<u32x4*>(to + n * 8 * 64) = line[n];
         }
     });
+}
+
+template <bool SUMS>
+__global__ void __launch_bounds__(512)
+bwd_sq64_stage_kernel(const Stage64 a)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char ldsb[];
+    bwd_sq64_stage<SUMS>(a, ldsb);
 }
 
 // Batch chunks of the two stages: with the eight workgroups of a chunk about one per CU, at least two steps of 32 rows
@@ -665,7 +702,7 @@ int fwd_sq64(const Problem& pb, const void* x, const void* R, const void* L, voi
     const int64_t grid = (pb.B + SQ_BM - 1) / SQ_BM;
     if (grid > 0x7fffffffLL) return -2;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), SQ_LDS, st, (const uint16_t*)x, (const uint16_t*)R,
-                       (const uint16_t*)L, (uint16_t*)y, pb.B);
+                       (const uint16_t*)L, (const uint16_t*)pb.bias, (uint16_t*)y, (uint16_t*)nullptr, pb.B);
     return hip_status(hipGetLastError());
 }
 
@@ -687,8 +724,21 @@ int fwd_sq64_ws(const Problem& pb, const void* x, const void* R, const void* L, 
         return -4;
     const int64_t grid = (pb.B + SQ_BM - 1) / SQ_BM;
     if (grid > 0x7fffffffLL) return -2;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), SQ_LDS, st, (const uint16_t*)x, Rp, Lp, (uint16_t*)y, pb.B);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), SQ_LDS, st, (const uint16_t*)x, Rp, Lp, (const uint16_t*)pb.bias,
+                       (uint16_t*)y, (uint16_t*)pb.saved, pb.B);
     return hip_status(hipGetLastError());
+}
+
+// ... that keeps the vector between the factors for the backward, which then neither reads x nor multiplies for it: a write
+// of U in place of a kernel that reads x and writes U.  kept = U, then the packed factors of this call.  Training step of
+// the layer, 16384 rows: 329 -> 287 us (forward 70 -> 90, without 54 + 5 in the backward), 4096 rows 106 -> 89; with a bias,
+// which took a pass over y and one over dy, 414 -> 290 and 137 -> 95.
+size_t sq64_mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B > 0 ? pb.B : 1) * N64 * 2, 256); }
+size_t sq64_kept_bytes(const Problem& pb) { return sq64_mid_bytes(pb) + fwd_sq64_workspace(pb); }
+int fwd_sq64_keep(Problem pb, const void* x, const void* R, const void* L, void* y, void* kept, hipStream_t st)
+{
+    pb.saved = kept;
+    return fwd_sq64_ws(pb, x, R, L, y, (char*)kept + sq64_mid_bytes(pb), st);
 }
 
 bool bwd_sq64_supported(const Problem& pb) { return sq64_supported(pb); }
@@ -735,28 +785,33 @@ int bwd_sq64(const Problem& pb, const void* dy, const void* x, const void* R, co
     const int64_t grid = (pb.B + SQ_BM - 1) / SQ_BM;
     if (grid > 0x7fffffffLL || pb.B > 0x7fffffffLL) return -2;
     char* w = (char*)ws;
-    uint16_t* U = (uint16_t*)(w + pl.off_u);
+    const uint16_t* U = pb.saved ? (const uint16_t*)pb.saved : (const uint16_t*)(w + pl.off_u);
     uint16_t* dU = (uint16_t*)(w + pl.off_du);
     uint16_t* Rp = (uint16_t*)(w + pl.off_rp);
+    auto stage = bwd_sq64_stage_kernel<false>, stage_sums = bwd_sq64_stage_kernel<true>;
     if (allow_dynamic_lds((const void*)u_sq64_kernel, SQ_LDS) != hipSuccess ||
-        allow_dynamic_lds((const void*)bwd_sq64_stage_kernel, ST_LDS) != hipSuccess)
+        allow_dynamic_lds((const void*)stage, ST_LDS) != hipSuccess || allow_dynamic_lds((const void*)stage_sums, ST_LDS) != hipSuccess)
         return -4;
-    const Pack64Job jr{(const uint16_t*)R, Rp, 0};
-    hipLaunchKernelGGL(pack64_kernel, dim3(128), dim3(256), 0, st, jr, jr);
-    hipLaunchKernelGGL(u_sq64_kernel, dim3((unsigned)grid), dim3(512), SQ_LDS, st, (const uint16_t*)x, Rp, U, pb.B);
-    if (hipGetLastError() != hipSuccess) return -4;
+    if (!pb.saved) {
+        const Pack64Job jr{(const uint16_t*)R, Rp, 0};
+        hipLaunchKernelGGL(pack64_kernel, dim3(128), dim3(256), 0, st, jr, jr);
+        hipLaunchKernelGGL(u_sq64_kernel, dim3((unsigned)grid), dim3(512), SQ_LDS, st, (const uint16_t*)x, Rp, (uint16_t*)(w + pl.off_u), pb.B);
+        if (hipGetLastError() != hipSuccess) return -4;
+    }
     WgradDesc dl{}, dr{};
     dl.M = dl.N = dl.G = M64; dl.seg_w = M64;
     dl.p_bf16 = pl.p_bf16;
     dr = dl;
     dl.P = (float*)(w + pl.off_partL); dl.out = dL;
     dr.P = (float*)(w + pl.off_partR); dr.out = dR;
-    const Stage64 sl{(const uint16_t*)dy, (const uint16_t*)L, U, dU, dl.P, dl.p_bf16, pl.nz, pl.steps, 1, pb.B};
-    const Stage64 sr{dU, (const uint16_t*)R, (const uint16_t*)x, (uint16_t*)dx, dr.P, dr.p_bf16, pl.nz, pl.steps, 0, pb.B};
-    hipLaunchKernelGGL(bwd_sq64_stage_kernel, dim3((unsigned)(8 * pl.nz)), dim3(512), ST_LDS, st, sl);
-    hipLaunchKernelGGL(bwd_sq64_stage_kernel, dim3((unsigned)(8 * pl.nz)), dim3(512), ST_LDS, st, sr);
+    ColsumJob cj{};
+    if (pb.dbias) cj = wgrad_colsum_job(pb, pl.nz);
+    const Stage64 sl{(const uint16_t*)dy, (const uint16_t*)L, U, dU, dl.P, cj.part, dl.p_bf16, pl.nz, pl.steps, 1, pb.B};
+    const Stage64 sr{dU, (const uint16_t*)R, (const uint16_t*)x, (uint16_t*)dx, dr.P, nullptr, dr.p_bf16, pl.nz, pl.steps, 0, pb.B};
+    hipLaunchKernelGGL(pb.dbias ? stage_sums : stage, dim3((unsigned)(8 * pl.nz)), dim3(512), ST_LDS, st, sl);
+    hipLaunchKernelGGL(stage, dim3((unsigned)(8 * pl.nz)), dim3(512), ST_LDS, st, sr);
     if (hipGetLastError() != hipSuccess) return -4;
-    return wgrad_reduce_pair(dl, dr, f32out, pl.nz, st);
+    return wgrad_reduce_pair(dl, dr, f32out, pl.nz, st, pb.dbias ? &cj : nullptr);
 }
 
 }  // namespace monarch

@@ -275,8 +275,9 @@ Tensor fwd_t(const Tensor& x, const Tensor& R, const Tensor& L, Tensor y, Tensor
 struct Saved {
     Tensor y, saved;
 };
+// layer: monarch_fwd_keep, which keeps the vector for more shapes
 Saved fwd_save(const Tensor& x, const Tensor& R, const Tensor& L, const Tensor& bias, Tensor y, Tensor saved, unsigned flags,
-               const StreamArg& st)
+               const StreamArg& st, bool layer = false)
 {
     const Shape sh(x, R, L);
     const Where w(sh, st);
@@ -284,15 +285,15 @@ Saved fwd_save(const Tensor& x, const Tensor& R, const Tensor& L, const Tensor& 
     sh.check_factors(R, L);
     if (bias.defined()) check(bias, "bias", {sh.n_out()}, sh.dtype, sh.device);
     y = out(y, "y", {sh.B, sh.n_out()}, sh.dtype, sh.device);
-    const size_t need = monarch_saved_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
+    const size_t need = (layer ? monarch_kept_bytes : monarch_saved_bytes)(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
     if (flags & MONARCH_FLAG_WS_PACKED) raise_status(MONARCH_ERR_INVALID, "monarch_fwd_save");
     // nothing to save for this shape: the forward that has a workspace (fp32, k = 64 blocks of 64, 12000 rows: 6050
     // us without one, which is the SIMT kernels there, 290 with)
     if (!need) return Saved{fwd_layer("monarch_fwd_save", x, R, L, bias, Act::none, {}, false, y, {}, flags, st).y, Tensor()};
     if (!saved.defined()) saved = make({(int64_t)need}, at::kByte, sh.device);
     const Bytes b(saved);
-    const int rc = monarch_fwd_bias_save(ptr(x), ptr(R), ptr(L), ptr(bias), ptr(y), b.p, b.n, sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q,
-                                         (int)sh.s, sh.code(), w.stream(), flags);
+    const int rc = (layer ? monarch_fwd_keep : monarch_fwd_bias_save)(ptr(x), ptr(R), ptr(L), ptr(bias), ptr(y), b.p, b.n, sh.B, (int)sh.n_in(),
+                                                                      (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), w.stream(), flags);
     if (rc) raise_status(rc, "monarch_fwd_save");
     return Saved{y, saved};
 }
@@ -303,7 +304,7 @@ struct Grads {
     Tensor dx, dR, dL, dbias;
 };
 Grads bwd(const char* name, const Tensor& dy, const Tensor& x, const Tensor& x_pre, const Tensor& saved, const Tensor& R,
-          const Tensor& L, Grads g, bool want_dbias, Tensor ws, unsigned flags, const StreamArg& st)
+          const Tensor& L, Grads g, bool want_dbias, Tensor ws, unsigned flags, const StreamArg& st, bool layer = false)
 {
     const Shape sh(x, R, L);
     const Where w(sh, st);
@@ -324,8 +325,9 @@ Grads bwd(const char* name, const Tensor& dy, const Tensor& x, const Tensor& x_p
     const int rc = x_pre.defined()
         ? monarch_bwd_bias_gelu_in(ptr(dy), ptr(x), ptr(x_pre), ptr(R), ptr(L), ptr(g.dx), ptr(g.dR), ptr(g.dL), ptr(g.dbias), sh.B,
                                    (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), w.stream(), b.p, b.n, flags)
-        : monarch_bwd_saved(ptr(dy), ptr(x), sv.p, sv.n, ptr(R), ptr(L), ptr(g.dx), ptr(g.dR), ptr(g.dL), ptr(g.dbias), sh.B,
-                            (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), w.stream(), b.p, b.n, flags);
+        : (layer ? monarch_bwd_kept : monarch_bwd_saved)(ptr(dy), ptr(x), sv.p, sv.n, ptr(R), ptr(L), ptr(g.dx), ptr(g.dR), ptr(g.dL), ptr(g.dbias),
+                                                         sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), w.stream(), b.p, b.n,
+                                                         flags);
     if (rc) raise_status(rc, name);
     return g;
 }
@@ -420,8 +422,8 @@ Grads c64_bwd(bool with_ws, const Tensor& dy, const Tensor& x, const Tensor& R, 
 // y = x M^T (+ bias).  The forward can keep the vector between the factors for the backward (save_intermediate), else
 // the backward recomputes it.
 struct LinearFn : torch::autograd::Function<LinearFn> {
-    // Where keeping the vector pays, by the GPU time of a training step with bias, recomputed and kept: fp32 and odd
-    // blocks always (192 x 192, four blocks, fp32, 12608 rows: one contraction of 53 us of 400 less).  The bf16
+    // Where keeping the vector pays, by the GPU time of a training step with bias, recomputed and kept: 64 blocks of 64
+    // always (16384 rows 329 us and 287, 4096 rows 106 and 89); fp32 and odd blocks always (192 x 192, four blocks, fp32, 12608 rows: one contraction of 53 us of 400 less).  The bf16
     // layers of four blocks that are multiples of 64 have other forwards for the call that keeps nothing.  Those of
     // short batches (256 x 1024: 300 rows 47 and 54 us, 1000 rows 58 and 59) lose their lead between 1500 and 3500
     // rows (256 x 1024: 2000 rows 76 and 73; 192 x 768: 2000 rows 60 and 62, 2500 rows 66 and 63; 192 x 192: 2500
@@ -455,7 +457,7 @@ struct LinearFn : torch::autograd::Function<LinearFn> {
         const Tensor x2 = rows_of(x, R.size(0) * R.size(2));
         const StreamArg current;
         Saved r;
-        if (save_intermediate && keeps(x2, R, L)) r = fwd_save(x2, R, L, bias.value_or(Tensor()), {}, {}, 0, current);
+        if (save_intermediate && keeps(x2, R, L)) r = fwd_save(x2, R, L, bias.value_or(Tensor()), {}, {}, 0, current, true);
         else if (bias.has_value()) r.y = fwd_layer("monarch_fwd_bias", x2, R, L, *bias, Act::none, {}, false, {}, {}, 0, current).y;
         else r.y = fwd_layer("monarch_fwd_ws", x2, R, L, {}, Act::none, {}, false, {}, {}, 0, current).y;
         ctx->save_for_backward({x2, R, L, r.saved});
@@ -473,7 +475,7 @@ struct LinearFn : torch::autograd::Function<LinearFn> {
         const Tensor &x2 = saved[0], &R = saved[1], &L = saved[2];
         const bool bias = ctx->saved_data.count("bias") != 0;
         const StreamArg current;
-        Grads g = bwd("monarch_bwd_saved", rows_of(dy[0], L.size(0) * L.size(1)), x2, {}, saved[3], R, L, {}, bias, {}, 0, current);
+        Grads g = bwd("monarch_bwd_saved", rows_of(dy[0], L.size(0) * L.size(1)), x2, {}, saved[3], R, L, {}, bias, {}, 0, current, true);
         const auto shape = ctx->saved_data.find("shape");
         if (shape != ctx->saved_data.end()) g.dx = g.dx.view(shape->second.toIntVector());
         return {g.dx, g.dR, g.dL, g.dbias, Tensor()};

@@ -29,3 +29,45 @@ def test_backward_at_the_edges(rows):
             assert err <= 2.0 ** -8, (name, rows, flags, err)
         again = B.monarch_bwd(dy, x, R, L, flags=flags)
         assert all(torch.equal(g, a) for g, a in zip(got, again))
+
+
+# The layer, which keeps the vector between the factors, against the calls that recompute it: the same bits, with a bias and without,
+# and the bias gradient from the sums of the weight gradient's fragments against 64 bits (fp32 sums of 8 rows, then of a chunk's).
+@pytest.mark.gpu
+@pytest.mark.parametrize("bias", (False, True), ids=("no_bias", "bias"))
+@pytest.mark.parametrize("rows", [1, 31, 64, 97, 257, 2113])
+def test_layer_keeps_the_vector(rows, bias):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import autograd
+    from paper_2204_00595_amd import binding as B
+    gen = torch.Generator(device="cuda").manual_seed(50 + rows)
+    x, dy, R, L, b = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+                      for shape in ((rows, 4096), (rows, 4096), (64, 64, 64), (64, 64, 64), (4096,)))
+    code = B.MONARCH_BF16
+    assert B.lib().monarch_kept_bytes(rows, 4096, 64, 64, 64, code, 0) >= rows * 8192
+    assert B.lib().monarch_kept_bytes(rows, 4096, 64, 64, 64, code, B.MONARCH_FLAG_GENERIC) == 0
+    layer = autograd.MonarchLinear(4096, 4096, nblocks=64, bias=bias, q=64, device="cuda", dtype=torch.bfloat16)
+    with torch.no_grad():
+        layer.R.copy_(R)
+        layer.L.copy_(L)
+        if bias:
+            layer.bias.copy_(b)
+    xg = x.clone().requires_grad_(True)
+    y = layer(xg)
+    y.backward(dy)
+    want = B.monarch_fwd_ws(x, R, L)
+    if bias:
+        want = (want.float() + b.float()).to(torch.bfloat16)
+        assert torch.equal(B.monarch_fwd_bias(x, R, L, b), want)
+    assert torch.equal(y, want)
+    for got, ref in zip((xg.grad, layer.R.grad, layer.L.grad), B.monarch_bwd(dy, x, R, L)):
+        assert torch.equal(got, ref)
+    if not bias:
+        return
+    exact = dy.double().sum(0)
+    size = dy.double().abs().sum(0)
+    for got in (layer.bias.grad, B.monarch_bwd_bias(dy, x, R, L)[3]):
+        assert bool(((got.double() - exact).abs() <= 2.0 ** -8 * exact.abs() + 1e-6 * size).all())
+    got = B.monarch_bwd_bias(dy, x, R, L, flags=B.MONARCH_FLAG_WGRAD_F32)[3]
+    assert bool(((got.double() - exact).abs() <= 1e-6 * size).all())
