@@ -113,6 +113,129 @@ split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__
     }
 }
 
+// Both factors in one launch, for a few rows on packed weights.  A workgroup computes 32 columns of one output block c, and
+// for them the vector that block c contracts by itself: those are the outputs c q/4 .. (c + 1) q/4 of every block of the
+// first factor, so that the workgroups of a block read the same quarter of R (128 KiB at 256 x 256) and none waits for
+// another.  Eight waves: wave = (block kk, one of the two 32-row tiles of R that the quarter touches), the contraction in
+// four parts that are added up as in split_stage1 (the same bits); then one wave multiplies with L, whose fragments it
+// requested at the start.  A workgroup's block goes by its XCD, for the quarter of R to come through two L2s.
+// Bound by latency: one of memory, the way of the quarter through the L1 (2500 clocks at 256 x 256) and two chains of
+// products.  On the GPU alone, 256 x 1024 blocks: 8 rows 6.5 us in two launches, 5.7 in one, 32 rows 6.9 and 6.8, 64 rows
+// 7.0 and 7.2; 192 x 768: 8 rows 6.3 and 5.0, 64 rows 6.9 and 6.2; 512 x 128 (the quarter of R as large, four times the
+// rows): 8 rows 5.6 and 6.3.  Both layers of width 1024 with the host's part, 8 rows: 15.8 and 12.9.
+template <int T4, int K4, bool ACT>
+__global__ void __launch_bounds__(512)
+split_once_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ RF1, const uint16_t* __restrict__ LF2,
+                  const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, uint16_t* __restrict__ y_pre, int64_t B, int P, int Q, int S)
+{
+    extern __shared__ __attribute__((aligned(16))) unsigned char split_lds[];
+    uint16_t* const Uf = reinterpret_cast<uint16_t*>(split_lds);  // fragments of the block's vector: [step][h][row][8]
+    uint16_t* const xs = Uf + 4 * K4 * 2 * 32 * 8;                // 16-byte pieces of x: [piece][row ^ piece % 32]
+    const int wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6), lane = threadIdx.x & 63, ln = lane & 31, h = lane >> 5;
+    const int bid = (int)blockIdx.x, c = (bid & 7) >> 1, lt = (bid >> 3) * 2 + (bid & 1), QT = Q / 32, KS = Q / 16, LT = S / 32;
+    if (lt >= LT) return;
+    const int64_t b0 = (int64_t)blockIdx.y * 32;
+    const int rows = B - b0 < 32 ? (int)(B - b0) : 32, j0 = c * (Q / 4);
+    const int kk = wave & 3, jt = j0 / 32 + (wave >> 2);
+    const bool work = jt * 32 < j0 + Q / 4;
+
+    // x in whole lines (taken as operands, 32 rows to a load, the launch was 8.6 us for 32 rows of 256 x 1024 blocks)
+    constexpr int XN = (T4 + 1) / 2;  // 64 pieces of each of a wave's four rows
+    const int pieces = P / 2;         // of a row
+    const auto rx = buffer_at(x + b0 * 4 * P);
+    u32x4 xv[4][XN];
+#pragma unroll
+    for (int i = 0; i < 4; ++i)
+#pragma unroll
+        for (int n = 0; n < XN; ++n)
+            xv[i][n] = __builtin_amdgcn_raw_buffer_load_b128(rx, wave * 4 + i < rows && n * 64 + lane < pieces ? (n * 64 + lane) * 16u : kNowhere,
+                                                             (uint32_t)(wave * 4 + i) * (8u * P), 0);
+    __builtin_amdgcn_sched_barrier(0);
+    u32x4 lf[4 * K4];
+    const auto rl = buffer_at(LF2 + (size_t)(c * LT + lt) * KS * 512);
+    if (wave == 0) {
+#pragma unroll
+        for (int ks = 0; ks < 4 * K4; ++ks) lf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rl, ks < KS ? lane * 16u : kNowhere, ks * 1024u, 0);
+    }
+    auto put = [&] {
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            if (wave * 4 + i >= rows) break;
+#pragma unroll
+            for (int n = 0; n < XN; ++n) {
+                const int pc = n * 64 + lane;
+                if (pc < pieces) *reinterpret_cast<u32x4*>(xs + (pc * 32 + ((wave * 4 + i) ^ (pc & 31))) * 8) = xv[i][n];
+            }
+        }
+    };
+    if (!work) {
+        put();
+        lds_barrier();
+    } else {
+        const int T = P / 16;
+        const auto rw = buffer_at(RF1 + (size_t)kk * Q * P);
+        const uint32_t w_at = (uint32_t)jt * 1024u + lane * 16u;
+        u32x4 wf[4][T4];
+#pragma unroll
+        for (int part = 0; part < 4; ++part) {
+            const int lo = T * part / 4, n = T * (part + 1) / 4 - lo;
+#pragma unroll
+            for (int t = 0; t < T4; ++t)
+                wf[part][t] = __builtin_amdgcn_raw_buffer_load_b128(rw, t < n ? w_at : kNowhere, (uint32_t)((lo + t) * QT) * 1024u, 0);
+        }
+        __builtin_amdgcn_sched_barrier(0);
+        put();
+        lds_barrier();
+        f32x16 acc[4];
+#pragma unroll
+        for (int part = 0; part < 4; ++part) {
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[part][r] = 0.f;
+            const int lo = T * part / 4, n = T * (part + 1) / 4 - lo;
+#pragma unroll
+            for (int t = 0; t < T4; ++t) {
+                if (t >= n) continue;
+                const int pc = (kk * T + lo + t) * 2 + h;
+                acc[part] = mfma32(as_bf16x8(wf[part][t]), as_bf16x8(lds128(xs + (pc * 32 + (ln ^ (pc & 31))) * 8)), acc[part]);
+            }
+        }
+        // element 8 (r/4) + 4 h + r%4 of the tile is the vector's (kk, j): four j are half of a step's 16 bytes
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+            const int step = (jt * 32 + 8 * q4 + 4 * h - j0) / 4;
+            float v[4];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = acc[0][4 * q4 + e] + acc[1][4 * q4 + e] + acc[2][4 * q4 + e] + acc[3][4 * q4 + e];
+            if (jt * 32 + 8 * q4 + 4 * h >= j0 && step < KS)
+                *reinterpret_cast<u32x2*>(Uf + ((step * 2 + (kk >> 1)) * 32 + ln) * 8 + (kk & 1) * 4) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+        }
+    }
+    lds_barrier();
+    if (wave != 0) return;
+    f32x16 acc;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) acc[r] = 0.f;
+#pragma unroll
+    for (int ks = 0; ks < 4 * K4; ++ks)
+        if (ks < KS) acc = mfma32(as_bf16x8(lds128(Uf + ((ks * 2 + h) * 32 + ln) * 8)), as_bf16x8(lf[ks]), acc);
+    const int col = (lt * 32 + ln) * 4 + c;
+    const float bv = bias ? __uint_as_float((uint32_t)bias[col] << 16) : 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+        const int row = 8 * (r / 4) + 4 * h + r % 4;
+        if (row >= rows) continue;
+        const size_t at = (size_t)(b0 + row) * 4 * S + col;
+        const float v = acc[r] + bv;
+        if constexpr (ACT) {
+            if (y_pre) y_pre[at] = (uint16_t)pack_bf16x2(v, v);
+            const float a = gelu_f(v);
+            y[at] = (uint16_t)pack_bf16x2(a, a);
+        } else {
+            y[at] = (uint16_t)pack_bf16x2(v, v);
+        }
+    }
+}
+
 struct SplitArgs {
     const uint16_t* x;
     SplitPack w;
@@ -164,6 +287,28 @@ int launch_factor(const Problem& pb, int stage, const SplitArgs& a, hipStream_t 
     return tiles <= 512 ? launch_steps<1, 1, 4>(pb, stage, a, st) : launch_steps<1, 2, 2>(pb, stage, a, st);
 }
 
+// Where one launch does for both factors (split_once_kernel): packed weights, p up to 256, one row tile, two where the
+// quarter of R is small.
+bool once_preferred(const Problem& pb) { return pb.ws_packed() && pb.p <= 256 && pb.B <= (pb.p * pb.q <= 192 * 192 ? 64 : 32); }
+// T4, 4 K4: K-steps of a quarter of the first contraction and of the second
+template <int T4, int K4>
+int launch_once(const Problem& pb, const SplitArgs& a, hipStream_t st)
+{
+    auto kern = pb.act ? split_once_kernel<T4, K4, true> : split_once_kernel<T4, K4, false>;
+    const dim3 grid((unsigned)((pb.s / 32 + 1) / 2 * 8), (unsigned)((pb.B + 31) / 32));
+    const size_t lds = (size_t)K4 * 4096 + (size_t)pb.p * 256;
+    if (hipError_t e = allow_dynamic_lds((const void*)kern, lds)) return hip_status(e);
+    hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, a.x, (const uint16_t*)a.w.RF1, (const uint16_t*)a.w.LF2, (const uint16_t*)pb.bias, a.y,
+                       (uint16_t*)pb.y_pre, pb.B, pb.p, pb.q, pb.s);
+    return hip_status(hipGetLastError());
+}
+template <int T4>
+int launch_once_steps(const Problem& pb, const SplitArgs& a, hipStream_t st)
+{
+    if (pb.q <= 128) return launch_once<T4, 2>(pb, a, st);
+    return pb.q <= 192 ? launch_once<T4, 3>(pb, a, st) : launch_once<T4, 4>(pb, a, st);
+}
+
 }  // namespace
 
 bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
@@ -190,6 +335,11 @@ int fwd_split(const Problem& pb, const void* x, const void* R, const void* L, ui
 {
     const SplitArgs a{(const uint16_t*)x, SplitPack{(const uint16_t*)R, (const uint16_t*)L, RF1, LF2, pb.s, (int)((pb.n_R() + pb.n_L()) / 8), 0},
                       (uint16_t*)y, (uint16_t*)U};
+    if (once_preferred(pb)) {
+        if (pb.p <= 128) return launch_once_steps<2>(pb, a, st);
+        if (pb.p <= 192) return launch_once_steps<3>(pb, a, st);
+        return launch_once_steps<4>(pb, a, st);
+    }
     const int rc = launch_factor(pb, 1, a, st);
     return rc ? rc : launch_factor(pb, 2, a, st);
 }

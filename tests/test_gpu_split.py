@@ -228,3 +228,29 @@ def test_backward_at_its_row_limits(case, past):
         assert err <= 4e-3, (name, err)
     rel = torch.linalg.norm(dx.double() - want[0], dim=1) / torch.linalg.norm(want[0], dim=1)
     assert float(rel.max()) <= 6e-3   # no row: twice the root mean square
+
+
+# A few rows on packed weights: both factors in one launch.  Every quarter of R against its tiles (q = 96: 24 rows, 192: 48), a last
+# pair of column tiles with one of them, rows at the edges of a tile and past the second one; the bits of the two launches that the same
+# call makes where it packs, with bias and nonlinearity too.
+@pytest.mark.parametrize("rows", (1, 7, 32, 33, 64, 65))
+@pytest.mark.parametrize("dims", [(256, 256, 1024), (192, 192, 768), (192, 192, 576), (128, 128, 512), (64, 64, 64), (128, 64, 64), (64, 128, 128)], ids=str)
+def test_few_rows_in_one_launch(dims, rows):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    p, q, s = dims
+    sh = synth.Shape("once_%s" % (dims,), "bf16", rows, 4, p, q, s, config=990 + rows)
+    x, R, L, _ = synth.make_inputs(sh)
+    bias = synth.quantize(synth.normal(78, (sh.n_out,)), "bf16")
+    xd, Rd, Ld, bd = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L, bias))
+    ws = torch.empty(B.monarch_fwd_workspace_bytes(rows, sh.n_in, 4, q, s, 1), dtype=torch.uint8, device="cuda")
+    guard = torch.full((rows + 1, sh.n_out), 7.0, device="cuda", dtype=torch.bfloat16)
+    want = (B.monarch_fwd_ws(xd, Rd, Ld, workspace=ws), B.monarch_fwd_bias(xd, Rd, Ld, bd, workspace=ws), *B.monarch_fwd_bias_gelu(xd, Rd, Ld, bd, workspace=ws))
+    flag = B.MONARCH_FLAG_WS_PACKED
+    got = (B.monarch_fwd_ws(xd, Rd, Ld, y=guard[:rows], workspace=ws, flags=flag), B.monarch_fwd_bias(xd, Rd, Ld, bd, workspace=ws, flags=flag),
+           *B.monarch_fwd_bias_gelu(xd, Rd, Ld, bd, workspace=ws, flags=flag))
+    assert bool((guard[rows] == 7.0).all())
+    for name, g, w in zip(("y", "bias", "pre", "gelu"), got, want):
+        assert torch.equal(g, w), name
+    parity_util.check("once_%s.y" % (dims,), got[0].float().cpu().numpy(), oracle.fwd(x, R, L), 2e-2)
