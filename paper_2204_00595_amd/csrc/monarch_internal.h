@@ -109,6 +109,7 @@ bool complex_fwd_h_supported(const Problem& pb);
 // takes real32_mfma_workspace(pb, pass) bytes (pass: 0 forward, 1 backward, 2 transposed multiply)
 bool real32_mfma_supported(const Problem& pb);
 size_t real32_mfma_workspace(const Problem& pb, int pass);
+size_t real32_mfma_bwd_least(const Problem& pb);  // as ops_bwd_least
 int real32_mfma_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 int real32_mfma_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st);
 int real32_mfma_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR,

@@ -120,7 +120,9 @@ size_t mfma_bwd_least(const Problem& pb)
     if (bwd_split_preferred(pb)) return bwd_split_least(pb);
     if (bwd_wide_supported(pb)) return bwd_wide_least(pb);
     if (bwd_sq64_supported(pb)) return bwd_sq64_least(pb);
-    return !sq16_supported(pb) && tiled_bwd_supported(pb) ? tiled_bwd_least(pb) : mfma_bwd_workspace(pb);
+    if (sq16_supported(pb)) return bwd_sq16_workspace(pb);
+    if (tiled_bwd_supported(pb)) return tiled_bwd_least(pb);
+    return real32_mfma_supported(pb) ? real32_mfma_bwd_least(pb) : 0;
 }
 const char* mfma_bwd_name(const Problem& pb)
 {

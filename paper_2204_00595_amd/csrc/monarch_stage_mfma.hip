@@ -35,8 +35,9 @@
 // one L2.
 //
 // Weight gradients: dL[c] = dW[c]^T conj(U[c]),  dR[kk] = dY1[kk]^T conj(x[kk]),  contracted over the batch by the
-// same MFMA (K = eight rows x two components); a workgroup owns one block and a share of the row tiles, the shares'
-// partial results go to the workspace and are summed in a fixed order (no atomics).
+// same MFMA (K = eight rows x two components), in the launch that computes the gradient of the factor's input
+// (cboth_kernel); a workgroup owns one block and a share of the row tiles, the shares' partial results go to the
+// workspace and are summed in a fixed order (no atomics).
 //
 // Real fp32 layers with square blocks of 32 or 64 run on the same kernels (template flag REAL): a float2 is then two
 // consecutive values of a row, the activation side is unchanged, the weights are taken as stored and the
@@ -217,24 +218,6 @@ struct ActTile {
         }
     }
 
-    // kInGather: the tile as it is, in the order of a kInT source
-    __device__ __forceinline__ void to_tile(float2* __restrict__ tile, int tid) const
-    {
-#pragma unroll
-        for (int n = 0; n < (REAL ? 2 : 1) * kPieces; ++n) {
-            const int idx = tid + n * NTHR;
-            if constexpr (REAL) {
-                const int row = idx / (2 * P), i = idx - row * (2 * P);
-                reinterpret_cast<float*>(tile)[((i >> 1) * kRT + row) * 2 + (i & 1)] = __uint_as_float(v[n / 4][n % 4]);
-            } else {
-                const int row = idx / P, i = idx - row * P;
-                const u32x4 w = v[n / 2];
-                if (has(idx)) tile[i * kRT + row] = (n & 1) ? make_float2(__uint_as_float(w.z), __uint_as_float(w.w))
-                                                           : make_float2(__uint_as_float(w.x), __uint_as_float(w.y));
-            }
-        }
-    }
-
     __device__ __forceinline__ void to_lds(bf16_t* act, int tid) const
     {
         if constexpr (IN == kInNat) {
@@ -286,11 +269,124 @@ struct ActTile {
         }
     }
 
+    // The tile in both orders at once, the one above and that of a weight-gradient operand (WgTile).
+    template <typename TW>
+    __device__ __forceinline__ void to_both(bf16_t* act, bf16_t* wg, int tid) const
+    {
+        constexpr int WS = TW::kStride, WP = TW::kPlane;
+        if constexpr (IN == kInGather && REAL) {
+#pragma unroll
+            for (int n = 0; n < 2 * kPieces; ++n) {
+                const int idx = tid + n * NTHR, row = idx / (2 * P), i = idx - row * (2 * P);
+                uint32_t a[3];
+                split3(v[n / 4][n % 4], 0u, a);
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    act[u * kPlane + row * kStride + i] = (bf16_t)a[u];
+                    wg[u * WP + i * WS + row] = (bf16_t)a[u];
+                }
+            }
+        } else if constexpr (IN == kInGather) {
+#pragma unroll
+            for (int n = 0; n < kPieces; ++n) {
+                const int idx = tid + n * NTHR, row = idx / P, i = idx - row * P;
+                const u32x4 w = v[n / 2];
+                uint32_t a[3];
+                if (n & 1) split3(w.z, w.w, a);
+                else split3(w.x, w.y, a);
+                if (!has(idx)) continue;
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    *reinterpret_cast<uint32_t*>(act + u * kPlane + row * kStride + 2 * i) = a[u];
+                    *reinterpret_cast<uint32_t*>(wg + u * WP + i * WS + 2 * row) = a[u];
+                }
+            }
+        } else {
+            static_assert(IN == kInT, "rows in their natural order are no operand of both");
+#pragma unroll
+            for (int n = 0; n < kPieces; ++n) {
+                const int idx = tid + n * NTHR, i = idx / (kRT / 2), row = 2 * (idx - i * (kRT / 2));
+                uint32_t a[3], b[3];
+                split3(v[n].x, v[n].y, a);
+                split3(v[n].z, v[n].w, b);
+                if (!has(idx)) continue;
+#pragma unroll
+                for (int u = 0; u < 3; ++u) {
+                    *reinterpret_cast<uint32_t*>(act + u * kPlane + row * kStride + 2 * i) = a[u];
+                    *reinterpret_cast<uint32_t*>(act + u * kPlane + (row + 1) * kStride + 2 * i) = b[u];
+                    if constexpr (REAL) {
+                        *reinterpret_cast<uint32_t*>(wg + u * WP + 2 * i * WS + row) = pick_lo16(a[u], b[u]);
+                        *reinterpret_cast<uint32_t*>(wg + u * WP + (2 * i + 1) * WS + row) = pick_hi16(a[u], b[u]);
+                    } else {
+                        *reinterpret_cast<u32x2*>(wg + u * WP + i * WS + 2 * row) = u32x2{a[u], b[u]};
+                    }
+                }
+            }
+        }
+    }
+
     // the MFMA operand of step t: lane (row, h) the components 16 t + 8 h ..
     static __device__ __forceinline__ void read(bf16x8 (&b)[3], const bf16_t* act, int t, int lane)
     {
 #pragma unroll
         for (int u = 0; u < 3; ++u) b[u] = as_bf16x8(lds128(act + u * kPlane + (lane & 31) * kStride + 16 * t + 8 * (lane >> 5)));
+    }
+};
+
+// Where a lane's results go within a tile of the workspace (kOutTFwd, kOutTBwd): 32-bit byte offsets, which leave
+// cstage_kernel room for a third workgroup.
+template <int Q, int OUT, bool REAL>
+struct TiledOut {
+    static constexpr bool kTiled = OUT == kOutTFwd || OUT == kOutTBwd, kWhole = Q % 16 == 0;
+    static constexpr int kOuts = kTiled ? (REAL ? 16 : 8) : 1;
+    uint32_t off[kOuts];
+    __device__ __forceinline__ void init(int g, int mt, int kh, int col, int k, bool pb)
+    {
+        if constexpr (!kTiled) return;
+#pragma unroll
+        for (int o = 0; o < kOuts; ++o) {
+            constexpr int E = REAL ? 2 : 1;  // values per float2 of the output
+            const int j = 16 * mt + 4 * (o / (2 * E)) + 2 * kh + o / E % 2, n = E * j + o % E;
+            const int d = (OUT == kOutTFwd) ? mid_dest(g * E * Q + n, k, E * Q, pb) : mid_src(g * E * Q + n, k, E * Q, pb);
+            const int blk = d / (E * Q), idx = d - blk * (E * Q);
+            off[o] = (uint32_t)(((blk * Q + idx / E) * kRT + col) * E + idx % E) * (uint32_t)(8 / E);
+        }
+    }
+    __device__ __forceinline__ void store(float2* __restrict__ out, const f32x16& acc, int64_t rt, int mt, int kh, int k) const
+    {
+        char* const to = reinterpret_cast<char*>(out + (size_t)rt * k * (Q * kRT));
+#pragma unroll
+        for (int o = 0; o < kOuts; ++o) {
+            if (!kWhole && 16 * mt + 4 * (o / 2) + 2 * kh + o % 2 >= Q) continue;
+            if constexpr (REAL) *reinterpret_cast<float*>(to + off[o]) = acc[o];
+            else *reinterpret_cast<float2*>(to + off[o]) = make_float2(acc[2 * o], acc[2 * o + 1]);
+        }
+    }
+};
+// kOutNat: a tile's results through LDS [row][Q + 1], then out in whole rows
+template <int Q, int NTHR>
+struct NatOut {
+    static constexpr int kStride = Q + 1, kLen = kRT * kStride;  // float2
+    static __device__ __forceinline__ void put(float2* ost, const f32x16& acc, int mt, int kh, int col)
+    {
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+            for (int h = 0; h < 2; ++h)
+                if (Q % 16 == 0 || 16 * mt + 4 * q4 + 2 * kh + h < Q)
+                    ost[col * kStride + 16 * mt + 4 * q4 + 2 * kh + h] = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
+    }
+    static __device__ __forceinline__ void emit(const float2* ost, float2* __restrict__ out, int64_t rt, int g, int64_t ld, int64_t B, int tid)
+    {
+        constexpr int kAll = kRT * Q / 2, kPieces = (kAll + NTHR - 1) / NTHR;
+#pragma unroll
+        for (int n = 0; n < kPieces; ++n) {
+            const int idx = tid + n * NTHR, r = idx / (Q / 2), c2 = idx - r * (Q / 2);
+            if (kAll % NTHR != 0 && idx >= kAll) continue;
+            const float2 v0 = ost[r * kStride + 2 * c2], v1 = ost[r * kStride + 2 * c2 + 1];
+            if (rt * kRT + r < B)
+                *reinterpret_cast<f32x4*>(out + (rt * kRT + r) * ld + (size_t)g * Q + 2 * c2) = f32x4{v0.x, v0.y, v1.x, v1.y};
+        }
     }
 };
 
@@ -306,20 +402,19 @@ struct ActTile {
 // is what one pair of K = 2 steps contracts, so the activation side is unchanged; the weights are used as they are
 // (CONJT: transposed), and since the permutations move single values, the two values of a result pair go to their
 // places separately (in the tiled workspace, to the pair slot [index / 2][row][index % 2] of the consumer's block).
-// kInGather: `tiles`, if given, receives the input as it is gathered, in the order of a kInT source.
 template <int P, int Q, int IN, int OUT, bool CONJT, bool REAL = false>
 __global__ void __launch_bounds__(kTileWaves<Q> * 64, P >= 56 || IN == kInGather ? 2 : 3)
 cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float2* __restrict__ out, int64_t B,
-              int k, int nsplit, int perm_b, float2* __restrict__ tiles)
+              int k, int nsplit, int perm_b)
 {
     constexpr int NTHR = kTileWaves<Q> * 64;
     constexpr bool kWhole = Q % 16 == 0;  // else the last wave has outputs that do not exist
     using Tile = ActTile<P, NTHR, IN, REAL>;
-    constexpr int OSTR = Q + 1;
+    using Nat = NatOut<Q, NTHR>;
     // kOutNat: the barrier before the results leave LDS also frees the tile, so one buffer will do
     constexpr int kBufs = OUT == kOutNat ? 1 : 2;
     __shared__ __align__(16) bf16_t act[kBufs][Tile::kLen];
-    __shared__ __align__(16) float2 ost[OUT == kOutNat ? kRT * OSTR : 1];
+    __shared__ __align__(16) float2 ost[OUT == kOutNat ? Nat::kLen : 1];
 
     const int g = (int)blockIdx.x / nsplit, split = (int)blockIdx.x - g * nsplit;
     const int tid = threadIdx.x, lane = tid & 63, mt = tid >> 6;
@@ -331,20 +426,9 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
     bf16x8 A[P / 8][3];
     load_weights<P, Q, CONJT, REAL>(A, W, g, mt, col, kh);
 
-    // where this lane's results go within a tile of the workspace: 32-bit offsets, which leave a third workgroup room
-    constexpr bool kTiled = OUT == kOutTFwd || OUT == kOutTBwd;
-    constexpr int kOuts = kTiled ? (REAL ? 16 : 8) : 1;
-    uint32_t off[kOuts];
-    if constexpr (kTiled) {
-#pragma unroll
-        for (int o = 0; o < kOuts; ++o) {
-            constexpr int E = REAL ? 2 : 1;  // values per float2 of the output
-            const int j = 16 * mt + 4 * (o / (2 * E)) + 2 * kh + o / E % 2, n = E * j + o % E;
-            const int d = (OUT == kOutTFwd) ? mid_dest(g * E * Q + n, k, E * Q, pb) : mid_src(g * E * Q + n, k, E * Q, pb);
-            const int blk = d / (E * Q), idx = d - blk * (E * Q);
-            off[o] = (uint32_t)(((blk * Q + idx / E) * kRT + col) * E + idx % E) * (uint32_t)(8 / E);
-        }
-    }
+    using Tiled = TiledOut<Q, OUT, REAL>;
+    Tiled tiled;
+    tiled.init(g, mt, kh, col, k, pb);
 
     Tile pre;
     int64_t rt = split;
@@ -352,9 +436,6 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
     for (int it = 0; rt < ntiles; rt += nsplit, ++it) {
         bf16_t* a = act[kBufs == 2 ? it & 1 : 0];
         pre.to_lds(a, tid);
-        if constexpr (IN == kInGather) {
-            if (tiles) pre.to_tile(tiles + ((size_t)rt * k + g) * (P * kRT), tid);
-        }
         lds_barrier();
         if (rt + nsplit < ntiles) pre.fetch(in, rt + nsplit, g, k, ld_in, B, tid);
 
@@ -371,30 +452,11 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
 
         const int64_t row = rt * kRT + col;
         if constexpr (OUT == kOutNat) {
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    if (kWhole || 16 * mt + 4 * q4 + 2 * kh + h < Q)
-                        ost[col * OSTR + 16 * mt + 4 * q4 + 2 * kh + h] = make_float2(acc[4 * q4 + 2 * h], acc[4 * q4 + 2 * h + 1]);
+            Nat::put(ost, acc, mt, kh, col);
             lds_barrier();
-            constexpr int kAll = kRT * Q / 2, kPieces = (kAll + NTHR - 1) / NTHR;
-#pragma unroll
-            for (int n = 0; n < kPieces; ++n) {
-                const int idx = tid + n * NTHR, r = idx / (Q / 2), c2 = idx - r * (Q / 2);
-                if (kAll % NTHR != 0 && idx >= kAll) continue;
-                const float2 v0 = ost[r * OSTR + 2 * c2], v1 = ost[r * OSTR + 2 * c2 + 1];
-                if (rt * kRT + r < B)
-                    *reinterpret_cast<f32x4*>(out + (rt * kRT + r) * ld_out + (size_t)g * Q + 2 * c2) = f32x4{v0.x, v0.y, v1.x, v1.y};
-            }
-        } else if constexpr (kTiled) {
-            char* const to = reinterpret_cast<char*>(out + (size_t)rt * k * (Q * kRT));
-#pragma unroll
-            for (int o = 0; o < kOuts; ++o) {
-                if (!kWhole && 16 * mt + 4 * (o / 2) + 2 * kh + o % 2 >= Q) continue;
-                if constexpr (REAL) *reinterpret_cast<float*>(to + off[o]) = acc[o];
-                else *reinterpret_cast<float2*>(to + off[o]) = make_float2(acc[2 * o], acc[2 * o + 1]);
-            }
+            Nat::emit(ost, out, rt, g, ld_out, B, tid);
+        } else if constexpr (Tiled::kTiled) {
+            tiled.store(out, acc, rt, mt, kh, k);
         } else {
 #pragma unroll
             for (int o = 0; o < 8; ++o) {
@@ -556,9 +618,7 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
 // cgather8_kernel: dy (read through the outer permutation) -> tiled workspace, weights conj(L[c])^T.  The eight
 // blocks' values of 32 rows x 16 inputs come in as 64-byte pieces and are laid out in LDS as one plane per block,
 // [row][16 + 2]; a wave takes its operands from its own plane.  Four (P = 64) such chunks make a tile; the next
-// chunk is fetched into registers while the current one is multiplied.  EMIT: the workgroups of M tile 0 also write
-// the chunk to the workspace in the tiled order (dW[row tile][block][l][32 rows]), the operand of the weight-gradient
-// kernel, which then does not have to gather dy again.
+// chunk is fetched into registers while the current one is multiplied.
 template <int P>
 struct Gather8 {
     static constexpr int kPlane = kRT * 18 + 2;
@@ -567,10 +627,10 @@ struct Gather8 {
 
 // REAL (see cstage_kernel): the pieces of dy are 32 bytes (eight blocks' values of one (row, input)), a chunk is
 // 32 inputs = 16 pairs, and the weights are L[c]^T as stored.  MTW: M tiles of a wave (launch_gather8).
-template <int P, int Q, bool EMIT, bool REAL, int MTW>
+template <int P, int Q, bool REAL, int MTW>
 __global__ void __launch_bounds__(512)
 cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float2* __restrict__ out,
-                float2* __restrict__ dwt, int64_t B, int k, int nsplit, int perm_b)
+                int64_t B, int k, int nsplit, int perm_b)
 {
     constexpr int MTG = kTileWaves<Q> / MTW;
     constexpr int NCHUNK = (P + 15) / 16;
@@ -663,14 +723,6 @@ cgather8_kernel(const float2* __restrict__ in, const float2* __restrict__ W, flo
 #pragma unroll
                 for (int m = 0; m < MTW; ++m) plane_products<3, 3>(A[m][2 * ch + u], b, acc[m], acc[m]);
             }
-            if constexpr (EMIT) {
-                if (mt0 == 0) {
-                    float2* dst = dwt + (((size_t)rt * k + g) * P + 16 * ch) * kRT;
-#pragma unroll
-                    for (int n = 0; n < 8; ++n)
-                        if (16 * ch + 2 * n < P) dst[(2 * n + kh) * kRT + col] = mine[col * 18 + 2 * n + kh];
-                }
-            }
         }
         char* const to = reinterpret_cast<char*>(out + (size_t)rt * k * (Q * kRT));
 #pragma unroll
@@ -760,7 +812,7 @@ ctile_kernel(const float2* __restrict__ in, float2* __restrict__ out, int64_t B,
 }
 
 // part[z][g][ma][nb] = sum over the rows b of the tiles z, z + Z, ... of  A[b][g][ma] * conj(Bv[b][g][nb])
-// A: dW or dY1 (kInT);  Bv: U (kInT) or x (kInNat).  M = 2*MA real rows (re and im of the
+// A: dW (kInT or kInGather) or dY1 (kInT);  Bv: U (kInT) or x (kInNat).  M = 2*MA real rows (re and im of the
 // result), N = NB columns, K = (row, component): with B'[(b,t)][nb] = component t of Bv[b][nb],
 //   A'[2ma][(b,0)] = ar,  A'[2ma][(b,1)] = ai,  A'[2ma+1][(b,0)] = ai,  A'[2ma+1][(b,1)] = -ar.
 // Wave w owns the 16 values ma = 16w .. 16w+15 and every column.  LDS holds each operand as three bf16 planes
@@ -862,49 +914,29 @@ struct WgTile {
 // REAL: real fp32 operands, two consecutive values per float2: out[g][ma'][nb'] = sum_b A[b][g][ma'] * Bv[b][g][nb']
 // for the 2*MA x 2*NB real indices; a K = 2 step contracts two batch rows, each lane picking its component of the
 // pair.
-template <int MA, int NB, int AMODE, int BMODE, bool REAL = false>
-__global__ void __launch_bounds__(kTileWaves<MA> * 64)
-cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float2* __restrict__ part, int64_t B, int k,
-              int Z, int64_t lda, int64_t ldb)
-{
-    constexpr int NTHR = kTileWaves<MA> * 64;
-    constexpr int NTN = REAL ? (2 * NB + 31) / 32 : (NB + 31) / 32;
-    using TA = WgTile<MA, NTHR, AMODE, REAL>;
+template <int MA, int NB, int AMODE, int BMODE, bool REAL>
+struct WgradSums {
+    static constexpr int NTHR = kTileWaves<MA> * 64, NTN = REAL ? (2 * NB + 31) / 32 : (NB + 31) / 32;
+    using TA = WgTile<MA, NTHR, AMODE == kInGather ? kInT : AMODE, REAL>;
     using TB = WgTile<NB, NTHR, BMODE, REAL>;
-    extern __shared__ __align__(16) bf16_t wg_lds[];  // TA::kLen + TB::kLen values: one buffer, two workgroups of a CU take turns
-
-    const int g = (int)blockIdx.x / Z, z = (int)blockIdx.x - g * Z;
-    const int tid = threadIdx.x, lane = tid & 63, mt = tid >> 6;
-    const int col = lane & 31, kh = lane >> 5, e = lane & 1;
-    int ma = 16 * mt + (col >> 1);
-    if (MA % 16 != 0 && ma >= MA) ma = MA - 1;  // a row that does not exist
-    const int64_t ntiles = (B + kRT - 1) / kRT;
-
     f32x16 acc[NTN];
-#pragma unroll
-    for (int nt = 0; nt < NTN; ++nt)
-#pragma unroll
-        for (int r = 0; r < 16; ++r) acc[nt][r] = 0.f;
 
-    TA pa;
-    TB pbv;
-    int64_t rt = z;
-    if (rt < ntiles) {
-        pa.fetch(A, rt, g, k, lda, B, tid);
-        pbv.fetch(Bv, rt, g, k, ldb, B, tid);
+    __device__ __forceinline__ void zero()
+    {
+#pragma unroll
+        for (int nt = 0; nt < NTN; ++nt)
+#pragma unroll
+            for (int r = 0; r < 16; ++r) acc[nt][r] = 0.f;
     }
-    bf16_t* const ta = wg_lds;
-    bf16_t* const tb = wg_lds + TA::kLen;
-    const uint32_t turn = e ? 0x01000302u : 0x03020100u, flip = e ? 0x80000000u : 0u;  // (ar, ai) or (ai, -ar)
-    for (; rt < ntiles; rt += Z) {
-        lds_barrier();
-        pa.to_lds(ta, tid);
-        pbv.to_lds(tb, tid);
-        lds_barrier();
-        if (rt + Z < ntiles) {
-            pa.fetch(A, rt + Z, g, k, lda, B, tid);
-            pbv.fetch(Bv, rt + Z, g, k, ldb, B, tid);
-        }
+    static __device__ __forceinline__ int row_of(int mt, int col)
+    {
+        const int ma = 16 * mt + (col >> 1);
+        return MA % 16 != 0 && ma >= MA ? MA - 1 : ma;  // a row that does not exist
+    }
+    __device__ __forceinline__ void add_tile(const bf16_t* ta, const bf16_t* tb, int mt, int lane)
+    {
+        const int col = lane & 31, kh = lane >> 5, e = lane & 1, ma = row_of(mt, col);
+        const uint32_t turn = e ? 0x01000302u : 0x03020100u, flip = e ? 0x80000000u : 0u;  // (ar, ai) or (ai, -ar)
 #pragma unroll
         for (int s = 0; s < (REAL ? 2 : 4); ++s) {
             bf16x8 av[3];
@@ -928,65 +960,153 @@ cwgrad_kernel(const float2* __restrict__ A, const float2* __restrict__ Bv, float
             }
         }
     }
-    const bool off = planes_overflowed(acc);
+    // the sums of the tiles z, z + Z, ...: unscaled, what is not finite computed again in fp32, and out
+    __device__ __forceinline__ void finish(const float2* __restrict__ A, const float2* __restrict__ Bv, float2* __restrict__ part, int64_t B,
+                                           int k, int g, int z, int Z, int64_t lda, int64_t ldb, int mt, int lane)
+    {
+        const int col = lane & 31, kh = lane >> 5, e = lane & 1, ma = row_of(mt, col);
+        const int64_t ntiles = (B + kRT - 1) / kRT;
+        const bool off = planes_overflowed(acc);
 #pragma unroll
-    for (int nt = 0; nt < NTN; ++nt) acc[nt] *= kPlaneUnscale<2>;
-    if (off) {
+        for (int nt = 0; nt < NTN; ++nt) acc[nt] *= kPlaneUnscale<2>;
+        if (off) {
 #pragma unroll
-        for (int nt = 0; nt < NTN; ++nt) {
-            if (!planes_overflowed(acc[nt])) continue;
-            const bool mine = planes_clear(acc[nt]);
-            int nb = REAL ? 16 * nt + (col >> 1) : 32 * nt + col;
-            if (nb >= NB) nb = NB - 1;
+            for (int nt = 0; nt < NTN; ++nt) {
+                if (!planes_overflowed(acc[nt])) continue;
+                const bool mine = planes_clear(acc[nt]);
+                int nb = REAL ? 16 * nt + (col >> 1) : 32 * nt + col;
+                if (nb >= NB) nb = NB - 1;
 #pragma clang loop unroll(disable)
-            for (int64_t t = z; t < ntiles; t += Z)
+                for (int64_t t = z; t < ntiles; t += Z)
 #pragma clang loop unroll(disable)
-                for (int u0 = 0; u0 < kRT / 2; u0 += 2) {
-                    float2 av[2], bv[2];
+                    for (int u0 = 0; u0 < kRT / 2; u0 += 2) {
+                        float2 av[2], bv[2];
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        av[u] = act_value<MA, AMODE, REAL>(A, t, 2 * (u0 + u) + kh, g, ma, k, lda, B);
-                        bv[u] = act_value<NB, BMODE, REAL>(Bv, t, 2 * (u0 + u) + kh, g, nb, k, ldb, B);
-                        if (!mine) bv[u] = make_float2(0.f, 0.f);
-                    }
+                        for (int u = 0; u < 2; ++u) {
+                            av[u] = act_value<MA, AMODE, REAL>(A, t, 2 * (u0 + u) + kh, g, ma, k, lda, B);
+                            bv[u] = act_value<NB, BMODE, REAL>(Bv, t, 2 * (u0 + u) + kh, g, nb, k, ldb, B);
+                            if (!mine) bv[u] = make_float2(0.f, 0.f);
+                        }
 #pragma unroll
-                    for (int u = 0; u < 2; ++u) {
-                        if constexpr (REAL) {
-                            acc[nt] = mfma_f32(e ? av[u].y : av[u].x, e ? bv[u].y : bv[u].x, acc[nt]);
-                        } else {
-                            acc[nt] = mfma_f32(e ? av[u].y : av[u].x, bv[u].x, acc[nt]);
-                            acc[nt] = mfma_f32(e ? -av[u].x : av[u].y, bv[u].y, acc[nt]);
+                        for (int u = 0; u < 2; ++u) {
+                            if constexpr (REAL) {
+                                acc[nt] = mfma_f32(e ? av[u].y : av[u].x, e ? bv[u].y : bv[u].x, acc[nt]);
+                            } else {
+                                acc[nt] = mfma_f32(e ? av[u].y : av[u].x, bv[u].x, acc[nt]);
+                                acc[nt] = mfma_f32(e ? -av[u].x : av[u].y, bv[u].y, acc[nt]);
+                            }
                         }
                     }
-                }
+            }
+        }
+        if constexpr (REAL) {
+            // acc[nt][r]: row 32*mt + 8*(r/4) + 4*kh + r%4, column 32*nt + col of the (2*MA) x (2*NB) block
+            float* o = reinterpret_cast<float*>(part) + ((size_t)z * k + g) * (4 * MA * NB);
+#pragma unroll
+            for (int nt = 0; nt < NTN; ++nt)
+#pragma unroll
+                for (int r = 0; r < 16; ++r)
+                    o[(size_t)(32 * mt + 8 * (r / 4) + 4 * kh + (r % 4)) * (2 * NB) + 32 * nt + col] = acc[nt][r];
+        } else {
+            float2* o = part + ((size_t)z * k + g) * (MA * NB);
+#pragma unroll
+            for (int nt = 0; nt < NTN; ++nt) {
+                const int nb = 32 * nt + col;
+                if (NB % 32 != 0 && nb >= NB) continue;
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+#pragma unroll
+                    for (int h = 0; h < 2; ++h)
+                        if (MA % 16 == 0 || 16 * mt + 4 * q4 + 2 * kh + h < MA) o[(16 * mt + 4 * q4 + 2 * kh + h) * NB + nb] = make_float2(acc[nt][4 * q4 + 2 * h], acc[nt][4 * q4 + 2 * h + 1]);
+            }
         }
     }
-    if constexpr (REAL) {
-        // acc[nt][r]: row 32*mt + 8*(r/4) + 4*kh + r%4, column 32*nt + col of the (2*MA) x (2*NB) block
-        float* o = reinterpret_cast<float*>(part) + ((size_t)z * k + g) * (4 * MA * NB);
+};
+
+// One factor's share of the backward in one launch: the gradient of its input, out = in W~ (cstage_kernel), and that of
+// its weights, part[z] = sum over its tiles of in^T conj(other) (WgradSums).  `in` comes from memory once for both; a
+// workgroup owns one block g and the row tiles z, z + Z, ..., and splits a tile of `in` into planes in both orders.
+// LDS: `in` as rows (where the results take their place on the way out in rows), `in` and `other` as weight-gradient
+// operands; 79.5 KiB at complex blocks of 64, so that two workgroups fit a CU.  In two launches `in` came twice and was
+// split twice.  Backward, with the sums of both gradients in one launch: 64 complex blocks of 64, 2048 rows 208 -> 187
+// us, 500 rows 86 -> 71; 48 of 48, 2048 rows 139 -> 110; 16 of 16, 64 rows 23.6 -> 15.5; real blocks, 64 of 64, 4000
+// rows 192 -> 179, 16384 rows 723 -> 604; 32 of 32, 400 rows 29.6 -> 21.6, 16384 rows 188 -> 162.
+template <int M, int IN, int OUT, int OTHER, bool REAL>
+__global__ void __launch_bounds__(kTileWaves<M> * 64, 2)
+cboth_kernel(const float2* __restrict__ in, const float2* __restrict__ W, const float2* __restrict__ other, float2* __restrict__ out,
+             float2* __restrict__ part, int64_t B, int k, int Z, int perm_b)
+{
+    constexpr int NTHR = kTileWaves<M> * 64;
+    using Tile = ActTile<M, NTHR, IN, REAL>;
+    using Sums = WgradSums<M, M, IN, OTHER, REAL>;
+    using Nat = NatOut<M, NTHR>;
+    using Tiled = TiledOut<M, OUT, REAL>;
+    static_assert(OUT != kOutNat || Nat::kLen * sizeof(float2) <= Tile::kLen * sizeof(bf16_t), "the results take the place of the rows");
+    extern __shared__ __align__(16) bf16_t both_lds[];
+    bf16_t *const act = both_lds, *const ta = act + Tile::kLen, *const tb = ta + Sums::TA::kLen;
+    float2* const ost = reinterpret_cast<float2*>(act);
+
+    const int g = (int)blockIdx.x / Z, z = (int)blockIdx.x - g * Z;
+    const int tid = threadIdx.x, lane = tid & 63, mt = tid >> 6;
+    const int col = lane & 31, kh = lane >> 5;
+    const int64_t ntiles = (B + kRT - 1) / kRT, ld = (int64_t)k * M;
+
+    bf16x8 A[M / 8][3];
+    load_weights<M, M, true, REAL>(A, W, g, mt, col, kh);
+    Tiled tiled;
+    tiled.init(g, mt, kh, col, k, perm_b != 0);
+    Sums sums;
+    sums.zero();
+    Tile pa;
+    typename Sums::TB pb;
+    int64_t rt = z;
+    if (rt < ntiles) {
+        pa.fetch(in, rt, g, k, ld, B, tid);
+        pb.fetch(other, rt, g, k, ld, B, tid);
+    }
+    for (; rt < ntiles; rt += Z) {
+        lds_barrier();
+        pa.template to_both<typename Sums::TA>(act, ta, tid);
+        pb.to_lds(tb, tid);
+        lds_barrier();
+        if (rt + Z < ntiles) {
+            pa.fetch(in, rt + Z, g, k, ld, B, tid);
+            pb.fetch(other, rt + Z, g, k, ld, B, tid);
+        }
+        f32x16 acc;
 #pragma unroll
-        for (int nt = 0; nt < NTN; ++nt)
+        for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-            for (int r = 0; r < 16; ++r)
-                o[(size_t)(32 * mt + 8 * (r / 4) + 4 * kh + (r % 4)) * (2 * NB) + 32 * nt + col] = acc[nt][r];
-    } else {
-        float2* o = part + ((size_t)z * k + g) * (MA * NB);
-#pragma unroll
-        for (int nt = 0; nt < NTN; ++nt) {
-            const int nb = 32 * nt + col;
-            if (NB % 32 != 0 && nb >= NB) continue;
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-#pragma unroll
-                for (int h = 0; h < 2; ++h)
-                    if (MA % 16 == 0 || 16 * mt + 4 * q4 + 2 * kh + h < MA) o[(16 * mt + 4 * q4 + 2 * kh + h) * NB + nb] = make_float2(acc[nt][4 * q4 + 2 * h], acc[nt][4 * q4 + 2 * h + 1]);
+        for (int t = 0; t < M / 8; ++t) {
+            bf16x8 xv[3];
+            Tile::read(xv, act, t, lane);
+            plane_products<3, 3>(A[t], xv, acc, acc);
+        }
+        stage_finish<M, M, IN, true, REAL>(acc, in, W, rt, g, mt, k, ld, B, lane);
+        if constexpr (OUT == kOutNat) {
+            lds_barrier();
+            Nat::put(ost, acc, mt, kh, col);
+        } else {
+            tiled.store(out, acc, rt, mt, kh, k);
+        }
+        sums.add_tile(ta, tb, mt, lane);
+        if constexpr (OUT == kOutNat) {
+            lds_barrier();
+            Nat::emit(ost, out, rt, g, ld, B, tid);
         }
     }
+    sums.finish(in, other, part, B, k, g, z, Z, ld, ld, mt, lane);
 }
 
-// out[e] = part[0][e] + part[1][e] + ... + part[Z-1][e], in that order; e counts float4s
-__global__ void __launch_bounds__(256) csum_kernel(const f32x4* __restrict__ part, f32x4* __restrict__ out, size_t n4, int Z)
+struct SumJob {
+    const f32x4* part;
+    f32x4* out;
+};
+// out[e] = part[0][e] + part[1][e] + ... + part[Z-1][e], in that order, for both gradients; e counts float4s
+__global__ void __launch_bounds__(256) csum_kernel(const SumJob first, const SumJob second, size_t n4, int Z)
 {
+    const f32x4* const part = blockIdx.y ? second.part : first.part;
+    f32x4* const out = blockIdx.y ? second.out : first.out;
     const size_t e = (size_t)blockIdx.x * 256 + threadIdx.x;
     if (e >= n4) return;
     f32x4 s = part[e];
@@ -1006,7 +1126,7 @@ __global__ void __launch_bounds__(256) csum_kernel(const f32x4* __restrict__ par
 }
 
 int64_t tiles_of(const Problem& pb) { return (pb.B + kRT - 1) / kRT; }
-size_t t_bytes(const Problem& pb) { return align_up((size_t)tiles_of(pb) * kRT * pb.kq() * sizeof(float2), 256); }
+size_t t_bytes(const Problem& pb, bool real) { return align_up((size_t)tiles_of(pb) * kRT * pb.kq() * (real ? sizeof(float) : sizeof(float2)), 256); }
 
 // workgroups of one block: about `target_waves` in all, a multiple of 8, at most one per tile.  A workgroup loads and
 // splits a block's weights before its first tile, so there are no more of them than stay resident: eight waves a CU (64
@@ -1022,6 +1142,8 @@ int splits_for(const Problem& pb, int waves_per_wg, int target_waves)
     return (int)(n < 1 ? 1 : n);
 }
 
+// Batch chunks of the weight gradients: 512 workgroups, no more than two of which fit a CU at blocks of 64 (with 1024,
+// 64 complex blocks of 64, 2048 rows, backward 194 -> 206 us, 48 112 -> 123, 64 real blocks of 64, 12000 rows 10 % more).
 int wgrad_chunks(const Problem& pb)
 {
     int64_t z = (512 + pb.k - 1) / pb.k;
@@ -1030,15 +1152,22 @@ int wgrad_chunks(const Problem& pb)
     if (z > t) z = t;
     return (int)(z < 1 ? 1 : z);
 }
+// Real blocks of 32 have workgroups of one wave: twice as many of them where each then still has two tiles (32 blocks,
+// 4000 rows, backward 58 -> 48 us, 16384 rows 197 -> 162; 20 blocks, 2000 rows, two tiles each before, 33 -> 37).
+int real_chunks(const Problem& pb)
+{
+    const int z = wgrad_chunks(pb);
+    return pb.p == 32 && tiles_of(pb) >= 4 * z ? 2 * z : z;
+}
 
 template <int M, int IN, int OUT, bool CONJT, bool REAL = false>
-int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hipStream_t st, void* tiles = nullptr)
+int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hipStream_t st)
 {
     const int nsplit = splits_for(pb, kTileWaves<M>, REAL && IN != kInGather ? 1024 : 2048);
     const int64_t grid = (int64_t)pb.k * nsplit;
     if (grid > 0x7fffffffLL) return -2;
     hipLaunchKernelGGL((cstage_kernel<M, M, IN, OUT, CONJT, REAL>), dim3((unsigned)grid), dim3(64 * kTileWaves<M>), 0, st, (const float2*)in,
-                       (const float2*)W, (float2*)out, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0, (float2*)tiles);
+                       (const float2*)W, (float2*)out, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0);
     return hip_status(hipGetLastError());
 }
 
@@ -1069,18 +1198,18 @@ int launch_scatter8(const Problem& pb, const void* T, const void* W, void* out, 
     return hip_status(hipGetLastError());
 }
 
-template <int M, bool EMIT, bool REAL, int MTW>
-int launch_gather8_tiles(const Problem& pb, const void* in, const void* W, void* out, void* dwt, hipStream_t st)
+template <int M, bool REAL, int MTW>
+int launch_gather8_tiles(const Problem& pb, const void* in, const void* W, void* out, hipStream_t st)
 {
     constexpr int MTG = kTileWaves<M> / MTW;
     const int nsplit = splits8_for(pb, MTG);
     const int64_t grid = (int64_t)(pb.k / 8) * MTG * nsplit;
     if (grid > 0x7fffffffLL) return -2;
-    auto kern = cgather8_kernel<M, M, EMIT, REAL, MTW>;
+    auto kern = cgather8_kernel<M, M, REAL, MTW>;
     constexpr size_t lds = Gather8<M>::kLds;
     if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess) return -4;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), lds, st, (const float2*)in, (const float2*)W,
-                       (float2*)out, (float2*)dwt, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0);
+                       (float2*)out, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0);
     return hip_status(hipGetLastError());
 }
 
@@ -1088,51 +1217,44 @@ int launch_gather8_tiles(const Problem& pb, const void* in, const void* W, void*
 // the real layers with blocks of 64 whose rows take more than 64 MB, so that they come from memory once (x M, 64
 // blocks: 2000 rows, 33 MB, 39 us with one and 43 with two; 6000 rows 128 and 106, 30000 rows 616 and 485; 32 blocks,
 // 6000 rows, 49 MB, 52 and 53, 12000 rows 122 and 100).
-template <int M, bool EMIT, bool REAL = false>
-int launch_gather8(const Problem& pb, const void* in, const void* W, void* out, void* dwt, hipStream_t st)
+template <int M, bool REAL = false>
+int launch_gather8(const Problem& pb, const void* in, const void* W, void* out, hipStream_t st)
 {
-    if constexpr (REAL && M == 32 && !EMIT) {
-        if (pb.B * pb.n_out() * (int64_t)sizeof(float) > (64LL << 20)) return launch_gather8_tiles<M, EMIT, REAL, 2>(pb, in, W, out, dwt, st);
+    if constexpr (REAL && M == 32) {
+        if (pb.B * pb.n_out() * (int64_t)sizeof(float) > (64LL << 20)) return launch_gather8_tiles<M, REAL, 2>(pb, in, W, out, st);
     }
-    return launch_gather8_tiles<M, EMIT, REAL, 1>(pb, in, W, out, dwt, st);
+    return launch_gather8_tiles<M, REAL, 1>(pb, in, W, out, st);
 }
 
-// lda, ldb: row lengths of row-major operands in float2 units
-template <int M, int AMODE, int BMODE, bool REAL = false>
-int launch_wgrad(const Problem& pb, const void* A, const void* Bv, void* out, void* part, int64_t lda, int64_t ldb,
-                 hipStream_t st)
+template <int M, int IN, int OUT, int OTHER, bool REAL>
+int launch_both(const Problem& pb, const void* in, const void* W, const void* other, void* out, void* part, int Z, hipStream_t st)
 {
-    const int Z = wgrad_chunks(pb);
     const int64_t grid = (int64_t)pb.k * Z;
     if (grid > 0x7fffffffLL) return -2;
-    float2* dst = Z == 1 ? (float2*)out : (float2*)part;
-    auto kern = cwgrad_kernel<M, M, AMODE, BMODE, REAL>;
-    const size_t lds = (size_t)(WgTile<M, 64 * kTileWaves<M>, AMODE, REAL>::kLen + WgTile<M, 64 * kTileWaves<M>, BMODE, REAL>::kLen) * sizeof(bf16_t);
+    auto kern = cboth_kernel<M, IN, OUT, OTHER, REAL>;
+    using Sums = WgradSums<M, M, IN, OTHER, REAL>;
+    constexpr size_t lds = (size_t)(ActTile<M, Sums::NTHR, IN, REAL>::kLen + Sums::TA::kLen + Sums::TB::kLen) * sizeof(bf16_t);
     if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess) return -4;
-    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(64 * kTileWaves<M>), lds, st, (const float2*)A, (const float2*)Bv, dst, pb.B,
-                       pb.k, Z, lda, ldb);
-    int rc = hip_status(hipGetLastError());
-    if (rc || Z == 1) return rc;
-    const size_t n4 = (size_t)pb.k * M * M / (REAL ? 1 : 2);  // float4s of one gradient: (2M)^2 floats, or M^2 complex values, per block
-    hipLaunchKernelGGL(csum_kernel, dim3((unsigned)((n4 + 255) / 256)), dim3(256), 0, st, (const f32x4*)part, (f32x4*)out, n4, Z);
+    hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(Sums::NTHR), lds, st, (const float2*)in, (const float2*)W, (const float2*)other,
+                       (float2*)out, (float2*)part, pb.B, pb.k, Z, pb.perm_b() ? 1 : 0);
     return hip_status(hipGetLastError());
 }
 
-// How dy gets into tiles: by a launch of its own (ctile_kernel), or by a stage that gathers it.
-//
-// The stage that gathers eight blocks side by side (multiples of eight) reads dy and lays it out once per M tile: not
-// for complex blocks with four M tiles (2048 rows: 28 + 40 us with the launch, 87 without; two: 8 + 13 against 14),
-// nor for real blocks of 64 (12000 rows, dy larger than the caches: 69 + 107 against 232).
-template <int M, bool REAL = false>
-constexpr bool kRelay = REAL ? M == 32 : M >= 56;
-// The stage that gathers one block does it where the launch would cost more than it saves: up to 3 MB, and up to
-// seven blocks, which leave ctile_kernel's lanes little to do.  Whole backward with the launch and without: 7 real
-// blocks of 32, 200 rows 26.5 and 24.2 us, 12000 rows 68.6 and 63.5; 20 blocks, 2000 rows 45.2 and 46.5, 12000 rows
-// 96.6 and 112; 1 block of 64, 30000 rows 124 and 98; 33 blocks, 500 rows 48.1 and 48.0, 2000 rows 79.7 and 93.0; 12
-// complex blocks of 32, 1000 rows 38.6 and 35.9, 8000 rows 85.8 and 87.6.
-bool lays_out(const Problem& pb, size_t value)
+// How dy gets to the backward's first factor: gathered by its workgroups in pieces of one value, or laid out in tiles by
+// a launch of its own (ctile_kernel), which costs a pass over it.  Up to seven blocks leave that launch's lanes little
+// to do.  Otherwise the pieces lose where they come from memory again and again: with many blocks from 4.5 MB on, with
+// large complex blocks, and else beyond 18 MB.  Whole backward with the launch and without: 7 complex blocks of 64,
+// 2048 rows 53.0 and 45.8 us; 32 of 32, 500 rows (4.1 MB) 30.7 and 27.5, 2048 rows 56.2 and 53.1; 48 of 48, 500 rows
+// 54.9 and 53.0; 24 of 24, 6000 rows (28 MB) 78.7 and 74.8; 64 of 64, 64 rows 32.4 and 30.9, 200 rows (6.5 MB) 47.7 and
+// 49.7; 12 of 64, 1500 rows (9 MB) 63.3 and 66.4; real blocks, 16 of 32, 8000 rows 52.1 and 47.0; 20 of 32, 2000 rows
+// 33.0 and 29.3; 32 of 32, 1000 rows (4.1 MB) 29.2 and 27.0, 2500 rows (10 MB) 40.1 and 42.0; 64 of 64, 256 rows 39.5
+// and 37.7, 330 rows (5.4 MB) 45.1 and 47.3.
+template <int M, bool REAL>
+bool gathers(const Problem& pb)
 {
-    return pb.k < 8 || (size_t)pb.B * pb.n_out() * value <= (3u << 20);
+    const bool far = REAL ? pb.k >= 32 : pb.k > 48 || M >= 56;
+    const size_t bytes = (size_t)pb.B * pb.n_out() * (REAL ? sizeof(float) : sizeof(float2));
+    return pb.B == 0 || pb.k < 8 || bytes <= (far ? (size_t)9 << 19 : (size_t)18 << 20);
 }
 
 template <int M, bool REAL = false>
@@ -1157,42 +1279,41 @@ int run_fwd(const Problem& pb, const void* x, const void* R, const void* L, void
 template <int M>
 int run_fwd_h(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
 {
-    int rc = pb.k % 8 == 0 ? launch_gather8<M, false>(pb, x, L, ws, nullptr, st)
+    int rc = pb.k % 8 == 0 ? launch_gather8<M>(pb, x, L, ws, st)
                            : launch_stage<M, kInGather, kOutTBwd, true>(pb, x, L, ws, st);
     if (rc) return rc;
     return launch_stage<M, kInT, kOutNat, true>(pb, ws, R, y, st);
 }
 
-template <int M>
+template <int M, bool REAL = false>
 int run_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR, void* dL,
             void* ws, hipStream_t st)
 {
-    char* w = (char*)ws;
-    void* Ut = w;
-    void* dY1t = w + t_bytes(pb);
-    void* dWt = w + 2 * t_bytes(pb);
-    void* part = w + 3 * t_bytes(pb);
-    int rc = launch_stage<M, kInNat, kOutTFwd, false>(pb, x, R, Ut, st);
+    const size_t mid = t_bytes(pb, REAL);
+    char* const w = (char*)ws;
+    void *const Ut = w, *const dWt = w + mid, *const dY1t = w + 2 * mid;
+    const int Z = REAL && pb.ws_bytes >= real32_mfma_workspace(pb, 1) ? real_chunks(pb) : wgrad_chunks(pb);
+    // the second factor's partial sums take the place of U and dW, which the first has read: Z <= the row tiles of 32,
+    // so that Z M^2 k values fit two times 32 M k for each
+    void* const partL = Z > 1 ? (void*)(w + 3 * mid) : dL;
+    void* const partR = Z > 1 ? (void*)w : dR;
+    int rc = launch_stage<M, kInNat, kOutTFwd, false, REAL>(pb, x, R, Ut, st);
     if (rc) return rc;
-    if (!kRelay<M> && pb.k % 8 == 0) {
-        rc = launch_gather8<M, true>(pb, dy, L, dY1t, dWt, st);
-    } else if (lays_out(pb, sizeof(float2))) {
-        rc = launch_stage<M, kInGather, kOutTBwd, true>(pb, dy, L, dY1t, st, dWt);
+    if (gathers<M, REAL>(pb)) {
+        rc = launch_both<M, kInGather, kOutTBwd, kInT, REAL>(pb, dy, L, Ut, dY1t, partL, Z, st);
     } else {
-        rc = launch_tile<M>(pb, dy, dWt, st);
-        if (!rc) rc = launch_stage<M, kInT, kOutTBwd, true>(pb, dWt, L, dY1t, st);
+        rc = launch_tile<M, REAL>(pb, dy, dWt, st);
+        if (!rc) rc = launch_both<M, kInT, kOutTBwd, kInT, REAL>(pb, dWt, L, Ut, dY1t, partL, Z, st);
     }
-    if (rc) return rc;
-    rc = launch_stage<M, kInT, kOutNat, true>(pb, dY1t, R, dx, st);
-    if (rc) return rc;
-    rc = launch_wgrad<M, kInT, kInT>(pb, dWt, Ut, dL, part, 0, 0, st);
-    if (rc) return rc;
-    return launch_wgrad<M, kInT, kInNat>(pb, dY1t, x, dR, part, 0, pb.n_in, st);
+    if (!rc) rc = launch_both<M, kInT, kOutNat, kInNat, REAL>(pb, dY1t, R, x, dx, partR, Z, st);
+    if (rc || Z == 1) return rc;
+    const size_t n4 = (size_t)pb.k * M * M / (REAL ? 1 : 2);  // float4s of one gradient: (2M)^2 floats, or M^2 complex values, per block
+    hipLaunchKernelGGL(csum_kernel, dim3((unsigned)((n4 + 255) / 256), 2), dim3(256), 0, st, SumJob{(const f32x4*)partL, (f32x4*)dL},
+                       SumJob{(const f32x4*)partR, (f32x4*)dR}, n4, Z);
+    return hip_status(hipGetLastError());
 }
 
 // ---- real fp32 layers with square blocks of 32 or 64 on the same kernels (REAL): M = block size / 2 ----
-size_t rt_bytes(const Problem& pb) { return align_up((size_t)tiles_of(pb) * kRT * pb.kq() * sizeof(float), 256); }
-
 template <int M>
 int run_real_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
 {
@@ -1205,37 +1326,10 @@ int run_real_fwd(const Problem& pb, const void* x, const void* R, const void* L,
 template <int M>
 int run_real_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
 {
-    int rc = pb.k % 8 == 0 ? launch_gather8<M, false, true>(pb, x, L, ws, nullptr, st)
+    int rc = pb.k % 8 == 0 ? launch_gather8<M, true>(pb, x, L, ws, st)
                            : launch_stage<M, kInGather, kOutTBwd, true, true>(pb, x, L, ws, st);
     if (rc) return rc;
     return launch_stage<M, kInT, kOutNat, true, true>(pb, ws, R, y, st);
-}
-
-template <int M>
-int run_real_bwd(const Problem& pb, const void* dy, const void* x, const void* R, const void* L, void* dx, void* dR,
-                 void* dL, void* ws, hipStream_t st)
-{
-    char* w = (char*)ws;
-    void* Ut = w;
-    void* dY1t = w + rt_bytes(pb);
-    void* dWt = w + 2 * rt_bytes(pb);
-    void* part = w + 3 * rt_bytes(pb);
-    int rc = launch_stage<M, kInNat, kOutTFwd, false, true>(pb, x, R, Ut, st);
-    if (rc) return rc;
-    if (!kRelay<M, true> && pb.k % 8 == 0) {
-        rc = launch_gather8<M, true, true>(pb, dy, L, dY1t, dWt, st);
-    } else if (lays_out(pb, sizeof(float))) {
-        rc = launch_stage<M, kInGather, kOutTBwd, true, true>(pb, dy, L, dY1t, st, dWt);
-    } else {
-        rc = launch_tile<M, true>(pb, dy, dWt, st);
-        if (!rc) rc = launch_stage<M, kInT, kOutTBwd, true, true>(pb, dWt, L, dY1t, st);
-    }
-    if (rc) return rc;
-    rc = launch_stage<M, kInT, kOutNat, true, true>(pb, dY1t, R, dx, st);
-    if (rc) return rc;
-    rc = launch_wgrad<M, kInT, kInT, true>(pb, dWt, Ut, dL, part, 0, 0, st);
-    if (rc) return rc;
-    return launch_wgrad<M, kInT, kInNat, true>(pb, dY1t, x, dR, part, 0, pb.n_in / 2, st);
 }
 
 }  // namespace
@@ -1246,12 +1340,15 @@ bool real32_mfma_supported(const Problem& pb)
 }
 
 // pass: 0 forward, 1 backward, 2 transposed multiply
+static size_t real32_bwd_bytes(const Problem& pb, int Z)
+{
+    return 3 * t_bytes(pb, true) + (Z > 1 ? align_up((size_t)Z * pb.n_L() * sizeof(float), 256) : 0);
+}
 size_t real32_mfma_workspace(const Problem& pb, int pass)
 {
-    if (pass != 1) return rt_bytes(pb);
-    const int Z = wgrad_chunks(pb);
-    return 3 * rt_bytes(pb) + (Z > 1 ? align_up((size_t)Z * pb.n_L() * sizeof(float), 256) : 0);
+    return pass != 1 ? t_bytes(pb, true) : real32_bwd_bytes(pb, real_chunks(pb));
 }
+size_t real32_mfma_bwd_least(const Problem& pb) { return real32_bwd_bytes(pb, wgrad_chunks(pb)); }
 
 int real32_mfma_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)
 {
@@ -1270,7 +1367,7 @@ int real32_mfma_bwd(const Problem& pb, const void* dy, const void* x, const void
         const int rc = launch_fill_zero_f32((float*)dR, pb.n_R(), st);
         return rc ? rc : launch_fill_zero_f32((float*)dL, pb.n_L(), st);
     }
-    return pb.p == 32 ? run_real_bwd<16>(pb, dy, x, R, L, dx, dR, dL, ws, st) : run_real_bwd<32>(pb, dy, x, R, L, dx, dR, dL, ws, st);
+    return pb.p == 32 ? run_bwd<16, true>(pb, dy, x, R, L, dx, dR, dL, ws, st) : run_bwd<32, true>(pb, dy, x, R, L, dx, dR, dL, ws, st);
 }
 
 bool complex_mfma_supported(const Problem& pb)
@@ -1281,9 +1378,9 @@ bool complex_mfma_supported(const Problem& pb)
 // pass: 0 forward, 1 backward, 2 conjugate-transpose forward
 size_t complex_mfma_workspace(const Problem& pb, int pass)
 {
-    if (pass != 1) return t_bytes(pb);
+    if (pass != 1) return t_bytes(pb, false);
     const int Z = wgrad_chunks(pb);
-    return 3 * t_bytes(pb) + (Z > 1 ? align_up((size_t)Z * pb.n_L() * sizeof(float2), 256) : 0);
+    return 3 * t_bytes(pb, false) + (Z > 1 ? align_up((size_t)Z * pb.n_L() * sizeof(float2), 256) : 0);
 }
 
 int complex_mfma_fwd(const Problem& pb, const void* x, const void* R, const void* L, void* y, void* ws, hipStream_t st)

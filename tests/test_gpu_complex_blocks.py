@@ -140,3 +140,43 @@ def test_layouts_of_dy(case, reading):
         g, w = (t.reshape(t.shape[0], -1).to(torch.complex128) for t in (g, w))
         rel = torch.linalg.norm(g - w, dim=1) / torch.linalg.norm(w, dim=1)
         assert float(rel.max()) <= 1e-5, (name, float(rel.max()))
+
+
+# The same on either side of the lines between gathering dy and laying it out first, and with either number of batch chunks.
+BOTH = [(1181, 32, 33, True), (1301, 32, 35, True), (10001, 64, 8, True), (2305, 32, 32, True), (4001, 32, 32, True), (1, 64, 3, True),
+        (1250, 64, 12, False), (2049, 64, 4, False), (8301, 24, 12, False), (1501, 16, 56, False), (65, 56, 49, False)]
+
+
+@pytest.mark.parametrize("case", BOTH, ids=str)
+def test_gradients_of_a_factor_in_one_launch(case):
+    test_layouts_of_dy(case, 0)
+
+
+@pytest.mark.parametrize("case", [(160, 64, 64), (161, 56, 56)], ids=str)
+def test_values_that_three_bf16_planes_cannot_hold_in_tiles(case):
+    test_values_that_three_bf16_planes_cannot_hold(case)
+
+
+def test_real_layers_with_such_values_in_tiles():
+    test_real_layers_with_values_that_three_bf16_planes_cannot_hold((330, 64, 64))
+
+
+# A workspace with room for half of the chunks of 32 blocks of 32 is taken as before.
+def test_fewer_chunks_in_a_shorter_workspace():
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, m, k = 4001, 32, 32
+    x, R, L, dy = (torch.from_numpy(synth.normal(9100 + i, shp, std).astype(np.float32)).cuda() for i, (shp, std) in enumerate(
+        (((rows, k * m), 1.0), ((k, m, m), m ** -0.5), ((k, m, m), m ** -0.5), ((rows, k * m), 1.0))))
+    need = B.monarch_bwd_workspace_bytes(rows, k * m, k, m, m, B.MONARCH_F32)
+    least = need - 16 * k * m * m * 4   # sixteen chunks of thirty-two
+    want = B.monarch_bwd(dy, x, R, L, flags=B.MONARCH_FLAG_GENERIC)
+    for room in (need, need - 256, least):
+        ws = torch.full((room + 256,), 0xA5, dtype=torch.uint8, device="cuda")
+        got = B.monarch_bwd(dy, x, R, L, workspace=ws[:room])
+        assert bool((ws[room:] == 0xA5).all())
+        for name, g, w in zip(("dx", "dR", "dL"), got, want):
+            assert float((g - w).double().norm()) <= 1e-5 * float(w.double().norm()), (room, name)
+    with pytest.raises(Exception):
+        B.monarch_bwd(dy, x, R, L, workspace=torch.empty(least - 256, dtype=torch.uint8, device="cuda"))
