@@ -271,7 +271,12 @@ int bwd_layer(const void* dy, const void* x, const void* x_pre, const void* save
         }
     }
     if (!workspace || !aligned(workspace, 256)) return MONARCH_ERR_WORKSPACE;
+    pb.act_split = x_pre != nullptr;
     pb.ws_bytes = bwd_kernel_room(pb, fam, workspace_bytes);
+    if (pb.ws_bytes == (size_t)-1 && pb.act_split) {
+        pb.act_split = false;
+        pb.ws_bytes = bwd_kernel_room(pb, fam, workspace_bytes);
+    }
     if (pb.ws_bytes == (size_t)-1) return MONARCH_ERR_WORKSPACE;
     hipStream_t st = (hipStream_t)stream;
     if (dbias) {

@@ -19,6 +19,7 @@ struct Problem {
     void* y_pre = nullptr;       // forward with act: the value before the nonlinearity also goes here (may be null)
     size_t ws_bytes = 0;         // forward with a workspace: its size; backward: bytes of the kernels' own area
     void* mid = nullptr;         // forward on packed weights, which it only reads: fwd_split_mid_bytes() of the call's own (may be null)
+    bool act_split = false;      // backward only: the nonlinearity's factor is wanted, the kernels of short batches may take it further
     const void* x_pre = nullptr; // backward only: the layer's input is gelu(x_pre); dx is returned with respect to x_pre
     int n_out() const { return k * s; }
     int kq() const { return k * q; }

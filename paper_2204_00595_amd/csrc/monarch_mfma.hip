@@ -108,7 +108,12 @@ bool mfma_bwd_supported(const Problem& pb)
 size_t mfma_bwd_workspace(const Problem& pb)
 {
     if (bwd_split_preferred(pb)) return bwd_split_workspace(pb);
-    if (bwd_wide_supported(pb)) return bwd_wide_workspace(pb);
+    if (bwd_wide_supported(pb)) {  // whoever asks for the size does not say whether the nonlinearity's factor will be wanted
+        Problem act = pb;
+        act.act_split = true;
+        const size_t wide = bwd_wide_workspace(pb), split = bwd_split_preferred(act) ? bwd_split_workspace(act) : 0;
+        return wide > split ? wide : split;
+    }
     if (bwd_sq64_supported(pb)) return bwd_sq64_workspace(pb);
     if (sq16_supported(pb)) return bwd_sq16_workspace(pb);
     if (tiled_bwd_supported(pb)) return tiled_bwd_workspace(pb);

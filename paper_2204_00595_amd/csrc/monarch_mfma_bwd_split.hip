@@ -70,8 +70,11 @@ bwd_split_prep_kernel(const BwdPrep w, int64_t B, SplitGrid gr)
 }
 
 // NS: K-steps of a wave, at most (see tile_product).  ACT: the result is multiplied by gelu'(x_pre).
+// The bounds on the registers keep two workgroups to a CU, three where the loads are few: left alone, the compiler kept
+// copies of the sums and took 290, for one (256 rows of dU x 1024 columns, 2000 rows: 27.4 us, now 17.0; with the
+// nonlinearity's factor, 700 rows 17.2, now 13.0).
 template <int NT, int NS, bool ACT>
-__global__ void __launch_bounds__(256)
+__global__ void __launch_bounds__(256, NT == 1 && NS <= 4 ? 3 : 2)
 adjoint_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ WT, uint16_t* __restrict__ out,
                const uint16_t* __restrict__ x_pre, int64_t B, int M, int N, SplitGrid gr)
 {
@@ -132,12 +135,21 @@ adjoint_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ WT,
         if (t + BUF < NS) load(t + BUF, t % BUF);
     }
 
+    auto at = [&](int j, int q4) { return (size_t)(b0 + ln) * 4 * N + wave * N + (nt0 + j) * 32 + 8 * q4 + 4 * h; };
+    u32x2 pre[ACT ? NT : 1][4];  // what the results of block `wave` are multiplied with
     lds_barrier();  // the sums take the place of the rows
     // the waves' sums: wave w hands two blocks to wave w ^ 2, then one to wave w ^ 1, and keeps block w
     auto slot = [&](int owner, int g, int j, int q4) { return (((owner * 2 + g) * NT + j) * 4 + q4) * 64 + lane; };
 #pragma unroll
     for (int round = 0; round < 2; ++round) {
         const int bit = 2 >> round;
+        if (ACT && round) {  // on its way during the second round: before the first there are no registers for it
+#pragma unroll
+            for (int j = 0; j < NT; ++j)
+#pragma unroll
+                for (int q4 = 0; q4 < 4; ++q4)
+                    pre[j][q4] = ln < rows && nt0 + j < NTT ? *reinterpret_cast<const u32x2*>(x_pre + at(j, q4)) : u32x2{0, 0};
+        }
         if (round) lds_barrier();  // the first round's values have been read
 #pragma unroll
         for (int g = 0; g < 4; ++g) {
@@ -171,16 +183,15 @@ adjoint_kernel(const uint16_t* __restrict__ in, const uint16_t* __restrict__ WT,
             if (nt0 + j >= NTT) continue;
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4) {
-                const size_t to = (size_t)(b0 + ln) * 4 * N + g * N + (nt0 + j) * 32 + 8 * q4 + 4 * h;
                 float v[4] = {acc[g][j][4 * q4], acc[g][j][4 * q4 + 1], acc[g][j][4 * q4 + 2], acc[g][j][4 * q4 + 3]};
                 if constexpr (ACT) {
-                    const u32x2 pre = *reinterpret_cast<const u32x2*>(x_pre + to);
-                    v[0] *= gelu_grad_f(__uint_as_float(pre[0] << 16));
-                    v[1] *= gelu_grad_f(__uint_as_float(pre[0] & 0xffff0000u));
-                    v[2] *= gelu_grad_f(__uint_as_float(pre[1] << 16));
-                    v[3] *= gelu_grad_f(__uint_as_float(pre[1] & 0xffff0000u));
+                    const u32x2 u = pre[j][q4];
+                    v[0] *= gelu_grad_f(__uint_as_float(u[0] << 16));
+                    v[1] *= gelu_grad_f(__uint_as_float(u[0] & 0xffff0000u));
+                    v[2] *= gelu_grad_f(__uint_as_float(u[1] << 16));
+                    v[3] *= gelu_grad_f(__uint_as_float(u[1] & 0xffff0000u));
                 }
-                *reinterpret_cast<u32x2*>(out + to) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
+                *reinterpret_cast<u32x2*>(out + at(j, q4)) = u32x2{pack_bf16x2(v[0], v[1]), pack_bf16x2(v[2], v[3])};
             }
         }
     }
@@ -224,7 +235,7 @@ int adjoint(const uint16_t* in, const uint16_t* WT, uint16_t* out, const void* x
 template <int NT>
 int launch_prep(const BwdPrep& w, int64_t B, const SplitGrid& gr, unsigned blocks, hipStream_t st)
 {
-    constexpr size_t lds = split_stage1_lds<1, NT, (NT > 1)>();
+    constexpr size_t lds = split_stage1_lds<1, NT, true>();
     const int ng = ((w.P / 16 + 3) / 4 + 3) / 4;
     auto kern = ng == 1 ? bwd_split_prep_kernel<NT, 1> : ng == 2 ? bwd_split_prep_kernel<NT, 2>
               : ng == 3 ? bwd_split_prep_kernel<NT, 3> : bwd_split_prep_kernel<NT, 4>;
@@ -282,24 +293,28 @@ Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 
 }  // namespace
 
-// Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows, 2048 where the
-// output is narrower than the input (dx is then the larger product, and every workgroup reads the rows of dU again),
-// and no more than 2^19 / q, where `adjoint` runs out of workgroups of one column tile.  Whole backward with bias on
-// these kernels and on the wide one, in brackets with the nonlinearity's factor: blocks of 256 and 1024, 300 rows 36
-// and 63 us, 2000 rows 54 and 68 (55 and 74), 2300 rows 72 and 69; of 192 and 768, 2500 rows 48 and 55, 3000 rows 64
-// and 55; of 192, 2500 rows 39 and 40 (40 and 44), 3000 rows 52 and 40; of 256, 2000 rows 42 and 46, 2300 rows 55 and
-// 46; of 1024 and 256, 1500 rows 66 and 70 (69 and 94), 2000 rows 77 and 71 (81 and 95), 2300 rows 93 and 72 (98 and
-// 97); of 768 and 192, 1500 rows 56 and 54 (60 and 71), 2300 rows 66 and 55 (71 and 72).  Not for blocks of 64 alone
-// (8 rows 19 and 18, 1000 rows 22 and 21).  Where the other choice is the shape-generic bf16 kernel (width 384) up to
-// 4096.  Not where it is the shape-generic contractions (q = 256 with p or s = 1024), which hold the vectors between
-// the factors in fp32.
+// Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows (3000 for wide
+// outputs of 256 blocks; 2048 for others with blocks of 256, where `adjoint` runs out of workgroups, and where the
+// output is narrower than the input: dx is then the larger product, and every workgroup reads the rows of dU again).
+// Training step on these kernels and on the wide one: blocks of 256 and 1024, 2200 rows 83 and 88 us, 3000 rows 87 and
+// 91; of 192 and 768, 2200 rows 62 and 61, 3000 rows 71 and 71; of 192, 2200 rows 54 and 53, 3000 rows 59 and 57; of
+// 256, 2200 rows 61 and 62, 3000 rows 66 and 64; of 1024 and 256, 2200 rows 94 and 94, 3000 rows 102 and 98; of 768 and
+// 192, 2200 rows 75 and 73, 3000 rows 82 and 75.  Up to 4096 where the nonlinearity's factor comes with a narrower
+// output (`act_split`), which costs the wide kernel the time of its products again (prep and both adjoint steps, 1024
+// and 256: 2200 rows 50 and 69, 4000 rows 71 and 76; 768 and 192, 4000 rows 50 and 53).  Not for blocks of 64 alone (8
+// rows 19 and 18, 1000 rows 22 and 21).
+// Where the other choice is the shape-generic bf16 kernel (width 384): up to 4096 rows for square layers (6000 rows 61
+// and 65, 8000 rows 70 and 69), 16384 for others (96 x 384 blocks, 6000 rows 69 and 76, 12000 rows 90 and 117; 384 x 96
+// 75 and 78, 112 and 124; 96 x 288 67 and 69, 88 and 100).  Not where it is the shape-generic contractions (q = 256
+// with p or s = 1024), which hold the vectors between the factors in fp32.
 bool bwd_split_preferred(const Problem& pb)
 {
     const bool wide = bwd_wide_supported(pb);
-    if (!wide && !tiled_bwd_supported(pb)) return false;
-    if (wide && (pb.B * pb.q > (1 << 19) || pb.B > (pb.s < pb.p ? 2048 : 2560) || (pb.p == 64 && pb.s == 64))) return false;
+    if ((!wide && !tiled_bwd_supported(pb)) || (wide && pb.p == 64 && pb.s == 64)) return false;
+    const int64_t most = !wide ? (pb.p == pb.s ? 4096 : 16384)
+                       : pb.s < pb.p ? (pb.act_split ? 4096 : 2048) : pb.q <= 192 ? 2560 : pb.s > pb.p ? 3000 : 2048;
     return pb.dtype == 1 && pb.k == 4 && !pb.perm_b() && pb.p % 32 == 0 && pb.q % 32 == 0 && pb.s % 32 == 0 && pb.p <= 1024 &&
-           pb.s <= 1024 && pb.q <= 256 && pb.B > 0 && pb.B <= 4096 && make_plan(pb).ok;
+           pb.s <= 1024 && pb.q <= 256 && pb.B > 0 && pb.B <= most && make_plan(pb).ok;
 }
 
 size_t bwd_split_workspace(const Problem& pb) { return make_plan(pb).total; }

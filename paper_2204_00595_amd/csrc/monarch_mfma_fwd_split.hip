@@ -78,7 +78,7 @@ split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__
 #pragma unroll
     for (int j = 0; j < NT; ++j) w_at[j] = lt0 + j < LT ? (uint32_t)((lt0 + j) * KS * 1024 + lane * 16) : kNowhere;
     static_assert(NB == 1, "a tile of U has the rows of the workgroup");
-    tile_product<NB, NT, NG, AHEAD, false, false>(U + b0 * 4 * Q + c * KS * rows * 16, a_at, (uint32_t)rows * 32, LF2 + (size_t)c * LT * KS * 512, w_at,
+    tile_product<NB, NT, NG, AHEAD, false, false, false>(U + b0 * 4 * Q + c * KS * rows * 16, a_at, (uint32_t)rows * 32, LF2 + (size_t)c * LT * KS * 512, w_at,
                                                   1024u, KS, acc, 0u, 0, nullptr);
 
 #pragma unroll
@@ -248,7 +248,7 @@ int launch_stage(const Problem& pb, int stage, const SplitArgs& a, hipStream_t s
     if (stage == 1) {
         const SplitGrid gr = split_grid(pb.B, 32 * NB, 4 * ((pb.q / 32 + NT - 1) / NT), &blocks);
         constexpr bool kTurn = NT > 1;  // many tiles: launch_factor
-        constexpr size_t lds = split_stage1_lds<NB, NT, kTurn>();
+        const size_t lds = pb.ws_packed() ? split_stage1_lds<NB, NT, kTurn>() : split_stage1_lds<NB, NT, true>();
         auto kern = pb.ws_packed() ? split_stage1_kernel<NB, NT, NG, AHEAD, false, kTurn> : split_stage1_kernel<NB, NT, NG, AHEAD, true, kTurn>;
         SplitPack w = a.w;
         w.blocks = (int)blocks;
@@ -317,14 +317,15 @@ bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
            pb.q <= 256;
 }
 
-// Where there is a fused kernel, up to 3072 rows (48 of its row tiles; it takes the same time for any number of them):
-// 1024 -> 4096 -> 1024, both layers with the nonlinearity, 2600 rows 70 and 46 us; 768 -> 3072 alone 3500 rows 17.4 and
-// 21.3, 3072 -> 768 28.0 and 27.0; 512 -> 2048 alone 13.2 and 15.3, 2048 -> 512 17.1 and 15.2.  Where the other choice
+// Where there is a fused kernel, up to 3072 rows (48 of its row tiles; it takes the same time for any number of them),
+// and up to 6144 where the output is narrower than the input: 1024 -> 4096 -> 1024, both layers with the nonlinearity,
+// 2600 rows 70 and 46 us; 768 -> 3072 alone, 4000 rows 20.2 and 22.9, 3072 -> 768 31.8 and 18.9; 512 -> 2048 alone,
+// 4000 rows 18.9 and 19.5, 2048 -> 512 17.6 and 12.3, 6000 rows 18.2 and 16.  Where the other choice
 // is the shape-generic kernel (width 384: 47 us for 300 rows, 60 for 8000), up to 8192.  And only where it all fits the
 // static workspace, so that monarch_fwd_static runs the same kernels as monarch_fwd_ws.
 bool fwd_split_preferred(const Problem& pb)
 {
-    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= (fwd_frag_supported(pb) ? 3072 : 8192) &&
+    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= (!fwd_frag_supported(pb) ? 8192 : pb.s < pb.p ? 6144 : 3072) &&
            fwd_frag_packed(pb) + fwd_split_mid_bytes(pb) <= MONARCH_STATIC_WORKSPACE_BYTES;
 }
 

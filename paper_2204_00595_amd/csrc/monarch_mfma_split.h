@@ -49,7 +49,8 @@ struct RowPieces {
 // `AHEAD` such groups ahead; the trip count is a template parameter because loads past the end, even of nothing, cost
 // as much as real ones.
 // TURN (NB = 1): the rows, of a_ld bytes, are read in whole lines (RowPieces); a_at is the uniform offset of the first.
-template <int NB, int NT, int NG, int AHEAD, bool W_FIRST, bool TURN>
+// W_TURN: so are the weights, whose rows have w_step bytes; w_at is the uniform offset of each tile's first row.
+template <int NB, int NT, int NG, int AHEAD, bool W_FIRST, bool TURN, bool W_TURN>
 __device__ __forceinline__ void tile_product(const void* a, const uint32_t (&a_at)[NB], uint32_t a_step, const void* w, const uint32_t (&w_at)[NT],
                                              uint32_t w_step, int steps, f32x16 (&acc)[NB][NT], uint32_t a_ld, int rows, uint16_t* lds)
 {
@@ -57,8 +58,7 @@ __device__ __forceinline__ void tile_product(const void* a, const uint32_t (&a_a
     constexpr int G = 4, BUF = AHEAD < NG ? AHEAD : NG;
     const int lane = threadIdx.x & 63;
     const auto ra = buffer_at(a), rw = buffer_at(w);
-    RowPieces af[BUF][NB];
-    u32x4 wf[BUF][G][NT];
+    RowPieces af[BUF][NB], wf[BUF][NT];
     auto load = [&](int gr, int buf) {
         if constexpr (TURN) {
             af[buf][0].fetch(ra, a_at[0] + gr * (G * 32), a_ld, rows, 2 * (steps - gr * G), lane);
@@ -70,10 +70,15 @@ __device__ __forceinline__ void tile_product(const void* a, const uint32_t (&a_a
                     af[buf][n].v[d] = __builtin_amdgcn_raw_buffer_load_b128(ra, gr * G + d < steps ? a_at[n] : kNowhere, (gr * G + d) * a_step, 0);
         }
 #pragma unroll
-        for (int n = 0; n < NT; ++n)
+        for (int n = 0; n < NT; ++n) {
+            if constexpr (W_TURN) {
+                wf[buf][n].fetch(rw, w_at[n] + gr * (G * 32), w_step, w_at[n] == kNowhere ? 0 : 32, 2 * (steps - gr * G), lane);
+            } else {
 #pragma unroll
-            for (int d = 0; d < G; ++d)
-                wf[buf][d][n] = __builtin_amdgcn_raw_buffer_load_b128(rw, gr * G + d < steps ? w_at[n] : kNowhere, (gr * G + d) * w_step, 0);
+                for (int d = 0; d < G; ++d)
+                    wf[buf][n].v[d] = __builtin_amdgcn_raw_buffer_load_b128(rw, gr * G + d < steps ? w_at[n] : kNowhere, (gr * G + d) * w_step, 0);
+            }
+        }
         __builtin_amdgcn_sched_barrier(0);
     };
 #pragma unroll
@@ -81,14 +86,18 @@ __device__ __forceinline__ void tile_product(const void* a, const uint32_t (&a_a
 #pragma unroll
     for (int gr = 0; gr < NG; ++gr) {
         if constexpr (TURN) af[gr % BUF][0].turn(lds, lane);
+        if constexpr (W_TURN) {
+#pragma unroll
+            for (int n = 0; n < NT; ++n) wf[gr % BUF][n].turn(lds, lane);
+        }
 #pragma unroll
         for (int d = 0; d < G; ++d)
 #pragma unroll
             for (int i = 0; i < NB; ++i)
 #pragma unroll
                 for (int j = 0; j < NT; ++j)
-                    acc[i][j] = W_FIRST ? mfma32(as_bf16x8(wf[gr % BUF][d][j]), as_bf16x8(af[gr % BUF][i].v[d]), acc[i][j])
-                                        : mfma32(as_bf16x8(af[gr % BUF][i].v[d]), as_bf16x8(wf[gr % BUF][d][j]), acc[i][j]);
+                    acc[i][j] = W_FIRST ? mfma32(as_bf16x8(wf[gr % BUF][j].v[d]), as_bf16x8(af[gr % BUF][i].v[d]), acc[i][j])
+                                        : mfma32(as_bf16x8(af[gr % BUF][i].v[d]), as_bf16x8(wf[gr % BUF][j].v[d]), acc[i][j]);
         __builtin_amdgcn_sched_barrier(0);
         if (gr + BUF < NG) load(gr + BUF, gr % BUF);
     }
@@ -108,11 +117,14 @@ __device__ __forceinline__ bool split_index(const SplitGrid& gr, int bid, int& r
 // Step 1 for one workgroup: Y1 of 32 * NB rows, block kk, NT column tiles of 32.  The four waves share out the
 // contraction, so that every byte of x and R the workgroup needs is loaded once, and add up their tiles through LDS
 // (split_stage1_lds bytes).
-// DIRECT: W is R as it is (read in 16-byte pieces of its rows, like x), else the packed copy RF1.  NATURAL: out[b][kk*Q
-// + j], else the order the packed L contracts, (j/4, kk, j%4), in MFMA fragments: out[b/32][j/4][h][row][e] = element 8
-// h + e of the 16 (kk, j%4) of row b % 32, with no more rows in the last tile than there are.
-template <int NB, int NT, bool TURN>
-constexpr size_t split_stage1_lds() { return (size_t)4 * NB * NT * 4096 + (TURN ? 4 * kTurnBytes : 0); }
+// DIRECT: W is R as it is, read in whole lines, else the packed copy RF1.  TURN: so is x.  NATURAL: out[b][kk*Q + j],
+// else the order the packed L contracts, (j/4, kk, j%4), in MFMA fragments: out[b/32][j/4][h][row][e] = element 8 h + e
+// of the 16 (kk, j%4) of row b % 32, with no more rows in the last tile than there are.
+// R as it is in 16-byte pieces of 32 of its rows held the address path of the L1 up three times as long as the packed
+// copy: blocks of 256 x 1024, 2000 rows 21.5 us, in whole lines 14.2, 300 rows 11.0 and 7.4; of 256 x 256, 2000 rows 9.3
+// and 8.2.
+template <int NB, int NT, bool LINES>
+constexpr size_t split_stage1_lds() { return (size_t)4 * NB * NT * 4096 + (LINES ? 4 * kTurnBytes : 0); }
 template <int NB, int NT, int NG, int AHEAD, bool DIRECT, bool NATURAL, bool TURN>
 __device__ __forceinline__ void split_stage1(const uint16_t* __restrict__ x, const uint16_t* __restrict__ W, uint16_t* __restrict__ U,
                                              int64_t B, int P, int Q, const SplitGrid& gr, int bid, f32x4* part)
@@ -140,10 +152,11 @@ __device__ __forceinline__ void split_stage1(const uint16_t* __restrict__ x, con
 #pragma unroll
     for (int j = 0; j < NT; ++j)
         w_at[j] = jt0 + j >= QT ? kNowhere
-                : DIRECT ? (uint32_t)((((jt0 + j) * 32 + ln) * P + 16 * lo + 8 * g) * 2) : (uint32_t)((lo * QT + jt0 + j) * 1024 + lane * 16);
-    tile_product<NB, NT, NG, AHEAD, true, TURN>(x + b0 * 4 * P + kk * P, a_at, 32u, W + (size_t)kk * Q * P, w_at,
-                                                DIRECT ? 32u : (uint32_t)QT * 1024, hi - lo, acc, (uint32_t)(8 * P), rows,
-                                                reinterpret_cast<uint16_t*>(part + 4 * NB * NT * 256) + wave * (int)(kTurnBytes / 2));
+                : DIRECT ? (uint32_t)(((jt0 + j) * 32 * P + 16 * lo) * 2)
+                           : (uint32_t)((lo * QT + jt0 + j) * 1024 + lane * 16);
+    tile_product<NB, NT, NG, AHEAD, true, TURN, DIRECT>(
+        x + b0 * 4 * P + kk * P, a_at, 32u, W + (size_t)kk * Q * P, w_at, DIRECT ? (uint32_t)(2 * P) : (uint32_t)QT * 1024, hi - lo, acc,
+        (uint32_t)(8 * P), rows, reinterpret_cast<uint16_t*>(part + 4 * NB * NT * 256) + wave * (int)(kTurnBytes / 2));
 
     // wave w keeps the four columns j = 8 * w + 4 * g .. of every tile
 #pragma unroll

@@ -48,6 +48,22 @@ def test_short_batch_forward(case):
     assert torch.equal(act, act2)
 
 
+# the last rows of narrow outputs, and the first past them
+@pytest.mark.parametrize("case", [(6144, 128, 64, 64), (6145, 128, 64, 64), (3073, 192, 192, 192)], ids=str)
+def test_forward_at_the_limits_of_the_short_batch_kernels(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, p, q, s = case
+    sh = synth.Shape("lfsplit_%s" % (case,), "bf16", rows, 4, p, q, s, config=550 + parity_util.stable_seed(str(case)))
+    x, R, L, _ = synth.make_inputs(sh)
+    xd, Rd, Ld = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L))
+    y, ys = B.monarch_fwd_ws(xd, Rd, Ld), torch.empty((rows, sh.n_out), dtype=torch.bfloat16, device="cuda")
+    B.monarch_fwd_static(xd, Rd, Ld, ys)
+    assert torch.equal(y, ys)
+    parity_util.check(sh.name, y.float().cpu().numpy(), oracle.fwd(x, R, L), 2e-2)
+
+
 # B, p, q, s: short-batch backward at the edges of its tiles, of its step counts (s = 1024 .. 32) and of its row limits
 BWD = [(1, 96, 96, 384), (33, 384, 96, 96), (4096, 32, 32, 64), (63, 64, 64, 64), (2559, 128, 128, 128), (97, 512, 128, 128), (545, 192, 192, 576),
        (65, 192, 192, 768), (31, 768, 192, 192), (130, 256, 256, 1024), (290, 1024, 256, 256)]
@@ -83,6 +99,36 @@ def test_short_batch_backward(case):
     _, saved = B.monarch_fwd_save(xd, Rd, Ld)
     for name, g, w in zip(("dx_s", "dR_s", "dL_s"), B.monarch_bwd_saved(dyd, xd, saved, Rd, Ld), want):
         check(name, g, w)
+
+
+# The last rows, and the first past them, of what the kernels of short batches take: wide outputs of blocks of 256, no fused kernel, and narrow
+# outputs with the nonlinearity's factor, which they take further; each in the room that is asked for, and in that of a slightly longer
+# batch.  For every width R read in whole lines with one column tile and with two is in BWD and CASES.
+LIMITS = [(3000, 256, 256, 1024), (3001, 256, 256, 1024), (16384, 32, 32, 64), (16385, 64, 32, 32), (2049, 768, 192, 192), (4096, 512, 128, 128),
+          (4097, 512, 128, 128), (2100, 128, 64, 64)]
+
+
+@pytest.mark.parametrize("case", LIMITS, ids=str)
+def test_backward_at_the_limits_of_the_short_batch_kernels(case):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    rows, p, q, s = case
+    sh = synth.Shape("lsplit_%s" % (case,), "bf16", rows, 4, p, q, s, config=650 + parity_util.stable_seed(str(case)))
+    x, R, L, dy = synth.make_inputs(sh)
+    pre = synth.quantize(synth.normal(79, (rows, sh.n_in)), "bf16")
+    xd, Rd, Ld, dyd, pred = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L, dy, pre))
+    want = oracle.bwd_bias(dy, x, R, L)
+    act = (want[0] * activation.gelu_grad(pre),) + tuple(want[1:])
+    need = B.monarch_bwd_workspace_bytes(rows, sh.n_in, 4, q, s, 1)
+    longer = B.monarch_bwd_workspace_bytes(rows + 1, sh.n_in, 4, q, s, 1)
+    for room in (need, longer):
+        ws = torch.full((room + 256,), 0xFF, dtype=torch.uint8, device="cuda")
+        for got, wanted in ((B.monarch_bwd_bias(dyd, xd, Rd, Ld, workspace=ws[:room]), want),
+                            (B.monarch_bwd_bias_gelu_in(dyd, xd, pred, Rd, Ld, workspace=ws[:room]), act)):
+            for name, g, w in zip(("dx", "dR", "dL", "dbias"), got, wanted):
+                parity_util.check("%s.%s" % (sh.name, name), g.float().cpu().numpy(), w, 2e-2)
+            assert bool((ws[room:] == 0xFF).all())
 
 
 # p, q, s without a fused kernel: what an earlier call left in the workspace depends on its batch and on the room it had
