@@ -293,16 +293,15 @@ Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 
 }  // namespace
 
-// Where there is a wide backward, which takes nearly the same time for any short batch: up to 2560 rows (3000 for wide
-// outputs of 256 blocks; 2048 for others with blocks of 256, where `adjoint` runs out of workgroups, and where the
-// output is narrower than the input: dx is then the larger product, and every workgroup reads the rows of dU again).
-// Training step on these kernels and on the wide one: blocks of 256 and 1024, 2200 rows 83 and 88 us, 3000 rows 87 and
-// 91; of 192 and 768, 2200 rows 62 and 61, 3000 rows 71 and 71; of 192, 2200 rows 54 and 53, 3000 rows 59 and 57; of
-// 256, 2200 rows 61 and 62, 3000 rows 66 and 64; of 1024 and 256, 2200 rows 94 and 94, 3000 rows 102 and 98; of 768 and
-// 192, 2200 rows 75 and 73, 3000 rows 82 and 75.  Up to 4096 where the nonlinearity's factor comes with a narrower
-// output (`act_split`), which costs the wide kernel the time of its products again (prep and both adjoint steps, 1024
-// and 256: 2200 rows 50 and 69, 4000 rows 71 and 76; 768 and 192, 4000 rows 50 and 53).  Not for blocks of 64 alone (8
-// rows 19 and 18, 1000 rows 22 and 21).
+// Where there is a wide backward: up to 1536 rows for square layers, 1800 for others, and there further where the
+// nonlinearity's factor comes with it (`act_split`), which costs the wide kernel the time of its products again.
+// Training step on these kernels and on the wide one: blocks of 128, 1000 rows 36 and 38 us, 2000 rows 42 and 41; of
+// 192, 1000 rows 43 and 44, 1600 rows 48 and 47; of 256, 1300 rows 50 and 51, 1600 rows 53 and 52; of 192 and 768, 1300
+// rows 55 and 57, 2000 rows 62 and 60; of 256 and 1024, 1600 rows 71 and 74, 2500 rows 84 and 79; of 1024 and 256, 1600
+// rows 75 and 76, 2000 rows 81 and 78; of 768 and 192, 1000 rows 52 and 55, 1600 rows 62 and 60; of the feed-forward
+// block of width 1024, 2000 rows 164 and 173, 2500 rows 190 and 183; of 768, 2000 rows 134 and 135, 2500 rows 147 and
+// 144; of 512, 2000 rows 100 and 105, 2500 rows 116 and 108.  Not for blocks of 64 alone (8 rows 19 and 18, 1000 rows
+// 22 and 21).
 // Where the other choice is the shape-generic bf16 kernel (width 384): up to 4096 rows for square layers (6000 rows 61
 // and 65, 8000 rows 70 and 69), 16384 for others (96 x 384 blocks, 6000 rows 69 and 76, 12000 rows 90 and 117; 384 x 96
 // 75 and 78, 112 and 124; 96 x 288 67 and 69, 88 and 100).  Not where it is the shape-generic contractions (q = 256
@@ -312,7 +311,7 @@ bool bwd_split_preferred(const Problem& pb)
     const bool wide = bwd_wide_supported(pb);
     if ((!wide && !tiled_bwd_supported(pb)) || (wide && pb.p == 64 && pb.s == 64)) return false;
     const int64_t most = !wide ? (pb.p == pb.s ? 4096 : 16384)
-                       : pb.s < pb.p ? (pb.act_split ? 4096 : 2048) : pb.q <= 192 ? 2560 : pb.s > pb.p ? 3000 : 2048;
+                       : pb.p == pb.s ? 1536 : !pb.act_split ? 1800 : pb.s < pb.p ? 2200 : 2560;
     return pb.dtype == 1 && pb.k == 4 && !pb.perm_b() && pb.p % 32 == 0 && pb.q % 32 == 0 && pb.s % 32 == 0 && pb.p <= 1024 &&
            pb.s <= 1024 && pb.q <= 256 && pb.B > 0 && pb.B <= most && make_plan(pb).ok;
 }

@@ -121,13 +121,13 @@ struct BwdWide {
     static_assert(LDS_BYTES <= kMaxLdsBytes, "LDS");
 };
 
-// cooperative copy of a [64][COLS] bf16 LDS tile (row stride `stride`) to global rows b0.. (row pitch ld);
+// cooperative copy of a [ROWS][COLS] bf16 LDS tile (row stride `stride`) to global rows b0.. (row pitch ld);
 // eight LDS reads are in flight per thread before the first store.  NT: streaming (non-temporal) stores.
-template <int COLS, int NTHREADS, bool NT>
+template <int COLS, int NTHREADS, bool NT, int ROWS = 64>
 __device__ __forceinline__ void copy_out_tile(const uint16_t* src, int stride, uint16_t* dst, int64_t ld,
                                               int64_t b0, int64_t B, int tid)
 {
-    constexpr int PER_ROW = COLS / 8, TASKS = 64 * PER_ROW, PER = (TASKS + NTHREADS - 1) / NTHREADS;
+    constexpr int PER_ROW = COLS / 8, TASKS = ROWS * PER_ROW, PER = (TASKS + NTHREADS - 1) / NTHREADS;
     // the rounds are not unrolled: unrolled, the compiler precomputes every round's addresses and, next
     // to the accumulators that are live around the copies, spills them
 #pragma unroll 1
@@ -433,18 +433,18 @@ bwd_wide_data_kernel(const uint16_t* __restrict__ dy, const uint16_t* __restrict
 // rows) do not pay.  With q = 256 the form that recomputes step 1 has 10 to 18 registers too few for two workgroups
 // and spills them; step 1 in a launch of its own instead (monarch_mfma_y1.hip) is no better up to 12000 rows (256 x
 // 1024, whole backward: 8192 rows 96 and 99 us, 12000 rows 120 and 118, 16384 rows 149 and 143).
-template <int P_, int Q_, int S_>
+template <int P_, int Q_, int S_, int BM_ = 64>
 struct BwdPair {
     static constexpr int K = 4, P = P_, Q = Q_, S = S_, IG = 4;
-    static constexpr int BM = 64, NBT = 4;           // rows of a workgroup, in stages A and B as 16-row tiles
+    static constexpr int BM = BM_, NBT = BM / 16;    // rows of a workgroup, in stages A and B as 16-row tiles
     static constexpr int QK = Q / K, KQ = K * Q;
     static constexpr int N_IN = K * P, N_OUT = K * S;
     static constexpr int JT = QK / 16;               // 16-wide j tiles per (kk, c)
-    static constexpr int T_STRIDE = 2 * Q + 8;       // LDS tile [64][two blocks of Q]
+    static constexpr int T_STRIDE = 2 * Q + 8;       // LDS tile [BM][two blocks of Q]
     static constexpr int DX_COLS = IG * 16;          // dx columns of a tile of stage B
     static constexpr int DX_STRIDE = DX_COLS + 8;
-    // stage B: the two waves of a block take every other tile of columns, or 32 rows each where the tiles do not come
-    // out even
+    // stage B: the two waves of a block take every other tile of columns, or half of the rows each where the tiles do
+    // not come out even
     static constexpr bool BY_COLS = P / DX_COLS % 2 == 0;
     static constexpr int BT = BY_COLS ? NBT : NBT / 2, TILES = BY_COLS ? P / DX_COLS / 2 : P / DX_COLS;
     static constexpr size_t LDS_TILE = (size_t)BM * T_STRIDE * 2;
@@ -452,7 +452,7 @@ struct BwdPair {
     static constexpr int RING = 4;                   // stage A: chunks of 32 l of dy in LDS, 256 bytes a row
     static constexpr size_t LDS_DY = (size_t)RING * BM * 256;
     // step-1 recompute, half of a block's columns per wave (x through an LDS ring, packed R fragments)
-    using S1 = Stage1<P_, Q_ / 2, Q_ / 32, 2>;
+    using S1 = Stage1<P_, Q_ / 2, Q_ / 32, 2, BM / 32>;
     static constexpr size_t max2(size_t a, size_t b) { return a > b ? a : b; }
     static constexpr size_t LDS_BYTES = max2(LDS_TILE + LDS_DX, max2(LDS_DY, S1::LDS_X));
     static_assert(P % DX_COLS == 0 && Q % 64 == 0 && S % 64 == 0, "tile shapes");
@@ -480,7 +480,7 @@ bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, c
         using S1 = typename C::S1;
         const int ln = lane & 31, g = lane >> 5;
         f32x16 acc[S1::QT * S1::NB];
-        stage1_block<S1>(x, XF, b0, B, kk, lane, lds + (size_t)wave * S1::XR * 4096, acc, half * S1::QT);
+        stage1_block<S1>(x, XF, b0, B, kk, lane, lds + (size_t)wave * S1::XR * S1::X_SLOT, acc, half * S1::QT);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();  // every wave is done with its x ring: the space becomes the Y1 tile
         // lane holds D^T[j][b] for b = nb*32 + ln and j = half*Q/2 + jt*32 + 8*(i/4) + 4*g + i%4
@@ -496,7 +496,7 @@ bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, c
                     *reinterpret_cast<u32x2*>(lds + (size_t)(nb * 32 + ln) * C::T_STRIDE + kl * C::Q + j) = v;
                 }
         __syncthreads();
-        copy_out_tile<2 * C::Q, 256, false>(lds, C::T_STRIDE, Y1ws + kp * 2 * C::Q, C::KQ, b0, B, tid);
+        copy_out_tile<2 * C::Q, 256, false, C::BM>(lds, C::T_STRIDE, Y1ws + kp * 2 * C::Q, C::KQ, b0, B, tid);
         __syncthreads();
     }
 
@@ -608,7 +608,7 @@ bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, c
 #pragma unroll
     for (int d = 0; d < NSB - 1; ++d) issue(0, d, d);
     // what a lane stores of a 16-row tile: two pieces of 16 bytes, eight lanes a row
-    const int row0 = C::BY_COLS ? 0 : 32 * half;
+    const int row0 = C::BY_COLS ? 0 : C::BM / 2 * half;
     uint16_t* stage = lds + C::LDS_TILE / 2 + (size_t)wave * 16 * C::DX_STRIDE;
     const auto row_at = [&](int bt, int i) { return b0 + row0 + bt * 16 + i * 8 + (lane >> 3); };
     u32x4 hp[ACT ? 2 * C::BT : 1];
@@ -622,7 +622,7 @@ bwd_pair_data(const uint16_t* __restrict__ dy, const uint16_t* __restrict__ x, c
         for (int i = 0; i < 2 * C::BT; ++i) load_pre(0, i >> 1, i & 1);
     }
     __syncthreads();  // the tile is complete; nothing below writes it
-    copy_out_tile<2 * C::Q, 256, false>(lds, C::T_STRIDE, dY1ws + kp * 2 * C::Q, C::KQ, b0, B, tid);
+    copy_out_tile<2 * C::Q, 256, false, C::BM>(lds, C::T_STRIDE, dY1ws + kp * 2 * C::Q, C::KQ, b0, B, tid);
 
     for (int n = 0; n < C::TILES; ++n) {
         f32x4 acc[C::IG * C::BT];
@@ -689,6 +689,14 @@ bwd_pair_data_kernel(const uint16_t* dy, const uint16_t* x, const uint16_t* XF, 
 // 168).
 bool pairs(const Problem& pb) { return pb.q > 128 || (pb.B + 63) / 64 <= 128; }
 
+// In tiles of 32 rows instead of 64 while every workgroup then has a CU of its own: the weights that a workgroup streams
+// are the same, but of the two chains of K-steps that bound it each step has half of the products (256 x 1024 blocks,
+// 4000 rows, the kernel alone 34.5 and 24.4 us, 1024 x 256 26.6 and 20.6; training step at 4000 rows, 128: 46 and 44,
+// 192: 58 and 56, 192 x 768: 75 and 68, 256 x 1024: 99 and 89, 768 x 192: 78 and 74, 512 x 128: 54 and 49; at 5000 rows
+// 80 and 78, 105 and 106, 81 and 81, 56 and 55; with the nonlinearity's factor, feed-forward block of width 768, 4000
+// rows 183 and 174, 5000 rows 209 and 218; 16384 rows, 192 x 768: 139 and 149).
+bool short_tiles(const Problem& pb) { return pb.B <= 4096; }
+
 template <typename K>
 int launch_data_on(K kern, size_t lds, int64_t grid, const Problem& pb, const void* dy, const void* x, const uint16_t* XF,
                    const uint16_t* LF, const uint16_t* RF, void* dx, uint16_t* Y1ws, uint16_t* dY1ws, hipStream_t st)
@@ -711,12 +719,15 @@ int launch_data(const Problem& pb, const void* dy, const void* x, const uint16_t
     auto run = [&](auto kern) { return launch_data_on(kern, C::LDS_BYTES, tiles, pb, dy, x, XF, LF, RF, dx, Y1ws, dY1ws, st); };
     if (!dY1ws) return pb.x_pre ? -2 : run(bwd_wide_data_kernel<C, 1, false>);
     if (pairs(pb)) {
-        using D = BwdPair<P, Q, S>;
-        auto run2 = [&](auto kern) {  // two workgroups for each row tile, whole sets of eight tiles
-            return launch_data_on(kern, D::LDS_BYTES, (tiles + 7) / 8 * 16, pb, dy, x, XF, LF, RF, dx, Y1ws, dY1ws, st);
+        auto pair = [&](auto shape) {
+            using D = decltype(shape);
+            auto run2 = [&](auto kern) {  // two workgroups for each row tile, whole sets of eight tiles
+                return launch_data_on(kern, D::LDS_BYTES, ((pb.B + D::BM - 1) / D::BM + 7) / 8 * 16, pb, dy, x, XF, LF, RF, dx, Y1ws, dY1ws, st);
+            };
+            if (Y1ws) return pb.x_pre ? run2(bwd_pair_data_kernel<D, 0, true>) : run2(bwd_pair_data_kernel<D, 0, false>);
+            return pb.x_pre ? run2(bwd_pair_data_kernel<D, 2, true>) : run2(bwd_pair_data_kernel<D, 2, false>);
         };
-        if (Y1ws) return pb.x_pre ? run2(bwd_pair_data_kernel<D, 0, true>) : run2(bwd_pair_data_kernel<D, 0, false>);
-        return pb.x_pre ? run2(bwd_pair_data_kernel<D, 2, true>) : run2(bwd_pair_data_kernel<D, 2, false>);
+        return short_tiles(pb) ? pair(BwdPair<P, Q, S, 32>()) : pair(BwdPair<P, Q, S>());
     }
     if constexpr (Q <= 128) {
         if (Y1ws) return pb.x_pre ? run(bwd_wide_data_kernel<C, 0, true>) : run(bwd_wide_data_kernel<C, 0, false>);

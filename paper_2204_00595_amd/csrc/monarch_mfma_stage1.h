@@ -39,30 +39,31 @@ __device__ __forceinline__ int unit_frag_off(int ln, int g, int u)
 
 // Compile-time shape of step 1: P inputs per block and the Q output columns one wave computes, N_IN = 4*P
 // columns per row of x.  QTS: 32-wide j tiles per block in the packed R (more than QT when a block's
-// columns are shared out over several waves); XRMAX: most ring slots a wave may use.
-template <int P_, int Q_, int QTS_ = Q_ / 32, int XRMAX_ = 3>
+// columns are shared out over several waves); XRMAX: most ring slots a wave may use; NB: 32-row tiles.
+template <int P_, int Q_, int QTS_ = Q_ / 32, int XRMAX_ = 3, int NB_ = 2>
 struct Stage1 {
     static constexpr int P = P_, Q = Q_, N_IN = 4 * P_;
-    static constexpr int NB = 2;              // two 32-row tiles
+    static constexpr int NB = NB_;
+    static constexpr int X_DMAS = 4 * NB, X_SLOT = NB * 2048;  // requests for a chunk of x, and bf16 values of it
     static constexpr int QT = Q / 32;         // 32-wide j tiles of this wave
     static constexpr int QTS = QTS_;
     static constexpr int T1 = P / 16;         // K-steps
     static constexpr int C1 = P / 64;         // x chunks (64 columns = one 128-byte line per row)
-    static constexpr int XR = C1 < XRMAX_ ? C1 : XRMAX_;  // x ring slots per wave (8 KiB each)
-    static constexpr size_t LDS_X = (size_t)4 * XR * 8192;  // four waves
+    static constexpr int XR = C1 < XRMAX_ ? C1 : XRMAX_;  // x ring slots per wave (4 KiB for each 32 rows)
+    static constexpr size_t LDS_X = (size_t)4 * XR * X_SLOT * 2;  // four waves
     // vmcnt values that guarantee an x chunk has landed: at most this many younger VMEM operations
     // may still be outstanding (stronger than necessary is safe, weaker is not)
     static constexpr int cap63(int v) { return v < 63 ? v : 63; }
-    static constexpr int W_FIRST = cap63(8 * (XR - 1) + QT * (T1 < 3 ? T1 : 3));
-    static constexpr int W_C0 = cap63(7 * QT + (XR > 2 ? 8 : 0));  // (+ the DMAs of chunk 2 when the prologue requested it)
+    static constexpr int W_FIRST = cap63(X_DMAS * (XR - 1) + QT * (T1 < 3 ? T1 : 3));
+    static constexpr int W_C0 = cap63(7 * QT + (XR > 2 ? X_DMAS : 0));  // (+ the DMAs of chunk 2 when the prologue requested it)
     // (a ring of two slots: chunk c+1 was requested at the end of chunk c-1, only chunk c's R loads follow it)
-    static constexpr int W_MID = XR == 2 ? cap63(4 * QT) : cap63(8 * QT + 8);
+    static constexpr int W_MID = XR == 2 ? cap63(4 * QT) : cap63(8 * QT + X_DMAS);
     static constexpr int W_LAST = XR == 2 ? cap63(4 * QT) : cap63(8 * QT);
     static_assert(P % 64 == 0 && Q % 32 == 0, "tile shapes");
 };
 
-// acc[jt*2 + nb] = D^T tile (j = (jt0 + jt)*32 .., b = nb*32 ..) of block kk for rows b0 .. b0+63 (rows past B
-// are computed from row B-1 and must be dropped by the caller).  `ring` = this wave's XR * 8 KiB of LDS.
+// acc[jt*NB + nb] = D^T tile (j = (jt0 + jt)*32 .., b = nb*32 ..) of block kk for rows b0 .. b0 + 32*NB - 1 (rows past
+// B are computed from row B-1 and must be dropped by the caller).  `ring` = this wave's XR slots of LDS.
 template <typename C>
 __device__ __forceinline__ void stage1_block(const uint16_t* __restrict__ x, const uint16_t* __restrict__ RF1,
                                              int64_t b0, int64_t B, int kk, int lane, uint16_t* ring,
@@ -70,17 +71,17 @@ __device__ __forceinline__ void stage1_block(const uint16_t* __restrict__ x, con
 {
     const int ln = lane & 31, g = lane >> 5;
     const int rb = lane >> 3, pe = (lane & 7) ^ rb;
-    const uint16_t* Xrow[8];
+    const uint16_t* Xrow[C::X_DMAS];
 #pragma unroll
-    for (int i = 0; i < 8; ++i) {
+    for (int i = 0; i < C::X_DMAS; ++i) {
         int64_t row = b0 + i * 8 + rb;
         row = row < B ? row : B - 1;  // rows past the end are computed from a valid row and dropped
         Xrow[i] = x + row * C::N_IN + kk * C::P;
     }
     auto issue_x = [&](int c64) {
-        uint16_t* dst = ring + (size_t)(c64 % C::XR) * 4096;
+        uint16_t* dst = ring + (size_t)(c64 % C::XR) * C::X_SLOT;
 #pragma unroll
-        for (int i = 0; i < 8; ++i)
+        for (int i = 0; i < C::X_DMAS; ++i)
             dma16(Xrow[i] + c64 * 64 + 8 * (pe ^ (i & 1)), dst + i * 512);
     };
     int foff[4];
@@ -100,7 +101,7 @@ __device__ __forceinline__ void stage1_block(const uint16_t* __restrict__ x, con
         for (int jt = 0; jt < C::QT; ++jt) rf[slot][jt] = ldg128(Rk + (size_t)(t * C::QTS + jt) * 512);
     };
     auto read_x = [&](int c64, int u, int slot) {
-        const uint16_t* buf = ring + (size_t)(c64 % C::XR) * 4096;
+        const uint16_t* buf = ring + (size_t)(c64 % C::XR) * C::X_SLOT;
 #pragma unroll
         for (int nb = 0; nb < C::NB; ++nb) xf[slot][nb] = lds128(buf + nb * 2048 + foff[u]);
     };
@@ -157,7 +158,7 @@ __device__ __forceinline__ void stage1_half(const uint16_t* __restrict__ x, cons
                                             f32x16 (&acc)[C::QT / 2 * C::NB])
 {
     constexpr int QH = C::QT / 2, XR = 3;
-    static_assert(C::QT % 2 == 0 && C::C1 >= XR, "column halves, ring depth");
+    static_assert(C::NB == 2 && C::QT % 2 == 0 && C::C1 >= XR, "column halves, ring depth");
     static_assert(8 * QH + 4 < 64, "vmcnt range");
     const int ln = lane & 31, g = lane >> 5;
     const int rb = lane >> 3, pe = (lane & 7) ^ rb;

@@ -101,11 +101,12 @@ def test_short_batch_backward(case):
         check(name, g, w)
 
 
-# The last rows, and the first past them, of what the kernels of short batches take: wide outputs of blocks of 256, no fused kernel, and narrow
-# outputs with the nonlinearity's factor, which they take further; each in the room that is asked for, and in that of a slightly longer
-# batch.  For every width R read in whole lines with one column tile and with two is in BWD and CASES.
-LIMITS = [(3000, 256, 256, 1024), (3001, 256, 256, 1024), (16384, 32, 32, 64), (16385, 64, 32, 32), (2049, 768, 192, 192), (4096, 512, 128, 128),
-          (4097, 512, 128, 128), (2100, 128, 64, 64)]
+# The last rows, and the first past them, of what the kernels of short batches take (square layers, others, without a fused kernel, with
+# the nonlinearity's factor, which they take further) and of the wide kernel in tiles of 32 rows; each in the room that is asked for,
+# and in that of a slightly longer batch.
+LIMITS = [(1536, 192, 192, 192), (1537, 128, 128, 128), (1800, 256, 256, 1024), (1801, 256, 256, 768), (1805, 192, 192, 576), (16384, 32, 32, 64),
+          (16385, 64, 32, 32), (2200, 768, 192, 192), (2201, 512, 128, 128), (2203, 1024, 256, 256), (2560, 128, 64, 64), (2561, 64, 64, 128),
+          (4096, 192, 192, 768), (4097, 192, 192, 192), (47, 64, 64, 64), (33, 64, 64, 64), (3009, 256, 256, 256)]
 
 
 @pytest.mark.parametrize("case", LIMITS, ids=str)
