@@ -95,8 +95,8 @@ int monarch_fwd_ex(const void* x, const void* R, const void* L, void* y,
  * Section 3.3 steps 1-3).  For the shapes that have a packed-weight kernel (bf16: k = 4 wide
  * blocks, and the square m = 64 case) the call first re-lays R and L in matrix-core fragment order into `workspace` and then
  * runs the fused forward on the packed copies, which removes the weights from the LDS traffic of
- * the kernel; for k = 4 and up to 3072 rows (6144 where s < p) it runs as one launch per factor instead, if the workspace also holds the vector
- * between them (and both fit MONARCH_STATIC_WORKSPACE_BYTES).  The other bf16 shapes with k = 4 and blocks that are multiples of 32 (p: of 16; q up to 256, p up to 1024) have
+ * the kernel; for k = 4 and up to a few thousand rows it runs as one launch per factor instead, if the workspace also holds the vector
+ * between them (in slices of the batch for which both fit MONARCH_STATIC_WORKSPACE_BYTES).  The other bf16 shapes with k = 4 and blocks that are multiples of 32 (p: of 16; q up to 256, p up to 1024) have
  * that form for up to 8192 rows; they pack in every call, the packed flag means nothing to them, and without a workspace, or with
  * a short one, the call runs as monarch_fwd_ex.  fp32 layers with square blocks p = q = s of 32 or 64 (any k) run on the fp32 matrix cores, one
  * launch per block-diagonal factor with the vector between the factors kept in `workspace` (the packed flag

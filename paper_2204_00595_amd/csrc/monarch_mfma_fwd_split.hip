@@ -309,6 +309,19 @@ int launch_once_steps(const Problem& pb, const SplitArgs& a, hipStream_t st)
     return pb.q <= 192 ? launch_once<T4, 3>(pb, a, st) : launch_once<T4, 4>(pb, a, st);
 }
 
+// Rows whose vector between the factors fits the static workspace behind the packed weights, in whole tiles, so that
+// monarch_fwd_static runs the same kernels as monarch_fwd_ws; longer batches go in slices of about the same length.
+// All of the batch where it fits; 0: not even a tile does.
+int64_t slice_rows(const Problem& pb)
+{
+    const size_t packed = fwd_frag_packed(pb), row = (size_t)pb.kq() * 2;
+    if (packed + align_up(pb.B * row, 256) <= MONARCH_STATIC_WORKSPACE_BYTES) return pb.B;
+    const int64_t fit = packed < MONARCH_STATIC_WORKSPACE_BYTES ? (int64_t)((MONARCH_STATIC_WORKSPACE_BYTES - packed) / row / 32 * 32) : 0;
+    if (fit == 0) return 0;
+    const int64_t n = (pb.B + fit - 1) / fit;
+    return ((pb.B + n - 1) / n + 31) / 32 * 32;
+}
+
 }  // namespace
 
 bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
@@ -317,32 +330,48 @@ bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
            pb.q <= 256;
 }
 
-// Where there is a fused kernel, up to 3072 rows (48 of its row tiles; it takes the same time for any number of them),
-// and up to 6144 where the output is narrower than the input: 1024 -> 4096 -> 1024, both layers with the nonlinearity,
-// 2600 rows 70 and 46 us; 768 -> 3072 alone, 4000 rows 20.2 and 22.9, 3072 -> 768 31.8 and 18.9; 512 -> 2048 alone,
-// 4000 rows 18.9 and 19.5, 2048 -> 512 17.6 and 12.3, 6000 rows 18.2 and 16.  Where the other choice
-// is the shape-generic kernel (width 384: 47 us for 300 rows, 60 for 8000), up to 8192.  And only where it all fits the
-// static workspace, so that monarch_fwd_static runs the same kernels as monarch_fwd_ws.
+// Where there is a fused kernel, which takes the same time for any number of row tiles that leaves CUs idle: up to 3072
+// rows, 4352 where the output is narrower than the input, 2048 for wider outputs of more than 128 columns a block.  us,
+// the fused kernel first, without packed weights and with them: 768 -> 3072 with the nonlinearity, 2000 rows 22.8 and
+// 18.4, 16.0 and 14.6, 2500 rows 23.1 and 22.6, 16.2 and 18.7; 1024 -> 4096, 1500 rows 26.7 and 22.2, 20.5 and 16.5,
+// 2500 rows 27.9 and 29.4, 21.6 and 22.9; 512 -> 2048, 3000 rows 21.8 and 17.3, 17.1 and 14.2, 4000 rows 22.2 and 21.2,
+// 17.1 and 18.0; 4096 -> 1024, 2500 rows 43.1 and 22.7, 37.1 and 20.5, 4000 rows (two slices) 43.2 and 37.1, 37.8 and
+// 35.2, 5000 rows 43.6 and 43.6, 38.5 and 40.9; 3072 -> 768, 4000 rows 30.5 and 21.5, 25.1 and 19.2, 5000 rows (two
+// slices) 30.7 and 31.3, 25.3 and 28.0; 2048 -> 512, 4000 rows 19.3 and 13.1, 12.9 and 12.7, 5000 rows 19.4 and 15.8,
+// 12.9 and 15.0; 768 -> 768, 3000 rows 17.6 and 12.9, 12.9 and 12.2; 1024 -> 1024 21.9 and 16.1, 16.5 and 14.2; 512 ->
+// 512 11.9 and 9.5, 7.9 and 9.1.  Where the other choice is the shape-generic kernel (width 384: 47 us for 300 rows, 60
+// for 8000), up to 8192.
 bool fwd_split_preferred(const Problem& pb)
 {
-    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= (!fwd_frag_supported(pb) ? 8192 : pb.s < pb.p ? 6144 : 3072) &&
-           fwd_frag_packed(pb) + fwd_split_mid_bytes(pb) <= MONARCH_STATIC_WORKSPACE_BYTES;
+    const int64_t most = !fwd_frag_supported(pb) ? 8192 : pb.s < pb.p ? 4352 : pb.s > pb.p && pb.q > 128 ? 2048 : 3072;
+    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= most && slice_rows(pb) > 0;
 }
 
-size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)pb.B * pb.kq() * 2, 256); }
+size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)slice_rows(pb) * pb.kq() * 2, 256); }
 
-int fwd_split(const Problem& pb, const void* x, const void* R, const void* L, uint16_t* RF1, uint16_t* LF2, void* y, void* U,
+int fwd_split(const Problem& given, const void* x, const void* R, const void* L, uint16_t* RF1, uint16_t* LF2, void* y, void* U,
               hipStream_t st)
 {
-    const SplitArgs a{(const uint16_t*)x, SplitPack{(const uint16_t*)R, (const uint16_t*)L, RF1, LF2, pb.s, (int)((pb.n_R() + pb.n_L()) / 8), 0},
-                      (uint16_t*)y, (uint16_t*)U};
-    if (once_preferred(pb)) {
-        if (pb.p <= 128) return launch_once_steps<2>(pb, a, st);
-        if (pb.p <= 192) return launch_once_steps<3>(pb, a, st);
-        return launch_once_steps<4>(pb, a, st);
+    Problem pb = given;
+    const int64_t rows = slice_rows(given);
+    for (int64_t b = 0; b < given.B; b += rows) {
+        pb.B = given.B - b < rows ? given.B - b : rows;
+        const size_t to = (size_t)b * pb.n_out();
+        if (given.y_pre) pb.y_pre = (uint16_t*)given.y_pre + to;
+        const SplitArgs a{(const uint16_t*)x + (size_t)b * pb.n_in,
+                          SplitPack{(const uint16_t*)R, (const uint16_t*)L, RF1, LF2, pb.s, (int)((pb.n_R() + pb.n_L()) / 8), 0}, (uint16_t*)y + to,
+                          (uint16_t*)U};
+        int rc;
+        if (once_preferred(pb)) {
+            rc = pb.p <= 128 ? launch_once_steps<2>(pb, a, st) : pb.p <= 192 ? launch_once_steps<3>(pb, a, st) : launch_once_steps<4>(pb, a, st);
+        } else {
+            rc = launch_factor(pb, 1, a, st);
+            if (!rc) rc = launch_factor(pb, 2, a, st);
+        }
+        if (rc) return rc;
+        pb.flags |= MONARCH_FLAG_WS_PACKED;  // the first slice has packed the weights
     }
-    const int rc = launch_factor(pb, 1, a, st);
-    return rc ? rc : launch_factor(pb, 2, a, st);
+    return 0;
 }
 
 }  // namespace monarch

@@ -48,8 +48,9 @@ def test_short_batch_forward(case):
     assert torch.equal(act, act2)
 
 
-# the last rows of narrow outputs, and the first past them
-@pytest.mark.parametrize("case", [(6144, 128, 64, 64), (6145, 128, 64, 64), (3073, 192, 192, 192)], ids=str)
+# the last rows of narrow, wide and square layers, and the first past them; batches in slices, with and without packed weights
+@pytest.mark.parametrize("case", [(4352, 128, 64, 64), (4353, 128, 64, 64), (2048, 192, 192, 768), (2049, 192, 192, 576), (3072, 64, 64, 128),
+                                  (3073, 192, 192, 192), (2848, 1024, 256, 256), (4352, 1024, 256, 256), (8190, 384, 96, 96)], ids=str)
 def test_forward_at_the_limits_of_the_short_batch_kernels(case):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
@@ -61,6 +62,11 @@ def test_forward_at_the_limits_of_the_short_batch_kernels(case):
     y, ys = B.monarch_fwd_ws(xd, Rd, Ld), torch.empty((rows, sh.n_out), dtype=torch.bfloat16, device="cuda")
     B.monarch_fwd_static(xd, Rd, Ld, ys)
     assert torch.equal(y, ys)
+    ws = torch.full((B.monarch_fwd_workspace_bytes(rows, sh.n_in, 4, q, s, 1),), 0xFF, dtype=torch.uint8, device="cuda")
+    pre, act = B.monarch_fwd_bias_gelu(xd, Rd, Ld, None, workspace=ws)
+    assert torch.equal(pre, y)
+    pre2, act2 = B.monarch_fwd_bias_gelu(xd, Rd, Ld, None, workspace=ws, flags=B.MONARCH_FLAG_WS_PACKED)
+    assert torch.equal(pre2, y) and torch.equal(act, act2)
     parity_util.check(sh.name, y.float().cpu().numpy(), oracle.fwd(x, R, L), 2e-2)
 
 
