@@ -8,16 +8,21 @@
 // (scaled to trace 1) until it is of rank one: after t squarings the second eigenvalue has shrunk to (sigma_2/sigma_1)^(2^(t+1)),
 // so a gap of 1e-6 is resolved in about twenty squarings, and rounding in a later squaring meets a wider gap than in the first.
 //
-// A squaring of a symmetric matrix on the fp32 matrix cores needs next to no data movement: lane (c, h) of a 16 x 16
+// A squaring of a symmetric matrix on the matrix cores needs next to no data movement: lane (c, h) of a 16 x 16
 // accumulator tile holds S[4h + r][c] = S[c][4h + r], which is what the same lane has to bring as either operand of
 // contraction step r.  Tiles below the diagonal are transposes of those above, by way of LDS.
 //
-// What bounds it: the matrix cores, 32 clocks for each of the NT^2 (NT + 1) / 2 * 4 steps of a squaring (m = 32: 768
-// clocks, one wave per SIMD; m = 64: 5120, four), then the transposition through LDS.  Sums over the lanes stay in the
-// vector registers and run beside the products (m = 32, 1024 slices: 15.8 us with shuffles between them, 13.3 now; the
-// four lanes of a column meet by row swaps).  The one-sided Jacobi SVD that was here before (all m triples, three
-// cross-lane shuffles per element and rotation) took 784 us for m = 32 and 5.8 ms for m = 64, and was less accurate
-// (products 2e-5 off at m = 64, here 5e-7).
+// From 17 rows on the products are those of three bf16 planes of the entries (six v_mfma_f32_16x16x32_bf16 for the
+// eight contraction indices of two tiles that a lane holds, 96 clocks for the 256 of v_mfma_f32_16x16x4_f32), which
+// costs 5.5 vector instructions an entry and leaves less rounding: products off float64 by 2.0e-7 of them for 4.7e-7
+// (root mean square over eight matrices, m = 32), 3.2e-7 for 5.6e-7 (m = 64).  m = 24: 10.3 us -> 8.7, 32: 11.6 -> 9.7,
+// 40: 35.5 -> 26.7, 48: 48.0 -> 35.5, 64: 139 -> 88.
+// What bounds it: from 33 rows on the vector units and the matrix cores, by about the same (m = 64: 1900 clocks of
+// products and 2000 of splitting, scaling and summing up for a squaring, two waves per SIMD), below the chain of
+// squarings.  Sums over the lanes stay in the vector registers and run beside the products (m = 32, 1024 slices: 15.8
+// us with shuffles between them, 13.3 without; the four lanes of a column meet by row swaps).  The one-sided Jacobi SVD
+// that was here before (all m triples, three cross-lane shuffles per element and rotation) took 784 us for m = 32 and
+// 5.8 ms for m = 64, and was less accurate (products 2e-5 off at m = 64).
 #include <type_traits>
 #include "monarch_internal.h"
 #include "monarch_device.h"
@@ -60,14 +65,44 @@ __device__ __forceinline__ float wave_sum(float v) { return wave_reduce(v, [](fl
 __device__ __forceinline__ float column_sum(float v) { return column_reduce(v, [](float a, float b) { return a + b; }); }
 __device__ __forceinline__ float wave_max(float v) { return wave_reduce(v, [](float a, float b) { return fmaxf(a, b); }); }
 
+// Eight values as three bf16 planes that add up to them, the values first rounded, what that leaves rounded, and the
+// rest: an operand of v_mfma_f32_16x16x32_bf16 each.  (Entries are at most one; what is below 2^-126 is lost.)
+__device__ __forceinline__ void planes_of(const f32x4& lo, const f32x4& hi, bf16x8 (&out)[3])
+{
+    float v[8] = {lo[0], lo[1], lo[2], lo[3], hi[0], hi[1], hi[2], hi[3]};
+#pragma unroll
+    for (int u = 0; u < 3; ++u) {
+        u32x4 w;
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            w[i] = pack_bf16x2(v[2 * i], v[2 * i + 1]);
+            if (u < 2) {
+                v[2 * i] -= __uint_as_float(w[i] << 16);
+                v[2 * i + 1] -= __uint_as_float(w[i] & 0xffff0000u);
+            }
+        }
+        out[u] = as_bf16x8(w);
+    }
+}
+// the six largest products of planes; the others add up to 2^-24 of the product
+__device__ __forceinline__ f32x4 plane_sums(const bf16x8 (&a)[3], const bf16x8 (&b)[3], f32x4 c)
+{
+#pragma unroll
+    for (int w = 2; w >= 0; --w)
+#pragma unroll
+        for (int u = 0; u <= w; ++u) c = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[u], b[w - u], c, 0, 0, 0);
+    return c;
+}
+
 // NT x NT tiles of 16 x 16
 template <typename T, int NT>
-__global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* __restrict__ A, T* __restrict__ R, T* __restrict__ L, int m)
+__global__ void __launch_bounds__(64 * kWavesPerBlock, 2) project_kernel(const T* __restrict__ A, T* __restrict__ R, T* __restrict__ L, int m)
 {
     constexpr int H = 4, TS = 16, NA = 4;             // lanes per column of a tile, its side, values per lane
     constexpr int GT = TS * NT / H;                   // steps of H rows of G
     constexpr int GP = NT == 3 ? 16 : GT;             // ... rounded up to a power of two
     constexpr int kStride = TS + 4, kUpper = NT * (NT - 1) / 2;
+    constexpr bool kPlanes = NT > 1;                  // the squarings on the bf16 matrix cores
     __shared__ __align__(16) float shared[kWavesPerBlock][kUpper > 0 ? kUpper * TS * kStride : H * GP];
     const int slice = blockIdx.x * kWavesPerBlock + (threadIdx.x >> 6);
     if (slice >= m * m) return;  // no barriers below
@@ -105,44 +140,78 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
     trace = wave_sum(trace);
 
     f32x4 S[NT][NT];  // S[a][b]: rows of tile a, columns of tile b
-#pragma unroll
-    for (int a = 0; a < NT; ++a)
-#pragma unroll
-        for (int b = 0; b < NT; ++b)
-#pragma unroll
-            for (int r = 0; r < NA; ++r) S[a][b][r] = 0.f;
-#pragma unroll
-    for (int t = 0; t < GT; ++t)
+    // the tiles below the diagonal from those above, by way of LDS
+    auto mirror = [&]() {
+        int at = 0;
 #pragma unroll
         for (int a = 0; a < NT; ++a)
 #pragma unroll
-            for (int b = 0; b < NT; ++b) S[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(g[a][t], g[b][t], S[a][b], 0, 0, 0);
+            for (int b = a + 1; b < NT; ++b, at += TS * kStride)
+#pragma unroll
+                for (int r = 0; r < NA; ++r) lds[at + (4 * h + r) * kStride + c] = S[a][b][r];
+        __builtin_amdgcn_wave_barrier();
+        at = 0;
+#pragma unroll
+        for (int a = 0; a < NT; ++a)
+#pragma unroll
+            for (int b = a + 1; b < NT; ++b, at += TS * kStride)
+                S[b][a] = *reinterpret_cast<const f32x4*>(lds + at + c * kStride + 4 * h);
+        __builtin_amdgcn_wave_barrier();
+    };
+    // S = X^T X above the diagonal: tile column a of X is `steps` pieces of four contraction indices, x(a, step), which lane
+    // (c, h) brings in the same places for both operands, so that their order does not matter
+    auto gram = [&](auto steps, auto x) {
+        constexpr int N = decltype(steps)::value;
+        if constexpr (kPlanes) {
+            bf16x8 p[(N + 1) / 2][NT][3];
+#pragma unroll
+            for (int t = 0; t < (N + 1) / 2; ++t)
+#pragma unroll
+                for (int a = 0; a < NT; ++a) planes_of(x(a, 2 * t), 2 * t + 1 < N ? x(a, 2 * t + 1) : f32x4{0.f, 0.f, 0.f, 0.f}, p[t][a]);
+#pragma unroll
+            for (int a = 0; a < NT; ++a)
+#pragma unroll
+                for (int b = a; b < NT; ++b) S[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < (N + 1) / 2; ++t)
+#pragma unroll
+                for (int a = 0; a < NT; ++a)
+#pragma unroll
+                    for (int b = a; b < NT; ++b) S[a][b] = plane_sums(p[t][a], p[t][b], S[a][b]);
+        } else {
+            f32x4 q[NT][NT];
+#pragma unroll
+            for (int a = 0; a < NT; ++a)
+#pragma unroll
+                for (int b = a; b < NT; ++b) q[a][b] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int t = 0; t < N; ++t)
+#pragma unroll
+                for (int r = 0; r < NA; ++r)
+#pragma unroll
+                    for (int a = 0; a < NT; ++a)
+#pragma unroll
+                        for (int b = a; b < NT; ++b) q[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(x(a, t)[r], x(b, t)[r], q[a][b], 0, 0, 0);
+#pragma unroll
+            for (int a = 0; a < NT; ++a)
+#pragma unroll
+                for (int b = a; b < NT; ++b) S[a][b] = q[a][b];
+        }
+    };
+    gram(std::integral_constant<int, NT>(), [&](int a, int t) { return f32x4{g[a][4 * t], g[a][4 * t + 1], g[a][4 * t + 2], g[a][4 * t + 3]}; });
+    mirror();
 
     // S = S^2 at trace 1; returns the trace before, |S|_F^2, which is 1 exactly when S, at trace 1 itself, is of rank
     // one.  The sum over the lanes runs beside the products.
     auto square = [&]() {
-        f32x4 Q[NT][NT];
         float norm2 = 0.f;
-#pragma unroll
-        for (int a = 0; a < NT; ++a)
-#pragma unroll
-            for (int b = a; b < NT; ++b)
-#pragma unroll
-                for (int r = 0; r < NA; ++r) Q[a][b][r] = 0.f;
-#pragma unroll
-        for (int e = 0; e < NT; ++e)
-#pragma unroll
-            for (int r = 0; r < NA; ++r)
-#pragma unroll
-                for (int a = 0; a < NT; ++a)
-#pragma unroll
-                    for (int b = a; b < NT; ++b) Q[a][b] = __builtin_amdgcn_mfma_f32_16x16x4f32(S[e][a][r], S[e][b][r], Q[a][b], 0, 0, 0);
 #pragma unroll
         for (int a = 0; a < NT; ++a)
 #pragma unroll
             for (int b = 0; b < NT; ++b)
 #pragma unroll
                 for (int r = 0; r < NA; ++r) norm2 = fmaf(S[a][b][r], S[a][b][r], norm2);
+        gram(std::integral_constant<int, NT>(), [&](int a, int t) { return S[t][a]; });
         norm2 = wave_sum(norm2);
         const float inv = norm2 > 0.f ? 1.f / norm2 : 0.f;
 #pragma unroll
@@ -150,26 +219,8 @@ __global__ void __launch_bounds__(64 * kWavesPerBlock) project_kernel(const T* _
 #pragma unroll
             for (int b = a; b < NT; ++b)
 #pragma unroll
-                for (int r = 0; r < NA; ++r) Q[a][b][r] *= inv;
-        int at = 0;
-#pragma unroll
-        for (int a = 0; a < NT; ++a)
-#pragma unroll
-            for (int b = a + 1; b < NT; ++b, at += TS * kStride)
-#pragma unroll
-                for (int r = 0; r < NA; ++r) lds[at + (4 * h + r) * kStride + c] = Q[a][b][r];
-        __builtin_amdgcn_wave_barrier();
-        at = 0;
-#pragma unroll
-        for (int a = 0; a < NT; ++a)
-#pragma unroll
-            for (int b = a + 1; b < NT; ++b, at += TS * kStride)
-                Q[b][a] = *reinterpret_cast<const f32x4*>(lds + at + c * kStride + 4 * h);
-        __builtin_amdgcn_wave_barrier();
-#pragma unroll
-        for (int a = 0; a < NT; ++a)
-#pragma unroll
-            for (int b = 0; b < NT; ++b) S[a][b] = Q[a][b];
+                for (int r = 0; r < NA; ++r) S[a][b][r] *= inv;
+        mirror();
         return norm2;
     };
     {
