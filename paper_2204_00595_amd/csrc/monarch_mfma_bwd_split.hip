@@ -17,11 +17,12 @@
 // Fragments: WT[g][nt][t][lane][e] = W[g][16t + 4*(e/2) + 2*(lane/32) + e%2][32*nt + lane%32]: lane half h holds, of
 // the 16 m of a step, the pairs that its 16-byte pieces 2i + h of the line bring.
 //
-// What bounds it: latency for a few row tiles (three launches of about 6 us), the address path of the L1 above; the
+// What bounds it: latency for a few row tiles (three launches of about 5 us), the address path of the L1 above; the
 // rows come in whole lines that change places through LDS (RowPieces; training step of the feed-forward block of width
-// 1024, 2000 rows: 224 -> 196 us, of width 768 169 -> 150, 200 rows 106 -> 99).  Measured, GPU time of a training step:
-// 256 -> 256 -> 1024 blocks, 200 rows 86 -> 57 us; the feed-forward block of width 1024 240 -> 101 us at 200 rows, 262
-// -> 153 at 1000; of width 384 119 -> 69 and 134 -> 88.
+// 1024, 2000 rows: 224 -> 196 us, of width 768 169 -> 150, 200 rows 106 -> 99).  Measured, GPU time of a training step,
+// before there were these kernels, with them, and with R in whole lines and two or three workgroups of `adjoint` to a
+// CU: the feed-forward block of width 1024, 1000 rows 262, 153 and 122 us, 2000 rows 189 (with them) and 165; of width
+// 384, 1500 rows 98 and 91.
 #include "monarch_internal.h"
 #include "monarch_mfma_common.h"
 #include "monarch_mfma_split.h"
