@@ -309,17 +309,19 @@ int launch_once_steps(const Problem& pb, const SplitArgs& a, hipStream_t st)
     return pb.q <= 192 ? launch_once<T4, 3>(pb, a, st) : launch_once<T4, 4>(pb, a, st);
 }
 
-// Rows whose vector between the factors fits the static workspace behind the packed weights, in whole tiles, so that
-// monarch_fwd_static runs the same kernels as monarch_fwd_ws; longer batches go in slices of about the same length.
-// All of the batch where it fits; 0: not even a tile does.
+// Rows whose vector between the factors fits the static workspace behind the packed weights, so that monarch_fwd_static
+// runs the same kernels as monarch_fwd_ws: all of the batch, or whole tiles of it; 0: not even one.
+int64_t fit_rows(const Problem& pb)
+{
+    const size_t packed = fwd_frag_packed(pb), row = (size_t)pb.kq() * 2, room = MONARCH_STATIC_WORKSPACE_BYTES;
+    if (packed + align_up(pb.B * row, 256) <= room) return pb.B;
+    return packed < room ? (int64_t)((room - packed) / row / 32 * 32) : 0;
+}
+// Longer batches go in slices of about the same length.
 int64_t slice_rows(const Problem& pb)
 {
-    const size_t packed = fwd_frag_packed(pb), row = (size_t)pb.kq() * 2;
-    if (packed + align_up(pb.B * row, 256) <= MONARCH_STATIC_WORKSPACE_BYTES) return pb.B;
-    const int64_t fit = packed < MONARCH_STATIC_WORKSPACE_BYTES ? (int64_t)((MONARCH_STATIC_WORKSPACE_BYTES - packed) / row / 32 * 32) : 0;
-    if (fit == 0) return 0;
-    const int64_t n = (pb.B + fit - 1) / fit;
-    return ((pb.B + n - 1) / n + 31) / 32 * 32;
+    const int64_t fit = fit_rows(pb), n = (pb.B + fit - 1) / fit;
+    return n == 1 ? pb.B : ((pb.B + n - 1) / n + 31) / 32 * 32;
 }
 
 }  // namespace
@@ -344,10 +346,10 @@ bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
 bool fwd_split_preferred(const Problem& pb)
 {
     const int64_t most = !fwd_frag_supported(pb) ? 8192 : pb.s < pb.p ? 4352 : pb.s > pb.p && pb.q > 128 ? 2048 : 3072;
-    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= most && slice_rows(pb) > 0;
+    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= most && fit_rows(pb) > 0;
 }
 
-size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)slice_rows(pb) * pb.kq() * 2, 256); }
+size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)fit_rows(pb) * pb.kq() * 2, 256); }
 
 int fwd_split(const Problem& given, const void* x, const void* R, const void* L, uint16_t* RF1, uint16_t* LF2, void* y, void* U,
               hipStream_t st)
