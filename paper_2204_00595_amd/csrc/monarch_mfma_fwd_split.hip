@@ -123,7 +123,9 @@ split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__
 // products.  On the GPU alone, 256 x 1024 blocks: 8 rows 6.5 us in two launches, 5.7 in one, 32 rows 6.9 and 6.8, 64 rows
 // 7.0 and 7.2; 192 x 768: 8 rows 6.3 and 5.0, 64 rows 6.9 and 6.2; 512 x 128 (the quarter of R as large, four times the
 // rows): 8 rows 5.6 and 6.3.  Both layers of width 1024 with the host's part, 8 rows: 15.8 and 12.9.
-template <int T4, int K4, bool ACT>
+// DIRECT: RF1 and LF2 are R and L as they are, for the shapes that no call packs for the next: R in whole lines that
+// change places through LDS, L in both halves of the 16 values that a step contracts.
+template <int T4, int K4, bool ACT, bool DIRECT>
 __global__ void __launch_bounds__(512)
 split_once_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ RF1, const uint16_t* __restrict__ LF2,
                   const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, uint16_t* __restrict__ y_pre, int64_t B, int P, int Q, int S)
@@ -151,11 +153,15 @@ split_once_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R
             xv[i][n] = __builtin_amdgcn_raw_buffer_load_b128(rx, wave * 4 + i < rows && n * 64 + lane < pieces ? (n * 64 + lane) * 16u : kNowhere,
                                                              (uint32_t)(wave * 4 + i) * (8u * P), 0);
     __builtin_amdgcn_sched_barrier(0);
-    u32x4 lf[4 * K4];
-    const auto rl = buffer_at(LF2 + (size_t)(c * LT + lt) * KS * 512);
+    u32x4 lf[4 * K4], lf2[DIRECT ? 4 * K4 : 1];
+    const uint32_t l_at = DIRECT ? (uint32_t)(ln * Q) * 2u : lane * 16u, l_step = DIRECT ? 32u : 1024u;
+    const auto rl = buffer_at(DIRECT ? LF2 + ((size_t)c * S + lt * 32) * Q : LF2 + (size_t)(c * LT + lt) * KS * 512);
     if (wave == 0) {
 #pragma unroll
-        for (int ks = 0; ks < 4 * K4; ++ks) lf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rl, ks < KS ? lane * 16u : kNowhere, ks * 1024u, 0);
+        for (int ks = 0; ks < 4 * K4; ++ks) {
+            lf[ks] = __builtin_amdgcn_raw_buffer_load_b128(rl, ks < KS ? l_at : kNowhere, ks * l_step, 0);
+            if constexpr (DIRECT) lf2[ks] = __builtin_amdgcn_raw_buffer_load_b128(rl, ks < KS ? l_at : kNowhere, ks * l_step + 16u, 0);
+        }
     }
     auto put = [&] {
 #pragma unroll
@@ -175,13 +181,19 @@ split_once_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R
         const int T = P / 16;
         const auto rw = buffer_at(RF1 + (size_t)kk * Q * P);
         const uint32_t w_at = (uint32_t)jt * 1024u + lane * 16u;
-        u32x4 wf[4][T4];
+        static_assert(!DIRECT || T4 <= 4, "a quarter of R's row is one line");
+        u32x4 wf[4][DIRECT ? 1 : T4];
+        RowPieces wr[DIRECT ? 4 : 1];
 #pragma unroll
         for (int part = 0; part < 4; ++part) {
             const int lo = T * part / 4, n = T * (part + 1) / 4 - lo;
+            if constexpr (DIRECT) {
+                wr[part].fetch(rw, (uint32_t)(jt * 32 * P + 16 * lo) * 2u, 2u * P, 32, 2 * n, lane);
+            } else {
 #pragma unroll
-            for (int t = 0; t < T4; ++t)
-                wf[part][t] = __builtin_amdgcn_raw_buffer_load_b128(rw, t < n ? w_at : kNowhere, (uint32_t)((lo + t) * QT) * 1024u, 0);
+                for (int t = 0; t < T4; ++t)
+                    wf[part][t] = __builtin_amdgcn_raw_buffer_load_b128(rw, t < n ? w_at : kNowhere, (uint32_t)((lo + t) * QT) * 1024u, 0);
+            }
         }
         __builtin_amdgcn_sched_barrier(0);
         put();
@@ -192,11 +204,13 @@ split_once_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R
 #pragma unroll
             for (int r = 0; r < 16; ++r) acc[part][r] = 0.f;
             const int lo = T * part / 4, n = T * (part + 1) / 4 - lo;
+            if constexpr (DIRECT) wr[part].turn(xs + P * 128 + wave * (int)(kTurnBytes / 2), lane);
 #pragma unroll
             for (int t = 0; t < T4; ++t) {
                 if (t >= n) continue;
                 const int pc = (kk * T + lo + t) * 2 + h;
-                acc[part] = mfma32(as_bf16x8(wf[part][t]), as_bf16x8(lds128(xs + (pc * 32 + (ln ^ (pc & 31))) * 8)), acc[part]);
+                const u32x4 w = DIRECT ? wr[DIRECT ? part : 0].v[t] : wf[part][DIRECT ? 0 : t];
+                acc[part] = mfma32(as_bf16x8(w), as_bf16x8(lds128(xs + (pc * 32 + (ln ^ (pc & 31))) * 8)), acc[part]);
             }
         }
         // element 8 (r/4) + 4 h + r%4 of the tile is the vector's (kk, j): four j are half of a step's 16 bytes
@@ -216,8 +230,14 @@ split_once_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R
 #pragma unroll
     for (int r = 0; r < 16; ++r) acc[r] = 0.f;
 #pragma unroll
-    for (int ks = 0; ks < 4 * K4; ++ks)
+    for (int ks = 0; ks < 4 * K4; ++ks) {
+        if constexpr (DIRECT) {  // of pairs 0 .. 7 those that half h brings: first values, then second ones (pack_fwd_piece)
+            const u32x4 a = lf[ks], b = lf2[ks];
+            const uint32_t d0 = h ? a[1] : a[0], d1 = h ? a[3] : a[2], d2 = h ? b[1] : b[0], d3 = h ? b[3] : b[2];
+            lf[ks] = u32x4{pick_lo16(d0, d1), pick_lo16(d2, d3), pick_hi16(d0, d1), pick_hi16(d2, d3)};
+        }
         if (ks < KS) acc = mfma32(as_bf16x8(lds128(Uf + ((ks * 2 + h) * 32 + ln) * 8)), as_bf16x8(lf[ks]), acc);
+    }
     const int col = (lt * 32 + ln) * 4 + c;
     const float bv = bias ? __uint_as_float((uint32_t)bias[col] << 16) : 0.f;
 #pragma unroll
@@ -288,25 +308,38 @@ int launch_factor(const Problem& pb, int stage, const SplitArgs& a, hipStream_t 
 }
 
 // Where one launch does for both factors (split_once_kernel): packed weights, p up to 256, one row tile, two where the
-// quarter of R is small.
-bool once_preferred(const Problem& pb) { return pb.ws_packed() && pb.p <= 256 && pb.B <= (pb.p * pb.q <= 192 * 192 ? 64 : 32); }
+// quarter of R is small.  Weights as they are where no call packs them for the next, with q up to 128 and p up to 256,
+// two row tiles; two launches and one, host included, us: blocks of 96 x 96 and 384 x 96 (width 384 -> 1536), 8 rows 8.7
+// and 5.2, 64 rows 8.7 and 6.2; 96 x 96 twice, 64 rows 7.0 and 5.3; 128 x 272 and 160 x 128, 64 rows 7.3 and 7.2; 96 x 384
+// and 96 x 96, 8 rows 7.4 and 8.0, 64 rows 7.3 and 8.7.
+bool once_direct(const Problem& pb) { return !fwd_frag_supported(pb) && pb.q <= 128 && pb.p <= 256 && pb.B <= 64; }
+bool once_preferred(const Problem& pb)
+{
+    return once_direct(pb) || (pb.ws_packed() && pb.p <= 256 && pb.B <= (pb.p * pb.q <= 192 * 192 ? 64 : 32));
+}
 // T4, 4 K4: K-steps of a quarter of the first contraction and of the second
-template <int T4, int K4>
+template <int T4, int K4, bool DIRECT>
 int launch_once(const Problem& pb, const SplitArgs& a, hipStream_t st)
 {
-    auto kern = pb.act ? split_once_kernel<T4, K4, true> : split_once_kernel<T4, K4, false>;
+    auto kern = pb.act ? split_once_kernel<T4, K4, true, DIRECT> : split_once_kernel<T4, K4, false, DIRECT>;
     const dim3 grid((unsigned)((pb.s / 32 + 1) / 2 * 8), (unsigned)((pb.B + 31) / 32));
-    const size_t lds = (size_t)K4 * 4096 + (size_t)pb.p * 256;
+    const size_t lds = (size_t)K4 * 4096 + (size_t)pb.p * 256 + (DIRECT ? 8 * kTurnBytes : 0);
     if (hipError_t e = allow_dynamic_lds((const void*)kern, lds)) return hip_status(e);
-    hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, a.x, (const uint16_t*)a.w.RF1, (const uint16_t*)a.w.LF2, (const uint16_t*)pb.bias, a.y,
-                       (uint16_t*)pb.y_pre, pb.B, pb.p, pb.q, pb.s);
+    hipLaunchKernelGGL(kern, grid, dim3(512), lds, st, a.x, DIRECT ? a.w.R : (const uint16_t*)a.w.RF1, DIRECT ? a.w.L : (const uint16_t*)a.w.LF2,
+                       (const uint16_t*)pb.bias, a.y, (uint16_t*)pb.y_pre, pb.B, pb.p, pb.q, pb.s);
     return hip_status(hipGetLastError());
 }
 template <int T4>
 int launch_once_steps(const Problem& pb, const SplitArgs& a, hipStream_t st)
 {
-    if (pb.q <= 128) return launch_once<T4, 2>(pb, a, st);
-    return pb.q <= 192 ? launch_once<T4, 3>(pb, a, st) : launch_once<T4, 4>(pb, a, st);
+    if (pb.q <= 128) return launch_once<T4, 2, false>(pb, a, st);
+    return pb.q <= 192 ? launch_once<T4, 3, false>(pb, a, st) : launch_once<T4, 4, false>(pb, a, st);
+}
+int launch_once_any(const Problem& pb, const SplitArgs& a, hipStream_t st)
+{
+    if (once_direct(pb))
+        return pb.p <= 128 ? launch_once<2, 2, true>(pb, a, st) : launch_once<4, 2, true>(pb, a, st);
+    return pb.p <= 128 ? launch_once_steps<2>(pb, a, st) : pb.p <= 192 ? launch_once_steps<3>(pb, a, st) : launch_once_steps<4>(pb, a, st);
 }
 
 // Rows whose vector between the factors fits the static workspace behind the packed weights, so that monarch_fwd_static
@@ -365,7 +398,7 @@ int fwd_split(const Problem& given, const void* x, const void* R, const void* L,
                           (uint16_t*)U};
         int rc;
         if (once_preferred(pb)) {
-            rc = pb.p <= 128 ? launch_once_steps<2>(pb, a, st) : pb.p <= 192 ? launch_once_steps<3>(pb, a, st) : launch_once_steps<4>(pb, a, st);
+            rc = launch_once_any(pb, a, st);
         } else {
             rc = launch_factor(pb, 1, a, st);
             if (!rc) rc = launch_factor(pb, 2, a, st);

@@ -307,3 +307,32 @@ def test_few_rows_in_one_launch(dims, rows):
     for name, g, w in zip(("y", "bias", "pre", "gelu"), got, want):
         assert torch.equal(g, w), name
     parity_util.check("once_%s.y" % (dims,), got[0].float().cpu().numpy(), oracle.fwd(x, R, L), 2e-2)
+
+
+# The same where no call leaves packed weights: R and L as they are, in one launch of up to 64 rows, against the rows of a 65-row batch,
+# which takes two launches: quarters of R inside a tile and across two, fewer K-steps than quarters of p, the longest p
+# and one past it, blocks of L that end a pair of column tiles.
+@pytest.mark.parametrize("dims", [(96, 96, 384), (256, 96, 96), (96, 96, 96), (16, 32, 32), (240, 128, 160), (144, 64, 96), (384, 96, 96)], ids=str)
+def test_few_rows_in_one_launch_on_weights_as_they_are(dims):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    p, q, s = dims
+    sh = synth.Shape("once_direct_%s" % (dims,), "bf16", 65, 4, p, q, s, config=996)
+    x, R, L, _ = synth.make_inputs(sh)
+    bias = synth.quantize(synth.normal(79, (sh.n_out,)), "bf16")
+    xd, Rd, Ld, bd = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L, bias))
+    ws = torch.empty(B.monarch_fwd_workspace_bytes(65, sh.n_in, 4, q, s, 1), dtype=torch.uint8, device="cuda")
+
+    def run(n, y=None):
+        return (B.monarch_fwd_ws(xd[:n], Rd, Ld, y=y, workspace=ws), B.monarch_fwd_bias(xd[:n], Rd, Ld, bd, workspace=ws),
+                *B.monarch_fwd_bias_gelu(xd[:n], Rd, Ld, bd, workspace=ws))
+
+    want = run(65)
+    parity_util.check("once_direct_%s.y" % (dims,), want[0].float().cpu().numpy(), oracle.fwd(x, R, L), 2e-2)
+    for rows in (1, 7, 32, 33, 64):
+        guard = torch.full((rows + 1, sh.n_out), 7.0, device="cuda", dtype=torch.bfloat16)
+        got = run(rows, guard[:rows])
+        assert bool((guard[rows] == 7.0).all())
+        for name, g, w in zip(("y", "bias", "pre", "gelu"), got, want):
+            assert torch.equal(g, w[:rows]), (name, rows)
