@@ -89,7 +89,7 @@ int mfma_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, v
 // Which of the forward kernels add pb.bias in their own epilogue (the others need launch_bias_add).
 bool mfma_fwd_fuses_bias(const Problem& pb, bool with_ws)
 {
-    if (with_ws && fwd_packed(pb)) return true;
+    if (with_ws && (fwd_packed(pb) || real32_mfma_supported(pb))) return true;
     // all of mfma_fwd's kernels have a bias epilogue
     return fwd_wide_supported(pb) || sq64_supported(pb) || sq16_supported(pb) || tiled_fwd_supported(pb);
 }

@@ -395,7 +395,7 @@ struct NatOut {
 //   kOutTFwd:    element (g, n) is stage-1 output f = g*Q + n; it goes to block c, index r of the permuted vector
 //   kOutTBwd:    element (g, n) is position g*Q + n of the permuted vector; it goes to block kk, index j of stage 1
 //   kOutNat:     out[row][g*Q + n]
-//   kOutScatter: out[row][n*k + g]
+//   kOutScatter: out[row][n*k + g], REAL: plus bias[n*k + g] where there is one
 // Grid: k * nsplit workgroups of Q/16 waves; workgroup (g, split) takes the row tiles split, split + nsplit, ...
 // (split = blockIdx % nsplit with nsplit a multiple of 8 keeps the blocks of one row range on one XCD).
 // REAL: real fp32 data and weights, block sizes 2P -> 2Q.  A float2 is then two consecutive values of a row, which
@@ -404,8 +404,8 @@ struct NatOut {
 // places separately (in the tiled workspace, to the pair slot [index / 2][row][index % 2] of the consumer's block).
 template <int P, int Q, int IN, int OUT, bool CONJT, bool REAL = false>
 __global__ void __launch_bounds__(kTileWaves<Q> * 64, P >= 56 || IN == kInGather ? 2 : 3)
-cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float2* __restrict__ out, int64_t B,
-              int k, int nsplit, int perm_b)
+cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, const float* __restrict__ bias, float2* __restrict__ out,
+              int64_t B, int k, int nsplit, int perm_b)
 {
     constexpr int NTHR = kTileWaves<Q> * 64;
     constexpr bool kWhole = Q % 16 == 0;  // else the last wave has outputs that do not exist
@@ -465,8 +465,9 @@ cstage_kernel(const float2* __restrict__ in, const float2* __restrict__ W, float
                 if (row >= B) continue;
                 if constexpr (REAL) {
                     float* outf = reinterpret_cast<float*>(out) + row * (2 * ld_out) + g;
-                    outf[(size_t)(2 * j) * k] = acc[2 * o];
-                    outf[(size_t)(2 * j + 1) * k] = acc[2 * o + 1];
+                    const int n0 = 2 * j * k, n1 = n0 + k;
+                    outf[n0] = bias ? acc[2 * o] + bias[g + n0] : acc[2 * o];
+                    outf[n1] = bias ? acc[2 * o + 1] + bias[g + n1] : acc[2 * o + 1];
                 } else {
                     out[row * ld_out + (size_t)j * k + g] = make_float2(acc[2 * o], acc[2 * o + 1]);
                 }
@@ -490,11 +491,14 @@ struct Scatter8 {
     static constexpr size_t kLds = 2 * (size_t)kRT * kRow * sizeof(float2);
 };
 
-// REAL (see cstage_kernel): the pieces of y are the eight blocks' values of one (row, output), 32 bytes.
+// REAL (see cstage_kernel): the pieces of y are the eight blocks' values of one (row, output), 32 bytes; a thread's are
+// those of one output, so its four values of the bias stay in registers (training step, 64 blocks of 64 with a bias and
+// without, us: 4000 rows 254.8 and 238.2, 16384 rows 912 and 842, what the bias's gradient takes; a pass over y of its
+// own made that difference 40 and 185).
 template <int P, int Q, bool REAL = false>
 __global__ void __launch_bounds__(512)
-cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, float2* __restrict__ out, int64_t B, int k,
-                 int nsplit)
+cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, const float* __restrict__ bias, float2* __restrict__ out,
+                 int64_t B, int k, int nsplit)
 {
     constexpr int MTG = kTileWaves<Q>;  // workgroups per (block octet, split)
     constexpr int STEPS = P / 8, NCH = STEPS >= 6 ? 2 : 1;  // pieces a tile's activations are fetched in
@@ -541,6 +545,10 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
             }
     };
     auto finish = [&](int64_t rt) { stage_finish<P, Q, kInT, false, REAL>(acc, T, W, rt, g, mt, k, 0, B, lane); };
+    f32x4 bv = {0.f, 0.f, 0.f, 0.f};
+    if constexpr (REAL) {
+        if (bias) bv = *reinterpret_cast<const f32x4*>(bias + (size_t)(32 * mt + (tid >> 1 & 31)) * k + 8 * oct + 4 * (tid & 1));
+    }
     // the results of one tile: exchange through LDS buffer it & 1 (one barrier per tile), then the 64-byte (REAL:
     // 32-byte) pieces of y
     auto emit = [&](int64_t rt, int it) {
@@ -559,7 +567,7 @@ cscatter8_kernel(const float2* __restrict__ T, const float2* __restrict__ W, flo
                 const float2 v1 = *reinterpret_cast<const float2*>(of + r * (2 * OROW) + nl * 8 + 4 * part + 2);
                 if (rt * kRT + r < B)
                     *reinterpret_cast<f32x4*>(outf + (rt * kRT + r) * (2 * ld_out) + (size_t)(32 * mt + nl) * k + 8 * oct + 4 * part) =
-                        f32x4{v0.x, v0.y, v1.x, v1.y};
+                        bias ? f32x4{v0.x + bv.x, v0.y + bv.y, v1.x + bv.z, v1.y + bv.w} : f32x4{v0.x, v0.y, v1.x, v1.y};
             }
         } else {
 #pragma unroll
@@ -1167,7 +1175,8 @@ int launch_stage(const Problem& pb, const void* in, const void* W, void* out, hi
     const int64_t grid = (int64_t)pb.k * nsplit;
     if (grid > 0x7fffffffLL) return -2;
     hipLaunchKernelGGL((cstage_kernel<M, M, IN, OUT, CONJT, REAL>), dim3((unsigned)grid), dim3(64 * kTileWaves<M>), 0, st, (const float2*)in,
-                       (const float2*)W, (float2*)out, pb.B, pb.k, nsplit, pb.perm_b() ? 1 : 0);
+                       (const float2*)W, REAL && OUT == kOutScatter ? (const float*)pb.bias : nullptr, (float2*)out, pb.B, pb.k, nsplit,
+                       pb.perm_b() ? 1 : 0);
     return hip_status(hipGetLastError());
 }
 
@@ -1194,7 +1203,7 @@ int launch_scatter8(const Problem& pb, const void* T, const void* W, void* out, 
     constexpr size_t lds = Scatter8<M, M>::kLds;
     if (allow_dynamic_lds((const void*)kern, lds) != hipSuccess) return -4;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), lds, st, (const float2*)T, (const float2*)W,
-                       (float2*)out, pb.B, pb.k, nsplit);
+                       REAL ? (const float*)pb.bias : nullptr, (float2*)out, pb.B, pb.k, nsplit);
     return hip_status(hipGetLastError());
 }
 

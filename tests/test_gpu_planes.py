@@ -231,3 +231,22 @@ def test_weight_gradients_in_large_tiles(shape, reading):
         error = np.linalg.norm(_wide(g) - w) / np.linalg.norm(w)
         print(shape, name, "%.2e" % error, flush=True)
         assert error <= 1e-6, (name, error)
+
+
+# The bias of real layers with blocks of 32 and 64, added where the second factor's results leave: the bits of the sum made afterwards,
+# for both kernels (block counts that are multiples of 8 and others) at the edges of row tiles, with something not finite in a row too.
+@pytest.mark.parametrize("rows", (1, 32, 33, 700))
+@pytest.mark.parametrize("k, m", [(8, 32), (32, 32), (5, 32), (64, 64), (16, 64), (9, 64)])
+def test_bias_of_real_blocks(k, m, rows):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    g = torch.Generator().manual_seed(k * m + rows)
+    x, R, L, b = (torch.randn(s, generator=g).cuda() for s in ((rows, k * m), (k, m, m), (k, m, m), (k * m,)))
+    x[rows // 2, 3] = float("inf")
+    ws = torch.empty(B.monarch_fwd_workspace_bytes(rows, k * m, k, m, m, 0), dtype=torch.uint8, device="cuda")
+    guard = torch.full((rows + 1, k * m), 7.0, device="cuda")
+    y = B.monarch_fwd_bias(x, R, L, b, y=guard[:rows], workspace=ws)
+    want = B.monarch_fwd_ws(x, R, L, workspace=ws) + b
+    assert bool((guard[rows] == 7.0).all())
+    assert torch.equal(torch.nan_to_num(y, 1.5, 2.5, 3.5), torch.nan_to_num(want, 1.5, 2.5, 3.5))
