@@ -116,9 +116,10 @@ split_stage2_kernel(const uint16_t* __restrict__ U, const uint16_t* __restrict__
 // Both factors in one launch, for a few rows on packed weights.  A workgroup computes 32 columns of one output block c, and
 // for them the vector that block c contracts by itself: those are the outputs c q/4 .. (c + 1) q/4 of every block of the
 // first factor, so that the workgroups of a block read the same quarter of R (128 KiB at 256 x 256) and none waits for
-// another.  Eight waves: wave = (block kk, one of the two 32-row tiles of R that the quarter touches), the contraction in
-// four parts that are added up as in split_stage1 (the same bits); then one wave multiplies with L, whose fragments it
-// requested at the start.  A workgroup's block goes by its XCD, for the quarter of R to come through two L2s.
+// another.  Eight waves: wave = (block kk, one of the two 32-row tiles of R that the quarter touches; once_covers says
+// where there are no more), the contraction in four parts that are added up as in split_stage1 (the same bits); then one
+// wave multiplies with L, whose fragments it requested at the start.  A workgroup's block goes by its XCD, for the
+// quarter of R to come through two L2s.
 // Bound by latency: one of memory, the way of the quarter through the L1 (2500 clocks at 256 x 256) and two chains of
 // products.  On the GPU alone, 256 x 1024 blocks: 8 rows 6.5 us in two launches, 5.7 in one, 32 rows 6.9 and 6.8, 64 rows
 // 7.0 and 7.2; 192 x 768: 8 rows 6.3 and 5.0, 64 rows 6.9 and 6.2; 512 x 128 (the quarter of R as large, four times the
@@ -307,6 +308,17 @@ int launch_factor(const Problem& pb, int stage, const SplitArgs& a, hipStream_t 
     return tiles <= 512 ? launch_steps<1, 1, 4>(pb, stage, a, st) : launch_steps<1, 2, 2>(pb, stage, a, st);
 }
 
+// split_once_kernel has waves for two 32-row tiles of R in a quarter c q/4 .. (c + 1) q/4.  Of the multiples of 32 up to
+// 256 only q = 224 has quarters that touch three (56 .. 111 and 112 .. 167).
+constexpr bool once_covers(int q)
+{
+    for (int c = 0; c < 4; ++c)
+        if (((c + 1) * q / 4 - 1) / 32 - c * q / 4 / 32 > 1) return false;
+    return true;
+}
+static_assert(once_covers(32) && once_covers(64) && once_covers(96) && once_covers(128) && once_covers(160) && once_covers(192) && !once_covers(224) &&
+              once_covers(256));
+
 // Where one launch does for both factors (split_once_kernel): packed weights, p up to 256, one row tile, two where the
 // quarter of R is small.  Weights as they are where no call packs them for the next, with q up to 128 and p up to 256,
 // two row tiles; two launches and one, host included, us: blocks of 96 x 96 and 384 x 96 (width 384 -> 1536), 8 rows 8.7
@@ -315,7 +327,7 @@ int launch_factor(const Problem& pb, int stage, const SplitArgs& a, hipStream_t 
 bool once_direct(const Problem& pb) { return !fwd_frag_supported(pb) && pb.q <= 128 && pb.p <= 256 && pb.B <= 64; }
 bool once_preferred(const Problem& pb)
 {
-    return once_direct(pb) || (pb.ws_packed() && pb.p <= 256 && pb.B <= (pb.p * pb.q <= 192 * 192 ? 64 : 32));
+    return once_covers(pb.q) && (once_direct(pb) || (pb.ws_packed() && pb.p <= 256 && pb.B <= (pb.p * pb.q <= 192 * 192 ? 64 : 32)));
 }
 // T4, 4 K4: K-steps of a quarter of the first contraction and of the second
 template <int T4, int K4, bool DIRECT>

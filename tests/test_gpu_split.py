@@ -336,3 +336,35 @@ def test_few_rows_in_one_launch_on_weights_as_they_are(dims):
         assert bool((guard[rows] == 7.0).all())
         for name, g, w in zip(("y", "bias", "pre", "gelu"), got, want):
             assert torch.equal(g, w[:rows]), (name, rows)
+
+
+# Shapes without a fused kernel whose packed weights leave the vector between the factors little of the workspace, for every q above
+# the 128 that the one-launch kernel takes on weights as they are: batches in slices whose later ones find the weights packed, and so
+# short that they are a few rows (42: 32 and 10; 100: 32, 32, 32 and 4).  Through both calls that have a workspace, with bias and
+# nonlinearity.
+@pytest.mark.parametrize("rows", (42, 100))
+@pytest.mark.parametrize("dims", [(256, 224, 4384), (224, 224, 4416), (256, 160, 6240), (128, 160, 6368), (256, 192, 5152), (256, 256, 3808)], ids=str)
+def test_short_slices_without_a_fused_kernel(dims, rows):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import binding as B
+    p, q, s = dims
+    room = B.MONARCH_STATIC_WORKSPACE_BYTES - 8 * q * (p + s)
+    assert 32 <= room // (8 * q) < 64   # rows of the vector between the factors
+    sh = synth.Shape("slices_%s" % (dims,), "bf16", rows, 4, p, q, s, config=1010)
+    x, R, L, _ = synth.make_inputs(sh)
+    bias = synth.quantize(synth.normal(82, (sh.n_out,)), "bf16")
+    xd, Rd, Ld, bd = (torch.from_numpy(np.ascontiguousarray(a)).cuda().to(torch.bfloat16) for a in (x, R, L, bias))
+    want, want_bias = oracle.fwd(x, R, L), oracle.fwd_bias(x, R, L, bias)
+
+    def check(name, got, want):
+        parity_util.check("%s.%s" % (sh.name, name), got.float().cpu().numpy(), want, 2e-2)
+
+    y, ys = B.monarch_fwd_ws(xd, Rd, Ld), torch.empty((rows, sh.n_out), dtype=torch.bfloat16, device="cuda")
+    check("y", y, want)
+    B.monarch_fwd_static(xd, Rd, Ld, ys)
+    assert torch.equal(y, ys)
+    check("bias", B.monarch_fwd_bias(xd, Rd, Ld, bd), want_bias)
+    pre, act = B.monarch_fwd_bias_gelu(xd, Rd, Ld, bd)
+    check("pre", pre, want_bias)
+    check("gelu", act, activation.gelu(want_bias))
