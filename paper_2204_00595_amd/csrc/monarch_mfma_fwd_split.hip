@@ -362,11 +362,27 @@ int64_t fit_rows(const Problem& pb)
     if (packed + align_up(pb.B * row, 256) <= room) return pb.B;
     return packed < room ? (int64_t)((room - packed) / row / 32 * 32) : 0;
 }
-// Longer batches go in slices of about the same length.
-int64_t slice_rows(const Problem& pb)
+// Longer batches go in slices of about the same length: `n`, each but the last of `rows`.
+struct Slices {
+    int64_t n, rows;
+};
+Slices slices(const Problem& pb)
 {
     const int64_t fit = fit_rows(pb), n = (pb.B + fit - 1) / fit;
-    return n == 1 ? pb.B : ((pb.B + n - 1) / n + 31) / 32 * 32;
+    return Slices{n, n == 1 ? pb.B : ((pb.B + n - 1) / n + 31) / 32 * 32};
+}
+// Where they pay: every slice reads the weights again, in launches of its own, while the shape-generic kernels, which run
+// otherwise, take the same time for any batch until their output is long.  Up to seven slices and 80 Mi output values;
+// shape-generic kernels and slices, us: blocks of 256 x 256 and 256 x 512, 3360 rows (two slices) 64 and 26, 8192 rows
+// (three) 66 and 49; 1024 x 256 and 256 x 2048, 4096 rows (four) 236 and 105; 256 x 256 and 256 x 3072, 3840 rows (five)
+// 214 and 140, 4608 rows (six) 213 and 166, 6144 rows (eight) 214 and 219 to 235, 8192 rows (eleven) 214 and 311; 1024 x
+// 256 and 256 x 2880, 768 rows (four of 192) 286 and 68, 8192 rows (43) 287 and 675; longer outputs, 256 x 192 and 192 x
+// 4096, 5120 rows (five, 80 Mi) 211 and 190, 6528 rows (six) 211 and 258; 128 x 128 and 128 x 4096, 5120 rows (two, 80 Mi)
+// 141 and 114, 7936 rows (two) 161 and 175.  The shapes with a fused kernel never have more than two.
+bool slices_pay(const Problem& pb)
+{
+    const int64_t n = slices(pb).n;
+    return n == 1 || (n <= 7 && pb.B * pb.n_out() <= (80 << 20));
 }
 
 }  // namespace
@@ -391,7 +407,7 @@ bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
 bool fwd_split_preferred(const Problem& pb)
 {
     const int64_t most = !fwd_frag_supported(pb) ? 8192 : pb.s < pb.p ? 4352 : pb.s > pb.p && pb.q > 128 ? 2048 : 3072;
-    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= most && fit_rows(pb) > 0;
+    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= most && fit_rows(pb) > 0 && slices_pay(pb);
 }
 
 size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)fit_rows(pb) * pb.kq() * 2, 256); }
@@ -400,7 +416,7 @@ int fwd_split(const Problem& given, const void* x, const void* R, const void* L,
               hipStream_t st)
 {
     Problem pb = given;
-    const int64_t rows = slice_rows(given);
+    const int64_t rows = slices(given).rows;
     for (int64_t b = 0; b < given.B; b += rows) {
         pb.B = given.B - b < rows ? given.B - b : rows;
         const size_t to = (size_t)b * pb.n_out();

@@ -48,9 +48,11 @@ def test_short_batch_forward(case):
     assert torch.equal(act, act2)
 
 
-# the last rows of narrow, wide and square layers, and the first past them; batches in slices, with and without packed weights
+# the last rows of narrow, wide and square layers, and the first past them; batches in slices, with and without packed weights, with and
+# without a fused kernel (four slices and an odd last one, two; one row more than seven can hold; two)
 @pytest.mark.parametrize("case", [(4352, 128, 64, 64), (4353, 128, 64, 64), (2048, 192, 192, 768), (2049, 192, 192, 576), (3072, 64, 64, 128),
-                                  (3073, 192, 192, 192), (2848, 1024, 256, 256), (4352, 1024, 256, 256), (8190, 384, 96, 96)], ids=str)
+                                  (3073, 192, 192, 192), (2848, 1024, 256, 256), (4352, 1024, 256, 256), (8190, 384, 96, 96), (1001, 256, 224, 4096),
+                                  (2047, 128, 160, 5120), (2241, 256, 224, 4096), (6235, 160, 160, 160)], ids=str)
 def test_forward_at_the_limits_of_the_short_batch_kernels(case):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -560,3 +560,16 @@ def test_kernel_name_does_not_depend_on_the_kernels_of_short_batches(binding):
     assert names(4096, 4, 256, 1024, 1) == ["mfma_fwd_tiled_bf16", "generic_bwd", "mfma_fwd_tiled_bf16", "generic_fwd_t"]
     # the shape-generic kernels, with and without a workspace
     assert names(196, 4, 49, 64, 1) == names(768, 4, 192, 192, 0) == ["generic_fwd", "generic_bwd", "generic_fwd", "generic_fwd_t"]
+
+
+# Four-block bf16 layers without a fused kernel whose packed weights leave little of the workspace: batches go in slices while there are no
+# more than seven (of 192, 768 and 320 rows here) and the output is no longer than 80 Mi values; past that the shape-generic kernels
+# run, which ask for no workspace.
+@pytest.mark.parametrize("p, q, s, last", [(1024, 256, 2880, 7 * 192), (256, 256, 3072, 7 * 768), (256, 224, 4096, 7 * 320), (256, 192, 4096, 5120),
+                                           (128, 128, 4096, 5120), (1024, 256, 512, 8192), (160, 160, 160, 8192), (96, 96, 384, 8192)])
+def test_batches_in_slices_end(binding, p, q, s, last):
+    def need(rows):
+        return binding.monarch_fwd_workspace_bytes(rows, 4 * p, 4, q, s, 1)
+
+    assert 8 * q * (p + s) < need(last) <= binding.MONARCH_STATIC_WORKSPACE_BYTES
+    assert need(last + 1) == 0
