@@ -355,21 +355,25 @@ int launch_once_any(const Problem& pb, const SplitArgs& a, hipStream_t st)
 }
 
 // Rows whose vector between the factors fits the static workspace behind the packed weights, so that monarch_fwd_static
-// runs the same kernels as monarch_fwd_ws: all of the batch, or whole tiles of it; 0: not even one.
+// runs the same kernels as monarch_fwd_ws: what a call asks room for, no less for a longer batch than for a shorter one.
+// A row takes q / 32 times 256 bytes.
 int64_t fit_rows(const Problem& pb)
 {
     const size_t packed = fwd_frag_packed(pb), row = (size_t)pb.kq() * 2, room = MONARCH_STATIC_WORKSPACE_BYTES;
-    if (packed + align_up(pb.B * row, 256) <= room) return pb.B;
-    return packed < room ? (int64_t)((room - packed) / row / 32 * 32) : 0;
+    const int64_t fit = packed < room ? (int64_t)((room - packed) / row) : 0;
+    return pb.B < fit ? pb.B : fit;
 }
-// Longer batches go in slices of about the same length: `n`, each but the last of `rows`.
+// Longer batches go in slices of about the same length: `n`, each but the last of `rows`, whole tiles.
 struct Slices {
     int64_t n, rows;
 };
 Slices slices(const Problem& pb)
 {
-    const int64_t fit = fit_rows(pb), n = (pb.B + fit - 1) / fit;
-    return Slices{n, n == 1 ? pb.B : ((pb.B + n - 1) / n + 31) / 32 * 32};
+    const int64_t fit = fit_rows(pb), most = fit / 32 * 32;
+    if (fit == pb.B) return Slices{1, pb.B};
+    if (most == 0) return Slices{0, 0};
+    const int64_t n = (pb.B + most - 1) / most;
+    return Slices{n, ((pb.B + n - 1) / n + 31) / 32 * 32};
 }
 // Where they pay: every slice reads the weights again, in launches of its own, while the shape-generic kernels, which run
 // otherwise, take the same time for any batch until their output is long.  Up to seven slices and 80 Mi output values;
@@ -382,7 +386,7 @@ Slices slices(const Problem& pb)
 bool slices_pay(const Problem& pb)
 {
     const int64_t n = slices(pb).n;
-    return n == 1 || (n <= 7 && pb.B * pb.n_out() <= (80 << 20));
+    return n == 1 || (n > 0 && n <= 7 && pb.B * pb.n_out() <= (80 << 20));
 }
 
 }  // namespace
@@ -407,7 +411,7 @@ bool fwd_split_supported(const Problem& pb)  // a wave holds 16 K-steps at most
 bool fwd_split_preferred(const Problem& pb)
 {
     const int64_t most = !fwd_frag_supported(pb) ? 8192 : pb.s < pb.p ? 4352 : pb.s > pb.p && pb.q > 128 ? 2048 : 3072;
-    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= most && fit_rows(pb) > 0 && slices_pay(pb);
+    return fwd_split_supported(pb) && pb.B > 0 && pb.B <= most && slices_pay(pb);
 }
 
 size_t fwd_split_mid_bytes(const Problem& pb) { return align_up((size_t)fit_rows(pb) * pb.kq() * 2, 256); }

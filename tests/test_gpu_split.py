@@ -234,7 +234,7 @@ def test_calls_on_two_streams_share_packed_weights():
 
 
 # the vector between the factors is kept in tiles of 32 rows, the last one no longer than it is: nothing past what the queries name
-@pytest.mark.parametrize("case", [(1, 64, 64, 64), (33, 128, 64, 64), (545, 256, 256, 768), (2817, 128, 128, 128)], ids=str)
+@pytest.mark.parametrize("case", [(1, 64, 64, 64), (33, 128, 64, 64), (545, 256, 256, 768), (2817, 128, 128, 128), (57, 128, 160, 6368), (58, 128, 160, 6368)], ids=str)
 def test_tiles_stay_inside_the_workspace(case):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")

@@ -573,3 +573,14 @@ def test_batches_in_slices_end(binding, p, q, s, last):
 
     assert 8 * q * (p + s) < need(last) <= binding.MONARCH_STATIC_WORKSPACE_BYTES
     assert need(last + 1) == 0
+
+
+# ... and what they ask for does not shrink as the batch grows: a workspace sized for any of these batches serves every shorter one, and a
+# short one would run on other kernels without a word.
+@pytest.mark.parametrize("p, q, s", [(160, 160, 160), (224, 224, 224), (256, 256, 1024), (96, 96, 384), (1024, 256, 512), (256, 224, 4096),
+                                     (256, 224, 4384), (224, 96, 1056)])
+def test_workspace_of_a_longer_batch_serves_a_shorter_one(binding, p, q, s):
+    need = [binding.monarch_fwd_workspace_bytes(rows, 4 * p, 4, q, s, 1) for rows in range(1, 8194)]
+    packed = 8 * q * (p + s)
+    on = [n for n in need if n > packed]   # the vector between the factors is in it: the kernels of short batches
+    assert on and need[:len(on)] == on and on == sorted(on) and on[-1] <= binding.MONARCH_STATIC_WORKSPACE_BYTES
