@@ -268,7 +268,8 @@ int monarch_bwd_saved(const void* dy, const void* x, const void* saved, size_t s
 
 /* monarch_fwd_bias_save and monarch_bwd_saved for a layer in training, which keeps the vector wherever its backward is faster for
  * it: also for bf16, k = 64 blocks of 64, where the calls above recompute.  monarch_kept_bytes is 0 where nothing is kept; there
- * the two calls are those above.  Errors as theirs; MONARCH_FLAG_GENERIC keeps nothing. */
+ * the two calls are those above.  What is kept lies in memory from the forward to the backward: k*q values a row (64 blocks of 64: 8 KB,
+ * 134 MB at 16384 rows) and some copies of the weights.  Errors as theirs; MONARCH_FLAG_GENERIC keeps nothing. */
 size_t monarch_kept_bytes(int64_t batch, int n_in, int k, int q, int s,
                           monarch_dtype dtype, unsigned flags);
 int monarch_fwd_keep(const void* x, const void* R, const void* L, const void* bias, void* y,
@@ -281,6 +282,11 @@ int monarch_bwd_kept(const void* dy, const void* x, const void* kept, size_t kep
                      int64_t batch, int n_in, int k, int q, int s,
                      monarch_dtype dtype, void* stream,
                      void* workspace, size_t workspace_bytes, unsigned flags);
+
+/* Bytes of device scratch with which monarch_bwd_kept runs best on what monarch_fwd_keep kept: monarch_bwd_workspace_bytes, less the
+ * place of the vector between the factors for bf16, k = 64 blocks of 64. */
+size_t monarch_bwd_kept_workspace_bytes(int64_t batch, int n_in, int k, int q, int s,
+                                        monarch_dtype dtype, unsigned flags);
 
 /* Bytes of device scratch with which monarch_bwd and monarch_bwd_bias run best (never 0 for a valid problem; 0 on invalid
  * arguments).  A batch may ask for more than a longer one does, but accepts less: a workspace sized for the longer batch serves

@@ -35,7 +35,7 @@ EXPORTS = (
     "monarch_fwd_packed", "monarch_fwd_packed_scratch_bytes", "monarch_bwd",
     "monarch_bwd_bias", "monarch_fwd_bias_gelu", "monarch_bwd_bias_gelu_in",
     "monarch_bwd_workspace_bytes",
-    "monarch_fwd_t", "monarch_fwd_t_workspace_bytes", "monarch_saved_bytes", "monarch_fwd_save", "monarch_fwd_bias_save", "monarch_bwd_saved", "monarch_kept_bytes", "monarch_fwd_keep", "monarch_bwd_kept", "monarch_fwd_c64", "monarch_fwd_h_c64", "monarch_bwd_c64", "monarch_fwd_c64_ws", "monarch_fwd_h_c64_ws", "monarch_bwd_c64_ws", "monarch_c64_workspace_bytes", "monarch_dft_factors", "monarch_to_dense", "monarch_project", "monarch_kernel_name", "monarch_status_string", "monarch_version", "monarch_stream_copy", "monarch_launch_probe",
+    "monarch_fwd_t", "monarch_fwd_t_workspace_bytes", "monarch_saved_bytes", "monarch_fwd_save", "monarch_fwd_bias_save", "monarch_bwd_saved", "monarch_kept_bytes", "monarch_fwd_keep", "monarch_bwd_kept", "monarch_bwd_kept_workspace_bytes", "monarch_fwd_c64", "monarch_fwd_h_c64", "monarch_bwd_c64", "monarch_fwd_c64_ws", "monarch_fwd_h_c64_ws", "monarch_bwd_c64_ws", "monarch_c64_workspace_bytes", "monarch_dft_factors", "monarch_to_dense", "monarch_project", "monarch_kernel_name", "monarch_status_string", "monarch_version", "monarch_stream_copy", "monarch_launch_probe",
 )
 
 _lib = None
@@ -103,6 +103,8 @@ def lib() -> ctypes.CDLL:
         L.monarch_fwd_keep.argtypes = L.monarch_fwd_bias_save.argtypes
         L.monarch_bwd_kept.restype = ci
         L.monarch_bwd_kept.argtypes = L.monarch_bwd_saved.argtypes
+        L.monarch_bwd_kept_workspace_bytes.restype = sz
+        L.monarch_bwd_kept_workspace_bytes.argtypes = L.monarch_saved_bytes.argtypes
         L.monarch_fwd_c64.restype = ci
         L.monarch_fwd_c64.argtypes = [vp, vp, vp, vp, i64, ci, ci, ci, ci, vp, cu]
         L.monarch_fwd_h_c64.restype = ci

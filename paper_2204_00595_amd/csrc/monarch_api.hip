@@ -507,6 +507,15 @@ int monarch_bwd_bias(const void* dy, const void* x, const void* R, const void* L
                              workspace_bytes, flags);
 }
 
+size_t monarch_bwd_kept_workspace_bytes(int64_t batch, int n_in, int k, int q, int s, monarch_dtype dtype, unsigned flags)
+{
+    Problem pb;
+    if (make_problem(pb, batch, n_in, k, q, s, (int)dtype, flags)) return 0;
+    if (!keeps_sq64(pb)) return monarch_bwd_workspace_bytes(batch, n_in, k, q, s, dtype, flags);
+    pb.saved = &pb;  // not read: that there is one
+    return bwd_need(pb, FAM_MFMA);
+}
+
 int monarch_bwd_saved(const void* dy, const void* x, const void* saved, size_t saved_bytes, const void* R,
                       const void* L, void* dx, void* dR, void* dL, void* dbias, int64_t batch, int n_in, int k, int q,
                       int s, monarch_dtype dtype, void* stream, void* workspace, size_t workspace_bytes, unsigned flags)

@@ -672,7 +672,7 @@ Plan64 make_plan64(const Problem& pb, size_t room = SIZE_MAX)
     pl.p_bf16 = pb.wgrad_f32() || pb.B <= 256 ? 0 : 1;
     size_t off = 0;
     const size_t act = align_up((size_t)(pb.B > 0 ? pb.B : 1) * N64 * 2, 256);
-    pl.off_u = off;  off += act;
+    pl.off_u = off;  off += pb.saved ? 0 : act;
     pl.off_du = off; off += act;
     pl.off_rp = off; off += align_up(pb.n_R() * 2, 256);
     const size_t chunk = (size_t)M64 * M64 * M64 * (pl.p_bf16 ? 2 : 4), fit = room > off ? (room - off) / (2 * chunk) : 0;
@@ -732,7 +732,9 @@ int fwd_sq64_ws(const Problem& pb, const void* x, const void* R, const void* L, 
 // ... that keeps the vector between the factors for the backward, which then neither reads x nor multiplies for it: a write
 // of U in place of a kernel that reads x and writes U.  kept = U, then the packed factors of this call.  Training step of
 // the layer, 16384 rows: 329 -> 287 us (forward 70 -> 90, without 54 + 5 in the backward), 4096 rows 106 -> 89; with a bias,
-// which took a pass over y and one over dy, 414 -> 290 and 137 -> 95.
+// which took a pass over y and one over dy, 414 -> 290 and 137 -> 95.  The price is memory from the forward to the
+// backward, 8 KB a row (134 MB at 16384 rows), which the workspace of that backward then does not need
+// (monarch_bwd_kept_workspace_bytes).
 size_t sq64_mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B > 0 ? pb.B : 1) * N64 * 2, 256); }
 size_t sq64_kept_bytes(const Problem& pb) { return sq64_mid_bytes(pb) + fwd_sq64_workspace(pb); }
 int fwd_sq64_keep(Problem pb, const void* x, const void* R, const void* L, void* y, void* kept, hipStream_t st)

@@ -318,7 +318,8 @@ Grads bwd(const char* name, const Tensor& dy, const Tensor& x, const Tensor& x_p
     g.dL = out(g.dL, "dL", {sh.k, sh.s, sh.q}, gt, sh.device);
     if (want_dbias || g.dbias.defined()) g.dbias = out(g.dbias, "dbias", {sh.n_out()}, gt, sh.device);
     if (!ws.defined()) {
-        const size_t need = monarch_bwd_workspace_bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
+        auto bytes = layer && saved.defined() ? monarch_bwd_kept_workspace_bytes : monarch_bwd_workspace_bytes;
+        const size_t need = bytes(sh.B, (int)sh.n_in(), (int)sh.k, (int)sh.q, (int)sh.s, sh.code(), flags);
         if (need) ws = w.scratch(need);
     }
     const Bytes b(ws), sv(saved);

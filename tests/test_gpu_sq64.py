@@ -71,3 +71,41 @@ def test_layer_keeps_the_vector(rows, bias):
         assert bool(((got.double() - exact).abs() <= 2.0 ** -8 * exact.abs() + 1e-6 * size).all())
     got = B.monarch_bwd_bias(dy, x, R, L, flags=B.MONARCH_FLAG_WGRAD_F32)[3]
     assert bool(((got.double() - exact).abs() <= 1e-6 * size).all())
+
+
+# ... whose backward's workspace has no place for a vector that it does not recompute: nothing behind what is asked for is written, the
+# bits are those of a longer workspace, and the layer's backward takes no more memory than that and its gradients.
+@pytest.mark.gpu
+@pytest.mark.parametrize("rows", [33, 2113])
+def test_backward_of_a_kept_vector_needs_no_place_for_it(rows):
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    from paper_2204_00595_amd import autograd
+    from paper_2204_00595_amd import binding as B
+    lib, dims, vector = B.lib(), (rows, 4096, 64, 64, 64, B.MONARCH_BF16), rows * 8192
+    need, whole = lib.monarch_bwd_kept_workspace_bytes(*dims, 0), lib.monarch_bwd_workspace_bytes(*dims, 0)
+    assert need == whole - vector
+    gen = torch.Generator(device="cuda").manual_seed(70 + rows)
+    x, dy, R, L = (torch.randn(shape, generator=gen, device="cuda").to(torch.bfloat16)
+                   for shape in ((rows, 4096), (rows, 4096), (64, 64, 64), (64, 64, 64)))
+    st = int(torch.cuda.current_stream().cuda_stream)
+    kept = torch.empty(lib.monarch_kept_bytes(*dims, 0), dtype=torch.uint8, device="cuda")
+    y = torch.empty_like(dy)
+    assert lib.monarch_fwd_keep(*(t.data_ptr() for t in (x, R, L)), None, y.data_ptr(), kept.data_ptr(), kept.numel(), *dims, st, 0) == 0
+    results = []
+    for room in (need, whole):
+        ws = torch.full((room + 65536,), 0xA5, dtype=torch.uint8, device="cuda")
+        g = [torch.empty_like(t) for t in (x, R, L)] + [torch.empty(4096, dtype=torch.bfloat16, device="cuda")]
+        assert lib.monarch_bwd_kept(*(t.data_ptr() for t in (dy, x, kept)), kept.numel(), R.data_ptr(), L.data_ptr(),
+                                    *(t.data_ptr() for t in g), *dims, st, ws.data_ptr(), room, 0) == 0
+        assert bool((ws[room:] == 0xA5).all())
+        results.append(g)
+    assert all(torch.equal(a, b) for a, b in zip(*results))
+    layer = autograd.MonarchLinear(4096, 4096, nblocks=64, bias=True, q=64, device="cuda", dtype=torch.bfloat16)
+    y = layer(x.clone().requires_grad_(True))
+    torch.cuda.synchronize()
+    before = torch.cuda.memory_allocated()
+    torch.cuda.reset_peak_memory_stats()
+    y.backward(dy)
+    gradients = vector + 2 * 2 * 64 ** 3 + 2 * 4096
+    assert torch.cuda.max_memory_allocated() - before <= need + gradients + 4 * 512   # a piece is a multiple of 512 bytes
