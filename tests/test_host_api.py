@@ -584,3 +584,11 @@ def test_workspace_of_a_longer_batch_serves_a_shorter_one(binding, p, q, s):
     packed = 8 * q * (p + s)
     on = [n for n in need if n > packed]   # the vector between the factors is in it: the kernels of short batches
     assert on and need[:len(on)] == on and on == sorted(on) and on[-1] <= binding.MONARCH_STATIC_WORKSPACE_BYTES
+
+
+# The weight gradients of the shape-generic contractions in small tiles: as many chunks of the batch, each a multiple of 32 rows, as come
+# from dividing it up; rounded up to more rows, fewer and longer chunks leave CUs waiting for the longest.
+@pytest.mark.parametrize("rows, k, p, q, s, chunks", [(6304, 8, 100, 40, 128, 29), (3231, 12, 48, 48, 192, 21), (3231, 12, 80, 80, 150, 15)])
+def test_chunks_of_the_weight_gradients(binding, rows, k, p, q, s, chunks):
+    need = binding.monarch_bwd_workspace_bytes(rows, k * p, k, q, s, 0)
+    assert need >= 2 * rows * k * q * 4 + chunks * k * q * (p + s) * 4
