@@ -1197,10 +1197,12 @@ int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t 
 // than the small ones and their chunks still have 256 rows: every value is split half or a third as often (768 -> 768 fp32,
 // 12608 rows, both contractions 77 us in 64 x 64 tiles, 53 in 192 x 192, of which the matrix cores alone take 30; backward
 // 176 and 152, at 1024 rows 41 and 48; 1024 -> 4096 in 128 x 128 tiles, 12608 rows 617 and 564, 4096 rows 212 and 201; 128
-// x 512 blocks, 4096 rows 83 and 94).  At least 128 rows each, in steps of 32 (with 64 x 64 tiles in steps of 64, chunks
-// were up to an eighth longer than the rest: backward of 12 fp32 blocks of 48 x 48 and 48 x 192, 3231 rows 105 us and 85,
-// of 12 of 80 x 80 and 80 x 150 133 and 119), and whole sets of eight, since a chunk
-// belongs to an XCD (4096 -> 1024 fp32 with three chunks: three XCDs busy, 1088 us; with eight 465 us).
+// x 512 blocks, 4096 rows 83 and 94).  At least 128 rows each, and whole sets of eight, since a chunk
+// belongs to an XCD (4096 -> 1024 fp32 with three chunks: three XCDs busy, 1088 us; with eight 465 us).  In steps of 32
+// rows: in steps of 64 the chunks were up to a fifth longer than an even share, and the launch waits for the longest
+// (backward of 12 fp32 blocks of 48 x 48 and 48 x 192, 3231 rows 105 us and 85, of 12 of 80 x 80 and 80 x 150 133 and 119;
+// two of 64 shapes lost 3 and 5 %).  One set of eight small tiles stays in steps of 64: 32 gain 1 to 3 % there, and a
+// batch would ask for as much room as a slightly longer one.
 struct WgradPlan {
     int cfg;
     int nz;
@@ -1227,7 +1229,8 @@ WgradPlan wgrad_plan(const Problem& pb, size_t room = SIZE_MAX)  // room: bytes 
         z = nz;
     }
     for (;; z = pl.nz - 1) {
-        pl.rows = tiles(tiles(rows, (int)z), 32) * 32;
+        const int step = pl.cfg == 0 && z <= 8 ? 64 : 32;
+        pl.rows = tiles(tiles(rows, (int)z), step) * step;
         pl.nz = (int)tiles(rows, (int)pl.rows);
         if (part_bytes(pb, pl.nz) <= room || pl.nz == 1) return pl;
     }
