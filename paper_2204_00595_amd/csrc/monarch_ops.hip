@@ -1052,25 +1052,43 @@ int pick_tile(int64_t M, int N, int G, bool pieces)
 
 // What a contraction reads and writes: the rows of the blocks interleaved on the way in or out, or on neither side.
 enum Sides { kPlain, kSpreadOut, kSpreadIn };
-// Columns per wave (NT tiles of 32) of the kernel with the weights laid out as planes, 0: not there.  It gains where a side
-// is interleaved, which it reads and writes in whole lines, and where splitting a row once instead of once per 64 columns
-// tells; its workgroups run one to a CU, so that it loses where the last round of them is far from full, and it pays 3 to 5
-// us for the weights.  us, contractions of 64-column tiles first: 768 -> 768 fp32 x M^T 12608 rows 80 and 67, 8192 rows
-// (half a round) 47 and 58; x M 83 and 73; 768 -> 3072 12608 rows 166 and 155, x M 182 and 140; 1024 -> 1024 fp32 x M^T
-// 16384 rows (two rounds of 128 columns) 133 and 126, 8192 rows and 1024 -> 4096 at 2048 (one round) 70 and 67, 50 and
-// 55; the plain contraction of 3072 -> 768 x M, four column tiles, 12608 rows: 146 and 163; with 96 of 128 columns: 384 ->
-// 384 16384 rows 36 and 45; 40 x 33 blocks, k = 8, bf16, 16384 rows 29 and 20, x M 35 and 25; in fp32 x M 22 and 26 at
-// 8192 rows; 49 x 49 bf16, 32768 rows 31 and 27; 20 x 20, k = 4, 16384 rows 12.2 and 13.5.
-int rows_tile(const Problem& pb, int N, Sides sides)
+// Columns per wave (NT tiles of 32) of the kernel with the weights laid out as planes.
+int rows_tile(int N) { return N <= 64 ? 1 : tiles(N, 192) * 192 <= tiles(N, 128) * 128 ? 3 : 2; }
+// Where that kernel gains.  It reads and writes an interleaved side in whole lines and splits a row once instead of once per
+// 64 columns; its workgroups run one to a CU, so that it loses where the last round of them is far from full, and the
+// weights are a launch of 3 to 5 us before it.  us, contractions of 64-column tiles first: 768 -> 768 fp32 x M^T 12608 rows
+// 80 and 67, 8192 rows (half a round) 47 and 58; x M 83 and 73; 768 -> 3072 12608 rows 166 and 155, x M 182 and 140; 1024
+// -> 1024 fp32 x M^T 16384 rows (two rounds of 128 columns) 133 and 126, 8192 rows and 1024 -> 4096 at 2048 (one round) 70
+// and 67, 50 and 55; with 96 of 128 columns: 384 -> 384 16384 rows 36 and 45; 40 x 33 blocks, k = 8, bf16, 16384 rows 29
+// and 20, x M 35 and 25; in fp32 x M 22 and 26 at 8192 rows.
+// kBeside: where it gains less than the launch costs, another contraction of the call has to share it, which takes no
+// more time for it.  Those are the ones with neither side interleaved (fp32, four blocks, 12608 rows: 132 x 16, alone in
+// the call, 18 and 23; 16384 rows, 160 x 72 41 and 47; beside another, 12608 rows, 170 x 180 82 and 76; two rounds of
+// them no better than 64-column tiles there either; bf16 with fp32 rows gains alone where the round is nearly full,
+// 14000 rows, 150 x 120 40 and 35), one round of 64 columns (bf16, four blocks of 49 x 49, 16384 rows 22 and 27, of 60 x
+// 80 21 and 28; both contractions of sixteen of 56 x 56, 4096 rows, 37 and 22), and the second factor of bf16 layers with
+// four blocks in 128 columns (240 x 200, 24000 rows 83 and 94; beside another, 128 x 128, 32768 rows 55 and 54).
+enum Gain { kNever, kBeside, kAlone };
+Gain rows_gain(const Problem& pb, int N, int K, Sides sides, bool wide)  // wide: the rows are fp32
 {
-    if (pb.k % 4) return 0;
-    const int nt = N <= 64 ? 1 : tiles(N, 192) * 192 <= tiles(N, 128) * 128 ? 3 : 2;
+    if (pb.k % 4) return kNever;
+    const int nt = rows_tile(N);
+    const bool bf16 = pb.dtype == 1;
     const int64_t cols = tiles(N, 64 * nt), wgs = tiles(pb.B, kRows) * (pb.k / 4) * cols, slots = tiles(wgs, kCUs) * kCUs;
-    if (sides == kPlain && !(nt == 3 && cols == 1) && !(nt == 1 && pb.dtype == 1)) return 0;
-    if (nt == 3) return 4 * wgs >= 3 * slots ? nt : 0;
-    if (10 * wgs < 9 * slots) return 0;
-    if (nt == 1) return (N > 48 || pb.k > 4) && !(sides == kSpreadIn && pb.dtype == 0) ? nt : 0;
-    return slots > kCUs && 5 * N >= 4 * 128 * cols ? nt : 0;
+    const bool full = 10 * wgs >= 9 * slots, rounds = slots > kCUs;
+    if (nt == 3) {
+        if (4 * wgs < 3 * slots) return kNever;
+        if (sides != kPlain) return kAlone;
+        if (cols > 1 || rounds) return kNever;
+        return bf16 && wide && K >= 40 && 5 * wgs >= 4 * slots ? kAlone : kBeside;
+    }
+    if (!full) return kNever;
+    if (nt == 1) {
+        if ((N <= 48 && pb.k <= 4) || (!bf16 && sides != kSpreadOut)) return kNever;
+        return sides != kPlain && (rounds || (sides == kSpreadIn && pb.k > 4)) ? kAlone : kBeside;
+    }
+    if (sides == kPlain || !rounds || 5 * N < 4 * 128 * cols) return kNever;
+    return bf16 && wide && sides == kSpreadOut && pb.k == 4 ? kBeside : kAlone;
 }
 // a weight (k blocks, N x K) as planes, bytes
 size_t plane_bytes(const Problem& pb, int N, int K)
@@ -1081,19 +1099,23 @@ struct Planes {  // of the weights of one call, in its workspace; those the call
     bf16_t* w[3] = {nullptr, nullptr, nullptr};
     PlaneJob job[3] = {};
     int n = 0;
+    int gain = 0;  // kAlone, or the sum of several kBeside: the launch pays
     size_t bytes = 0;
     // the next weight, element (g, n, k) at g*N*K + n*n_s + k*k_s
-    void add(const Problem& pb, const void* src, int N, int K, int n_s, int k_s, Sides sides)
+    void add(const Problem& pb, const void* src, int N, int K, int n_s, int k_s, Sides sides, bool wide)
     {
         const size_t b = plane_bytes(pb, N, K);
-        if (rows_tile(pb, N, sides) && b < (1u << 30)) {
+        const Gain one = b < (1u << 30) ? rows_gain(pb, N, K, sides, wide) : kNever;
+        if (one) {
             PlaneJob& j = job[n];
             j = PlaneJob{src, reinterpret_cast<bf16_t*>(bytes), N, K, n_s, k_s, (int)tiles(N, 32), (int)tiles(K, kStep), 0};
             j.blocks = (int)tiles((int64_t)pb.k * j.tiles_n * j.steps, 4);
             bytes += b;
         }
+        gain += one;
         ++n;
     }
+    Planes done() const { return gain >= kAlone ? *this : Planes{}; }
     // `at`: room for them, or null; cj (may be null): the first pass of the bias gradient with them
     int launch(const Problem& pb, void* at, const ColsumJob* cj, hipStream_t st)
     {
@@ -1175,7 +1197,7 @@ int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t 
     d.G = pb.k;
     d.k_chunk = K;
     if (planes) {
-        const int nt = rows_tile(pb, N, d.a.take == kElements ? kSpreadIn : o_n == 1 ? kPlain : kSpreadOut);
+        const int nt = rows_tile(N);
         d.tiles_n = (int)tiles(N, 64 * nt);
         const bool whole = N % 4 == 0 && ldo % 4 == 0;  // pieces of four elements begin at multiples of their size
         if (o_mid) d.o_turn = whole && N % (4 * d.G) == 0 && 64 * nt % (4 * d.G) == 0 ? kTurnMid : 64 * nt % d.G == 0 ? kTurnMidAny : kTurnDirect;
@@ -1275,17 +1297,17 @@ int fwd_t_typed(const Problem& pb, const void* x, const void* R, const void* L, 
 Planes fwd_planes(const Problem& pb, const void* R, const void* L)
 {
     Planes pl;
-    pl.add(pb, R, pb.q, pb.p, pb.p, 1, pb.perm_b() ? kPlain : kSpreadOut);
-    pl.add(pb, L, pb.s, pb.q, pb.q, 1, pb.perm_b() ? kSpreadIn : kSpreadOut);
-    return pl;
+    pl.add(pb, R, pb.q, pb.p, pb.p, 1, pb.perm_b() ? kPlain : kSpreadOut, pb.dtype == 0);
+    pl.add(pb, L, pb.s, pb.q, pb.q, 1, pb.perm_b() ? kSpreadIn : kSpreadOut, true);
+    return pl.done();
 }
 Planes fwd_t_planes(const Problem& pb, const void* R, const void* L, bool recompute)
 {
     Planes pl;
-    pl.add(pb, L, pb.q, pb.s, 1, pb.q, kSpreadIn);
-    pl.add(pb, R, pb.p, pb.q, 1, pb.p, kPlain);
-    if (recompute) pl.add(pb, R, pb.q, pb.p, pb.p, 1, pb.perm_b() ? kPlain : kSpreadOut);
-    return pl;
+    pl.add(pb, L, pb.q, pb.s, 1, pb.q, kSpreadIn, pb.dtype == 0);
+    pl.add(pb, R, pb.p, pb.q, 1, pb.p, kPlain, true);
+    if (recompute) pl.add(pb, R, pb.q, pb.p, pb.p, 1, pb.perm_b() ? kPlain : kSpreadOut, pb.dtype == 0);
+    return pl.done();
 }
 int run_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, const Planes& pl, void* y, void* dU, hipStream_t st)
 {

@@ -592,3 +592,23 @@ def test_workspace_of_a_longer_batch_serves_a_shorter_one(binding, p, q, s):
 def test_chunks_of_the_weight_gradients(binding, rows, k, p, q, s, chunks):
     need = binding.monarch_bwd_workspace_bytes(rows, k * p, k, q, s, 0)
     assert need >= 2 * rows * k * q * 4 + chunks * k * q * (p + s) * 4
+
+
+# Which calls on the shape-generic kernels ask for room to lay the weights out as planes, beside the vector between the factors: a launch,
+# which one contraction alone has to pay for where no other in the call shares it.
+@pytest.mark.parametrize("call, dtype, flags, rows, k, p, q, s, planes", [
+    ("fwd_t", "f32", 0, 32768, 4, 170, 64, 64, False),    # neither side interleaved, two rounds of workgroups: 59.8 us without, 67.7 with
+    ("fwd_t", "f32", 0, 12608, 4, 180, 56, 56, False),    # the same, one round, alone in the call: 29.7, 34.0
+    ("fwd_t", "f32", 0, 12608, 4, 192, 192, 192, True),   # beside one that gains
+    ("fwd_t", "bf16", 0, 14000, 4, 150, 112, 112, True),  # bf16 with fp32 rows, a nearly full round
+    ("fwd", "bf16", 2, 12608, 4, 140, 170, 16, False),    # ... with bf16 rows
+    ("fwd", "bf16", 0, 16384, 4, 40, 100, 64, False),     # one round of 64 columns, alone: 24.6, 31.4
+    ("fwd", "bf16", 0, 32768, 4, 49, 49, 64, True),       # two rounds
+    ("fwd", "f32", 0, 4096, 16, 56, 56, 64, True),        # one round, both contractions
+    ("fwd", "bf16", 0, 24000, 4, 200, 100, 240, False),   # second factor of four bf16 blocks in 128 columns, alone: 82.9, 94.3
+    ("fwd", "bf16", 0, 32768, 4, 120, 120, 120, True)])
+def test_weights_as_planes_where_the_launch_pays(binding, call, dtype, flags, rows, k, p, q, s, planes):
+    code = 0 if dtype == "f32" else 1
+    need = getattr(binding, "monarch_%s_workspace_bytes" % call)(rows, k * p, k, q, s, code, flags)
+    vector = (rows * k * q * 4 + 255) // 256 * 256
+    assert (need > vector) == planes
