@@ -180,25 +180,32 @@ def test_weight_gradients_of_a_batch_with_infinities(shape):
 # Batches whose contractions take the kernel with the weights laid out as planes (64 rows of four blocks; 64, 128 and 192 columns),
 # and the same call with room for the vector between the factors alone, which takes the weights as they are: the same bits.  Contractions
 # that end in the first and the second half of a chunk, pieces that start anywhere, blocks that leave whole pieces of four and not, block
-# counts of 4, 8, 12 and 16; rows that hold something not finite.
-@pytest.mark.parametrize("reading", (0, 1))
-@pytest.mark.parametrize("shape", [(12500, 4, 192, 192, 192, "f32"), (12500, 4, 50, 180, 179, "f32"), (15041, 4, 250, 256, 250, "f32"),
-                                   (16329, 8, 40, 33, 63, "f32"), (5400, 12, 32, 24, 20, "f32"), (12300, 4, 400, 192, 384, "f32"),
-                                   (16301, 4, 49, 49, 64, "bf16"), (32703, 4, 16, 64, 49, "bf16"), (4070, 16, 17, 31, 33, "bf16"),
-                                   (16300, 4, 130, 128, 120, "bf16"), (12500, 4, 70, 190, 190, "bf16")], ids=str)
-def test_weights_as_planes_give_the_same_bits(shape, reading):
+# counts of 4, 8, 12 and 16; rows that hold something not finite.  For each reading: does x M^T take planes, does x M?
+PLANES = [((12500, 4, 192, 192, 192, "f32"), (1, 1), (1, 1)), ((12500, 4, 50, 180, 179, "f32"), (1, 1), (1, 1)),
+          ((15041, 4, 250, 256, 250, "f32"), (1, 1), (1, 1)), ((16329, 8, 40, 33, 63, "f32"), (1, 0), None), ((5400, 12, 32, 24, 20, "f32"), (1, 0), None),
+          ((12300, 4, 400, 192, 384, "f32"), (1, 1), (1, 1)), ((16301, 4, 49, 49, 64, "bf16"), (1, 1), (1, 1)),
+          ((32703, 4, 16, 64, 49, "bf16"), (1, 1), (1, 1)), ((4070, 16, 17, 31, 33, "bf16"), (1, 1), (1, 1)),
+          ((16300, 4, 130, 128, 120, "bf16"), (0, 1), (0, 1)), ((12500, 4, 70, 190, 190, "bf16"), (1, 1), (1, 1)),
+          ((8165, 8, 150, 130, 140, "f32"), (1, 1), (1, 1))]
+
+
+@pytest.mark.parametrize("shape, reading, takes", [(c[0], r, c[1 + r]) for c in PLANES for r in (0, 1) if c[1 + r]], ids=str)
+def test_weights_as_planes_give_the_same_bits(shape, reading, takes):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     from paper_2204_00595_amd import binding as B
     rows, k, p, q, s, dtype = shape
     x, R, L, dy = (torch.randn(size, generator=torch.Generator("cuda").manual_seed(9400 + i), device="cuda") * std
                    for i, (size, std) in enumerate((((rows, k * p), 1.0), ((k, q, p), p ** -0.5), ((k, s, q), q ** -0.5), ((rows, k * s), 1.0))))
+    finite = x.clone(), dy.clone()
     x[3, 5], x[rows - 1, 2], dy[35, 1], dy[rows - 2, 0] = float("inf"), float("nan"), 3e38, float("-inf")
     if dtype == "bf16":
         x, R, L, dy = (t.to(torch.bfloat16) for t in (x, R, L, dy))
     flags, code = (B.MONARCH_FLAG_PERM_B if reading else 0), B.MONARCH_F32 if dtype == "f32" else B.MONARCH_BF16
+    dims = (rows, k * p, k, q, s, code, flags)
     vector = (rows * k * q * 4 + 255) // 256 * 256
-    assert reading or max(f(rows, k * p, k, q, s, code, flags) for f in (B.monarch_fwd_workspace_bytes, B.monarch_fwd_t_workspace_bytes)) > vector
+    room = B.monarch_fwd_workspace_bytes(*dims) - vector, B.monarch_fwd_t_workspace_bytes(*dims) - vector
+    assert tuple(int(r > 0) for r in room) == takes and any(takes)
     bare = torch.empty(vector, dtype=torch.uint8, device="cuda")
     for name, call, args in (("y", B.monarch_fwd_ws, (x, R, L)), ("xM", B.monarch_fwd_t, (dy, R, L))):
         a, b = call(*args, flags=flags), call(*args, workspace=bare, flags=flags)
@@ -212,6 +219,23 @@ def test_weights_as_planes_give_the_same_bits(shape, reading):
                            B.monarch_bwd_saved(dy, x, bare, R, L, flags=flags, want_dbias=True)):
         assert torch.equal(torch.nan_to_num(part), torch.nan_to_num(again))
     assert torch.equal(torch.nan_to_num(B.monarch_bwd(dy, x, R, L, flags=flags)[0]), torch.nan_to_num(B.monarch_fwd_t(dy, R, L, workspace=bare, flags=flags)))
+    # The whole backward in the least room: two vectors, one chunk of partial sums and the partial rows of the bias gradient.  bf16
+    # weights as planes take half of that chunk and always fit; fp32 ones take 6 bytes a weight against its 4, and more where blocks
+    # are filled up to whole tiles.  The weight gradients are then summed in one chunk, with a rounding for 16 rows and product of planes:
+    # for 12500 rows 800 of them, which add up to some sqrt(800) 2^-25 of the norm, 8e-7.
+    if not takes[1] or dtype != "f32" or room[1] <= k * q * (p + s) * 4:
+        return
+    x, dy = finite
+    n_out = k * s
+    tiles = -(-(n_out // 4 if n_out % 4 == 0 else n_out) // 64)
+    chunks = max(1, min(-(-rows // 16), max(1, 1024 // tiles)))
+    least = 2 * vector + (k * q * (p + s) * 4 + 255) // 256 * 256 + (chunks * n_out * 4 + 255) // 256 * 256
+    ws = torch.full((least + 4096,), 0xA5, dtype=torch.uint8, device="cuda")
+    short, full = B.monarch_bwd_bias(dy, x, R, L, workspace=ws[:least], flags=flags), B.monarch_bwd_bias(dy, x, R, L, flags=flags)
+    assert bool((ws[least:] == 0xA5).all())
+    assert torch.equal(short[0], full[0]) and torch.equal(short[3], full[3])
+    for a, b in zip(short[1:3], full[1:3]):
+        assert float(torch.linalg.norm((a - b).double()) / torch.linalg.norm(b.double())) <= 2e-6
 
 
 # Weight gradients of long batches in tiles of 128 x 128 and 192 x 192, at and below the edges of a tile, dy in single elements and U from
