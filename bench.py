@@ -262,6 +262,29 @@ def measure_layer(name: str, with_dense: bool = True, with_extras: bool = False,
         bwd_saved_ms = timed_runs(bwd_saved_only, calls // 2)[0]
         del svs
 
+    # the layer's calls where they keep a vector that the two above recompute (64 blocks of 64)
+    lib, dims = binding.lib(), (sh.B, sh.n_in, sh.k, sh.q, sh.s, code)
+    kneed = lib.monarch_kept_bytes(*dims, 0) if variants and not sneed else 0
+    fwd_keep_ms = bwd_kept_ms = None
+    if kneed:
+        kept = [torch.empty(kneed, dtype=torch.uint8, device=dev) for _ in range(nsets)]
+        stream = int(torch.cuda.current_stream().cuda_stream)
+
+        def fwd_keep_only(i):
+            xs, _, y, _ = sets[i % nsets]
+            v = kept[i % nsets]
+            assert lib.monarch_fwd_keep(xs.data_ptr(), Rd.data_ptr(), Ld.data_ptr(), None, y.data_ptr(), v.data_ptr(), kneed, *dims, stream, 0) == 0
+
+        def bwd_kept_only(i):
+            xs, dys, _, dx = sets[i % nsets]
+            v = kept[i % nsets]
+            assert lib.monarch_bwd_kept(dys.data_ptr(), xs.data_ptr(), v.data_ptr(), kneed, Rd.data_ptr(), Ld.data_ptr(), dx.data_ptr(), dR.data_ptr(),
+                                        dL.data_ptr(), None, *dims, stream, ws.data_ptr(), ws.numel(), 0) == 0
+
+        fwd_keep_ms = timed_runs(fwd_keep_only, calls // 2)[0]
+        bwd_kept_ms = timed_runs(bwd_kept_only, calls // 2)[0]
+        del kept
+
     out = {
         "workload": name, "shape": "k=%d p=%d q=%d s=%d (%d->%d), B=%d, %s" % (sh.k, sh.p, sh.q, sh.s, sh.n_in, sh.n_out, sh.B, sh.dtype),
         "timed_calls": ncalls, "statistic": "median / min over %d runs of %d consecutive calls (time per call of a run)" % (RUNS, ncalls // RUNS),
@@ -274,6 +297,8 @@ def measure_layer(name: str, with_dense: bool = True, with_extras: bool = False,
         "fwd_ws_kernel": binding.monarch_kernel_name(2, sh.n_in, sh.k, sh.q, sh.s, code),
         # monarch_fwd_save / monarch_bwd_saved (the intermediate goes through HBM once instead of being recomputed)
         "fwd_save_us": fwd_save_ms and fwd_save_ms * 1e3, "bwd_saved_us": bwd_saved_ms and bwd_saved_ms * 1e3,
+        # monarch_fwd_keep / monarch_bwd_kept, as a layer in training calls them, where those above keep nothing
+        "fwd_keep_us": fwd_keep_ms and fwd_keep_ms * 1e3, "bwd_kept_us": bwd_kept_ms and bwd_kept_ms * 1e3,
         "fwd_tflops": sh.fwd_flops() / (fwd_med * 1e-3) / 1e12, "bwd_tflops": sh.bwd_flops() / (bwd_med * 1e-3) / 1e12,
         "fwd_gbs": sh.fwd_bytes() / (fwd_med * 1e-3) / 1e9, "bwd_gbs": sh.bwd_bytes() / (bwd_med * 1e-3) / 1e9,
         "fwd_algorithmic_bytes": sh.fwd_bytes(), "bwd_algorithmic_bytes": sh.bwd_bytes(),
