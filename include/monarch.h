@@ -98,7 +98,7 @@ int monarch_fwd_ex(const void* x, const void* R, const void* L, void* y,
  * the kernel; for k = 4 and up to a few thousand rows it runs as one launch per factor instead, if the workspace also holds the vector
  * between them (in slices of the batch for which both fit MONARCH_STATIC_WORKSPACE_BYTES).  The other bf16 shapes with k = 4 and blocks that are multiples of 32 (p: of 16; q up to 256, p up to 1024) have
  * that form for up to 8192 rows that go in a few slices at most; they pack in every call, the packed flag means nothing to them, and without a workspace, or with
- * a short one, the call runs as monarch_fwd_ex.  fp32 layers with square blocks p = q = s of 32 or 64 (any k) run on the fp32 matrix cores, one
+ * a short one, the call runs as monarch_fwd_ex.  fp32 layers with square blocks p = q = s of 32 or 64 (any k) run on the matrix cores, one
  * launch per block-diagonal factor with the vector between the factors kept in `workspace` (the packed flag
  * means nothing to them and is ignored).  Shapes that only the shape-generic kernels serve (p, q and s of 16 or more) run
  * on the matrix cores too, with the vector between the factors in `workspace`; for them the workspace is optional, and

@@ -8,11 +8,11 @@
 //
 // fp32 throughout.  exp(-2u) is one v_exp_f32 (base 2, log2(e) folded into the polynomial).  From |v| = 16 on it is
 // infinite or zero whatever the polynomial overflows to, so that s is exactly 0 or 1; in the gradient v is held to
-// [-16, 16] (one v_med3_f32), or s (1 - s) = 0 would meet an infinite d(2u)/dv.  s (1 - s) stays two operations: as
-// s - s s in one the last bit moves, and with it bf16 roundings of everything behind the gradient (1.7e-4 of the norm of
-// a feed-forward block's).  In the epilogues that apply these, the vector units are what bounds them: in a loop of
-// nothing else a value of gelu takes 39 clocks of a wave (47 with v clamped by maximum and minimum), of the gradient 59
-// (63).
+// [-16, 16] (one v_med3_f32), or s (1 - s) = 0 would meet an infinite d(2u)/dv.  s (1 - s) stays two operations: as s
+// - s s in one the last bit moves, and with it bf16 roundings of everything behind the gradient (1.7e-4 of the norm
+// of a feed-forward block's).  In the epilogues that apply these, the vector units are what bounds them: in a loop of
+// nothing else a value of gelu takes 39 clocks of a wave (47 with v clamped by maximum and minimum), of the gradient
+// 59 (63).
 #pragma once
 #include <hip/hip_runtime.h>
 

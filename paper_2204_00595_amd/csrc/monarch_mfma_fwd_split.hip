@@ -308,8 +308,8 @@ int launch_factor(const Problem& pb, int stage, const SplitArgs& a, hipStream_t 
     return tiles <= 512 ? launch_steps<1, 1, 4>(pb, stage, a, st) : launch_steps<1, 2, 2>(pb, stage, a, st);
 }
 
-// split_once_kernel has waves for two 32-row tiles of R in a quarter c q/4 .. (c + 1) q/4.  Of the multiples of 32 up to
-// 256 only q = 224 has quarters that touch three (56 .. 111 and 112 .. 167).
+// split_once_kernel has waves for two 32-row tiles of R in a quarter c q/4 .. (c + 1) q/4.  Of the multiples of 32 up
+// to 256 only q = 224 has quarters that touch three (56 .. 111 and 112 .. 167).
 constexpr bool once_covers(int q)
 {
     for (int c = 0; c < 4; ++c)
@@ -355,8 +355,8 @@ int launch_once_any(const Problem& pb, const SplitArgs& a, hipStream_t st)
 }
 
 // Rows whose vector between the factors fits the static workspace behind the packed weights, so that monarch_fwd_static
-// runs the same kernels as monarch_fwd_ws: what a call asks room for, no less for a longer batch than for a shorter one.
-// A row takes q / 32 times 256 bytes.
+// runs the same kernels as monarch_fwd_ws: what a call asks room for, no less for a longer batch than for a shorter
+// one. A row takes q / 32 times 256 bytes.
 int64_t fit_rows(const Problem& pb)
 {
     const size_t packed = fwd_frag_packed(pb), row = (size_t)pb.kq() * 2, room = MONARCH_STATIC_WORKSPACE_BYTES;
@@ -375,14 +375,15 @@ Slices slices(const Problem& pb)
     const int64_t n = (pb.B + most - 1) / most;
     return Slices{n, ((pb.B + n - 1) / n + 31) / 32 * 32};
 }
-// Where they pay: every slice reads the weights again, in launches of its own, while the shape-generic kernels, which run
-// otherwise, take the same time for any batch until their output is long.  Up to seven slices and 80 Mi output values;
-// shape-generic kernels and slices, us: blocks of 256 x 256 and 256 x 512, 3360 rows (two slices) 64 and 26, 8192 rows
-// (three) 66 and 49; 1024 x 256 and 256 x 2048, 4096 rows (four) 236 and 105; 256 x 256 and 256 x 3072, 3840 rows (five)
-// 214 and 140, 4608 rows (six) 213 and 166, 6144 rows (eight) 214 and 219 to 235, 8192 rows (eleven) 214 and 311; 1024 x
-// 256 and 256 x 2880, 768 rows (four of 192) 286 and 68, 8192 rows (43) 287 and 675; longer outputs, 256 x 192 and 192 x
-// 4096, 5120 rows (five, 80 Mi) 211 and 190, 6528 rows (six) 211 and 258; 128 x 128 and 128 x 4096, 5120 rows (two, 80 Mi)
-// 141 and 114, 7936 rows (two) 161 and 175.  The shapes with a fused kernel never have more than two.
+// Where they pay: every slice reads the weights again, in launches of its own, while the shape-generic kernels, which
+// run otherwise, take the same time for any batch until their output is long.  Up to seven slices and 80 Mi output
+// values; shape-generic kernels and slices, us: blocks of 256 x 256 and 256 x 512, 3360 rows (two slices) 64 and 26,
+// 8192 rows (three) 66 and 49; 1024 x 256 and 256 x 2048, 4096 rows (four) 236 and 105; 256 x 256 and 256 x 3072, 3840
+// rows (five) 214 and 140, 4608 rows (six) 213 and 166, 6144 rows (eight) 214 and 219 to 235, 8192 rows (eleven) 214
+// and 311; 1024 x 256 and 256 x 2880, 768 rows (four of 192) 286 and 68, 8192 rows (43) 287 and 675; longer outputs,
+// 256 x 192 and 192 x 4096, 5120 rows (five, 80 Mi) 211 and 190, 6528 rows (six) 211 and 258; 128 x 128 and 128 x 4096,
+// 5120 rows (two, 80 Mi) 141 and 114, 7936 rows (two) 161 and 175.  The shapes with a fused kernel never have more than
+// two.
 bool slices_pay(const Problem& pb)
 {
     const int64_t n = slices(pb).n;

@@ -31,12 +31,13 @@
 // barrier and multiply, and what hides it is the number of workgroups on a CU.  So a chunk is 16 contraction indices,
 // one MFMA deep: 64 x 64 tiles then take 30 KB of LDS, five to a CU, where chunks of 32 leave two (4096 -> 1024 fp32,
 // 8000 rows, whole step: 660 us on the fp32 matrix cores, 674 in planes with chunks of 32, 455 with 16); few workgroups
-// take chunks of 32 (launch_chunks).  Small and odd bf16 layers are bound by the memory system.  The intermediate
-// goes through memory (for most shapes it stays in the last-level cache): a fused kernel would hold all k blocks of a
-// row tile, which leaves the large shapes one 16-row tile per CU. Measured, training step: 768 -> 768 fp32, k = 4,
-// 12608 rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix cores, now 256 (one contraction of 3.7 GFLOP takes
-// 35 to 40 us, 50 where an operand is strided, the two weight gradients 74); 196 -> 256 bf16, blocks of 49 and 64,
-// 32768 rows: 458, 121, now 96 us; 2048 -> 512 fp32, 3000 rows: 137, now 112.
+// take chunks of 32 (launch_chunks).  Small and odd bf16 layers are bound by the memory system.  The intermediate goes
+// through memory (for most shapes it stays in the last-level cache): a fused kernel would hold all k blocks of a row
+// tile, which leaves the large shapes one 16-row tile per CU. Measured, training step: 768 -> 768 fp32, k = 4, 12608
+// rows: 4369 us on the SIMT kernels, 297 on the fp32 matrix cores, 256 in planes, with the weights laid out as planes
+// and large tiles for their gradients 210 to 217 (one contraction of 3.7 GFLOP takes 34 us, 38 where its rows come
+// interleaved, the two weight gradients 55); 196 -> 256 bf16, blocks of 49 and 64, 32768 rows: 458, 121, 96, now 86 to
+// 93 us; 2048 -> 512 fp32, 3000 rows: 137, in planes 112.
 #include <algorithm>
 #include <type_traits>
 #include "monarch_internal.h"
@@ -1054,20 +1055,21 @@ int pick_tile(int64_t M, int N, int G, bool pieces)
 enum Sides { kPlain, kSpreadOut, kSpreadIn };
 // Columns per wave (NT tiles of 32) of the kernel with the weights laid out as planes.
 int rows_tile(int N) { return N <= 64 ? 1 : tiles(N, 192) * 192 <= tiles(N, 128) * 128 ? 3 : 2; }
-// Where that kernel gains.  It reads and writes an interleaved side in whole lines and splits a row once instead of once per
-// 64 columns; its workgroups run one to a CU, so that it loses where the last round of them is far from full, and the
-// weights are a launch of 3 to 5 us before it.  us, contractions of 64-column tiles first: 768 -> 768 fp32 x M^T 12608 rows
-// 80 and 67, 8192 rows (half a round) 47 and 58; x M 83 and 73; 768 -> 3072 12608 rows 166 and 155, x M 182 and 140; 1024
-// -> 1024 fp32 x M^T 16384 rows (two rounds of 128 columns) 133 and 126, 8192 rows and 1024 -> 4096 at 2048 (one round) 70
-// and 67, 50 and 55; with 96 of 128 columns: 384 -> 384 16384 rows 36 and 45; 40 x 33 blocks, k = 8, bf16, 16384 rows 29
-// and 20, x M 35 and 25; in fp32 x M 22 and 26 at 8192 rows.
+// Where that kernel gains.  It reads and writes an interleaved side in whole lines and splits a row once instead of
+// once per 64 columns; its workgroups run one to a CU, so that it loses where the last round of them is far from full,
+// and the weights are a launch of 3 to 5 us before it.  us, contractions of 64-column tiles first: 768 -> 768 fp32 x
+// M^T 12608 rows 80 and 67, 8192 rows (half a round) 47 and 58; x M 83 and 73; 768 -> 3072 12608 rows 166 and 155, x M
+// 182 and 140; 1024 -> 1024 fp32 x M^T 16384 rows (two rounds of 128 columns) 133 and 126, 8192 rows and 1024 -> 4096
+// at 2048 (one round) 70 and 67, 50 and 55; with 96 of 128 columns: 384 -> 384 16384 rows 36 and 45; 40 x 33 blocks, k
+// = 8, bf16, 16384 rows 29 and 20, x M 35 and 25; in fp32 x M 22 and 26 at 8192 rows.
 // kBeside: where it gains less than the launch costs, another contraction of the call has to share it, which takes no
-// more time for it.  Those are the ones with neither side interleaved (fp32, four blocks, 12608 rows: 132 x 16, alone in
-// the call, 18 and 23; 16384 rows, 160 x 72 41 and 47; beside another, 12608 rows, 170 x 180 82 and 76; two rounds of
-// them no better than 64-column tiles there either; bf16 with fp32 rows gains alone where the round is nearly full,
-// 14000 rows, 150 x 120 40 and 35), one round of 64 columns (bf16, four blocks of 49 x 49, 16384 rows 22 and 27, of 60 x
-// 80 21 and 28; both contractions of sixteen of 56 x 56, 4096 rows, 37 and 22), and the second factor of bf16 layers with
-// four blocks in 128 columns (240 x 200, 24000 rows 83 and 94; beside another, 128 x 128, 32768 rows 55 and 54).
+// more time for it.  Those are the ones with neither side interleaved (fp32, four blocks, 12608 rows: 132 x 16, alone
+// in the call, 18 and 23; 16384 rows, 160 x 72 41 and 47; beside another, 12608 rows, 170 x 180 82 and 76; two rounds
+// of them no better than 64-column tiles there either, more than one column tile worse, 3072 -> 768 x M 146 and 163;
+// bf16 with fp32 rows gains alone where the round is nearly full, 14000 rows, 150 x 120 40 and 35), one round of 64
+// columns (bf16, four blocks of 49 x 49, 16384 rows 22 and 27, of 60 x 80 21 and 28; both contractions of sixteen of 56
+// x 56, 4096 rows, 37 and 22), and the second factor of bf16 layers with four blocks in 128 columns (240 x 200, 24000
+// rows 83 and 94; beside another, 128 x 128, 32768 rows 55 and 54).
 enum Gain { kNever, kBeside, kAlone };
 Gain rows_gain(const Problem& pb, int N, int K, Sides sides, bool wide)  // wide: the rows are fp32
 {
@@ -1213,18 +1215,18 @@ int data_op(const Problem& pb, const void* a, int64_t a_g, int64_t a_k, int64_t 
     return launch_op<TA, TW, TO>(w_rc, cfg, d, st);
 }
 
-// Tiles and batch chunks of the weight-gradient contractions.  64 x 64, about four workgroups per CU over both contractions
-// (768 -> 768 fp32: 131 us with two, 104 with four; 128 x 64 gained nothing anywhere: 96 x 384 blocks, 4096 rows, backward
-// 64 us and 73).  Larger tiles, 128 x 128 two to a CU and 192 x 192 (twelve waves) one to a CU, where they cover no more
-// than the small ones and their chunks still have 256 rows: every value is split half or a third as often (768 -> 768 fp32,
-// 12608 rows, both contractions 77 us in 64 x 64 tiles, 53 in 192 x 192, of which the matrix cores alone take 30; backward
-// 176 and 152, at 1024 rows 41 and 48; 1024 -> 4096 in 128 x 128 tiles, 12608 rows 617 and 564, 4096 rows 212 and 201; 128
-// x 512 blocks, 4096 rows 83 and 94).  At least 128 rows each, and whole sets of eight, since a chunk
-// belongs to an XCD (4096 -> 1024 fp32 with three chunks: three XCDs busy, 1088 us; with eight 465 us).  In steps of 32
-// rows: in steps of 64 the chunks were up to a fifth longer than an even share, and the launch waits for the longest
-// (backward of 12 fp32 blocks of 48 x 48 and 48 x 192, 3231 rows 105 us and 85, of 12 of 80 x 80 and 80 x 150 133 and 119;
-// two of 64 shapes lost 3 and 5 %).  One set of eight small tiles stays in steps of 64: 32 gain 1 to 3 % there, and a
-// batch would ask for as much room as a slightly longer one.
+// Tiles and batch chunks of the weight-gradient contractions.  64 x 64, about four workgroups per CU over both
+// contractions (768 -> 768 fp32: 131 us with two, 104 with four; 128 x 64 gained nothing anywhere: 96 x 384 blocks,
+// 4096 rows, backward 64 us and 73).  Larger tiles, 128 x 128 two to a CU and 192 x 192 (twelve waves) one to a CU,
+// where they cover no more than the small ones and their chunks still have 256 rows: every value is split half or a
+// third as often (768 -> 768 fp32, 12608 rows, both contractions 77 us in 64 x 64 tiles, 53 in 192 x 192, of which the
+// matrix cores alone take 30; backward 176 and 152, at 1024 rows 41 and 48; 1024 -> 4096 in 128 x 128 tiles, 12608 rows
+// 617 and 564, 4096 rows 212 and 201; 128 x 512 blocks, 4096 rows 83 and 94).  At least 128 rows each, and whole sets
+// of eight, since a chunk belongs to an XCD (4096 -> 1024 fp32 with three chunks: three XCDs busy, 1088 us; with eight
+// 465 us).  In steps of 32 rows: in steps of 64 the chunks were up to a fifth longer than an even share, and the launch
+// waits for the longest (backward of 12 fp32 blocks of 48 x 48 and 48 x 192, 3231 rows 105 us and 85, of 12 of 80 x 80
+// and 80 x 150 133 and 119; two of 64 shapes lost 3 and 5 %).  One set of eight small tiles stays in steps of 64: 32
+// gain 1 to 3 % there, and a batch would ask for as much room as a slightly longer one.
 struct WgradPlan {
     int cfg;
     int nz;

@@ -15,8 +15,9 @@
 // From 17 rows on the products are those of three bf16 planes of the entries (six v_mfma_f32_16x16x32_bf16 for the
 // eight contraction indices of two tiles that a lane holds, 96 clocks for the 256 of v_mfma_f32_16x16x4_f32), which
 // costs 5.5 vector instructions an entry and leaves less rounding: products off float64 by 2.0e-7 of them for 4.7e-7
-// (root mean square over eight matrices, m = 32), 3.2e-7 for 5.6e-7 (m = 64).  m = 24: 10.3 us -> 8.7, 32: 11.6 -> 9.7,
-// 40: 35.5 -> 26.7, 48: 48.0 -> 35.5, 64: 139 -> 88.
+// (root mean square over eight matrices, m = 32), 3.2e-7 for 5.6e-7 (m = 64).  Calls in a row, on the fp32 matrix cores
+// and in planes, us: m = 24 10.3 to 11.3 and 8.9 to 9.3, 32 10.8 to 11.6 and 9.0 to 10.6, 40 35 and 27, 48 47 and 34,
+// 64 135 and 84 (a profiler, which separates the launches, has 10.7 to 11.9 for m = 32).
 // What bounds it: from 33 rows on the vector units and the matrix cores, by about the same (m = 64: 1900 clocks of
 // products and 2000 of splitting, scaling and summing up for a squaring, two waves per SIMD), below the chain of
 // squarings.  Sums over the lanes stay in the vector registers and run beside the products (m = 32, 1024 slices: 15.8
