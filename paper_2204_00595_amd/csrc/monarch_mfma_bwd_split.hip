@@ -303,15 +303,20 @@ Plan make_plan(const Problem& pb, size_t room = SIZE_MAX)
 // block of width 1024, 2000 rows 164 and 173, 2500 rows 190 and 183; of 768, 2000 rows 134 and 135, 2500 rows 147 and
 // 144; of 512, 2000 rows 100 and 105, 2500 rows 116 and 108.  Not for blocks of 64 alone (8 rows 19 and 18, 1000 rows
 // 22 and 21).
-// Where the other choice is the shape-generic bf16 kernel (width 384): up to 4096 rows for square layers (6000 rows 61
-// and 65, 8000 rows 70 and 69), 16384 for others (96 x 384 blocks, 6000 rows 69 and 76, 12000 rows 90 and 117; 384 x 96
-// 75 and 78, 112 and 124; 96 x 288 67 and 69, 88 and 100).  Not where it is the shape-generic contractions (q = 256
-// with p or s = 1024), which hold the vectors between the factors in fp32.
+// Where the other choice is the shape-generic bf16 kernel: up to 4096 rows for square layers (width 384, 6000 rows 61 and
+// 65, 8000 rows 70 and 69).  For others as far as p + s goes, which that kernel's data path grows with while here every
+// row tile costs its launches of workgroups: 16384 rows from p + s = 384 on (96 x 384 blocks, 6000 rows 69 and 76, 12000
+// rows 90 and 117; 384 x 96 75 and 78, 112 and 124; 96 x 288 67 and 69, 88 and 100; the worst of 103 shapes, blocks of 320
+// x 32 and 32 x 96, 8000 rows 41 and 36), 6144 from 128 on with q up to 128 (backward of 96 x 96 and 96 x 192, 6000 rows 43
+// and 48, 14000 rows 64 and 54; of 160 x 96 and 96 x 32 40 and 40, 57 and 43), else 4096 (64 x 160 and 160 x 32, 6000 rows
+// 43 and 41, 16384 rows 70 and 46).  Not where it is the shape-generic contractions (q = 256 with p or s = 1024), which
+// hold the vectors between the factors in fp32.
 bool bwd_split_preferred(const Problem& pb)
 {
     const bool wide = bwd_wide_supported(pb);
     if ((!wide && !tiled_bwd_supported(pb)) || (wide && pb.p == 64 && pb.s == 64)) return false;
-    const int64_t most = !wide ? (pb.p == pb.s ? 4096 : 16384)
+    const int both = pb.p + pb.s;
+    const int64_t most = !wide ? (pb.p == pb.s ? 4096 : both >= 384 ? 16384 : both >= 128 && pb.q <= 128 ? 6144 : 4096)
                        : pb.p == pb.s ? 1536 : !pb.act_split ? 1800 : pb.s < pb.p ? 2200 : 2560;
     return pb.dtype == 1 && pb.k == 4 && !pb.perm_b() && pb.p % 32 == 0 && pb.q % 32 == 0 && pb.s % 32 == 0 && pb.p <= 1024 &&
            pb.s <= 1024 && pb.q <= 256 && pb.B > 0 && pb.B <= most && make_plan(pb).ok;

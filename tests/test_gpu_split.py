@@ -114,7 +114,8 @@ def test_short_batch_backward(case):
 # and in that of a slightly longer batch.
 LIMITS = [(1536, 192, 192, 192), (1537, 128, 128, 128), (1800, 256, 256, 1024), (1801, 256, 256, 768), (1805, 192, 192, 576), (16384, 32, 32, 64),
           (16385, 64, 32, 32), (2200, 768, 192, 192), (2201, 512, 128, 128), (2203, 1024, 256, 256), (2560, 128, 64, 64), (2561, 64, 64, 128),
-          (4096, 192, 192, 768), (4097, 192, 192, 192), (47, 64, 64, 64), (33, 64, 64, 64), (3009, 256, 256, 256)]
+          (4096, 192, 192, 768), (4097, 192, 192, 192), (47, 64, 64, 64), (33, 64, 64, 64), (3009, 256, 256, 256),
+          (4096, 64, 160, 32), (4097, 32, 160, 64), (6144, 96, 96, 192), (6145, 160, 96, 32), (16384, 96, 96, 288), (16385, 288, 96, 96)]
 
 
 @pytest.mark.parametrize("case", LIMITS, ids=str)

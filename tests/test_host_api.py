@@ -612,3 +612,12 @@ def test_weights_as_planes_where_the_launch_pays(binding, call, dtype, flags, ro
     need = getattr(binding, "monarch_%s_workspace_bytes" % call)(rows, k * p, k, q, s, code, flags)
     vector = (rows * k * q * 4 + 255) // 256 * 256
     assert (need > vector) == planes
+
+
+# The last batch of the backward's short-batch kernels where the other choice is the shape-generic bf16 kernel, which takes over at once:
+# its workspace is another one.  Narrow layers (p + s) end sooner.
+@pytest.mark.parametrize("p, q, s, last", [(96, 96, 384, 16384), (288, 96, 96, 16384), (96, 96, 192, 6144), (160, 96, 32, 6144), (64, 160, 32, 4096),
+                                           (64, 32, 32, 4096), (96, 96, 96, 4096)])
+def test_backward_of_short_batches_ends(binding, p, q, s, last):
+    need = [binding.monarch_bwd_workspace_bytes(rows, 4 * p, 4, q, s, 1) for rows in (last, last + 1)]
+    assert abs(need[1] - need[0]) > 500_000   # of one kernel, a row more, and with it a chunk of the batch more: 450 KB at most
