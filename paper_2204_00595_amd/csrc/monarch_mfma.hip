@@ -90,8 +90,9 @@ int mfma_fwd_t(const Problem& pb, const void* x, const void* R, const void* L, v
 bool mfma_fwd_fuses_bias(const Problem& pb, bool with_ws)
 {
     if (with_ws && (fwd_packed(pb) || real32_mfma_supported(pb))) return true;
-    // all of mfma_fwd's kernels have a bias epilogue
-    return fwd_wide_supported(pb) || sq64_supported(pb) || sq16_supported(pb) || tiled_fwd_supported(pb);
+    if (sq64_supported(pb)) return with_ws;
+    // the others of mfma_fwd's kernels have a bias epilogue
+    return fwd_wide_supported(pb) || sq16_supported(pb) || tiled_fwd_supported(pb);
 }
 
 bool mfma_bwd_fuses_dbias(const Problem& pb) { return bwd_split_preferred(pb) || bwd_wide_supported(pb) || bwd_sq64_supported(pb); }

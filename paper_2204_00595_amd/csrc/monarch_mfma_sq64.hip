@@ -211,10 +211,10 @@ __device__ __forceinline__ void column_stage_inplace(const Lane& t_, const uint1
 // 128 lines, eight per instruction (1 KiB contiguous).  Line (b, jl) goes to
 // dst[(b0 + b) * 4096 + (col0 + jl) * 64 ..].  SWZ: tile rows are 4096 bytes and the 16-byte piece
 // index is XOR-ed with b % 8; otherwise rows are SQ_ROWB bytes, pieces in order.
-// bias (may be null): added to the bf16 results, 64 values a line.
-template <bool SWZ, bool NT = SWZ>
+// BIAS: `add`, 64 values a line (line_bias), is added to the bf16 results.
+template <bool SWZ, bool NT = SWZ, bool BIAS = false>
 __device__ __forceinline__ void copy_out(const Lane& t_, const unsigned char* ldsb, uint16_t* __restrict__ dst,
-                                         int64_t b0, int64_t B, int col0, const uint16_t* __restrict__ bias = nullptr)
+                                         int64_t b0, int64_t B, int col0, const u32x4* add = nullptr)
 {
 #pragma unroll
     for (int k2 = 0; k2 < 16; ++k2) {
@@ -223,12 +223,11 @@ __device__ __forceinline__ void copy_out(const Lane& t_, const unsigned char* ld
         const unsigned char* src = SWZ ? ldsb + (size_t)b * 4096 + jl * 128 + ((pc ^ (b & 7)) * 16)
                                        : ldsb + (size_t)b * SQ_ROWB + jl * 128 + pc * 16;
         u32x4 v = *reinterpret_cast<const u32x4*>(src);
-        if (bias) {
-            const u32x4 a = ldg128(bias + (size_t)(col0 + jl) * M64 + 8 * pc);
+        if constexpr (BIAS) {
 #pragma unroll
             for (int w = 0; w < 4; ++w)
-                v[w] = pack_bf16x2(__uint_as_float(v[w] << 16) + __uint_as_float(a[w] << 16),
-                                   __uint_as_float(v[w] & 0xffff0000u) + __uint_as_float(a[w] & 0xffff0000u));
+                v[w] = pack_bf16x2(__uint_as_float(v[w] << 16) + __uint_as_float(add[k2 & 3][w] << 16),
+                                   __uint_as_float(v[w] & 0xffff0000u) + __uint_as_float(add[k2 & 3][w] & 0xffff0000u));
         }
         if (b0 + b < B) {
             uint16_t* p = dst + (b0 + b) * N64 + (size_t)(col0 + jl) * M64 + 8 * pc;
@@ -236,6 +235,12 @@ __device__ __forceinline__ void copy_out(const Lane& t_, const unsigned char* ld
             else *reinterpret_cast<u32x4*>(p) = v;
         }
     }
+}
+// what a lane of copy_out adds to its lines: 8 of them apart, the same for every row
+__device__ __forceinline__ void line_bias(const Lane& t_, const uint16_t* __restrict__ bias, int col0, u32x4 (&add)[4])
+{
+#pragma unroll
+    for (int n = 0; n < 4; ++n) add[n] = ldg128(bias + (size_t)(col0 + 8 * n + (t_.lane >> 3)) * M64 + 8 * (t_.lane & 7));
 }
 
 __device__ __forceinline__ Lane make_lane()
@@ -251,9 +256,10 @@ __device__ __forceinline__ Lane make_lane()
 
 // ------------------------------------------------------------------------ forward ----
 
-// U (may be null): the vector between the factors also goes there, in the exchange layout, which is the one the backward
-// reads.
-template <bool PACKED>
+// KEEP: the vector between the factors also goes to U, in the exchange layout, which is the one the backward reads.
+// BIAS and KEEP are variants of their own: with tests of the pointers instead the plain forward took 0.6 to 2.4 us
+// longer (packed, one row 16.6 us and 14.6, 16384 rows 68.2 and 66.3), and with a bias every line waited for its own.
+template <bool PACKED, bool BIAS, bool KEEP>
 __global__ void __launch_bounds__(512)
 fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R, const uint16_t* __restrict__ L,
                 const uint16_t* __restrict__ bias, uint16_t* __restrict__ y, uint16_t* __restrict__ U, int64_t B)
@@ -281,7 +287,7 @@ fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R, 
             exchange_write(t, ldsb, pk1);
         }
         __syncthreads();
-        if (U) copy_out<false>(t, ldsb, U, b0, B, 32 * h);
+        if constexpr (KEEP) copy_out<false>(t, ldsb, U, b0, B, 32 * h);
         f32x16 ev;
         column_stage<PACKED>(t, L, ldsb, h, [&](int cc, const f32x16& acc) {
             if ((cc & 1) == 0) {
@@ -298,6 +304,8 @@ fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R, 
     // adjacent lanes hit 8 different slots.
 #pragma unroll
     for (int rnd = 0; rnd < 2; ++rnd) {
+        u32x4 add[4];
+        if constexpr (BIAS) line_bias(t, bias, 32 * rnd, add);
         __syncthreads();  // the exchange buffer (or the previous round's tile) is dead
         if (lt == rnd) {
 #pragma unroll
@@ -311,7 +319,7 @@ fwd_sq64_kernel(const uint16_t* __restrict__ x, const uint16_t* __restrict__ R, 
                 }
         }
         __syncthreads();
-        copy_out<true>(t, ldsb, y, b0, B, 32 * rnd, bias);
+        copy_out<true, true, BIAS>(t, ldsb, y, b0, B, 32 * rnd, add);
     }
 }
 
@@ -696,13 +704,13 @@ bool sq64_supported(const Problem& pb)
 int fwd_sq64(const Problem& pb, const void* x, const void* R, const void* L, void* y, hipStream_t st)
 {
     if (!sq64_supported(pb)) return -2;
-    auto kern = fwd_sq64_kernel<false>;
+    auto kern = fwd_sq64_kernel<false, false, false>;
     if (allow_dynamic_lds((const void*)kern, SQ_LDS) != hipSuccess)
         return -4;
     const int64_t grid = (pb.B + SQ_BM - 1) / SQ_BM;
     if (grid > 0x7fffffffLL) return -2;
     hipLaunchKernelGGL(kern, dim3((unsigned)grid), dim3(512), SQ_LDS, st, (const uint16_t*)x, (const uint16_t*)R,
-                       (const uint16_t*)L, (const uint16_t*)pb.bias, (uint16_t*)y, (uint16_t*)nullptr, pb.B);
+                       (const uint16_t*)L, (const uint16_t*)nullptr, (uint16_t*)y, (uint16_t*)nullptr, pb.B);
     return hip_status(hipGetLastError());
 }
 
@@ -719,7 +727,8 @@ int fwd_sq64_ws(const Problem& pb, const void* x, const void* R, const void* L, 
         hipLaunchKernelGGL(pack64_kernel, dim3(2 * 128), dim3(256), 0, st, jr, jl);
         if (hipGetLastError() != hipSuccess) return -4;
     }
-    auto kern = fwd_sq64_kernel<true>;
+    auto kern = pb.saved ? (pb.bias ? fwd_sq64_kernel<true, true, true> : fwd_sq64_kernel<true, false, true>)
+                         : (pb.bias ? fwd_sq64_kernel<true, true, false> : fwd_sq64_kernel<true, false, false>);
     if (allow_dynamic_lds((const void*)kern, SQ_LDS) != hipSuccess)
         return -4;
     const int64_t grid = (pb.B + SQ_BM - 1) / SQ_BM;
@@ -729,11 +738,11 @@ int fwd_sq64_ws(const Problem& pb, const void* x, const void* R, const void* L, 
     return hip_status(hipGetLastError());
 }
 
-// ... that keeps the vector between the factors for the backward, which then neither reads x nor multiplies for it: a write
-// of U in place of a kernel that reads x and writes U.  kept = U, then the packed factors of this call.  Training step of
-// the layer, 16384 rows: 329 -> 287 us (forward 70 -> 90, without 54 + 5 in the backward), 4096 rows 106 -> 89; with a bias,
-// which took a pass over y and one over dy, 414 -> 290 and 137 -> 95.  The price is memory from the forward to the
-// backward, 8 KB a row (134 MB at 16384 rows), which the workspace of that backward then does not need
+// ... that keeps the vector between the factors for the backward, which then neither reads x nor multiplies for it: a
+// write of U in place of a kernel that reads x and writes U.  kept = U, then the packed factors of this call.  Training
+// step of the layer, 16384 rows: 329 -> 287 us (forward 70 -> 90, without 54 + 5 in the backward), 4096 rows 106 -> 89;
+// with a bias, which took a pass over y and one over dy, 414 -> 290 and 137 -> 90.  The price is memory from the
+// forward to the backward, 8 KB a row (134 MB at 16384 rows), which the workspace of that backward then does not need
 // (monarch_bwd_kept_workspace_bytes).
 size_t sq64_mid_bytes(const Problem& pb) { return align_up((size_t)(pb.B > 0 ? pb.B : 1) * N64 * 2, 256); }
 size_t sq64_kept_bytes(const Problem& pb) { return sq64_mid_bytes(pb) + fwd_sq64_workspace(pb); }
